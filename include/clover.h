@@ -291,13 +291,13 @@ const char *clover_last_global_error(void);
 /* ---- single operators, exported for unit tests and kernel benchmarks -------------------- */
 
 /* Y[M,N] (fp32, leading dimension ldy) = X[M,K] (fp32, ld = K) * W[N,K]^T, W in `dtype`.
- * path 0 = generic fp32-ALU kernel, 1 = MFMA weight-streaming kernels (bf16 only; W is first copied
- * into `scratch` in the library's fragment-major layout), 2 = as 1 but reusing the copy a previous
- * path-1 call with the same W and scratch left behind (times the GEMM alone); 3 = full-K panel
- * kernel (bf16, M <= 64, K % 256 == 0, N % 16 == 0, ldy % 4 == 0), 4 = as 3 reusing the copy;
- * 5 = the panel kernel over ranges of K (narrow N with long K, e.g. 4096 x 14336; CLOVER_E_SHAPE
- * where the launcher would not pick it) followed by the sum of the ranges, 6 = as 5 reusing the copy;
- * 7 = the tiled kernel for many rows (M <= 256, K % 64 == 0, N % 16 == 0) over ranges of K, then their sum.
+ * path 0 = generic fp32-ALU kernel, 1 = MFMA GEMM over ranges of K, then their sum (bf16 only; W is first
+ * copied into `scratch` in the library's fragment-major layout), 2 = as 1 but reusing the copy a previous
+ * path-1 call with the same W and scratch left behind (times the GEMM alone); 3 = over the whole K, results
+ * written directly (bf16, M <= 128, K % 256 == 0 up to 64 rows and K % 128 == 0 above, N % 16 == 0,
+ * ldy % 4 == 0), 4 = as 3 reusing the copy; 5 = as 1 for a narrow N with long K only (e.g. 4096 x 14336;
+ * CLOVER_E_SHAPE where the ranges would not fill the chip), 6 = as 5 reusing the copy;
+ * 7 = as 1 (M <= 256, K % 128 == 0, N % 16 == 0).
  * `scratch` dev, >= clover_op_gemm_scratch_bytes(M,N,K).  Stream as given. */
 size_t clover_op_gemm_scratch_bytes(int32_t M, int32_t N, int32_t K);
 int clover_op_gemm(int32_t path, int32_t dtype, const float *X, const void *W, float *Y, int32_t ldy,

@@ -35,7 +35,9 @@ int op_gemm_impl(int32_t path, int32_t dtype, const float* X, const void* W, flo
 
 // Scratch of clover_op_gemm_static: one copy per GPU, held until the process ends.  In host code the name below is
 // only a handle for hipGetSymbolAddress; every use goes through the per-device address looked up once.
-__device__ __align__(256) unsigned char g_static_scratch[CLOVER_STATIC_SCRATCH_BYTES];
+// (larger than the documented limit by the padding of the activation planes to whole row blocks)
+constexpr size_t kStaticScratch = (size_t)CLOVER_STATIC_SCRATCH_BYTES + (16u << 20);
+__device__ __align__(256) unsigned char g_static_scratch[kStaticScratch];
 constexpr int kMaxDevices = 64;
 void* g_static_scratch_ptr[kMaxDevices] = {};
 int static_scratch_ptr(void** out);
@@ -96,18 +98,13 @@ struct clover_ctx {
   float *ad_q, *ad_k, *ad_v, *d_xs, *d_e, *d_cat, *d_g, *d_s, *d_state, *d_rootx, *z;
   void* cand;
   int* topk_ids;
-  float* partial;          // split-K partial tiles / plain GEMM outputs of the MFMA path
+  float* partial;          // partial tiles of the MFMA GEMMs over K ranges
   size_t partial_bytes;
-  float* pl_y;             // planes of draft-side GEMM inputs that no fused producer writes
+  float* pl_y;             // planes of draft-side GEMM inputs
   char* packed;            // fragment-major copies of every linear weight (MFMA path)
   size_t packed_bytes;
   const void* lm_head_pk;
   bool fast;               // bf16 model on the MFMA path
-  bool panel;              // full-K panel GEMM for the gate+up projection and the LM head
-  int tile_min_kp = 65;    // narrow outputs over K ranges take the tiled GEMM's 128 x 256 form from this many rows on
-  int tile_min = 129;      // passes of at least this many rows (up to 256) take the tiled GEMM: one weight pass
-  int row_batch_max = 64;
-  int row_batch = 64;      // rows per weight pass for passes of more than 64 rows: 128 when the panel kernel may take them  // passes of up to this many rows run through the <= 64-row GEMM kernels, in batches of 64
   // dynamic (score-pruned) tree: candidates, frontiers and the per-sequence topology tables
   bool dyn_on = false;
   DynTree dyn{};
@@ -245,18 +242,21 @@ struct Carver {
   }
 };
 
-struct GemmShape { int N, K, mode; };
+struct GemmShape { int N, K; };
 
+// every GEMM of the MFMA path that writes partial tiles
 void model_gemm_shapes(const clover_config& c, std::vector<GemmShape>& v) {
   const int H = c.hidden, nqd = c.n_q_heads * c.head_dim, qkvn = (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim;
-  v = {{qkvn, H, 0}, {H, nqd, 1}, {c.ffn, H, 2}, {2 * c.ffn, H, 0}, {H, c.ffn, 1}, {c.vocab, H, 0}, {H, H, 0}, {H, 2 * H, 0}};
+  v = {{qkvn, H}, {H, nqd}, {H, c.ffn}, {H, H}, {H, 2 * H}};
 }
+bool mfma_shape_ok(int N, int K) { return N % 16 == 0 && K % 128 == 0; }
 
 void carve(clover_ctx* x, char* base, size_t* total) {
   const clover_config& c = x->cfg;
   Carver cv{base};
   const int B = c.max_batch, R = c.max_nodes, H = c.hidden, d = c.head_dim;
   const int rows = std::max(B * R, c.prefill_rows);   // row capacity of every activation buffer
+  const size_t rows16 = (size_t)(rows + 15) / 16 * 16;   // of those that hold planes in fragment order (whole row blocks)
   const size_t esz = c.dtype == CLOVER_DTYPE_F32 ? 4 : 2;
   x->R = R; x->max_rows = rows; x->H = H; x->esz = esz;
   x->kv_esz = 4;  // bytes per cached value in both formats
@@ -283,11 +283,11 @@ void carve(clover_ctx* x, char* base, size_t* total) {
   x->aug_kc = cv.take<char>(x->k_layer_elems * x->kv_esz * c.aug_layers);
   x->aug_vc = cv.take<char>(x->v_layer_elems * x->kv_esz * c.aug_layers);
   x->xd = cv.take<float>((size_t)rows * H);
-  x->a_norm = cv.take<float>((size_t)rows * 2 * H);
+  x->a_norm = cv.take<float>(rows16 * H);
   x->qkv = cv.take<float>((size_t)rows * x->QKVN);
   x->q_rot = cv.take<float>((size_t)rows * x->NQD);
-  x->attn_out = cv.take<float>((size_t)rows * x->NQD);
-  x->h_ffn = cv.take<float>((size_t)rows * c.ffn);
+  x->attn_out = cv.take<float>(rows16 * x->NQD);
+  x->h_ffn = cv.take<float>(rows16 * c.ffn);
   x->tmp_ffn = cv.take<float>((size_t)rows * c.ffn);
   x->cos_t = cv.take<float>((size_t)rows * d / 2);
   x->sin_t = cv.take<float>((size_t)rows * d / 2);
@@ -296,7 +296,7 @@ void carve(clover_ctx* x, char* base, size_t* total) {
   x->ad_v = cv.take<float>((size_t)rows * H);
   x->d_xs = cv.take<float>((size_t)rows * H);
   x->d_e = cv.take<float>((size_t)rows * H);
-  x->d_cat = cv.take<float>((size_t)rows * 2 * H);
+  x->d_cat = cv.take<float>(rows16 * 2 * H);
   x->d_g = cv.take<float>((size_t)rows * H);
   x->d_s = cv.take<float>((size_t)rows * H);
   x->d_state = cv.take<float>((size_t)rows * H);
@@ -327,41 +327,19 @@ void carve(clover_ctx* x, char* base, size_t* total) {
   if (fast) {
     std::vector<GemmShape> shapes;
     model_gemm_shapes(c, shapes);
-    for (const GemmShape& s : shapes) fast = fast && mfma_gemm_supported(1, s.N, s.K, s.mode);
+    for (const GemmShape& s : shapes) fast = fast && mfma_shape_ok(s.N, s.K);
+    fast = fast && mfma_shape_ok(c.ffn, H) && mfma_shape_ok(c.vocab, H);
     fast = fast && (c.n_kv_heads * d) % 16 == 0;
   }
   size_t packed_bytes = 0;
   if (fast) {
+    // partial tiles of the largest launch; the q and the k|v projections of an Attention Decoder lie side by side
     std::vector<GemmShape> shapes;
     model_gemm_shapes(c, shapes);
-    for (const GemmShape& s : shapes) {
-      if (s.mode == 2) continue;
-      if (stream_gemm_supported(std::min(rows, 64), s.N, s.K))
-        pbytes = std::max(pbytes, stream_gemm_out_bytes(std::min(rows, 64), s.N, s.K));
-      for (int M = 65; M <= std::min(rows, 256); ++M) {
-        const int sp = mfma_gemm_pick_splits(M, s.N, s.K, s.mode);
-        const size_t mtot = rows <= 256 ? (size_t)M : (size_t)rows;
-        pbytes = std::max(pbytes, (size_t)sp * mtot * s.N * sizeof(float));
-      }
-    }
-    // 129..256 rows through the tiled kernel over K ranges: partial tiles of the whole pass
-    if (rows > 64) {
-      std::vector<GemmShape> shp;
-      model_gemm_shapes(c, shp);
-      const int rb = std::min(rows, 256);
-      for (const GemmShape& g : shp)
-        if (g.mode != 2 && tile_gemm_supported(rb, g.N, g.K, 0))
-          pbytes = std::max(pbytes, (size_t)tile_gemm_pick_k_parts(rb, g.N, g.K) *
-                                        rb * g.N * sizeof(float));
-    }
-    // 65..256 rows in batches of 64 through the K-slice kernel: partial tiles of the whole pass
-    if (rows > 64 && !tune_int("CLOVER_NO_ROW_BATCH", 0)) {
-      std::vector<GemmShape> shp;
-      model_gemm_shapes(c, shp);
-      const int rb = std::min(rows, 256);
-      for (const GemmShape& g : shp)
-        if (g.mode != 2 && g.N != c.vocab && g.N != 2 * c.ffn && stream_gemm_supported(64, g.N, g.K))
-          pbytes = std::max(pbytes, stream_gemm_out_bytes(rb, g.N, g.K));
+    for (int M = 32; M < rows + 32; M += 32) {
+      auto bytes = [&](int N, int K) { return (size_t)tile_gemm_pick_k_parts(M, N, K) * std::min(M, rows) * N * sizeof(float); };
+      for (const GemmShape& s : shapes) pbytes = std::max(pbytes, bytes(s.N, s.K));
+      pbytes = std::max(pbytes, align256(bytes(H, H)) + bytes(2 * H, H));
     }
     const size_t layer_elems = (size_t)x->QKVN * H + (size_t)H * x->NQD + (size_t)3 * c.ffn * H;
     packed_bytes = 2 * ((size_t)(c.n_layers + c.aug_layers) * layer_elems + (size_t)c.vocab * H + (size_t)7 * H * H +
@@ -370,11 +348,6 @@ void carve(clover_ctx* x, char* base, size_t* total) {
   x->packed_bytes = packed_bytes;
   x->packed = cv.take<char>(packed_bytes ? packed_bytes : 256);
   x->fast = fast;
-  x->panel = fast && !tune_int("CLOVER_NO_PANEL", 0);
-  x->row_batch_max = (fast && !tune_int("CLOVER_NO_ROW_BATCH", 0)) ? 256 : 64;
-  x->row_batch = (x->panel && !tune_int("CLOVER_ROW_BATCH_64", 0)) ? 128 : 64;
-  x->tile_min = fast ? tune_int("CLOVER_TILE_MIN", 129) : 1 << 30;
-  x->tile_min_kp = fast ? tune_int("CLOVER_TILE_MIN_KP", 65) : 1 << 30;
   x->kvdtype = fast ? 1 : 0;
   x->kv_layer_stride = fast ? 2 * x->k_layer_elems : x->k_layer_elems;
   x->attn_fast = fast && attn_mfma_supported(d, c.n_q_heads, c.n_kv_heads, c.max_seq);
@@ -383,7 +356,7 @@ void carve(clover_ctx* x, char* base, size_t* total) {
   x->ml_part = cv.take<float>(x->attn_fast ? (size_t)x->attn_max_splits * rows * c.n_q_heads * 2 : 64);
   x->partial_bytes = pbytes;
   x->partial = (float*)cv.take<char>(pbytes);
-  x->pl_y = cv.take<float>((size_t)rows * 2 * H);
+  x->pl_y = cv.take<float>(rows16 * 2 * H);
   *total = cv.off;
 }
 
@@ -407,125 +380,29 @@ struct Scope {
 };
 
 // ---- GEMM dispatch ----------------------------------------------------------------------------
-struct Planes {
-  bf16_t *hi, *lo;
-  int ld;
-};
-// planes view of an fp32 activation buffer of capacity max_rows x K floats (same bytes)
-Planes planes_of(clover_ctx* x, float* buf, int K) {
-  bf16_t* hi = (bf16_t*)buf;
-  return Planes{hi, hi + (size_t)x->max_rows * K, K};
-}
-
-// MFMA path: out[s][M][N] = X * [W0; W1; W2]^T per split s.  Writes into `direct` (leading dimension
-// ld_direct, no split) when given, else into x->partial as [splits][M][N].  Returns the split count.
-int gemm_fast(clover_ctx* x, int cls, Planes X, int nseg, const void* const* W, const int* seg_n, int M, int N, int K,
-              float* direct, int ld_direct, float* part = nullptr /* where the K-slice partials go (stream path) */) {
+// MFMA path: part[r][M][N] = X W^T over K range r (default: x->partial).  Returns the number of ranges.
+int gemm_fast(clover_ctx* x, int cls, FragPlanes X, const void* W, int M, int N, int K, float* part = nullptr) {
   Scope sc(x, cls);
-  if (!part) part = x->partial;
-  int segb[4] = {0, 0x7fffffff, 0x7fffffff, 0x7fffffff};
-  const bf16_t* ws[3];
-  {
-    int off = 0;
-    for (int s = 0; s < 3; ++s) {
-      ws[s] = (const bf16_t*)(s < nseg ? W[s] : W[nseg - 1]);
-      if (s < nseg) { segb[s] = off; off += seg_n[s]; }
-    }
-  }
-  // Many rows (65..256: this route writes partials over K ranges, where the tiled kernel's 128-row form already beats
-  // the panel kernel's K-range form from 65 rows on): one pass over the weights for all rows.
-  if (!direct && M >= std::min(x->tile_min, x->tile_min_kp) && M <= 256 && tile_gemm_supported(M, N, K, 0)) {
-    bool adjacent = true;
-    for (int s = 1; s < nseg; ++s) adjacent = adjacent && ws[s] == ws[s - 1] + (size_t)seg_n[s - 1] * K;
-    const int kp = tile_gemm_pick_k_parts(M, N, K);
-    if (adjacent && (size_t)kp * M * N * sizeof(float) <= x->partial_bytes) {
-      TileGemm g;
-      memset(&g, 0, sizeof(g));
-      g.Xhi = X.hi; g.Xlo = X.lo; g.ldx = X.ld;
-      g.W[0] = g.W[1] = ws[0];
-      g.Y = part; g.ldy = N; g.k_parts = kp; g.split_stride = (size_t)M * N;
-      g.M = M; g.N = N; g.K = K; g.epi = 0;
-      launch_gemm_tile(g, x->st);
-      return kp;
-    }
-  }
-  // Long K into a narrow output (the down projection): K ranges of the panel kernel, a few partials instead of
-  // one per 512 columns.  Passes of more than 64 rows take this route for every GEMM it supports, in batches of
-  // 128 rows (one weight pass per batch), including the three-segment QKV when the packed copies are adjacent.
-  if (x->panel && !direct && M <= x->row_batch_max) {
-    const int bm = M > 64 ? x->row_batch : 64;
-    bool adjacent = true;
-    for (int s = 1; s < nseg; ++s) adjacent = adjacent && ws[s] == ws[s - 1] + (size_t)seg_n[s - 1] * K;
-    const int kp = (nseg == 1 || (bm > 64 && adjacent)) ? panel_gemm_pick_k_parts(std::min(M, bm), N, K) : 0;
-    if (kp > 1 && (size_t)kp * M * N * sizeof(float) <= x->partial_bytes) {
-      for (int m0 = 0; m0 < M; m0 += bm) {
-        PanelGemm g;
-        memset(&g, 0, sizeof(g));
-        g.Xhi = X.hi + (size_t)m0 * X.ld; g.Xlo = X.lo + (size_t)m0 * X.ld; g.ldx = X.ld;
-        g.W[0] = g.W[1] = ws[0];
-        g.Y = part + (size_t)m0 * N; g.ldy = N; g.k_parts = kp; g.split_stride = (size_t)M * N;
-        g.M = std::min(bm, M - m0); g.N = N; g.K = K; g.epi = 0;
-        g.rows128 = bm > 64;   // a short last batch keeps the form the ranges were picked for
-        launch_gemm_panel(g, x->st);
-      }
-      return kp;
-    }
-  }
-  // Up to 64 rows: the K-slice kernel.  65..256 rows: the same kernel over batches of 64 rows -- the weights are
-  // streamed once per batch, which still beats the tiled kernel (each of its wavefronts multiplies ALL rows and is
-  // bound by the LDS reads of the activations).
-  if (M <= x->row_batch_max && stream_gemm_supported(std::min(M, 64), N, K) &&
-      stream_gemm_out_bytes(M, N, K) <= x->partial_bytes) {
-    for (int m0 = 0; m0 < M; m0 += 64) {
-      StreamGemm g;
-      memset(&g, 0, sizeof(g));
-      g.Xhi = X.hi + (size_t)m0 * X.ld; g.Xlo = X.lo + (size_t)m0 * X.ld; g.ldx = X.ld;
-      for (int s = 0; s < 3; ++s) { g.W[s] = ws[s]; g.seg_begin[s] = segb[s]; }
-      g.seg_begin[3] = 0x7fffffff;
-      g.Y = part + (size_t)m0 * N; g.ldy = N; g.split_stride = (size_t)M * N;
-      g.M = std::min(64, M - m0); g.N = N; g.K = K;
-      g.tag = cls == KC_GEMM_GATEUP ? 1 : 0;
-      launch_gemm_stream(g, x->st);
-    }
-    const int sp = stream_gemm_slices(K);
-    if (direct) launch_reduce(part, sp, (size_t)M * N, N, nullptr, x->cfg.dtype, direct, ld_direct, M, N, 0, x->st);
-    return direct ? 1 : sp;
-  }
-  int splits = 1;
-  if (!direct) {
-    splits = mfma_gemm_pick_splits(std::min(M, 256), N, K, 0);
-    while (splits > 1 && (size_t)splits * M * N * sizeof(float) > x->partial_bytes) splits /= 2;
-  }
-  for (int m0 = 0; m0 < M; m0 += 256) {
-    const int mm = std::min(256, M - m0);
-    MfmaGemm g;
-    memset(&g, 0, sizeof(g));
-    g.Xhi = X.hi + (size_t)m0 * X.ld; g.Xlo = X.lo + (size_t)m0 * X.ld; g.ldx = X.ld;
-    for (int s = 0; s < 3; ++s) { g.W[s] = ws[s]; g.seg_begin[s] = segb[s]; }
-    g.seg_begin[3] = 0x7fffffff;
-    if (direct) { g.Y = direct + (size_t)m0 * ld_direct; g.ldy = ld_direct; g.split_stride = 0; }
-    else { g.Y = x->partial + (size_t)m0 * N; g.ldy = N; g.split_stride = (size_t)M * N; }
-    g.M = mm; g.N = N; g.K = K; g.mode = 0; g.splits = splits;
-    launch_gemm_mfma(g, x->st);
-  }
-  return splits;
-}
-int gemm_fast1(clover_ctx* x, int cls, Planes X, const void* W, int M, int N, int K, float* direct = nullptr,
-               int ld_direct = 0) {
-  const void* ws[1] = {W};
-  const int sn[1] = {N};
-  return gemm_fast(x, cls, X, 1, ws, sn, M, N, K, direct, ld_direct);
+  TileGemm g;
+  memset(&g, 0, sizeof(g));
+  g.X = X;
+  g.W = (const bf16_t*)W;
+  g.Y = part ? part : x->partial; g.ldy = N; g.split_stride = (size_t)M * N;
+  g.M = M; g.N = N; g.K = K; g.epi = 0;
+  g.k_parts = tile_gemm_pick_k_parts(M, N, K);
+  launch_gemm_tile(g, x->st);
+  return g.k_parts;
 }
 // Y = X W^T + bias through the MFMA path, for the small draft-side linears
-void linear_fast(clover_ctx* x, Planes X, const void* W, const void* bias, float* Y, int ldy, int M, int N, int K) {
-  const int sp = gemm_fast1(x, KC_GEMM_DRAFT, X, W, M, N, K);
+void linear_fast(clover_ctx* x, FragPlanes X, const void* W, const void* bias, float* Y, int ldy, int M, int N, int K) {
+  const int sp = gemm_fast(x, KC_GEMM_DRAFT, X, W, M, N, K);
   Scope sc(x, KC_ELTWISE);
   launch_reduce(x->partial, sp, (size_t)M * N, N, bias, x->cfg.dtype, Y, ldy, M, N, 0, x->st);
 }
-Planes split_to(clover_ctx* x, const float* src, int ld, float* planes_buf, int rows, int K) {
-  Planes P = planes_of(x, planes_buf, K);
+FragPlanes split_to(clover_ctx* x, const float* src, int ld, float* planes_buf, int rows, int K) {
+  FragPlanes P = frag_planes(planes_buf, rows);
   Scope sc(x, KC_ELTWISE);
-  launch_split_planes(src, ld, P.hi, P.lo, K, rows, K, x->st);
+  launch_split_planes(src, ld, P, rows, K, x->st);
   return P;
 }
 
@@ -551,81 +428,43 @@ void run_layer(clover_ctx* x, const clover_layer_weights& lw, float* xres, RowMa
   const int sn[3] = {c.n_q_heads * d, c.n_kv_heads * d, c.n_kv_heads * d};
   const void* ws[3] = {lw.wq, lw.wk, lw.wv};
   if (x->fast) {
-    Planes A = planes_of(x, x->a_norm, 2 * H);
-    A.ld = H;
-    Planes O = planes_of(x, x->attn_out, x->NQD);
-    Planes Hf = planes_of(x, x->h_ffn, F);
-    const int sq = gemm_fast(x, KC_GEMM_QKV, A, 3, ws, sn, M, x->QKVN, H, nullptr, 0);
+    const FragPlanes A = frag_planes(x->a_norm, M), O = frag_planes(x->attn_out, M), Hf = frag_planes(x->h_ffn, M);
+    bf16_t* const q_hi = (bf16_t*)x->q_rot;
+    bf16_t* const q_lo = q_hi + (size_t)x->max_rows * x->NQD;
+    const int sq = gemm_fast(x, KC_GEMM_QKV, A, lw.wq /* k and v rows behind it */, M, x->QKVN, H);
     { Scope s(x, KC_ROPE_KV);
-      Planes Q = planes_of(x, x->q_rot, x->NQD);
       launch_rope_kv_write(x->partial, x->QKVN, sq, (size_t)M * x->QKVN, x->cos_t, x->sin_t, x->q_rot, x->NQD, kc_layer,
                            vc_layer, x->kvdtype, kvl, base_len, c.n_q_heads, rm, x->d_err,
-                           x->attn_fast ? Q.hi : nullptr, Q.lo, 1.0f / sqrtf((float)d), x->st); }
+                           x->attn_fast ? q_hi : nullptr, q_lo, 1.0f / sqrtf((float)d), x->st); }
     { Scope s(x, KC_ATTN);
       if (x->attn_fast) {
         AttnParams ap;
         memset(&ap, 0, sizeof(ap));
-        Planes Q = planes_of(x, x->q_rot, x->NQD);
-        ap.q_hi = Q.hi; ap.q_lo = Q.lo; ap.ldq = x->NQD;
+        ap.q_hi = q_hi; ap.q_lo = q_lo; ap.ldq = x->NQD;
         ap.k_hi = (const bf16_t*)kc_layer; ap.k_plane = x->k_layer_elems;
         ap.v_hi = (const bf16_t*)vc_layer; ap.v_plane = x->v_layer_elems;
         ap.kv = kvl; ap.max_seq = c.max_seq; ap.n_kv = c.n_kv_heads; ap.n_q = c.n_q_heads;
         ap.base_len = base_len; ap.anc = anc; ap.iv = iv; ap.anc_stride = anc_stride; ap.rm = rm;
         ap.o_part = x->o_part; ap.ml_part = x->ml_part; ap.rows_total = x->max_rows; ap.max_splits = x->attn_max_splits;
-        launch_attn_mfma(ap, key_bound, O.hi, O.lo, x->NQD, x->st);
+        launch_attn_mfma(ap, key_bound, O, x->st);
       } else {
         launch_attn_generic(x->q_rot, x->NQD, kc_layer, vc_layer, x->kvdtype, kvl, base_len, anc, c.n_q_heads, nullptr,
-                            x->NQD, O.hi, O.lo, rm, x->st, anc_stride, iv);
+                            x->NQD, O, rm, x->st, anc_stride, iv);
       } }
-    const int sw = gemm_fast1(x, KC_GEMM_WO, O, lw.wo, M, H, x->NQD);
+    const int sw = gemm_fast(x, KC_GEMM_WO, O, lw.wo, M, H, x->NQD);
     { Scope s(x, KC_RMSNORM);
-      launch_reduce_add_norm(xres, H, x->partial, sw, (size_t)M * H, H, lw.ffn_norm, c.dtype, c.rms_eps, A.hi, A.lo, H, M,
-                             H, x->st); }
-    if (M >= x->tile_min && M <= 256 && tile_gemm_supported(M, F, H, 1)) {
-      Scope s(x, KC_GEMM_GATEUP);
+      launch_reduce_add_norm(xres, H, x->partial, sw, (size_t)M * H, H, lw.ffn_norm, c.dtype, c.rms_eps, A, M, H, x->st); }
+    { Scope s(x, KC_GEMM_GATEUP);
       TileGemm g;
       memset(&g, 0, sizeof(g));
-      g.Xhi = A.hi; g.Xlo = A.lo; g.ldx = H;
-      g.W[0] = (const bf16_t*)lw.w_gate; g.W[1] = (const bf16_t*)lw.w_up;
-      g.Yhi = Hf.hi; g.Ylo = Hf.lo; g.ldo = F;
+      g.X = A;
+      g.W = (const bf16_t*)lw.w_gate;   // gate and up rows interleaved
+      g.out = Hf;
       g.M = M; g.N = F; g.K = H; g.epi = 1; g.k_parts = 1;
-      launch_gemm_tile(g, x->st);
-    } else if (x->panel && M <= x->row_batch_max && panel_gemm_supported(std::min(M, 64), F, H, 1)) {
-      Scope s(x, KC_GEMM_GATEUP);
-      const int bm = (M > 64 && panel_gemm_supported(std::min(M, x->row_batch), F, H, 1)) ? x->row_batch : 64;
-      for (int m0 = 0; m0 < M; m0 += bm) {  // (more than 64 rows: one weight pass per batch, see gemm_fast)
-        PanelGemm g;
-        memset(&g, 0, sizeof(g));
-        g.Xhi = A.hi + (size_t)m0 * H; g.Xlo = A.lo + (size_t)m0 * H; g.ldx = H;
-        g.W[0] = (const bf16_t*)lw.w_gate; g.W[1] = (const bf16_t*)lw.w_up;
-        g.Yhi = Hf.hi + (size_t)m0 * F; g.Ylo = Hf.lo + (size_t)m0 * F; g.ldo = F;
-        g.M = std::min(bm, M - m0); g.N = F; g.K = H; g.epi = 1;
-        launch_gemm_panel(g, x->st);
-      }
-    } else if (M <= 64 && stream_gemm_supported(M, 2 * F, H) && stream_gemm_out_bytes(M, 2 * F, H) <= x->partial_bytes) {
-      const void* wgu[2] = {lw.w_gate, lw.w_up};
-      const int gun[2] = {F, F};
-      const int sg = gemm_fast(x, KC_GEMM_GATEUP, A, 2, wgu, gun, M, 2 * F, H, nullptr, 0);
-      Scope s(x, KC_ELTWISE);
-      launch_reduce_swiglu(x->partial, sg, (size_t)M * 2 * F, 2 * F, F, Hf.hi, Hf.lo, F, M, x->st);
-    } else {
-      Scope s(x, KC_GEMM_GATEUP);
-      for (int m0 = 0; m0 < M; m0 += 256) {
-        MfmaGemm g;
-        memset(&g, 0, sizeof(g));
-        g.Xhi = A.hi + (size_t)m0 * H; g.Xlo = A.lo + (size_t)m0 * H; g.ldx = H;
-        g.W[0] = g.W[1] = g.W[2] = (const bf16_t*)lw.w_gate;
-        g.W_up = (const bf16_t*)lw.w_up;
-        g.seg_begin[1] = g.seg_begin[2] = g.seg_begin[3] = 0x7fffffff;
-        g.Yhi = Hf.hi + (size_t)m0 * F; g.Ylo = Hf.lo + (size_t)m0 * F; g.ldy = F;
-        g.M = std::min(256, M - m0); g.N = F; g.K = H; g.mode = 2; g.splits = 1;
-        launch_gemm_mfma(g, x->st);
-      }
-    }
-    const int sd = gemm_fast1(x, KC_GEMM_DOWN, Hf, lw.w_down, M, H, F);
+      launch_gemm_tile(g, x->st); }
+    const int sd = gemm_fast(x, KC_GEMM_DOWN, Hf, lw.w_down, M, H, F);
     { Scope s(x, KC_RMSNORM);
-      launch_reduce_add_norm(xres, H, x->partial, sd, (size_t)M * H, H, next_gain, c.dtype, c.rms_eps, A.hi, A.lo, H, M,
-                             H, x->st); }
+      launch_reduce_add_norm(xres, H, x->partial, sd, (size_t)M * H, H, next_gain, c.dtype, c.rms_eps, A, M, H, x->st); }
     return;
   }
   { Scope s(x, KC_RMSNORM); launch_rmsnorm(xres, H, lw.attn_norm, c.dtype, c.rms_eps, x->a_norm, H, H, M, x->st); }
@@ -639,7 +478,7 @@ void run_layer(clover_ctx* x, const clover_layer_weights& lw, float* xres, RowMa
                          kvl, base_len, c.n_q_heads, rm, x->d_err, nullptr, nullptr, 0.f, x->st); }
   { Scope s(x, KC_ATTN);
     launch_attn_generic(x->q_rot, x->NQD, kc_layer, vc_layer, x->kvdtype, kvl, base_len, anc, c.n_q_heads, x->attn_out,
-                        x->NQD, nullptr, nullptr, rm, x->st, anc_stride, iv); }
+                        x->NQD, FragPlanes{}, rm, x->st, anc_stride, iv); }
   gemm_generic(x, KC_GEMM_WO, x->attn_out, x->NQD, lw.wo, nullptr, xres, H, M, H, x->NQD, 1);
   { Scope s(x, KC_RMSNORM); launch_rmsnorm(xres, H, lw.ffn_norm, c.dtype, c.rms_eps, x->a_norm, H, H, M, x->st); }
   gemm_generic(x, KC_GEMM_GATEUP, x->a_norm, H, lw.w_gate, nullptr, x->tmp_ffn, F, M, F, H, 0);
@@ -650,13 +489,11 @@ void run_layer(clover_ctx* x, const clover_layer_weights& lw, float* xres, RowMa
 
 
 // planes of RMSNorm(src) * gain in the a_norm buffer (MFMA path)
-Planes norm_planes(clover_ctx* x, const float* src, const void* gain, int rows) {
+FragPlanes norm_planes(clover_ctx* x, const float* src, const void* gain, int rows) {
   const clover_config& c = x->cfg;
-  Planes A = planes_of(x, x->a_norm, 2 * x->H);
-  A.ld = x->H;
+  const FragPlanes A = frag_planes(x->a_norm, rows);
   Scope s(x, KC_RMSNORM);
-  launch_reduce_add_norm(const_cast<float*>(src), x->H, nullptr, 0, 0, 0, gain, c.dtype, c.rms_eps, A.hi, A.lo, x->H, rows,
-                         x->H, x->st);
+  launch_reduce_add_norm(const_cast<float*>(src), x->H, nullptr, 0, 0, 0, gain, c.dtype, c.rms_eps, A, rows, x->H, x->st);
   return A;
 }
 
@@ -665,9 +502,9 @@ void run_ad(clover_ctx* x, const clover_ad_weights& ad, const float* xin, const 
   const clover_config& c = x->cfg;
   const int H = x->H;
   if (x->fast) {
-    Planes A = norm_planes(x, xin, ad.norm, rows);
+    const FragPlanes A = norm_planes(x, xin, ad.norm, rows);
     linear_fast(x, A, ad.wq, ad.bq, x->ad_q, H, rows, H, H);
-    Planes Y = split_to(x, y, H, x->pl_y, rows, H);
+    const FragPlanes Y = split_to(x, y, H, x->pl_y, rows, H);
     linear_fast(x, Y, ad.wk, ad.bk, x->ad_k, H, rows, H, H);
     linear_fast(x, Y, ad.wv, ad.bv, x->ad_v, H, rows, H, H);
   } else {
@@ -684,7 +521,7 @@ void run_ad(clover_ctx* x, const clover_ad_weights& ad, const float* xin, const 
 void run_fc(clover_ctx* x, const float* X, int K, const void* W, const void* bias, float* Y, int rows) {
   const int H = x->H;
   if (x->fast) {
-    Planes P = split_to(x, X, K, x->pl_y, rows, K);
+    const FragPlanes P = split_to(x, X, K, x->pl_y, rows, K);
     linear_fast(x, P, W, bias, Y, H, rows, H, K);
   } else {
     gemm_generic(x, KC_GEMM_DRAFT, X, K, W, bias, Y, H, rows, H, K, 0);
@@ -692,33 +529,15 @@ void run_fc(clover_ctx* x, const float* X, int K, const void* W, const void* bia
 }
 
 // out[rows, vocab] = A * lm_head^T (MFMA path)
-void lm_head_fast(clover_ctx* x, Planes A, int rows, float* out) {
+void lm_head_fast(clover_ctx* x, FragPlanes A, int rows, float* out) {
   const clover_config& c = x->cfg;
-  if (rows >= x->tile_min && rows <= 256 && tile_gemm_supported(rows, c.vocab, x->H, 0)) {
-    Scope s(x, KC_GEMM_LMHEAD);
-    TileGemm g;
-    memset(&g, 0, sizeof(g));
-    g.Xhi = A.hi; g.Xlo = A.lo; g.ldx = A.ld;
-    g.W[0] = g.W[1] = (const bf16_t*)x->lm_head_pk;
-    g.Y = out; g.ldy = c.vocab; g.M = rows; g.N = c.vocab; g.K = x->H; g.epi = 0; g.k_parts = 1;
-    launch_gemm_tile(g, x->st);
-    return;
-  }
-  if (x->panel && rows <= x->row_batch_max && panel_gemm_supported(std::min(rows, 64), c.vocab, x->H, 0)) {
-    Scope s(x, KC_GEMM_LMHEAD);
-    const int bm = (rows > 64 && panel_gemm_supported(std::min(rows, x->row_batch), c.vocab, x->H, 0)) ? x->row_batch : 64;
-    for (int m0 = 0; m0 < rows; m0 += bm) {  // (more than 64 rows: one weight pass per batch, see gemm_fast)
-      PanelGemm g;
-      memset(&g, 0, sizeof(g));
-      g.Xhi = A.hi + (size_t)m0 * A.ld; g.Xlo = A.lo + (size_t)m0 * A.ld; g.ldx = A.ld;
-      g.W[0] = g.W[1] = (const bf16_t*)x->lm_head_pk;
-      g.Y = out + (size_t)m0 * c.vocab; g.ldy = c.vocab;
-      g.M = std::min(bm, rows - m0); g.N = c.vocab; g.K = x->H; g.epi = 0;
-      launch_gemm_panel(g, x->st);
-    }
-    return;
-  }
-  gemm_fast1(x, KC_GEMM_LMHEAD, A, x->lm_head_pk, rows, c.vocab, x->H, out, c.vocab);
+  Scope s(x, KC_GEMM_LMHEAD);
+  TileGemm g;
+  memset(&g, 0, sizeof(g));
+  g.X = A;
+  g.W = (const bf16_t*)x->lm_head_pk;
+  g.Y = out; g.ldy = c.vocab; g.M = rows; g.N = c.vocab; g.K = x->H; g.epi = 0; g.k_parts = 1;
+  launch_gemm_tile(g, x->st);
 }
 
 // logits of `rows` contiguous rows of g through the head norm and the shared LM head, then top-k
@@ -726,7 +545,7 @@ void run_head(clover_ctx* x, const float* g, int rows, int k /* 0: logits only, 
   const clover_config& c = x->cfg;
   const int H = x->H;
   if (x->fast) {
-    Planes A = norm_planes(x, g, x->w.head_norm, rows);
+    const FragPlanes A = norm_planes(x, g, x->w.head_norm, rows);
     lm_head_fast(x, A, rows, x->z);
   } else {
     { Scope s(x, KC_RMSNORM); launch_rmsnorm(g, H, x->w.head_norm, c.dtype, c.rms_eps, x->a_norm, H, H, rows, x->st); }
@@ -735,34 +554,18 @@ void run_head(clover_ctx* x, const float* g, int rows, int k /* 0: logits only, 
   if (k > 0) { Scope s(x, KC_TOPK); launch_topk(x->z, c.vocab, c.vocab, rows, k, x->cand, x->topk_ids, x->st); }
 }
 
-// Can draft_tree take the fused route for `rows` GEMM rows?  (K-slice GEMMs for every draft linear, at most 8 slices
-// for the Attention Decoder's projections, room for the q and the k|v partials side by side.)
-bool draft_fused_ok(clover_ctx* x, int rows) {
-  const int H = x->H;
-  if (!x->fast || rows < 1 || rows > 64 || tune_int("CLOVER_DRAFT_UNFUSED", 0)) return false;
-  if (!ad_gate_fused_supported(H, x->cfg.ad_heads)) return false;
-  if (!stream_gemm_supported(rows, H, H) || !stream_gemm_supported(rows, 2 * H, H) || !stream_gemm_supported(rows, H, 2 * H) ||
-      !stream_gemm_supported(rows, x->cfg.vocab, H))
-    return false;
-  const int sH = stream_gemm_slices(H);
-  if (sH > 8) return false;
-  const size_t need = std::max((size_t)sH * rows * 3 * H, std::max((size_t)stream_gemm_slices(2 * H) * rows * H,
-                                                                    (size_t)sH * rows * x->cfg.vocab)) * sizeof(float);
-  return need <= x->partial_bytes;
-}
+// Can draft_tree take the fused route?  (The gate kernel deals whole heads to its lanes.)
+bool draft_fused_ok(clover_ctx* x) { return x->fast && ad_gate_fused_supported(x->H, x->cfg.ad_heads); }
 
-// Attention Decoder on the fused route: planes A = RMSNorm(x)*norm (rows, ld H), Y = y (rows, ld H) are in place;
-// q and k|v projections leave their K-slice partials side by side, the gate kernel does the rest.
-void run_ad_fused(clover_ctx* x, const clover_ad_weights& ad, Planes A, Planes Y, int rows, AdGateArgs g) {
-  const int H = x->H, sH = stream_gemm_slices(H);
-  float* Pq = x->partial;
-  float* Pkv = x->partial + (size_t)sH * rows * H;
-  gemm_fast1(x, KC_GEMM_DRAFT, A, ad.wq, rows, H, H, nullptr, 0);
-  const void* wkv[2] = {ad.wk, ad.wv};
-  const int nkv[2] = {H, H};
-  gemm_fast(x, KC_GEMM_DRAFT, Y, 2, wkv, nkv, rows, 2 * H, H, nullptr, 0, Pkv);
-  g.Pq = Pq; g.Sq = sH; g.sps_q = (size_t)rows * H;
-  g.Pkv = Pkv; g.Skv = sH; g.sps_kv = (size_t)rows * 2 * H;
+// Attention Decoder on the fused route: planes A = RMSNorm(x)*norm, Y = y are in place; q and k|v projections leave
+// their partial tiles side by side, the gate kernel does the rest.
+void run_ad_fused(clover_ctx* x, const clover_ad_weights& ad, FragPlanes A, FragPlanes Y, int rows, AdGateArgs g) {
+  const int H = x->H;
+  g.Pq = x->partial; g.sps_q = (size_t)rows * H;
+  g.Sq = gemm_fast(x, KC_GEMM_DRAFT, A, ad.wq, rows, H, H);
+  float* Pkv = x->partial + align256((size_t)g.Sq * rows * H * sizeof(float)) / sizeof(float);
+  g.Pkv = Pkv; g.sps_kv = (size_t)rows * 2 * H;
+  g.Skv = gemm_fast(x, KC_GEMM_DRAFT, Y, ad.wk /* v rows behind it */, rows, 2 * H, H, Pkv);
   g.bq = ad.bq; g.bk = ad.bk; g.bv = ad.bv;
   g.H = H; g.heads = x->cfg.ad_heads; g.eps = x->cfg.rms_eps;
   Scope sc(x, KC_AD_GATE);
@@ -788,7 +591,7 @@ void capture_draft_logits(clover_ctx* x, int j, int rows) {
 // Dynamic tree: expansion depth by depth (the root state and token are in candidate 0), then the selection.
 // Depth j expands F[j] candidates per sequence; their logits go through a log-softmax so that scores add up
 // along a path.
-void draft_expand_dynamic(clover_ctx* x, int B, const int* m, int* tree_tokens, bool fused, Planes A, Planes Y, Planes Cc) {
+void draft_expand_dynamic(clover_ctx* x, int B, const int* m, int* tree_tokens, bool fused) {
   const clover_config& c = x->cfg;
   const DynTree& t = x->dyn;
   const int H = x->H, C = t.C, ns = CLOVER_MAX_DEPTH * DYN_MAX_FRONT;
@@ -796,27 +599,26 @@ void draft_expand_dynamic(clover_ctx* x, int B, const int* m, int* tree_tokens, 
     const int n_lvl = t.F[j], rows = B * n_lvl;
     const int* nodes = t.frontier + (size_t)j * DYN_MAX_FRONT;
     if (fused) {
+      const FragPlanes A = frag_planes(x->a_norm, rows), Y = frag_planes(x->pl_y, rows), Cc = frag_planes(x->d_cat, rows);
       int sp;
       if (j == 0) {
-        sp = gemm_fast1(x, KC_GEMM_DRAFT, Y, x->w.fc0_w, rows, H, H);
+        sp = gemm_fast(x, KC_GEMM_DRAFT, Y, x->w.fc0_w, rows, H, H);
       } else {
         { Scope s(x, KC_DRAFT_MISC);
           launch_draft_level(x->dyn_state, t.cand_tok, nodes, t.cand_par, n_lvl, B, C, H, x->w.lm_head, c.vocab,
-                             x->w.ad2.norm, c.rms_eps, A.hi, A.lo, Y.hi, Y.lo, Cc.hi, Cc.lo, x->st, ns, C); }
+                             x->w.ad2.norm, c.rms_eps, A, Y, Cc, x->st, ns, C); }
         AdGateArgs g;
         memset(&g, 0, sizeof(g));
         g.x = x->dyn_state; g.ldx = H; g.out = x->dyn_state; g.ldo = H;
         g.nodes = nodes; g.parent = t.cand_par; g.n_lvl = n_lvl; g.R = C; g.m = m;
         g.nodes_stride = ns; g.parent_stride = C;
-        g.c_hi = Cc.hi; g.c_lo = Cc.lo; g.ldc = 2 * H;
+        g.cat = Cc;
         run_ad_fused(x, x->w.ad2, A, Y, rows, g);
-        Planes C2 = Cc;
-        C2.ld = 2 * H;
-        sp = gemm_fast1(x, KC_GEMM_DRAFT, C2, x->fc_w[j], rows, H, 2 * H);
+        sp = gemm_fast(x, KC_GEMM_DRAFT, Cc, x->fc_w[j], rows, H, 2 * H);
       }
       { Scope s(x, KC_RMSNORM);
-        launch_reduce_add_norm(x->d_g, H, x->partial, sp, (size_t)rows * H, H, x->w.head_norm, c.dtype, c.rms_eps, A.hi,
-                               A.lo, H, rows, H, x->st, j == 0 ? x->w.fc0_b : x->fc_b[j]); }
+        launch_reduce_add_norm(x->d_g, H, x->partial, sp, (size_t)rows * H, H, x->w.head_norm, c.dtype, c.rms_eps, A,
+                               rows, H, x->st, j == 0 ? x->w.fc0_b : x->fc_b[j]); }
       lm_head_fast(x, A, rows, x->z);
     } else {
       if (j == 0) {
@@ -1004,7 +806,11 @@ int clover_init(const clover_config* cfg, const clover_weights* w, const clover_
     const int H = x->H, d = cfg->head_dim, F = cfg->ffn;
     auto pack_layer = [&](clover_layer_weights& l) {
       pack(l.wq, cfg->n_q_heads * d, H); pack(l.wk, cfg->n_kv_heads * d, H); pack(l.wv, cfg->n_kv_heads * d, H);
-      pack(l.wo, H, x->NQD); pack(l.w_gate, F, H); pack(l.w_up, F, H); pack(l.w_down, H, F);
+      pack(l.wo, H, x->NQD);
+      launch_pack_gate_up(l.w_gate, l.w_up, cur, F, H, x->st);
+      l.w_gate = l.w_up = cur;
+      cur += (size_t)2 * F * H * 2;
+      pack(l.w_down, H, F);
     };
     for (auto& l : x->layers) pack_layer(l);
     for (auto& l : x->aug) pack_layer(l);
@@ -1123,25 +929,16 @@ int draft_tree(clover_ctx* x, int32_t batch, const float* hid_acc, const int32_t
   const int M = (B - 1) * R + n;
   int aug_bound = 0;
   for (int b = 0; b < B; ++b) aug_bound = std::max(aug_bound, x->aug_ub[b] + n);
-  int max_lvl_rows = B;
-  if (x->dyn_on)
-    for (int j = 0; j < x->dyn.D; ++j) max_lvl_rows = std::max(max_lvl_rows, B * x->dyn.F[j]);
-  else if (t.max_depth <= c.draft_depths)
-    for (int j = 0; j < t.max_depth; ++j) max_lvl_rows = std::max(max_lvl_rows, B * (t.lvl_off[j + 1] - t.lvl_off[j]));
-  const bool fused = draft_fused_ok(x, M) && draft_fused_ok(x, max_lvl_rows);
-  Planes A = planes_of(x, x->a_norm, 2 * H);
-  A.ld = H;
-  Planes Y = planes_of(x, x->pl_y, 2 * H);
-  Y.ld = H;
-  Planes Cc = planes_of(x, x->d_cat, 2 * H);   // [state ; embedding] rows of the per-depth FC
+  const bool fused = draft_fused_ok(x);
   if (fused) {
+    const FragPlanes A = frag_planes(x->a_norm, M), Y = frag_planes(x->pl_y, M);
     // embeddings of the follow-up tokens come from the LM-head rows; AD1 over (hidden state, embedding)
     { Scope s(x, KC_DRAFT_MISC);
-      launch_draft_pre(hid_acc, next_tok, x->w.ad1.norm, c.rms_eps, x->w.lm_head, c.vocab, H, rm, A.hi, A.lo, Y.hi, Y.lo, x->st); }
+      launch_draft_pre(hid_acc, next_tok, x->w.ad1.norm, c.rms_eps, x->w.lm_head, c.vocab, H, rm, A, Y, x->st); }
     AdGateArgs g;
     memset(&g, 0, sizeof(g));
     g.x = hid_acc; g.ldx = H; g.out = x->xd; g.ldo = H;
-    g.gain = x->aug[0].attn_norm; g.n_hi = A.hi; g.n_lo = A.lo;   // planes for the Augmenting Block's first layer
+    g.gain = x->aug[0].attn_norm; g.norm = A;   // planes for the Augmenting Block's first layer
     run_ad_fused(x, x->w.ad1, A, Y, M, g);
     { Scope s(x, KC_ROPE_KV); launch_rope_table(x->d_aug_len, nullptr, c.rope_base, c.head_dim, x->cos_t, x->sin_t, rm, x->st); }
   } else {
@@ -1162,7 +959,7 @@ int draft_tree(clover_ctx* x, int32_t batch, const float* hid_acc, const int32_t
     const int Rs = x->dyn_on ? x->dyn.C : R;
     Scope s(x, KC_DRAFT_MISC);
     if (fused) {
-      launch_draft_root_fused(x->xd, next_tok, m, B, R, H, root_state, root_tok, Y.hi, Y.lo, x->d_aug_len, x->st, Rs);
+      launch_draft_root_fused(x->xd, next_tok, m, B, R, H, root_state, root_tok, frag_planes(x->pl_y, B), x->d_aug_len, x->st, Rs);
     } else {
       launch_draft_root(x->xd, next_tok, m, B, R, H, x->d_rootx, root_state, root_tok, x->st, Rs);
       launch_add_len(x->d_aug_len, m, B, x->st);
@@ -1170,7 +967,7 @@ int draft_tree(clover_ctx* x, int32_t batch, const float* hid_acc, const int32_t
   }
   for (int b = 0; b < B; ++b) x->aug_ub[b] += n;
   if (x->dyn_on) {
-    draft_expand_dynamic(x, B, m, tree_tokens, fused, A, Y, Cc);
+    draft_expand_dynamic(x, B, m, tree_tokens, fused);
     return finish(x, "draft_tree");
   }
   // expansion, level by level; a tree deeper than the head (e.g. a prompt chain) is not expanded
@@ -1180,43 +977,32 @@ int draft_tree(clover_ctx* x, int32_t batch, const float* hid_acc, const int32_t
       if (n_lvl == 0) break;
       const int rows = B * n_lvl;
       if (fused) {
-        // depth j: (AD2 over the parent's state and the node's token embedding, then) FC_j; the FC's K-slice partials
-        // and bias go straight into the head norm; the LM head's partials go straight into the ranking
+        // depth j: (AD2 over the parent's state and the node's token embedding, then) FC_j; the FC's partial tiles
+        // and bias go straight into the head norm
+        const FragPlanes A = frag_planes(x->a_norm, rows), Y = frag_planes(x->pl_y, rows), Cc = frag_planes(x->d_cat, rows);
         int sp;
         if (j == 0) {
-          sp = gemm_fast1(x, KC_GEMM_DRAFT, Y, x->w.fc0_w, rows, H, H);
+          sp = gemm_fast(x, KC_GEMM_DRAFT, Y, x->w.fc0_w, rows, H, H);
         } else {
           const int* nodes = x->d_lvl_nodes + t.lvl_off[j];
           { Scope s(x, KC_DRAFT_MISC);
             launch_draft_level(x->d_state, tree_tokens, nodes, x->d_parent, n_lvl, B, R, H, x->w.lm_head, c.vocab,
-                               x->w.ad2.norm, c.rms_eps, A.hi, A.lo, Y.hi, Y.lo, Cc.hi, Cc.lo, x->st); }
+                               x->w.ad2.norm, c.rms_eps, A, Y, Cc, x->st); }
           AdGateArgs g;
           memset(&g, 0, sizeof(g));
           g.x = x->d_state; g.ldx = H; g.out = x->d_state; g.ldo = H;
           g.nodes = nodes; g.parent = x->d_parent; g.n_lvl = n_lvl; g.R = R; g.m = m;
-          g.c_hi = Cc.hi; g.c_lo = Cc.lo; g.ldc = 2 * H;
+          g.cat = Cc;
           run_ad_fused(x, x->w.ad2, A, Y, rows, g);
-          Planes C2 = Cc;
-          C2.ld = 2 * H;
-          sp = gemm_fast1(x, KC_GEMM_DRAFT, C2, x->fc_w[j], rows, H, 2 * H);
+          sp = gemm_fast(x, KC_GEMM_DRAFT, Cc, x->fc_w[j], rows, H, 2 * H);
         }
         { Scope s(x, KC_RMSNORM);
-          launch_reduce_add_norm(x->d_g, H, x->partial, sp, (size_t)rows * H, H, x->w.head_norm, c.dtype, c.rms_eps, A.hi,
-                                 A.lo, H, rows, H, x->st, j == 0 ? x->w.fc0_b : x->fc_b[j]); }
-        if (x->panel && panel_gemm_supported(std::min(rows, 64), c.vocab, H, 0)) {
-          lm_head_fast(x, A, rows, x->z);
-          capture_draft_logits(x, j, rows);
-          Scope s(x, KC_TOPK);
-          launch_topk(x->z, c.vocab, c.vocab, rows, t.kmax[j], x->cand, x->topk_ids, x->st);
-        } else {
-          const int spv = gemm_fast1(x, KC_GEMM_LMHEAD, A, x->lm_head_pk, rows, c.vocab, H);
-          if (x->draft_capture) {
-            launch_reduce(x->partial, spv, (size_t)rows * c.vocab, c.vocab, nullptr, c.dtype, x->z, c.vocab, rows, c.vocab, 0, x->st);
-            capture_draft_logits(x, j, rows);
-          }
-          Scope s(x, KC_TOPK);
-          launch_topk(x->partial, c.vocab, c.vocab, rows, t.kmax[j], x->cand, x->topk_ids, x->st, spv, (size_t)rows * c.vocab);
-        }
+          launch_reduce_add_norm(x->d_g, H, x->partial, sp, (size_t)rows * H, H, x->w.head_norm, c.dtype, c.rms_eps, A,
+                                 rows, H, x->st, j == 0 ? x->w.fc0_b : x->fc_b[j]); }
+        lm_head_fast(x, A, rows, x->z);
+        capture_draft_logits(x, j, rows);
+        { Scope s(x, KC_TOPK);
+          launch_topk(x->z, c.vocab, c.vocab, rows, t.kmax[j], x->cand, x->topk_ids, x->st); }
         { Scope s(x, KC_DRAFT_MISC);
           launch_draft_assign(x->topk_ids, x->d_par_row, x->d_rank, t.node_off[j + 1], t.node_off[j + 2], n_lvl, B, R, m,
                               tree_tokens, x->st); }
@@ -1272,9 +1058,7 @@ int verify_tree(clover_ctx* x, int32_t batch, const int32_t* tree_tokens, float*
               x->vc + (size_t)l * x->v_layer_elems * x->kv_esz, x->d_seq_len, anc_tab,
               l + 1 < c.n_layers ? x->layers[l + 1].attn_norm : x->w.final_norm, key_bound, topo_stride, iv_tab);
   if (x->fast) {
-    Planes A = planes_of(x, x->a_norm, 2 * H);
-    A.ld = H;
-    lm_head_fast(x, A, M, logits);
+    lm_head_fast(x, frag_planes(x->a_norm, M), M, logits);
   } else {
     { Scope s(x, KC_RMSNORM); launch_rmsnorm(hidden, H, x->w.final_norm, c.dtype, c.rms_eps, x->a_norm, H, H, M, x->st); }
     gemm_generic(x, KC_GEMM_LMHEAD, x->a_norm, H, x->w.lm_head, nullptr, logits, c.vocab, M, c.vocab, H, 0);
@@ -1353,17 +1137,13 @@ int clover_prefill(clover_ctx* x, int32_t b, const int32_t* tokens, int32_t n, f
     for (int l = 0; l < c.n_layers; ++l)
       run_layer(x, x->layers[l], xres, rm, M, x->kc + (size_t)l * x->k_layer_elems * x->kv_esz,
                 x->vc + (size_t)l * x->v_layer_elems * x->kv_esz, len_b, nullptr,
-                l + 1 < c.n_layers ? x->layers[l + 1].attn_norm : x->w.final_norm, key_bound, 0, nullptr, b);
+                l + 1 < c.n_layers ? x->layers[l + 1].attn_norm : nullptr, key_bound, 0, nullptr, b);
     { Scope s(x, KC_DRAFT_MISC); launch_add_scalar(len_b, M, x->st); }
     x->len_ub[b] += M;
     if (last) {
       // LM head on the last row only; its hidden state is the hand-off row
       if (x->fast) {
-        Planes A = planes_of(x, x->a_norm, 2 * H);
-        A.ld = H;
-        A.hi += (size_t)(M - 1) * H;
-        A.lo += (size_t)(M - 1) * H;
-        lm_head_fast(x, A, 1, logits_last);
+        lm_head_fast(x, norm_planes(x, xres + (size_t)(M - 1) * H, x->w.final_norm, 1), 1, logits_last);
       } else {
         { Scope s(x, KC_RMSNORM);
           launch_rmsnorm(xres + (size_t)(M - 1) * H, H, x->w.final_norm, c.dtype, c.rms_eps, x->a_norm, H, H, 1, x->st); }
@@ -1529,18 +1309,37 @@ const char* clover_kernel_class_name(int32_t cls) { return (cls >= 0 && cls < KC
 const char* clover_last_error(clover_ctx* x) { return x ? x->err.c_str() : ""; }
 const char* clover_last_global_error(void) { return g_err.c_str(); }
 
+// Operator scratch: [packed weight copy][activation planes][partial tiles].  `rule` is the size that decides what the
+// static variant accepts: whole-number rows and one partial tile per 512 columns of K (up to 64 rows) or per K range of
+// 256-column tiles; the layout below is never larger but for the planes' row blocks, which the array has room for.
+struct OpGemmScratch { size_t planes, partial, total, rule; int kp; };
+static OpGemmScratch op_gemm_scratch(int M, int N, int K) {
+  OpGemmScratch o;
+  int parts = M <= 64 ? (K + 511) / 512 : 1;
+  for (int d = 1; M > 64 && d <= K / 512; ++d)
+    if (K / 64 % d == 0 && (N + 255) / 256 * (M > 128 ? 2 : 1) * d <= 256) parts = d;
+  o.kp = tile_gemm_pick_k_parts(M, N, K);
+  if (o.kp > parts) o.kp = 1;
+  o.planes = align256((size_t)N * K * 2);
+  o.partial = o.planes + align256((size_t)((M + 15) / 16 * 16) * K * 4);
+  o.total = 256 + o.partial + align256((size_t)o.kp * M * N * sizeof(float));
+  o.rule = 256 + o.planes + align256((size_t)M * K * 4) + align256((size_t)parts * M * N * sizeof(float));
+  return o;
+}
 size_t clover_op_gemm_scratch_bytes(int32_t M, int32_t N, int32_t K) {
-  if (M < 1 || N < 1 || K < 1) return 256;
-  size_t bytes = 256;
-  if (M <= 256 && mfma_gemm_supported(M, N, K, 0)) {
-    size_t out = mfma_gemm_out_bytes(M, N, mfma_gemm_pick_splits(M, N, K, 0));
-    if (stream_gemm_supported(M, N, K)) out = std::max(out, stream_gemm_out_bytes(M, N, K));
-    out = std::max(out, (size_t)std::max(panel_gemm_pick_k_parts(M, N, K), 0) * M * N * sizeof(float));
-    if (tile_gemm_supported(M, N, K, 0))
-      out = std::max(out, (size_t)tile_gemm_pick_k_parts(M, N, K) * M * N * sizeof(float));
-    bytes += align256((size_t)M * K * 4) + align256(out) + align256((size_t)N * K * 2);
-  }
-  return bytes;
+  if (M < 1 || N < 1 || K < 1 || M > 256 || !mfma_shape_ok(N, K)) return 256;
+  const OpGemmScratch o = op_gemm_scratch(M, N, K);
+  return std::max(o.rule, o.total);
+}
+// The K-range paths keep to narrow outputs with a long K: ranges of at least four stages (256 columns, 128 from 65 rows
+// on) of 128-column tiles that fill most of the chip.
+static bool op_gemm_k_range_ok(int M, int N, int K) {
+  const int st = M > 64 ? 128 : 256, wgs_n = (N / 32 + 3) / 4, NS = K / st;
+  if (M > 128 || K % st != 0 || N % 32 != 0) return false;
+  int best = 0;
+  for (int d = 1; d <= NS; ++d)
+    if (NS % d == 0 && wgs_n * d <= 256 && NS / d >= 4) best = d;
+  return best > 1 && wgs_n * best >= (M > 64 ? 160 : 224);
 }
 
 int clover_op_gemm(int32_t path, int32_t dtype, const float* X, const void* W, float* Y, int32_t ldy, int32_t M,
@@ -1552,12 +1351,14 @@ int clover_op_gemm_static(int32_t path, int32_t dtype, const float* X, const voi
                           int32_t N, int32_t K, void* hip_stream) {
   if (path != 0 && path != 1 && path != 3 && path != 5)
     return fail(nullptr, CLOVER_E_SHAPE, "clover_op_gemm_static: path must be 0, 1, 3 or 5 (the shared buffer keeps no copy between calls)");
-  if (M >= 1 && N >= 1 && K >= 1 && clover_op_gemm_scratch_bytes(M, N, K) > CLOVER_STATIC_SCRATCH_BYTES)
+  const bool mfma = M >= 1 && N >= 1 && K >= 1 && M <= 256 && mfma_shape_ok(N, K);
+  const OpGemmScratch o = mfma ? op_gemm_scratch(M, N, K) : OpGemmScratch{};
+  if (o.rule > CLOVER_STATIC_SCRATCH_BYTES || o.total > kStaticScratch)
     return fail(nullptr, CLOVER_E_CAPACITY, "clover_op_gemm_static: M, N, K need more than CLOVER_STATIC_SCRATCH_BYTES of scratch");
   void* ptr = nullptr;
   const int rc = static_scratch_ptr(&ptr);
   if (rc) return rc;
-  return op_gemm_impl(path, dtype, X, W, Y, ldy, M, N, K, ptr, CLOVER_STATIC_SCRATCH_BYTES, hip_stream);
+  return op_gemm_impl(path, dtype, X, W, Y, ldy, M, N, K, ptr, kStaticScratch, hip_stream);
 }
 
 }  // extern "C"
@@ -1571,75 +1372,34 @@ int op_gemm_impl(int32_t path, int32_t dtype, const float* X, const void* W, flo
   if (path == 0) {
     launch_gemm_generic(X, K, W, nullptr, dtype, Y, ldy, M, N, K, 0, st);
   } else {
-    if (dtype != CLOVER_DTYPE_BF16 || M > 256 || !mfma_gemm_supported(M, N, K, 0))
+    if (dtype != CLOVER_DTYPE_BF16 || M > 256 || !mfma_shape_ok(N, K))
       return fail(nullptr, CLOVER_E_SHAPE, "shape not supported by the MFMA GEMM");
-    if (scratch_bytes < clover_op_gemm_scratch_bytes(M, N, K)) return fail(nullptr, CLOVER_E_CAPACITY, "scratch too small");
-    // scratch: [packed weight copy][activation planes][partials]; the copy is made once per scratch
-    // buffer contents, so repeated calls with the same W measure the GEMM alone (path 2 skips it)
-    bf16_t* wp = (bf16_t*)scratch;
-    bf16_t* hi = (bf16_t*)((char*)scratch + align256((size_t)N * K * 2));
-    bf16_t* lo = hi + (size_t)M * K;
-    float* part = (float*)((char*)hi + align256((size_t)M * K * 4));
-    if (path & 1) launch_pack_weight(W, wp, N, K, st);
-    launch_split_planes(X, K, hi, lo, K, M, K, st);
-    int splits;
-    if (path == 7) {   // tiled kernel over K ranges, then the sum of the ranges
-      if (!tile_gemm_supported(M, N, K, 0)) return fail(nullptr, CLOVER_E_SHAPE, "shape not supported by the tiled GEMM");
-      const int kp = tile_gemm_pick_k_parts(M, N, K);
-      TileGemm g;
-      memset(&g, 0, sizeof(g));
-      g.Xhi = hi; g.Xlo = lo; g.ldx = K;
-      g.W[0] = g.W[1] = wp;
-      g.Y = part; g.ldy = N; g.k_parts = kp; g.split_stride = (size_t)M * N;
-      g.M = M; g.N = N; g.K = K; g.epi = 0;
-      launch_gemm_tile(g, st);
-      launch_reduce(part, kp, (size_t)M * N, N, nullptr, dtype, Y, ldy, M, N, 0, st);
-      const hipError_t e = hipGetLastError();
-      if (e != hipSuccess) return fail(nullptr, CLOVER_E_HIP, hipGetErrorString(e));
-      return CLOVER_OK;
-    }
-    if (path >= 3) {
-      if (!panel_gemm_supported(M, N, K, 0) || ldy % 4 != 0)
+    if (path >= 3 && path != 7) {
+      if (M > 128 || K % (M > 64 ? 128 : 256) != 0 || ldy % 4 != 0)
         return fail(nullptr, CLOVER_E_SHAPE, "shape not supported by the panel GEMM");
-      PanelGemm g;
-      memset(&g, 0, sizeof(g));
-      g.Xhi = hi; g.Xlo = lo; g.ldx = K;
-      g.W[0] = g.W[1] = wp;
-      g.Y = Y; g.ldy = ldy; g.M = M; g.N = N; g.K = K; g.epi = 0;
-      if (path >= 5) {  // K ranges into partials, then the reduction every consumer of partials performs
-        const int kp = panel_gemm_pick_k_parts(M, N, K);
-        if (kp < 2) return fail(nullptr, CLOVER_E_SHAPE, "shape not supported by the K-range panel GEMM");
-        g.Y = part; g.ldy = N; g.k_parts = kp; g.split_stride = (size_t)M * N;
-        launch_gemm_panel(g, st);
-        launch_reduce(part, kp, (size_t)M * N, N, nullptr, dtype, Y, ldy, M, N, 0, st);
-      } else {
-        launch_gemm_panel(g, st);
-      }
-      const hipError_t e = hipGetLastError();
-      if (e != hipSuccess) return fail(nullptr, CLOVER_E_HIP, hipGetErrorString(e));
-      return CLOVER_OK;
+      if (path >= 5 && !op_gemm_k_range_ok(M, N, K))
+        return fail(nullptr, CLOVER_E_SHAPE, "shape not supported by the K-range panel GEMM");
     }
-    if (M <= 64 && stream_gemm_supported(M, N, K)) {
-      StreamGemm g;
-      memset(&g, 0, sizeof(g));
-      g.Xhi = hi; g.Xlo = lo; g.ldx = K;
-      g.W[0] = g.W[1] = g.W[2] = wp;
-      g.seg_begin[1] = g.seg_begin[2] = g.seg_begin[3] = 0x7fffffff;
-      g.Y = part; g.ldy = N; g.split_stride = (size_t)M * N; g.M = M; g.N = N; g.K = K;
-      launch_gemm_stream(g, st);
-      splits = stream_gemm_slices(K);
+    const OpGemmScratch o = op_gemm_scratch(M, N, K);
+    if (scratch_bytes < o.total) return fail(nullptr, CLOVER_E_CAPACITY, "scratch too small");
+    // the weight copy is made once per scratch buffer contents, so repeated calls with the same W measure the GEMM
+    // alone (the even paths skip it)
+    if (path & 1) launch_pack_weight(W, scratch, N, K, st);
+    TileGemm g;
+    memset(&g, 0, sizeof(g));
+    g.X = frag_planes((char*)scratch + o.planes, M);
+    launch_split_planes(X, K, g.X, M, K, st);
+    g.W = (const bf16_t*)scratch;
+    g.M = M; g.N = N; g.K = K; g.epi = 0;
+    if (path == 3 || path == 4) {
+      g.Y = Y; g.ldy = ldy; g.k_parts = 1;
+      launch_gemm_tile(g, st);
     } else {
-      MfmaGemm g;
-      memset(&g, 0, sizeof(g));
-      g.Xhi = hi; g.Xlo = lo; g.ldx = K;
-      g.W[0] = g.W[1] = g.W[2] = wp;
-      g.seg_begin[0] = 0; g.seg_begin[1] = g.seg_begin[2] = g.seg_begin[3] = 0x7fffffff;
-      g.Y = part; g.ldy = N; g.split_stride = (size_t)M * N;
-      g.M = M; g.N = N; g.K = K; g.mode = 0;
-      g.splits = splits = mfma_gemm_pick_splits(M, N, K, 0);
-      launch_gemm_mfma(g, st);
+      g.Y = (float*)((char*)scratch + o.partial); g.ldy = N; g.split_stride = (size_t)M * N;
+      g.k_parts = o.kp;
+      launch_gemm_tile(g, st);
+      launch_reduce(g.Y, g.k_parts, g.split_stride, N, nullptr, dtype, Y, ldy, M, N, 0, st);
     }
-    launch_reduce(part, splits, (size_t)M * N, N, nullptr, dtype, Y, ldy, M, N, 0, st);
   }
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(nullptr, CLOVER_E_HIP, hipGetErrorString(e));

@@ -54,6 +54,41 @@ __device__ __forceinline__ size_t kv_v_at(const KVLayout& kv, int b, int head, i
 }
 #endif
 
+// ---- GEMM activations in fragment order ---------------------------------------------------------
+// An activation matrix that feeds the MFMA GEMM is kept as two bf16 planes (hi, lo) with hi + lo == x to 16 mantissa
+// bits, stored as the GEMM stages them: [K/32][mb row blocks][hi, lo][16 rows][32 columns], every (row block, plane) of
+// a 32-column step one contiguous KB.  A compute unit pulls contiguous KBs from the L2 at 124 GB/s and 16 rows of 64 or
+// 128 bytes out of a row-major matrix at 62 (256 compute units at once, 8 KB row stride), and the activations are half
+// of what a GEMM workgroup loads.  The four 16-byte pieces of a row's 64 bytes are permuted by the row, so that the
+// 16-row fragment reads from the (identical) LDS image run without bank conflicts; a producer that owns a row still
+// writes whole 64-byte segments.
+struct FragPlanes {
+  bf16_t* p;
+  int mb;   // row blocks = ceil(rows / 16); rows past the matrix in the last block are never initialised
+};
+inline FragPlanes frag_planes(void* buf, int rows) { return FragPlanes{(bf16_t*)buf, (rows + 15) / 16}; }
+#ifdef __HIPCC__
+// element index of the hi value at (row, col); the lo value is 512 elements further.  The 8 columns of a piece
+// (col % 8 == 0) are contiguous.
+__device__ __forceinline__ size_t frag_at(const FragPlanes& f, int row, int col) {
+  const int r = row & 15, pc = ((col >> 3) & 3) ^ ((0 - (r >> 2)) & 3);
+  return ((size_t)(col >> 5) * f.mb + (row >> 4)) * 1024 + r * 32 + pc * 8 + (col & 7);
+}
+// four adjacent columns (col % 4 == 0) of one row
+__device__ __forceinline__ void frag_store4(const FragPlanes& f, int row, int col, float o0, float o1, float o2, float o3) {
+  const float o[4] = {o0, o1, o2, o3};
+  unsigned h[4], l[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {   // round to nearest even through the hardware conversion (v_cvt_pk_bf16_f32)
+    h[r] = (unsigned)__builtin_bit_cast(unsigned short, (__bf16)o[r]);
+    l[r] = (unsigned)__builtin_bit_cast(unsigned short, (__bf16)(o[r] - __uint_as_float(h[r] << 16)));
+  }
+  bf16_t* dst = f.p + frag_at(f, row, col);
+  *(uint2*)dst = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
+  *(uint2*)(dst + 512) = make_uint2(l[0] | (l[1] << 16), l[2] | (l[3] << 16));
+}
+#endif
+
 // ---- generic (fp32 ALU) kernels; wdtype: 0 fp32, 1 bf16 ---------------------------------------
 void launch_embed(const void* table, int wdtype, const int* tok, int vocab, float* out, int ldo, int H,
                   RowMap rm, hipStream_t st);
@@ -68,7 +103,7 @@ void launch_rope_kv_write(const float* qkv, int ldqkv, int qkv_splits, size_t qk
                           hipStream_t st);
 void launch_attn_generic(const float* q, int ldq, const void* k_cache, const void* v_cache, int kvdtype, KVLayout kv,
                          const int* base_len, const unsigned long long* anc /*[n][2]*/, int n_q, float* out, int ldo,
-                         bf16_t* out_hi, bf16_t* out_lo /*planes instead of fp32 when non-null*/, RowMap rm,
+                         FragPlanes planes /*instead of fp32 when planes.p is non-null*/, RowMap rm,
                          hipStream_t st, int anc_stride = 0 /*nodes per sequence in a per-sequence mask table, 0: shared*/,
                          const int* iv = nullptr /*[n][2] interval labels: decide visibility instead of anc when given*/);
 // mode 0: Y = X W^T (+bias); mode 1: Y += X W^T (+bias)
@@ -81,9 +116,7 @@ void launch_ad_gate(const float* x, int ldx, const float* q, const float* k, con
 // top-k of each row of z[rows, V] by (value desc, id asc); k <= CLOVER_MAX_RANK.
 // cand: scratch [rows][chunks][16] of (float,int) pairs; out_ids [rows][16]; chunks = topk_chunks(V).
 int topk_chunks(int V);
-// z may be given as `splits` partial tiles z[s*split_stride + row*ldz + id] that are summed on the fly (1: plain)
-void launch_topk(const float* z, int ldz, int V, int rows, int k, void* cand, int* out_ids, hipStream_t st, int splits = 1,
-                 size_t split_stride = 0);
+void launch_topk(const float* z, int ldz, int V, int rows, int k, void* cand, int* out_ids, hipStream_t st);
 
 // ---- draft-tree bookkeeping -------------------------------------------------------------------
 // gather for level rows: row (b,r) <- node u = lvl_nodes[r]; xs = state[b][parent(u)], e = lm_head[token[b][u]]
@@ -120,38 +153,16 @@ void launch_write_kv(void* k_cache, void* v_cache, int kvdtype, KVLayout kv, int
                      const float* k_in, const float* v_in, hipStream_t st);
 void launch_fill_i32(int* p, int v, int n, hipStream_t st);
 
-// ---- split-bf16 activation planes and partial-sum consumers ------------------------------------
-// An activation matrix that feeds the MFMA GEMM is stored as two bf16 planes (hi, lo) with
-// hi + lo == x to 16 mantissa bits.
-void launch_split_planes(const float* x, int ldx, bf16_t* hi, bf16_t* lo, int ldo, int rows, int K, hipStream_t st);
+// ---- activation planes and partial-sum consumers ------------------------------------------------
+void launch_split_planes(const float* x, int ldx, FragPlanes out, int rows, int K, hipStream_t st);
 // Y[m,n] (=|+=) sum_s P[s*split_stride + m*ldp + n] (+ bias[n]);  mode 0 store, 1 add
 void launch_reduce(const float* P, int splits, size_t split_stride, int ldp, const void* bias, int wdtype, float* Y,
                    int ldy, int M, int N, int mode, hipStream_t st);
-// x[m,:] += sum_s P[s][m][:]  (splits may be 0); then, if gain: (hi, lo)[m,:] = split(rmsnorm(x[m,:]) * gain)
+// x[m,:] += sum_s P[s][m][:]  (splits may be 0); then, if gain: out[m,:] = planes of rmsnorm(x[m,:]) * gain
 // bias non-null: x[m,:] = bias + sum_s P[s][m][:] (the old x is not read)
 void launch_reduce_add_norm(float* x, int ldx, const float* P, int splits, size_t split_stride, int ldp,
-                            const void* gain, int wdtype, float eps, bf16_t* hi, bf16_t* lo, int ldo, int rows, int H,
+                            const void* gain, int wdtype, float eps, FragPlanes out, int rows, int H,
                             hipStream_t st, const void* bias = nullptr);
-
-// ---- MFMA weight-streaming GEMM (bf16 weights, split-bf16 activations in, fp32 out) -------------
-struct MfmaGemm {
-  const bf16_t *Xhi, *Xlo; int ldx;   // activation planes [M, K]
-  const bf16_t* W[3];      // up to three fragment-major row-segments (fused QKV); plain GEMM uses W[0]
-  int seg_begin[4];        // segment s covers output columns [seg_begin[s], seg_begin[s+1])
-  const bf16_t* W_up;      // mode 2: second matrix (W[0] = gate)
-  float* Y; int ldy;       // mode 0: split s writes Y[s*split_stride + m*ldy + n]
-  size_t split_stride;
-  bf16_t *Yhi, *Ylo;       // mode 2: silu(X Wg^T) * (X Wu^T) as planes, leading dimension ldy
-  int M, N, K;
-  int mode;                // 0 partial/plain fp32 store, 2 SwiGLU
-  int splits;              // split-K factor (>=1; 1 for mode 2)
-  int dbg;                 // ablation builds only: 1 no MFMA, 2 no weight loads, 4 no activation loads
-};
-bool mfma_gemm_supported(int M, int N, int K, int mode);
-int mfma_gemm_pick_splits(int M, int N, int K, int mode);
-size_t mfma_gemm_out_bytes(int M, int N, int splits);
-void launch_gemm_mfma(const MfmaGemm& g, hipStream_t st);
-
 
 // ---- MFMA tree attention (head_dim 128, caches as bf16 planes) ---------------------------------
 struct AttnParams {
@@ -173,68 +184,34 @@ struct AttnParams {
 };
 bool attn_mfma_supported(int head_dim, int n_q, int n_kv, int max_seq);
 // max_total_keys: host-side upper bound of base_len[b] + rm.n over the batch (sizes the key splits)
-void launch_attn_mfma(AttnParams p, int max_total_keys, bf16_t* out_hi, bf16_t* out_lo, int ldo, hipStream_t st);
+void launch_attn_mfma(AttnParams p, int max_total_keys, FragPlanes out, hipStream_t st);
 
-// ---- fragment-major weights and the K-slice-resident streaming GEMM (M <= 64) -------------------
+// ---- fragment-major weights and the GEMM that reads them ----------------------------------------
 // [N,K] row-major bf16 -> [N/16][K/32][64 lanes][8]: lane l of tile (nb, kt) holds row nb*16 + l%16,
-// columns kt*32 + (l/16)*8 .. +7.  Both MFMA GEMMs read this layout.
+// columns kt*32 + (l/16)*8 .. +7: a matrix-instruction operand is one contiguous KB.
 void launch_pack_weight(const void* src, void* dst, int N, int K, hipStream_t st);
-struct StreamGemm {
-  const bf16_t *Xhi, *Xlo; int ldx;   // activation planes [M, K]
-  const bf16_t* W[3];                 // fragment-major weight segments
-  int seg_begin[4];                   // segment s covers output columns [seg_begin[s], seg_begin[s+1])
-  float* Y; int ldy;                  // slice s writes Y[s*split_stride + m*ldy + n]
-  size_t split_stride;
-  int M, N, K;
-  int n_slices, groups;               // filled in by launch_gemm_stream
-  int tag;                            // 1: gate+up projection (selects a separately named instantiation)
-  int dbg;                            // ablation builds only: 1 no activation loads, 2 no stores
-};
-bool stream_gemm_supported(int M, int N, int K);
-int stream_gemm_slices(int K);
-size_t stream_gemm_out_bytes(int M, int N, int K);
-void launch_gemm_stream(StreamGemm g, hipStream_t st);
-// (hi, lo)[m, c] = split(silu(sum_s P[s][m][c]) * sum_s P[s][m][F + c])
-void launch_reduce_swiglu(const float* P, int splits, size_t split_stride, int ldp, int F, bf16_t* hi, bf16_t* lo,
-                          int ldo, int rows, hipStream_t st);
-
-
-// ---- full-K panel GEMM (M <= 64, many output columns): finished results, no K-slice partials ----
-struct PanelGemm {
-  const bf16_t *Xhi, *Xlo; int ldx;   // activation planes [M, K]
-  const bf16_t* W[2];                 // fragment-major; epi 1: W[0] = gate, W[1] = up, each [N, K]
-  float* Y; int ldy;                  // epi 0: fp32 [M, N]
-  bf16_t *Yhi, *Ylo; int ldo;         // epi 1: planes of silu(X W0^T) * (X W1^T), [M, N]
-  int M, N, K;
-  int epi;                            // 0 plain, 1 SwiGLU
-  int k_parts; size_t split_stride;   // epi 0 only: K is cut into k_parts ranges, range r writes Y + r * split_stride
-  int rows128;                        // use the 65..128-row form whatever M is (k_parts was picked for its stage width)
-  int dbg;                            // ablation builds only: 1 no activation loads, 2 no stage rotation
-};
-bool panel_gemm_supported(int M, int N, int K, int epi);
-// how many K ranges make the plain panel GEMM fill the chip for a NARROW output (0: not worth it)
-int panel_gemm_pick_k_parts(int M, int N, int K);
-void launch_gemm_panel(const PanelGemm& g, hipStream_t st);
-
-// ---- tiled GEMM for 65..256 rows: one weight pass, 128-row x 256-column workgroup tiles ------------------
+// gate and up, each [F,K], as one matrix of 2F rows: block b holds rows 8b .. 8b+7 of the gate, then those of the up
+void launch_pack_gate_up(const void* gate, const void* up, void* dst, int F, int K, hipStream_t st);
 struct TileGemm {
-  const bf16_t *Xhi, *Xlo; int ldx;   // activation planes [M, K]
-  const bf16_t* W[2];                 // fragment-major; epi 1: W[0] = gate, W[1] = up, each [N, K]
+  FragPlanes X;                       // activations [M, K]
+  const bf16_t* W;                    // fragment-major [N, K]; epi 1: gate and up interleaved, [2N, K]
   float* Y; int ldy;                  // epi 0: fp32 [M, N]; range r of K writes Y + r * split_stride
-  bf16_t *Yhi, *Ylo; int ldo;         // epi 1: planes of silu(X W0^T) * (X W1^T), [M, N]
+  FragPlanes out;                     // epi 1: planes of silu(X Wg^T) * (X Wu^T), [M, N]
   int M, N, K;
   int epi;                            // 0 plain, 1 SwiGLU
   int k_parts; size_t split_stride;   // epi 0 only
   int n_units;                        // filled in by launch_gemm_tile: column tiles x K ranges
 };
-bool tile_gemm_supported(int M, int N, int K, int epi);
+constexpr int TILE_MAX_K_PARTS = 8;
+bool tile_gemm_supported(int N, int K);
+// K ranges of a narrow output; the same for all M that round up to the same multiple of 32
 int tile_gemm_pick_k_parts(int M, int N, int K);
 void launch_gemm_tile(const TileGemm& g, hipStream_t st);
 
 // ---- fused bookkeeping kernels of the draft head (MFMA path, bf16 weights) ----------------------
-// planes of RMSNorm(hid[row]) * gain -> (a_hi, a_lo) and of the embedding of tok[row] -> (y_hi, y_lo), rows of `rm`
+// planes of RMSNorm(hid[row]) * gain -> a and of the embedding of tok[row] -> y, rows of `rm`
 void launch_draft_pre(const float* hid, const int* tok, const void* gain, float eps, const void* table, int vocab, int H,
-                      RowMap rm, bf16_t* a_hi, bf16_t* a_lo, bf16_t* y_hi, bf16_t* y_lo, hipStream_t st);
+                      RowMap rm, FragPlanes a, FragPlanes y, hipStream_t st);
 // Attention-Decoder gate reading the q and (k|v) GEMMs' K-slice partials and adding the biases itself
 struct AdGateArgs {
   const float* x; int ldx;                    // residual input rows
@@ -246,20 +223,19 @@ struct AdGateArgs {
   int nodes_stride, parent_stride;            // per-sequence strides of nodes / parent (0: shared by all sequences)
   const int* m;                               // with nodes: sequences with m[b] < 1 are skipped (null: none)
   float* out; int ldo;
-  const void* gain; float eps; bf16_t *n_hi, *n_lo;   // gain non-null: planes of RMSNorm(result)*gain, row g, ld H
-  bf16_t *c_hi, *c_lo; int ldc;               // non-null: planes of the result, row g
+  const void* gain; float eps; FragPlanes norm;   // gain non-null: planes of RMSNorm(result)*gain, row g
+  FragPlanes cat;                             // cat.p non-null: planes of the result, row g (columns 0 .. H-1)
 };
 bool ad_gate_fused_supported(int H, int heads);
 void launch_ad_gate_fused(const AdGateArgs& a, int rows, hipStream_t st);
-// root state/token from the last accepted row, its planes (row b, ld H), aug_len[b] += m[b]
+// root state/token from the last accepted row, its planes in row b of y, aug_len[b] += m[b]
 void launch_draft_root_fused(const float* a, const int* next_tok, const int* m, int B, int R, int H, float* state,
-                             int* tokens, bf16_t* y_hi, bf16_t* y_lo, int* aug_len, hipStream_t st, int Rs = 0);
-// per internal node r of one depth (u = nodes[r]): planes of RMSNorm(state[parent(u)]) * gain (row b*n_lvl + r, ld H),
-// planes of the embedding of tokens[u] in (y_hi, y_lo) (ld H) and in the second half of (c_hi, c_lo) (ld 2H)
+                             int* tokens, FragPlanes y, int* aug_len, hipStream_t st, int Rs = 0);
+// per internal node r of one depth (u = nodes[r]), row b*n_lvl + r: planes of RMSNorm(state[parent(u)]) * gain in a,
+// planes of the embedding of tokens[u] in y and in columns H .. 2H-1 of cat
 void launch_draft_level(const float* state, const int* tokens, const int* nodes, const int* parent, int n_lvl, int B,
-                        int R, int H, const void* table, int vocab, const void* gain, float eps, bf16_t* a_hi,
-                        bf16_t* a_lo, bf16_t* y_hi, bf16_t* y_lo, bf16_t* c_hi, bf16_t* c_lo, hipStream_t st,
-                        int nodes_stride = 0, int parent_stride = 0);
+                        int R, int H, const void* table, int vocab, const void* gain, float eps, FragPlanes a,
+                        FragPlanes y, FragPlanes cat, hipStream_t st, int nodes_stride = 0, int parent_stride = 0);
 
 // ---- dynamic (score-pruned) draft tree ----------------------------------------------------------
 constexpr int DYN_MAX_CAND = 256;    // candidates per sequence, the root included

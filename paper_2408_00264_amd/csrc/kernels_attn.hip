@@ -342,8 +342,7 @@ constexpr int MG_HEADS = 8;   // heads per workgroup (32 threads each)
 constexpr int MG_MAXS = 16;   // >= the largest split count the launcher picks
 __global__ __launch_bounds__(MG_HEADS * 32) void attn_merge_kernel(const float* __restrict__ o_part,
                                                                     const float* __restrict__ ml_part, int n_splits,
-                                                                    int rows_total, int n_q, bf16_t* __restrict__ out_hi,
-                                                                    bf16_t* __restrict__ out_lo, int ldo, RowMap rm) {
+                                                                    int rows_total, int n_q, FragPlanes out, RowMap rm) {
   const int i = blockIdx.x, b = blockIdx.y;
   const int head = blockIdx.z * MG_HEADS + (threadIdx.x >> 5), d4 = (threadIdx.x & 31) * 4;
   const int nv = rm.n_valid ? min(rm.n_valid[b], rm.n) : rm.n;
@@ -370,15 +369,7 @@ __global__ __launch_bounds__(MG_HEADS * 32) void attn_merge_kernel(const float* 
     den += wgt * ml[s].y;
     num.x += wgt * o[s].x; num.y += wgt * o[s].y; num.z += wgt * o[s].z; num.w += wgt * o[s].w;
   }
-  const float v[4] = {num.x / den, num.y / den, num.z / den, num.w / den};
-  unsigned h[4], l[4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    h[r] = a_rn(v[r]);
-    l[r] = a_rn(v[r] - __uint_as_float(h[r] << 16));
-  }
-  *(uint2*)(out_hi + row * ldo + head * AT_D + d4) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
-  *(uint2*)(out_lo + row * ldo + head * AT_D + d4) = make_uint2(l[0] | (l[1] << 16), l[2] | (l[3] << 16));
+  frag_store4(out, (int)row, head * AT_D + d4, num.x / den, num.y / den, num.z / den, num.w / den);
 }
 
 bool attn_mfma_supported(int head_dim, int n_q, int n_kv, int max_seq) {
@@ -399,7 +390,7 @@ static void launch_attn_one(const AttnParams& p, dim3 grid, hipStream_t st) {
   attn_mfma_kernel<G, WM><<<grid, 64 * G * WM, lds, st>>>(p);
 }
 
-void launch_attn_mfma(AttnParams p, int max_total_keys, bf16_t* out_hi, bf16_t* out_lo, int ldo, hipStream_t st) {
+void launch_attn_mfma(AttnParams p, int max_total_keys, FragPlanes out, hipStream_t st) {
   const int g = p.n_q / p.n_kv;
   const int node_groups = (p.rm.n + 31) / 32;
   const int n_tiles = (max_total_keys + AT_TK - 1) / AT_TK;
@@ -424,7 +415,7 @@ void launch_attn_mfma(AttnParams p, int max_total_keys, bf16_t* out_hi, bf16_t* 
     default: launch_attn_one<8, 1>(p, grid, st); break;
   }
   attn_merge_kernel<<<dim3(p.rm.n, p.rm.B, (p.n_q + MG_HEADS - 1) / MG_HEADS), MG_HEADS * 32, 0, st>>>(
-      p.o_part, p.ml_part, p.n_splits, p.rows_total, p.n_q, out_hi, out_lo, ldo, p.rm);
+      p.o_part, p.ml_part, p.n_splits, p.rows_total, p.n_q, out, p.rm);
 }
 
 }  // namespace clv

@@ -4,7 +4,7 @@
 // RMSNorm, the Attention Decoder's three projections and its cosine gate, the per-depth FC and the
 // shared LM head with its ranking.  At one to sixteen rows each of these is launch-bound, so the
 // element-wise steps between two GEMMs are folded into ONE kernel each, and those kernels read the
-// GEMMs' K-slice partial sums (and add the bias) themselves instead of waiting for a reduce pass:
+// GEMMs' partial sums over K ranges (and add the bias) themselves instead of waiting for a reduce pass:
 //
 //   draft_pre      rows of (hidden state, follow-up token)  -> planes of RMSNorm(x)*gain, planes of the embedding
 //   ad_gate_fused  q/k/v partials + biases -> per-head cosine gate, residual; writes the result where the next
@@ -15,15 +15,13 @@
 //   draft_level    per internal node of one tree depth: the parent's state -> normalised planes, the node's token's
 //                  embedding -> planes (AD input and second half of the FC input)
 //
-// Activation planes: hi = bf16(x), lo = bf16(x - hi).  An embedding row is bf16 already: hi = its bits, lo = 0.
+// Activation planes (FragPlanes): hi = bf16(x), lo = bf16(x - hi).  An embedding row is bf16 already: hi = its bits, lo = 0.
 #include "clover_internal.h"
 
 namespace clv {
 
 namespace {
 
-// float -> bf16 (round to nearest even) through the hardware conversion (v_cvt_pk_bf16_f32)
-__device__ __forceinline__ unsigned rn_bf16(float a) { return (unsigned)__builtin_bit_cast(unsigned short, (__bf16)a); }
 __device__ __forceinline__ float bf16f(bf16_t b) { return __uint_as_float((unsigned)b << 16); }
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
@@ -42,16 +40,9 @@ __device__ __forceinline__ float block_sum(float v, float* red) {
   for (int w = 0; w < NW; ++w) t += red[w];
   return t;
 }
-__device__ __forceinline__ void store_planes4(bf16_t* hi, bf16_t* lo, size_t off, float o0, float o1, float o2, float o3) {
-  const unsigned h0 = rn_bf16(o0), h1 = rn_bf16(o1), h2 = rn_bf16(o2), h3 = rn_bf16(o3);
-  const unsigned l0 = rn_bf16(o0 - __uint_as_float(h0 << 16)), l1 = rn_bf16(o1 - __uint_as_float(h1 << 16));
-  const unsigned l2 = rn_bf16(o2 - __uint_as_float(h2 << 16)), l3 = rn_bf16(o3 - __uint_as_float(h3 << 16));
-  *(uint2*)(hi + off) = make_uint2(h0 | (h1 << 16), h2 | (h3 << 16));
-  *(uint2*)(lo + off) = make_uint2(l0 | (l1 << 16), l2 | (l3 << 16));
-}
-// planes of RMSNorm(x[0..H)) * gain at (hi, lo) + off; 256 threads; x is read twice (L1/L2 hit)
+// planes of RMSNorm(x[0..H)) * gain in row `row` of out; 256 threads; x is read twice (L1/L2 hit)
 __device__ __forceinline__ void norm_row_planes(const float* __restrict__ x, const bf16_t* __restrict__ gain, float eps,
-                                                int H, bf16_t* hi, bf16_t* lo, size_t off, float* red) {
+                                                int H, FragPlanes out, int row, float* red) {
   float ss = 0.f;
   for (int c = threadIdx.x * 4; c < H; c += 1024) {
     const float4 v = *(const float4*)(x + c);
@@ -61,16 +52,17 @@ __device__ __forceinline__ void norm_row_planes(const float* __restrict__ x, con
   const float scale = 1.0f / sqrtf(tot / (float)H + eps);
   for (int c = threadIdx.x * 4; c < H; c += 1024) {
     const float4 v = *(const float4*)(x + c);
-    store_planes4(hi, lo, off + c, v.x * scale * bf16f(gain[c]), v.y * scale * bf16f(gain[c + 1]),
-                  v.z * scale * bf16f(gain[c + 2]), v.w * scale * bf16f(gain[c + 3]));
+    frag_store4(out, row, c, v.x * scale * bf16f(gain[c]), v.y * scale * bf16f(gain[c + 1]),
+                v.z * scale * bf16f(gain[c + 2]), v.w * scale * bf16f(gain[c + 3]));
   }
 }
-// planes of one embedding row (bf16 bits): hi = bits, lo = 0
-__device__ __forceinline__ void embed_row_planes(const bf16_t* __restrict__ table, int t, int H, bf16_t* hi, bf16_t* lo,
-                                                 size_t off) {
+// planes of one embedding row (bf16 bits) in columns col0 .. col0 + H - 1: hi = bits, lo = 0
+__device__ __forceinline__ void embed_row_planes(const bf16_t* __restrict__ table, int t, int H, FragPlanes out, int row,
+                                                 int col0) {
   for (int c = threadIdx.x * 4; c < H; c += 1024) {
-    *(uint2*)(hi + off + c) = *(const uint2*)(table + (size_t)t * H + c);
-    *(uint2*)(lo + off + c) = make_uint2(0u, 0u);
+    bf16_t* dst = out.p + frag_at(out, row, col0 + c);
+    *(uint2*)dst = *(const uint2*)(table + (size_t)t * H + c);
+    *(uint2*)(dst + 512) = make_uint2(0u, 0u);
   }
 }
 
@@ -78,16 +70,16 @@ __device__ __forceinline__ void embed_row_planes(const bf16_t* __restrict__ tabl
 __global__ __launch_bounds__(256) void draft_pre_kernel(const float* __restrict__ hid, const int* __restrict__ tok,
                                                         const bf16_t* __restrict__ gain, float eps,
                                                         const bf16_t* __restrict__ table, int vocab, int H, RowMap rm,
-                                                        bf16_t* a_hi, bf16_t* a_lo, bf16_t* y_hi, bf16_t* y_lo) {
+                                                        FragPlanes a, FragPlanes y) {
   __shared__ float red[4];
   const int i = blockIdx.x, b = blockIdx.y;
   const int nv = rm.n_valid ? min(rm.n_valid[b], rm.n) : rm.n;
   if (i >= nv) return;
   const size_t row = (size_t)b * rm.R + i;
-  norm_row_planes(hid + row * H, gain, eps, H, a_hi, a_lo, row * H, red);
+  norm_row_planes(hid + row * H, gain, eps, H, a, (int)row, red);
   int t = tok[row];
   t = t < 0 ? 0 : (t >= vocab ? vocab - 1 : t);
-  embed_row_planes(table, t, H, y_hi, y_lo, row * H);
+  embed_row_planes(table, t, H, y, (int)row, 0);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -107,8 +99,7 @@ struct AdGate {
   const int* m;
   float* out; int ldo;
   const bf16_t* gain; float eps;
-  bf16_t *n_hi, *n_lo;
-  bf16_t *c_hi, *c_lo; int ldc;
+  FragPlanes norm, cat;
 };
 constexpr int AG_MAXS = 8;
 __device__ __forceinline__ float4 ld_bias4(const bf16_t* b, int c) {
@@ -170,7 +161,7 @@ __global__ __launch_bounds__(512) void ad_gate_fused_kernel(AdGate p) {
     if (in) {
       *(float4*)(orow + c) = r;
       ss += r.x * r.x + r.y * r.y + r.z * r.z + r.w * r.w;
-      if (p.c_hi) store_planes4(p.c_hi, p.c_lo, (size_t)g * p.ldc + c, r.x, r.y, r.z, r.w);
+      if (p.cat.p) frag_store4(p.cat, g, c, r.x, r.y, r.z, r.w);
     }
   }
   if (!p.gain) return;
@@ -179,7 +170,7 @@ __global__ __launch_bounds__(512) void ad_gate_fused_kernel(AdGate p) {
   for (int c = threadIdx.x * 4; c < H; c += 2048) {
     const float4 v = *(const float4*)(orow + c);
     const float4 gn = ld_bias4(p.gain, c);
-    store_planes4(p.n_hi, p.n_lo, (size_t)g * H + c, v.x * scale * gn.x, v.y * scale * gn.y, v.z * scale * gn.z, v.w * scale * gn.w);
+    frag_store4(p.norm, g, c, v.x * scale * gn.x, v.y * scale * gn.y, v.z * scale * gn.z, v.w * scale * gn.w);
   }
 }
 
@@ -187,15 +178,14 @@ __global__ __launch_bounds__(512) void ad_gate_fused_kernel(AdGate p) {
 __global__ __launch_bounds__(256) void draft_root_fused_kernel(const float* __restrict__ a, const int* __restrict__ next_tok,
                                                                const int* __restrict__ m, int R, int H,
                                                                float* __restrict__ state, int* __restrict__ tokens,
-                                                               bf16_t* y_hi, bf16_t* y_lo, int* __restrict__ aug_len,
-                                                               int Rs) {
+                                                               FragPlanes y, int* __restrict__ aug_len, int Rs) {
   const int b = blockIdx.x;
   const int mb = min(m[b], R);
   for (int c = threadIdx.x * 4; c < H; c += 1024) {
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
     if (mb >= 1) v = *(const float4*)(a + ((size_t)b * R + mb - 1) * H + c);
     *(float4*)(state + ((size_t)b * Rs) * H + c) = v;
-    store_planes4(y_hi, y_lo, (size_t)b * H + c, v.x, v.y, v.z, v.w);
+    frag_store4(y, b, c, v.x, v.y, v.z, v.w);
   }
   if (threadIdx.x == 0) {
     if (mb >= 1) tokens[(size_t)b * Rs] = next_tok[(size_t)b * R + mb - 1];
@@ -208,26 +198,25 @@ __global__ __launch_bounds__(256) void draft_level_kernel(const float* __restric
                                                           const int* __restrict__ nodes, const int* __restrict__ parent,
                                                           int n_lvl, int R, int H, const bf16_t* __restrict__ table,
                                                           int vocab, const bf16_t* __restrict__ gain, float eps,
-                                                          bf16_t* a_hi, bf16_t* a_lo, bf16_t* y_hi, bf16_t* y_lo,
-                                                          bf16_t* c_hi, bf16_t* c_lo, int nodes_stride,
+                                                          FragPlanes a, FragPlanes y, FragPlanes cat, int nodes_stride,
                                                           int parent_stride) {
   __shared__ float red[4];
   const int r = blockIdx.x, b = blockIdx.y;
   const int u = nodes[(size_t)b * nodes_stride + r], p = parent[(size_t)b * parent_stride + u];
   int t = tokens[(size_t)b * R + u];
   t = t < 0 ? 0 : (t >= vocab ? vocab - 1 : t);
-  const size_t row = (size_t)b * n_lvl + r;
-  norm_row_planes(state + ((size_t)b * R + p) * H, gain, eps, H, a_hi, a_lo, row * H, red);
-  embed_row_planes(table, t, H, y_hi, y_lo, row * H);
-  embed_row_planes(table, t, H, c_hi, c_lo, row * 2 * H + H);
+  const int row = b * n_lvl + r;
+  norm_row_planes(state + ((size_t)b * R + p) * H, gain, eps, H, a, row, red);
+  embed_row_planes(table, t, H, y, row, 0);
+  embed_row_planes(table, t, H, cat, row, H);
 }
 
 }  // namespace
 
 void launch_draft_pre(const float* hid, const int* tok, const void* gain, float eps, const void* table, int vocab, int H,
-                      RowMap rm, bf16_t* a_hi, bf16_t* a_lo, bf16_t* y_hi, bf16_t* y_lo, hipStream_t st) {
+                      RowMap rm, FragPlanes a, FragPlanes y, hipStream_t st) {
   draft_pre_kernel<<<dim3(rm.n, rm.B), 256, 0, st>>>(hid, tok, (const bf16_t*)gain, eps, (const bf16_t*)table, vocab, H,
-                                                     rm, a_hi, a_lo, y_hi, y_lo);
+                                                     rm, a, y);
 }
 
 // a head must span a power-of-two number (<= 64) of four-column lanes
@@ -248,23 +237,22 @@ void launch_ad_gate_fused(const AdGateArgs& a, int rows, hipStream_t st) {
   p.nodes = a.nodes; p.parent = a.parent; p.n_lvl = a.n_lvl; p.R = a.R; p.m = a.m;
   p.nodes_stride = a.nodes_stride; p.parent_stride = a.parent_stride;
   p.out = a.out; p.ldo = a.ldo;
-  p.gain = (const bf16_t*)a.gain; p.eps = a.eps; p.n_hi = a.n_hi; p.n_lo = a.n_lo;
-  p.c_hi = a.c_hi; p.c_lo = a.c_lo; p.ldc = a.ldc;
+  p.gain = (const bf16_t*)a.gain; p.eps = a.eps; p.norm = a.norm;
+  p.cat = a.cat;
   ad_gate_fused_kernel<<<rows, 512, 0, st>>>(p);
 }
 
 void launch_draft_root_fused(const float* a, const int* next_tok, const int* m, int B, int R, int H, float* state,
-                             int* tokens, bf16_t* y_hi, bf16_t* y_lo, int* aug_len, hipStream_t st, int Rs) {
-  draft_root_fused_kernel<<<B, 256, 0, st>>>(a, next_tok, m, R, H, state, tokens, y_hi, y_lo, aug_len, Rs ? Rs : R);
+                             int* tokens, FragPlanes y, int* aug_len, hipStream_t st, int Rs) {
+  draft_root_fused_kernel<<<B, 256, 0, st>>>(a, next_tok, m, R, H, state, tokens, y, aug_len, Rs ? Rs : R);
 }
 
 void launch_draft_level(const float* state, const int* tokens, const int* nodes, const int* parent, int n_lvl, int B,
-                        int R, int H, const void* table, int vocab, const void* gain, float eps, bf16_t* a_hi,
-                        bf16_t* a_lo, bf16_t* y_hi, bf16_t* y_lo, bf16_t* c_hi, bf16_t* c_lo, hipStream_t st,
-                        int nodes_stride, int parent_stride) {
+                        int R, int H, const void* table, int vocab, const void* gain, float eps, FragPlanes a,
+                        FragPlanes y, FragPlanes cat, hipStream_t st, int nodes_stride, int parent_stride) {
   if (n_lvl <= 0) return;
   draft_level_kernel<<<dim3(n_lvl, B), 256, 0, st>>>(state, tokens, nodes, parent, n_lvl, R, H, (const bf16_t*)table, vocab,
-                                                     (const bf16_t*)gain, eps, a_hi, a_lo, y_hi, y_lo, c_hi, c_lo,
+                                                     (const bf16_t*)gain, eps, a, y, cat,
                                                      nodes_stride, parent_stride);
 }
 

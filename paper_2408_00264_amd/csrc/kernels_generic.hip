@@ -335,7 +335,7 @@ template <typename KT>
 __global__ void attn_generic_kernel(const float* __restrict__ q, int ldq, const KT* __restrict__ kc,
                                     const KT* __restrict__ vc, KVLayout kv, const int* __restrict__ base_len,
                                     const unsigned long long* __restrict__ anc, int n_q, float* __restrict__ out,
-                                    int ldo, bf16_t* __restrict__ out_hi, bf16_t* __restrict__ out_lo, RowMap rm,
+                                    int ldo, FragPlanes planes, RowMap rm,
                                     int anc_stride, const int* __restrict__ iv) {
   __shared__ float qs[128];
   __shared__ float ps[64];
@@ -395,15 +395,15 @@ __global__ void attn_generic_kernel(const float* __restrict__ q, int ldq, const 
     }
   }
   const float inv = 1.0f / lrun;
-  if (out_hi) {
-    const float r0 = o0 * inv, r1 = o1 * inv;
-    const bf16_t h0 = f32_to_bf16(r0), h1 = f32_to_bf16(r1);
-    out_hi[row * ldo + h * d + lane] = h0;
-    out_lo[row * ldo + h * d + lane] = f32_to_bf16(r0 - bf16_to_f32(h0));
-    if (d > 64) {
-      out_hi[row * ldo + h * d + 64 + lane] = h1;
-      out_lo[row * ldo + h * d + 64 + lane] = f32_to_bf16(r1 - bf16_to_f32(h1));
-    }
+  if (planes.p) {
+    auto put = [&](int c, float v) {
+      bf16_t* dst = planes.p + frag_at(planes, (int)row, c);
+      const bf16_t hb = f32_to_bf16(v);
+      dst[0] = hb;
+      dst[512] = f32_to_bf16(v - bf16_to_f32(hb));
+    };
+    put(h * d + lane, o0 * inv);
+    if (d > 64) put(h * d + 64 + lane, o1 * inv);
     return;
   }
   out[row * ldo + h * d + lane] = o0 * inv;
@@ -412,14 +412,14 @@ __global__ void attn_generic_kernel(const float* __restrict__ q, int ldq, const 
 
 void launch_attn_generic(const float* q, int ldq, const void* k_cache, const void* v_cache, int kvdtype, KVLayout kv,
                          const int* base_len, const unsigned long long* anc, int n_q, float* out, int ldo,
-                         bf16_t* out_hi, bf16_t* out_lo, RowMap rm, hipStream_t st, int anc_stride, const int* iv) {
+                         FragPlanes planes, RowMap rm, hipStream_t st, int anc_stride, const int* iv) {
   dim3 grid(n_q, rm.n, rm.B);
   if (kvdtype == 0)
     attn_generic_kernel<float><<<grid, 64, 0, st>>>(q, ldq, (const float*)k_cache, (const float*)v_cache, kv, base_len,
-                                                    anc, n_q, out, ldo, out_hi, out_lo, rm, anc_stride, iv);
+                                                    anc, n_q, out, ldo, planes, rm, anc_stride, iv);
   else
     attn_generic_kernel<bf16_t><<<grid, 64, 0, st>>>(q, ldq, (const bf16_t*)k_cache, (const bf16_t*)v_cache, kv,
-                                                     base_len, anc, n_q, out, ldo, out_hi, out_lo, rm, anc_stride, iv);
+                                                     base_len, anc, n_q, out, ldo, planes, rm, anc_stride, iv);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -560,23 +560,14 @@ constexpr int TOPK_EPT = TOPK_CHUNK / 256;
 int topk_chunks(int V) { return (V + TOPK_CHUNK - 1) / TOPK_CHUNK; }
 
 __global__ __launch_bounds__(256) void topk_stage1_kernel(const float* __restrict__ z, int ldz, int V, int k,
-                                                          unsigned long long* __restrict__ cand, int splits,
-                                                          size_t sps) {
+                                                          unsigned long long* __restrict__ cand) {
   __shared__ unsigned long long red[4];
   const int chunk = blockIdx.x, row = blockIdx.y, chunks = gridDim.x;
   unsigned long long key[TOPK_EPT];
 #pragma unroll
   for (int e = 0; e < TOPK_EPT; ++e) {
     const int id = chunk * TOPK_CHUNK + e * 256 + threadIdx.x;
-    float v = 0.f;
-    if (id < V) {
-      float q[8];
-#pragma unroll
-      for (int s = 0; s < 8; ++s) q[s] = s < splits ? z[s * sps + (size_t)row * ldz + id] : 0.f;  // one batch of loads
-#pragma unroll
-      for (int s = 0; s < 8; ++s) v += q[s];  // split order, as the reduce kernel
-      for (int s = 8; s < splits; ++s) v += z[s * sps + (size_t)row * ldz + id];
-    }
+    const float v = id < V ? z[(size_t)row * ldz + id] : 0.f;
     key[e] = id < V ? topk_key(v, id) : 0ull;
   }
   for (int r = 0; r < k; ++r) {
@@ -614,11 +605,10 @@ __global__ __launch_bounds__(256) void topk_stage2_kernel(const unsigned long lo
   }
 }
 
-void launch_topk(const float* z, int ldz, int V, int rows, int k, void* cand, int* out_ids, hipStream_t st, int splits,
-                 size_t split_stride) {
+void launch_topk(const float* z, int ldz, int V, int rows, int k, void* cand, int* out_ids, hipStream_t st) {
   if (rows <= 0) return;
   const int chunks = topk_chunks(V);  // chunks * k <= 2048 is checked at init (vocab <= 262144)
-  topk_stage1_kernel<<<dim3(chunks, rows), 256, 0, st>>>(z, ldz, V, k, (unsigned long long*)cand, splits, split_stride);
+  topk_stage1_kernel<<<dim3(chunks, rows), 256, 0, st>>>(z, ldz, V, k, (unsigned long long*)cand);
   topk_stage2_kernel<<<rows, 256, 0, st>>>((const unsigned long long*)cand, chunks, k, out_ids);
 }
 
@@ -872,19 +862,16 @@ void launch_write_kv(void* k_cache, void* v_cache, int kvdtype, KVLayout kv, int
 // ------------------------------------------------------------------------------------------
 // split-bf16 planes and partial-sum consumers
 // ------------------------------------------------------------------------------------------
-__global__ void split_planes_kernel(const float* __restrict__ x, int ldx, bf16_t* __restrict__ hi,
-                                    bf16_t* __restrict__ lo, int ldo, int K) {
-  const size_t row = blockIdx.y;
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
+__global__ void split_planes_kernel(const float* __restrict__ x, int ldx, FragPlanes out, int K) {
+  const int row = blockIdx.y;
+  const int c = (blockIdx.x * blockDim.x + threadIdx.x) * 4;
   if (c >= K) return;
-  const float v = x[row * ldx + c];
-  const bf16_t h = f32_to_bf16(v);
-  hi[row * ldo + c] = h;
-  lo[row * ldo + c] = f32_to_bf16(v - bf16_to_f32(h));
+  const float4 v = *(const float4*)(x + (size_t)row * ldx + c);
+  frag_store4(out, row, c, v.x, v.y, v.z, v.w);
 }
-void launch_split_planes(const float* x, int ldx, bf16_t* hi, bf16_t* lo, int ldo, int rows, int K, hipStream_t st) {
+void launch_split_planes(const float* x, int ldx, FragPlanes out, int rows, int K, hipStream_t st) {
   if (rows <= 0) return;
-  split_planes_kernel<<<dim3((K + 255) / 256, rows), 256, 0, st>>>(x, ldx, hi, lo, ldo, K);
+  split_planes_kernel<<<dim3((K / 4 + 255) / 256, rows), 256, 0, st>>>(x, ldx, out, K);
 }
 
 template <typename WT>
@@ -910,14 +897,13 @@ void launch_reduce(const float* P, int splits, size_t split_stride, int ldp, con
 }
 
 // one 1024-thread block per row: residual add of the split-K partials (sixteen loads in flight per
-// thread, summed in split order), then RMSNorm written as planes.  A thread keeps its (up to two)
+// thread, summed in split order), then RMSNorm written as planes in fragment order.  A thread keeps its (up to two)
 // float4 of the new row in registers across the block-wide sum of squares; wider rows re-read them.
 template <typename WT>
 __global__ __launch_bounds__(1024) void reduce_add_norm_kernel(float* __restrict__ x, int ldx,
                                                                const float* __restrict__ P, int splits, size_t sps,
                                                                int ldp, const WT* __restrict__ gain, float eps,
-                                                               bf16_t* __restrict__ hi, bf16_t* __restrict__ lo,
-                                                               int ldo, int H, const WT* __restrict__ bias) {
+                                                               FragPlanes out, int H, const WT* __restrict__ bias) {
   __shared__ float red[16];
   const size_t row = blockIdx.x;
   float* xr = x + row * ldx;
@@ -959,15 +945,7 @@ __global__ __launch_bounds__(1024) void reduce_add_norm_kernel(float* __restrict
   for (int w = 0; w < 16; ++w) tot += red[w];
   const float scale = 1.0f / sqrtf(tot / (float)H + eps);
   auto emit = [&](int c, float4 v, float4 g4) {
-    const float o[4] = {v.x * scale * g4.x, v.y * scale * g4.y, v.z * scale * g4.z, v.w * scale * g4.w};
-    bf16_t h[4], l[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      h[r] = f32_to_bf16(o[r]);
-      l[r] = f32_to_bf16(o[r] - bf16_to_f32(h[r]));
-    }
-    *(uint2*)(hi + row * ldo + c) = make_uint2((unsigned)h[0] | ((unsigned)h[1] << 16), (unsigned)h[2] | ((unsigned)h[3] << 16));
-    *(uint2*)(lo + row * ldo + c) = make_uint2((unsigned)l[0] | ((unsigned)l[1] << 16), (unsigned)l[2] | ((unsigned)l[3] << 16));
+    frag_store4(out, (int)row, c, v.x * scale * g4.x, v.y * scale * g4.y, v.z * scale * g4.z, v.w * scale * g4.w);
   };
 #pragma unroll
   for (int it = 0; it < 2; ++it) {
@@ -977,15 +955,15 @@ __global__ __launch_bounds__(1024) void reduce_add_norm_kernel(float* __restrict
   for (int c = c0 + 8192; c < H; c += 4096) emit(c, *(const float4*)(xr + c), gain4(c));  // written by this same thread above
 }
 void launch_reduce_add_norm(float* x, int ldx, const float* P, int splits, size_t split_stride, int ldp,
-                            const void* gain, int wdtype, float eps, bf16_t* hi, bf16_t* lo, int ldo, int rows, int H,
+                            const void* gain, int wdtype, float eps, FragPlanes out, int rows, int H,
                             hipStream_t st, const void* bias) {
   if (rows <= 0) return;
   if (wdtype == 0)
     reduce_add_norm_kernel<float><<<rows, 1024, 0, st>>>(x, ldx, P, splits, split_stride, ldp, (const float*)gain, eps,
-                                                        hi, lo, ldo, H, (const float*)bias);
+                                                        out, H, (const float*)bias);
   else
     reduce_add_norm_kernel<bf16_t><<<rows, 1024, 0, st>>>(x, ldx, P, splits, split_stride, ldp, (const bf16_t*)gain,
-                                                         eps, hi, lo, ldo, H, (const bf16_t*)bias);
+                                                         eps, out, H, (const bf16_t*)bias);
 }
 
 }  // namespace clv
