@@ -478,10 +478,81 @@ __global__ __launch_bounds__(256) void gemm_generic_kernel(const float* __restri
   }
 }
 
+// The same product for launches that give the tiles above no chip to fill: one wavefront per 16 rows x 4 columns, its
+// lanes split K (four adjacent columns each), the 64 sums are exchanged so that every lane ends with one output.  What
+// bounds a 16 x 256 x 256 product in 64 x 64 tiles is a chain of 16 K steps with two barriers and a memory round trip
+// each on 4 workgroups, 36 us; here it is one round trip on 64 wavefronts, ~5 us.
+constexpr int GS_ROWS = 16, GS_COLS = 4;
+__device__ __forceinline__ float4 ldw4(const float* w) { return *(const float4*)w; }
+__device__ __forceinline__ float4 ldw4(const bf16_t* w) {
+  const uint2 u = *(const uint2*)w;
+  return make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xFFFF0000u), __uint_as_float(u.y << 16),
+                     __uint_as_float(u.y & 0xFFFF0000u));
+}
+template <typename WT>
+__global__ __launch_bounds__(64) void gemm_small_kernel(const float* __restrict__ X, int ldx, const WT* __restrict__ W,
+                                                        const WT* __restrict__ bias, float* __restrict__ Y, int ldy,
+                                                        int M, int N, int K, int mode) {
+  const int lane = threadIdx.x, n0 = blockIdx.x * GS_COLS, m0 = blockIdx.y * GS_ROWS;
+  float acc[64];   // [column][row]
+#pragma unroll
+  for (int i = 0; i < 64; ++i) acc[i] = 0.f;
+  for (int k0 = 0; k0 < K; k0 += 256) {
+    const int k = k0 + lane * 4, kc = min(k, K - 4);   // (K % 4 == 0; lanes past K multiply zeros)
+    const bool in = k < K;
+    float4 w[GS_COLS], x[GS_ROWS];
+#pragma unroll
+    for (int c = 0; c < GS_COLS; ++c) w[c] = ldw4(W + (size_t)min(n0 + c, N - 1) * K + kc);
+#pragma unroll
+    for (int r = 0; r < GS_ROWS; ++r) x[r] = *(const float4*)(X + (size_t)min(m0 + r, M - 1) * ldx + kc);
+    if (!in) {
+#pragma unroll
+      for (int c = 0; c < GS_COLS; ++c) w[c] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+      for (int r = 0; r < GS_ROWS; ++r) x[r] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+#pragma unroll
+    for (int c = 0; c < GS_COLS; ++c)
+#pragma unroll
+      for (int r = 0; r < GS_ROWS; ++r) {
+        float a = acc[c * GS_ROWS + r];
+        a += x[r].x * w[c].x; a += x[r].y * w[c].y; a += x[r].z * w[c].z; a += x[r].w * w[c].w;
+        acc[c * GS_ROWS + r] = a;
+      }
+  }
+  // 64 sums over 64 lanes: each step halves the sums a lane holds and pairs it with the lane `o` away
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const bool up = (lane & o) != 0;
+#pragma unroll
+    for (int i = 0; i < o; ++i) {
+      const float keep = up ? acc[i + o] : acc[i], send = up ? acc[i] : acc[i + o];
+      acc[i] = keep + __shfl_xor(send, o, 64);
+    }
+  }
+  const int m = m0 + (lane & 15), n = n0 + (lane >> 4);
+  if (m >= M || n >= N) return;
+  float v = acc[0];
+  if (bias) v += ldf(bias, n);
+  float* y = Y + (size_t)m * ldy + n;
+  *y = mode == 1 ? *y + v : v;
+}
+
 void launch_gemm_generic(const float* X, int ldx, const void* W, const void* bias, int wdtype, float* Y, int ldy,
                          int M, int N, int K, int mode, hipStream_t st) {
   if (M <= 0 || N <= 0) return;
   dim3 grid((N + 63) / 64, (M + 63) / 64);
+  // fewer tiles than compute units: the tile kernel's time is its K chain.  (16-byte loads: rows of X and W must
+  // start on 16 bytes, 8 for bf16 weights.)
+  const size_t walign = wdtype == 0 ? 15 : 7;
+  if (grid.x * grid.y < 256 && K % 4 == 0 && ldx % 4 == 0 && ((uintptr_t)X & 15) == 0 && ((uintptr_t)W & walign) == 0) {
+    dim3 sgrid((N + GS_COLS - 1) / GS_COLS, (M + GS_ROWS - 1) / GS_ROWS);
+    if (wdtype == 0)
+      gemm_small_kernel<float><<<sgrid, 64, 0, st>>>(X, ldx, (const float*)W, (const float*)bias, Y, ldy, M, N, K, mode);
+    else
+      gemm_small_kernel<bf16_t><<<sgrid, 64, 0, st>>>(X, ldx, (const bf16_t*)W, (const bf16_t*)bias, Y, ldy, M, N, K, mode);
+    return;
+  }
   if (wdtype == 0)
     gemm_generic_kernel<float><<<grid, 256, 0, st>>>(X, ldx, (const float*)W, (const float*)bias, Y, ldy, M, N, K, mode);
   else
