@@ -431,7 +431,7 @@ void run_layer(clover_ctx* x, const clover_layer_weights& lw, float* xres, RowMa
     const FragPlanes A = frag_planes(x->a_norm, M), O = frag_planes(x->attn_out, M), Hf = frag_planes(x->h_ffn, M);
     bf16_t* const q_hi = (bf16_t*)x->q_rot;
     bf16_t* const q_lo = q_hi + (size_t)x->max_rows * x->NQD;
-    const int sq = gemm_fast(x, KC_GEMM_QKV, A, lw.wq /* k and v rows behind it */, M, x->QKVN, H);
+    const int sq = gemm_fast(x, KC_GEMM_QKV, A, lw.wq /* q, k and v rows */, M, x->QKVN, H);
     { Scope s(x, KC_ROPE_KV);
       launch_rope_kv_write(x->partial, x->QKVN, sq, (size_t)M * x->QKVN, x->cos_t, x->sin_t, x->q_rot, x->NQD, kc_layer,
                            vc_layer, x->kvdtype, kvl, base_len, c.n_q_heads, rm, x->d_err,
@@ -497,16 +497,43 @@ FragPlanes norm_planes(clover_ctx* x, const float* src, const void* gain, int ro
   return A;
 }
 
+// Can draft_tree take the fused route?  (The gate kernel deals whole heads to its lanes.)
+bool draft_fused_ok(clover_ctx* x) { return x->fast && ad_gate_fused_supported(x->H, x->cfg.ad_heads); }
+
+// Attention Decoder on the fused route: planes A = RMSNorm(x)*norm, Y = y are in place; q and k|v projections leave
+// their partial tiles side by side, the gate kernel does the rest.
+void run_ad_fused(clover_ctx* x, const clover_ad_weights& ad, FragPlanes A, FragPlanes Y, int rows, AdGateArgs g) {
+  const int H = x->H;
+  g.Pq = x->partial; g.sps_q = (size_t)rows * H;
+  g.Sq = gemm_fast(x, KC_GEMM_DRAFT, A, ad.wq, rows, H, H);
+  float* Pkv = x->partial + align256((size_t)g.Sq * rows * H * sizeof(float)) / sizeof(float);
+  g.Pkv = Pkv; g.sps_kv = (size_t)rows * 2 * H;
+  g.Skv = gemm_fast(x, KC_GEMM_DRAFT, Y, ad.wk /* k and v rows */, rows, 2 * H, H, Pkv);
+  g.bq = ad.bq; g.bk = ad.bk; g.bv = ad.bv;
+  g.H = H; g.heads = x->cfg.ad_heads; g.eps = x->cfg.rms_eps;
+  Scope sc(x, KC_AD_GATE);
+  launch_ad_gate_fused(g, rows, x->st);
+}
+
 // Attention Decoder on `rows` contiguous rows: out = x + gate(q(norm(x)), k(y)) * v(y)
 void run_ad(clover_ctx* x, const clover_ad_weights& ad, const float* xin, const float* y, int rows, float* out) {
   const clover_config& c = x->cfg;
   const int H = x->H;
   if (x->fast) {
     const FragPlanes A = norm_planes(x, xin, ad.norm, rows);
-    linear_fast(x, A, ad.wq, ad.bq, x->ad_q, H, rows, H, H);
     const FragPlanes Y = split_to(x, y, H, x->pl_y, rows, H);
-    linear_fast(x, Y, ad.wk, ad.bk, x->ad_k, H, rows, H, H);
-    linear_fast(x, Y, ad.wv, ad.bv, x->ad_v, H, rows, H, H);
+    if (draft_fused_ok(x)) {
+      AdGateArgs g;
+      memset(&g, 0, sizeof(g));
+      g.x = xin; g.ldx = H; g.out = out; g.ldo = H;
+      run_ad_fused(x, ad, A, Y, rows, g);
+      return;
+    }
+    linear_fast(x, A, ad.wq, ad.bq, x->ad_q, H, rows, H, H);
+    const int sp = gemm_fast(x, KC_GEMM_DRAFT, Y, ad.wk /* k and v rows */, rows, 2 * H, H);
+    Scope sc(x, KC_ELTWISE);
+    launch_reduce(x->partial, sp, (size_t)rows * 2 * H, 2 * H, ad.bk, c.dtype, x->ad_k, H, rows, H, 0, x->st);
+    launch_reduce(x->partial + H, sp, (size_t)rows * 2 * H, 2 * H, ad.bv, c.dtype, x->ad_v, H, rows, H, 0, x->st);
   } else {
     { Scope s(x, KC_RMSNORM); launch_rmsnorm(xin, H, ad.norm, c.dtype, c.rms_eps, x->a_norm, H, H, rows, x->st); }
     gemm_generic(x, KC_GEMM_DRAFT, x->a_norm, H, ad.wq, ad.bq, x->ad_q, H, rows, H, H, 0);
@@ -552,24 +579,6 @@ void run_head(clover_ctx* x, const float* g, int rows, int k /* 0: logits only, 
     gemm_generic(x, KC_GEMM_LMHEAD, x->a_norm, H, x->w.lm_head, nullptr, x->z, c.vocab, rows, c.vocab, H, 0);
   }
   if (k > 0) { Scope s(x, KC_TOPK); launch_topk(x->z, c.vocab, c.vocab, rows, k, x->cand, x->topk_ids, x->st); }
-}
-
-// Can draft_tree take the fused route?  (The gate kernel deals whole heads to its lanes.)
-bool draft_fused_ok(clover_ctx* x) { return x->fast && ad_gate_fused_supported(x->H, x->cfg.ad_heads); }
-
-// Attention Decoder on the fused route: planes A = RMSNorm(x)*norm, Y = y are in place; q and k|v projections leave
-// their partial tiles side by side, the gate kernel does the rest.
-void run_ad_fused(clover_ctx* x, const clover_ad_weights& ad, FragPlanes A, FragPlanes Y, int rows, AdGateArgs g) {
-  const int H = x->H;
-  g.Pq = x->partial; g.sps_q = (size_t)rows * H;
-  g.Sq = gemm_fast(x, KC_GEMM_DRAFT, A, ad.wq, rows, H, H);
-  float* Pkv = x->partial + align256((size_t)g.Sq * rows * H * sizeof(float)) / sizeof(float);
-  g.Pkv = Pkv; g.sps_kv = (size_t)rows * 2 * H;
-  g.Skv = gemm_fast(x, KC_GEMM_DRAFT, Y, ad.wk /* v rows behind it */, rows, 2 * H, H, Pkv);
-  g.bq = ad.bq; g.bk = ad.bk; g.bv = ad.bv;
-  g.H = H; g.heads = x->cfg.ad_heads; g.eps = x->cfg.rms_eps;
-  Scope sc(x, KC_AD_GATE);
-  launch_ad_gate_fused(g, rows, x->st);
 }
 
 // test hook: copy the logits of the depth-j internal nodes (rows x vocab in x->z) behind those of the shallower depths
@@ -799,13 +808,24 @@ int clover_init(const clover_config* cfg, const clover_weights* w, const clover_
     // (and, for the LM head, by the draft's embedding gathers)
     char* cur = x->packed;
     auto pack = [&](const void*& w, int N, int K) {
-      launch_pack_weight(w, cur, N, K, x->st);
+      launch_pack_weight(w, cur, N, K, 0, N, x->st);
       w = cur;
       cur += (size_t)N * K * 2;
     };
+    // linears that share their input, as one matrix: every pointer names the whole
+    auto pack_joint = [&](std::initializer_list<std::pair<const void**, int>> parts, int K) {
+      int n_rows = 0, row0 = 0;
+      for (const auto& p : parts) n_rows += p.second;
+      for (const auto& p : parts) {
+        launch_pack_weight(*p.first, cur, p.second, K, row0, n_rows, x->st);
+        *p.first = cur;
+        row0 += p.second;
+      }
+      cur += (size_t)n_rows * K * 2;
+    };
     const int H = x->H, d = cfg->head_dim, F = cfg->ffn;
     auto pack_layer = [&](clover_layer_weights& l) {
-      pack(l.wq, cfg->n_q_heads * d, H); pack(l.wk, cfg->n_kv_heads * d, H); pack(l.wv, cfg->n_kv_heads * d, H);
+      pack_joint({{&l.wq, cfg->n_q_heads * d}, {&l.wk, cfg->n_kv_heads * d}, {&l.wv, cfg->n_kv_heads * d}}, H);
       pack(l.wo, H, x->NQD);
       launch_pack_gate_up(l.w_gate, l.w_up, cur, F, H, x->st);
       l.w_gate = l.w_up = cur;
@@ -816,7 +836,7 @@ int clover_init(const clover_config* cfg, const clover_weights* w, const clover_
     for (auto& l : x->aug) pack_layer(l);
     x->lm_head_pk = x->w.lm_head;
     pack(x->lm_head_pk, cfg->vocab, H);
-    for (clover_ad_weights* a : {&x->w.ad1, &x->w.ad2}) { pack(a->wq, H, H); pack(a->wk, H, H); pack(a->wv, H, H); }
+    for (clover_ad_weights* a : {&x->w.ad1, &x->w.ad2}) { pack(a->wq, H, H); pack_joint({{&a->wk, H}, {&a->wv, H}}, H); }
     pack(x->w.fc0_w, H, H);
     for (int j = 1; j < cfg->draft_depths; ++j) pack(x->fc_w[j], H, 2 * H);
     if ((size_t)(cur - x->packed) > x->packed_bytes) { delete x; return fail(nullptr, CLOVER_E_CAPACITY, "internal: packed weights overflow"); }
@@ -1384,7 +1404,7 @@ int op_gemm_impl(int32_t path, int32_t dtype, const float* X, const void* W, flo
     if (scratch_bytes < o.total) return fail(nullptr, CLOVER_E_CAPACITY, "scratch too small");
     // the weight copy is made once per scratch buffer contents, so repeated calls with the same W measure the GEMM
     // alone (the even paths skip it)
-    if (path & 1) launch_pack_weight(W, scratch, N, K, st);
+    if (path & 1) launch_pack_weight(W, scratch, N, K, 0, N, st);
     TileGemm g;
     memset(&g, 0, sizeof(g));
     g.X = frag_planes((char*)scratch + o.planes, M);

@@ -187,14 +187,17 @@ bool attn_mfma_supported(int head_dim, int n_q, int n_kv, int max_seq);
 void launch_attn_mfma(AttnParams p, int max_total_keys, FragPlanes out, hipStream_t st);
 
 // ---- fragment-major weights and the GEMM that reads them ----------------------------------------
-// [N,K] row-major bf16 -> [N/16][K/32][64 lanes][8]: lane l of tile (nb, kt) holds row nb*16 + l%16,
-// columns kt*32 + (l/16)*8 .. +7: a matrix-instruction operand is one contiguous KB.
-void launch_pack_weight(const void* src, void* dst, int N, int K, hipStream_t st);
+// [N,K] row-major bf16 -> rows row0 .. row0+N-1 of a packed matrix of n_rows rows, [K/32][n_rows/16][64 lanes][8]: lane
+// l of block (kt, nb) holds row nb*16 + l%16, columns kt*32 + (l/16)*8 .. +7, so a matrix-instruction operand is one
+// contiguous KB.  K steps outermost: the workgroups of a launch walk K side by side and so read one contiguous region
+// at a time.  (Row blocks outermost, every workgroup reads at the same offset of its own power-of-two-sized blocks;
+// gate+up at one row 43 -> 40 us, LM head 168 -> 164, 64 rows and more within noise.)
+void launch_pack_weight(const void* src, void* dst, int N, int K, int row0, int n_rows, hipStream_t st);
 // gate and up, each [F,K], as one matrix of 2F rows: block b holds rows 8b .. 8b+7 of the gate, then those of the up
 void launch_pack_gate_up(const void* gate, const void* up, void* dst, int F, int K, hipStream_t st);
 struct TileGemm {
   FragPlanes X;                       // activations [M, K]
-  const bf16_t* W;                    // fragment-major [N, K]; epi 1: gate and up interleaved, [2N, K]
+  const bf16_t* W;                    // packed [N, K]; epi 1: gate and up interleaved, [2N, K]
   float* Y; int ldy;                  // epi 0: fp32 [M, N]; range r of K writes Y + r * split_stride
   FragPlanes out;                     // epi 1: planes of silu(X Wg^T) * (X Wu^T), [M, N]
   int M, N, K;

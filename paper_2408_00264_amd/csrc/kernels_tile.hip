@@ -124,6 +124,8 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(TileGemm p) {
   const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)sm;
   const unsigned lane16 = (unsigned)lane * 16u;
   const size_t xstage = (size_t)p.X.mb * 2048;          // bytes of a 32-column step of all rows
+  const int n_wb = p.N / (EPI == 1 ? 8 : 16);           // weight blocks of 16 rows
+  const size_t wstage = (size_t)n_wb * 1024;            // bytes of a 32-column step of the whole matrix
   const char* xsrc[XL];
   const char* wsrc[WL];
 #pragma unroll
@@ -133,8 +135,8 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(TileGemm p) {
   }
 #pragma unroll
   for (int i = 0; i < WL; ++i) {   // (an odd block count: two wavefronts stage the last block again, same bytes)
-    const int c = min(tile * WF + min(i * 4 + wave, WF - 1), p.N / (EPI == 1 ? 8 : 16) - 1);
-    wsrc[i] = (const char*)(p.W + ((size_t)c * KT + kt0) * 512);
+    const int c = min(tile * WF + min(i * 4 + wave, WF - 1), n_wb - 1);
+    wsrc[i] = (const char*)(p.W + (size_t)kt0 * wstage / 2 + (size_t)c * 512);
   }
   auto issue = [&](auto jc, int s, unsigned buf) __attribute__((always_inline)) {   // load j of stage s into the buffer at byte `buf`
     constexpr int j = decltype(jc)::value;
@@ -142,7 +144,7 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(TileGemm p) {
       stage16<false>(xsrc[j] + (size_t)s * xstage, lane16, lds0 + buf + (unsigned)(j * 4 + wave) * 1024u);
     } else {
       constexpr int i = j - XL;
-      stage16<NT>(wsrc[i] + (size_t)s * 1024, lane16, lds0 + buf + (unsigned)(XF + min(i * 4 + wave, WF - 1)) * 1024u);
+      stage16<NT>(wsrc[i] + (size_t)s * wstage, lane16, lds0 + buf + (unsigned)(XF + min(i * 4 + wave, WF - 1)) * 1024u);
     }
   };
 
@@ -353,28 +355,29 @@ void launch_gemm_tile(const TileGemm& g_in, hipStream_t st) {
 // weights in fragment order, once at init
 // ------------------------------------------------------------------------------------------
 namespace {
-// one 16-byte piece per thread; GU: block b of the packed matrix is 8 rows of src, then the same 8 of src2
+// one 16-byte piece per thread: row block nb of src becomes block nb0 + nb of a matrix of n_wb row blocks;
+// GU: block b of the packed matrix is 8 rows of src, then the same 8 of src2
 template <bool GU>
 __global__ void pack_weight_kernel(const bf16_t* __restrict__ src, const bf16_t* __restrict__ src2, bf16_t* __restrict__ dst,
-                                   size_t pieces, int K) {
+                                   size_t pieces, int K, int nb0, int n_wb) {
   const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= pieces) return;
-  const int lane = (int)(idx & 63), r = lane & 15;
-  const size_t blk = idx >> 6;
-  const int KT = K / 32;
-  const size_t nb = blk / KT;
-  const int k = (int)(blk % KT) * 32 + (lane >> 4) * 8;
+  const int lane = (int)(idx & 63), r = lane & 15, KT = K / 32;
+  const size_t blk = idx >> 6, nb = blk / KT;
+  const int kt = (int)(blk % KT), k = kt * 32 + (lane >> 4) * 8;
   const bf16_t* from = GU ? (r < 8 ? src : src2) + (nb * 8 + (r & 7)) * K : src + (nb * 16 + r) * K;
-  *(u32x4*)(dst + idx * 8) = *(const u32x4*)(from + k);
+  *(u32x4*)(dst + (((size_t)kt * n_wb + nb0 + nb) * 64 + lane) * 8) = *(const u32x4*)(from + k);
 }
 }  // namespace
-void launch_pack_weight(const void* src, void* dst, int N, int K, hipStream_t st) {
+void launch_pack_weight(const void* src, void* dst, int N, int K, int row0, int n_rows, hipStream_t st) {
   const size_t pieces = (size_t)N * K / 8;
-  pack_weight_kernel<false><<<(unsigned)((pieces + 255) / 256), 256, 0, st>>>((const bf16_t*)src, nullptr, (bf16_t*)dst, pieces, K);
+  pack_weight_kernel<false><<<(unsigned)((pieces + 255) / 256), 256, 0, st>>>((const bf16_t*)src, nullptr, (bf16_t*)dst, pieces, K,
+                                                                              row0 / 16, n_rows / 16);
 }
 void launch_pack_gate_up(const void* gate, const void* up, void* dst, int F, int K, hipStream_t st) {
   const size_t pieces = (size_t)2 * F * K / 8;
-  pack_weight_kernel<true><<<(unsigned)((pieces + 255) / 256), 256, 0, st>>>((const bf16_t*)gate, (const bf16_t*)up, (bf16_t*)dst, pieces, K);
+  pack_weight_kernel<true><<<(unsigned)((pieces + 255) / 256), 256, 0, st>>>((const bf16_t*)gate, (const bf16_t*)up, (bf16_t*)dst, pieces, K,
+                                                                             0, F / 8);
 }
 
 }  // namespace clv
