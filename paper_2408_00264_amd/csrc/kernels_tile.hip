@@ -7,7 +7,7 @@
 // matrix instructions per fragment pair), and everywhere the load path of a compute unit, which takes the activations
 // as well as the weights.
 //
-// Shape.  A workgroup of four wavefronts (2 x 2, one per SIMD) owns 32 RB rows x 32 CB columns; a wavefront RB x CB
+// Shape.  A workgroup of four wavefronts (2 x 2, one per SIMD; up to 16 rows 1 x 4) owns 32 RB rows x 32 CB columns; a wavefront RB x CB
 // products of 16 x 16.  Both operands go global -> LDS directly, 32 columns of K per stage, as 1 KB blocks that are
 // contiguous in global memory too (one load instruction each), NBUF stages deep: the loads of stage s + NBUF are issued
 // while stage s is multiplied, ~100 KB in flight per compute unit, which covers an HBM round trip.  The fragments
@@ -81,30 +81,40 @@ __device__ __forceinline__ void wait_barrier() {
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(N) : "memory");
 }
 
+// RB 0: the form for up to 16 rows: one row block, the four wavefronts side by side on its columns, 64 columns of K per
+// stage.  (As RB 1, half of the activation loads would fetch the same row block again: gate+up at one row 40 us of which
+// the weights alone take 36 and the activations 11.)
 template <int RB, int CB>
 struct TileShape {
-  static constexpr int XF = 4 * RB, WF = 2 * CB;       // fragment blocks of a stage: activations (hi, lo), weights
+  static constexpr bool ONE = RB == 0;
+  static constexpr int KS = ONE ? 2 : 1;               // 32-column steps per stage
+  static constexpr int RBT = ONE ? 1 : 2 * RB;         // row blocks of the workgroup
+  static constexpr int RBW = ONE ? 1 : RB;             // row and column blocks of a wavefront
+  static constexpr int CBW = ONE ? CB / 2 : CB;
+  static constexpr int WB = 2 * CB;                    // weight blocks of the workgroup per step
+  static constexpr int XF = KS * RBT * 2, WF = KS * WB;   // fragment blocks of a stage: activations (hi, lo), weights
   static constexpr int STAGE = (XF + WF) * 1024;       // bytes
   static constexpr int NBUF = std::min(6, 160 * 1024 / STAGE);   // (12 for the narrow tiles measured 2 % slower)
   static constexpr int EPI_LD = CB * 32 + 16;          // EPI 1: LDS row stride of the finished planes (bytes)
-  static constexpr int LDS = std::max(NBUF * STAGE, 2 * RB * 32 * EPI_LD);
+  static constexpr int LDS = std::max(NBUF * STAGE, 2 * RBT * 16 * EPI_LD);
 };
 
 template <int RB, int CB, int EPI, bool NT>
 __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(TileGemm p) {
   using T = TileShape<RB, CB>;
-  constexpr int XF = T::XF, WF = T::WF, STAGE = T::STAGE, NBUF = T::NBUF;
-  constexpr int XL = RB, WL = (WF + 3) / 4, L = XL + WL;   // staging loads per wavefront and stage
-  constexpr int NR = 2 * RB + CB;                          // fragments a wavefront reads per stage
-  constexpr int MM = 2 * RB * CB;                          // matrix instructions per wavefront and stage
+  constexpr int XF = T::XF, WF = T::WF, WB = T::WB, STAGE = T::STAGE, NBUF = T::NBUF;
+  constexpr int KS = T::KS, RBT = T::RBT, RBW = T::RBW, CBW = T::CBW;
+  constexpr int XL = XF / 4, WL = (WF + 3) / 4, L = XL + WL;   // staging loads per wavefront and stage
+  constexpr int NRS = 2 * RBW + CBW, NR = KS * NRS;            // fragments a wavefront reads per step and stage
+  constexpr int MMS = 2 * RBW * CBW, MM = KS * MMS;            // matrix instructions per wavefront, step and stage
   static_assert(T::LDS <= 160 * 1024 && (NBUF - 2) * L <= 63, "stage buffers exceed the LDS or the load counter");
   extern __shared__ __attribute__((aligned(16))) char sm[];
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int l16 = lane & 15, g4 = lane >> 4;
-  const int wr = wave & 1, wc = wave >> 1;
+  const int wr = T::ONE ? 0 : wave & 1, wc = T::ONE ? wave : wave >> 1;
   // workgroup id -> (row tile, column tile, K range): ids 8 apart share an XCD (dealt round-robin), so the row tiles
   // of the same columns are neighbours in that XCD's own order and find the weights in its L2
-  const int rt = (p.M + 32 * RB - 1) / (32 * RB);
+  const int rt = (p.M + 16 * RBT - 1) / (16 * RBT);
   int rh = 0, unit = (int)blockIdx.x;
   if (rt > 1) {
     const int xcd = (int)blockIdx.x & 7, j = (int)blockIdx.x >> 3;
@@ -113,9 +123,9 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(TileGemm p) {
   }
   if (unit >= p.n_units) return;   // (grid rounded up to whole XCD rows; uniform over the workgroup)
   const int part = unit % p.k_parts, tile = unit / p.k_parts;
-  const int KT = p.K / TL_KST, NS = KT / p.k_parts;    // stages of this workgroup's K range
-  const int kt0 = part * NS;
-  const int row0 = rh * 32 * RB;
+  const int NS = p.K / (TL_KST * KS) / p.k_parts;      // stages of this workgroup's K range
+  const int kt0 = part * NS * KS;
+  const int row0 = rh * 16 * RBT;
 
   // ---- staging: activation block f of a stage = (row block f / 2, plane f % 2), weight block c = 16 rows of W (epi 1:
   // 8 gate and the 8 up rows of the same F columns, so that a lane pair (l, l + 32) ends up with both factors).  Row
@@ -130,42 +140,42 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(TileGemm p) {
   const char* wsrc[WL];
 #pragma unroll
   for (int j = 0; j < XL; ++j) {
-    const int rblk = min(row0 / 16 + j * 2 + (wave >> 1), p.X.mb - 1);
-    xsrc[j] = (const char*)p.X.p + (size_t)kt0 * xstage + (size_t)rblk * 2048 + (wave & 1) * 1024;
+    const int f = (j * 4 + wave) >> 1, rblk = min(row0 / 16 + f % RBT, p.X.mb - 1);
+    xsrc[j] = (const char*)p.X.p + (size_t)(kt0 + f / RBT) * xstage + (size_t)rblk * 2048 + (wave & 1) * 1024;
   }
 #pragma unroll
   for (int i = 0; i < WL; ++i) {   // (an odd block count: two wavefronts stage the last block again, same bytes)
-    const int c = min(tile * WF + min(i * 4 + wave, WF - 1), n_wb - 1);
-    wsrc[i] = (const char*)(p.W + (size_t)kt0 * wstage / 2 + (size_t)c * 512);
+    const int f = min(i * 4 + wave, WF - 1), c = min(tile * WB + f % WB, n_wb - 1);
+    wsrc[i] = (const char*)p.W + (size_t)(kt0 + f / WB) * wstage + (size_t)c * 1024;
   }
   auto issue = [&](auto jc, int s, unsigned buf) __attribute__((always_inline)) {   // load j of stage s into the buffer at byte `buf`
     constexpr int j = decltype(jc)::value;
     if constexpr (j < XL) {
-      stage16<false>(xsrc[j] + (size_t)s * xstage, lane16, lds0 + buf + (unsigned)(j * 4 + wave) * 1024u);
+      stage16<false>(xsrc[j] + (size_t)s * (KS * xstage), lane16, lds0 + buf + (unsigned)(j * 4 + wave) * 1024u);
     } else {
       constexpr int i = j - XL;
-      stage16<NT>(wsrc[i] + (size_t)s * wstage, lane16, lds0 + buf + (unsigned)(XF + min(i * 4 + wave, WF - 1)) * 1024u);
+      stage16<NT>(wsrc[i] + (size_t)s * (KS * wstage), lane16, lds0 + buf + (unsigned)(XF + min(i * 4 + wave, WF - 1)) * 1024u);
     }
   };
 
-  f32x4 acc[CB][RB];
+  f32x4 acc[CBW][RBW];
 #pragma unroll
-  for (int c = 0; c < CB; ++c)
+  for (int c = 0; c < CBW; ++c)
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb) acc[c][rb] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    for (int rb = 0; rb < RBW; ++rb) acc[c][rb] = (f32x4){0.f, 0.f, 0.f, 0.f};
   asm volatile("s_nop 7" ::: "memory");   // (write of an accumulator register -> matrix instruction, which the compiler does not see)
 
-  Frag fa[NR], fb[NR];   // [2 rb + plane], then [2 RB + column block]
-  const char* const xrd = sm + wr * RB * 2048 + l16 * 64 + ((g4 ^ ((0 - (l16 >> 2)) & 3)) * 16);
-  const char* const wrd = sm + (XF + wc * CB) * 1024 + lane * 16;
+  Frag fa[NR], fb[NR];   // per step: [2 rb + plane], then [2 RBW + column block]
+  const char* const xrd = sm + wr * RBW * 2048 + l16 * 64 + ((g4 ^ ((0 - (l16 >> 2)) & 3)) * 16);
+  const char* const wrd = sm + (XF + wc * CBW) * 1024 + lane * 16;
   auto read1 = [&](Frag (&f)[NR], auto rc, unsigned buf) __attribute__((always_inline)) {
-    constexpr int r = decltype(rc)::value;
-    if constexpr (r < 2 * RB) f[r].u = *(const u32x4*)(xrd + buf + r * 1024);
-    else f[r].u = *(const u32x4*)(wrd + buf + (r - 2 * RB) * 1024);
+    constexpr int k = decltype(rc)::value / NRS, r = decltype(rc)::value % NRS;
+    if constexpr (r < 2 * RBW) f[k * NRS + r].u = *(const u32x4*)(xrd + buf + (k * RBT * 2 + r) * 1024);
+    else f[k * NRS + r].u = *(const u32x4*)(wrd + buf + (k * WB + r - 2 * RBW) * 1024);
   };
   auto mm = [&](const Frag (&f)[NR], auto mc) __attribute__((always_inline)) {   // lo plane first, then hi
-    constexpr int m = decltype(mc)::value, lo = m < RB * CB, rb = (m / CB) % RB, c = m % CB;
-    mfma_acc(acc[c][rb], f[2 * RB + c].v, f[2 * rb + lo].v);
+    constexpr int k = decltype(mc)::value / MMS, m = decltype(mc)::value % MMS, lo = m < RBW * CBW, rb = (m / CBW) % RBW, c = m % CBW;
+    mfma_acc(acc[c][rb], f[k * NRS + 2 * RBW + c].v, f[k * NRS + 2 * rb + lo].v);
   };
 
   // ---- prologue: NBUF stages requested, the fragments of the first one read ----
@@ -213,13 +223,13 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(TileGemm p) {
     // Lanes 0..31 hold the gate, 32..63 the up factors of the same 8 columns: one half-wavefront swap of two row blocks
     // leaves both factors of the first block in the lower lanes and of the second in the upper ones.  The finished
     // planes pass through the LDS so that they leave as whole pieces of the fragment order.
-    constexpr int LD = T::EPI_LD, PLANE = RB * 32 * LD;
+    constexpr int LD = T::EPI_LD, PLANE = RBT * 16 * LD;
     const int up = lane >> 5, cl = (g4 & 1) * 4;
 #pragma unroll
-    for (int c = 0; c < CB; ++c)
+    for (int c = 0; c < CBW; ++c)
 #pragma unroll
-      for (int rb = 0; rb < RB; rb += 2) {
-        const int rb2 = rb + 1 < RB ? rb + 1 : rb;
+      for (int rb = 0; rb < RBW; rb += 2) {
+        const int rb2 = rb + 1 < RBW ? rb + 1 : rb;
         unsigned h[4], l[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -229,8 +239,8 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(TileGemm p) {
           h[r] = t_rn(o);
           l[r] = t_rn(o - __uint_as_float(h[r] << 16));
         }
-        if (rb + up < RB) {
-          char* dst = sm + ((wr * RB + rb + up) * 16 + l16) * LD + ((wc * CB + c) * 8 + cl) * 2;
+        if (rb + up < RBW) {
+          char* dst = sm + ((wr * RBW + rb + up) * 16 + l16) * LD + ((wc * CBW + c) * 8 + cl) * 2;
           *(uint2*)dst = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
           *(uint2*)(dst + PLANE) = make_uint2(l[0] | (l[1] << 16), l[2] | (l[3] << 16));
         }
@@ -238,7 +248,7 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(TileGemm p) {
     __syncthreads();
     // pairs of pieces (8 columns each; 2 CB of them, an even number that starts at an even piece): 16 rows x 32 bytes of
     // a KB block per half wavefront
-    constexpr int PAIRS = CB, RBT = 2 * RB;
+    constexpr int PAIRS = CB;
     for (int i = tid; i < PAIRS * RBT * 64; i += 256) {
       const int q = i & 1, r = (i >> 1) & 15, plane = (i >> 5) & 1, rb = (i >> 6) % RBT, pc = (i >> 6) / RBT * 2 + q;
       const int row = rb * 16 + r, m = row0 + row, col = (tile * 2 * CB + pc) * 8;
@@ -247,13 +257,13 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(TileGemm p) {
     }
   } else {
 #pragma unroll
-    for (int c = 0; c < CB; ++c) {
-      const int blk = tile * WF + wc * CB + c;
+    for (int c = 0; c < CBW; ++c) {
+      const int blk = tile * WB + wc * CBW + c;
       if (blk * 16 >= p.N) continue;
       const int col = blk * 16 + 4 * g4;
 #pragma unroll
-      for (int rb = 0; rb < RB; ++rb) {
-        const int m = row0 + (wr * RB + rb) * 16 + l16;
+      for (int rb = 0; rb < RBW; ++rb) {
+        const int m = row0 + (wr * RBW + rb) * 16 + l16;
         const f32x4 v = acc[c][rb];
         if (m < p.M) *(float4*)(p.Y + part * p.split_stride + (size_t)m * p.ldy + col) = make_float4(v[0], v[1], v[2], v[3]);
       }
@@ -282,8 +292,10 @@ void launch_tile_many(const TileGemm& g, int rb, int cb, int wgs, hipStream_t st
 #undef CLV_TL
 }
 template <int EPI>
-void launch_tile_few(const TileGemm& g, int rb, int cb, int wgs, hipStream_t st) {    // rb 1: cb 4, 6; rb 2: cb 4, 6, 8
-  if (rb == 1 && cb == 4) launch_tile_one<1, 4, EPI, true>(g, wgs, st);
+void launch_tile_few(const TileGemm& g, int rb, int cb, int wgs, hipStream_t st) {    // rb 0, 1: cb 4, 6; rb 2: cb 4, 6, 8
+  if (rb == 0 && cb == 4) launch_tile_one<0, 4, EPI, true>(g, wgs, st);
+  else if (rb == 0) launch_tile_one<0, 6, EPI, true>(g, wgs, st);
+  else if (rb == 1 && cb == 4) launch_tile_one<1, 4, EPI, true>(g, wgs, st);
   else if (rb == 1) launch_tile_one<1, 6, EPI, true>(g, wgs, st);
   else if (cb == 4) launch_tile_one<2, 4, EPI, true>(g, wgs, st);
   else if (cb == 6) launch_tile_one<2, 6, EPI, true>(g, wgs, st);
@@ -303,10 +315,11 @@ struct TilePick { int rb, cb, kp; };
 // kp_fixed > 0 fixes the K ranges.
 TilePick pick_tile(int M, int N, int K, int epi, int kp_fixed) {
   static const int cbs[4] = {4, 6, 7, 8};
+  const bool one = M <= 16;
   M = (M + 31) / 32 * 32;   // the K ranges (and with them the size of the partial tiles) depend on this only
-  const int KT = K / TL_KST, blocks = epi == 1 ? N / 8 : N / 16;
+  const int blocks = epi == 1 ? N / 8 : N / 16;
   const double stream = (double)blocks * 32.0 * K / 2450.0;
-  const int rb_lo = M > 64 ? 3 : M / 32, rb_hi = M > 64 ? 5 : M / 32;
+  const int rb_lo = M > 64 ? 3 : M / 32, rb_hi = M > 64 ? 5 : M / 32, KT = K / TL_KST;
   TilePick best{rb_lo, 4, 1};
   double best_t = 1e30;
   for (int rb = rb_lo; rb <= rb_hi; ++rb)
@@ -324,13 +337,15 @@ TilePick pick_tile(int M, int N, int K, int epi, int kp_fixed) {
         if (t < best_t) { best_t = t; best = TilePick{rb, cb, kp}; }
       }
     }
+  // Up to 16 rows over the whole K: the one-row-block form (gate+up 41 -> 36 us, LM head 165 -> 157 at one row).  Over K
+  // ranges its 64-column stages are too coarse for 8 to 16 of them (QKV 10.9 -> 12.7, Wo and down 13.5 -> 14.0).
+  if (one && best.kp == 1) best.rb = 0;
   return best;
 }
 
 }  // namespace
 
-// N: rows of W (epi 1: the FFN width F)
-bool tile_gemm_supported(int N, int K) { return K % TL_KST == 0 && N % 16 == 0; }
+// N: rows of W (epi 1: the FFN width F), N % 16 == 0, K % 64 == 0
 int tile_gemm_pick_k_parts(int M, int N, int K) { return pick_tile(M, N, K, 0, 0).kp; }
 
 void launch_gemm_tile(const TileGemm& g_in, hipStream_t st) {
@@ -339,7 +354,7 @@ void launch_gemm_tile(const TileGemm& g_in, hipStream_t st) {
   const TilePick t = pick_tile(g.M, g.N, g.K, g.epi, g.k_parts);
   const int blocks = g.epi == 1 ? g.N / 8 : g.N / 16;
   g.n_units = (blocks + 2 * t.cb - 1) / (2 * t.cb) * g.k_parts;
-  const int rt = (g.M + 32 * t.rb - 1) / (32 * t.rb);
+  const int rows = t.rb == 0 ? 16 : 32 * t.rb, rt = (g.M + rows - 1) / rows;
   const int wgs = rt > 1 ? (g.n_units + 7) / 8 * 8 * rt : g.n_units;
   auto go = [&](auto epic) {
     constexpr int EPI = decltype(epic)::value;
