@@ -306,7 +306,7 @@ void carve(clover_ctx* x, char* base, size_t* total) {
   x->topk_ids = cv.take<int>((size_t)rows * 16);
   x->topk_vals = cv.take<float>((size_t)rows * 16);
   x->topk_lse = cv.take<float>((size_t)rows);
-  x->topk_aux = cv.take<float>((size_t)rows * topk_chunks(c.vocab) * 2);
+  x->topk_aux = cv.take<float>(std::max((size_t)rows * topk_chunks(c.vocab), (size_t)B * sample_chunks(c.vocab)) * 2);
   x->dyn.cand_tok = cv.take<int>((size_t)B * DYN_MAX_CAND);
   x->dyn.cand_score = cv.take<float>((size_t)B * DYN_MAX_CAND);
   x->dyn.cand_par = cv.take<int>((size_t)B * DYN_MAX_CAND);

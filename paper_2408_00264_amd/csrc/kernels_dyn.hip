@@ -269,110 +269,181 @@ __global__ __launch_bounds__(DYN_MAX_CAND) void dyn_finalize_kernel(DynTree t, i
   }
 }
 
-// Verification at a temperature > 0 (one 1024-thread workgroup per sequence).  Thread 0 walks the tree: at node u
-// with p = softmax(logits[u] / T), the children are tried in index order, child i accepted when
-// uniforms[u][i] < p(token) / (1 - mass of the children already refused).  When none is accepted (or u is a leaf)
-// the whole workgroup draws the next token from what is left of p (refused tokens removed) by inverting its
-// cumulative sum in token order with uniforms[u][16]; sums are carried in double precision.
-constexpr int SAMPLE_THREADS = 1024;
-__global__ __launch_bounds__(SAMPLE_THREADS) void accept_sample_kernel(
+// Verification at a temperature > 0, in three launches.
+//   walk   one wavefront per sequence: at node u with p = softmax(logits[u] / T), the children (one per lane) are tried
+//          in index order, child i accepted when uniforms[u][i] < p(token) / (1 - mass of the children already refused)
+//   mass   where none is accepted (or u is a leaf) the next token is drawn from what is left of p (refused tokens
+//          removed): its mass per chunk of 2048 tokens, one workgroup each
+//   pick   inverts the cumulative sum in token order with uniforms[u][16]: the chunk first, then the token in it
+// Sums are carried in double precision.  What bounds it is one sequence's row of V exponentials in double precision: a
+// single workgroup that summed the row and searched it took 290 us at V = 128256; spread over 63 workgroups the row
+// is a few us and the search reads one chunk again.
+constexpr int SAMPLE_CHUNK = 2048;   // tokens per chunk, 8 adjacent ones per thread
+__global__ __launch_bounds__(64) void sample_walk_kernel(
     const float* __restrict__ logits, int V, const float* __restrict__ lse, float inv_temp, const int* __restrict__ tokens,
     const int* __restrict__ first_child, const int* __restrict__ n_child, int child_stride, int R,
     const float* __restrict__ uniforms, int* __restrict__ m, int* __restrict__ acc_idx, int* __restrict__ new_tokens,
     int* __restrict__ next_tok) {
-  __shared__ int s_u, s_len, s_nk, s_kid_tok[CLOVER_MAX_RANK], s_pick;
-  __shared__ double s_part[SAMPLE_THREADS / 64], s_total;
-  const int b = blockIdx.x, tid = threadIdx.x;
+  const int b = blockIdx.x, lane = threadIdx.x;
   const size_t o = (size_t)b * R;
   first_child += (size_t)b * child_stride;
   n_child += (size_t)b * child_stride;
-  if (tid == 0) {
-    int u = 0, len = 1;
-    acc_idx[o] = 0;
-    for (;;) {
-      const float* zr = logits + (o + u) * (size_t)V;
-      const float l = lse[o + u];
-      const int c0 = first_child[u], nk = min(n_child[u], CLOVER_MAX_RANK);
-      double refused = 0.0;
-      int accepted = -1;
-      for (int i = 0; i < nk; ++i) {
-        const int x = tokens[o + c0 + i];
-        const double px = (x >= 0 && x < V) ? exp((double)(zr[x] * inv_temp) - (double)l) : 0.0;
-        const double a = px / fmax(1.0 - refused, 1e-300);
-        if ((double)uniforms[(o + u) * 17 + i] < a) { accepted = c0 + i; break; }
-        refused += px;
-      }
-      if (accepted < 0 || len >= R) break;
-      u = accepted;
-      acc_idx[o + len++] = u;
+  int u = 0, len = 1;
+  if (lane == 0) acc_idx[o] = 0;
+  for (;;) {   // (uniform: every lane takes the same decisions)
+    const int c0 = first_child[u], nk = min(n_child[u], CLOVER_MAX_RANK);
+    const double l = (double)lse[o + u];
+    int x = -1;
+    double px = 0.0, un = 1.0;
+    if (lane < nk) {
+      x = tokens[o + c0 + lane];
+      if (x >= 0 && x < V) px = exp((double)(logits[(o + u) * (size_t)V + x] * inv_temp) - l);
+      un = (double)uniforms[(o + u) * 17 + lane];
     }
-    s_u = u; s_len = len;
-    const int nk = min(n_child[u], CLOVER_MAX_RANK);
-    s_nk = nk;
-    for (int i = 0; i < nk; ++i) s_kid_tok[i] = tokens[o + first_child[u] + i];
-    s_pick = V - 1;
+    double refused = 0.0;
+    int accepted = -1;
+    for (int i = 0; i < nk; ++i) {
+      const double pi = __shfl(px, i, 64);
+      if (__shfl(un, i, 64) < pi / fmax(1.0 - refused, 1e-300)) { accepted = i; break; }
+      refused += pi;
+    }
+    if (accepted < 0 || len >= R) break;
+    const int t = __shfl(x, accepted, 64);
+    u = c0 + accepted;
+    if (lane == 0) {
+      acc_idx[o + len] = u;
+      new_tokens[o + len - 1] = t;
+      next_tok[o + len - 1] = t;
+    }
+    ++len;
   }
-  __syncthreads();
-  const int u = s_u, nk = s_nk;
-  const float* zr = logits + (o + u) * (size_t)V;
-  const double l = (double)lse[o + u];
-  // each thread owns a contiguous range of token ids
-  const int per = (V + SAMPLE_THREADS - 1) / SAMPLE_THREADS;
-  const int t0 = tid * per, t1 = min(V, t0 + per);
-  auto rest = [&](int t) -> double {
-    for (int i = 0; i < nk; ++i)
-      if (s_kid_tok[i] == t) return 0.0;
-    return exp((double)(zr[t] * inv_temp) - l);
-  };
-  double mine = 0.0;
-  for (int t = t0; t < t1; ++t) mine += rest(t);
-  // inclusive scan over the threads: wavefront scan, then the wavefront totals
-  double incl = mine;
+  if (lane == 0) m[b] = len;
+}
+
+// what is left of p at the last accepted node of a sequence: p without the node's children
+struct SampleRest {
+  const float* zr;
+  double l;
+  float inv_temp;
+  int nk, kid[CLOVER_MAX_RANK];
+  __device__ __forceinline__ SampleRest(const float* logits, int V, const float* lse, float inv_t, const int* tokens,
+                                        const int* first_child, const int* n_child, size_t o, int u) {
+    zr = logits + (o + u) * (size_t)V;
+    l = (double)lse[o + u];
+    inv_temp = inv_t;
+    nk = min(n_child[u], CLOVER_MAX_RANK);
+    const int c0 = first_child[u];
+#pragma unroll
+    for (int i = 0; i < CLOVER_MAX_RANK; ++i) kid[i] = i < nk ? tokens[o + c0 + i] : -1;
+  }
+  __device__ __forceinline__ double at(int t) const {
+    bool refused = false;
+#pragma unroll
+    for (int i = 0; i < CLOVER_MAX_RANK; ++i) refused = refused || kid[i] == t;
+    return refused ? 0.0 : exp((double)(zr[t] * inv_temp) - l);
+  }
+};
+__device__ __forceinline__ double d_wave_scan(double v) {   // inclusive
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) {
-    const double v = __shfl_up(incl, d, 64);
-    if ((tid & 63) >= d) incl += v;
+    const double w = __shfl_up(v, d, 64);
+    if ((int)(threadIdx.x & 63) >= d) v += w;
   }
-  if ((tid & 63) == 63) s_part[tid >> 6] = incl;
+  return v;
+}
+__global__ __launch_bounds__(256) void sample_mass_kernel(
+    const float* __restrict__ logits, int V, const float* __restrict__ lse, float inv_temp, const int* __restrict__ tokens,
+    const int* __restrict__ first_child, const int* __restrict__ n_child, int child_stride, int R, const int* __restrict__ m,
+    const int* __restrict__ acc_idx, double* __restrict__ mass) {
+  __shared__ double part[4];
+  const int b = blockIdx.y, tid = threadIdx.x;
+  const size_t o = (size_t)b * R;
+  const SampleRest rest(logits, V, lse, inv_temp, tokens, first_child + (size_t)b * child_stride, n_child + (size_t)b * child_stride, o,
+                        acc_idx[o + m[b] - 1]);
+  const int t0 = blockIdx.x * SAMPLE_CHUNK + tid * 8;
+  double mine = 0.0;
+#pragma unroll
+  for (int e = 0; e < 8; ++e)
+    if (t0 + e < V) mine += rest.at(t0 + e);
+  const double incl = d_wave_scan(mine);
+  if ((tid & 63) == 63) part[tid >> 6] = incl;
   __syncthreads();
-  if (tid == 0) {
+  if (tid == 0) mass[(size_t)b * gridDim.x + blockIdx.x] = ((part[0] + part[1]) + part[2]) + part[3];
+}
+__global__ __launch_bounds__(256) void sample_pick_kernel(
+    const float* __restrict__ logits, int V, const float* __restrict__ lse, float inv_temp, const int* __restrict__ tokens,
+    const int* __restrict__ first_child, const int* __restrict__ n_child, int child_stride, int R,
+    const float* __restrict__ uniforms, const int* __restrict__ m, const int* __restrict__ acc_idx,
+    const double* __restrict__ mass, int chunks, int* __restrict__ new_tokens, int* __restrict__ next_tok) {
+  __shared__ double part[4], s_before, s_target;
+  __shared__ int s_chunk, s_pick;
+  const int b = blockIdx.x, tid = threadIdx.x, len = m[b];
+  const size_t o = (size_t)b * R;
+  const int u = acc_idx[o + len - 1];
+  const SampleRest rest(logits, V, lse, inv_temp, tokens, first_child + (size_t)b * child_stride, n_child + (size_t)b * child_stride, o, u);
+  if (tid < 64) {   // the chunk: prefix sums of 64 chunks at a time, in chunk order
+    const double* mb = mass + (size_t)b * chunks;
+    double total = 0.0;
+    for (int c0 = 0; c0 < chunks; c0 += 64) total += __shfl(d_wave_scan(c0 + tid < chunks ? mb[c0 + tid] : 0.0), 63, 64);
+    const double target = (double)uniforms[(o + u) * 17 + 16] * total;
+    if (tid == 0) { s_chunk = -1; s_target = target; s_pick = V - 1; }
     double run = 0.0;
-    for (int w = 0; w < SAMPLE_THREADS / 64; ++w) { const double v = s_part[w]; s_part[w] = run; run += v; }
-    s_total = run;
-  }
-  __syncthreads();
-  const double before = s_part[tid >> 6] + incl - mine;      // mass of all smaller token ids
-  const double target = (double)uniforms[(o + u) * 17 + 16] * s_total;
-  if (mine > 0.0 && before <= target && target < before + mine) {
-    double run = before;
-    int pick = t1 - 1;
-    for (int t = t0; t < t1; ++t) {
-      run += rest(t);
-      if (run > target) { pick = t; break; }
+    for (int c0 = 0; c0 < chunks; c0 += 64) {
+      const double mine = c0 + tid < chunks ? mb[c0 + tid] : 0.0, incl = d_wave_scan(mine);
+      const double before = run + incl - mine;
+      if (mine > 0.0 && before <= target && target < before + mine) { s_chunk = c0 + tid; s_before = before; }   // one lane at most
+      run += __shfl(incl, 63, 64);
     }
-    s_pick = pick;   // exactly one thread's range contains the target
   }
   __syncthreads();
+  const int chunk = s_chunk;
+  if (chunk >= 0) {   // uniform over the workgroup
+    const int t0 = chunk * SAMPLE_CHUNK + tid * 8;
+    double p[8], mine = 0.0;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      p[e] = t0 + e < V ? rest.at(t0 + e) : 0.0;
+      mine += p[e];
+    }
+    const double incl = d_wave_scan(mine);
+    if ((tid & 63) == 63) part[tid >> 6] = incl;
+    if (tid == 0) s_pick = min(V, (chunk + 1) * SAMPLE_CHUNK) - 1;   // (where rounding leaves the target at the chunk's end)
+    __syncthreads();
+    double run = s_before + incl - mine;
+    for (int w = 0; w < (tid >> 6); ++w) run += part[w];
+    const double target = s_target;
+    if (mine > 0.0 && run <= target && target < run + mine) {
+      int pick = min(t0 + 7, V - 1);
+      for (int e = 7; e >= 0; --e) {   // the first token whose running sum exceeds the target
+        double upto = run;
+#pragma unroll
+        for (int f = 0; f < 8; ++f) upto += f <= e ? p[f] : 0.0;
+        if (upto > target) pick = min(t0 + e, V - 1);
+      }
+      s_pick = pick;
+    }
+    __syncthreads();
+  }
   if (tid == 0) {
-    const int len = s_len, bonus = s_pick;
-    for (int j = 1; j < len; ++j) {
-      const int t = tokens[o + acc_idx[o + j]];
-      new_tokens[o + j - 1] = t;
-      next_tok[o + j - 1] = t;
-    }
-    new_tokens[o + len - 1] = bonus;
-    next_tok[o + len - 1] = bonus;
-    m[b] = len;
+    new_tokens[o + len - 1] = s_pick;
+    next_tok[o + len - 1] = s_pick;
   }
 }
 
 }  // namespace
 
+int sample_chunks(int V) { return (V + SAMPLE_CHUNK - 1) / SAMPLE_CHUNK; }
 void launch_accept_sample(const float* logits, int V, const float* lse, float inv_temp, const int* tokens,
                           const int* first_child, const int* n_child, int child_stride, int B, int R,
-                          const float* uniforms, int* m, int* acc_idx, int* new_tokens, int* next_tok, hipStream_t st) {
-  accept_sample_kernel<<<B, SAMPLE_THREADS, 0, st>>>(logits, V, lse, inv_temp, tokens, first_child, n_child, child_stride, R,
-                                                     uniforms, m, acc_idx, new_tokens, next_tok);
+                          const float* uniforms, int* m, int* acc_idx, int* new_tokens, int* next_tok, double* mass,
+                          hipStream_t st) {
+  const int chunks = sample_chunks(V);
+  sample_walk_kernel<<<B, 64, 0, st>>>(logits, V, lse, inv_temp, tokens, first_child, n_child, child_stride, R, uniforms, m, acc_idx,
+                                       new_tokens, next_tok);
+  sample_mass_kernel<<<dim3(chunks, B), 256, 0, st>>>(logits, V, lse, inv_temp, tokens, first_child, n_child, child_stride, R, m,
+                                                      acc_idx, mass);
+  sample_pick_kernel<<<B, 256, 0, st>>>(logits, V, lse, inv_temp, tokens, first_child, n_child, child_stride, R, uniforms, m, acc_idx,
+                                        mass, chunks, new_tokens, next_tok);
 }
 
 void launch_topk_lse(const float* z, int ldz, int V, int rows, int k, void* cand, float* aux, int* out_ids,
