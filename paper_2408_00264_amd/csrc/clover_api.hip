@@ -336,7 +336,7 @@ void carve(clover_ctx* x, char* base, size_t* total) {
     // partial tiles of the largest launch; the q and the k|v projections of an Attention Decoder lie side by side
     std::vector<GemmShape> shapes;
     model_gemm_shapes(c, shapes);
-    for (int M = 32; M < rows + 32; M += 32) {
+    for (int M = 32; M < rows + 32; M += 32) {   // one row count of each class of equal K ranges
       auto bytes = [&](int N, int K) { return (size_t)tile_gemm_pick_k_parts(M, N, K) * std::min(M, rows) * N * sizeof(float); };
       for (const GemmShape& s : shapes) pbytes = std::max(pbytes, bytes(s.N, s.K));
       pbytes = std::max(pbytes, align256(bytes(H, H)) + bytes(2 * H, H));
@@ -702,7 +702,8 @@ int accept_common(clover_ctx* x, int batch, const int* tree_tokens, const float*
       launch_topk_lse(logits, c.vocab, c.vocab, M, 1, x->cand, x->topk_aux, x->topk_ids, x->topk_vals, x->topk_lse, x->st, inv_t); }
     { Scope s(x, KC_ACCEPT);
       launch_accept_sample(logits, c.vocab, x->topk_lse, inv_t, tree_tokens, fc_tab, nc_tab, x->dyn_on ? R : 0, batch, R,
-                           uniforms, m, acc_idx, new_tokens, next_tok, x->st); }
+                           uniforms, m, acc_idx, new_tokens, next_tok,
+                           (double*)x->topk_aux /* read by the launch above, free now */, x->st); }
   } else {
   { Scope s(x, KC_TOPK); launch_topk(logits, c.vocab, c.vocab, M, 1, x->cand, x->topk_ids, x->st); }
   { Scope s(x, KC_ACCEPT);
@@ -945,19 +946,21 @@ int draft_tree(clover_ctx* x, int32_t batch, const float* hid_acc, const int32_t
   const int B = batch, R = x->R, H = x->H, n = std::min(x->m_upper, R);
   for (int b = 0; b < B; ++b)
     if (x->aug_ub[b] + n > c.max_seq) return fail(x, CLOVER_E_CAPACITY, "augmenting-block cache could exceed max_seq");
-  const RowMap rm{B, R, n, m};
-  const int M = (B - 1) * R + n;
+  const bool fused = draft_fused_ok(x);
+  // rows of the accepted tokens: the caller's arrays hold R rows per sequence of which at most n are accepted; the fused
+  // route packs them (16 sequences x 32 nodes: 80 rows instead of 485)
+  const RowMap in{B, R, n, m}, rm{B, fused ? n : R, n, m};
+  const int M = (B - 1) * rm.R + n;
   int aug_bound = 0;
   for (int b = 0; b < B; ++b) aug_bound = std::max(aug_bound, x->aug_ub[b] + n);
-  const bool fused = draft_fused_ok(x);
   if (fused) {
     const FragPlanes A = frag_planes(x->a_norm, M), Y = frag_planes(x->pl_y, M);
     // embeddings of the follow-up tokens come from the LM-head rows; AD1 over (hidden state, embedding)
     { Scope s(x, KC_DRAFT_MISC);
-      launch_draft_pre(hid_acc, next_tok, x->w.ad1.norm, c.rms_eps, x->w.lm_head, c.vocab, H, rm, A, Y, x->st); }
+      launch_draft_pre(hid_acc, next_tok, x->w.ad1.norm, c.rms_eps, x->w.lm_head, c.vocab, H, in, A, Y, x->st); }
     AdGateArgs g;
     memset(&g, 0, sizeof(g));
-    g.x = hid_acc; g.ldx = H; g.out = x->xd; g.ldo = H;
+    g.x = hid_acc; g.ldx = H; g.out = x->xd; g.ldo = H; g.n_lvl = n; g.R = R;
     g.gain = x->aug[0].attn_norm; g.norm = A;   // planes for the Augmenting Block's first layer
     run_ad_fused(x, x->w.ad1, A, Y, M, g);
     { Scope s(x, KC_ROPE_KV); launch_rope_table(x->d_aug_len, nullptr, c.rope_base, c.head_dim, x->cos_t, x->sin_t, rm, x->st); }
@@ -979,7 +982,7 @@ int draft_tree(clover_ctx* x, int32_t batch, const float* hid_acc, const int32_t
     const int Rs = x->dyn_on ? x->dyn.C : R;
     Scope s(x, KC_DRAFT_MISC);
     if (fused) {
-      launch_draft_root_fused(x->xd, next_tok, m, B, R, H, root_state, root_tok, frag_planes(x->pl_y, B), x->d_aug_len, x->st, Rs);
+      launch_draft_root_fused(x->xd, next_tok, m, B, R, n, H, root_state, root_tok, frag_planes(x->pl_y, B), x->d_aug_len, x->st, Rs);
     } else {
       launch_draft_root(x->xd, next_tok, m, B, R, H, x->d_rootx, root_state, root_tok, x->st, Rs);
       launch_add_len(x->d_aug_len, m, B, x->st);

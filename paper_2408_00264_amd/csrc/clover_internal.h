@@ -206,13 +206,13 @@ struct TileGemm {
   int n_units;                        // filled in by launch_gemm_tile: column tiles x K ranges
 };
 constexpr int TILE_MAX_K_PARTS = 8;
-bool tile_gemm_supported(int N, int K);
 // K ranges of a narrow output; the same for all M that round up to the same multiple of 32
 int tile_gemm_pick_k_parts(int M, int N, int K);
 void launch_gemm_tile(const TileGemm& g, hipStream_t st);
 
 // ---- fused bookkeeping kernels of the draft head (MFMA path, bf16 weights) ----------------------
-// planes of RMSNorm(hid[row]) * gain -> a and of the embedding of tok[row] -> y, rows of `rm`
+// planes of RMSNorm(hid[row]) * gain -> a and of the embedding of tok[row] -> y, rows of `rm` in,
+// row b * rm.n + i out
 void launch_draft_pre(const float* hid, const int* tok, const void* gain, float eps, const void* table, int vocab, int H,
                       RowMap rm, FragPlanes a, FragPlanes y, hipStream_t st);
 // Attention-Decoder gate reading the q and (k|v) GEMMs' K-slice partials and adding the biases itself
@@ -222,7 +222,7 @@ struct AdGateArgs {
   const float* Pkv; int Skv; size_t sps_kv;   // [Skv][M][2H]: k columns, then v columns, Skv <= 8
   const void *bq, *bk, *bv;                   // bf16 [H]
   int H, heads;
-  const int *nodes, *parent; int n_lvl, R;    // nodes null: row g -> row g; else g = b*n_lvl + r, u = nodes[r]: row b*R+parent[u] -> row b*R+u
+  const int *nodes, *parent; int n_lvl, R;    // nodes null: row g -> row g, read from row (g / n_lvl)*R + g % n_lvl if n_lvl > 0; else g = b*n_lvl + r, u = nodes[r]: row b*R+parent[u] -> row b*R+u
   int nodes_stride, parent_stride;            // per-sequence strides of nodes / parent (0: shared by all sequences)
   const int* m;                               // with nodes: sequences with m[b] < 1 are skipped (null: none)
   float* out; int ldo;
@@ -231,8 +231,9 @@ struct AdGateArgs {
 };
 bool ad_gate_fused_supported(int H, int heads);
 void launch_ad_gate_fused(const AdGateArgs& a, int rows, hipStream_t st);
-// root state/token from the last accepted row, its planes in row b of y, aug_len[b] += m[b]
-void launch_draft_root_fused(const float* a, const int* next_tok, const int* m, int B, int R, int H, float* state,
+// root state/token from the last accepted row, its planes in row b of y, aug_len[b] += m[b]; R, Ra: rows per
+// sequence of next_tok and of a
+void launch_draft_root_fused(const float* a, const int* next_tok, const int* m, int B, int R, int Ra, int H, float* state,
                              int* tokens, FragPlanes y, int* aug_len, hipStream_t st, int Rs = 0);
 // per internal node r of one depth (u = nodes[r]), row b*n_lvl + r: planes of RMSNorm(state[parent(u)]) * gain in a,
 // planes of the embedding of tokens[u] in y and in columns H .. 2H-1 of cat
@@ -259,8 +260,8 @@ struct DynTree {
 void launch_topk_lse(const float* z, int ldz, int V, int rows, int k, void* cand, float* aux, int* out_ids,
                      float* out_vals, float* out_lse, hipStream_t st, float scale = 1.0f);
 // verification at a temperature > 0: lse[row] = log-sum-exp of logits[row] * inv_temp; uniforms [B][R][17]
-void launch_accept_sample(const float* logits, int V, const float* lse, float inv_temp, const int* tokens,
 int sample_chunks(int V);
+void launch_accept_sample(const float* logits, int V, const float* lse, float inv_temp, const int* tokens,
                           const int* first_child, const int* n_child, int child_stride, int B, int R,
                           const float* uniforms, int* m, int* acc_idx, int* new_tokens, int* next_tok,
                           double* mass /* scratch, B * sample_chunks(V) */, hipStream_t st);

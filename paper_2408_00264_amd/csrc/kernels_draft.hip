@@ -76,10 +76,11 @@ __global__ __launch_bounds__(256) void draft_pre_kernel(const float* __restrict_
   const int nv = rm.n_valid ? min(rm.n_valid[b], rm.n) : rm.n;
   if (i >= nv) return;
   const size_t row = (size_t)b * rm.R + i;
-  norm_row_planes(hid + row * H, gain, eps, H, a, (int)row, red);
+  const int out = b * rm.n + i;
+  norm_row_planes(hid + row * H, gain, eps, H, a, out, red);
   int t = tok[row];
   t = t < 0 ? 0 : (t >= vocab ? vocab - 1 : t);
-  embed_row_planes(table, t, H, y, (int)row, 0);
+  embed_row_planes(table, t, H, y, out, 0);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -116,6 +117,8 @@ __global__ __launch_bounds__(512) void ad_gate_fused_kernel(AdGate p) {
     if (p.m && p.m[b] < 1) return;  // whole block
     xin = (size_t)b * p.R + p.parent[(size_t)b * p.parent_stride + u];
     xout = (size_t)b * p.R + u;
+  } else if (p.n_lvl > 0) {
+    xin = (size_t)(g / p.n_lvl) * p.R + g % p.n_lvl;
   }
   const int H = p.H, lanes_per_head = H / p.heads / 4;  // power of two, <= 64
   const float* xr = p.x + xin * p.ldx;
@@ -176,14 +179,14 @@ __global__ __launch_bounds__(512) void ad_gate_fused_kernel(AdGate p) {
 
 // ------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void draft_root_fused_kernel(const float* __restrict__ a, const int* __restrict__ next_tok,
-                                                               const int* __restrict__ m, int R, int H,
+                                                               const int* __restrict__ m, int R, int Ra, int H,
                                                                float* __restrict__ state, int* __restrict__ tokens,
                                                                FragPlanes y, int* __restrict__ aug_len, int Rs) {
   const int b = blockIdx.x;
-  const int mb = min(m[b], R);
+  const int mb = min(m[b], Ra);
   for (int c = threadIdx.x * 4; c < H; c += 1024) {
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (mb >= 1) v = *(const float4*)(a + ((size_t)b * R + mb - 1) * H + c);
+    if (mb >= 1) v = *(const float4*)(a + ((size_t)b * Ra + mb - 1) * H + c);
     *(float4*)(state + ((size_t)b * Rs) * H + c) = v;
     frag_store4(y, b, c, v.x, v.y, v.z, v.w);
   }
@@ -242,9 +245,9 @@ void launch_ad_gate_fused(const AdGateArgs& a, int rows, hipStream_t st) {
   ad_gate_fused_kernel<<<rows, 512, 0, st>>>(p);
 }
 
-void launch_draft_root_fused(const float* a, const int* next_tok, const int* m, int B, int R, int H, float* state,
+void launch_draft_root_fused(const float* a, const int* next_tok, const int* m, int B, int R, int Ra, int H, float* state,
                              int* tokens, FragPlanes y, int* aug_len, hipStream_t st, int Rs) {
-  draft_root_fused_kernel<<<B, 256, 0, st>>>(a, next_tok, m, R, H, state, tokens, y, aug_len, Rs ? Rs : R);
+  draft_root_fused_kernel<<<B, 256, 0, st>>>(a, next_tok, m, R, Ra, H, state, tokens, y, aug_len, Rs ? Rs : R);
 }
 
 void launch_draft_level(const float* state, const int* tokens, const int* nodes, const int* parent, int n_lvl, int B,
