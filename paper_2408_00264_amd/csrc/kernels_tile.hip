@@ -282,19 +282,22 @@ void launch_tile_one(const TileGemm& g, int wgs, hipStream_t st) {
   gemm_tile_kernel<RB, CB, EPI, NT><<<wgs, 256, lds, st>>>(g);
 }
 template <int EPI, bool NT>
-void launch_tile_many(const TileGemm& g, int rb, int cb, int wgs, hipStream_t st) {   // rb 3..5, cb 4, 6, 7, 8
+void launch_tile_many(const TileGemm& g, int rb, int cb, int wgs, hipStream_t st) {   // rb 3..5, cb 4, 6, 7, 8; rb 3, cb 3
 #define CLV_TL(RB_)                                                   \
   if (cb == 4) launch_tile_one<RB_, 4, EPI, NT>(g, wgs, st);          \
   else if (cb == 6) launch_tile_one<RB_, 6, EPI, NT>(g, wgs, st);     \
   else if (cb == 7) launch_tile_one<RB_, 7, EPI, NT>(g, wgs, st);     \
   else launch_tile_one<RB_, 8, EPI, NT>(g, wgs, st);
-  if (rb == 3) { CLV_TL(3) } else if (rb == 4) { CLV_TL(4) } else { CLV_TL(5) }
+  if (rb == 3 && cb == 3) launch_tile_one<3, 3, EPI, NT>(g, wgs, st);
+  else if (rb == 3) { CLV_TL(3) } else if (rb == 4) { CLV_TL(4) } else { CLV_TL(5) }
 #undef CLV_TL
 }
 template <int EPI>
-void launch_tile_few(const TileGemm& g, int rb, int cb, int wgs, hipStream_t st) {    // rb 0, 1: cb 4, 6; rb 2: cb 4, 6, 8
+void launch_tile_few(const TileGemm& g, int rb, int cb, int wgs, hipStream_t st) {    // rb 0: cb 4, 6; rb 1: cb 3, 4, 6; rb 2: cb 3, 4, 6, 8
   if (rb == 0 && cb == 4) launch_tile_one<0, 4, EPI, true>(g, wgs, st);
   else if (rb == 0) launch_tile_one<0, 6, EPI, true>(g, wgs, st);
+  else if (rb == 1 && cb == 3) launch_tile_one<1, 3, EPI, true>(g, wgs, st);
+  else if (rb == 2 && cb == 3) launch_tile_one<2, 3, EPI, true>(g, wgs, st);
   else if (rb == 1 && cb == 4) launch_tile_one<1, 4, EPI, true>(g, wgs, st);
   else if (rb == 1) launch_tile_one<1, 6, EPI, true>(g, wgs, st);
   else if (cb == 4) launch_tile_one<2, 4, EPI, true>(g, wgs, st);
@@ -314,7 +317,7 @@ struct TilePick { int rb, cb, kp; };
 // round, where 256-column tiles leave 32 compute units idle), 133 rows one row tile of 160, 80 rows one of 96.
 // kp_fixed > 0 fixes the K ranges.
 TilePick pick_tile(int M, int N, int K, int epi, int kp_fixed) {
-  static const int cbs[4] = {4, 6, 7, 8};
+  static const int cbs[5] = {3, 4, 6, 7, 8};
   const bool one = M <= 16;
   M = (M + 31) / 32 * 32;   // the K ranges (and with them the size of the partial tiles) depend on this only
   const int blocks = epi == 1 ? N / 8 : N / 16;
@@ -325,7 +328,7 @@ TilePick pick_tile(int M, int N, int K, int epi, int kp_fixed) {
   for (int rb = rb_lo; rb <= rb_hi; ++rb)
     for (int cb : cbs) {
       // (up to 32 rows a tile of 256 columns is slower than one of 192 however the rounds fall: LM head 176 against 166 us)
-      if ((rb == 1 && cb > 6) || (rb == 2 && cb == 7)) continue;
+      if ((rb == 1 && cb > 6) || (rb == 2 && cb == 7) || (rb > 3 && cb == 3)) continue;
       const int rt = (M + 32 * rb - 1) / (32 * rb), tiles = (blocks + 2 * cb - 1) / (2 * cb);
       const int nbuf = std::min(6, 160 / (4 * rb + 2 * cb));
       const double stage = std::max(std::max(rb * cb * 2 * 19.0, (4 * rb + 2 * cb) * 1024 / 40.0), 4300.0 / nbuf);
@@ -339,7 +342,7 @@ TilePick pick_tile(int M, int N, int K, int epi, int kp_fixed) {
     }
   // Up to 16 rows over the whole K: the one-row-block form (gate+up 41 -> 36 us, LM head 165 -> 157 at one row).  Over K
   // ranges its 64-column stages are too coarse for 8 to 16 of them (QKV 10.9 -> 12.7, Wo and down 13.5 -> 14.0).
-  if (one && best.kp == 1) best.rb = 0;
+  if (one && best.kp == 1 && best.cb != 3) best.rb = 0;
   return best;
 }
 

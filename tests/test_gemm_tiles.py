@@ -14,6 +14,8 @@ CASES = [(7, 1, m, n, k) for m in (1, 16, 17, 32, 33, 64, 65, 96, 97, 128, 129, 
          for n, k in ((16, 128), (1040, 640), (400, 4096))]
 CASES += [(3, 1, m, n, 512) for m in (1, 31, 64, 65, 128) for n in (48, 2064)]
 CASES += [(0, d, m, n, k) for d in (0, 1) for m, n, k in ((1, 1, 4), (17, 5, 260), (16, 257, 256), (33, 1023, 688), (3, 130, 1028))]
+# column counts at which the rule takes tiles of 96 columns (6 blocks of 16 fill more of the chip than 8)
+CASES += [(7, 1, m, 6144, 4096) for m in (33, 64, 80)] + [(3, 1, m, 22016, 512) for m in (23, 64, 96)]
 # 255 tiles of 64 x 64 (the few-output kernel) and 256 (the tiles)
 CASES += [(0, 0, 64, 255 * 64, 64), (0, 0, 64, 256 * 64, 64)]
 
