@@ -121,13 +121,25 @@ __global__ __launch_bounds__(256) void topk_lse_stage2_kernel(const unsigned lon
     const int idx = e * 256 + threadIdx.x;
     key[e] = idx < total ? cand[((size_t)row * chunks + idx / k) * 16 + idx % k] : 0ull;
   }
-  if (threadIdx.x == 0) {
-    float M = -INFINITY;
-    for (int c = 0; c < chunks; ++c) M = fmaxf(M, aux[((size_t)row * chunks + c) * 2]);
-    float S = 0.f;
-    for (int c = 0; c < chunks; ++c) S += aux[((size_t)row * chunks + c) * 2 + 1] * expf(aux[((size_t)row * chunks + c) * 2] - M);
-    out_lse[row] = M + logf(S);
+  // (the terms by all threads into the LDS, their sum in order by one: as a loop over global memory this was the kernel's
+  // 16 us)
+  __shared__ float fred[4], term[256];
+  float M = -INFINITY;
+  for (int c = threadIdx.x; c < chunks; c += 256) M = fmaxf(M, aux[((size_t)row * chunks + c) * 2]);
+  M = d_wave_max(M);
+  if ((threadIdx.x & 63) == 0) fred[threadIdx.x >> 6] = M;
+  __syncthreads();
+  M = fmaxf(fmaxf(fred[0], fred[1]), fmaxf(fred[2], fred[3]));
+  float S = 0.f;
+  for (int c0 = 0; c0 < chunks; c0 += 256) {
+    const int c = c0 + threadIdx.x;
+    if (c < chunks) term[threadIdx.x] = aux[((size_t)row * chunks + c) * 2 + 1] * expf(aux[((size_t)row * chunks + c) * 2] - M);
+    __syncthreads();
+    if (threadIdx.x == 0)
+      for (int i = 0; i < min(256, chunks - c0); ++i) S += term[i];
+    __syncthreads();
   }
+  if (threadIdx.x == 0) out_lse[row] = M + logf(S);
   for (int r = 0; r < k; ++r) {
     unsigned long long best = 0ull;
 #pragma unroll

@@ -653,6 +653,35 @@ __global__ __launch_bounds__(256) void topk_stage1_kernel(const float* __restric
   }
 }
 
+// stage 1 for k = 1 (the target's argmax over every row): one wavefront per chunk, 16-byte loads, the 64-bit key only for
+// the exchange between lanes.  Bound by reading the logits: 256 rows x 128256 are 131 MB, 49 us through the kernel above
+// (16128 workgroups of 8 KB with two barriers each).
+__global__ __launch_bounds__(256) void argmax_stage1_kernel(const float* __restrict__ z, int ldz, int V, int chunks,
+                                                            unsigned long long* __restrict__ cand) {
+  const int lane = threadIdx.x & 63, chunk = blockIdx.x * 4 + (threadIdx.x >> 6), row = blockIdx.y;
+  if (chunk >= chunks) return;
+  const float* zr = z + (size_t)row * ldz;
+  float4 v[TOPK_CHUNK / 256];
+#pragma unroll
+  for (int e = 0; e < TOPK_CHUNK / 256; ++e)   // (V % 4 == 0: a piece is inside or outside as a whole)
+    v[e] = *(const float4*)(zr + min(chunk * TOPK_CHUNK + (e * 64 + lane) * 4, V - 4));
+  unsigned best = 0u;
+  int id = 0;
+#pragma unroll
+  for (int e = 0; e < TOPK_CHUNK / 256; ++e) {
+    const int i0 = chunk * TOPK_CHUNK + (e * 64 + lane) * 4;
+    const float f[4] = {v[e].x, v[e].y, v[e].z, v[e].w};
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const unsigned u = (unsigned)(topk_key(f[r], 0) >> 32);
+      if (i0 < V && u > best) { best = u; id = i0 + r; }   // ids ascend: the smallest of equals stays
+    }
+  }
+  unsigned long long key = best ? ((unsigned long long)best << 32) | (unsigned long long)(0xFFFFFFFFu - (unsigned)id) : 0ull;
+  key = wave_max_u64(key);
+  if (lane == 0) cand[((size_t)row * chunks + chunk) * 16] = key;
+}
+
 __global__ __launch_bounds__(256) void topk_stage2_kernel(const unsigned long long* __restrict__ cand, int chunks,
                                                           int k, int* __restrict__ out_ids) {
   __shared__ unsigned long long red[4];
@@ -679,7 +708,10 @@ __global__ __launch_bounds__(256) void topk_stage2_kernel(const unsigned long lo
 void launch_topk(const float* z, int ldz, int V, int rows, int k, void* cand, int* out_ids, hipStream_t st) {
   if (rows <= 0) return;
   const int chunks = topk_chunks(V);  // chunks * k <= 2048 is checked at init (vocab <= 262144)
-  topk_stage1_kernel<<<dim3(chunks, rows), 256, 0, st>>>(z, ldz, V, k, (unsigned long long*)cand);
+  if (k == 1 && V % 4 == 0 && ldz % 4 == 0 && ((uintptr_t)z & 15) == 0)
+    argmax_stage1_kernel<<<dim3((chunks + 3) / 4, rows), 256, 0, st>>>(z, ldz, V, chunks, (unsigned long long*)cand);
+  else
+    topk_stage1_kernel<<<dim3(chunks, rows), 256, 0, st>>>(z, ldz, V, k, (unsigned long long*)cand);
   topk_stage2_kernel<<<rows, 256, 0, st>>>((const unsigned long long*)cand, chunks, k, out_ids);
 }
 
