@@ -276,11 +276,10 @@ def main():
     kernels = {k: {"ms_per_step": v[0] / K, "launches_per_step": v[1] / K} for k, v in prof.items() if v[1]}
     ver_med = float(np.median(ver))
 
-    # ---- per kernel class: bytes the class has to move per call and what it reached.  Up to 256 rows go through
-    # one launch that streams the weights once (the <= 64-row, the 128-row panel and the 129..256-row tiled kernel);
-    # the class timer brackets the whole call, so a class's rate is against ONE pass over its weights. ----
+    # ---- per kernel class: bytes the class has to move per call and what it reached.  All rows go through one launch
+    # that streams the weights once; the class timer brackets the whole call. ----
     rows = B * N
-    passes = (rows + 255) // 256
+    passes = 1
     lp = layer_params(shape)
     classes = {}
     for name, params in list(lp.items()) + [("gemm_lm_head", shape.vocab * shape.hidden)]:
@@ -300,7 +299,7 @@ def main():
                                      "note": "attention kernel + the merge of its key splits"}
 
     # dominant kernel: the fused gate/up projection (largest weight stream of a layer); one launch = one pass over
-    # both weight matrices for up to 256 rows.  Every product is issued twice (hi and lo activation planes), so the
+    # both weight matrices.  Every product is issued twice (hi and lo activation planes), so the
     # launch sits under the HBM roof up to 2*P_mfma/(4*P_hbm) = 156 rows and under the bf16 MFMA roof above that;
     # the line reports the roof that binds the workload and keeps the other one beside it.
     dom_name = "gemm_gate_up (fused SwiGLU projection, one launch = one pass over both weight matrices)"

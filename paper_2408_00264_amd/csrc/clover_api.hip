@@ -1399,9 +1399,9 @@ int op_gemm_impl(int32_t path, int32_t dtype, const float* X, const void* W, flo
       return fail(nullptr, CLOVER_E_SHAPE, "shape not supported by the MFMA GEMM");
     if (path >= 3 && path != 7) {
       if (M > 128 || K % (M > 64 ? 128 : 256) != 0 || ldy % 4 != 0)
-        return fail(nullptr, CLOVER_E_SHAPE, "shape not supported by the panel GEMM");
+        return fail(nullptr, CLOVER_E_SHAPE, "shape not supported over the whole K");
       if (path >= 5 && !op_gemm_k_range_ok(M, N, K))
-        return fail(nullptr, CLOVER_E_SHAPE, "shape not supported by the K-range panel GEMM");
+        return fail(nullptr, CLOVER_E_SHAPE, "shape not supported over K ranges");
     }
     const OpGemmScratch o = op_gemm_scratch(M, N, K);
     if (scratch_bytes < o.total) return fail(nullptr, CLOVER_E_CAPACITY, "scratch too small");

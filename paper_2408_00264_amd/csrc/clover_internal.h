@@ -215,7 +215,7 @@ void launch_gemm_tile(const TileGemm& g, hipStream_t st);
 // row b * rm.n + i out
 void launch_draft_pre(const float* hid, const int* tok, const void* gain, float eps, const void* table, int vocab, int H,
                       RowMap rm, FragPlanes a, FragPlanes y, hipStream_t st);
-// Attention-Decoder gate reading the q and (k|v) GEMMs' K-slice partials and adding the biases itself
+// Attention-Decoder gate reading the q and (k|v) GEMMs' partial tiles and adding the biases itself
 struct AdGateArgs {
   const float* x; int ldx;                    // residual input rows
   const float* Pq; int Sq; size_t sps_q;      // [Sq][M][H], Sq <= 8
@@ -272,14 +272,11 @@ void launch_dyn_finalize(const DynTree& t, int B, int R, const int* m, int* tree
 
 // ---- tuning knobs -------------------------------------------------------------------------------
 // The shipped library reads no environment variable: every knob is its default.  A build with
-// -DCLOVER_ABLATE (kernel-tuning experiments only) reads CLOVER_<NAME> once per process instead, and only
-// such a build honours the `dbg` fields of the GEMM descriptors (ablations that skip loads or stores).
+// -DCLOVER_ABLATE (kernel-tuning experiments only) reads CLOVER_<NAME> once per process instead.
 #ifdef CLOVER_ABLATE
 int tune_int(const char* name, int dflt);
-#define CLV_DBG(p, bit) ((p).dbg & (bit))
 #else
 inline int tune_int(const char*, int dflt) { return dflt; }
-#define CLV_DBG(p, bit) 0
 #endif
 
 }  // namespace clv
