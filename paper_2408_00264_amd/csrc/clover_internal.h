@@ -54,6 +54,27 @@ __device__ __forceinline__ size_t kv_v_at(const KVLayout& kv, int b, int head, i
 }
 #endif
 
+// ---- staging loads: global -> LDS without a stop in registers -------------------------------------
+#ifdef __HIPCC__
+typedef const __attribute__((address_space(1))) char* gbyte_ptr;
+// 64 lanes x 16 bytes from (uniform base) + (lane offset) to the KB at LDS byte address `dst` (the same for all lanes;
+// the hardware adds lane * 16, lane l's piece lands at dst + 16 l).  The compiler is not told that this writes the LDS:
+// it would wait for every load in flight before each LDS read that follows.  The waits before the barriers are written by
+// hand, and there is no memory clobber (the staged data is read only behind a later barrier, which is a fence for the
+// compiler; a clobber would turn scalar loads around it into vector loads that wait for the staging loads in flight).
+// The no-op is the wait state gfx950 needs between a scalar write of M0 and a load to the LDS that reads it; the compiler
+// places it for its own loads but does not look inside an asm string.  It is one issue slot beside a load of 64 clocks.
+// NT: non-temporal.
+template <bool NT>
+__device__ __forceinline__ void lds_load16(gbyte_ptr base, unsigned lane_off, unsigned dst) {
+  const unsigned m0 = __builtin_amdgcn_readfirstlane(dst);
+  if constexpr (NT)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" : : "s"(m0), "v"(lane_off), "s"(base) : "m0");
+  else
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(m0), "v"(lane_off), "s"(base) : "m0");
+}
+#endif
+
 // ---- GEMM activations in fragment order ---------------------------------------------------------
 // An activation matrix that feeds the MFMA GEMM is kept as two bf16 planes (hi, lo) with hi + lo == x to 16 mantissa
 // bits, stored as the GEMM stages them: [K/32][mb row blocks][hi, lo][16 rows][32 columns], every (row block, plane) of

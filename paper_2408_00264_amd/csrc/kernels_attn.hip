@@ -66,15 +66,6 @@ constexpr int AT_NKB = 2, AT_NVB = 2;         // K and V^T buffers: tile i in bu
 constexpr int AT_LDS_EL = AT_NKB * AT_KSTAGE + AT_NVB * AT_VSTAGE;
 constexpr int AT_MAX_IV = CLOVER_MAX_NODES_INTERVAL;   // interval labels of the tree keys kept in the LDS
 
-// One staging load: 64 lanes x 16 bytes from (uniform base) + (lane offset) in global memory to the KB at `dst` in
-// the LDS (the hardware adds lane * 16 to dst).  dst is the same for all lanes.  (No memory clobber: the staged data is
-// read only behind a later barrier, which is a fence for the compiler, and a clobber would turn the scalar loads of the
-// page table into vector loads that wait for every staging load in flight.)
-__device__ __forceinline__ void lds_dma16(const __attribute__((address_space(1))) char* base, unsigned lane_off,
-                                          unsigned dst /* LDS byte address */) {
-  const unsigned m0 = __builtin_amdgcn_readfirstlane(dst);
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(m0), "v"(lane_off), "s"(base) : "m0");
-}
 // Wait until at most N of this wavefront's vector-memory loads are outstanding (the vmcnt field of s_waitcnt: bits 3:0
 // and 15:14; the other counters are left alone).
 template <int N>
@@ -131,7 +122,6 @@ __global__ __launch_bounds__(64 * G * WM) void attn_mfma_kernel(AttnParams p) {
     }
     return pg;
   };
-  typedef const __attribute__((address_space(1))) char* gbyte_ptr;
   const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)sm;   // LDS byte address of sm
   auto stage_tile = [&](int kbuf, int vbuf, int page) __attribute__((always_inline)) {
     const size_t blk = ((size_t)page * kv.n_kv + kvh) * (size_t)(KV_PAGE * AT_D);   // elements; K and V^T blocks are equal
@@ -140,8 +130,8 @@ __global__ __launch_bounds__(64 * G * WM) void attn_mfma_kernel(AttnParams p) {
       const int f = wave_u * FPW + j, plane = f >> 3;
       const bf16_t* ksrc = p.k_hi + blk + (size_t)plane * p.k_plane + ((f >> 2) & 1) * 4 * AT_D + (f & 3) * 32;
       const bf16_t* vsrc = p.v_hi + blk + (size_t)plane * p.v_plane + (f & 7) * 16 * AT_TK;
-      lds_dma16((gbyte_ptr)ksrc, k_lane, lds0 + 2u * (unsigned)(kbuf * AT_KSTAGE + f * AT_FRAG));
-      lds_dma16((gbyte_ptr)vsrc, v_lane, lds0 + 2u * (unsigned)(AT_NKB * AT_KSTAGE + vbuf * AT_VSTAGE + f * AT_FRAG));
+      lds_load16<false>((gbyte_ptr)ksrc, k_lane, lds0 + 2u * (unsigned)(kbuf * AT_KSTAGE + f * AT_FRAG));
+      lds_load16<false>((gbyte_ptr)vsrc, v_lane, lds0 + 2u * (unsigned)(AT_NKB * AT_KSTAGE + vbuf * AT_VSTAGE + f * AT_FRAG));
     }
   };
   // The first key tile is requested before anything else is waited for (its address needs the page table only:

@@ -61,19 +61,11 @@ __device__ __forceinline__ void mfma_acc(f32x4& acc, const bf16x8& a, const bf16
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
 }
 
-typedef const __attribute__((address_space(1))) char* gbyte_ptr;
-
-// One staging load: 64 lanes x 16 bytes from (uniform base) + (lane offset) to the KB at `dst` in the LDS (lane l's
-// piece lands at dst + 16 l).  The compiler is not told that it writes the LDS; the waits are written by hand.
-// NT: non-temporal, for weights that no other workgroup reads (gate+up at 64 rows 47.0 -> 44.6 us; where row tiles share
-// them it costs: 256 rows 96.5 -> 100).
+// One staging load of a KB.  NT: non-temporal, for weights that no other workgroup reads (gate+up at 64 rows 47.0 ->
+// 44.6 us; where row tiles share them it costs: 256 rows 96.5 -> 100).
 template <bool NT>
 __device__ __forceinline__ void stage16(const char* base, unsigned lane_off, unsigned dst) {
-  const unsigned m0 = __builtin_amdgcn_readfirstlane(dst);
-  if constexpr (NT)
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2 nt" : : "s"(m0), "v"(lane_off), "s"((gbyte_ptr)base) : "m0");
-  else
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(m0), "v"(lane_off), "s"((gbyte_ptr)base) : "m0");
+  lds_load16<NT>((gbyte_ptr)base, lane_off, dst);
 }
 // this wavefront's staging loads but the youngest N have landed and its LDS reads are done; then the workgroup meets
 template <int N>
