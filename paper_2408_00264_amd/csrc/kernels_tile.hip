@@ -155,7 +155,12 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(TileGemm p) {
   for (int c = 0; c < CBW; ++c)
 #pragma unroll
     for (int rb = 0; rb < RBW; ++rb) acc[c][rb] = (f32x4){0.f, 0.f, 0.f, 0.f};
-  asm volatile("s_nop 7" ::: "memory");   // (write of an accumulator register -> matrix instruction, which the compiler does not see)
+  // (the wait states between the write of an accumulator and the first matrix instruction, which the compiler does not see)
+#pragma unroll
+  for (int c = 0; c < CBW; ++c)
+#pragma unroll
+    for (int rb = 0; rb < RBW; ++rb) asm volatile("" : "+a"(acc[c][rb]));
+  asm volatile("s_nop 7" ::: "memory");
 
   Frag fa[NR], fb[NR];   // per step: [2 rb + plane], then [2 RBW + column block]
   const char* const xrd = sm + wr * RBW * 2048 + l16 * 64 + ((g4 ^ ((0 - (l16 >> 2)) & 3)) * 16);
@@ -208,8 +213,13 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(TileGemm p) {
   wait_barrier<0>();   // no load may land in the LDS once it is used for the results, or given back
 
   // (the compiler does not know that the asm statements are matrix instructions, so the wait states between the last
-  // of them and the first read of an accumulator are spelled out: two no-ops of 16 cover the longest one)
-  asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+  // of them and the first read of an accumulator are spelled out: 8 are needed, and the statements that follow the no-op
+  // take every accumulator, so that no read can be moved in front of it)
+  asm volatile("s_nop 15" ::: "memory");
+#pragma unroll
+  for (int c = 0; c < CBW; ++c)
+#pragma unroll
+    for (int rb = 0; rb < RBW; ++rb) asm volatile("" : "+a"(acc[c][rb]));
   // ---- epilogue: lane holds rows rb*16 + l16 of the wavefront's tile, columns 4*g4 .. 4*g4+3 of each block ----
   if (EPI == 1) {
     // Lanes 0..31 hold the gate, 32..63 the up factors of the same 8 columns: one half-wavefront swap of two row blocks

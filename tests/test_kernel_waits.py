@@ -57,3 +57,22 @@ def test_lds_loads_wait_for_their_m0(kernels):
                     break
                 states += wait_states(before)
     assert n > 100, n                                # the GEMM's and the attention's staging loads
+
+
+def test_accumulators_are_read_behind_the_wait(kernels):
+    """The GEMM's matrix instructions are asm statements: 8 wait states (what the compiler places for its own) between the
+    last of them and the first read of an accumulator must come from a no-op, not from whatever was scheduled in between."""
+    n = 0
+    for name, code in kernels.items():
+        if "gemm_tile_kernel" not in name:
+            continue
+        nop = 0
+        for ins in code:
+            if ins.startswith("v_mfma"):
+                nop = 0
+            elif ins.startswith("s_nop"):
+                nop = max(nop, wait_states(ins))
+            elif ins.startswith("v_accvgpr_read"):
+                assert nop >= 8, (name, ins)
+                n += 1
+    assert n > 100, n
