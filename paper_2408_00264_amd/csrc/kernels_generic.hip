@@ -666,7 +666,7 @@ __global__ __launch_bounds__(256) void argmax_stage1_kernel(const float* __restr
   for (int e = 0; e < TOPK_CHUNK / 256; ++e)   // (V % 4 == 0: a piece is inside or outside as a whole)
     v[e] = *(const float4*)(zr + min(chunk * TOPK_CHUNK + (e * 64 + lane) * 4, V - 4));
   unsigned best = 0u;
-  int id = 0;
+  int id = -1;   // none yet: a NaN of all ones has the key 0 and is a value all the same
 #pragma unroll
   for (int e = 0; e < TOPK_CHUNK / 256; ++e) {
     const int i0 = chunk * TOPK_CHUNK + (e * 64 + lane) * 4;
@@ -674,10 +674,10 @@ __global__ __launch_bounds__(256) void argmax_stage1_kernel(const float* __restr
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const unsigned u = (unsigned)(topk_key(f[r], 0) >> 32);
-      if (i0 < V && u > best) { best = u; id = i0 + r; }   // ids ascend: the smallest of equals stays
+      if (i0 < V && (u > best || id < 0)) { best = u; id = i0 + r; }   // ids ascend: the smallest of equals stays
     }
   }
-  unsigned long long key = best ? ((unsigned long long)best << 32) | (unsigned long long)(0xFFFFFFFFu - (unsigned)id) : 0ull;
+  unsigned long long key = id >= 0 ? ((unsigned long long)best << 32) | (unsigned long long)(0xFFFFFFFFu - (unsigned)id) : 0ull;
   key = wave_max_u64(key);
   if (lane == 0) cand[((size_t)row * chunks + chunk) * 16] = key;
 }
