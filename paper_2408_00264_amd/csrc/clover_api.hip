@@ -35,8 +35,9 @@ int op_gemm_impl(int32_t path, int32_t dtype, const float* X, const void* W, flo
 
 // Scratch of clover_op_gemm_static: one copy per GPU, held until the process ends.  In host code the name below is
 // only a handle for hipGetSymbolAddress; every use goes through the per-device address looked up once.
-// (larger than the documented limit by the padding of the activation planes to whole row blocks)
-constexpr size_t kStaticScratch = (size_t)CLOVER_STATIC_SCRATCH_BYTES + (16u << 20);
+// The limit that callers know counts M rows of activations; the array also holds the rows that pad them to a whole row
+// block: at most 15 rows of 4 K bytes, K at most limit / 36 (one row and 16 columns).
+constexpr size_t kStaticScratch = (size_t)CLOVER_STATIC_SCRATCH_BYTES + 15 * 4 * ((size_t)CLOVER_STATIC_SCRATCH_BYTES / 36);
 __device__ __align__(256) unsigned char g_static_scratch[kStaticScratch];
 constexpr int kMaxDevices = 64;
 void* g_static_scratch_ptr[kMaxDevices] = {};
@@ -1332,37 +1333,49 @@ const char* clover_kernel_class_name(int32_t cls) { return (cls >= 0 && cls < KC
 const char* clover_last_error(clover_ctx* x) { return x ? x->err.c_str() : ""; }
 const char* clover_last_global_error(void) { return g_err.c_str(); }
 
-// Operator scratch: [packed weight copy][activation planes][partial tiles].  `rule` is the size that decides what the
-// static variant accepts: whole-number rows and one partial tile per 512 columns of K (up to 64 rows) or per K range of
-// 256-column tiles; the layout below is never larger but for the planes' row blocks, which the array has room for.
-struct OpGemmScratch { size_t planes, partial, total, rule; int kp; };
+// ---- operator entry points ----
+// Their limits belong to the interface and stay fixed; the kernel's own choices (tile, K ranges) vary underneath.
+
+// K ranges of a narrow output with a long K, for the paths that require them: ranges of at least four steps (256 columns,
+// 128 from 65 rows on) of 128-column tiles that fill most of the chip.  0: the shape has none.
+static int op_gemm_k_ranges(int M, int N, int K) {
+  const int st = M > 64 ? 128 : 256, wgs_n = (N / 32 + 3) / 4, NS = K / st;
+  if (M > 128 || K % st != 0 || N % 32 != 0) return 0;
+  int best = 0;
+  for (int d = 1; d <= NS; ++d)
+    if (NS % d == 0 && wgs_n * d <= 256 && NS / d >= 4) best = d;
+  return best > 1 && wgs_n * best >= (M > 64 ? 160 : 224) ? best : 0;
+}
+// Partial tiles [M, N] that the scratch size counts; the kernel never gets more K ranges than this.
+static int op_gemm_counted_parts(int M, int N, int K) {
+  if (M <= 64 && N % 32 == 0) return (K + 511) / 512;
+  int parts = op_gemm_k_ranges(M, N, K);
+  const int tiles = (N + 255) / 256 * (M > 128 ? 2 : 1);
+  for (int d = 1; d <= K / 512; ++d)
+    if (K / 64 % d == 0 && tiles * d <= 256) parts = std::max(parts, d);
+  const int cols = N % 32 == 0 && N >= 8192 ? 128 : 64, steps = K / (M <= 64 ? 128 : M <= 128 ? 64 : 32);
+  int s = 1;
+  while ((N + cols - 1) / cols * s < 256 && s * 8 <= steps && (size_t)s * M * 32 <= (size_t)K * 2) s *= 2;
+  return std::max(parts, s);
+}
+// [packed weight copy][activation planes][partial tiles].  counted: with M rows of planes and the counted partial tiles;
+// total: what the launch uses, whole row blocks of planes and its own K ranges.
+struct OpGemmScratch { size_t planes, partial, total, counted; int kp; };
 static OpGemmScratch op_gemm_scratch(int M, int N, int K) {
   OpGemmScratch o;
-  int parts = M <= 64 ? (K + 511) / 512 : 1;
-  for (int d = 1; M > 64 && d <= K / 512; ++d)
-    if (K / 64 % d == 0 && (N + 255) / 256 * (M > 128 ? 2 : 1) * d <= 256) parts = d;
+  const int parts = op_gemm_counted_parts(M, N, K);
   o.kp = tile_gemm_pick_k_parts(M, N, K);
   if (o.kp > parts) o.kp = 1;
   o.planes = align256((size_t)N * K * 2);
   o.partial = o.planes + align256((size_t)((M + 15) / 16 * 16) * K * 4);
   o.total = 256 + o.partial + align256((size_t)o.kp * M * N * sizeof(float));
-  o.rule = 256 + o.planes + align256((size_t)M * K * 4) + align256((size_t)parts * M * N * sizeof(float));
+  o.counted = 256 + o.planes + align256((size_t)M * K * 4) + align256((size_t)parts * M * N * sizeof(float));
   return o;
 }
 size_t clover_op_gemm_scratch_bytes(int32_t M, int32_t N, int32_t K) {
   if (M < 1 || N < 1 || K < 1 || M > 256 || !mfma_shape_ok(N, K)) return 256;
   const OpGemmScratch o = op_gemm_scratch(M, N, K);
-  return std::max(o.rule, o.total);
-}
-// The K-range paths keep to narrow outputs with a long K: ranges of at least four stages (256 columns, 128 from 65 rows
-// on) of 128-column tiles that fill most of the chip.
-static bool op_gemm_k_range_ok(int M, int N, int K) {
-  const int st = M > 64 ? 128 : 256, wgs_n = (N / 32 + 3) / 4, NS = K / st;
-  if (M > 128 || K % st != 0 || N % 32 != 0) return false;
-  int best = 0;
-  for (int d = 1; d <= NS; ++d)
-    if (NS % d == 0 && wgs_n * d <= 256 && NS / d >= 4) best = d;
-  return best > 1 && wgs_n * best >= (M > 64 ? 160 : 224);
+  return std::max(o.counted, o.total);
 }
 
 int clover_op_gemm(int32_t path, int32_t dtype, const float* X, const void* W, float* Y, int32_t ldy, int32_t M,
@@ -1376,7 +1389,7 @@ int clover_op_gemm_static(int32_t path, int32_t dtype, const float* X, const voi
     return fail(nullptr, CLOVER_E_SHAPE, "clover_op_gemm_static: path must be 0, 1, 3 or 5 (the shared buffer keeps no copy between calls)");
   const bool mfma = M >= 1 && N >= 1 && K >= 1 && M <= 256 && mfma_shape_ok(N, K);
   const OpGemmScratch o = mfma ? op_gemm_scratch(M, N, K) : OpGemmScratch{};
-  if (o.rule > CLOVER_STATIC_SCRATCH_BYTES || o.total > kStaticScratch)
+  if (o.counted > CLOVER_STATIC_SCRATCH_BYTES)
     return fail(nullptr, CLOVER_E_CAPACITY, "clover_op_gemm_static: M, N, K need more than CLOVER_STATIC_SCRATCH_BYTES of scratch");
   void* ptr = nullptr;
   const int rc = static_scratch_ptr(&ptr);
@@ -1400,11 +1413,11 @@ int op_gemm_impl(int32_t path, int32_t dtype, const float* X, const void* W, flo
     if (path >= 3 && path != 7) {
       if (M > 128 || K % (M > 64 ? 128 : 256) != 0 || ldy % 4 != 0)
         return fail(nullptr, CLOVER_E_SHAPE, "shape not supported over the whole K");
-      if (path >= 5 && !op_gemm_k_range_ok(M, N, K))
+      if (path >= 5 && op_gemm_k_ranges(M, N, K) == 0)
         return fail(nullptr, CLOVER_E_SHAPE, "shape not supported over K ranges");
     }
     const OpGemmScratch o = op_gemm_scratch(M, N, K);
-    if (scratch_bytes < o.total) return fail(nullptr, CLOVER_E_CAPACITY, "scratch too small");
+    if (scratch_bytes < std::max(o.counted, o.total)) return fail(nullptr, CLOVER_E_CAPACITY, "scratch too small");
     // the weight copy is made once per scratch buffer contents, so repeated calls with the same W measure the GEMM
     // alone (the even paths skip it)
     if (path & 1) launch_pack_weight(W, scratch, N, K, 0, N, st);

@@ -139,3 +139,33 @@ def test_tuning_builds_never_overwrite_the_shipped_library():
         B.build(defines=("CLOVER_TILE_ABLATE=1",), out="/tmp/x.so")   # macros without --ablate
     with pytest.raises(ValueError):
         B.build(ablate=True, defines=("CLOVER_TILE_ABLATE=1",))
+
+
+# shapes around the limit of clover_op_gemm_static and around its rules: row classes, N % 32, long and short K
+STATIC_ACCEPTED = [
+    (16, 9552, 1664), (5, 8560, 1920), (16, 3984, 3968), (16, 13520, 1152), (1, 432, 38528), (1, 26128, 640), (1, 16, 524288),
+    (1, 16, 900096), (64, 48, 89856), (1, 32, 483584), (6, 119824, 128), (1, 65024, 256), (32, 176, 64000), (65, 21680, 640),
+    (97, 28896, 384), (65, 16, 113024), (230, 28432, 128), (130, 32384, 256), (129, 16, 60032), (300, 4096, 4096), (8, 8, 4096)]
+STATIC_REFUSED = [
+    (65, 848, 15616), (65, 688, 17024), (65, 4736, 2944), (65, 80, 73600), (65, 96, 67456), (256, 208, 22144), (209, 384, 19328),
+    (15, 106160, 128), (16, 7680, 2048), (64, 80, 74368), (24, 128, 89216), (74, 60720, 128), (128, 2560, 4096),
+    (145, 40048, 128), (129, 32512, 256)]
+
+
+@pytest.mark.parametrize("path", [0, 1, 3, 5])
+def test_static_gemm_accepts_what_it_always_accepted(lib, path):
+    """The size limit of the static variant is part of the interface.  (A null operand: what passes the size test is
+    refused behind it, nothing is ever launched.)"""
+    for M, N, K in STATIC_ACCEPTED:
+        rc = lib.clover_op_gemm_static(path, clover.DTYPE_BF16, None, None, None, N, M, N, K, None)
+        assert rc in (clover.E_NULL, clover.E_HIP), (M, N, K, rc)        # (E_HIP: no device)
+    for M, N, K in STATIC_REFUSED:
+        rc = lib.clover_op_gemm_static(path, clover.DTYPE_BF16, None, None, None, N, M, N, K, None)
+        assert rc == clover.E_CAPACITY, (M, N, K, rc)
+
+
+def test_op_gemm_refuses_less_scratch_than_it_names(lib):
+    fake = C.c_void_p(0x10000)                               # never dereferenced: refused on the host
+    for M, N, K in [(16, 3984, 3968), (85, 2720, 1664), (128, 256, 25088), (64, 4096, 4096), (1, 4096, 14336)]:
+        nb = lib.clover_op_gemm_scratch_bytes(M, N, K)
+        assert lib.clover_op_gemm(1, clover.DTYPE_BF16, fake, fake, fake, N, M, N, K, fake, nb - 1, None) == clover.E_CAPACITY

@@ -62,3 +62,19 @@ def test_static_scratch_limits():
     assert b"CLOVER_STATIC_SCRATCH_BYTES" in lib.clover_last_global_error()
     # the copy-reusing paths make no sense on a shared array
     assert lib.clover_op_gemm_static(2, 1, p, p, p, 512, 16, 512, 512, None) == clover.E_SHAPE
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 16, 900096), (16, 9552, 1664), (5, 8560, 1920), (16, 3984, 3968)])
+def test_static_scratch_at_its_limit(M, N, K):
+    """Shapes that the limit just admits; the first one needs the most of the array (15 rows of padding, the longest K)."""
+    import torch
+    assert torch.cuda.is_available()
+    lib = clover.load_library()
+    print(f"static-scratch gemm at its limit: M={M} N={N} K={K}", flush=True)
+    got, ref = _run(lib, torch, True, 1, M, N, K, seed=7)
+    want, _ = _run(lib, torch, False, 1, M, N, K, seed=7)
+    np.testing.assert_array_equal(got, want)
+    # planes: 2^-17 of a term of 0.02 (as above); fp32 sums of up to K / 32 steps in a row: 2^-24 of sums of 0.02 sqrt(K),
+    # sqrt(K / 32) of them
+    tol = 0.02 * np.sqrt(K) * 4 * (4e-5 + 2.0 ** -24 * np.sqrt(K / 32))
+    assert np.abs(got - ref).max() <= tol
