@@ -388,29 +388,38 @@ __global__ __launch_bounds__(256) void sample_pick_kernel(
     const float* __restrict__ uniforms, const int* __restrict__ m, const int* __restrict__ acc_idx,
     const double* __restrict__ mass, int chunks, int* __restrict__ new_tokens, int* __restrict__ next_tok) {
   __shared__ double part[4], s_before, s_target;
-  __shared__ int s_chunk, s_pick;
+  __shared__ int s_chunk, s_first, s_last, s_pick;
   const int b = blockIdx.x, tid = threadIdx.x, len = m[b];
   const size_t o = (size_t)b * R;
   const int u = acc_idx[o + len - 1];
   const SampleRest rest(logits, V, lse, inv_temp, tokens, first_child + (size_t)b * child_stride, n_child + (size_t)b * child_stride, o, u);
+  // At every level the choice is the first of those with mass whose running sum exceeds the target: one chunk, one thread,
+  // one token, whatever the rounding of sums taken in different orders.
   if (tid < 64) {   // the chunk: prefix sums of 64 chunks at a time, in chunk order
     const double* mb = mass + (size_t)b * chunks;
     double total = 0.0;
     for (int c0 = 0; c0 < chunks; c0 += 64) total += __shfl(d_wave_scan(c0 + tid < chunks ? mb[c0 + tid] : 0.0), 63, 64);
     const double target = (double)uniforms[(o + u) * 17 + 16] * total;
-    if (tid == 0) { s_chunk = -1; s_target = target; s_pick = V - 1; }
-    double run = 0.0;
-    for (int c0 = 0; c0 < chunks; c0 += 64) {
+    double run = 0.0, before = 0.0;
+    int chunk = -1;
+    for (int c0 = 0; c0 < chunks && chunk < 0; c0 += 64) {   // (uniform over the wavefront)
       const double mine = c0 + tid < chunks ? mb[c0 + tid] : 0.0, incl = d_wave_scan(mine);
-      const double before = run + incl - mine;
-      if (mine > 0.0 && before <= target && target < before + mine) { s_chunk = c0 + tid; s_before = before; }   // one lane at most
+      const unsigned long long beyond = __ballot(mine > 0.0 && run + incl > target);
+      if (beyond) {
+        const int lane = __ffsll(beyond) - 1;
+        const double upto = __shfl(incl, max(lane - 1, 0), 64);
+        chunk = c0 + lane;
+        before = lane > 0 ? run + upto : run;
+      }
       run += __shfl(incl, 63, 64);
     }
+    if (tid == 0) { s_chunk = chunk; s_before = before; s_target = target; s_first = 256; s_last = 0; s_pick = V - 1; }
   }
   __syncthreads();
   const int chunk = s_chunk;
   if (chunk >= 0) {   // uniform over the workgroup
     const int t0 = chunk * SAMPLE_CHUNK + tid * 8;
+    const double target = s_target;
     double p[8], mine = 0.0;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
@@ -419,20 +428,27 @@ __global__ __launch_bounds__(256) void sample_pick_kernel(
     }
     const double incl = d_wave_scan(mine);
     if ((tid & 63) == 63) part[tid >> 6] = incl;
-    if (tid == 0) s_pick = min(V, (chunk + 1) * SAMPLE_CHUNK) - 1;   // (where rounding leaves the target at the chunk's end)
     __syncthreads();
-    double run = s_before + incl - mine;
+    double run = s_before;
     for (int w = 0; w < (tid >> 6); ++w) run += part[w];
-    const double target = s_target;
-    if (mine > 0.0 && run <= target && target < run + mine) {
-      int pick = min(t0 + 7, V - 1);
-      for (int e = 7; e >= 0; --e) {   // the first token whose running sum exceeds the target
-        double upto = run;
+    if (mine > 0.0) {
+      if (run + incl > target) atomicMin(&s_first, tid);
+      atomicMax(&s_last, tid);
+    }
+    const double upto = __shfl_up(incl, 1, 64);
+    if ((tid & 63) > 0) run += upto;
+    __syncthreads();
+    if (tid == (s_first < 256 ? s_first : s_last)) {   // (the last one where rounding leaves the target at the chunk's end)
+      int pick = -1, last = 0;
 #pragma unroll
-        for (int f = 0; f < 8; ++f) upto += f <= e ? p[f] : 0.0;
-        if (upto > target) pick = min(t0 + e, V - 1);
+      for (int e = 0; e < 8; ++e) {
+        run += p[e];
+        if (p[e] > 0.0) {
+          last = e;
+          if (pick < 0 && run > target) pick = e;
+        }
       }
-      s_pick = pick;
+      s_pick = t0 + (pick >= 0 ? pick : last);
     }
     __syncthreads();
   }

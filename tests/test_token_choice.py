@@ -53,3 +53,38 @@ def test_argmax_of_crafted_rows(V):
     key = np.where(u >> 31, ~u, u | np.uint32(1 << 31))
     np.testing.assert_array_equal(got, key.argmax(1))
     assert g.m.cpu().tolist() == [1] * len(rows)
+
+
+def draw_rows(V):
+    """(tokens and their log-masses, uniform): the draw must land in the middle of a step of the cumulative sum, or, with
+    the uniform 0, on the first token that has any mass, however small beside the rest"""
+    at = lambda t: min(t, V - 1)
+    quarters = [3, at(63 * 2048 + 5), at(64 * 2048 + 7), V - 1]          # chunks 0, 63, 64 and the last one
+    cases = [({t: np.log(0.25) for t in quarters}, u) for u in (0.1, 0.4, 0.6, 0.9, 0.0, 1.0 - 2.0 ** -24)]
+    t = at(2048) if V > 4096 else 0                                      # one chunk: neighbours, another thread, wavefront
+    fifths = [t + d for d in (0, 1, 9, 600, 1023) if t + d < V]
+    cases += [({f: np.log(0.2) for f in fifths}, u) for u in (0.1, 0.3, 0.5, 0.7, 0.9, 0.0, 1.0 - 2.0 ** -24)]
+    for tiny, big in ((0, V - 1), (5, V // 2), (t + 3, t + 700), (t, t + 1), (t + 2, at(t + 130 * 2048))):
+        if tiny < big < V:
+            cases.append(({tiny: -50.0, big: 0.0}, 0.0))                 # the step at the small token holds the target
+            cases.append(({tiny: -50.0, big: 0.0}, 0.5))
+    return cases
+
+
+@pytest.mark.parametrize("V", [1024, 5004, 5003, 128256, 200002, 262144])
+@pytest.mark.parametrize("floor", [-1e4, -np.inf], ids=["finite", "masked"])
+def test_draw_from_crafted_rows(V, floor):
+    cases = draw_rows(V)
+    torch, g = _context(V, len(cases))
+    print(f"draw from {len(cases)} rows, vocabulary {V}", flush=True)
+    rows = np.full((len(cases), V), floor, np.float32)
+    uni = np.zeros((len(cases), 1, 17), np.float32)
+    for i, (mass, u) in enumerate(cases):
+        for t, z in mass.items():
+            rows[i, t] = z
+        uni[i, 0, 16] = u
+    g.logits[:, 0].copy_(torch.from_numpy(rows).cuda())
+    g.accept_and_compact_sampled(len(cases), 1.0, torch.from_numpy(uni).cuda())
+    got = g.new_tokens[:, 0].cpu().numpy().tolist()
+    want = [O.accept_sampled([0], rows[i:i + 1].astype(np.float64), [-1], 1.0, uni[i].astype(np.float64))[1] for i in range(len(cases))]
+    assert got == want, [(c, a, b) for c, a, b in zip(cases, got, want) if a != b]
