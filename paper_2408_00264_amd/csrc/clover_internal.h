@@ -7,6 +7,7 @@
 #include <stddef.h>
 
 #include "../../include/clover.h"
+#include "once_per_device.h"
 
 namespace clv {
 
@@ -107,6 +108,15 @@ __device__ __forceinline__ void frag_store4(const FragPlanes& f, int row, int co
   bf16_t* dst = f.p + frag_at(f, row, col);
   *(uint2*)dst = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
   *(uint2*)(dst + 512) = make_uint2(l[0] | (l[1] << 16), l[2] | (l[3] << 16));
+}
+#endif
+
+#ifdef __HIPCC__
+// raises the limit of a kernel's dynamic LDS, once per device
+inline void allow_dynamic_lds(OncePerDevice& once, const void* kernel, int bytes) {
+  int dev = -1;
+  hipGetDevice(&dev);
+  once(dev, [&] { hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes); });
 }
 #endif
 

@@ -372,11 +372,8 @@ bool attn_mfma_supported(int head_dim, int n_q, int n_kv, int max_seq) {
 template <int G, int WM>
 static void launch_attn_one(const AttnParams& p, dim3 grid, hipStream_t st) {
   constexpr size_t lds = (size_t)AT_LDS_EL * sizeof(bf16_t) + AT_MAX_IV * sizeof(int2);
-  static bool attr_done = false;
-  if (!attr_done) {
-    hipFuncSetAttribute((const void*)attn_mfma_kernel<G, WM>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    attr_done = true;
-  }
+  static OncePerDevice once;
+  allow_dynamic_lds(once, (const void*)attn_mfma_kernel<G, WM>, (int)lds);
   attn_mfma_kernel<G, WM><<<grid, 64 * G * WM, lds, st>>>(p);
 }
 

@@ -276,11 +276,8 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(TileGemm p) {
 template <int RB, int CB, int EPI, bool NT>
 void launch_tile_one(const TileGemm& g, int wgs, hipStream_t st) {
   constexpr int lds = TileShape<RB, CB>::LDS;
-  static bool attr_done = false;
-  if (!attr_done) {
-    hipFuncSetAttribute((const void*)gemm_tile_kernel<RB, CB, EPI, NT>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    attr_done = true;
-  }
+  static OncePerDevice once;
+  allow_dynamic_lds(once, (const void*)gemm_tile_kernel<RB, CB, EPI, NT>, lds);
   gemm_tile_kernel<RB, CB, EPI, NT><<<wgs, 256, lds, st>>>(g);
 }
 template <int EPI, bool NT>

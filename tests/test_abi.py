@@ -169,3 +169,36 @@ def test_op_gemm_refuses_less_scratch_than_it_names(lib):
     for M, N, K in [(16, 3984, 3968), (85, 2720, 1664), (128, 256, 25088), (64, 4096, 4096), (1, 4096, 14336)]:
         nb = lib.clover_op_gemm_scratch_bytes(M, N, K)
         assert lib.clover_op_gemm(1, clover.DTYPE_BF16, fake, fake, fake, N, M, N, K, fake, nb - 1, None) == clover.E_CAPACITY
+
+
+def test_set_up_runs_once_per_device(tmp_path):
+    """The kernels' LDS limits are set per GPU, not per process, and before any thread goes on to launch."""
+    import subprocess
+    src = tmp_path / "once.cpp"
+    src.write_text("""
+#include "once_per_device.h"
+#include <thread>
+#include <vector>
+int main() {
+  static clv::OncePerDevice once;
+  int calls[70] = {};
+  for (int round = 0; round < 3; ++round)
+    for (int d = 0; d < 70; ++d) once(d, [&] { ++calls[d]; });
+  for (int d = 0; d < 70; ++d)
+    if (calls[d] != (d < 64 ? 1 : 3)) return 1;
+  static clv::OncePerDevice other;
+  std::atomic<int> ready{0}, early{0};
+  std::vector<std::thread> t;
+  for (int i = 0; i < 8; ++i)
+    t.emplace_back([&] { other(5, [&] { ready = 1; }); if (!ready) early = 1; });
+  for (auto& x : t) x.join();
+  return early ? 2 : 0;
+}
+""")
+    exe = tmp_path / "once"
+    subprocess.run(["g++", "-std=c++17", "-O1", "-pthread", "-I", os.path.join(ROOT, "paper_2408_00264_amd", "csrc"), str(src),
+                    "-o", str(exe)], check=True)
+    assert subprocess.run([str(exe)]).returncode == 0
+    # and every kernel that asks for more goes through it
+    for f in ("kernels_tile.hip", "kernels_attn.hip", "kernels_generic.hip", "kernels_dyn.hip", "kernels_draft.hip"):
+        assert "hipFuncSetAttribute" not in open(os.path.join(ROOT, "paper_2408_00264_amd", "csrc", f)).read(), f
