@@ -316,6 +316,23 @@ int clover_op_gemm(int32_t path, int32_t dtype, const float *X, const void *W, f
 int clover_op_gemm_static(int32_t path, int32_t dtype, const float *X, const void *W, float *Y, int32_t ldy,
                           int32_t M, int32_t N, int32_t K, void *hip_stream);
 
+/* The SwiGLU projection: out = planes of silu(X Wg^T) * (X Wu^T), X[M,K] fp32, Wg and Wu [F,K] bf16 row-major,
+ * F % 32 == 0, K % 128 == 0, M <= 1024 (CLOVER_E_SHAPE otherwise).  `planes` dev, ceil(M / 16) * 16 * F * 4 bytes: the
+ * activation format of the GEMM, hi and lo bf16 planes (value = hi + lo) in the order
+ * [F/32][row block of 16][hi, lo][16 rows][32 columns], where the 8-column piece c of row r stands at position
+ * c ^ (-(r / 4) & 3) of its row.  Rows past M are not written.
+ * `scratch` dev, >= clover_op_swiglu_scratch_bytes(M,F,K). */
+size_t clover_op_swiglu_scratch_bytes(int32_t M, int32_t F, int32_t K);
+int clover_op_swiglu(const float *X, const void *Wg, const void *Wu, void *planes, int32_t M, int32_t F, int32_t K,
+                     void *scratch, size_t scratch_bytes, void *hip_stream);
+
+/* Host only: the form of the MFMA GEMM that a launch takes.  form[0]: 0 = one row block, four wavefronts side by side, else
+ * RB (a workgroup owns 32 RB rows); form[1]: CB (32 CB columns); form[2]: row tiles; form[3]: ranges of K; form[4]: stages
+ * per range.  epi 0: Y[M,N] over k_parts ranges of K, or over those that clover_op_gemm sums (k_parts 0; more than 256 rows:
+ * those that a model's pass sums); epi 1: clover_op_swiglu with N = F.  CLOVER_E_SHAPE unless N % 16 == 0, K % 128 == 0 and
+ * k_parts is a count the kernel takes. */
+int clover_op_gemm_form(int32_t epi, int32_t M, int32_t N, int32_t K, int32_t k_parts, int32_t form[5]);
+
 #ifdef __cplusplus
 }
 #endif

@@ -1397,6 +1397,40 @@ int clover_op_gemm_static(int32_t path, int32_t dtype, const float* X, const voi
   return op_gemm_impl(path, dtype, X, W, Y, ldy, M, N, K, ptr, kStaticScratch, hip_stream);
 }
 
+size_t clover_op_swiglu_scratch_bytes(int32_t M, int32_t F, int32_t K) {
+  if (M < 1 || F < 1 || K < 1) return 256;
+  return 256 + align256((size_t)2 * F * K * 2) + align256((size_t)((M + 15) / 16 * 16) * K * 4);
+}
+int clover_op_swiglu(const float* X, const void* Wg, const void* Wu, void* planes, int32_t M, int32_t F, int32_t K,
+                     void* scratch, size_t scratch_bytes, void* hip_stream) {
+  if (!X || !Wg || !Wu || !planes || !scratch) return fail(nullptr, CLOVER_E_NULL, "null argument");
+  if (M < 1 || M > 1024 || F < 1 || K < 1 || F % 32 != 0 || !mfma_shape_ok(F, K)) return fail(nullptr, CLOVER_E_SHAPE, "shape not supported by the MFMA GEMM");
+  if (scratch_bytes < clover_op_swiglu_scratch_bytes(M, F, K)) return fail(nullptr, CLOVER_E_CAPACITY, "scratch too small");
+  hipStream_t st = (hipStream_t)hip_stream;
+  launch_pack_gate_up(Wg, Wu, scratch, F, K, st);
+  TileGemm g;
+  memset(&g, 0, sizeof(g));
+  g.X = frag_planes((char*)scratch + align256((size_t)2 * F * K * 2), M);
+  launch_split_planes(X, K, g.X, M, K, st);
+  g.W = (const bf16_t*)scratch;
+  g.out = frag_planes(planes, M);
+  g.M = M; g.N = F; g.K = K; g.epi = 1; g.k_parts = 1;
+  launch_gemm_tile(g, st);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return fail(nullptr, CLOVER_E_HIP, hipGetErrorString(e));
+  return CLOVER_OK;
+}
+
+int clover_op_gemm_form(int32_t epi, int32_t M, int32_t N, int32_t K, int32_t k_parts, int32_t form[5]) {
+  if (!form) return fail(nullptr, CLOVER_E_NULL, "null argument");
+  if (epi < 0 || epi > 1 || M < 1 || N < 1 || K < 1 || !mfma_shape_ok(N, K) || k_parts < 0 || k_parts > TILE_MAX_K_PARTS ||
+      (k_parts > 0 && K / 32 % k_parts != 0) || (epi == 1 && k_parts > 1))
+    return fail(nullptr, CLOVER_E_SHAPE, "shape not supported by the MFMA GEMM");
+  const TileForm f = tile_gemm_form(M, N, K, epi, k_parts == 0 && epi == 0 && M <= 256 ? op_gemm_scratch(M, N, K).kp : k_parts);
+  form[0] = f.rb; form[1] = f.cb; form[2] = f.row_tiles; form[3] = f.k_parts; form[4] = f.stages;
+  return CLOVER_OK;
+}
+
 }  // extern "C"
 
 namespace {

@@ -240,6 +240,9 @@ constexpr int TILE_MAX_K_PARTS = 8;
 // K ranges of a narrow output; the same for all M that round up to the same multiple of 32
 int tile_gemm_pick_k_parts(int M, int N, int K);
 void launch_gemm_tile(const TileGemm& g, hipStream_t st);
+// what launch_gemm_tile runs for M rows (N = F for epi 1; k_parts 0: its own choice)
+struct TileForm { int rb, cb, row_tiles, k_parts, stages; };
+TileForm tile_gemm_form(int M, int N, int K, int epi, int k_parts);
 
 // ---- fused bookkeeping kernels of the draft head (MFMA path, bf16 weights) ----------------------
 // planes of RMSNorm(hid[row]) * gain -> a and of the embedding of tok[row] -> y, rows of `rm` in,

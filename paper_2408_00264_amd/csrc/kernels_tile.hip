@@ -350,13 +350,18 @@ TilePick pick_tile(int M, int N, int K, int epi, int kp_fixed) {
 // N: rows of W (epi 1: the FFN width F), N % 16 == 0, K % 64 == 0
 int tile_gemm_pick_k_parts(int M, int N, int K) { return pick_tile(M, N, K, 0, 0).kp; }
 
+TileForm tile_gemm_form(int M, int N, int K, int epi, int k_parts) {
+  const TilePick t = pick_tile(M, N, K, epi, epi == 1 ? 1 : k_parts);
+  const int rows = t.rb == 0 ? 16 : 32 * t.rb;
+  return TileForm{t.rb, t.cb, (M + rows - 1) / rows, t.kp, K / (t.rb == 0 ? 2 * TL_KST : TL_KST) / t.kp};
+}
+
 void launch_gemm_tile(const TileGemm& g_in, hipStream_t st) {
   TileGemm g = g_in;
   if (g.k_parts < 1 || g.epi == 1) g.k_parts = 1;
-  const TilePick t = pick_tile(g.M, g.N, g.K, g.epi, g.k_parts);
-  const int blocks = g.epi == 1 ? g.N / 8 : g.N / 16;
+  const TileForm t = tile_gemm_form(g.M, g.N, g.K, g.epi, g.k_parts);
+  const int blocks = g.epi == 1 ? g.N / 8 : g.N / 16, rt = t.row_tiles;
   g.n_units = (blocks + 2 * t.cb - 1) / (2 * t.cb) * g.k_parts;
-  const int rows = t.rb == 0 ? 16 : 32 * t.rb, rt = (g.M + rows - 1) / rows;
   const int wgs = rt > 1 ? (g.n_units + 7) / 8 * 8 * rt : g.n_units;
   auto go = [&](auto epic) {
     constexpr int EPI = decltype(epic)::value;

@@ -1,5 +1,9 @@
-"""The GEMM kernels at the edges of their tiles: every row class and column remainder of the MFMA kernel, and the
-few-output fp32 kernel at one row, one column, K tails and the tile count where the larger tiles take over."""
+"""The GEMM kernels at the edges of their tiles.  `CASES`: row classes and column remainders through clover_op_gemm, and the
+few-output fp32 kernel at one row, one column, K tails and the tile count where the larger tiles take over.  `PLAIN` and
+`SWIGLU`: every form (tile, one or several row tiles) of the MFMA kernel, each with fewer stages of K than buffers and with
+more, odd stage counts, first and last rows of a row block; the form is asserted, so that another choice by the rule shows.
+(The plain result with RB 5 and several row tiles needs more rows than the operator takes; its loop is that of the SwiGLU
+cases of that form.)"""
 import ctypes as C
 
 import numpy as np
@@ -52,3 +56,132 @@ def test_gemm_tile_edges(path, dtype, M, N, K):
     tol = (1e-5 if path == 0 else 4e-5) * np.sqrt(K) * 0.02 * 4
     err = np.abs(got[:, :N] - X.astype(np.float64) @ Wf.T).max()
     assert err <= tol, (err, tol)
+
+
+# (M, N, K, RB, CB, row tiles, stages)
+PLAIN = [
+    (1, 26000, 128, 0, 4, 1, 2), (1, 34704, 128, 0, 6, 1, 2), (1, 16, 128, 1, 3, 1, 4), (17, 26000, 128, 1, 4, 1, 4),
+    (17, 34704, 128, 1, 6, 1, 4), (33, 16, 128, 2, 3, 1, 4), (33, 26000, 128, 2, 4, 1, 4), (33, 34704, 128, 2, 6, 1, 4),
+    (33, 52000, 128, 2, 8, 1, 4), (65, 16, 128, 3, 3, 1, 4), (97, 16, 128, 3, 3, 2, 4), (65, 26000, 128, 3, 4, 1, 4),
+    (200, 8192, 128, 3, 4, 3, 4), (65, 34704, 128, 3, 6, 1, 4), (200, 10928, 128, 3, 6, 3, 4), (65, 52000, 128, 3, 7, 1, 4),
+    (200, 17344, 128, 3, 7, 3, 4), (65, 58384, 128, 3, 8, 1, 4), (200, 19472, 128, 3, 8, 3, 4), (97, 26000, 128, 4, 4, 1, 4),
+    (200, 16384, 128, 4, 4, 2, 4), (97, 34704, 128, 4, 6, 1, 4), (200, 21856, 128, 4, 6, 2, 4), (97, 52000, 128, 4, 7, 1, 4),
+    (200, 26000, 128, 4, 7, 2, 4), (97, 58384, 128, 4, 8, 1, 4), (200, 29184, 128, 4, 8, 2, 4), (129, 29184, 128, 5, 4, 1, 4),
+    (129, 34704, 128, 5, 6, 1, 4), (129, 52000, 128, 5, 7, 1, 4), (129, 58384, 128, 5, 8, 1, 4),
+    (15, 26000, 640, 0, 4, 1, 10), (15, 34704, 640, 0, 6, 1, 10), (15, 16, 640, 1, 3, 1, 20), (15, 12992, 640, 1, 4, 1, 10),
+    (15, 17344, 640, 1, 6, 1, 10), (50, 16, 640, 2, 3, 1, 20), (50, 12992, 640, 2, 4, 1, 10), (50, 34704, 640, 2, 6, 1, 20),
+    (50, 52000, 640, 2, 8, 1, 20), (95, 16, 640, 3, 3, 1, 20), (127, 16, 640, 3, 3, 2, 20), (95, 26000, 640, 3, 4, 1, 20),
+    (250, 8192, 640, 3, 4, 3, 20), (95, 34704, 640, 3, 6, 1, 20), (250, 10928, 640, 3, 6, 3, 20),
+    (95, 52000, 640, 3, 7, 1, 20), (250, 17344, 640, 3, 7, 3, 20), (95, 58384, 640, 3, 8, 1, 20),
+    (250, 19472, 640, 3, 8, 3, 20), (127, 26000, 640, 4, 4, 1, 20), (250, 16384, 640, 4, 4, 2, 20),
+    (127, 34704, 640, 4, 6, 1, 20), (250, 21856, 640, 4, 6, 2, 20), (127, 52000, 640, 4, 7, 1, 20),
+    (250, 26000, 640, 4, 7, 2, 20), (127, 58384, 640, 4, 8, 1, 20), (250, 29184, 640, 4, 8, 2, 20),
+    (159, 29184, 640, 5, 4, 1, 20), (159, 34704, 640, 5, 6, 1, 20), (159, 52000, 640, 5, 7, 1, 20),
+    (159, 58384, 640, 5, 8, 1, 20), (1, 16, 2176, 1, 3, 1, 17), (1, 6496, 2176, 1, 4, 1, 17), (1, 8672, 1920, 1, 6, 1, 15),
+    (33, 16, 2176, 2, 3, 1, 17), (33, 6496, 1920, 2, 4, 1, 15), (33, 8672, 2176, 2, 6, 1, 17), (65, 16, 2176, 3, 3, 1, 17),
+    (65, 6496, 2176, 3, 4, 1, 17), (65, 8672, 2176, 3, 6, 1, 17),
+]
+# (M, F, K, RB, CB, row tiles, stages)
+SWIGLU = [
+    (1, 12992, 128, 0, 4, 1, 2), (1, 17344, 128, 0, 6, 1, 2), (1, 32, 128, 1, 3, 1, 4), (17, 12992, 128, 1, 4, 1, 4),
+    (17, 17344, 128, 1, 6, 1, 4), (33, 32, 128, 2, 3, 1, 4), (33, 12992, 128, 2, 4, 1, 4), (33, 17344, 128, 2, 6, 1, 4),
+    (33, 27552, 128, 2, 8, 1, 4), (65, 32, 128, 3, 3, 1, 4), (97, 32, 128, 3, 3, 2, 4), (65, 12992, 128, 3, 4, 1, 4),
+    (512, 2048, 128, 3, 4, 6, 4), (65, 17344, 128, 3, 6, 1, 4), (512, 2720, 128, 3, 6, 6, 4), (65, 27552, 128, 3, 7, 1, 4),
+    (1000, 2432, 128, 3, 7, 11, 4), (65, 29184, 128, 3, 8, 1, 4), (700, 3648, 128, 3, 8, 8, 4), (97, 12992, 128, 4, 4, 1, 4),
+    (512, 4096, 128, 4, 4, 4, 4), (97, 17344, 128, 4, 6, 1, 4), (640, 4864, 128, 4, 6, 5, 4), (97, 27552, 128, 4, 7, 1, 4),
+    (400, 6880, 128, 4, 7, 4, 4), (97, 29184, 128, 4, 8, 1, 4), (1000, 3648, 128, 4, 8, 8, 4), (129, 14592, 128, 5, 4, 1, 4),
+    (640, 4096, 128, 5, 4, 4, 4), (129, 17344, 128, 5, 6, 1, 4), (700, 4864, 128, 5, 6, 5, 4), (129, 27552, 128, 5, 7, 1, 4),
+    (400, 8672, 128, 5, 7, 3, 4), (129, 29184, 128, 5, 8, 1, 4), (700, 5792, 128, 5, 8, 5, 4), (15, 12992, 640, 0, 4, 1, 10),
+    (15, 17344, 640, 0, 6, 1, 10), (15, 32, 640, 1, 3, 1, 20), (31, 12992, 640, 1, 4, 1, 20), (31, 17344, 640, 1, 6, 1, 20),
+    (50, 32, 640, 2, 3, 1, 20), (50, 12992, 640, 2, 4, 1, 20), (50, 17344, 640, 2, 6, 1, 20), (50, 27552, 640, 2, 8, 1, 20),
+    (95, 32, 640, 3, 3, 1, 20), (127, 32, 640, 3, 3, 2, 20), (95, 12992, 640, 3, 4, 1, 20), (960, 1216, 640, 3, 4, 10, 20),
+    (95, 17344, 640, 3, 6, 1, 20), (799, 1824, 640, 3, 6, 9, 20), (95, 27552, 640, 3, 7, 1, 20),
+    (960, 2432, 640, 3, 7, 10, 20), (95, 29184, 640, 3, 8, 1, 20), (450, 5792, 640, 3, 8, 5, 20),
+    (127, 12992, 640, 4, 4, 1, 20), (250, 8192, 640, 4, 4, 2, 20), (127, 17344, 640, 4, 6, 1, 20),
+    (620, 4864, 640, 4, 6, 5, 20), (127, 27552, 640, 4, 7, 1, 20), (799, 3648, 640, 4, 7, 7, 20),
+    (127, 29184, 640, 4, 8, 1, 20), (960, 4096, 640, 4, 8, 8, 20), (159, 14592, 640, 5, 4, 1, 20),
+    (620, 4096, 640, 5, 4, 4, 20), (159, 17344, 640, 5, 6, 1, 20), (960, 3648, 640, 5, 6, 6, 20),
+    (159, 27552, 640, 5, 7, 1, 20), (799, 5152, 640, 5, 7, 5, 20), (159, 29184, 640, 5, 8, 1, 20),
+    (960, 4864, 640, 5, 8, 6, 20),
+]
+
+
+def _form(lib, epi, M, N, K):
+    f = (C.c_int32 * 5)()
+    assert lib.clover_op_gemm_form(epi, M, N, K, 1 if epi else 0, f) == 0, lib.clover_last_global_error()
+    return f[0], f[1], f[2], f[4]
+
+
+def _operands(torch, M, N, K, seed, n):
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    X = torch.randn(M, K, generator=gen, device="cuda")
+    return X, [(torch.randn(N, K, generator=gen, device="cuda") * 0.02).bfloat16() for _ in range(n)]
+
+
+def _ptr(t):
+    return C.c_void_p(t.data_ptr())
+
+
+@pytest.mark.parametrize("M,N,K,RB,CB,row_tiles,stages", PLAIN)
+def test_plain_forms(M, N, K, RB, CB, row_tiles, stages):
+    import torch
+    print(f"gemm form RB={RB} CB={CB} M={M} N={N} K={K}", flush=True)
+    lib = clover.load_library()
+    assert _form(lib, 0, M, N, K) == (RB, CB, row_tiles, stages)
+    X, (W,) = _operands(torch, M, N, K, M + N + K, 1)
+    Y = torch.full((M, N), -7.0, device="cuda")
+    nb = lib.clover_op_gemm_scratch_bytes(M, N, K)
+    scratch = torch.full((nb,), 255, dtype=torch.uint8, device="cuda")   # (NaNs, as above)
+    rc = lib.clover_op_gemm(7, 1, _ptr(X), _ptr(W), _ptr(Y), N, M, N, K, _ptr(scratch), nb,
+                            C.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert rc == 0, lib.clover_last_global_error()
+    tol = 4e-5 * np.sqrt(K) * 0.02 * 4                                   # (as above)
+    err = (Y.double() - X.double() @ W.double().T).abs().max().item()
+    assert err <= tol, (err, tol)
+
+
+@pytest.mark.parametrize("M,F,K,RB,CB,row_tiles,stages", SWIGLU)
+def test_swiglu_forms(M, F, K, RB, CB, row_tiles, stages):
+    import torch
+    print(f"swiglu form RB={RB} CB={CB} M={M} F={F} K={K}", flush=True)
+    lib = clover.load_library()
+    assert _form(lib, 1, M, F, K) == (RB, CB, row_tiles, stages)
+    X, (Wg, Wu) = _operands(torch, M, F, K, M + F + K, 2)
+    mb = (M + 15) // 16
+    planes = torch.full((F // 32, mb, 2, 16, 4, 8), -1, dtype=torch.int16, device="cuda")   # [step][row block][hi, lo][row][piece][column]
+    nb = lib.clover_op_swiglu_scratch_bytes(M, F, K)
+    scratch = torch.full((nb,), 255, dtype=torch.uint8, device="cuda")
+    rc = lib.clover_op_swiglu(_ptr(X), _ptr(Wg), _ptr(Wu), _ptr(planes), M, F, K, _ptr(scratch), nb,
+                              C.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert rc == 0, lib.clover_last_global_error()
+    where = torch.tensor([[c ^ (-(r // 4) & 3) for c in range(4)] for r in range(16)], device="cuda")   # of piece c in row r
+    bits = planes.gather(4, where[None, None, None, :, :, None].expand(planes.shape))
+    rows = bits.permute(2, 1, 3, 0, 4, 5).reshape(2, mb * 16, F)                            # [hi, lo][row][column]
+    assert bool((rows[:, M:] == -1).all())                                                  # rows past M stay as they were
+    got = rows[:, :M].contiguous().view(torch.bfloat16).double().sum(0)
+    g, u = X.double() @ Wg.double().T, X.double() @ Wu.double().T
+    s = g * torch.sigmoid(g)
+    # a product's error (the bound above) through the two factors (silu' <= 1.1), the planes' 16 mantissa bits
+    tol = 4e-5 * np.sqrt(K) * 0.02 * 4 * (1.1 * u.abs() + s.abs()) + 2.0 ** -16 * (s * u).abs() + 1e-9
+    bad = (got - s * u).abs() - tol
+    assert bad.max().item() <= 0.0, (bad.max().item(), (bad > 0).nonzero()[:4].tolist())
+
+
+@pytest.mark.parametrize("path,K", [(7, 640), (0, 260)])
+def test_operands_off_the_16_byte_grid(path, K):
+    """X may start on any 4 bytes and the rows of Y on any: the few-output kernel steps back to the tiles, the planes' reader
+    takes it as it is"""
+    import torch
+    lib = clover.load_library()
+    M, N = 33, 48
+    X, (W,) = _operands(torch, M, N, K, K, 1)
+    Xo = torch.empty(M * K + 1, device="cuda")[1:]
+    Xo.copy_(X.flatten())
+    Y = torch.full((M, N + 1), -7.0, device="cuda")
+    nb = lib.clover_op_gemm_scratch_bytes(M, N, K)
+    scratch = torch.full((nb,), 255, dtype=torch.uint8, device="cuda")
+    rc = lib.clover_op_gemm(path, 1, _ptr(Xo), _ptr(W), _ptr(Y), N + 1, M, N, K, _ptr(scratch), nb,
+                            C.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert rc == 0, lib.clover_last_global_error()
+    assert (Y[:, :N].double() - X.double() @ W.double().T).abs().max().item() <= 4e-5 * np.sqrt(K) * 0.02 * 4
+    assert bool((Y[:, N:] == -7.0).all())
