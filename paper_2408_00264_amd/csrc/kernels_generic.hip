@@ -965,12 +965,14 @@ void launch_write_kv(void* k_cache, void* v_cache, int kvdtype, KVLayout kv, int
 // ------------------------------------------------------------------------------------------
 // split-bf16 planes and partial-sum consumers
 // ------------------------------------------------------------------------------------------
+// (16 bytes at once from any multiple of 4: the operator's callers owe x no more, and the load instruction takes it)
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 __global__ void split_planes_kernel(const float* __restrict__ x, int ldx, FragPlanes out, int K) {
   const int row = blockIdx.y;
   const int c = (blockIdx.x * blockDim.x + threadIdx.x) * 4;
   if (c >= K) return;
-  const float4 v = *(const float4*)(x + (size_t)row * ldx + c);
-  frag_store4(out, row, c, v.x, v.y, v.z, v.w);
+  const f32x4_any v = *(const f32x4_any*)(x + (size_t)row * ldx + c);
+  frag_store4(out, row, c, v[0], v[1], v[2], v[3]);
 }
 void launch_split_planes(const float* x, int ldx, FragPlanes out, int rows, int K, hipStream_t st) {
   if (rows <= 0) return;
