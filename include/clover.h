@@ -298,7 +298,8 @@ const char *clover_last_global_error(void);
  * ldy % 4 == 0), 4 = as 3 reusing the copy; 5 = as 1 for a narrow N with long K only (e.g. 4096 x 14336;
  * CLOVER_E_SHAPE where the ranges would not fill the chip), 6 = as 5 reusing the copy;
  * 7 = as 1 (M <= 256, K % 128 == 0, N % 16 == 0).
- * `scratch` dev, >= clover_op_gemm_scratch_bytes(M,N,K).  Stream as given. */
+ * The bounds on M, N and K of a path are limits of this interface; one kernel runs all paths but 0.
+ * `scratch` dev, >= clover_op_gemm_scratch_bytes(M,N,K) (CLOVER_E_CAPACITY otherwise).  Stream as given. */
 size_t clover_op_gemm_scratch_bytes(int32_t M, int32_t N, int32_t K);
 int clover_op_gemm(int32_t path, int32_t dtype, const float *X, const void *W, float *Y, int32_t ldy,
                    int32_t M, int32_t N, int32_t K, void *scratch, size_t scratch_bytes, void *hip_stream);

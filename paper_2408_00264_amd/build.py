@@ -26,7 +26,7 @@ def _hipcc() -> str:
 def build(verbose: bool = False, ablate: bool = False, out: str = "", defines=()) -> str:
     """Compile every source and link the library.  `ablate` adds -DCLOVER_ABLATE (kernel-tuning builds that read
     CLOVER_* environment switches; never the shipped library) and needs an explicit `out` path; `defines` are further
-    NAME=VALUE macros of such a build."""
+    NAME=VALUE macros of such a build (none are defined by the sources as they stand)."""
     if (ablate or defines) and not out:
         raise ValueError("an ablation build must not overwrite the shipped library: pass out=<path>")
     if defines and not ablate:
@@ -74,6 +74,6 @@ if __name__ == "__main__":
     ap.add_argument("--ablate", action="store_true", help="tuning build that reads CLOVER_* switches (needs --out)")
     ap.add_argument("--out", default="")
     ap.add_argument("--define", action="append", default=[], metavar="NAME=VALUE",
-                    help="macro for an ablation build, (repeatable)")
+                    help="extra macro for a tuning build (repeatable)")
     a = ap.parse_args()
     print(build(verbose=True, ablate=a.ablate, out=a.out, defines=tuple(a.define)))

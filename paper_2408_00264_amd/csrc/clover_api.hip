@@ -14,14 +14,10 @@ using namespace clv;
 
 #ifdef CLOVER_ABLATE
 #include <cstdlib>
-#include <map>
 namespace clv {
 int tune_int(const char* name, int dflt) {
-  static std::map<std::string, int> seen;   // read once per process
-  auto it = seen.find(name);
-  if (it != seen.end()) return it->second;
   const char* v = getenv(name);
-  return seen[name] = v ? atoi(v) : dflt;
+  return v ? atoi(v) : dflt;
 }
 }  // namespace clv
 #endif
@@ -338,7 +334,9 @@ void carve(clover_ctx* x, char* base, size_t* total) {
     std::vector<GemmShape> shapes;
     model_gemm_shapes(c, shapes);
     for (int M = 32; M < rows + 32; M += 32) {   // one row count of each class of equal K ranges
-      auto bytes = [&](int N, int K) { return (size_t)tile_gemm_pick_k_parts(M, N, K) * std::min(M, rows) * N * sizeof(float); };
+      auto bytes = [&](int N, int K) {   // (a tuning build that changes the ranges afterwards makes room for them here)
+        return (size_t)std::max(tile_gemm_pick_k_parts(M, N, K), tune_int("CLOVER_TILE_KP_ROOM", 1)) * std::min(M, rows) * N * sizeof(float);
+      };
       for (const GemmShape& s : shapes) pbytes = std::max(pbytes, bytes(s.N, s.K));
       pbytes = std::max(pbytes, align256(bytes(H, H)) + bytes(2 * H, H));
     }

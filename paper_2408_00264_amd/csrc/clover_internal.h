@@ -306,7 +306,8 @@ void launch_dyn_finalize(const DynTree& t, int B, int R, const int* m, int* tree
 
 // ---- tuning knobs -------------------------------------------------------------------------------
 // The shipped library reads no environment variable: every knob is its default.  A build with
-// -DCLOVER_ABLATE (kernel-tuning experiments only) reads CLOVER_<NAME> once per process instead.
+// -DCLOVER_ABLATE (kernel-tuning experiments only) reads CLOVER_<NAME> at every use instead, so that one process can
+// sweep them.
 #ifdef CLOVER_ABLATE
 int tune_int(const char* name, int dflt);
 #else

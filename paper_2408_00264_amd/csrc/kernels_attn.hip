@@ -40,11 +40,10 @@ union Frag {
   bf16x8 v;
 };
 
-// float -> bf16 (round to nearest even) through the hardware conversion (v_cvt_pk_bf16_f32)
-__device__ __forceinline__ unsigned a_rn(float a) { return (unsigned)__builtin_bit_cast(unsigned short, (__bf16)a); }
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
-// (a, b) -> packed hi pair and packed lo pair, hi + lo == value to 16 mantissa bits: six instructions per pair
+// (a, b) -> packed hi pair and packed lo pair (round to nearest even through v_cvt_pk_bf16_f32), hi + lo == value to 16
+// mantissa bits: six instructions per pair
 __device__ __forceinline__ void a_split2(float a, float b, unsigned& hi, unsigned& lo) {
   const f32x2_t v = {a, b};
   const bf16x2_t h = __builtin_convertvector(v, bf16x2_t);

@@ -481,7 +481,8 @@ __global__ __launch_bounds__(256) void gemm_generic_kernel(const float* __restri
 // The same product for launches that give the tiles above no chip to fill: one wavefront per 16 rows x 4 columns, its
 // lanes split K (four adjacent columns each), the 64 sums are exchanged so that every lane ends with one output.  What
 // bounds a 16 x 256 x 256 product in 64 x 64 tiles is a chain of 16 K steps with two barriers and a memory round trip
-// each on 4 workgroups, 36 us; here it is one round trip on 64 wavefronts, ~5 us.
+// each on 4 workgroups, 22 us; here it is one round trip on 64 wavefronts, 4 us.  Beyond that its loads bound it, 20
+// loads of 16 bytes per 256 multiply-adds of a lane, out of the L2: 64 x 4096 x 14336 198 us (the tiles 1960).
 constexpr int GS_ROWS = 16, GS_COLS = 4;
 __device__ __forceinline__ float4 ldw4(const float* w) { return *(const float4*)w; }
 __device__ __forceinline__ float4 ldw4(const bf16_t* w) {
@@ -542,8 +543,9 @@ void launch_gemm_generic(const float* X, int ldx, const void* W, const void* bia
                          int M, int N, int K, int mode, hipStream_t st) {
   if (M <= 0 || N <= 0) return;
   dim3 grid((N + 63) / 64, (M + 63) / 64);
-  // fewer tiles than compute units: the tile kernel's time is its K chain.  (16-byte loads: rows of X and W must
-  // start on 16 bytes, 8 for bf16 weights.)
+  // Fewer tiles than compute units: the tile kernel's time is its K chain, which the small kernel beats at every shape
+  // measured up to there, by 27 times (few rows, K of 14336) down to twice (512 x 1024 x 256: 26.7 -> 13.2 us, 64 x 8192 x
+  // 256: 26.4 -> 11.9).  (16-byte loads: rows of X and W must start on 16 bytes, 8 for bf16 weights.)
   const size_t walign = wdtype == 0 ? 15 : 7;
   if (grid.x * grid.y < 256 && K % 4 == 0 && ldx % 4 == 0 && ((uintptr_t)X & 15) == 0 && ((uintptr_t)W & walign) == 0) {
     dim3 sgrid((N + GS_COLS - 1) / GS_COLS, (M + GS_ROWS - 1) / GS_ROWS);

@@ -10,15 +10,20 @@
 // Shape.  A workgroup of four wavefronts (2 x 2, one per SIMD; up to 16 rows 1 x 4) owns 32 RB rows x 32 CB columns; a wavefront RB x CB
 // products of 16 x 16.  Both operands go global -> LDS directly, 32 columns of K per stage, as 1 KB blocks that are
 // contiguous in global memory too (one load instruction each), NBUF stages deep: the loads of stage s + NBUF are issued
-// while stage s is multiplied, ~100 KB in flight per compute unit, which covers an HBM round trip.  The fragments
+// while stage s is multiplied.  In flight per workgroup (mostly one to a compute unit): NBUF stages of 2 KB per 16 rows and
+// 1 KB per 16 columns, 60 to 108 KB for tiles of up to 64 rows and 128 columns (and 32 x 192, 96 x 96), else 120 to 160.  The fragments
 // of stage s + 1 are read from the LDS into the other of two register sets meanwhile, so a stage costs one barrier and
 // no wait that is not already over.  Every operand byte crosses the L1 once per workgroup.
 //
-// Measured (8B shapes, cold weights, us per launch by events, this kernel / the kernels it replaced, which read row-major
-// planes: K-slice and panel form up to 64 rows, 128-row panel and 128 x 256 tiles above):
-//   gate+up  1 row 42.6 / 43, 23 rows 39.8 / 49, 64 rows 44.6 / 55, 80 rows 50.5 / 80, 256 rows 96 / 101
-//   down     1 row 19.6 / 21, 64 rows 24.6 / 30,  80 rows 31 / 36,  256 rows 49 / 57
-//   QKV      1 row 10.6 / 12, 64 rows 15.1 / 18,  80 rows 17 / 27,  256 rows 27 / 34
+// Measured (8B shapes, weights from HBM, us per launch by kernel trace in passes of two layers; in brackets by events the
+// kernels it replaced, which read row-major planes: K-slice and panel form up to 64 rows, 128-row panel and 128 x 256
+// tiles above):
+//   rows        1          23         64         80         133    256
+//   gate+up     35.0 (43)  37.8 (49)  45.5 (55)  50.8 (80)  74.4   90.5 (101)
+//   down        18.9 (21)  20.4       25.6 (30)  27.8 (36)  37.4   53.9 (57)
+//   QKV          9.7 (12)  11.4       15.0 (18)  16.8 (27)  22.3   26.8 (34)
+//   Wo           6.6        8.5       11.0       13.4       16.9   21.7
+//   LM head    154        171        180        195        245    382
 // The same kernel on row-major planes (64-byte row pieces): gate+up 64.4 at 64 rows, 69.5 at 80, 107 at 256.
 //
 // RB, CB and the K ranges are chosen per launch (pick_tile).
@@ -310,10 +315,11 @@ struct TilePick { int rb, cb, kp; };
 // instructions, of its 1 KB loads at 40 B/clk (what is left of the load path's 55 beside the LDS reads) and of an HBM
 // round trip shared by the stages in flight; rounds of workgroups over the compute units times stages, against the time
 // of the weight stream at 5.3 TB/s (fourth-power mean: near the crossing the two do not overlap freely), + start and
-// end of each round, + the partial tiles, written here and read by the consumer.  Over the measured launches (1 to 256
-// rows, every tile shape, the 8B shapes) the choice is within 4 % of the best shape.  So few rows take narrow tiles
+// end of each round, + the partial tiles, written here and read by the consumer.  Over 75 launches (the five 8B shapes at
+// 15 row counts from 1 to 256, up to 63 combinations of tile and ranges each) the choice is the best or within 3 % of it,
+// except gate+up at 133 rows (74.4 us against 69.2 with one row tile of 160) and QKV at 110 (6 %).  So few rows take narrow tiles
 // (the weight stream needs every compute unit), 256 rows of gate+up 2 x 128 tiles of 128 rows x 224 columns (one whole
-// round, where 256-column tiles leave 32 compute units idle), 133 rows one row tile of 160, 80 rows one of 96.
+// round, where 256-column tiles leave 32 compute units idle), 80 rows one row tile of 96.
 // kp_fixed > 0 fixes the K ranges.
 TilePick pick_tile(int M, int N, int K, int epi, int kp_fixed) {
   static const int cbs[5] = {3, 4, 6, 7, 8};
@@ -322,10 +328,12 @@ TilePick pick_tile(int M, int N, int K, int epi, int kp_fixed) {
   const int blocks = epi == 1 ? N / 8 : N / 16;
   const double stream = (double)blocks * 32.0 * K / 2450.0;
   const int rb_lo = M > 64 ? 3 : M / 32, rb_hi = M > 64 ? 5 : M / 32, KT = K / TL_KST;
+  const int only_rb = tune_int("CLOVER_TILE_RB", 0), only_cb = tune_int("CLOVER_TILE_CB", 0), only_kp = tune_int("CLOVER_TILE_KP", 0);
   TilePick best{rb_lo, 4, 1};
   double best_t = 1e30;
   for (int rb = rb_lo; rb <= rb_hi; ++rb)
     for (int cb : cbs) {
+      if ((only_rb > 0 && rb != only_rb) || (only_cb > 0 && cb != only_cb)) continue;
       // (up to 32 rows a tile of 256 columns is slower than one of 192 however the rounds fall: LM head 176 against 166 us)
       if ((rb == 1 && cb > 6) || (rb == 2 && cb == 7) || (rb > 3 && cb == 3)) continue;
       const int rt = (M + 32 * rb - 1) / (32 * rb), tiles = (blocks + 2 * cb - 1) / (2 * cb);
@@ -333,6 +341,7 @@ TilePick pick_tile(int M, int N, int K, int epi, int kp_fixed) {
       const double stage = std::max(std::max(rb * cb * 2 * 19.0, (4 * rb + 2 * cb) * 1024 / 40.0), 4300.0 / nbuf);
       for (int kp = 1; kp <= TILE_MAX_K_PARTS; ++kp) {
         if (kp_fixed > 0 ? kp != kp_fixed : KT % kp != 0 || (kp > 1 && (KT / kp < 8 || rt * tiles * kp > TL_CUS))) continue;
+        if (kp_fixed <= 0 && only_kp > 0 && kp != only_kp) continue;
         const int rounds = (rt * tiles * kp + TL_CUS - 1) / TL_CUS;
         const double work = rounds * (KT / kp) * stage, a = work * work, b = stream * stream;
         const double t = std::sqrt(std::sqrt(a * a + b * b)) + rounds * 5000.0 + (kp > 1 ? kp * (double)M * N * 8.0 / 2300.0 : 0.0);

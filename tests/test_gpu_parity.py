@@ -33,16 +33,15 @@ GEMM_CASES = [
     (1, 1, 64, 6144, 4096), (1, 1, 5, 4096, 8192), (1, 1, 16, 4096, 4096), (1, 1, 24, 1024, 512),
     (1, 1, 96, 4096, 14336), (1, 1, 256, 4096, 4096), (1, 1, 1, 32000, 4096), (1, 1, 130, 8192, 512),
     (1, 1, 64, 160, 256), (1, 1, 64, 28672, 4096), (1, 1, 48, 4096, 1536),
-    # full-K panel kernel: odd block count, ragged rows, one row, LM-head width
+    # whole K, results written directly: odd block count, ragged rows, one row, LM-head width
     (3, 1, 64, 28672, 4096), (3, 1, 17, 1040, 768), (3, 1, 5, 4096, 512), (3, 1, 64, 160, 256), (3, 1, 1, 2064, 256),
     (3, 1, 33, 128256, 4096),
-    # panel kernel over K ranges (the down projection's shape): full and ragged rows, one row
+    # K ranges of a narrow output (the down projection's shape): full and ragged rows, one row
     (5, 1, 64, 4096, 14336), (5, 1, 37, 4096, 14336), (5, 1, 1, 4096, 14336), (5, 1, 16, 4096, 8192),
-    # 65..128 rows in one weight pass (eight row blocks, 128-column stages): plain, odd rows, K ranges
+    # 65..128 rows: whole K, odd rows, K ranges
     (3, 1, 128, 4096, 1024), (3, 1, 97, 28672, 4096), (5, 1, 96, 4096, 14336), (5, 1, 128, 6144, 4096),
     (5, 1, 65, 4096, 4096),
-    # tiled kernel (one weight pass for up to 256 rows, 128 x 256 workgroup tiles): two row halves, a ragged second half,
-    # one half only, odd widths, K ranges, one stage
+    # up to 256 rows: several row tiles, a ragged last one, one row tile, odd widths, K ranges, fewer stages than buffers
     (7, 1, 256, 4096, 4096), (7, 1, 160, 6144, 4096), (7, 1, 129, 4096, 14336), (7, 1, 97, 1040, 512), (7, 1, 200, 8208, 1024),
     (7, 1, 256, 28672, 4096), (7, 1, 255, 512, 128), (7, 1, 256, 2064, 384), (7, 1, 33, 1040, 512), (7, 1, 97, 4096, 14336),
 ]
@@ -666,13 +665,12 @@ def test_config2_full_size_step():
 @pytest.mark.parametrize("cfg,batch", [(4, 8), (4, 5), (5, 1)], ids=["batch8_256_rows", "batch5_160_rows", "tree96_depth5"])
 def test_full_width_two_layers(cfg, batch):
     """Configs 4 and 5 at their real widths (H 4096, FFN 14336, vocab 128256, 32/8 heads) with two layers and short
-    prompts, so that the oracle stays quick: passes of 96 and 256 rows take the 128-row routes of the real shapes
-    (QKV, Wo and down over K ranges of the panel kernel, gate+up and LM head full-K), which the small models above
-    are too narrow for."""
+    prompts, so that the oracle stays quick: passes of 96, 160 and 256 rows take the tiles and K ranges of the real
+    shapes (QKV, Wo and down over K ranges, gate+up and LM head over the whole K), which the small models above are
+    too narrow for."""
     _torch()
     O = __import__("oracle.clover2_oracle", fromlist=["x"])
     base = synth.CONFIGS[cfg]
-    # (160 rows: a full 128-row batch followed by a short one)
     shape = synth.scaled(base, name=f"wide-{cfg}-{batch}", n_layers=2, batch=batch,
                          prompt_len=(24, 90) if cfg == 4 else (150, 150), seed=31 + cfg + batch)
     ls = _lockstep(shape, batch=shape.batch, max_seq=384)
