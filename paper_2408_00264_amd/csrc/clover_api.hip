@@ -317,8 +317,7 @@ void carve(clover_ctx* x, char* base, size_t* total) {
   x->dyn.t_anc = cv.take<unsigned long long>((size_t)rows * 2);
   x->dyn.t_iv = cv.take<int>((size_t)rows * 2);
   x->dyn_state = cv.take<float>((size_t)B * DYN_MAX_CAND * H);
-  // MFMA path: is every GEMM shape of this model supported, and how large can an output with its
-  // split-K partials get?
+  // MFMA path: is every GEMM shape of this model supported, and how large can the partial tiles over K ranges get?
   size_t pbytes = 256;
   bool fast = c.dtype == CLOVER_DTYPE_BF16 && !(c.flags & CLOVER_FLAG_GENERIC);
   if (fast) {

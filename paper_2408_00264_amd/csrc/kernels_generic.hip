@@ -136,7 +136,7 @@ void launch_rope_table(const int* base_len, const int* depth, float rope_base, i
 
 // ------------------------------------------------------------------------------------------
 // RoPE on q and k (half-split pairing), K rows and transposed V columns into the cache; sums the
-// split-K partials of the QKV projection on the way (fixed order, eight loads in flight).
+// QKV projection's partial tiles on the way (fixed order, eight loads in flight).
 // blocks [0, n*hc): 256 (head, pair) items of one row; then blocks of 8 (head,dim) lines of V^T
 // ------------------------------------------------------------------------------------------
 __device__ __forceinline__ float sum_partials(const float* __restrict__ p, int nsp, size_t sps) {
@@ -1003,7 +1003,7 @@ void launch_reduce(const float* P, int splits, size_t split_stride, int ldp, con
     reduce_kernel<bf16_t><<<grid, 256, 0, st>>>(P, splits, split_stride, ldp, (const bf16_t*)bias, Y, ldy, N, mode);
 }
 
-// one 1024-thread block per row: residual add of the split-K partials (sixteen loads in flight per
+// one 1024-thread block per row: residual add of the partial tiles over K ranges (sixteen loads in flight per
 // thread, summed in split order), then RMSNorm written as planes in fragment order.  A thread keeps its (up to two)
 // float4 of the new row in registers across the block-wide sum of squares; wider rows re-read them.
 template <typename WT>

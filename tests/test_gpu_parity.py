@@ -68,7 +68,7 @@ def test_op_gemm(path, dtype, M, N, K):
     nb = lib.clover_op_gemm_scratch_bytes(M, N, K)
     scratch = torch.zeros(nb, dtype=torch.uint8, device="cuda")
     st = torch.cuda.current_stream().cuda_stream
-    for rep in range(2):       # twice: the split-K counters must be back at zero
+    for rep in range(2):       # twice: the second call finds the first one's scratch
         rc = lib.clover_op_gemm(path, dtype, C.c_void_p(Xd.data_ptr()), C.c_void_p(Wd.data_ptr()),
                                 C.c_void_p(Y.data_ptr()), ldy, M, N, K, C.c_void_p(scratch.data_ptr()), nb,
                                 C.c_void_p(st))
@@ -235,7 +235,7 @@ def test_batch8_ragged_32_node_tree():
 
 def test_batch12_384_rows():
     """More than 8 sequences and more than 256 rows per pass (12 ragged sequences x 32-node tree = 384 rows): the GEMMs
-    run as several row batches, attention and acceptance per sequence."""
+    run over several row tiles, attention and acceptance per sequence."""
     _torch()
     shape = synth.scaled(synth.CONFIGS[4], name="mini-b12", n_layers=2, hidden=512, n_q_heads=4, n_kv_heads=2,
                          ffn=1536, vocab=8192, batch=12, prompt_len=(10, 120), seed=43)
