@@ -4,8 +4,9 @@
 //   EPI 1:  out[M,F]    = planes of silu(X Wg^T) * (X Wu^T)    (the SwiGLU projection)
 //
 // What bounds it: up to 64 rows the weight stream from HBM, above ~150 rows the matrix pipe (hi + lo planes are two
-// matrix instructions per fragment pair), and everywhere the load path of a compute unit, which takes the activations
-// as well as the weights.
+// matrix instructions per fragment pair; from 512 rows on its power: it is busy 77 % of the time at 1.83 GHz, and without
+// the staging loads at 80 % and 2.01), and everywhere the load path of a compute unit, which takes the activations as well as
+// the weights.
 //
 // Shape.  A workgroup of four wavefronts (2 x 2, one per SIMD; up to 16 rows 1 x 4) owns 32 RB rows x 32 CB columns; a wavefront RB x CB
 // products of 16 x 16.  Both operands go global -> LDS directly, 32 columns of K per stage, as 1 KB blocks that are
@@ -25,6 +26,8 @@
 //   Wo           6.6        8.5       11.0       13.4       16.9   21.7
 //   LM head    154        171        180        195        245    382
 // The same kernel on row-major planes (64-byte row pieces): gate+up 64.4 at 64 rows, 69.5 at 80, 107 at 256.
+// Many rows, tiles of up to 160 / of 256 rows (and half the staged bytes per product): gate+up 179 / 165 at 512, 351 / 327
+// at 1024, 701 / 652 at 2048, LM head 777 / 709 at 512, 3106 / 2785 at 2048, down 322 / 306 at 2048, QKV 159 / 146.
 //
 // RB, CB and the K ranges are chosen per launch (pick_tile).
 #include "clover_internal.h"
@@ -66,12 +69,6 @@ __device__ __forceinline__ void mfma_acc(f32x4& acc, const bf16x8& a, const bf16
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
 }
 
-// One staging load of a KB.  NT: non-temporal, for weights that no other workgroup reads (gate+up at 64 rows 47.0 ->
-// 44.6 us; where row tiles share them it costs: 256 rows 96.5 -> 100).
-template <bool NT>
-__device__ __forceinline__ void stage16(const char* base, unsigned lane_off, unsigned dst) {
-  lds_load16<NT>((gbyte_ptr)base, lane_off, dst);
-}
 // this wavefront's staging loads but the youngest N have landed and its LDS reads are done; then the workgroup meets
 template <int N>
 __device__ __forceinline__ void wait_barrier() {
@@ -96,6 +93,8 @@ struct TileShape {
   static constexpr int LDS = std::max(NBUF * STAGE, 2 * RBT * 16 * EPI_LD);
 };
 
+// NT: non-temporal loads, for weights that no other workgroup reads (gate+up at 64 rows 47.0 -> 44.6 us; where row tiles
+// share them it costs: 256 rows 96.5 -> 100).
 template <int RB, int CB, int EPI, bool NT>
 __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(TileGemm p) {
   using T = TileShape<RB, CB>;
@@ -133,26 +132,54 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(TileGemm p) {
   const size_t xstage = (size_t)p.X.mb * 2048;          // bytes of a 32-column step of all rows
   const int n_wb = p.N / (EPI == 1 ? 8 : 16);           // weight blocks of 16 rows
   const size_t wstage = (size_t)n_wb * 1024;            // bytes of a 32-column step of the whole matrix
-  const char* xsrc[XL];
-  const char* wsrc[WL];
+  // A load's address is the stage's (one scalar pair each for activations and weights, advanced once per stage) plus the
+  // load's own 32-bit lane offset: between two matrix instructions of 16 clocks a wavefront has issue slots for two more
+  // instructions, and a load with 64-bit address arithmetic of its own took six (512 rows of the LM head 738 -> 715 us).
+  unsigned xoff[XL], woff[WL];
 #pragma unroll
   for (int j = 0; j < XL; ++j) {
     const int f = (j * 4 + wave) >> 1, rblk = min(row0 / 16 + f % RBT, p.X.mb - 1);
-    xsrc[j] = (const char*)p.X.p + (size_t)(kt0 + f / RBT) * xstage + (size_t)rblk * 2048 + (wave & 1) * 1024;
+    xoff[j] = lane16 + (unsigned)(f / RBT) * (unsigned)xstage + (unsigned)rblk * 2048u + (unsigned)(wave & 1) * 1024u;
   }
 #pragma unroll
   for (int i = 0; i < WL; ++i) {   // (an odd block count: two wavefronts stage the last block again, same bytes)
     const int f = min(i * 4 + wave, WF - 1), c = min(tile * WB + f % WB, n_wb - 1);
-    wsrc[i] = (const char*)p.W + (size_t)(kt0 + f / WB) * wstage + (size_t)c * 1024;
+    woff[i] = lane16 + (unsigned)(f / WB) * (unsigned)wstage + (unsigned)c * 1024u;
   }
-  auto issue = [&](auto jc, int s, unsigned buf) __attribute__((always_inline)) {   // load j of stage s into the buffer at byte `buf`
+  const char* xp = (const char*)p.X.p + (size_t)kt0 * xstage;   // the stage that is requested next
+  const char* wp = (const char*)p.W + (size_t)kt0 * wstage;
+  const unsigned ldsw = lds0 + (unsigned)wave * 1024u;
+  const unsigned wlast = (unsigned)__builtin_amdgcn_readfirstlane((XF + min((WL - 1) * 4 + wave, WF - 1) - wave) * 1024);   // the last load's destination
+  // load j of the stage at (xp, wp), M0 set in front of it: at least one instruction (or the no-op) has to lie in between
+  auto set_m0 = [&](auto jc, unsigned buf) __attribute__((always_inline)) {
+    constexpr int j = decltype(jc)::value, i = j - XL;
+    const unsigned base = ldsw + buf, last = wlast;
+    if constexpr (j < XL) asm volatile("s_add_u32 m0, %0, %1" : : "s"(base), "n"(j * 4096) : "m0", "scc");
+    else if constexpr (i * 4 + 3 < WF) asm volatile("s_add_u32 m0, %0, %1" : : "s"(base), "n"((XF + i * 4) * 1024) : "m0", "scc");
+    else asm volatile("s_add_u32 m0, %0, %1" : : "s"(base), "s"(last) : "m0", "scc");
+  };
+  auto load = [&](auto jc, auto nopc) __attribute__((always_inline)) {
     constexpr int j = decltype(jc)::value;
+    if constexpr (decltype(nopc)::value) asm volatile("s_nop 0");
     if constexpr (j < XL) {
-      stage16<false>(xsrc[j] + (size_t)s * (KS * xstage), lane16, lds0 + buf + (unsigned)(j * 4 + wave) * 1024u);
+      const unsigned off = xoff[j];
+      const gbyte_ptr src = (gbyte_ptr)xp;
+      asm volatile("global_load_lds_dwordx4 %0, %1" : : "v"(off), "s"(src));
     } else {
-      constexpr int i = j - XL;
-      stage16<NT>(wsrc[i] + (size_t)s * (KS * wstage), lane16, lds0 + buf + (unsigned)(XF + min(i * 4 + wave, WF - 1)) * 1024u);
+      const unsigned off = woff[j - XL];
+      const gbyte_ptr src = (gbyte_ptr)wp;
+      if constexpr (NT) asm volatile("global_load_lds_dwordx4 %0, %1 nt" : : "v"(off), "s"(src));
+      else asm volatile("global_load_lds_dwordx4 %0, %1" : : "v"(off), "s"(src));
     }
+  };
+  const size_t xstep = KS * xstage, wstep = KS * wstage;
+  // (xp, wp) from stage t to t + 1, or not behind the last one: that one is requested again, into a buffer that nothing reads
+  // any more; those loads hit the cache, and a loop without conditions keeps the accumulators in place -- with separate
+  // code for the last NBUF stages the allocator moved all of them at every hand-over
+  auto advance = [&](int t) __attribute__((always_inline)) {
+    const bool more = t + 1 < NS;
+    xp += more ? xstep : 0;
+    wp += more ? wstep : 0;
   };
 
   f32x4 acc[CBW][RBW];
@@ -175,17 +202,22 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(TileGemm p) {
     if constexpr (r < 2 * RBW) f[k * NRS + r].u = *(const u32x4*)(xrd + buf + (k * RBT * 2 + r) * 1024);
     else f[k * NRS + r].u = *(const u32x4*)(wrd + buf + (k * WB + r - 2 * RBW) * 1024);
   };
-  auto mm = [&](const Frag (&f)[NR], auto mc) __attribute__((always_inline)) {   // lo plane first, then hi
-    constexpr int k = decltype(mc)::value / MMS, m = decltype(mc)::value % MMS, lo = m < RBW * CBW, rb = (m / CBW) % RBW, c = m % CBW;
+  // Order of a stage's products: lo plane, then hi plane of the same output block back to back (the second takes the sum and
+  // the weights that the first has just used).  Long launches are bound by power -- the clock falls to what the matrix
+  // pipe's switching allows -- and this order needs the least of ten tried: 2.16 PFLOP/s at 2.17 GHz in a loop of nothing
+  // but products of 8 x 8 blocks, against 2.00 at 2.01 GHz with all of the lo plane in front of the hi plane and 1.74 for
+  // 32 x 32 x 16 products (in the kernel: 512 rows of the LM head 731 -> 700 us, 1024 rows of down 168 -> 159).
+  auto mm = [&](const Frag (&f)[NR], auto mc) __attribute__((always_inline)) {
+    constexpr int k = decltype(mc)::value / MMS, m = decltype(mc)::value % MMS, rb = m / (2 * CBW), c = m / 2 % CBW, lo = 1 - m % 2;
     mfma_acc(acc[c][rb], f[k * NRS + 2 * RBW + c].v, f[k * NRS + 2 * rb + lo].v);
   };
 
   // ---- prologue: NBUF stages requested, the fragments of the first one read ----
-  // (Behind the last stage the last one is requested again, into a buffer that nothing reads any more: those loads hit
-  // the cache, and a loop without conditions keeps the accumulators in place -- with separate code for the last NBUF
-  // stages the allocator moved all of them at every hand-over.)
 #pragma unroll
-  for (int s = 0; s < NBUF; ++s) static_for<0, L>([&](auto jc) { issue(jc, min(s, NS - 1), (unsigned)(s * STAGE)); });
+  for (int t = 0; t < NBUF; ++t) {
+    static_for<0, L>([&](auto jc) { set_m0(jc, (unsigned)(t * STAGE)); load(jc, std::true_type{}); });
+    advance(t);
+  }
   wait_barrier<(NBUF - 2) * L>();
   static_for<0, NR>([&](auto rc) { read1(fa, rc, 0u); });
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" : : : "memory");   // buffer 0 may be overwritten
@@ -195,17 +227,18 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(TileGemm p) {
   unsigned cur = 0;   // byte offset of stage s's buffer
   auto stage = [&](const Frag (&f)[NR], Frag (&fn)[NR], int s) __attribute__((always_inline)) {
     const unsigned nxt = cur + STAGE == (unsigned)(NBUF * STAGE) ? 0u : cur + STAGE;
-    const int sn = min(s + NBUF, NS - 1);
-    constexpr int O = NR + L, SPAN = MM - MM / 8;
+    constexpr int O = NR + 2 * L, SPAN = MM - MM / 8;   // operations: reads, then (M0, load) pairs
     static_for<0, MM>([&](auto mc) {
-      constexpr int m = decltype(mc)::value;
+      constexpr int m = decltype(mc)::value, o0 = std::min((m * O + SPAN - 1) / SPAN, O);
       mm(f, mc);
-      static_for<std::min((m * O + SPAN - 1) / SPAN, O), std::min(((m + 1) * O + SPAN - 1) / SPAN, O)>([&](auto oc) {
-        constexpr int o = decltype(oc)::value;
+      static_for<o0, std::min(((m + 1) * O + SPAN - 1) / SPAN, O)>([&](auto oc) {
+        constexpr int o = decltype(oc)::value, j = (o - NR) / 2;
         if constexpr (o < NR) read1(fn, oc, nxt);   // (behind the last stage: bytes of an older one, never used)
-        else issue(std::integral_constant<int, o - NR>{}, sn, cur);
+        else if constexpr ((o - NR) % 2 == 0) set_m0(std::integral_constant<int, j>{}, cur);
+        else load(std::integral_constant<int, j>{}, std::bool_constant<(o - 1 >= o0)>{});   // M0 in the same gap: no-op
       });
     });
+    advance(s + NBUF);
     wait_barrier<(NBUF - 2) * L>();
     cur = nxt;
   };
@@ -297,6 +330,12 @@ void launch_tile_many(const TileGemm& g, int rb, int cb, int wgs, hipStream_t st
 #undef CLV_TL
 }
 template <int EPI>
+void launch_tile_big(const TileGemm& g, int cb, int wgs, hipStream_t st) {   // rb 8 (always several row tiles): cb 6, 7, 8
+  if (cb == 6) launch_tile_one<8, 6, EPI, false>(g, wgs, st);
+  else if (cb == 7) launch_tile_one<8, 7, EPI, false>(g, wgs, st);
+  else launch_tile_one<8, 8, EPI, false>(g, wgs, st);
+}
+template <int EPI>
 void launch_tile_few(const TileGemm& g, int rb, int cb, int wgs, hipStream_t st) {    // rb 0: cb 4, 6; rb 1: cb 3, 4, 6; rb 2: cb 3, 4, 6, 8
   if (rb == 0 && cb == 4) launch_tile_one<0, 4, EPI, true>(g, wgs, st);
   else if (rb == 0) launch_tile_one<0, 6, EPI, true>(g, wgs, st);
@@ -320,6 +359,11 @@ struct TilePick { int rb, cb, kp; };
 // except gate+up at 133 rows (74.4 us against 69.2 with one row tile of 160) and QKV at 110 (6 %).  So few rows take narrow tiles
 // (the weight stream needs every compute unit), 256 rows of gate+up 2 x 128 tiles of 128 rows x 224 columns (one whole
 // round, where 256-column tiles leave 32 compute units idle), 80 rows one row tile of 96.
+// More than 256 rows over 1024 columns of K or more also have tiles of 256 rows (256 accumulators and 200 other registers a
+// lane with 256 columns; 128 columns were slower than 128 x 256 at every shape), a stage there costs 260 + 20.6 clocks per product
+// (2 % to 8 % off over 40 forms at 512, 1024 and 2048 rows; the choice is the best or within 4 % of it in 15 launches), and a
+// round ends with the XCD that has most row tiles (Wo at 1024 rows: 264 workgroups of 96 x 192, 33 of them on one XCD, 114 us;
+// 256 of 128 x 128 58).
 // kp_fixed > 0 fixes the K ranges.
 TilePick pick_tile(int M, int N, int K, int epi, int kp_fixed) {
   static const int cbs[5] = {3, 4, 6, 7, 8};
@@ -329,20 +373,24 @@ TilePick pick_tile(int M, int N, int K, int epi, int kp_fixed) {
   const double stream = (double)blocks * 32.0 * K / 2450.0;
   const int rb_lo = M > 64 ? 3 : M / 32, rb_hi = M > 64 ? 5 : M / 32, KT = K / TL_KST;
   const int only_rb = tune_int("CLOVER_TILE_RB", 0), only_cb = tune_int("CLOVER_TILE_CB", 0), only_kp = tune_int("CLOVER_TILE_KP", 0);
+  const bool many = M > 256 && K >= 1024;
   TilePick best{rb_lo, 4, 1};
   double best_t = 1e30;
-  for (int rb = rb_lo; rb <= rb_hi; ++rb)
+  for (int rb = rb_lo; rb <= (many ? 8 : rb_hi); ++rb)
     for (int cb : cbs) {
+      if (rb == 6 || rb == 7) continue;
       if ((only_rb > 0 && rb != only_rb) || (only_cb > 0 && cb != only_cb)) continue;
       // (up to 32 rows a tile of 256 columns is slower than one of 192 however the rounds fall: LM head 176 against 166 us)
-      if ((rb == 1 && cb > 6) || (rb == 2 && cb == 7) || (rb > 3 && cb == 3)) continue;
+      if ((rb == 1 && cb > 6) || (rb == 2 && cb == 7) || (rb > 3 && cb == 3) || (rb == 8 && cb == 4)) continue;
       const int rt = (M + 32 * rb - 1) / (32 * rb), tiles = (blocks + 2 * cb - 1) / (2 * cb);
       const int nbuf = std::min(6, 160 / (4 * rb + 2 * cb));
-      const double stage = std::max(std::max(rb * cb * 2 * 19.0, (4 * rb + 2 * cb) * 1024 / 40.0), 4300.0 / nbuf);
+      const double products = rb * cb * 2 * 19.0 + (many ? 260.0 + rb * cb * 1.6 : 0.0);
+      const double stage = std::max(std::max(products, (4 * rb + 2 * cb) * 1024 / 40.0), 4300.0 / nbuf);
       for (int kp = 1; kp <= TILE_MAX_K_PARTS; ++kp) {
-        if (kp_fixed > 0 ? kp != kp_fixed : KT % kp != 0 || (kp > 1 && (KT / kp < 8 || rt * tiles * kp > TL_CUS))) continue;
+        // (row tiles of the same columns stay on one XCD: its 32 compute units bound the round, not the 256 of all eight)
+        const int rounds = many ? ((tiles * kp + 7) / 8 * rt + TL_CUS / 8 - 1) / (TL_CUS / 8) : (rt * tiles * kp + TL_CUS - 1) / TL_CUS;
+        if (kp_fixed > 0 ? kp != kp_fixed : KT % kp != 0 || (kp > 1 && (KT / kp < 8 || rounds > 1))) continue;
         if (kp_fixed <= 0 && only_kp > 0 && kp != only_kp) continue;
-        const int rounds = (rt * tiles * kp + TL_CUS - 1) / TL_CUS;
         const double work = rounds * (KT / kp) * stage, a = work * work, b = stream * stream;
         const double t = std::sqrt(std::sqrt(a * a + b * b)) + rounds * 5000.0 + (kp > 1 ? kp * (double)M * N * 8.0 / 2300.0 : 0.0);
         if (t < best_t) { best_t = t; best = TilePick{rb, cb, kp}; }
@@ -374,7 +422,8 @@ void launch_gemm_tile(const TileGemm& g_in, hipStream_t st) {
   const int wgs = rt > 1 ? (g.n_units + 7) / 8 * 8 * rt : g.n_units;
   auto go = [&](auto epic) {
     constexpr int EPI = decltype(epic)::value;
-    if (t.rb < 3) launch_tile_few<EPI>(g, t.rb, t.cb, wgs, st);
+    if (t.rb == 8) launch_tile_big<EPI>(g, t.cb, wgs, st);
+    else if (t.rb < 3) launch_tile_few<EPI>(g, t.rb, t.cb, wgs, st);
     else if (rt > 1) launch_tile_many<EPI, false>(g, t.rb, t.cb, wgs, st);
     else launch_tile_many<EPI, true>(g, t.rb, t.cb, wgs, st);
   };
