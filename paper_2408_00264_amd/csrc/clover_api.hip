@@ -74,7 +74,7 @@ struct clover_ctx {
   TreeHost tree;
   std::string err;
   // sizes
-  int R, max_rows, H, QKVN, NQD;
+  int R, max_rows, z_rows /* of z */, H, QKVN, NQD;
   KVLayout kv;
   size_t k_layer_elems, v_layer_elems, esz, kv_esz;
   int kvdtype;  // 0: fp32 cache elements; 1: (hi, lo) bf16 planes, same bytes (a random-init 32-layer stack amplifies
@@ -145,6 +145,15 @@ int check_config(const clover_config* c, std::string& why) {
   if (c->max_seq < c->max_nodes) return bad("max_seq smaller than max_nodes");
   if (!(c->rope_base > 1.f) || !(c->rms_eps > 0.f)) return bad("rope_base must be > 1 and rms_eps > 0");
   return CLOVER_OK;
+}
+
+// Rows of a prefill pass.  prefill_rows at its bound asks for the longest passes: 2048 rows, where the narrow GEMMs (QKV,
+// Wo, down) fill the chip without ranges of K and every weight byte staged serves 256 rows.  Per 256 rows and layer of the
+// 8B shape in passes of 256 / 512 / 1024 / 2048 rows: gate+up 91 / 83 / 82 / 81 us, down, Wo and QKV with the kernels behind
+// them 125 / 101 / 88 / 81.
+int prefill_pass_rows(const clover_config& c) {
+  if (c.prefill_rows == CLOVER_MAX_PREFILL_ROWS) return std::max(CLOVER_MAX_PREFILL_ROWS, std::min(2048, c.max_seq));
+  return std::min(std::max(c.max_batch * c.max_nodes, c.prefill_rows), CLOVER_MAX_PREFILL_ROWS);
 }
 
 int build_tree(const clover_config& cfg, const clover_tree* t, TreeHost& out, std::string& why) {
@@ -252,10 +261,11 @@ void carve(clover_ctx* x, char* base, size_t* total) {
   const clover_config& c = x->cfg;
   Carver cv{base};
   const int B = c.max_batch, R = c.max_nodes, H = c.hidden, d = c.head_dim;
-  const int rows = std::max(B * R, c.prefill_rows);   // row capacity of every activation buffer
+  const int own_rows = std::max(B * R, c.prefill_rows);
+  const int rows = std::max(own_rows, prefill_pass_rows(c));   // row capacity of every activation buffer
   const size_t rows16 = (size_t)(rows + 15) / 16 * 16;   // of those that hold planes in fragment order (whole row blocks)
   const size_t esz = c.dtype == CLOVER_DTYPE_F32 ? 4 : 2;
-  x->R = R; x->max_rows = rows; x->H = H; x->esz = esz;
+  x->R = R; x->max_rows = rows; x->z_rows = own_rows; x->H = H; x->esz = esz;
   x->kv_esz = 4;  // bytes per cached value in both formats
   x->NQD = c.n_q_heads * d;
   x->QKVN = (c.n_q_heads + 2 * c.n_kv_heads) * d;
@@ -298,12 +308,12 @@ void carve(clover_ctx* x, char* base, size_t* total) {
   x->d_s = cv.take<float>((size_t)rows * H);
   x->d_state = cv.take<float>((size_t)rows * H);
   x->d_rootx = cv.take<float>((size_t)B * H);
-  x->z = cv.take<float>((size_t)rows * c.vocab);
-  x->cand = cv.take<unsigned long long>((size_t)rows * topk_chunks(c.vocab) * 16);
+  x->z = cv.take<float>((size_t)own_rows * c.vocab);
+  x->cand = cv.take<unsigned long long>((size_t)own_rows * topk_chunks(c.vocab) * 16);
   x->topk_ids = cv.take<int>((size_t)rows * 16);
   x->topk_vals = cv.take<float>((size_t)rows * 16);
   x->topk_lse = cv.take<float>((size_t)rows);
-  x->topk_aux = cv.take<float>(std::max((size_t)rows * topk_chunks(c.vocab), (size_t)B * sample_chunks(c.vocab)) * 2);
+  x->topk_aux = cv.take<float>(std::max((size_t)own_rows * topk_chunks(c.vocab), (size_t)B * sample_chunks(c.vocab)) * 2);
   x->dyn.cand_tok = cv.take<int>((size_t)B * DYN_MAX_CAND);
   x->dyn.cand_score = cv.take<float>((size_t)B * DYN_MAX_CAND);
   x->dyn.cand_par = cv.take<int>((size_t)B * DYN_MAX_CAND);
@@ -1142,7 +1152,7 @@ int clover_prefill(clover_ctx* x, int32_t b, const int32_t* tokens, int32_t n, f
   if (x->len_ub[b] + n > c.max_seq || x->aug_ub[b] + n - 1 > c.max_seq)
     return fail(x, CLOVER_E_CAPACITY, "prompt would exceed max_seq (call clover_seq_len to refresh the bound)");
   const int H = x->H;
-  const int P = std::min(x->max_rows, CLOVER_MAX_PREFILL_ROWS);   // rows per pass
+  const int P = prefill_pass_rows(c);
   int* len_b = x->d_seq_len + b;
   int* aug_len_b = x->d_aug_len + b;
   float* xres = x->d_xs;   // residual stream of the pass (the draft head's staging buffers are idle here)
@@ -1242,7 +1252,7 @@ int clover_read_kv(clover_ctx* x, int32_t stack, int32_t layer, int32_t b, int32
       slot0 + n_slots > c.max_seq)
     return fail(x, CLOVER_E_SHAPE, "clover_read_kv: index out of range");
   const size_t n = (size_t)n_slots * c.n_kv_heads * c.head_dim;
-  if (2 * n > (size_t)x->max_rows * c.vocab) return fail(x, CLOVER_E_SHAPE, "clover_read_kv: too many slots at once");
+  if (2 * n > (size_t)x->z_rows * c.vocab) return fail(x, CLOVER_E_SHAPE, "clover_read_kv: too many slots at once");
   if (n == 0) return CLOVER_OK;
   const char* kbase = (stack == 0 ? x->kc : x->aug_kc) + (size_t)layer * x->k_layer_elems * x->kv_esz;
   const char* vbase = (stack == 0 ? x->vc : x->aug_vc) + (size_t)layer * x->v_layer_elems * x->kv_esz;
@@ -1263,7 +1273,7 @@ int clover_write_kv(clover_ctx* x, int32_t stack, int32_t layer, int32_t b, int3
       slot0 + n_slots > c.max_seq)
     return fail(x, CLOVER_E_SHAPE, "clover_write_kv: index out of range");
   const size_t n = (size_t)n_slots * c.n_kv_heads * c.head_dim;
-  if (2 * n > (size_t)x->max_rows * c.vocab) return fail(x, CLOVER_E_SHAPE, "clover_write_kv: too many slots at once");
+  if (2 * n > (size_t)x->z_rows * c.vocab) return fail(x, CLOVER_E_SHAPE, "clover_write_kv: too many slots at once");
   if (n == 0) return CLOVER_OK;
   char* kbase = (stack == 0 ? x->kc : x->aug_kc) + (size_t)layer * x->k_layer_elems * x->kv_esz;
   char* vbase = (stack == 0 ? x->vc : x->aug_vc) + (size_t)layer * x->v_layer_elems * x->kv_esz;
