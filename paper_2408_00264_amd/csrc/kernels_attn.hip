@@ -8,10 +8,19 @@
 // two integers per node) tree key w is visible to node u iff enter[w] <= enter[u] <= exit[w]; the labels of the tree
 // keys sit in the LDS behind the stage buffers, so the test is two integer compares against LDS values.
 //
-// Work split: a workgroup = (sequence, KV head, group of 32 nodes, range of 32-key tiles); its G
-// wavefronts are the G query heads.  K and V^T tiles are staged once per workgroup in LDS and
-// shared by the heads; every split writes an un-normalised partial (O, running max, running sum)
-// and a small kernel merges the splits with the usual log-sum-exp weights.
+// Work split: a workgroup = (sequence, KV head, group of 32 to 128 nodes, range of 32-key tiles); its wavefronts are 16 nodes
+// each of the G query heads.  K and V^T tiles are staged once per workgroup in LDS and shared by the wavefronts; with several
+// ranges every split writes an un-normalised partial (O, reference, running sum) and a small kernel merges them with the
+// usual log-sum-exp weights, with one range the workgroup writes the finished rows.
+//
+// What bounds it: the waits between the steps of a tile (matrix pipe 52 % busy over a 2048-row pass behind 3072 keys, vector
+// ALU 18 %, LDS 34 %), so what counts is wavefronts in flight (120 registers and 66 KB of LDS: two workgroups of eight to a
+// CU), independent work inside a wavefront (scores of the next tile beside the probabilities of this one) and no exchange
+// between lanes.  8B shape, 8 KV heads, us per launch, before (tiles one after the other, row maximum exchanged in every tile)
+// and now: 64 nodes at 1024 keys 14.1 / 12.9, 96 at 8192 54.9 / 47.8, 8 x 32 ragged to 2048 37.1 / 35.1, one row at 1024
+// 9.1 / 8.1, prompts in 2048-row passes 475 / 342 (8192 tokens, average).  Two blocks of 16 nodes per wavefront (half the
+// LDS reads) need 220 registers and with them half the wavefronts: 574 there.  Reading fragments two pairs ahead by
+// scheduling barriers: 360.
 //
 // MFMA mapping (v_mfma_f32_16x16x32_bf16, D[i][j] += sum_k A[i][k] B[j][k]):
 //   scores   S^T[key][row] : A = K tile  (16 keys x 32 d),  B = Q (16 rows x 32 d)
@@ -54,15 +63,16 @@ __device__ __forceinline__ void a_split2(float a, float b, unsigned& hi, unsigne
 
 constexpr int AT_D = 128;         // head dim
 constexpr int AT_TK = KV_PAGE;    // keys per tile = one page of the caches
-// (WM, a template parameter: wavefronts per query head; a workgroup always covers 32 nodes, a wavefront 32 / WM)
+// (template parameters: WM wavefronts per query head, MB blocks of 16 nodes per wavefront; a workgroup covers 16 MB WM nodes)
 // A staged tile lies in the LDS fragment by fragment: 1 KB blocks in which lane l's 16 bytes sit at l * 16, exactly what
 // one 16x32 MFMA operand read takes (a contiguous KB: the LDS's full 256 B/clk).  K: blocks [plane][tt][ks] (16 keys of
 // sub-tile tt, head-dim columns 32 ks ..), V^T: blocks [plane][db] (head-dim rows 16 db .., the 32 keys).
 constexpr int AT_FRAG = 512;                  // bf16 elements of a fragment block
 constexpr int AT_KSTAGE = 16 * AT_FRAG, AT_VSTAGE = 16 * AT_FRAG;   // one staged tile: 16 KB of K, 16 KB of V^T
-constexpr int AT_PGR = 4;                    // page-number registers: at most 64 * AT_PGR tiles per split
 constexpr int AT_NKB = 2, AT_NVB = 2;         // K and V^T buffers: tile i in buffers i % 2
 constexpr int AT_LDS_EL = AT_NKB * AT_KSTAGE + AT_NVB * AT_VSTAGE;
+constexpr float LOG2E = 1.44269504088896f;
+constexpr float AT_SLACK = 8.f;               // log2 of how far a score may exceed the reference of the soft-max
 constexpr int AT_MAX_IV = CLOVER_MAX_NODES_INTERVAL;   // interval labels of the tree keys kept in the LDS
 
 // Wait until at most N of this wavefront's vector-memory loads are outstanding (the vmcnt field of s_waitcnt: bits 3:0
@@ -73,95 +83,98 @@ __device__ __forceinline__ void wait_staging() {
   __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
 }
 
-template <int G, int WM>
+template <int G, int WM, int MB>
 __global__ __launch_bounds__(64 * G * WM) void attn_mfma_kernel(AttnParams p) {
-  constexpr int AT_MB = 2 / WM;     // 16-row blocks of nodes per wavefront
+  constexpr int NODES = 16 * MB * WM;   // nodes per workgroup
   extern __shared__ __attribute__((aligned(16))) bf16_t sm[];  // [2][AT_KSTAGE] [2][AT_VSTAGE] [AT_MAX_IV] labels
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int l16 = lane & 15, g4 = lane >> 4;
-  const int split = blockIdx.x, ng = blockIdx.y / p.n_kv, kvh = blockIdx.y % p.n_kv, b = blockIdx.z;
+  const bool chain = p.anc == nullptr && p.iv == nullptr;
+  // (a chain's last nodes see most keys: their workgroups first, so that the short ones fill the gaps at the end)
+  const int ngi = blockIdx.y / p.n_kv, ng = chain ? (int)gridDim.y / p.n_kv - 1 - ngi : ngi;
+  const int split = blockIdx.x, kvh = blockIdx.y % p.n_kv, b = blockIdx.z;
   const RowMap& rm = p.rm;
   const int t0 = split * p.tiles_per_split;
   const int head = kvh * G + wave % G;
-  const int nsub = (wave / G) * AT_MB * 16;   // this wavefront's first node within the workgroup's 32
+  const int node0 = ng * NODES + (wave / G) * MB * 16;   // this wavefront's first node
 
   // ---- staging: global -> LDS without a stop in registers.  A wavefront instruction moves one fragment block: lane l
   // fetches the 16 bytes the MFMA operand layout wants at l * 16 (K: key 8 (l%16 / 4) + 4 tt + l%16 % 4, columns
   // 32 ks + 8 (l / 16) ..; V^T: row 16 db + l % 16, keys 8 (l / 16) ..) and the hardware writes them to
-  // (LDS base of the block) + l * 16.  The 32 blocks of a tile are dealt to the workgroup's wavefronts.
+  // (LDS base of the block) + l * 16.  The 16 blocks of a K and of a V^T tile are dealt to the workgroup's wavefronts.
   // Key tile t of this sequence is page pages[b * T + t] of the paged caches: the K rows and the V^T columns of
   // (page, KV head) are one contiguous 8 KB block each per plane.  An address is a uniform base plus the lane's 32-bit
   // offset, so staging costs no vector-ALU instruction.  The compiler is not told that these loads write the LDS (it would wait for all of
   // them before every LDS read that follows): the waits before the barriers below are written by hand.
   constexpr int NT = 64 * G * WM, NW = G * WM;
   constexpr int FPW = 16 / NW;          // K blocks and V^T blocks per wavefront and tile
-  constexpr int DPT = 2 * FPW;          // staging loads per wavefront and tile
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
   const unsigned k_lane = (unsigned)((((l16 >> 2) * 8 + (l16 & 3)) * AT_D + g4 * 8) * 2);   // bytes
   const unsigned v_lane = (unsigned)((l16 * AT_TK + g4 * 8) * 2);
   bf16_t* const k_lds = sm;
   bf16_t* const v_lds = sm + AT_NKB * AT_KSTAGE;
   const KVLayout& kv = p.kv;
-  // Page numbers of this split's tiles: lane l of register r holds the page of tile t0 + 64 r + l, read from the page
-  // table once, before the first staging load (a table read inside the loop would have to be a vector load -- the
-  // compiler must assume that the staging statements write memory -- and its wait would drain the staging loads in
-  // flight).  page_of(i) then is a lane read: no memory, no wait.
-  int pgv[AT_PGR];
-#pragma unroll
-  for (int r = 0; r < AT_PGR; ++r) {
-    const int lp = (b + kv.b0) * kv.T + min(t0 + 64 * r + lane, kv.T - 1);
-    pgv[r] = kv.pages ? kv.pages[lp] : lp;
-  }
-  auto page_of = [&](int i) __attribute__((always_inline)) -> int {   // i: tile index within the split, < 64 AT_PGR
-    int pg = __builtin_amdgcn_readlane(pgv[0], i & 63);              // (one lane read per register and a scalar
-#pragma unroll                                                       //  select: a select between the registers
-    for (int r = 1; r < AT_PGR; ++r) {                               //  would be turned into an indexed array)
-      const int q = __builtin_amdgcn_readlane(pgv[r], i & 63);
-      pg = (i >> 6) == r ? q : pg;
-    }
-    return pg;
+  // Page numbers: lane l holds the page of tile t0 + 64 r + l of this split, read 64 tiles at a time (a table read per tile
+  // would have to be a vector load -- the compiler must assume that the staging statements write memory -- and its wait
+  // would drain the staging loads in flight).  page_of(i) then is a lane read: no memory, no wait.
+  int pgv;
+  auto read_pages = [&](int i) __attribute__((always_inline)) {   // for tiles i .. i + 63 of the split
+    const int lp = (b + kv.b0) * kv.T + min(t0 + i + lane, kv.T - 1);
+    pgv = kv.pages ? kv.pages[lp] : lp;
   };
+  auto page_of = [&](int i) __attribute__((always_inline)) -> int { return __builtin_amdgcn_readlane(pgv, i & 63); };
+  read_pages(0);
   const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)sm;   // LDS byte address of sm
-  auto stage_tile = [&](int kbuf, int vbuf, int page) __attribute__((always_inline)) {
+  auto stage_k = [&](int buf, int page) __attribute__((always_inline)) {
     const size_t blk = ((size_t)page * kv.n_kv + kvh) * (size_t)(KV_PAGE * AT_D);   // elements; K and V^T blocks are equal
 #pragma unroll
     for (int j = 0; j < FPW; ++j) {
       const int f = wave_u * FPW + j, plane = f >> 3;
-      const bf16_t* ksrc = p.k_hi + blk + (size_t)plane * p.k_plane + ((f >> 2) & 1) * 4 * AT_D + (f & 3) * 32;
-      const bf16_t* vsrc = p.v_hi + blk + (size_t)plane * p.v_plane + (f & 7) * 16 * AT_TK;
-      lds_load16<false>((gbyte_ptr)ksrc, k_lane, lds0 + 2u * (unsigned)(kbuf * AT_KSTAGE + f * AT_FRAG));
-      lds_load16<false>((gbyte_ptr)vsrc, v_lane, lds0 + 2u * (unsigned)(AT_NKB * AT_KSTAGE + vbuf * AT_VSTAGE + f * AT_FRAG));
+      const bf16_t* src = p.k_hi + blk + (size_t)plane * p.k_plane + ((f >> 2) & 1) * 4 * AT_D + (f & 3) * 32;
+      lds_load16<false>((gbyte_ptr)src, k_lane, lds0 + 2u * (unsigned)(buf * AT_KSTAGE + f * AT_FRAG));
+    }
+  };
+  auto stage_v = [&](int buf, int page) __attribute__((always_inline)) {
+    const size_t blk = ((size_t)page * kv.n_kv + kvh) * (size_t)(KV_PAGE * AT_D);
+#pragma unroll
+    for (int j = 0; j < FPW; ++j) {
+      const int f = wave_u * FPW + j, plane = f >> 3;
+      const bf16_t* src = p.v_hi + blk + (size_t)plane * p.v_plane + (f & 7) * 16 * AT_TK;
+      lds_load16<false>((gbyte_ptr)src, v_lane, lds0 + 2u * (unsigned)(AT_NKB * AT_KSTAGE + buf * AT_VSTAGE + f * AT_FRAG));
     }
   };
   // The first key tile is requested before anything else is waited for (its address needs the page table only:
   // keys past the cache are clamped and masked later), so its HBM latency overlaps the loads of the lengths,
   // the masks and Q.
-  stage_tile(0, 0, page_of(0));
+  stage_k(0, page_of(0));
+  stage_v(0, page_of(0));
   const int nv = rm.n_valid ? min(rm.n_valid[b], rm.n) : rm.n;
   const int L = p.base_len[b];
-  if (ng * 32 >= nv || L + nv > p.max_seq) {  // whole workgroup
+  if (ng * NODES >= nv || L + nv > p.max_seq) {  // whole workgroup
     wait_staging<0>();   // no staging load may land in the LDS after the workgroup has given it back
     return;
   }
   const int total = L + nv;
-  const bool chain = p.anc == nullptr && p.iv == nullptr;
   int2* kiv = (int2*)(sm + AT_LDS_EL);   // [AT_MAX_IV] (enter, exit) of the tree keys; published by the first barrier
   if (p.iv)
     for (int w = tid; w < nv; w += NT) kiv[w] = *(const int2*)(p.iv + 2 * ((size_t)b * p.anc_stride + w));
-  const int n_tiles = ((chain ? min(total, L + ng * 32 + 32) : total) + AT_TK - 1) / AT_TK;
-  const int t1 = min(n_tiles, t0 + p.tiles_per_split);
+  const bool work = __builtin_amdgcn_readfirstlane(node0) < nv;   // (a wavefront without nodes only helps with the staging)
+  const int open = L + (chain ? ng * NODES : 0);
+  const int n_tiles = ((chain ? min(total, L + ng * NODES + NODES) : total) + AT_TK - 1) / AT_TK;
+  const int n = min(n_tiles, t0 + p.tiles_per_split) - t0;   // tiles of this split (<= 0: none)
+  if (n > 1) stage_k(1, page_of(1));
 
   // ---- Q fragments (already scaled and split by the RoPE kernel), ancestor masks ----
-  Frag qh[AT_MB][4], ql[AT_MB][4];
-  unsigned long long a0[AT_MB], a1[AT_MB];
-  int my_enter[AT_MB];
+  Frag qh[MB][4], ql[MB][4];
+  unsigned long long a0[MB], a1[MB];
+  int my_enter[MB];
 #pragma unroll
-  for (int mb = 0; mb < AT_MB; ++mb) {
-    const int node = ng * 32 + nsub + mb * 16 + l16;
+  for (int mb = 0; mb < MB; ++mb) {
+    const int node = node0 + mb * 16 + l16;
     const bool ok = node < nv;
     const bool bits = !chain && !p.iv;
-    a0[mb] = !ok ? 0ull : bits ? p.anc[2 * ((size_t)b * p.anc_stride + node)] : ~0ull;
-    a1[mb] = !ok ? 0ull : bits ? p.anc[2 * ((size_t)b * p.anc_stride + node) + 1] : ~0ull;
+    a0[mb] = ok && bits ? p.anc[2 * ((size_t)b * p.anc_stride + node)] : 0ull;
+    a1[mb] = ok && bits ? p.anc[2 * ((size_t)b * p.anc_stride + node) + 1] : 0ull;
     my_enter[mb] = ok && p.iv ? p.iv[2 * ((size_t)b * p.anc_stride + node)] : 0;
     const size_t qo = ((size_t)b * rm.R + (ok ? node : 0)) * p.ldq + head * AT_D + g4 * 8;
 #pragma unroll
@@ -175,24 +188,25 @@ __global__ __launch_bounds__(64 * G * WM) void attn_mfma_kernel(AttnParams p) {
     }
   }
 
-  f32x4 O[8][AT_MB];
+  f32x4 O[8][MB];
 #pragma unroll
   for (int db = 0; db < 8; ++db)
 #pragma unroll
-    for (int mb = 0; mb < AT_MB; ++mb) O[db][mb] = (f32x4){0.f, 0.f, 0.f, 0.f};
-  float m_run[AT_MB], l_run[AT_MB];
+    for (int mb = 0; mb < MB; ++mb) O[db][mb] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  // Running reference of the soft-max in units of log2: m2 is what the probabilities so far are relative to (not necessarily
+  // the largest score, see below), ms the same with 0 for "none yet"; l_run this lane's share of the running sum.
+  float m2[MB], ms[MB], l_run[MB];
 #pragma unroll
-  for (int mb = 0; mb < AT_MB; ++mb) { m_run[mb] = -INFINITY; l_run[mb] = 0.f; }
+  for (int mb = 0; mb < MB; ++mb) { m2[mb] = -INFINITY; ms[mb] = 0.f; l_run[mb] = 0.f; }
 
-  // ---- the three steps of a key tile.  scores: S^T = K Q^T (matrix pipe); soft_max: running statistics, the
-  // probabilities as hi/lo fragments and the factor the output so far has to be scaled by (vector ALU);
-  // output: O^T += V^T P (matrix pipe). ----
-  auto scores = [&](int kbuf, f32x4 (&sc)[2][AT_MB]) __attribute__((always_inline)) {
+  // ---- the steps of a key tile.  scores: S^T = K Q^T (matrix pipe); probabilities: exp2 of the scores relative to m2, as hi/lo
+  // fragments (vector ALU); output: O^T += V^T P (matrix pipe); limit: masks, and a new reference if a score asks for it. ----
+  auto scores = [&](int kbuf, f32x4 (&sc)[2][MB]) __attribute__((always_inline)) {
     const bf16_t* kb = k_lds + kbuf * AT_KSTAGE + lane * 8;
 #pragma unroll
     for (int tt = 0; tt < 2; ++tt)
 #pragma unroll
-      for (int mb = 0; mb < AT_MB; ++mb) sc[tt][mb] = (f32x4){0.f, 0.f, 0.f, 0.f};
+      for (int mb = 0; mb < MB; ++mb) sc[tt][mb] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int tt = 0; tt < 2; ++tt)
 #pragma unroll
@@ -201,50 +215,20 @@ __global__ __launch_bounds__(64 * G * WM) void attn_mfma_kernel(AttnParams p) {
         kh.u = *(const u32x4*)(kb + (tt * 4 + ks) * AT_FRAG);
         kl.u = *(const u32x4*)(kb + (8 + tt * 4 + ks) * AT_FRAG);
 #pragma unroll
-        for (int mb = 0; mb < AT_MB; ++mb) {
+        for (int mb = 0; mb < MB; ++mb) {
           sc[tt][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kl.v, qh[mb][ks].v, sc[tt][mb], 0, 0, 0);
           sc[tt][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kh.v, ql[mb][ks].v, sc[tt][mb], 0, 0, 0);
           sc[tt][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kh.v, qh[mb][ks].v, sc[tt][mb], 0, 0, 0);
         }
       }
   };
-  auto soft_max_t = [&](int t, const f32x4 (&sc)[2][AT_MB], Frag (&ph)[AT_MB], Frag (&pl)[AT_MB], auto cachedc)
-                        __attribute__((always_inline)) {
-    constexpr bool CACHED = decltype(cachedc)::value;  // every key of the tile is a cached token: no tree mask
+  auto probabilities = [&](const f32x4 (&sc)[2][MB], Frag (&ph)[MB], Frag (&pl)[MB]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int mb = 0; mb < AT_MB; ++mb) {
-      float sv[8];
-      float tmax = -INFINITY;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {  // e-th key of this lane: slot t*32 + 8*g4 + e
-        const int j = t * AT_TK + 8 * g4 + e;
-        bool vis = CACHED || j < L;
-        if (!CACHED && !vis && j < total) {
-          const int wn = j - L;
-          if (chain) vis = wn <= ng * 32 + nsub + mb * 16 + l16;
-          else if (p.iv) { const int2 ke = kiv[wn]; vis = ke.x <= my_enter[mb] && my_enter[mb] <= ke.y; }
-          else vis = ((wn < 64 ? (a0[mb] >> wn) : (a1[mb] >> (wn - 64))) & 1ull) != 0ull;
-        }
-        if (a0[mb] == 0ull && a1[mb] == 0ull) vis = false;  // padding row
-        sv[e] = vis ? sc[e >> 2][mb][e & 3] : -INFINITY;
-        tmax = fmaxf(tmax, sv[e]);
-      }
-      tmax = fmaxf(tmax, __shfl_xor(tmax, 16, 64));
-      tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
-      const float m_new = fmaxf(m_run[mb], tmax);
-      const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
-      const float corr = __expf(m_run[mb] - m_safe);  // exp(-inf) = 0 on the first visible tile
+    for (int mb = 0; mb < MB; ++mb) {
       float pe[8], psum = 0.f;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) { pe[e] = __expf(sv[e] - m_safe); psum += pe[e]; }
-      l_run[mb] = l_run[mb] * corr + psum;
-      m_run[mb] = m_new;
-      // the running maximum rarely moves after the first tiles: rescale only when some row of the wavefront needs it
-      // (every output product issued before this point has been accumulated by the time the scaling reads O)
-      if (__builtin_amdgcn_ballot_w64(corr != 1.0f) != 0ull) {
-#pragma unroll
-        for (int db = 0; db < 8; ++db) O[db][mb] *= corr;
-      }
+      for (int e = 0; e < 8; ++e) { pe[e] = __builtin_amdgcn_exp2f(fmaf(sc[e >> 2][mb][e & 3], LOG2E, -ms[mb])); psum += pe[e]; }
+      l_run[mb] += psum;
       unsigned h, l;
       a_split2(pe[0], pe[1], h, l); ph[mb].u.x = h; pl[mb].u.x = l;
       a_split2(pe[2], pe[3], h, l); ph[mb].u.y = h; pl[mb].u.y = l;
@@ -252,12 +236,7 @@ __global__ __launch_bounds__(64 * G * WM) void attn_mfma_kernel(AttnParams p) {
       a_split2(pe[6], pe[7], h, l); ph[mb].u.w = h; pl[mb].u.w = l;
     }
   };
-  auto soft_max = [&](int t, const f32x4 (&sc)[2][AT_MB], Frag (&ph)[AT_MB], Frag (&pl)[AT_MB]) __attribute__((always_inline)) {
-    // (specialised only where the register file has room for both versions)
-    if ((G == 2 || G == 4 || WM == 2) && (t + 1) * AT_TK <= L) soft_max_t(t, sc, ph, pl, std::true_type{});  // uniform
-    else soft_max_t(t, sc, ph, pl, std::false_type{});
-  };
-  auto output = [&](int vbuf, const Frag (&ph)[AT_MB], const Frag (&pl)[AT_MB]) __attribute__((always_inline)) {
+  auto output = [&](int vbuf, const Frag (&ph)[MB], const Frag (&pl)[MB]) __attribute__((always_inline)) {
     const bf16_t* vb = v_lds + vbuf * AT_VSTAGE + lane * 8;
 #pragma unroll
     for (int db = 0; db < 8; ++db) {
@@ -265,66 +244,136 @@ __global__ __launch_bounds__(64 * G * WM) void attn_mfma_kernel(AttnParams p) {
       vh.u = *(const u32x4*)(vb + db * AT_FRAG);
       vl.u = *(const u32x4*)(vb + (8 + db) * AT_FRAG);
 #pragma unroll
-      for (int mb = 0; mb < AT_MB; ++mb) {
+      for (int mb = 0; mb < MB; ++mb) {
         O[db][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vl.v, ph[mb].v, O[db][mb], 0, 0, 0);
         O[db][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vh.v, pl[mb].v, O[db][mb], 0, 0, 0);
         O[db][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vh.v, ph[mb].v, O[db][mb], 0, 0, 0);
       }
     }
   };
+  auto limit = [&](int t, f32x4 (&sc)[2][MB]) __attribute__((always_inline)) {
+    // Uniform: some key of the tile may be hidden from some row (keys in front of `open` are visible to every row).  Rows past
+    // the last node are multiplied along, their results are never stored.
+    if ((t + 1) * AT_TK > open) {
+      const int w0 = t * AT_TK + 8 * g4 - L;   // the lane's keys are slots L + w0 .. + 7: new rows w0 .. where not negative
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) {
+        unsigned seen = 0u;   // bit e: the lane's e-th key is visible to its row
+        if (chain) {
+          seen = (1u << max(0, min(8, node0 + mb * 16 + l16 - w0 + 1))) - 1u;
+        } else if (!p.iv) {   // (no bits behind the last node)
+          const int lo = max(0, min(8, -w0)), w = max(w0, 0);
+          const unsigned long long a = w < 64 ? (a0[mb] >> w) | (w > 0 ? a1[mb] << (64 - w) : 0ull) : w < 128 ? a1[mb] >> (w - 64) : 0ull;
+          seen = (unsigned)(a << lo) | ((1u << lo) - 1u);
+        } else {
+#pragma unroll 1
+          for (int e = 0; e < 8; ++e) {
+            const int wn = w0 + e;
+            bool vis = wn < 0;
+            if (wn >= 0 && wn < nv) { const int2 ke = kiv[wn]; vis = ke.x <= my_enter[mb] && my_enter[mb] <= ke.y; }
+            if (vis) seen |= 1u << e;
+          }
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (!(seen >> e & 1u)) sc[e >> 2][mb][e & 3] = -INFINITY;
+      }
+    }
+    // The reference moves only when some score exceeds it by a factor of 2^AT_SLACK (the first visible scores exceed "none"):
+    // probabilities up to that factor above one are as exact in floating point as those below one, and the exchange between
+    // the lanes of a row and the rescaling drop out of nearly every tile.
+    float tmax[MB];
+    bool above = false;
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+      tmax[mb] = sc[0][mb][0];
+#pragma unroll
+      for (int e = 1; e < 8; ++e) tmax[mb] = fmaxf(tmax[mb], sc[e >> 2][mb][e & 3]);
+      above = above || tmax[mb] * LOG2E > m2[mb] + AT_SLACK;
+    }
+    if (__builtin_amdgcn_ballot_w64(above) != 0ull) {
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) {
+        float t2 = fmaxf(tmax[mb], __shfl_xor(tmax[mb], 16, 64));
+        t2 = fmaxf(t2, __shfl_xor(t2, 32, 64)) * LOG2E;
+        const float m_new = fmaxf(m2[mb], t2);
+        ms[mb] = m_new == -INFINITY ? 0.f : m_new;
+        const float corr = __builtin_amdgcn_exp2f(m2[mb] - ms[mb]);   // exp2(-inf) = 0 on the first visible tile
+        m2[mb] = m_new;
+        l_run[mb] *= corr;
+#pragma unroll
+        for (int db = 0; db < 8; ++db) O[db][mb] *= corr;
+      }
+    }
+  };
 
-  // ---- the loop over this split's key tiles.  Tile i + 1 is requested at the top of iteration i into the buffers
-  // tile i - 1 has left (every wavefront is past the barrier of iteration i - 1) and has to be complete, and visible
-  // to every wavefront, at the barrier that ends iteration i: each wavefront waits for its own staging loads first.
-  // Measured on the same machine, 8192 + 96 keys (attention + merge, us): this form 58.9; the tile after next in
-  // flight as well (three K and four V^T buffers, output product one tile behind the scores) 62.2; tiles staged
-  // through registers and padded LDS rows, two in flight, 61.3.  Two workgroups of this kernel fit a CU (114
-  // registers, 66 KB of LDS) and a launch of two per CU is no faster than one per CU: per key tile a workgroup costs
-  // the CU ~1.5 us however the work is arranged -- scores 0.29, soft-max 0.40, output 0.23 (each timed by leaving
-  // it out), the rest barriers, waits and the parts of the staging latency that the products do not cover -- and on
-  // this chip a SIMD's matrix and vector instructions hardly overlap, whichever wavefronts they come from (24 MFMA
-  // in one wavefront and 96 fma in another take 86-100 % of the sum of their times: probes/mfma_valu_overlap.hip),
-  // so running half of the wavefronts one step out of phase with the others gains nothing either. ----
-  if (t0 < t1) {  // uniform over the workgroup
-    const int n = t1 - t0;
-    f32x4 sc[2][AT_MB];
-    Frag ph[AT_MB], pl[AT_MB];
+  // ---- the loop over this split's key tiles: the scores of tile i + 1 (matrix pipe) are computed beside the probabilities of
+  // tile i (vector ALU), so K runs one tile ahead of V^T.  Requested at the top of iteration i: K tile i + 2 into the buffer of
+  // tile i (its scores were computed in iteration i - 1, every wavefront is past that barrier), V^T tile i + 1.  Both are
+  // complete, and visible to every wavefront, at the barrier that ends iteration i: each wavefront waits for its own
+  // staging loads first. ----
+  if (n > 0) {  // uniform over the workgroup
+    f32x4 sa[2][MB], sb[2][MB];
+    Frag ph[MB], pl[MB];
     wait_staging<0>();
     __syncthreads();
-    for (int i = 0; i < n; ++i) {
-      const int cur = i & 1;
-      if (i + 1 < n) stage_tile(cur ^ 1, cur ^ 1, page_of(i + 1));
-      scores(cur, sc);
-      soft_max(t0 + i, sc, ph, pl);
-      output(cur, ph, pl);
+    if (work) { scores(0, sa); limit(t0, sa); }
+    __syncthreads();   // K buffer 0 is overwritten from here on
+    for (int i = 0; i + 1 < n; ++i) {
+      const int page1 = page_of(i + 1);
+      if (i + 2 < n) {
+        if (((i + 2) & 63) == 0) read_pages(i + 2);
+        stage_k(i & 1, page_of(i + 2));
+      }
+      stage_v((i + 1) & 1, page1);
+      if (work) {
+        scores((i + 1) & 1, sb);
+        probabilities(sa, ph, pl);
+        output(i & 1, ph, pl);
+        limit(t0 + i + 1, sb);
+#pragma unroll
+      for (int tt = 0; tt < 2; ++tt)
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) sa[tt][mb] = sb[tt][mb];
+      }
       wait_staging<0>();
       __syncthreads();
     }
+    if (work) { probabilities(sa, ph, pl); output((n - 1) & 1, ph, pl); }
   }
 
   wait_staging<0>();   // (a split without tiles still has its first staging loads in flight)
-  // ---- partial result of this split ----
+  // ---- one split: the finished rows as planes; several: the partial result of this split ----
 #pragma unroll
-  for (int mb = 0; mb < AT_MB; ++mb) {
-    const int node = ng * 32 + nsub + mb * 16 + l16;
+  for (int mb = 0; mb < MB; ++mb) {
+    const int node = node0 + mb * 16 + l16;
     float lsum = l_run[mb];
     lsum += __shfl_xor(lsum, 16, 64);
     lsum += __shfl_xor(lsum, 32, 64);
     if (node >= nv) continue;
-    const size_t prow = ((size_t)split * p.rows_total + (size_t)b * rm.R + node) * p.n_q + head;
+    const size_t row = (size_t)b * rm.R + node;
+    if (p.n_splits == 1) {
+#pragma unroll
+      for (int db = 0; db < 8; ++db) {
+        const f32x4 v = O[db][mb];
+        frag_store4(p.out, (int)row, head * AT_D + db * 16 + 4 * g4, v[0] / lsum, v[1] / lsum, v[2] / lsum, v[3] / lsum);
+      }
+      continue;
+    }
+    const size_t prow = ((size_t)split * p.rows_total + row) * p.n_q + head;
 #pragma unroll
     for (int db = 0; db < 8; ++db) {
       const f32x4 v = O[db][mb];
       *(float4*)(p.o_part + prow * AT_D + db * 16 + 4 * g4) = make_float4(v[0], v[1], v[2], v[3]);
     }
     if (g4 == 0) {
-      p.ml_part[prow * 2] = m_run[mb];
+      p.ml_part[prow * 2] = m2[mb];
       p.ml_part[prow * 2 + 1] = lsum;
     }
   }
 }
 
-// merge the splits of one (row, head): out = sum_s e^{m_s - M} O_s / sum_s e^{m_s - M} l_s, as planes.
+// merge the splits of one (row, head): out = sum_s 2^{m_s - M} O_s / sum_s 2^{m_s - M} l_s, as planes.
 // One thread owns four adjacent channels of one head; the (m, l) pairs and then the partial rows of
 // all splits are loaded as one batch each, so a thread waits for memory twice, not once per split.
 constexpr int MG_HEADS = 8;   // heads per workgroup (32 threads each)
@@ -354,7 +403,7 @@ __global__ __launch_bounds__(MG_HEADS * 32) void attn_merge_kernel(const float* 
   float den = 0.f;
 #pragma unroll
   for (int s = 0; s < MG_MAXS; ++s) {  // split order: the sum does not depend on how the loads were batched
-    const float wgt = ml[s].x == -INFINITY ? 0.f : __expf(ml[s].x - M);
+    const float wgt = ml[s].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml[s].x - M);
     den += wgt * ml[s].y;
     num.x += wgt * o[s].x; num.y += wgt * o[s].y; num.z += wgt * o[s].z; num.w += wgt * o[s].w;
   }
@@ -363,45 +412,56 @@ __global__ __launch_bounds__(MG_HEADS * 32) void attn_merge_kernel(const float* 
 
 bool attn_mfma_supported(int head_dim, int n_q, int n_kv, int max_seq) {
   const int g = n_q / n_kv;
-  // (a split keeps the page numbers of at most 64 * AT_PGR tiles in registers, and there are at most MG_MAXS splits)
   return head_dim == AT_D && (g == 1 || g == 2 || g == 4 || g == 8) && max_seq % KV_PAGE == 0 && max_seq >= KV_PAGE &&
-         max_seq / KV_PAGE <= 64 * AT_PGR * MG_MAXS;
+         max_seq / KV_PAGE <= 4096;
 }
 
-template <int G, int WM>
+template <int G, int WM, int MB>
 static void launch_attn_one(const AttnParams& p, dim3 grid, hipStream_t st) {
   constexpr size_t lds = (size_t)AT_LDS_EL * sizeof(bf16_t) + AT_MAX_IV * sizeof(int2);
   static OncePerDevice once;
-  allow_dynamic_lds(once, (const void*)attn_mfma_kernel<G, WM>, (int)lds);
-  attn_mfma_kernel<G, WM><<<grid, 64 * G * WM, lds, st>>>(p);
+  allow_dynamic_lds(once, (const void*)attn_mfma_kernel<G, WM, MB>, (int)lds);
+  attn_mfma_kernel<G, WM, MB><<<grid, 64 * G * WM, lds, st>>>(p);
 }
 
 void launch_attn_mfma(AttnParams p, int max_total_keys, FragPlanes out, hipStream_t st) {
   const int g = p.n_q / p.n_kv;
-  const int node_groups = (p.rm.n + 31) / 32;
   const int n_tiles = (max_total_keys + AT_TK - 1) / AT_TK;
-  // about one workgroup per CU (two fit and do not overlap: a key tile costs the CU ~1.5 us of a workgroup's time
-  // whether the workgroup shares the CU or not, so a launch of 1.5 workgroups per CU takes as long as one of 2), at
-  // least two tiles per split, within the partial buffer
-  const int target = tune_int("CLOVER_ATTN_WGS", 256);
-  int splits = std::max(1, target / (p.rm.B * p.n_kv * node_groups));
-  splits = std::max(1, std::min(std::min(splits, std::min(p.max_splits, MG_MAXS)), (n_tiles + 1) / 2));
-  splits = std::max(splits, (n_tiles + 64 * AT_PGR - 1) / (64 * AT_PGR));   // <= MG_MAXS: attn_mfma_supported
+  // Nodes per workgroup: with one or two query heads per KV head 64 or 128 where they are there, so that up to eight
+  // wavefronts share a staged tile (32 heads of their own K/V, us: 64 nodes at 512 keys 13.6 -> 11.2, 128 nodes at 1500 keys
+  // 36.6 -> 22.7, a 2048-token prompt 224 -> 122; 16 KV heads, 8 x 60 nodes at 700 keys 41.1 -> 32.5)
+  const int nodes = g == 1 && p.rm.n > 64 ? 128 : g <= 2 && p.rm.n > 32 ? 64 : 32;
+  const int node_groups = (p.rm.n + nodes - 1) / nodes;
+  // Key splits by estimated time, in us.  A key tile costs a compute unit 1.5 whether one workgroup is at it or two; splitting
+  // at all costs the merge launch and the traffic of the partial results, 5.2 + 0.4 per MB (32 heads, 8 KV heads: prompts of 133 /
+  // 300 / 500 tokens unsplit 12.7 / 19.7 / 31.4, in two or three splits 15.9 / 22.2 / 31.2; 64 nodes at 512 keys unsplit 31.0,
+  // in 9 splits 15.4; 8 x 60 nodes at 700 keys 41.5 and 36.1).
+  const int wgs = p.rm.B * p.n_kv * node_groups, only = tune_int("CLOVER_ATTN_SPLITS", 0);
+  const double mb = (double)p.rm.B * p.rm.n * p.n_q * AT_D * 4e-6;
+  int splits = 1;
+  double best = 1e30;
+  for (int s = 1; s <= std::min(p.max_splits, MG_MAXS) && s <= (n_tiles + 1) / 2; ++s) {
+    const int tiles = (n_tiles + s - 1) / s, n = (n_tiles + tiles - 1) / tiles;
+    const double t = 1.5 * tiles * ((wgs * n + 255) / 256) + (n > 1 ? 5.2 + 0.4 * mb * n : 0.0);
+    if (only > 0 ? s <= only : t < best) { best = t; splits = s; }
+  }
   p.tiles_per_split = (n_tiles + splits - 1) / splits;
   p.n_splits = (n_tiles + p.tiles_per_split - 1) / p.tiles_per_split;
+  p.out = out;
   dim3 grid(p.n_splits, node_groups * p.n_kv, p.rm.B);
-  // Two wavefronts per head (16 nodes each, two per SIMD): while one waits for fragments, a shuffle or the
-  // barrier the other issues, and both share the staged K / V^T tile (one wavefront per head with 32 nodes measured
-  // slower at every launch size).
-  const int wm1 = tune_int("CLOVER_ATTN_WM1", 0);
   switch (g) {
-    case 1: if (wm1) launch_attn_one<1, 1>(p, grid, st); else launch_attn_one<1, 2>(p, grid, st); break;
-    case 2: if (wm1) launch_attn_one<2, 1>(p, grid, st); else launch_attn_one<2, 2>(p, grid, st); break;
-    case 4: if (wm1) launch_attn_one<4, 1>(p, grid, st); else launch_attn_one<4, 2>(p, grid, st); break;
-    default: launch_attn_one<8, 1>(p, grid, st); break;
+    case 1:
+      if (nodes == 128) launch_attn_one<1, 8, 1>(p, grid, st);
+      else if (nodes == 64) launch_attn_one<1, 4, 1>(p, grid, st);
+      else launch_attn_one<1, 2, 1>(p, grid, st);
+      break;
+    case 2: if (nodes == 64) launch_attn_one<2, 4, 1>(p, grid, st); else launch_attn_one<2, 2, 1>(p, grid, st); break;
+    case 4: launch_attn_one<4, 2, 1>(p, grid, st); break;
+    default: launch_attn_one<8, 1, 2>(p, grid, st); break;
   }
-  attn_merge_kernel<<<dim3(p.rm.n, p.rm.B, (p.n_q + MG_HEADS - 1) / MG_HEADS), MG_HEADS * 32, 0, st>>>(
-      p.o_part, p.ml_part, p.n_splits, p.rows_total, p.n_q, out, p.rm);
+  if (p.n_splits > 1)
+    attn_merge_kernel<<<dim3(p.rm.n, p.rm.B, (p.n_q + MG_HEADS - 1) / MG_HEADS), MG_HEADS * 32, 0, st>>>(
+        p.o_part, p.ml_part, p.n_splits, p.rows_total, p.n_q, out, p.rm);
 }
 
 }  // namespace clv
