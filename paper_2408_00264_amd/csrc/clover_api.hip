@@ -475,12 +475,16 @@ void run_layer(clover_ctx* x, const clover_layer_weights& lw, float* xres, RowMa
       launch_reduce_add_norm(xres, H, x->partial, sd, (size_t)M * H, H, next_gain, c.dtype, c.rms_eps, A, M, H, x->st); }
     return;
   }
-  { Scope s(x, KC_RMSNORM); launch_rmsnorm(xres, H, lw.attn_norm, c.dtype, c.rms_eps, x->a_norm, H, H, M, x->st); }
-  { int off = 0;
-    for (int sgm = 0; sgm < 3; ++sgm) {
+  // (few rows: the norm and the three projections in one launch, below the norm, both projections and SwiGLU)
+  SmallGemm g3[3];
+  for (int sgm = 0, off = 0; sgm < 3; off += sn[sgm++]) g3[sgm] = SmallGemm{xres, H, ws[sgm], nullptr, lw.attn_norm, x->qkv + off, x->QKVN, sn[sgm]};
+  bool small;
+  { Scope s(x, KC_GEMM_QKV); small = launch_gemm_small(g3, 3, false, c.dtype, M, H, 0, c.rms_eps, x->st); }
+  if (!small) {
+    { Scope s(x, KC_RMSNORM); launch_rmsnorm(xres, H, lw.attn_norm, c.dtype, c.rms_eps, x->a_norm, H, H, M, x->st); }
+    for (int sgm = 0, off = 0; sgm < 3; off += sn[sgm++])
       gemm_generic(x, KC_GEMM_QKV, x->a_norm, H, ws[sgm], nullptr, x->qkv + off, x->QKVN, M, sn[sgm], H, 0);
-      off += sn[sgm];
-    } }
+  }
   { Scope s(x, KC_ROPE_KV);
     launch_rope_kv_write(x->qkv, x->QKVN, 1, 0, x->cos_t, x->sin_t, x->q_rot, x->NQD, kc_layer, vc_layer, x->kvdtype,
                          kvl, base_len, c.n_q_heads, rm, x->d_err, nullptr, nullptr, 0.f, x->st); }
@@ -488,10 +492,15 @@ void run_layer(clover_ctx* x, const clover_layer_weights& lw, float* xres, RowMa
     launch_attn_generic(x->q_rot, x->NQD, kc_layer, vc_layer, x->kvdtype, kvl, base_len, anc, c.n_q_heads, x->attn_out,
                         x->NQD, FragPlanes{}, rm, x->st, anc_stride, iv); }
   gemm_generic(x, KC_GEMM_WO, x->attn_out, x->NQD, lw.wo, nullptr, xres, H, M, H, x->NQD, 1);
-  { Scope s(x, KC_RMSNORM); launch_rmsnorm(xres, H, lw.ffn_norm, c.dtype, c.rms_eps, x->a_norm, H, H, M, x->st); }
-  gemm_generic(x, KC_GEMM_GATEUP, x->a_norm, H, lw.w_gate, nullptr, x->tmp_ffn, F, M, F, H, 0);
-  gemm_generic(x, KC_GEMM_GATEUP, x->a_norm, H, lw.w_up, nullptr, x->h_ffn, F, M, F, H, 0);
-  { Scope s(x, KC_ELTWISE); launch_swiglu(x->tmp_ffn, x->h_ffn, x->h_ffn, (size_t)M * F, x->st); }
+  const SmallGemm gu[2] = {{xres, H, lw.w_gate, nullptr, lw.ffn_norm, x->h_ffn, F, F}, {xres, H, lw.w_up, nullptr, lw.ffn_norm, nullptr, F, F}};
+  { Scope s(x, KC_GEMM_GATEUP); small = launch_gemm_small(gu, 2, true, c.dtype, M, H, 0, c.rms_eps, x->st); }
+  if (!small) {
+    { Scope s(x, KC_RMSNORM); launch_rmsnorm(xres, H, lw.ffn_norm, c.dtype, c.rms_eps, x->a_norm, H, H, M, x->st); }
+    gemm_generic(x, KC_GEMM_GATEUP, x->a_norm, H, lw.w_gate, nullptr, x->tmp_ffn, F, M, F, H, 0);
+    gemm_generic(x, KC_GEMM_GATEUP, x->a_norm, H, lw.w_up, nullptr, x->h_ffn, F, M, F, H, 0);
+    Scope s(x, KC_ELTWISE);
+    launch_swiglu(x->tmp_ffn, x->h_ffn, x->h_ffn, (size_t)M * F, x->st);
+  }
   gemm_generic(x, KC_GEMM_DOWN, x->h_ffn, F, lw.w_down, nullptr, xres, H, M, H, F, 1);
 }
 
@@ -543,10 +552,16 @@ void run_ad(clover_ctx* x, const clover_ad_weights& ad, const float* xin, const 
     launch_reduce(x->partial, sp, (size_t)rows * 2 * H, 2 * H, ad.bk, c.dtype, x->ad_k, H, rows, H, 0, x->st);
     launch_reduce(x->partial + H, sp, (size_t)rows * 2 * H, 2 * H, ad.bv, c.dtype, x->ad_v, H, rows, H, 0, x->st);
   } else {
-    { Scope s(x, KC_RMSNORM); launch_rmsnorm(xin, H, ad.norm, c.dtype, c.rms_eps, x->a_norm, H, H, rows, x->st); }
-    gemm_generic(x, KC_GEMM_DRAFT, x->a_norm, H, ad.wq, ad.bq, x->ad_q, H, rows, H, H, 0);
-    gemm_generic(x, KC_GEMM_DRAFT, y, H, ad.wk, ad.bk, x->ad_k, H, rows, H, H, 0);
-    gemm_generic(x, KC_GEMM_DRAFT, y, H, ad.wv, ad.bv, x->ad_v, H, rows, H, H, 0);
+    const SmallGemm g[3] = {{xin, H, ad.wq, ad.bq, ad.norm, x->ad_q, H, H}, {y, H, ad.wk, ad.bk, nullptr, x->ad_k, H, H},
+                            {y, H, ad.wv, ad.bv, nullptr, x->ad_v, H, H}};
+    bool small;
+    { Scope s(x, KC_GEMM_DRAFT); small = launch_gemm_small(g, 3, false, c.dtype, rows, H, 0, c.rms_eps, x->st); }
+    if (!small) {
+      { Scope s(x, KC_RMSNORM); launch_rmsnorm(xin, H, ad.norm, c.dtype, c.rms_eps, x->a_norm, H, H, rows, x->st); }
+      gemm_generic(x, KC_GEMM_DRAFT, x->a_norm, H, ad.wq, ad.bq, x->ad_q, H, rows, H, H, 0);
+      gemm_generic(x, KC_GEMM_DRAFT, y, H, ad.wk, ad.bk, x->ad_k, H, rows, H, H, 0);
+      gemm_generic(x, KC_GEMM_DRAFT, y, H, ad.wv, ad.bv, x->ad_v, H, rows, H, H, 0);
+    }
   }
   { Scope s(x, KC_AD_GATE);
     launch_ad_gate(xin, H, x->ad_q, x->ad_k, x->ad_v, H, c.ad_heads, out, H, nullptr, 0, rows, x->st); }
@@ -575,6 +590,16 @@ void lm_head_fast(clover_ctx* x, FragPlanes A, int rows, float* out) {
   launch_gemm_tile(g, x->st);
 }
 
+// out[rows, vocab] = RMSNorm(src) * gain through the LM head (generic path)
+void lm_head_generic(clover_ctx* x, const float* src, const void* gain, int rows, float* out) {
+  const clover_config& c = x->cfg;
+  const int H = x->H;
+  const SmallGemm g{src, H, x->w.lm_head, nullptr, gain, out, c.vocab, c.vocab};
+  { Scope s(x, KC_GEMM_LMHEAD); if (launch_gemm_small(&g, 1, false, c.dtype, rows, H, 0, c.rms_eps, x->st)) return; }
+  { Scope s(x, KC_RMSNORM); launch_rmsnorm(src, H, gain, c.dtype, c.rms_eps, x->a_norm, H, H, rows, x->st); }
+  gemm_generic(x, KC_GEMM_LMHEAD, x->a_norm, H, x->w.lm_head, nullptr, out, c.vocab, rows, c.vocab, H, 0);
+}
+
 // logits of `rows` contiguous rows of g through the head norm and the shared LM head, then top-k
 void run_head(clover_ctx* x, const float* g, int rows, int k /* 0: logits only, left in x->z */) {
   const clover_config& c = x->cfg;
@@ -583,8 +608,7 @@ void run_head(clover_ctx* x, const float* g, int rows, int k /* 0: logits only, 
     const FragPlanes A = norm_planes(x, g, x->w.head_norm, rows);
     lm_head_fast(x, A, rows, x->z);
   } else {
-    { Scope s(x, KC_RMSNORM); launch_rmsnorm(g, H, x->w.head_norm, c.dtype, c.rms_eps, x->a_norm, H, H, rows, x->st); }
-    gemm_generic(x, KC_GEMM_LMHEAD, x->a_norm, H, x->w.lm_head, nullptr, x->z, c.vocab, rows, c.vocab, H, 0);
+    lm_head_generic(x, g, x->w.head_norm, rows, x->z);
   }
   if (k > 0) { Scope s(x, KC_TOPK); launch_topk(x->z, c.vocab, c.vocab, rows, k, x->cand, x->topk_ids, x->st); }
 }
@@ -1091,8 +1115,7 @@ int verify_tree(clover_ctx* x, int32_t batch, const int32_t* tree_tokens, float*
   if (x->fast) {
     lm_head_fast(x, frag_planes(x->a_norm, M), M, logits);
   } else {
-    { Scope s(x, KC_RMSNORM); launch_rmsnorm(hidden, H, x->w.final_norm, c.dtype, c.rms_eps, x->a_norm, H, H, M, x->st); }
-    gemm_generic(x, KC_GEMM_LMHEAD, x->a_norm, H, x->w.lm_head, nullptr, logits, c.vocab, M, c.vocab, H, 0);
+    lm_head_generic(x, hidden, x->w.final_norm, M, logits);
   }
   return finish(x, "verify_tree");
 }
@@ -1176,9 +1199,7 @@ int clover_prefill(clover_ctx* x, int32_t b, const int32_t* tokens, int32_t n, f
       if (x->fast) {
         lm_head_fast(x, norm_planes(x, xres + (size_t)(M - 1) * H, x->w.final_norm, 1), 1, logits_last);
       } else {
-        { Scope s(x, KC_RMSNORM);
-          launch_rmsnorm(xres + (size_t)(M - 1) * H, H, x->w.final_norm, c.dtype, c.rms_eps, x->a_norm, H, H, 1, x->st); }
-        gemm_generic(x, KC_GEMM_LMHEAD, x->a_norm, H, x->w.lm_head, nullptr, logits_last, c.vocab, 1, c.vocab, H, 0);
+        lm_head_generic(x, xres + (size_t)(M - 1) * H, x->w.final_norm, 1, logits_last);
       }
       hipMemcpyAsync(hid_last, xres + (size_t)(M - 1) * H, (size_t)H * sizeof(float), hipMemcpyDeviceToDevice, x->st);
       if (next_tok_out) {

@@ -3,6 +3,9 @@
 // as the on-device cross-check of the MFMA path.
 #include "clover_internal.h"
 
+#include <algorithm>
+#include <type_traits>
+
 namespace clv {
 
 // ------------------------------------------------------------------------------------------
@@ -331,18 +334,29 @@ void launch_rope_kv_write(const float* qkv, int ldqkv, int qkv_splits, size_t qk
 // anc == null: the rows form a chain (row i sees new rows 0..i), any number of rows.
 // iv != null: new row w is visible to row i iff enter[w] <= enter[i] <= exit[w] (interval labels, two ints per node).
 // ------------------------------------------------------------------------------------------
-template <typename KT>
-__global__ void attn_generic_kernel(const float* __restrict__ q, int ldq, const KT* __restrict__ kc,
-                                    const KT* __restrict__ vc, KVLayout kv, const int* __restrict__ base_len,
-                                    const unsigned long long* __restrict__ anc, int n_q, float* __restrict__ out,
-                                    int ldo, FragPlanes planes, RowMap rm,
-                                    int anc_stride, const int* __restrict__ iv) {
-  __shared__ float qs[128];
-  __shared__ float ps[64];
+// What bounds it: memory round trips.  A lane fetches its key's row and its channel's 64 values in 16-byte pieces that are all
+// requested before the first is used (3 launches of 16 rows x 80 keys: 64 us with one 4-byte load after the other, 22 so).
+// Sums run in key and channel order as before.
+__device__ __forceinline__ float4 ldkv4(const float* p, size_t i, size_t) { return *(const float4*)(p + i); }
+__device__ __forceinline__ float4 ldkv4(const bf16_t* p, size_t i, size_t plane) {
+  const uint2 h = *(const uint2*)(p + i), l = *(const uint2*)(p + i + plane);
+  return make_float4(__uint_as_float(h.x << 16) + __uint_as_float(l.x << 16),
+                     __uint_as_float(h.x & 0xFFFF0000u) + __uint_as_float(l.x & 0xFFFF0000u),
+                     __uint_as_float(h.y << 16) + __uint_as_float(l.y << 16),
+                     __uint_as_float(h.y & 0xFFFF0000u) + __uint_as_float(l.y & 0xFFFF0000u));
+}
+template <typename KT, int D>
+__global__ __launch_bounds__(64) void attn_generic_kernel(const float* __restrict__ q, int ldq, const KT* __restrict__ kc,
+                                                          const KT* __restrict__ vc, KVLayout kv, const int* __restrict__ base_len,
+                                                          const unsigned long long* __restrict__ anc, int n_q,
+                                                          float* __restrict__ out, int ldo, FragPlanes planes, RowMap rm,
+                                                          int anc_stride, const int* __restrict__ iv) {
+  __shared__ __attribute__((aligned(16))) float qs[D];
+  __shared__ __attribute__((aligned(16))) float ps[64];
   const int h = blockIdx.x, i = blockIdx.y, b = blockIdx.z, lane = threadIdx.x;
   const int nv = rows_valid(rm, b);
   if (i >= nv) return;
-  const int d = kv.d, n_kv = kv.n_kv;
+  const int n_kv = kv.n_kv;
   const int L = base_len[b];
   if (L + nv > kv.max_seq) return;
   const size_t row = (size_t)b * rm.R + i;
@@ -352,10 +366,12 @@ __global__ void attn_generic_kernel(const float* __restrict__ q, int ldq, const 
   const unsigned long long a1 = bits ? anc[2 * ((size_t)b * anc_stride + i) + 1] : 0ull;
   const int my_enter = iv ? iv[2 * ((size_t)b * anc_stride + i)] : 0;
   const int g = h / (n_q / n_kv);
-  const float scale = 1.0f / sqrtf((float)d);
-  for (int c = lane; c < d; c += 64) qs[c] = q[row * ldq + h * d + c] * scale;
+  const float scale = 1.0f / sqrtf((float)D);
+  for (int c = lane; c < D; c += 64) qs[c] = q[row * ldq + h * D + c] * scale;
   __syncthreads();
-  float mrun = -INFINITY, lrun = 0.f, o0 = 0.f, o1 = 0.f;
+  float mrun = -INFINITY, lrun = 0.f, o[D / 64];
+#pragma unroll
+  for (int u = 0; u < D / 64; ++u) o[u] = 0.f;
   const int total = L + rm.n;
   const int ntiles = (total + 63) / 64;
   for (int t = 0; t < ntiles; ++t) {
@@ -367,59 +383,82 @@ __global__ void attn_generic_kernel(const float* __restrict__ q, int ldq, const 
       else if (iv) vis = iv[2 * ((size_t)b * anc_stride + w)] <= my_enter && my_enter <= iv[2 * ((size_t)b * anc_stride + w) + 1];
       else vis = ((w < 64 ? (a0 >> w) : (a1 >> (w - 64))) & 1ull) != 0ull;
     }
-    float sc = -INFINITY;
-    if (vis) {
-      const KT* kr = kc + kv_k_at(kv, b, s, g);
-      float acc = 0.f;
-      for (int c = 0; c < d; ++c) acc += qs[c] * ldkv(kr, c, kv.plane);
-      sc = acc;
+    // (slots of the tile behind the cache's last page are read from the last page and never used)
+    const size_t kr = kv_k_at(kv, b, min(s, kv.max_seq - 1), g);
+    float4 kx[D / 4];
+#pragma unroll
+    for (int c = 0; c < D / 4; ++c) kx[c] = ldkv4(kc, kr + c * 4, kv.plane);
+    float4 vx[16];
+    auto load_v = [&](int u) __attribute__((always_inline)) {   // channel lane + 64 u of the tile's two pages
+#pragma unroll
+      for (int pg = 0; pg < 2; ++pg) {
+        const size_t at = kv_v_at(kv, b, g, lane + 64 * u, min(t * 64 + pg * KV_PAGE, kv.max_seq - KV_PAGE));
+#pragma unroll
+        for (int c = 0; c < 8; ++c) vx[pg * 8 + c] = ldkv4(vc, at + c * 4, kv.plane);
+      }
+    };
+    load_v(0);
+    float acc = 0.f;
+#pragma unroll
+    for (int c = 0; c < D / 4; ++c) {
+      const float4 qv = *(const float4*)(qs + c * 4);
+      acc += qv.x * kx[c].x; acc += qv.y * kx[c].y; acc += qv.z * kx[c].z; acc += qv.w * kx[c].w;
     }
+    const float sc = vis ? acc : -INFINITY;
     const float mnew = fmaxf(mrun, wave_max(sc));
     if (mnew == -INFINITY) continue;  // uniform across the wave
     const float p = vis ? expf(sc - mnew) : 0.f;
     const float corr = (mrun == -INFINITY) ? 0.f : expf(mrun - mnew);
     lrun = lrun * corr + wave_sum(p);
-    o0 *= corr;
-    o1 *= corr;
+#pragma unroll
+    for (int u = 0; u < D / 64; ++u) o[u] *= corr;
     mrun = mnew;
     __syncthreads();
     ps[lane] = p;
     __syncthreads();
-    const int jmax = min(64, total - t * 64);
-    for (int j = 0; j < jmax; ++j) {
-      const float pj = ps[j];
-      if (pj != 0.f) {
-        o0 += pj * ldkv(vc, kv_v_at(kv, b, g, lane, t * 64 + j), kv.plane);
-        if (d > 64) o1 += pj * ldkv(vc, kv_v_at(kv, b, g, lane + 64, t * 64 + j), kv.plane);
+#pragma unroll
+    for (int u = 0; u < D / 64; ++u) {
+      if (u > 0) load_v(u);
+#pragma unroll
+      for (int c = 0; c < 16; ++c) {   // (a hidden key's value, or an unwritten slot's, has no part in the sum whatever it holds)
+        const float4 pj = *(const float4*)(ps + c * 4);
+        o[u] += pj.x != 0.f ? pj.x * vx[c].x : 0.f;
+        o[u] += pj.y != 0.f ? pj.y * vx[c].y : 0.f;
+        o[u] += pj.z != 0.f ? pj.z * vx[c].z : 0.f;
+        o[u] += pj.w != 0.f ? pj.w * vx[c].w : 0.f;
       }
     }
   }
   const float inv = 1.0f / lrun;
-  if (planes.p) {
-    auto put = [&](int c, float v) {
+#pragma unroll
+  for (int u = 0; u < D / 64; ++u) {
+    const int c = h * D + 64 * u + lane;
+    const float v = o[u] * inv;
+    if (planes.p) {
       bf16_t* dst = planes.p + frag_at(planes, (int)row, c);
       const bf16_t hb = f32_to_bf16(v);
       dst[0] = hb;
       dst[512] = f32_to_bf16(v - bf16_to_f32(hb));
-    };
-    put(h * d + lane, o0 * inv);
-    if (d > 64) put(h * d + 64 + lane, o1 * inv);
-    return;
+    } else {
+      out[row * ldo + c] = v;
+    }
   }
-  out[row * ldo + h * d + lane] = o0 * inv;
-  if (d > 64) out[row * ldo + h * d + 64 + lane] = o1 * inv;
 }
 
 void launch_attn_generic(const float* q, int ldq, const void* k_cache, const void* v_cache, int kvdtype, KVLayout kv,
                          const int* base_len, const unsigned long long* anc, int n_q, float* out, int ldo,
                          FragPlanes planes, RowMap rm, hipStream_t st, int anc_stride, const int* iv) {
-  dim3 grid(n_q, rm.n, rm.B);
-  if (kvdtype == 0)
-    attn_generic_kernel<float><<<grid, 64, 0, st>>>(q, ldq, (const float*)k_cache, (const float*)v_cache, kv, base_len,
-                                                    anc, n_q, out, ldo, planes, rm, anc_stride, iv);
-  else
-    attn_generic_kernel<bf16_t><<<grid, 64, 0, st>>>(q, ldq, (const bf16_t*)k_cache, (const bf16_t*)v_cache, kv,
-                                                     base_len, anc, n_q, out, ldo, planes, rm, anc_stride, iv);
+  const dim3 grid(n_q, rm.n, rm.B);
+  auto go = [&](auto kc, auto vc, auto dc) {
+    using KT = std::remove_const_t<std::remove_pointer_t<decltype(kc)>>;
+    attn_generic_kernel<KT, decltype(dc)::value><<<grid, 64, 0, st>>>(q, ldq, kc, vc, kv, base_len, anc, n_q, out, ldo, planes, rm, anc_stride, iv);
+  };
+  auto with_d = [&](auto kc, auto vc) {   // head_dim is 64 or 128
+    if (kv.d == 64) go(kc, vc, std::integral_constant<int, 64>{});
+    else go(kc, vc, std::integral_constant<int, 128>{});
+  };
+  if (kvdtype == 0) with_d((const float*)k_cache, (const float*)v_cache);
+  else with_d((const bf16_t*)k_cache, (const bf16_t*)v_cache);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -483,78 +522,170 @@ __global__ __launch_bounds__(256) void gemm_generic_kernel(const float* __restri
 // bounds a 16 x 256 x 256 product in 64 x 64 tiles is a chain of 16 K steps with two barriers and a memory round trip
 // each on 4 workgroups, 22 us; here it is one round trip on 64 wavefronts, 4 us.  Beyond that its loads bound it, 20
 // loads of 16 bytes per 256 multiply-adds of a lane, out of the L2: 64 x 4096 x 14336 198 us (the tiles 1960).
-constexpr int GS_ROWS = 16, GS_COLS = 4;
+constexpr int GS_ROWS = 16, GS_COLS = 4, GS_WAVES = 4;
 __device__ __forceinline__ float4 ldw4(const float* w) { return *(const float4*)w; }
 __device__ __forceinline__ float4 ldw4(const bf16_t* w) {
   const uint2 u = *(const uint2*)w;
   return make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xFFFF0000u), __uint_as_float(u.y << 16),
                      __uint_as_float(u.y & 0xFFFF0000u));
 }
-template <typename WT>
-__global__ __launch_bounds__(64) void gemm_small_kernel(const float* __restrict__ X, int ldx, const WT* __restrict__ W,
-                                                        const WT* __restrict__ bias, float* __restrict__ Y, int ldy,
-                                                        int M, int N, int K, int mode) {
-  const int lane = threadIdx.x, n0 = blockIdx.x * GS_COLS, m0 = blockIdx.y * GS_ROWS;
-  float acc[64];   // [column][row]
+// Sums over the lanes of a wavefront without the LDS: 2 O values per lane become one per lane, each step halving the values
+// and adding the two lanes that differ in bit O (for O = 4: and in the bits below, which are summed over anyway).
+template <int O>
+__device__ __forceinline__ float add_halves(float a, float b) {   // lanes without bit O: the pair's sum of a, with it: of b
+  const unsigned ua = __float_as_uint(a), ub = __float_as_uint(b);
+  if constexpr (O == 32) { const auto s = __builtin_amdgcn_permlane32_swap(ua, ub, false, false); return __uint_as_float(s[0]) + __uint_as_float(s[1]); }
+  else { const auto s = __builtin_amdgcn_permlane16_swap(ua, ub, false, false); return __uint_as_float(s[0]) + __uint_as_float(s[1]); }
+}
+template <int O>
+__device__ __forceinline__ float add_pair(float v) {   // the partner: O 8 row_ror:8, 4 row_half_mirror, 2 and 1 quad_perm
+  constexpr int ctrl = O == 8 ? 0x128 : O == 4 ? 0x141 : O == 2 ? 0x4E : 0xB1;
+  return v + __uint_as_float(__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), ctrl, 0xF, 0xF, true));
+}
+template <int O>
+__device__ __forceinline__ void exchange_sums(float* v, int lane) {
+#pragma unroll
+  for (int i = 0; i < O; ++i) {
+    if constexpr (O >= 16) {
+      v[i] = add_halves<O>(v[i], v[i + O]);
+    } else {
+      const float a = add_pair<O>(v[i]), b = add_pair<O>(v[i + O]);
+      v[i] = (lane & O) ? b : a;
+    }
+  }
+  if constexpr (O > 1) exchange_sums<O / 2>(v, lane);
+}
+// One launch takes up to three products over the same rows and K (blocks of the second behind those of the first), sums the
+// squares of its rows on the way where a product's input is to be normalised (RMSNorm's factor belongs to the row and is
+// applied to the finished sums, its gain to the weights), and for SwiGLU computes two gate and the two up columns that belong
+// to them in one wavefront: a fp32 step of 16 rows is a chain of launches of 3 to 4 us each, whatever they do (87 -> 52 of
+// them, 351 -> 188 us of kernels, with the attention above).
+struct SmallArgs {
+  SmallGemm g[3];
+  int first[3];       // first column block of each product
+  int M, K, mode, swiglu;
+  float eps;
+};
+template <typename WT, bool NORM, bool SWIGLU>
+__global__ __launch_bounds__(64 * GS_WAVES) void gemm_small_kernel(SmallArgs a) {
+  __shared__ float part[2][GS_WAVES][64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6, cb = blockIdx.x, m0 = blockIdx.y * GS_ROWS, M = a.M, K = a.K;
+  const int which = SWIGLU ? 0 : cb >= a.first[2] ? 2 : cb >= a.first[1] ? 1 : 0;
+  const SmallGemm g = a.g[which];
+  const float* const X = g.X;
+  const WT* const W = (const WT*)g.W;
+  const int N = g.N, n0 = (cb - (SWIGLU ? 0 : a.first[which])) * (SWIGLU ? 2 : GS_COLS);
+  const WT* wrow[GS_COLS];
+#pragma unroll
+  for (int c = 0; c < GS_COLS; ++c)
+    wrow[c] = SWIGLU ? (c < 2 ? W : (const WT*)a.g[1].W) + (size_t)min(n0 + (c & 1), N - 1) * K : W + (size_t)min(n0 + c, N - 1) * K;
+  float acc[64], ss[GS_ROWS];   // [column][row], sums of squares
 #pragma unroll
   for (int i = 0; i < 64; ++i) acc[i] = 0.f;
-  for (int k0 = 0; k0 < K; k0 += 256) {
+#pragma unroll
+  for (int r = 0; r < GS_ROWS; ++r) ss[r] = 0.f;
+  for (int k0 = wave * 256; k0 < K; k0 += waves * 256) {
     const int k = k0 + lane * 4, kc = min(k, K - 4);   // (K % 4 == 0; lanes past K multiply zeros)
     const bool in = k < K;
-    float4 w[GS_COLS], x[GS_ROWS];
+    float4 w[GS_COLS], x[GS_ROWS], gn;
 #pragma unroll
-    for (int c = 0; c < GS_COLS; ++c) w[c] = ldw4(W + (size_t)min(n0 + c, N - 1) * K + kc);
+    for (int c = 0; c < GS_COLS; ++c) w[c] = ldw4(wrow[c] + kc);
+    if (NORM && g.gain) gn = ldw4((const WT*)g.gain + kc);
 #pragma unroll
-    for (int r = 0; r < GS_ROWS; ++r) x[r] = *(const float4*)(X + (size_t)min(m0 + r, M - 1) * ldx + kc);
+    for (int r = 0; r < GS_ROWS; ++r) x[r] = *(const float4*)(X + (size_t)min(m0 + r, M - 1) * g.ldx + kc);
     if (!in) {
 #pragma unroll
       for (int c = 0; c < GS_COLS; ++c) w[c] = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
       for (int r = 0; r < GS_ROWS; ++r) x[r] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
+    if (NORM && g.gain) {   // uniform
+#pragma unroll
+      for (int c = 0; c < GS_COLS; ++c) { w[c].x *= gn.x; w[c].y *= gn.y; w[c].z *= gn.z; w[c].w *= gn.w; }
+#pragma unroll
+      for (int r = 0; r < GS_ROWS; ++r) ss[r] += x[r].x * x[r].x + x[r].y * x[r].y + x[r].z * x[r].z + x[r].w * x[r].w;
+    }
 #pragma unroll
     for (int c = 0; c < GS_COLS; ++c)
 #pragma unroll
       for (int r = 0; r < GS_ROWS; ++r) {
-        float a = acc[c * GS_ROWS + r];
-        a += x[r].x * w[c].x; a += x[r].y * w[c].y; a += x[r].z * w[c].z; a += x[r].w * w[c].w;
-        acc[c * GS_ROWS + r] = a;
+        float v = acc[c * GS_ROWS + r];
+        v += x[r].x * w[c].x; v += x[r].y * w[c].y; v += x[r].z * w[c].z; v += x[r].w * w[c].w;
+        acc[c * GS_ROWS + r] = v;
       }
   }
-  // 64 sums over 64 lanes: each step halves the sums a lane holds and pairs it with the lane `o` away
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const bool up = (lane & o) != 0;
-#pragma unroll
-    for (int i = 0; i < o; ++i) {
-      const float keep = up ? acc[i + o] : acc[i], send = up ? acc[i] : acc[i + o];
-      acc[i] = keep + __shfl_xor(send, o, 64);
-    }
-  }
-  const int m = m0 + (lane & 15), n = n0 + (lane >> 4);
-  if (m >= M || n >= N) return;
+  exchange_sums<32>(acc, lane);   // lane's sum: column lane / 16, row lane % 16
+  const int m = m0 + (lane & 15), n = n0 + (SWIGLU ? (lane >> 4) & 1 : lane >> 4);
   float v = acc[0];
-  if (bias) v += ldf(bias, n);
-  float* y = Y + (size_t)m * ldy + n;
-  *y = mode == 1 ? *y + v : v;
+  if (NORM && g.gain) {   // the same for the 16 sums of squares: lane's row is lane % 16
+    exchange_sums<8>(ss, lane);
+    ss[0] = add_halves<16>(ss[0], ss[0]);
+    ss[0] = add_halves<32>(ss[0], ss[0]);
+  }
+  if (waves > 1) {   // uniform: the wavefronts' sums, in their order
+    part[0][wave][lane] = v;
+    part[1][wave][lane] = ss[0];
+    __syncthreads();
+    if (wave > 0) return;
+    for (int w = 1; w < waves; ++w) { v += part[0][w][lane]; ss[0] += part[1][w][lane]; }
+  }
+  if (NORM && g.gain) {
+    v *= 1.0f / sqrtf(ss[0] / (float)K + a.eps);
+  }
+  if (SWIGLU) {   // lanes 0 .. 31 hold the gate, 32 .. 63 the up factor of the same output
+    const float u = __uint_as_float(__builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false)[1]);
+    v = v / (1.0f + expf(-v)) * u;
+    if (lane >= 32) return;
+  }
+  if (m >= M || n >= N) return;
+  if (g.bias) v += ldf((const WT*)g.bias, n);
+  float* y = g.Y + (size_t)m * g.ldy + n;
+  *y = a.mode == 1 ? *y + v : v;
+}
+
+// Fewer 64 x 64 tiles than compute units: the tile kernel's time is its K chain, which the small kernel beats at every shape
+// measured up to there, by 27 times (few rows, K of 14336) down to twice (512 x 1024 x 256: 26.7 -> 13.2 us, 64 x 8192 x
+// 256: 26.4 -> 11.9).  (16-byte loads: rows of X and W must start on 16 bytes, 8 for bf16 weights.)
+static bool gemm_small_ok(const SmallGemm& g, int wdtype, int M, int K) {
+  const size_t walign = wdtype == 0 ? 15 : 7;
+  return (size_t)((g.N + 63) / 64) * ((M + 63) / 64) < 256 && K % 4 == 0 && g.ldx % 4 == 0 && ((uintptr_t)g.X & 15) == 0 &&
+         ((uintptr_t)g.W & walign) == 0 && ((uintptr_t)g.gain & walign) == 0;
+}
+template <typename WT>
+static void launch_small_one(const SmallArgs& a, bool norm, dim3 grid, hipStream_t st) {
+  const int nt = 64 * std::min(GS_WAVES, (a.K + 255) / 256);   // wavefronts share K: a round trip per 1024 columns (K 256 to 688 of the fp32 step: 4.8 -> 4.3 us)
+  if (a.swiglu && norm) gemm_small_kernel<WT, true, true><<<grid, nt, 0, st>>>(a);
+  else if (a.swiglu) gemm_small_kernel<WT, false, true><<<grid, nt, 0, st>>>(a);
+  else if (norm) gemm_small_kernel<WT, true, false><<<grid, nt, 0, st>>>(a);
+  else gemm_small_kernel<WT, false, false><<<grid, nt, 0, st>>>(a);
+}
+bool launch_gemm_small(const SmallGemm* g, int n, bool swiglu, int wdtype, int M, int K, int mode, float eps, hipStream_t st) {
+  SmallArgs a{};
+  bool norm = false;
+  int blocks = 0;
+  for (int i = 0; i < 3; ++i) {
+    a.first[i] = i < n ? blocks : 1 << 30;
+    if (i >= n) continue;
+    if (!gemm_small_ok(g[i], wdtype, M, K)) return false;
+    a.g[i] = g[i];
+    norm = norm || g[i].gain;
+    blocks += (g[i].N + GS_COLS - 1) / GS_COLS;
+  }
+  if (swiglu) blocks = (g[0].N + 1) / 2;
+  if (M <= 0 || blocks <= 0) return true;
+  a.M = M; a.K = K; a.mode = mode; a.swiglu = swiglu; a.eps = eps;
+  const dim3 grid(blocks, (M + GS_ROWS - 1) / GS_ROWS);
+  if (wdtype == 0) launch_small_one<float>(a, norm, grid, st);
+  else launch_small_one<bf16_t>(a, norm, grid, st);
+  return true;
 }
 
 void launch_gemm_generic(const float* X, int ldx, const void* W, const void* bias, int wdtype, float* Y, int ldy,
                          int M, int N, int K, int mode, hipStream_t st) {
   if (M <= 0 || N <= 0) return;
+  const SmallGemm g{X, ldx, W, bias, nullptr, Y, ldy, N};
+  if (launch_gemm_small(&g, 1, false, wdtype, M, K, mode, 0.f, st)) return;
   dim3 grid((N + 63) / 64, (M + 63) / 64);
-  // Fewer tiles than compute units: the tile kernel's time is its K chain, which the small kernel beats at every shape
-  // measured up to there, by 27 times (few rows, K of 14336) down to twice (512 x 1024 x 256: 26.7 -> 13.2 us, 64 x 8192 x
-  // 256: 26.4 -> 11.9).  (16-byte loads: rows of X and W must start on 16 bytes, 8 for bf16 weights.)
-  const size_t walign = wdtype == 0 ? 15 : 7;
-  if (grid.x * grid.y < 256 && K % 4 == 0 && ldx % 4 == 0 && ((uintptr_t)X & 15) == 0 && ((uintptr_t)W & walign) == 0) {
-    dim3 sgrid((N + GS_COLS - 1) / GS_COLS, (M + GS_ROWS - 1) / GS_ROWS);
-    if (wdtype == 0)
-      gemm_small_kernel<float><<<sgrid, 64, 0, st>>>(X, ldx, (const float*)W, (const float*)bias, Y, ldy, M, N, K, mode);
-    else
-      gemm_small_kernel<bf16_t><<<sgrid, 64, 0, st>>>(X, ldx, (const bf16_t*)W, (const bf16_t*)bias, Y, ldy, M, N, K, mode);
-    return;
-  }
   if (wdtype == 0)
     gemm_generic_kernel<float><<<grid, 256, 0, st>>>(X, ldx, (const float*)W, (const float*)bias, Y, ldy, M, N, K, mode);
   else
@@ -633,7 +764,7 @@ constexpr int TOPK_EPT = TOPK_CHUNK / 256;
 int topk_chunks(int V) { return (V + TOPK_CHUNK - 1) / TOPK_CHUNK; }
 
 __global__ __launch_bounds__(256) void topk_stage1_kernel(const float* __restrict__ z, int ldz, int V, int k,
-                                                          unsigned long long* __restrict__ cand) {
+                                                          unsigned long long* __restrict__ cand, int* __restrict__ out_ids) {
   __shared__ unsigned long long red[4];
   const int chunk = blockIdx.x, row = blockIdx.y, chunks = gridDim.x;
   unsigned long long key[TOPK_EPT];
@@ -651,7 +782,10 @@ __global__ __launch_bounds__(256) void topk_stage1_kernel(const float* __restric
 #pragma unroll
     for (int e = 0; e < TOPK_EPT; ++e)
       if (key[e] == best) key[e] = 0ull;
-    if (threadIdx.x == 0) cand[((size_t)row * chunks + chunk) * 16 + r] = best;
+    if (threadIdx.x == 0) {
+      if (out_ids) out_ids[row * 16 + r] = (int)(0xFFFFFFFFu - (unsigned)(best & 0xFFFFFFFFull));   // the only chunk
+      else cand[((size_t)row * chunks + chunk) * 16 + r] = best;
+    }
   }
 }
 
@@ -710,10 +844,14 @@ __global__ __launch_bounds__(256) void topk_stage2_kernel(const unsigned long lo
 void launch_topk(const float* z, int ldz, int V, int rows, int k, void* cand, int* out_ids, hipStream_t st) {
   if (rows <= 0) return;
   const int chunks = topk_chunks(V);  // chunks * k <= 2048 is checked at init (vocab <= 262144)
+  if (chunks == 1) {   // (a vocabulary of up to 2048: nothing to merge)
+    topk_stage1_kernel<<<dim3(1, rows), 256, 0, st>>>(z, ldz, V, k, (unsigned long long*)cand, out_ids);
+    return;
+  }
   if (k == 1 && V % 4 == 0 && ldz % 4 == 0 && ((uintptr_t)z & 15) == 0)
     argmax_stage1_kernel<<<dim3((chunks + 3) / 4, rows), 256, 0, st>>>(z, ldz, V, chunks, (unsigned long long*)cand);
   else
-    topk_stage1_kernel<<<dim3(chunks, rows), 256, 0, st>>>(z, ldz, V, k, (unsigned long long*)cand);
+    topk_stage1_kernel<<<dim3(chunks, rows), 256, 0, st>>>(z, ldz, V, k, (unsigned long long*)cand, nullptr);
   topk_stage2_kernel<<<rows, 256, 0, st>>>((const unsigned long long*)cand, chunks, k, out_ids);
 }
 
