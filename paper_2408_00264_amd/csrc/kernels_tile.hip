@@ -8,7 +8,7 @@
 // the staging loads at 80 % and 2.01), and everywhere the load path of a compute unit, which takes the activations as well as
 // the weights.
 //
-// Shape.  A workgroup of four wavefronts (2 x 2, one per SIMD; up to 16 rows 1 x 4) owns 32 RB rows x 32 CB columns; a wavefront RB x CB
+// Shape.  A workgroup of four wavefronts (2 x 2, one per SIMD; up to 16 rows 1 x 4) owns 32 RB rows x 32 CB columns (RB 1 to 5 and 8); a wavefront RB x CB
 // products of 16 x 16.  Both operands go global -> LDS directly, 32 columns of K per stage, as 1 KB blocks that are
 // contiguous in global memory too (one load instruction each), NBUF stages deep: the loads of stage s + NBUF are issued
 // while stage s is multiplied.  In flight per workgroup (mostly one to a compute unit): NBUF stages of 2 KB per 16 rows and
@@ -20,11 +20,11 @@
 // kernels it replaced, which read row-major planes: K-slice and panel form up to 64 rows, 128-row panel and 128 x 256
 // tiles above):
 //   rows        1          23         64         80         133    256
-//   gate+up     35.0 (43)  37.8 (49)  45.5 (55)  50.8 (80)  74.4   90.5 (101)
-//   down        18.9 (21)  20.4       25.6 (30)  27.8 (36)  37.4   53.9 (57)
-//   QKV          9.7 (12)  11.4       15.0 (18)  16.8 (27)  22.3   26.8 (34)
-//   Wo           6.6        8.5       11.0       13.4       16.9   21.7
-//   LM head    154        171        180        195        245    382
+//   gate+up     35.0 (43)  37.7 (49)  44.8 (55)  50.6 (80)  69.8   83.4 (101)
+//   down        18.9 (21)  20.4       25.4 (30)  27.2 (36)  36.3   51.4 (57)
+//   QKV          9.7 (12)  11.2       14.9 (18)  16.2 (27)  20.5   25.7 (34)
+//   Wo           6.6        8.8       11.1       12.9       15.8   20.6
+//   LM head    154        170        177        187        229    365
 // The same kernel on row-major planes (64-byte row pieces): gate+up 64.4 at 64 rows, 69.5 at 80, 107 at 256.
 // Many rows, tiles of up to 160 / of 256 rows (and half the staged bytes per product): gate+up 179 / 165 at 512, 351 / 327
 // at 1024, 701 / 652 at 2048, LM head 777 / 709 at 512, 3106 / 2785 at 2048, down 322 / 306 at 2048, QKV 159 / 146.
@@ -354,9 +354,9 @@ struct TilePick { int rb, cb, kp; };
 // instructions, of its 1 KB loads at 40 B/clk (what is left of the load path's 55 beside the LDS reads) and of an HBM
 // round trip shared by the stages in flight; rounds of workgroups over the compute units times stages, against the time
 // of the weight stream at 5.3 TB/s (fourth-power mean: near the crossing the two do not overlap freely), + start and
-// end of each round, + the partial tiles, written here and read by the consumer.  Over 75 launches (the five 8B shapes at
-// 15 row counts from 1 to 256, up to 63 combinations of tile and ranges each) the choice is the best or within 3 % of it,
-// except gate+up at 133 rows (74.4 us against 69.2 with one row tile of 160) and QKV at 110 (6 %).  So few rows take narrow tiles
+// end of each round, + the partial tiles, written here and read by the consumer.  Over 50 launches (the five 8B shapes at
+// ten row counts from 23 to 256, up to 63 combinations of tile and ranges each) the choice is the best or within 5 % of it,
+// except Wo at 112 rows (8 %: 22.2 us with its consumer against 20.6 with two row tiles of 96).  So few rows take narrow tiles
 // (the weight stream needs every compute unit), 256 rows of gate+up 2 x 128 tiles of 128 rows x 224 columns (one whole
 // round, where 256-column tiles leave 32 compute units idle), 80 rows one row tile of 96.
 // More than 256 rows over 1024 columns of K or more also have tiles of 256 rows (256 accumulators and 200 other registers a
