@@ -25,7 +25,7 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
 MFMA_BF16_PEAK_TFLOPS = 2500.0
-PREFILL_ROWS = 256           # the longest passes the prefill call makes (set-up; outside the timed region)
+PREFILL_ROWS = 256           # row capacity of the workspace, for long prompt passes (set-up; outside the timed region)
 
 
 def log(*a):
@@ -347,7 +347,7 @@ def main():
                      "kernel_trace_avg_launch_ms": trace_us * 1e-3 if trace_us else None,
                      "source_fingerprint": fp},
         "prefill": {"tokens": n_prompt, "ms": prefill_ms, "tokens_per_s": n_prompt / prefill_ms * 1e3,
-                    "rows_per_pass": max(PREFILL_ROWS, min(2048, max_seq)),
+                    "prefill_rows": PREFILL_ROWS,
                     "note": "set-up through clover_prefill, one sequence after the other; not part of the timed step"},
         "kernel_classes": classes,
         "kernels": kernels,

@@ -56,7 +56,7 @@ enum {
                                          dynamic tree still has at most 128 nodes) */
 #define CLOVER_MAX_DEPTH 8   /* upper bound on draft_depths */
 #define CLOVER_MAX_RANK 16   /* ranks are < 16 */
-#define CLOVER_MAX_PREFILL_ROWS 256 /* upper bound on prefill_rows; this value asks for the longest passes there are */
+#define CLOVER_MAX_PREFILL_ROWS 256 /* upper bound on prefill_rows */
 
 /* Model + capacity description.  Plain data, copied at init. */
 typedef struct {
@@ -70,10 +70,10 @@ typedef struct {
   int32_t draft_depths;  /* D: deepest tree level the draft head can fill (FC_0 .. FC_{D-1}) */
   int32_t max_batch, max_seq, max_nodes;   /* max_seq: a multiple of 32 (the page size of the caches) */
   int32_t flags;         /* CLOVER_FLAG_* */
-  int32_t prefill_rows;  /* prompt rows clover_prefill processes per pass (0: max_batch * max_nodes); the row buffers
-                            of the workspace are sized for max(max_batch * max_nodes, prefill_rows).  At most 256; 256
-                            leaves the length of a pass to the library, which takes up to min(2048, max_seq) rows at
-                            once and sizes the row buffers for them (about 1.5 GB at the LLaMA3-8B widths). */
+  int32_t prefill_rows;  /* the row buffers of the workspace are sized for max(max_batch * max_nodes, prefill_rows) rows of
+                            a step.  clover_prefill takes as many prompt rows per pass as the same memory holds without
+                            what only a step needs: at least min(256, that many), at most 2048 (LLaMA3-8B widths:
+                            256 rows for a 64-node tree alone, 2048 with prefill_rows = 256).  At most 256. */
 } clover_config;
 
 /* Static tree topology (Sec. 2.1: candidates merged on common prefixes form a tree).
@@ -221,7 +221,7 @@ int clover_accept_forced(clover_ctx *ctx, int32_t batch, const int32_t *tree_tok
 
 /* Prefill of one sequence (Sec. 1: the prefill phase that precedes the decode phase; Sec. 3.1, 3.3: the
  * Augmenting Block sees every earlier position paired with its follow-up token).  The n prompt tokens run through
- * the target in passes of up to prefill_rows rows (see there) -- every GEMM one weight pass over all rows of the pass, causal
+ * the target in passes of as many rows as the workspace holds (prefill_rows) -- every GEMM one weight pass over all rows of the pass, causal
  * attention over the cache and the pass's own rows, K/V written in place at slots len .. len+n-1 -- and the
  * LM head runs on the LAST row only.  The draft side pairs position i with token i+1 for i < n-1 (Attention
  * Decoder 1, then the Augmenting Block, causal over its own cache): n-1 rows appended there.  Afterwards

@@ -63,9 +63,20 @@ struct ProfEvent {
   hipEvent_t a, b;
 };
 
+// The buffers over the rows of a pass.  Two sets share the same memory: one for the rows of a step, all of it side by side with
+// what drafting and ranking need, and one for the longer passes of a prompt (carve).
+struct RowBufs {
+  int rows;                // their capacity
+  float *xd, *a_norm, *qkv, *q_rot, *attn_out, *h_ffn, *tmp_ffn, *cos_t, *sin_t, *ad_q, *ad_k, *ad_v, *d_xs, *d_e;
+  float* pl_y;             // planes of draft-side GEMM inputs
+  float* partial;          // partial tiles of the MFMA GEMMs over K ranges
+  float *o_part, *ml_part; // partial results of the MFMA attention
+  size_t split_rows;       // rows times key splits that they hold
+};
+
 }  // namespace
 
-struct clover_ctx {
+struct clover_ctx : RowBufs {
   clover_config cfg;
   hipStream_t st;
   clover_weights w;
@@ -74,15 +85,14 @@ struct clover_ctx {
   TreeHost tree;
   std::string err;
   // sizes
-  int R, max_rows, z_rows /* of z */, H, QKVN, NQD;
+  int R, H, QKVN, NQD;
+  RowBufs step, pass;      // clover_prefill works on `pass`, every other call on `step`
   KVLayout kv;
   size_t k_layer_elems, v_layer_elems, esz, kv_esz;
   int kvdtype;  // 0: fp32 cache elements; 1: (hi, lo) bf16 planes, same bytes (a random-init 32-layer stack amplifies
                 // plain bf16 cache rounding ~20x, so 16 mantissa bits are kept either way)
   size_t kv_layer_stride;  // cache elements (of the kvdtype's element type) per layer
   bool attn_fast;
-  float *o_part, *ml_part;
-  int attn_max_splits;
   // device regions
   int *d_seq_len, *d_aug_len, *d_err;
   int *d_depth, *d_parent, *d_rank, *d_first_child, *d_n_child, *d_lvl_nodes, *d_par_row;
@@ -91,13 +101,9 @@ struct clover_ctx {
   int* d_iv;               // interval labels of the static tree [R][2]
   bool interval;           // CLOVER_FLAG_INTERVAL_MASK: tree attention reads the labels instead of the bit sets
   char *kc, *vc, *aug_kc, *aug_vc;
-  float *xd, *a_norm, *qkv, *q_rot, *attn_out, *h_ffn, *tmp_ffn, *cos_t, *sin_t;
-  float *ad_q, *ad_k, *ad_v, *d_xs, *d_e, *d_cat, *d_g, *d_s, *d_state, *d_rootx, *z;
+  float *d_cat, *d_g, *d_s, *d_state, *d_rootx, *z;
   void* cand;
   int* topk_ids;
-  float* partial;          // partial tiles of the MFMA GEMMs over K ranges
-  size_t partial_bytes;
-  float* pl_y;             // planes of draft-side GEMM inputs
   char* packed;            // fragment-major copies of every linear weight (MFMA path)
   size_t packed_bytes;
   const void* lm_head_pk;
@@ -145,15 +151,6 @@ int check_config(const clover_config* c, std::string& why) {
   if (c->max_seq < c->max_nodes) return bad("max_seq smaller than max_nodes");
   if (!(c->rope_base > 1.f) || !(c->rms_eps > 0.f)) return bad("rope_base must be > 1 and rms_eps > 0");
   return CLOVER_OK;
-}
-
-// Rows of a prefill pass.  prefill_rows at its bound asks for the longest passes: 2048 rows, where the narrow GEMMs (QKV,
-// Wo, down) fill the chip without ranges of K and every weight byte staged serves 256 rows.  Per 256 rows and layer of the
-// 8B shape in passes of 256 / 512 / 1024 / 2048 rows: gate+up 91 / 83 / 82 / 81 us, down, Wo and QKV with the kernels behind
-// them 125 / 101 / 88 / 81.
-int prefill_pass_rows(const clover_config& c) {
-  if (c.prefill_rows == CLOVER_MAX_PREFILL_ROWS) return std::max(CLOVER_MAX_PREFILL_ROWS, std::min(2048, c.max_seq));
-  return std::min(std::max(c.max_batch * c.max_nodes, c.prefill_rows), CLOVER_MAX_PREFILL_ROWS);
 }
 
 int build_tree(const clover_config& cfg, const clover_tree* t, TreeHost& out, std::string& why) {
@@ -257,15 +254,78 @@ void model_gemm_shapes(const clover_config& c, std::vector<GemmShape>& v) {
 }
 bool mfma_shape_ok(int N, int K) { return N % 16 == 0 && K % 128 == 0; }
 
+// bytes of the partial tiles of the largest launch over up to `rows` rows, for each row count 32, 64 .. (the q and the k|v
+// projections of an Attention Decoder lie side by side)
+std::vector<size_t> partial_tile_bytes(const clover_config& c, int rows) {
+  std::vector<GemmShape> shapes;
+  model_gemm_shapes(c, shapes);
+  std::vector<size_t> v;
+  size_t most = 256;
+  for (int M = 32; M < rows + 32; M += 32) {   // one row count of each class of equal K ranges
+    auto bytes = [&](int N, int K) {   // (a tuning build that changes the ranges afterwards makes room for them here)
+      return (size_t)std::max(tile_gemm_pick_k_parts(M, N, K), tune_int("CLOVER_TILE_KP_ROOM", 1)) * std::min(M, rows) * N * sizeof(float);
+    };
+    for (const GemmShape& s : shapes) most = std::max(most, bytes(s.N, s.K));
+    most = std::max(most, align256(bytes(c.hidden, c.hidden)) + bytes(2 * c.hidden, c.hidden));
+    v.push_back(most);
+  }
+  return v;
+}
+
+// The layout of a prompt pass of `rows` rows: what is alive at the same time side by side, the rest on top of each other.
+// Returns its bytes.
+size_t carve_pass(const clover_ctx* x, char* base, int rows, size_t partial_bytes, RowBufs& b) {
+  const clover_config& c = x->cfg;
+  Carver cv{base};
+  const size_t H = c.hidden, rows16 = ((size_t)rows + 15) / 16 * 16;
+  b = RowBufs{};
+  b.rows = rows;
+  b.cos_t = cv.take<float>((size_t)rows * c.head_dim / 2);
+  b.sin_t = cv.take<float>((size_t)rows * c.head_dim / 2);
+  b.d_xs = cv.take<float>(rows * H);
+  b.xd = cv.take<float>(rows * H);
+  b.a_norm = cv.take<float>(rows16 * H);
+  Carver at = cv, ff = cv, ad = cv;   // attention | FFN | Attention Decoder 1
+  if (!x->fast) b.qkv = at.take<float>((size_t)rows * x->QKVN);
+  b.q_rot = at.take<float>((size_t)rows * x->NQD);
+  b.attn_out = at.take<float>(rows16 * x->NQD);
+  b.h_ffn = ff.take<float>(rows16 * c.ffn);
+  if (!x->fast) b.tmp_ffn = ff.take<float>((size_t)rows * c.ffn);
+  b.d_e = ad.take<float>(rows * H);
+  if (x->fast) b.pl_y = ad.take<float>(rows16 * H);
+  if (!(x->fast && ad_gate_fused_supported(c.hidden, c.ad_heads)))
+    for (float** p : {&b.ad_q, &b.ad_k, &b.ad_v}) *p = ad.take<float>(rows * H);
+  cv.off = std::max(at.off, std::max(ff.off, ad.off));
+  // The attention's partial results lie on the GEMMs' partial tiles: the projection's are summed by then.
+  b.partial = (float*)cv.take<char>(partial_bytes);
+  b.split_rows = x->attn_fast ? (partial_bytes - 256) / (sizeof(float) * (x->NQD + 2 * c.n_q_heads)) : 0;
+  b.o_part = b.partial;
+  b.ml_part = base ? (float*)((char*)b.partial + align256(b.split_rows * x->NQD * sizeof(float))) : nullptr;
+  return cv.off;
+}
+
+// Rows of a prompt pass: as many as the memory of a step's buffers holds, up to 2048, where the narrow GEMMs (QKV, Wo, down) fill
+// the chip without ranges of K and every weight byte staged serves 256 rows.  (8B shape, step buffers of 256 rows: 2048.)  Per
+// 256 rows and layer there in passes of 256 / 2048 rows: gate+up 91 / 75 us, QKV, Wo and down with the kernels behind them
+// 125 / 75.
+void carve_passes(clover_ctx* x, char* base, size_t bytes) {
+  const int most = std::min(2048, x->cfg.max_seq), own = std::min(x->step.rows, std::min(most, 256));
+  const std::vector<size_t> part = x->fast ? partial_tile_bytes(x->cfg, most) : std::vector<size_t>(most / 32, 256);
+  int rows = most;
+  while (rows > own && carve_pass(x, nullptr, rows, part[rows / 32 - 1], x->pass) > bytes)
+    rows = rows > 256 ? (rows - 1) / 256 * 256 : (rows - 1) / 32 * 32;
+  if (rows > own) carve_pass(x, base, rows, part[rows / 32 - 1], x->pass);
+  else carve_pass(x, base, own, x->fast ? partial_tile_bytes(x->cfg, own).back() : 256, x->pass);   // (a part of the step's: fits)
+}
+
 void carve(clover_ctx* x, char* base, size_t* total) {
   const clover_config& c = x->cfg;
   Carver cv{base};
   const int B = c.max_batch, R = c.max_nodes, H = c.hidden, d = c.head_dim;
-  const int own_rows = std::max(B * R, c.prefill_rows);
-  const int rows = std::max(own_rows, prefill_pass_rows(c));   // row capacity of every activation buffer
+  const int rows = std::max(B * R, c.prefill_rows);   // row capacity of every activation buffer
   const size_t rows16 = (size_t)(rows + 15) / 16 * 16;   // of those that hold planes in fragment order (whole row blocks)
   const size_t esz = c.dtype == CLOVER_DTYPE_F32 ? 4 : 2;
-  x->R = R; x->max_rows = rows; x->z_rows = own_rows; x->H = H; x->esz = esz;
+  x->R = R; x->H = H; x->esz = esz;
   x->kv_esz = 4;  // bytes per cached value in both formats
   x->NQD = c.n_q_heads * d;
   x->QKVN = (c.n_q_heads + 2 * c.n_kv_heads) * d;
@@ -289,31 +349,8 @@ void carve(clover_ctx* x, char* base, size_t* total) {
   x->vc = cv.take<char>(x->v_layer_elems * x->kv_esz * c.n_layers);
   x->aug_kc = cv.take<char>(x->k_layer_elems * x->kv_esz * c.aug_layers);
   x->aug_vc = cv.take<char>(x->v_layer_elems * x->kv_esz * c.aug_layers);
-  x->xd = cv.take<float>((size_t)rows * H);
-  x->a_norm = cv.take<float>(rows16 * H);
-  x->qkv = cv.take<float>((size_t)rows * x->QKVN);
-  x->q_rot = cv.take<float>((size_t)rows * x->NQD);
-  x->attn_out = cv.take<float>(rows16 * x->NQD);
-  x->h_ffn = cv.take<float>(rows16 * c.ffn);
-  x->tmp_ffn = cv.take<float>((size_t)rows * c.ffn);
-  x->cos_t = cv.take<float>((size_t)rows * d / 2);
-  x->sin_t = cv.take<float>((size_t)rows * d / 2);
-  x->ad_q = cv.take<float>((size_t)rows * H);
-  x->ad_k = cv.take<float>((size_t)rows * H);
-  x->ad_v = cv.take<float>((size_t)rows * H);
-  x->d_xs = cv.take<float>((size_t)rows * H);
-  x->d_e = cv.take<float>((size_t)rows * H);
-  x->d_cat = cv.take<float>(rows16 * 2 * H);
-  x->d_g = cv.take<float>((size_t)rows * H);
-  x->d_s = cv.take<float>((size_t)rows * H);
-  x->d_state = cv.take<float>((size_t)rows * H);
-  x->d_rootx = cv.take<float>((size_t)B * H);
-  x->z = cv.take<float>((size_t)own_rows * c.vocab);
-  x->cand = cv.take<unsigned long long>((size_t)own_rows * topk_chunks(c.vocab) * 16);
+  x->cand = cv.take<unsigned long long>((size_t)rows * topk_chunks(c.vocab) * 16);
   x->topk_ids = cv.take<int>((size_t)rows * 16);
-  x->topk_vals = cv.take<float>((size_t)rows * 16);
-  x->topk_lse = cv.take<float>((size_t)rows);
-  x->topk_aux = cv.take<float>(std::max((size_t)own_rows * topk_chunks(c.vocab), (size_t)B * sample_chunks(c.vocab)) * 2);
   x->dyn.cand_tok = cv.take<int>((size_t)B * DYN_MAX_CAND);
   x->dyn.cand_score = cv.take<float>((size_t)B * DYN_MAX_CAND);
   x->dyn.cand_par = cv.take<int>((size_t)B * DYN_MAX_CAND);
@@ -326,9 +363,7 @@ void carve(clover_ctx* x, char* base, size_t* total) {
   x->dyn.t_keep = cv.take<int>((size_t)rows);
   x->dyn.t_anc = cv.take<unsigned long long>((size_t)rows * 2);
   x->dyn.t_iv = cv.take<int>((size_t)rows * 2);
-  x->dyn_state = cv.take<float>((size_t)B * DYN_MAX_CAND * H);
-  // MFMA path: is every GEMM shape of this model supported, and how large can the partial tiles over K ranges get?
-  size_t pbytes = 256;
+  // MFMA path: is every GEMM shape of this model supported?
   bool fast = c.dtype == CLOVER_DTYPE_BF16 && !(c.flags & CLOVER_FLAG_GENERIC);
   if (fast) {
     std::vector<GemmShape> shapes;
@@ -339,16 +374,6 @@ void carve(clover_ctx* x, char* base, size_t* total) {
   }
   size_t packed_bytes = 0;
   if (fast) {
-    // partial tiles of the largest launch; the q and the k|v projections of an Attention Decoder lie side by side
-    std::vector<GemmShape> shapes;
-    model_gemm_shapes(c, shapes);
-    for (int M = 32; M < rows + 32; M += 32) {   // one row count of each class of equal K ranges
-      auto bytes = [&](int N, int K) {   // (a tuning build that changes the ranges afterwards makes room for them here)
-        return (size_t)std::max(tile_gemm_pick_k_parts(M, N, K), tune_int("CLOVER_TILE_KP_ROOM", 1)) * std::min(M, rows) * N * sizeof(float);
-      };
-      for (const GemmShape& s : shapes) pbytes = std::max(pbytes, bytes(s.N, s.K));
-      pbytes = std::max(pbytes, align256(bytes(H, H)) + bytes(2 * H, H));
-    }
     const size_t layer_elems = (size_t)x->QKVN * H + (size_t)H * x->NQD + (size_t)3 * c.ffn * H;
     packed_bytes = 2 * ((size_t)(c.n_layers + c.aug_layers) * layer_elems + (size_t)c.vocab * H + (size_t)7 * H * H +
                         (size_t)(c.draft_depths - 1) * 2 * H * H);
@@ -359,14 +384,51 @@ void carve(clover_ctx* x, char* base, size_t* total) {
   x->kvdtype = fast ? 1 : 0;
   x->kv_layer_stride = fast ? 2 * x->k_layer_elems : x->k_layer_elems;
   x->attn_fast = fast && attn_mfma_supported(d, c.n_q_heads, c.n_kv_heads, c.max_seq);
-  x->attn_max_splits = 16;
-  x->o_part = cv.take<float>(x->attn_fast ? (size_t)x->attn_max_splits * rows * x->NQD : 64);
-  x->ml_part = cv.take<float>(x->attn_fast ? (size_t)x->attn_max_splits * rows * c.n_q_heads * 2 : 64);
-  x->partial_bytes = pbytes;
-  x->partial = (float*)cv.take<char>(pbytes);
-  x->pl_y = cv.take<float>(rows16 * 2 * H);
+  // From here on nothing outlives the call that wrote it, so a prompt pass may lay it out in its own way.
+  const size_t own = cv.off;
+  RowBufs& b = x->step;
+  b.rows = rows;
+  b.xd = cv.take<float>((size_t)rows * H);
+  b.a_norm = cv.take<float>(rows16 * H);
+  b.qkv = cv.take<float>((size_t)rows * x->QKVN);
+  b.q_rot = cv.take<float>((size_t)rows * x->NQD);
+  b.attn_out = cv.take<float>(rows16 * x->NQD);
+  b.h_ffn = cv.take<float>(rows16 * c.ffn);
+  b.tmp_ffn = cv.take<float>((size_t)rows * c.ffn);
+  b.cos_t = cv.take<float>((size_t)rows * d / 2);
+  b.sin_t = cv.take<float>((size_t)rows * d / 2);
+  b.ad_q = cv.take<float>((size_t)rows * H);
+  b.ad_k = cv.take<float>((size_t)rows * H);
+  b.ad_v = cv.take<float>((size_t)rows * H);
+  b.d_xs = cv.take<float>((size_t)rows * H);
+  b.d_e = cv.take<float>((size_t)rows * H);
+  x->d_cat = cv.take<float>(rows16 * 2 * H);
+  x->d_g = cv.take<float>((size_t)rows * H);
+  x->d_s = cv.take<float>((size_t)rows * H);
+  x->d_state = cv.take<float>((size_t)rows * H);
+  x->d_rootx = cv.take<float>((size_t)B * H);
+  x->z = cv.take<float>((size_t)rows * c.vocab);
+  x->topk_vals = cv.take<float>((size_t)rows * 16);
+  x->topk_lse = cv.take<float>((size_t)rows);
+  x->topk_aux = cv.take<float>(std::max((size_t)rows * topk_chunks(c.vocab), (size_t)B * sample_chunks(c.vocab)) * 2);
+  x->dyn_state = cv.take<float>((size_t)B * DYN_MAX_CAND * H);
+  const size_t splits = 16;
+  b.split_rows = splits * rows;
+  b.o_part = cv.take<float>(x->attn_fast ? splits * rows * x->NQD : 64);
+  b.ml_part = cv.take<float>(x->attn_fast ? splits * rows * c.n_q_heads * 2 : 64);
+  b.partial = (float*)cv.take<char>(fast ? partial_tile_bytes(c, rows).back() : 256);
+  b.pl_y = cv.take<float>(rows16 * 2 * H);
+  static_cast<RowBufs&>(*x) = b;
+  if (base) carve_passes(x, base + own, cv.off - own);
   *total = cv.off;
 }
+
+// the buffers of prompt passes, for as long as this lives
+struct PassBufs {
+  clover_ctx* x;
+  explicit PassBufs(clover_ctx* ctx) : x(ctx) { static_cast<RowBufs&>(*x) = x->pass; }
+  ~PassBufs() { static_cast<RowBufs&>(*x) = x->step; }
+};
 
 // ---- profiling ------------------------------------------------------------------------------
 struct Scope {
@@ -438,7 +500,7 @@ void run_layer(clover_ctx* x, const clover_layer_weights& lw, float* xres, RowMa
   if (x->fast) {
     const FragPlanes A = frag_planes(x->a_norm, M), O = frag_planes(x->attn_out, M), Hf = frag_planes(x->h_ffn, M);
     bf16_t* const q_hi = (bf16_t*)x->q_rot;
-    bf16_t* const q_lo = q_hi + (size_t)x->max_rows * x->NQD;
+    bf16_t* const q_lo = q_hi + (size_t)x->rows * x->NQD;
     const int sq = gemm_fast(x, KC_GEMM_QKV, A, lw.wq /* q, k and v rows */, M, x->QKVN, H);
     { Scope s(x, KC_ROPE_KV);
       launch_rope_kv_write(x->partial, x->QKVN, sq, (size_t)M * x->QKVN, x->cos_t, x->sin_t, x->q_rot, x->NQD, kc_layer,
@@ -453,7 +515,7 @@ void run_layer(clover_ctx* x, const clover_layer_weights& lw, float* xres, RowMa
         ap.v_hi = (const bf16_t*)vc_layer; ap.v_plane = x->v_layer_elems;
         ap.kv = kvl; ap.max_seq = c.max_seq; ap.n_kv = c.n_kv_heads; ap.n_q = c.n_q_heads;
         ap.base_len = base_len; ap.anc = anc; ap.iv = iv; ap.anc_stride = anc_stride; ap.rm = rm;
-        ap.o_part = x->o_part; ap.ml_part = x->ml_part; ap.rows_total = x->max_rows; ap.max_splits = x->attn_max_splits;
+        ap.o_part = x->o_part; ap.ml_part = x->ml_part; ap.rows_total = M; ap.max_splits = (int)(x->split_rows / M);
         launch_attn_mfma(ap, key_bound, O, x->st);
       } else {
         launch_attn_generic(x->q_rot, x->NQD, kc_layer, vc_layer, x->kvdtype, kvl, base_len, anc, c.n_q_heads, nullptr,
@@ -1175,7 +1237,8 @@ int clover_prefill(clover_ctx* x, int32_t b, const int32_t* tokens, int32_t n, f
   if (x->len_ub[b] + n > c.max_seq || x->aug_ub[b] + n - 1 > c.max_seq)
     return fail(x, CLOVER_E_CAPACITY, "prompt would exceed max_seq (call clover_seq_len to refresh the bound)");
   const int H = x->H;
-  const int P = prefill_pass_rows(c);
+  const PassBufs bufs(x);
+  const int P = x->rows;
   int* len_b = x->d_seq_len + b;
   int* aug_len_b = x->d_aug_len + b;
   float* xres = x->d_xs;   // residual stream of the pass (the draft head's staging buffers are idle here)
@@ -1273,7 +1336,7 @@ int clover_read_kv(clover_ctx* x, int32_t stack, int32_t layer, int32_t b, int32
       slot0 + n_slots > c.max_seq)
     return fail(x, CLOVER_E_SHAPE, "clover_read_kv: index out of range");
   const size_t n = (size_t)n_slots * c.n_kv_heads * c.head_dim;
-  if (2 * n > (size_t)x->z_rows * c.vocab) return fail(x, CLOVER_E_SHAPE, "clover_read_kv: too many slots at once");
+  if (2 * n > (size_t)x->rows * c.vocab) return fail(x, CLOVER_E_SHAPE, "clover_read_kv: too many slots at once");
   if (n == 0) return CLOVER_OK;
   const char* kbase = (stack == 0 ? x->kc : x->aug_kc) + (size_t)layer * x->k_layer_elems * x->kv_esz;
   const char* vbase = (stack == 0 ? x->vc : x->aug_vc) + (size_t)layer * x->v_layer_elems * x->kv_esz;
@@ -1294,7 +1357,7 @@ int clover_write_kv(clover_ctx* x, int32_t stack, int32_t layer, int32_t b, int3
       slot0 + n_slots > c.max_seq)
     return fail(x, CLOVER_E_SHAPE, "clover_write_kv: index out of range");
   const size_t n = (size_t)n_slots * c.n_kv_heads * c.head_dim;
-  if (2 * n > (size_t)x->z_rows * c.vocab) return fail(x, CLOVER_E_SHAPE, "clover_write_kv: too many slots at once");
+  if (2 * n > (size_t)x->rows * c.vocab) return fail(x, CLOVER_E_SHAPE, "clover_write_kv: too many slots at once");
   if (n == 0) return CLOVER_OK;
   char* kbase = (stack == 0 ? x->kc : x->aug_kc) + (size_t)layer * x->k_layer_elems * x->kv_esz;
   char* vbase = (stack == 0 ? x->vc : x->aug_vc) + (size_t)layer * x->v_layer_elems * x->kv_esz;
