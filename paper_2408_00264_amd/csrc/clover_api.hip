@@ -540,9 +540,10 @@ void run_layer(clover_ctx* x, const clover_layer_weights& lw, float* xres, RowMa
   // (few rows: the norm and the three projections in one launch, below the norm, both projections and SwiGLU)
   SmallGemm g3[3];
   for (int sgm = 0, off = 0; sgm < 3; off += sn[sgm++]) g3[sgm] = SmallGemm{xres, H, ws[sgm], nullptr, lw.attn_norm, x->qkv + off, x->QKVN, sn[sgm]};
-  bool small;
-  { Scope s(x, KC_GEMM_QKV); small = launch_gemm_small(g3, 3, false, c.dtype, M, H, 0, c.rms_eps, x->st); }
-  if (!small) {
+  if (gemm_small_joins(g3, 3, false, c.dtype, M, H)) {
+    Scope s(x, KC_GEMM_QKV);
+    launch_gemm_small(g3, 3, false, c.dtype, M, H, 0, c.rms_eps, x->st);
+  } else {
     { Scope s(x, KC_RMSNORM); launch_rmsnorm(xres, H, lw.attn_norm, c.dtype, c.rms_eps, x->a_norm, H, H, M, x->st); }
     for (int sgm = 0, off = 0; sgm < 3; off += sn[sgm++])
       gemm_generic(x, KC_GEMM_QKV, x->a_norm, H, ws[sgm], nullptr, x->qkv + off, x->QKVN, M, sn[sgm], H, 0);
@@ -555,8 +556,10 @@ void run_layer(clover_ctx* x, const clover_layer_weights& lw, float* xres, RowMa
                         x->NQD, FragPlanes{}, rm, x->st, anc_stride, iv); }
   gemm_generic(x, KC_GEMM_WO, x->attn_out, x->NQD, lw.wo, nullptr, xres, H, M, H, x->NQD, 1);
   const SmallGemm gu[2] = {{xres, H, lw.w_gate, nullptr, lw.ffn_norm, x->h_ffn, F, F}, {xres, H, lw.w_up, nullptr, lw.ffn_norm, nullptr, F, F}};
-  { Scope s(x, KC_GEMM_GATEUP); small = launch_gemm_small(gu, 2, true, c.dtype, M, H, 0, c.rms_eps, x->st); }
-  if (!small) {
+  if (gemm_small_joins(gu, 2, true, c.dtype, M, H)) {
+    Scope s(x, KC_GEMM_GATEUP);
+    launch_gemm_small(gu, 2, true, c.dtype, M, H, 0, c.rms_eps, x->st);
+  } else {
     { Scope s(x, KC_RMSNORM); launch_rmsnorm(xres, H, lw.ffn_norm, c.dtype, c.rms_eps, x->a_norm, H, H, M, x->st); }
     gemm_generic(x, KC_GEMM_GATEUP, x->a_norm, H, lw.w_gate, nullptr, x->tmp_ffn, F, M, F, H, 0);
     gemm_generic(x, KC_GEMM_GATEUP, x->a_norm, H, lw.w_up, nullptr, x->h_ffn, F, M, F, H, 0);
@@ -616,9 +619,10 @@ void run_ad(clover_ctx* x, const clover_ad_weights& ad, const float* xin, const 
   } else {
     const SmallGemm g[3] = {{xin, H, ad.wq, ad.bq, ad.norm, x->ad_q, H, H}, {y, H, ad.wk, ad.bk, nullptr, x->ad_k, H, H},
                             {y, H, ad.wv, ad.bv, nullptr, x->ad_v, H, H}};
-    bool small;
-    { Scope s(x, KC_GEMM_DRAFT); small = launch_gemm_small(g, 3, false, c.dtype, rows, H, 0, c.rms_eps, x->st); }
-    if (!small) {
+    if (gemm_small_joins(g, 3, false, c.dtype, rows, H)) {
+      Scope s(x, KC_GEMM_DRAFT);
+      launch_gemm_small(g, 3, false, c.dtype, rows, H, 0, c.rms_eps, x->st);
+    } else {
       { Scope s(x, KC_RMSNORM); launch_rmsnorm(xin, H, ad.norm, c.dtype, c.rms_eps, x->a_norm, H, H, rows, x->st); }
       gemm_generic(x, KC_GEMM_DRAFT, x->a_norm, H, ad.wq, ad.bq, x->ad_q, H, rows, H, H, 0);
       gemm_generic(x, KC_GEMM_DRAFT, y, H, ad.wk, ad.bk, x->ad_k, H, rows, H, H, 0);
@@ -657,7 +661,10 @@ void lm_head_generic(clover_ctx* x, const float* src, const void* gain, int rows
   const clover_config& c = x->cfg;
   const int H = x->H;
   const SmallGemm g{src, H, x->w.lm_head, nullptr, gain, out, c.vocab, c.vocab};
-  { Scope s(x, KC_GEMM_LMHEAD); if (launch_gemm_small(&g, 1, false, c.dtype, rows, H, 0, c.rms_eps, x->st)) return; }
+  if (gemm_small_joins(&g, 1, false, c.dtype, rows, H)) {
+    Scope s(x, KC_GEMM_LMHEAD);
+    return launch_gemm_small(&g, 1, false, c.dtype, rows, H, 0, c.rms_eps, x->st);
+  }
   { Scope s(x, KC_RMSNORM); launch_rmsnorm(src, H, gain, c.dtype, c.rms_eps, x->a_norm, H, H, rows, x->st); }
   gemm_generic(x, KC_GEMM_LMHEAD, x->a_norm, H, x->w.lm_head, nullptr, out, c.vocab, rows, c.vocab, H, 0);
 }

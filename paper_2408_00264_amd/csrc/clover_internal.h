@@ -140,15 +140,16 @@ void launch_attn_generic(const float* q, int ldq, const void* k_cache, const voi
 // mode 0: Y = X W^T (+bias); mode 1: Y += X W^T (+bias)
 void launch_gemm_generic(const float* X, int ldx, const void* W, const void* bias, int wdtype, float* Y, int ldy,
                          int M, int N, int K, int mode, hipStream_t st);
-// Up to three such products over the same M rows and K in one launch, where the outputs are too few for larger tiles; false:
-// not eligible, nothing launched.  gain non-null: of RMSNorm(X) * gain.  swiglu: Y of g[0] = silu(X g[0].W^T) * (X g[1].W^T)
-// (no bias, mode 0).
+// Up to three such products over the same M rows and K in one launch.  gain non-null: of RMSNorm(X) * gain.  swiglu: Y of
+// g[0] = silu(X g[0].W^T) * (X g[1].W^T) (no bias, mode 0).  Only where gemm_small_joins says so: the outputs are too few for
+// larger tiles, and one launch is faster than the norm and the products by themselves.
 struct SmallGemm {
   const float* X; int ldx;
   const void *W, *bias, *gain;
   float* Y; int ldy, N;
 };
-bool launch_gemm_small(const SmallGemm* g, int n, bool swiglu, int wdtype, int M, int K, int mode, float eps, hipStream_t st);
+bool gemm_small_joins(const SmallGemm* g, int n, bool swiglu, int wdtype, int M, int K);
+void launch_gemm_small(const SmallGemm* g, int n, bool swiglu, int wdtype, int M, int K, int mode, float eps, hipStream_t st);
 void launch_swiglu(const float* g, const float* u, float* h, size_t n, hipStream_t st);
 void launch_ad_gate(const float* x, int ldx, const float* q, const float* k, const float* v, int H, int heads,
                     float* out, int ldo, float* out2, int ldo2, int rows, hipStream_t st);

@@ -651,40 +651,59 @@ static bool gemm_small_ok(const SmallGemm& g, int wdtype, int M, int K) {
   return (size_t)((g.N + 63) / 64) * ((M + 63) / 64) < 256 && K % 4 == 0 && g.ldx % 4 == 0 && ((uintptr_t)g.X & 15) == 0 &&
          ((uintptr_t)g.W & walign) == 0 && ((uintptr_t)g.gain & walign) == 0;
 }
+// Wavefronts that share a block's K.  Few blocks: a round trip per 1024 columns of K instead of one per 256 (64 x 1024 x 4096:
+// one 20.7 us, two 18.5, four 19.9; 16 x 1024 x 4096: 18.2, 11.9, 9.1).  Many: the exchange of the 64 sums, which every wavefront
+// does for itself, is paid for in throughput (128 x 1024 x 1024: 11.8, 13.0, 12.9; 256 x 4096 x 1024: 48, 53, 76).
+static int small_waves(long blocks, int K) { return std::min(blocks <= 512 ? 4 : blocks <= 1024 ? 2 : 1, (K + 255) / 256); }
+static int small_blocks(const SmallGemm* g, int n, bool swiglu) {
+  if (swiglu) return (g[0].N + 1) / 2;
+  int blocks = 0;
+  for (int i = 0; i < n; ++i) blocks += (g[i].N + GS_COLS - 1) / GS_COLS;
+  return blocks;
+}
 template <typename WT>
 static void launch_small_one(const SmallArgs& a, bool norm, dim3 grid, hipStream_t st) {
-  const int nt = 64 * std::min(GS_WAVES, (a.K + 255) / 256);   // wavefronts share K: a round trip per 1024 columns (K 256 to 688 of the fp32 step: 4.8 -> 4.3 us)
+  const int nt = 64 * small_waves((long)grid.x * grid.y, a.K);
   if (a.swiglu && norm) gemm_small_kernel<WT, true, true><<<grid, nt, 0, st>>>(a);
   else if (a.swiglu) gemm_small_kernel<WT, false, true><<<grid, nt, 0, st>>>(a);
   else if (norm) gemm_small_kernel<WT, true, false><<<grid, nt, 0, st>>>(a);
   else gemm_small_kernel<WT, false, false><<<grid, nt, 0, st>>>(a);
 }
-bool launch_gemm_small(const SmallGemm* g, int n, bool swiglu, int wdtype, int M, int K, int mode, float eps, hipStream_t st) {
+// Is the joint launch faster than what it replaces?  It saves launches and their round trips, and pays with a fifth of its
+// vector work for the squares, which every block sums for itself, and for SwiGLU with a second matrix that streams through the
+// L2 for every row block.  In units of blocks times columns of K, the crossings lie at (us, joint and separate):
+//   norm in front of one product    6 M   1024 wide: 128 x 2816 24.9 / 25.1, 128 x 4096 32.1 / 30.0; 4096: 48 x 2816 45.2 / 39.7
+//   norm and three products        26 M   1024: 512 rows 85 / 96, 1024 rows 165 / 171; 4096, GQA: 64 rows 85.5 / 97, 128 rows 160 / 153
+//   norm, two products and SwiGLU  16 M   1024: 64 x 4096 33.8 / 38.7, 128 x 4096 61.7 / 59.6; 4096: 16 x 4096 33 / 50, 48 x 4096 98 / 93
+bool gemm_small_joins(const SmallGemm* g, int n, bool swiglu, int wdtype, int M, int K) {
+  for (int i = 0; i < n; ++i)
+    if (!gemm_small_ok(g[i], wdtype, M, K)) return false;
+  const double work = (double)small_blocks(g, n, swiglu) * ((M + GS_ROWS - 1) / GS_ROWS) * K;
+  return work <= (swiglu ? 16e6 : n == 1 ? 6e6 : 26e6);
+}
+void launch_gemm_small(const SmallGemm* g, int n, bool swiglu, int wdtype, int M, int K, int mode, float eps, hipStream_t st) {
   SmallArgs a{};
   bool norm = false;
-  int blocks = 0;
-  for (int i = 0; i < 3; ++i) {
+  for (int i = 0, blocks = 0; i < 3; ++i) {
     a.first[i] = i < n ? blocks : 1 << 30;
     if (i >= n) continue;
-    if (!gemm_small_ok(g[i], wdtype, M, K)) return false;
     a.g[i] = g[i];
     norm = norm || g[i].gain;
-    blocks += (g[i].N + GS_COLS - 1) / GS_COLS;
+    blocks += small_blocks(&g[i], 1, false);
   }
-  if (swiglu) blocks = (g[0].N + 1) / 2;
-  if (M <= 0 || blocks <= 0) return true;
+  const int blocks = small_blocks(g, n, swiglu);
+  if (M <= 0 || blocks <= 0) return;
   a.M = M; a.K = K; a.mode = mode; a.swiglu = swiglu; a.eps = eps;
   const dim3 grid(blocks, (M + GS_ROWS - 1) / GS_ROWS);
   if (wdtype == 0) launch_small_one<float>(a, norm, grid, st);
   else launch_small_one<bf16_t>(a, norm, grid, st);
-  return true;
 }
 
 void launch_gemm_generic(const float* X, int ldx, const void* W, const void* bias, int wdtype, float* Y, int ldy,
                          int M, int N, int K, int mode, hipStream_t st) {
   if (M <= 0 || N <= 0) return;
   const SmallGemm g{X, ldx, W, bias, nullptr, Y, ldy, N};
-  if (launch_gemm_small(&g, 1, false, wdtype, M, K, mode, 0.f, st)) return;
+  if (gemm_small_ok(g, wdtype, M, K)) return launch_gemm_small(&g, 1, false, wdtype, M, K, mode, 0.f, st);
   dim3 grid((N + 63) / 64, (M + 63) / 64);
   if (wdtype == 0)
     gemm_generic_kernel<float><<<grid, 256, 0, st>>>(X, ldx, (const float*)W, (const float*)bias, Y, ldy, M, N, K, mode);
