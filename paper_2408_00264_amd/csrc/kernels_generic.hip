@@ -643,13 +643,15 @@ __global__ __launch_bounds__(64 * GS_WAVES) void gemm_small_kernel(SmallArgs a) 
   *y = a.mode == 1 ? *y + v : v;
 }
 
-// Fewer 64 x 64 tiles than compute units: the tile kernel's time is its K chain, which the small kernel beats at every shape
-// measured up to there, by 27 times (few rows, K of 14336) down to twice (512 x 1024 x 256: 26.7 -> 13.2 us, 64 x 8192 x
-// 256: 26.4 -> 11.9).  (16-byte loads: rows of X and W must start on 16 bytes, 8 for bf16 weights.)
+// Up to three 64 x 64 tiles to a compute unit (half of that at K of 256, where the tile kernel's K chain is short): the tile
+// kernel takes its K chain's time whether a compute unit has one tile or three.  us, this kernel and the tiles: 1 x 14336 x 4096
+// 50 / 397, 256 x 4096 x 4096 (256 tiles) 201 / 483, 512 x 4096 x 1024 (512) 94 / 110, 1000 x 2816 x 1024 (704) 131 / 146,
+// 1000 x 4096 x 1024 (1024) 180 / 169; K of 256: 512 x 2816 (352) 27.5 / 28.9, 512 x 4096 (512) 35 / 29.
+// (16-byte loads: rows of X and W must start on 16 bytes, 8 for bf16 weights.)
 static bool gemm_small_ok(const SmallGemm& g, int wdtype, int M, int K) {
   const size_t walign = wdtype == 0 ? 15 : 7;
-  return (size_t)((g.N + 63) / 64) * ((M + 63) / 64) < 256 && K % 4 == 0 && g.ldx % 4 == 0 && ((uintptr_t)g.X & 15) == 0 &&
-         ((uintptr_t)g.W & walign) == 0 && ((uintptr_t)g.gain & walign) == 0;
+  return (size_t)((g.N + 63) / 64) * ((M + 63) / 64) < (K > 256 ? 768 : 384) && K % 4 == 0 && g.ldx % 4 == 0 &&
+         ((uintptr_t)g.X & 15) == 0 && ((uintptr_t)g.W & walign) == 0 && ((uintptr_t)g.gain & walign) == 0;
 }
 // Wavefronts that share a block's K.  Few blocks: a round trip per 1024 columns of K instead of one per 256 (64 x 1024 x 4096:
 // one 20.7 us, two 18.5, four 19.9; 16 x 1024 x 4096: 18.2, 11.9, 9.1).  Many: the exchange of the 64 sums, which every wavefront

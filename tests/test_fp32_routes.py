@@ -41,6 +41,12 @@ def test_rows_do_not_depend_on_the_route(batch, want):
 @pytest.mark.parametrize("dtype", [clover.DTYPE_F32, clover.DTYPE_BF16])
 @pytest.mark.parametrize("M,N,K", [(16, 2048, 1020), (16, 2064, 516), (16, 4096, 260), (16, 4112, 1284), (33, 1363, 772), (63, 1024, 1000)])
 def test_product_over_shared_k(dtype, M, N, K):
+    X, W, Y = _product(dtype, M, N, K)
+    err = (Y.double() - X.double() @ W.double().T).abs().max().item()
+    assert err <= 1e-5 * K ** 0.5 * 0.02 * 4, err   # (the bound of the fp32 GEMM tests)
+
+
+def _product(dtype, M, N, K):
     lib = clover.load_library()
     gen = torch.Generator(device="cuda").manual_seed(M + N + K)
     X = torch.randn(M, K, generator=gen, device="cuda")
@@ -49,5 +55,18 @@ def test_product_over_shared_k(dtype, M, N, K):
     st = torch.cuda.current_stream().cuda_stream
     p = lambda t: C.c_void_p(t.data_ptr())
     assert lib.clover_op_gemm(0, dtype, p(X), p(W), p(Y), N, M, N, K, p(Y), 0, C.c_void_p(st)) == 0
+    return X, W, Y
+
+
+# tiles of 64 x 64: 256, 752 | 768, at a K of 256 368 | 384: the longer passes of a prompt take the sums of a few rows
+@pytest.mark.parametrize("M,N,K,same", [(256, 4096, 516, True), (1000, 3000, 260, True), (1010, 3060, 260, False), (1000, 1450, 256, True),
+                                        (1024, 1536, 256, False)])
+def test_products_up_to_three_tiles_a_compute_unit(M, N, K, same):
+    X, W, Y = _product(clover.DTYPE_F32, M, N, K)
     err = (Y.double() - X.double() @ W.double().T).abs().max().item()
-    assert err <= 1e-5 * K ** 0.5 * 0.02 * 4, err   # (the bound of the fp32 GEMM tests)
+    assert err <= 1e-5 * K ** 0.5 * 0.02 * 4, err
+    few = torch.empty(64, N, device="cuda")      # more than 1024 blocks too, so one wavefront to a block in both
+    p = lambda t: C.c_void_p(t.data_ptr())
+    assert clover.load_library().clover_op_gemm(0, clover.DTYPE_F32, p(X), p(W), p(few), N, 64, N, K, p(few), 0,
+                                                C.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+    assert torch.equal(few, Y[:64]) == same
