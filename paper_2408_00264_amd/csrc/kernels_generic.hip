@@ -336,7 +336,8 @@ void launch_rope_kv_write(const float* qkv, int ldqkv, int qkv_splits, size_t qk
 // ------------------------------------------------------------------------------------------
 // What bounds it: memory round trips.  A lane fetches its key's row and its channel's 64 values in 16-byte pieces that are all
 // requested before the first is used (3 launches of 16 rows x 80 keys: 64 us with one 4-byte load after the other, 22 so).
-// Sums run in key and channel order as before.
+// Tiles that are hidden from a row altogether are not loaded, and a chain's row ends with its own tile (bf16 model with heads of
+// 64, 1000 tokens in one pass: 1300 -> 730 us a layer; fp32 with heads of 128: 880 -> 480).
 __device__ __forceinline__ float4 ldkv4(const float* p, size_t i, size_t) { return *(const float4*)(p + i); }
 __device__ __forceinline__ float4 ldkv4(const bf16_t* p, size_t i, size_t plane) {
   const uint2 h = *(const uint2*)(p + i), l = *(const uint2*)(p + i + plane);
@@ -372,17 +373,18 @@ __global__ __launch_bounds__(64) void attn_generic_kernel(const float* __restric
   float mrun = -INFINITY, lrun = 0.f, o[D / 64];
 #pragma unroll
   for (int u = 0; u < D / 64; ++u) o[u] = 0.f;
-  const int total = L + rm.n;
+  const int total = L + (chain ? i + 1 : rm.n);   // (a chain's row sees nothing behind itself)
   const int ntiles = (total + 63) / 64;
   for (int t = 0; t < ntiles; ++t) {
     const int s = t * 64 + lane;
     bool vis = s < L;
     if (!vis && s < total) {
       const int w = s - L;
-      if (chain) vis = w <= i;
+      if (chain) vis = true;
       else if (iv) vis = iv[2 * ((size_t)b * anc_stride + w)] <= my_enter && my_enter <= iv[2 * ((size_t)b * anc_stride + w) + 1];
       else vis = ((w < 64 ? (a0 >> w) : (a1 >> (w - 64))) & 1ull) != 0ull;
     }
+    if (__builtin_amdgcn_ballot_w64(vis) == 0ull) continue;   // uniform: nothing of a hidden tile is loaded
     // (slots of the tile behind the cache's last page are read from the last page and never used)
     const size_t kr = kv_k_at(kv, b, min(s, kv.max_seq - 1), g);
     float4 kx[D / 4];
@@ -406,7 +408,7 @@ __global__ __launch_bounds__(64) void attn_generic_kernel(const float* __restric
     }
     const float sc = vis ? acc : -INFINITY;
     const float mnew = fmaxf(mrun, wave_max(sc));
-    if (mnew == -INFINITY) continue;  // uniform across the wave
+    if (mnew == -INFINITY) continue;  // uniform across the wave (every visible score is)
     const float p = vis ? expf(sc - mnew) : 0.f;
     const float corr = (mrun == -INFINITY) ? 0.f : expf(mrun - mnew);
     lrun = lrun * corr + wave_sum(p);
