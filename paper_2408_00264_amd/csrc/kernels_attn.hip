@@ -432,17 +432,22 @@ void launch_attn_mfma(AttnParams p, int max_total_keys, FragPlanes out, hipStrea
   // 36.6 -> 22.7, a 2048-token prompt 224 -> 122; 16 KV heads, 8 x 60 nodes at 700 keys 41.1 -> 32.5)
   const int nodes = g == 1 && p.rm.n > 64 ? 128 : g <= 2 && p.rm.n > 32 ? 64 : 32;
   const int node_groups = (p.rm.n + nodes - 1) / nodes;
-  // Key splits by estimated time, in us.  A key tile costs a compute unit 1.5 whether one workgroup is at it or two; splitting
-  // at all costs the merge launch and the traffic of the partial results, 5.2 + 0.4 per MB (32 heads, 8 KV heads: prompts of 133 /
-  // 300 / 500 tokens unsplit 12.7 / 19.7 / 31.4, in two or three splits 15.9 / 22.2 / 31.2; 64 nodes at 512 keys unsplit 31.0,
-  // in 9 splits 15.4; 8 x 60 nodes at 700 keys 41.5 and 36.1).
+  // Key splits by estimated time, in us, fitted to every split count of 283 launches (1 to 32 KV heads' groups of 1 to 8 heads, 1
+  // to 16 sequences, 1 to 128 nodes, 8 to 8192 keys, prompts to 2000 tokens; on average 1.7 % behind the best).  A key tile
+  // takes a lone workgroup of a compute unit 1.05; two share it in 1.8, counted as two here, which keeps a second workgroup for
+  // where it pays.  Splitting at all costs the merge launch and the traffic of the partial results, 2 + 0.2 per MB (32 heads, 8 KV
+  // heads: one node at 133 keys unsplit 14.9, in 3 splits 10.4; 64 nodes at 100 keys 17.1 and 15.3, at 1024 keys 47 and 19 in 12;
+  // 128 nodes at 8192 keys 59.4 in 8, 55.5 in 16).  Where most keys are the launch's own new rows the workgroups' tiles grow from
+  // one to all, so a split shortens only the last of them: 1.5 and 5.2 + 0.4 there (200 tokens unsplit 17.0, in 4 splits 20.9).
   const int wgs = p.rm.B * p.n_kv * node_groups, only = tune_int("CLOVER_ATTN_SPLITS", 0);
   const double mb = (double)p.rm.B * p.rm.n * p.n_q * AT_D * 4e-6;
+  const bool fresh = p.anc == nullptr && p.iv == nullptr && 2 * p.rm.n > max_total_keys;
+  const double tile = fresh ? 1.5 : 1.05, merge = fresh ? 5.2 : 2.0, per_mb = fresh ? 0.4 : 0.2;
   int splits = 1;
   double best = 1e30;
   for (int s = 1; s <= std::min(p.max_splits, MG_MAXS) && s <= (n_tiles + 1) / 2; ++s) {
     const int tiles = (n_tiles + s - 1) / s, n = (n_tiles + tiles - 1) / tiles;
-    const double t = 1.5 * tiles * ((wgs * n + 255) / 256) + (n > 1 ? 5.2 + 0.4 * mb * n : 0.0);
+    const double t = tile * tiles * ((wgs * n + 255) / 256) + (n > 1 ? merge + per_mb * mb * n : 0.0);
     if (only > 0 ? s <= only : t < best) { best = t; splits = s; }
   }
   p.tiles_per_split = (n_tiles + splits - 1) / splits;
