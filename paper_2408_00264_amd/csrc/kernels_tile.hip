@@ -150,7 +150,10 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(TileGemm p) {
   const char* wp = (const char*)p.W + (size_t)kt0 * wstage;
   const unsigned ldsw = lds0 + (unsigned)wave * 1024u;
   const unsigned wlast = (unsigned)__builtin_amdgcn_readfirstlane((XF + min((WL - 1) * 4 + wave, WF - 1) - wave) * 1024);   // the last load's destination
-  // load j of the stage at (xp, wp), M0 set in front of it: at least one instruction (or the no-op) has to lie in between
+  // Load j of the stage at (xp, wp), M0 set in front of it: at least one instruction (or the no-op) has to lie in between.
+  // Contract: each load has one set_m0 of its own, with no other load and no jump in between.  The load cannot say that it
+  // reads M0, so nothing but that order -- kept, both are volatile -- and the absence of compiler-made writes of M0 carries
+  // the address; tests/test_kernel_waits.py looks for both in the machine code.
   auto set_m0 = [&](auto jc, unsigned buf) __attribute__((always_inline)) {
     constexpr int j = decltype(jc)::value, i = j - XL;
     const unsigned base = ldsw + buf, last = wlast;

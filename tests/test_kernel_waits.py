@@ -76,3 +76,22 @@ def test_accumulators_are_read_behind_the_wait(kernels):
                 assert nop >= 8, (name, ins)
                 n += 1
     assert n > 100, n
+
+
+def test_every_lds_load_of_the_gemm_has_an_m0_of_its_own(kernels):
+    """The GEMM writes M0 in one asm statement and loads in a later one, and the load does not say that it reads M0: between two
+    loads there must be exactly one write of M0, the GEMM's own, and no jump between it and its load."""
+    n = 0
+    for name, code in kernels.items():
+        if "gemm_tile_kernel" not in name:
+            continue
+        since = []                                   # writes of M0, and jumps behind the last of them
+        for ins in code:
+            if re.match(r"global_load_lds_", ins):
+                assert len(since) == 1 and since[0].startswith("s_add_u32 m0,"), (name, since, ins)
+                n, since = n + 1, []
+            elif re.match(r"[sv]_\w+ m0\b", ins):
+                since.append(ins)
+            elif since and re.match(r"s_c?branch|s_setpc|s_swappc|s_call", ins):
+                since.append(ins)
+    assert n > 1000, n
