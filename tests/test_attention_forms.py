@@ -1,6 +1,7 @@
 """The MFMA tree attention against the fp32-ALU kernels on the same caches: every form (query heads per KV head, nodes per
 workgroup), trees and interval labels around the 32, 64 and 128 nodes of a workgroup, caches around a tile, over 64 tiles
-unsplit and over several splits, and scores that grow along the cache so that the reference of the soft-max moves."""
+unsplit and over several splits, and scores that grow along the cache so that the reference of the soft-max moves.  (With
+these scores the new rows hardly count: test_attention_masks.py has the masks.)"""
 import numpy as np
 import pytest
 

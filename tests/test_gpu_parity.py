@@ -690,19 +690,20 @@ def test_full_width_two_layers(cfg, batch):
 # ------------------------------------------------------------------------------------------
 # the prefill call: many-row passes with causal attention, LM head on the last row only (Sec. 1, 3.1, 3.3)
 # ------------------------------------------------------------------------------------------
-@pytest.mark.parametrize("flags,prefill_rows,lengths", [
-    (0, 128, [300, 77]),                       # 128 + 128 + 44 rows; a prompt shorter than one pass
-    (0, 256, [600, 1]),                        # 256 + 256 + 88 rows; a one-token prompt (no draft-side row)
-    (0, 0, [50, 24]),                          # no extra capacity: passes of max_batch * max_nodes = 48 rows
-    (clover.FLAG_GENERIC, 96, [200, 96]),      # the plain fp32 kernels; a prompt of exactly one pass
-], ids=["mfma_128", "mfma_256", "mfma_default_rows", "generic_96"])
+@pytest.mark.parametrize("flags,prefill_rows,lengths", [   # (rows per pass that the workspace holds: 256, with 128 512, with 256 768)
+    (0, 128, [300, 77]),                       # one pass each
+    (0, 256, [600, 1]),                        # one pass; a one-token prompt (no draft-side row)
+    (0, 0, [600, 256]),                        # 256 + 256 + 88 rows; a prompt of exactly one pass
+    (0, 0, [50, 257]),                         # one pass; 256 + 1 rows (a last pass without a draft-side row)
+    (clover.FLAG_GENERIC, 96, [200, 513]),     # the plain fp32 kernels; 256 + 256 + 1 rows
+], ids=["mfma_128", "mfma_256", "mfma_three_passes", "mfma_default_rows", "generic_96"])
 def test_prefill_call_mini_bf16(flags, prefill_rows, lengths):
     _torch()
     shape = synth.scaled(MINI, batch=2, seed=41)
     ls = _lockstep(shape, flags=flags, gain_jitter=0.1, batch=2, max_seq=768, prefill_rows=prefill_rows)
     rng = np.random.default_rng(7)
     prompts = [rng.integers(0, shape.vocab, size=n).astype(np.int32) for n in lengths]
-    say(f"prefill call, flags={flags}, rows per pass {prefill_rows or 48}: prompts {lengths}")
+    say(f"prefill call, flags={flags}, prefill_rows {prefill_rows}: prompts {lengths}")
     ls.prefill_prompts(prompts, oracle_chunk=64)
     say(f"  after prefill: max|dlogit|={ls.max_logit_err:.2e} max|dKV|={ls.max_kv_err:.2e} max|dhid|={ls.max_hidden_err:.2e}")
     for s in range(3):
@@ -713,9 +714,9 @@ def test_prefill_call_mini_bf16(flags, prefill_rows, lengths):
 
 def test_prefill_call_config1_fp32():
     _torch()
-    ls = _lockstep(TINY, max_seq=256, prefill_rows=40)
-    prompts = synth.make_prompts(TINY)
-    say("config 1: prefill call, 64 tokens in passes of 40 rows")
+    ls = _lockstep(TINY, max_seq=256)
+    prompts = [np.random.default_rng(8).integers(0, TINY.vocab, size=200).astype(np.int32)]
+    say("config 1: prefill call, 200 tokens in passes of 64 rows")
     ls.prefill_prompts(prompts, oracle_chunk=16)
     for s in range(4):
         ms = ls.step()
@@ -724,12 +725,13 @@ def test_prefill_call_config1_fp32():
 
 
 def test_prefill_call_full_width_two_layers():
-    """The prefill call at the LLaMA3-8B widths (two layers): a 600-token prompt in passes of 256 rows through the
-    many-row GEMM, causal attention over eight node groups, then two speculative steps on top."""
+    """The prefill call at the LLaMA3-8B widths (two layers): a 600-token prompt in passes of 256 + 256 + 88 rows (what the
+    workspace of a 64-node tree holds) through the many-row GEMM, causal attention over eight node groups, then two
+    speculative steps on top."""
     _torch()
     O = __import__("oracle.clover2_oracle", fromlist=["x"])
     shape = synth.scaled(synth.CONFIGS[3], name="wide-3-prefill", n_layers=2, seed=43)
-    ls = _lockstep(shape, max_seq=768, prefill_rows=256)
+    ls = _lockstep(shape, max_seq=768)
     assert ls.gpu.path_info() & 3 == 3
     ls.ocfg.dtype = np.float32
     ls.W = O.Weights(ls.store.get_f32, np.float32)

@@ -38,9 +38,11 @@ def _prompt(shape, n, seed):
     return torch.randint(0, shape.vocab, (n,), generator=torch.Generator().manual_seed(seed)).int().cuda()
 
 
-def _prefill(shape, dev_w, n, max_seq, prefill_rows, flags=0):
+def _prefill(shape, dev_w, n, max_seq, prefill_rows, flags=0, shuffled=False):
     """(passes, K and V of the last layer, those of the Augmenting Block, logits, hidden) of one prompt"""
     g = clover.Clover(shape, dev_w, *_tree(shape), 1, max_seq, shape.tree_nodes, flags=flags, prefill_rows=prefill_rows)
+    if shuffled:
+        g.set_page_table(np.random.default_rng(n).permutation(max_seq // 32).astype(np.int32))
     g.profile_enable(True)
     g.prefill_prompt(0, _prompt(shape, n, n))
     torch.cuda.synchronize()
@@ -52,7 +54,7 @@ def _prefill(shape, dev_w, n, max_seq, prefill_rows, flags=0):
     return (embeds + 1) // 2, out
 
 
-# (model, prompt, prefill_rows of the two sides, passes of the first): around whole passes, one row left, the fp32-ALU route and
+# (model, prompt, prefill_rows of the two sides, flags; the first side's pages are shuffled): around whole passes, one row left, the fp32-ALU route and
 # fp32; LLaMA3-8B widths: passes of 2048 rows against 256-row ones
 CASES = [(MINI, 600, 0, 256, 0), (MINI, 256, 0, 255, 0), (MINI, 257, 0, 256, 0), (MINI, 513, 1, 64, 0),
          (MINI, 600, 0, 200, clover.FLAG_GENERIC), (synth.scaled(synth.CONFIGS[1], seed=20), 500, 0, 256, 0),
@@ -65,7 +67,8 @@ def test_state_does_not_depend_on_the_passes(case):
     shape, n, rows_a, rows_b, flags = case
     dev_w = clover.upload_weights(synth.WeightStore(shape))
     max_seq = (n + 95) // 32 * 32
-    (p_a, a), (p_b, b) = (_prefill(shape, dev_w, n, max_seq, r, flags) for r in (rows_a, rows_b))
+    p_a, a = _prefill(shape, dev_w, n, max_seq, rows_a, flags, shuffled=True)
+    p_b, b = _prefill(shape, dev_w, n, max_seq, rows_b, flags)
     print(f"{shape.name}: {n} tokens in {p_a} and {p_b} passes", flush=True)
     assert max(p_a, p_b) > 1 or n <= 256
     if n == 4173:
