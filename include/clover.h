@@ -73,7 +73,7 @@ typedef struct {
   int32_t prefill_rows;  /* the row buffers of the workspace are sized for max(max_batch * max_nodes, prefill_rows) rows of
                             a step.  clover_prefill takes as many prompt rows per pass as the same memory holds without
                             what only a step needs: at least min(256, that many), at most 2048 (LLaMA3-8B widths:
-                            256 rows for a 64-node tree alone, 2048 with prefill_rows = 256).  At most 256. */
+                            512 rows for a 64-node tree alone, 2048 with prefill_rows = 256).  At most 256. */
 } clover_config;
 
 /* Static tree topology (Sec. 2.1: candidates merged on common prefixes form a tree).

@@ -254,38 +254,49 @@ void model_gemm_shapes(const clover_config& c, std::vector<GemmShape>& v) {
 }
 bool mfma_shape_ok(int N, int K) { return N % 16 == 0 && K % 128 == 0; }
 
-// bytes of the partial tiles of the largest launch over up to `rows` rows, for each row count 32, 64 .. (the q and the k|v
-// projections of an Attention Decoder lie side by side)
-std::vector<size_t> partial_tile_bytes(const clover_config& c, int rows) {
-  std::vector<GemmShape> shapes;
-  model_gemm_shapes(c, shapes);
-  std::vector<size_t> v;
-  size_t most = 256;
+// Bytes of the partial tiles of launches over up to a number of rows: QKV and Wo, down, the projections of an Attention Decoder
+// (q and k|v lie side by side), the draft head's FC.
+struct TileBytes {
+  size_t attn = 0, down = 0, ad = 0, fc = 0;
+  size_t most() const { return std::max(std::max(attn, down), std::max(ad, fc)); }
+};
+// for up to 32, 64 .. rows
+std::vector<TileBytes> tile_bytes(const clover_config& c, int rows) {
+  std::vector<GemmShape> s;
+  model_gemm_shapes(c, s);   // QKV, Wo, down, an Attention Decoder's q, the FC
+  std::vector<TileBytes> v;
+  TileBytes t{256, 256, 256, 256};
   for (int M = 32; M < rows + 32; M += 32) {   // one row count of each class of equal K ranges
     auto bytes = [&](int N, int K) {   // (a tuning build that changes the ranges afterwards makes room for them here)
       return (size_t)std::max(tile_gemm_pick_k_parts(M, N, K), tune_int("CLOVER_TILE_KP_ROOM", 1)) * std::min(M, rows) * N * sizeof(float);
     };
-    for (const GemmShape& s : shapes) most = std::max(most, bytes(s.N, s.K));
-    most = std::max(most, align256(bytes(c.hidden, c.hidden)) + bytes(2 * c.hidden, c.hidden));
-    v.push_back(most);
+    t.attn = std::max(t.attn, std::max(bytes(s[0].N, s[0].K), bytes(s[1].N, s[1].K)));
+    t.down = std::max(t.down, bytes(s[2].N, s[2].K));
+    t.ad = std::max(t.ad, align256(bytes(s[3].N, s[3].K)) + bytes(2 * c.hidden, c.hidden));
+    t.fc = std::max(t.fc, bytes(s[4].N, s[4].K));
+    v.push_back(t);
   }
   return v;
 }
 
 // The layout of a prompt pass of `rows` rows: what is alive at the same time side by side, the rest on top of each other.
 // Returns its bytes.
-size_t carve_pass(const clover_ctx* x, char* base, int rows, size_t partial_bytes, RowBufs& b) {
+size_t carve_pass(const clover_ctx* x, char* base, int rows, const TileBytes& t, RowBufs& b) {
   const clover_config& c = x->cfg;
   Carver cv{base};
   const size_t H = c.hidden, rows16 = ((size_t)rows + 15) / 16 * 16;
+  const bool fused = x->fast && ad_gate_fused_supported(c.hidden, c.ad_heads);
   b = RowBufs{};
   b.rows = rows;
   b.cos_t = cv.take<float>((size_t)rows * c.head_dim / 2);
   b.sin_t = cv.take<float>((size_t)rows * c.head_dim / 2);
   b.d_xs = cv.take<float>(rows * H);
-  b.xd = cv.take<float>(rows * H);
+  b.xd = fused ? b.d_xs : cv.take<float>(rows * H);   // (the fused gate kernel writes where it read)
   b.a_norm = cv.take<float>(rows16 * H);
-  Carver at = cv, ff = cv, ad = cv;   // attention | FFN | Attention Decoder 1
+  Carver at = cv, ff = cv, ad = cv;   // attention | FFN | Attention Decoder 1, each behind its own partial tiles
+  b.partial = (float*)at.take<char>(t.attn);
+  ff.take<char>(t.down);
+  ad.take<char>(t.ad);
   if (!x->fast) b.qkv = at.take<float>((size_t)rows * x->QKVN);
   b.q_rot = at.take<float>((size_t)rows * x->NQD);
   b.attn_out = at.take<float>(rows16 * x->NQD);
@@ -293,15 +304,13 @@ size_t carve_pass(const clover_ctx* x, char* base, int rows, size_t partial_byte
   if (!x->fast) b.tmp_ffn = ff.take<float>((size_t)rows * c.ffn);
   b.d_e = ad.take<float>(rows * H);
   if (x->fast) b.pl_y = ad.take<float>(rows16 * H);
-  if (!(x->fast && ad_gate_fused_supported(c.hidden, c.ad_heads)))
+  if (!fused)
     for (float** p : {&b.ad_q, &b.ad_k, &b.ad_v}) *p = ad.take<float>(rows * H);
-  cv.off = std::max(at.off, std::max(ff.off, ad.off));
-  // The attention's partial results lie on the GEMMs' partial tiles: the projection's are summed by then.
-  b.partial = (float*)cv.take<char>(partial_bytes);
-  b.split_rows = x->attn_fast ? (partial_bytes - 256) / (sizeof(float) * (x->NQD + 2 * c.n_q_heads)) : 0;
+  // The attention's partial results lie on the projection's partial tiles, which are summed by then.
+  b.split_rows = x->attn_fast ? (t.attn - 256) / (sizeof(float) * (x->NQD + 2 * c.n_q_heads)) : 0;
   b.o_part = b.partial;
   b.ml_part = base ? (float*)((char*)b.partial + align256(b.split_rows * x->NQD * sizeof(float))) : nullptr;
-  return cv.off;
+  return std::max(at.off, std::max(ff.off, ad.off));
 }
 
 // Rows of a prompt pass: as many as the memory of a step's buffers holds, up to 2048, where the narrow GEMMs (QKV, Wo, down) fill
@@ -310,12 +319,12 @@ size_t carve_pass(const clover_ctx* x, char* base, int rows, size_t partial_byte
 // 125 / 75.
 void carve_passes(clover_ctx* x, char* base, size_t bytes) {
   const int most = std::min(2048, x->cfg.max_seq), own = std::min(x->step.rows, std::min(most, 256));
-  const std::vector<size_t> part = x->fast ? partial_tile_bytes(x->cfg, most) : std::vector<size_t>(most / 32, 256);
+  const std::vector<TileBytes> tiles = x->fast ? tile_bytes(x->cfg, most) : std::vector<TileBytes>(most / 32);
   int rows = most;
-  while (rows > own && carve_pass(x, nullptr, rows, part[rows / 32 - 1], x->pass) > bytes)
+  while (rows > own && carve_pass(x, nullptr, rows, tiles[rows / 32 - 1], x->pass) > bytes)
     rows = rows > 256 ? (rows - 1) / 256 * 256 : (rows - 1) / 32 * 32;
-  if (rows > own) carve_pass(x, base, rows, part[rows / 32 - 1], x->pass);
-  else carve_pass(x, base, own, x->fast ? partial_tile_bytes(x->cfg, own).back() : 256, x->pass);   // (a part of the step's: fits)
+  if (rows > own) carve_pass(x, base, rows, tiles[rows / 32 - 1], x->pass);
+  else carve_pass(x, base, own, x->fast ? tile_bytes(x->cfg, own).back() : TileBytes{}, x->pass);   // (a part of the step's: fits)
 }
 
 void carve(clover_ctx* x, char* base, size_t* total) {
@@ -416,7 +425,7 @@ void carve(clover_ctx* x, char* base, size_t* total) {
   b.split_rows = splits * rows;
   b.o_part = cv.take<float>(x->attn_fast ? splits * rows * x->NQD : 64);
   b.ml_part = cv.take<float>(x->attn_fast ? splits * rows * c.n_q_heads * 2 : 64);
-  b.partial = (float*)cv.take<char>(fast ? partial_tile_bytes(c, rows).back() : 256);
+  b.partial = (float*)cv.take<char>(fast ? tile_bytes(c, rows).back().most() : 256);
   b.pl_y = cv.take<float>(rows16 * 2 * H);
   static_cast<RowBufs&>(*x) = b;
   if (base) carve_passes(x, base + own, cv.off - own);

@@ -690,7 +690,7 @@ def test_full_width_two_layers(cfg, batch):
 # ------------------------------------------------------------------------------------------
 # the prefill call: many-row passes with causal attention, LM head on the last row only (Sec. 1, 3.1, 3.3)
 # ------------------------------------------------------------------------------------------
-@pytest.mark.parametrize("flags,prefill_rows,lengths", [   # (rows per pass that the workspace holds: 256, with 128 512, with 256 768)
+@pytest.mark.parametrize("flags,prefill_rows,lengths", [   # (rows per pass that the workspace holds: 256, with 128 or 256 768)
     (0, 128, [300, 77]),                       # one pass each
     (0, 256, [600, 1]),                        # one pass; a one-token prompt (no draft-side row)
     (0, 0, [600, 256]),                        # 256 + 256 + 88 rows; a prompt of exactly one pass
@@ -725,8 +725,8 @@ def test_prefill_call_config1_fp32():
 
 
 def test_prefill_call_full_width_two_layers():
-    """The prefill call at the LLaMA3-8B widths (two layers): a 600-token prompt in passes of 256 + 256 + 88 rows (what the
-    workspace of a 64-node tree holds) through the many-row GEMM, causal attention over eight node groups, then two
+    """The prefill call at the LLaMA3-8B widths (two layers): a 600-token prompt in passes of 512 + 88 rows (what the
+    workspace of a 64-node tree holds) through the many-row GEMM, causal attention over sixteen node groups, then two
     speculative steps on top."""
     _torch()
     O = __import__("oracle.clover2_oracle", fromlist=["x"])
