@@ -222,7 +222,7 @@ struct AttnParams {
   float* ml_part;                        // [max_splits][rows_total][n_q][2]
   int rows_total, max_splits;
   int tiles_per_split, n_splits;         // filled in by launch_attn_mfma
-  FragPlanes out;                        //
+  FragPlanes out;                        // finished rows where there is one split; filled in by launch_attn_mfma
 };
 bool attn_mfma_supported(int head_dim, int n_q, int n_kv, int max_seq);
 // max_total_keys: host-side upper bound of base_len[b] + rm.n over the batch (sizes the key splits)

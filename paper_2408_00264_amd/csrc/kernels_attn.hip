@@ -13,8 +13,8 @@
 // ranges every split writes an un-normalised partial (O, reference, running sum) and a small kernel merges them with the
 // usual log-sum-exp weights, with one range the workgroup writes the finished rows.
 //
-// What bounds it: the waits between the steps of a tile (matrix pipe 52 % busy over a 2048-row pass behind 3072 keys, vector
-// ALU 18 %, LDS 34 %), so what counts is wavefronts in flight (120 registers and 66 KB of LDS: two workgroups of eight to a
+// What bounds it: the waits between the steps of a tile (matrix pipe 69 % busy over the 2048-row passes of an 8192-token prompt,
+// two workgroups to a CU, 42 % with one, 96 nodes at 8192 keys), so what counts is wavefronts in flight (120 registers and 66 KB of LDS: two workgroups of eight to a
 // CU), independent work inside a wavefront (scores of the next tile beside the probabilities of this one) and no exchange
 // between lanes.  8B shape, 8 KV heads, us per launch, before (tiles one after the other, row maximum exchanged in every tile)
 // and now: 64 nodes at 1024 keys 14.1 / 12.9, 96 at 8192 54.9 / 47.8, 8 x 32 ragged to 2048 37.1 / 35.1, one row at 1024

@@ -4,9 +4,9 @@
 //   EPI 1:  out[M,F]    = planes of silu(X Wg^T) * (X Wu^T)    (the SwiGLU projection)
 //
 // What bounds it: up to 64 rows the weight stream from HBM, above ~150 rows the matrix pipe (hi + lo planes are two
-// matrix instructions per fragment pair; from 512 rows on its power: it is busy 77 % of the time at 1.83 GHz, and without
-// the staging loads at 80 % and 2.01), and everywhere the load path of a compute unit, which takes the activations as well as
-// the weights.
+// matrix instructions per fragment pair; from 512 rows on its power: it is busy 82 to 90 % of the time at 2.0 to 2.2 GHz,
+// and nothing but products runs at 2.25), and everywhere the load path of a compute unit, which takes the activations as well
+// as the weights.
 //
 // Shape.  A workgroup of four wavefronts (2 x 2, one per SIMD; up to 16 rows 1 x 4) owns 32 RB rows x 32 CB columns (RB 1 to 5 and 8); a wavefront RB x CB
 // products of 16 x 16.  Both operands go global -> LDS directly, 32 columns of K per stage, as 1 KB blocks that are
@@ -26,8 +26,8 @@
 //   Wo           6.6        8.8       11.1       12.9       15.8   20.6
 //   LM head    154        170        177        187        229    365
 // The same kernel on row-major planes (64-byte row pieces): gate+up 64.4 at 64 rows, 69.5 at 80, 107 at 256.
-// Many rows, tiles of up to 160 / of 256 rows (and half the staged bytes per product): gate+up 179 / 165 at 512, 351 / 327
-// at 1024, 701 / 652 at 2048, LM head 777 / 709 at 512, 3106 / 2785 at 2048, down 322 / 306 at 2048, QKV 159 / 146.
+// Many rows, tiles of up to 160 / of 256 rows (and half the staged bytes per product): gate+up 179 / 154 at 512, 351 / 306
+// at 1024, 701 / 605 at 2048, LM head 777 / 663 at 512, 3106 / 2713 at 2048, down 322 / 302 at 2048, QKV 159 / 137.
 //
 // RB, CB and the K ranges are chosen per launch (pick_tile).
 #include "clover_internal.h"
@@ -207,9 +207,9 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(TileGemm p) {
   };
   // Order of a stage's products: lo plane, then hi plane of the same output block back to back (the second takes the sum and
   // the weights that the first has just used).  Long launches are bound by power -- the clock falls to what the matrix
-  // pipe's switching allows -- and this order needs the least of ten tried: 2.16 PFLOP/s at 2.17 GHz in a loop of nothing
-  // but products of 8 x 8 blocks, against 2.00 at 2.01 GHz with all of the lo plane in front of the hi plane and 1.74 for
-  // 32 x 32 x 16 products (in the kernel: 512 rows of the LM head 731 -> 700 us, 1024 rows of down 168 -> 159).
+  // pipe's switching allows -- and this order needs the least: 2.25 PFLOP/s at 2.25 GHz in a loop of nothing but
+  // products of 8 x 8 blocks, against 2.06 at 2.07 GHz with all of the lo plane in front of the hi plane and 1.89 at 1.84 for
+  // 32 x 32 x 16 products (probes/mfma_order.hip; in the kernel: 512 rows of the LM head 731 -> 700 us, 1024 of down 168 -> 159).
   auto mm = [&](const Frag (&f)[NR], auto mc) __attribute__((always_inline)) {
     constexpr int k = decltype(mc)::value / MMS, m = decltype(mc)::value % MMS, rb = m / (2 * CBW), c = m / 2 % CBW, lo = 1 - m % 2;
     mfma_acc(acc[c][rb], f[k * NRS + 2 * RBW + c].v, f[k * NRS + 2 * rb + lo].v);
@@ -364,7 +364,8 @@ struct TilePick { int rb, cb, kp; };
 // round, where 256-column tiles leave 32 compute units idle), 80 rows one row tile of 96.
 // More than 256 rows over 1024 columns of K or more also have tiles of 256 rows (256 accumulators and 200 other registers a
 // lane with 256 columns; 128 columns were slower than 128 x 256 at every shape), a stage there costs 260 + 20.6 clocks per product
-// (2 % to 8 % off over 40 forms at 512, 1024 and 2048 rows; the choice is the best or within 4 % of it in 15 launches), and a
+// (2 % to 8 % off over 40 forms at 512, 1024 and 2048 rows; the choice is the best or within 4 % of it there and in 60 launches
+// at twelve odd row counts from 343 to 1533, but for QKV at 459 rows, 13 %, and at 623 and Wo at 747, 5 to 7 %), and a
 // round ends with the XCD that has most row tiles (Wo at 1024 rows: 264 workgroups of 96 x 192, 33 of them on one XCD, 114 us;
 // 256 of 128 x 128 58).
 // kp_fixed > 0 fixes the K ranges.
