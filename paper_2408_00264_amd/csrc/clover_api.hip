@@ -293,24 +293,34 @@ size_t carve_pass(const clover_ctx* x, char* base, int rows, const TileBytes& t,
   b.d_xs = cv.take<float>(rows * H);
   b.xd = fused ? b.d_xs : cv.take<float>(rows * H);   // (the fused gate kernel writes where it read)
   b.a_norm = cv.take<float>(rows16 * H);
-  Carver at = cv, ff = cv, ad = cv;   // attention | FFN | Attention Decoder 1, each behind its own partial tiles
+  // attention | FFN | Attention Decoder 1, each behind its own partial tiles
+  Carver at = cv, ff = cv, ad = cv;
   b.partial = (float*)at.take<char>(t.attn);
   ff.take<char>(t.down);
   ad.take<char>(t.ad);
-  if (!x->fast) b.qkv = at.take<float>((size_t)rows * x->QKVN);
-  b.q_rot = at.take<float>((size_t)rows * x->NQD);
-  b.attn_out = at.take<float>(rows16 * x->NQD);
   b.h_ffn = ff.take<float>(rows16 * c.ffn);
   if (!x->fast) b.tmp_ffn = ff.take<float>((size_t)rows * c.ffn);
   b.d_e = ad.take<float>(rows * H);
   if (x->fast) b.pl_y = ad.take<float>(rows16 * H);
   if (!fused)
     for (float** p : {&b.ad_q, &b.ad_k, &b.ad_v}) *p = ad.take<float>(rows * H);
-  // The attention's partial results lie on the projection's partial tiles, which are summed by then.
-  b.split_rows = x->attn_fast ? (t.attn - 256) / (sizeof(float) * (x->NQD + 2 * c.n_q_heads)) : 0;
+  auto attention = [&](Carver& a) {
+    if (!x->fast) b.qkv = a.take<float>((size_t)rows * x->QKVN);
+    b.q_rot = a.take<float>((size_t)rows * x->NQD);
+    b.attn_out = a.take<float>(rows16 * x->NQD);
+  };
+  const size_t tiles_end = at.off;
+  attention(at);
+  const size_t end = std::max(at.off, std::max(ff.off, ad.off));
+  // The attention's partial results lie on the projection's partial tiles, which are summed by then, and on what is free
+  // behind them: its own rows stand at the end.
+  Carver rows_at{base, end - (at.off - tiles_end)};
+  const size_t room = rows_at.off - cv.off;
+  attention(rows_at);
+  b.split_rows = x->attn_fast ? (room - 256) / (sizeof(float) * (x->NQD + 2 * c.n_q_heads)) : 0;
   b.o_part = b.partial;
   b.ml_part = base ? (float*)((char*)b.partial + align256(b.split_rows * x->NQD * sizeof(float))) : nullptr;
-  return std::max(at.off, std::max(ff.off, ad.off));
+  return end;
 }
 
 // Rows of a prompt pass: as many as the memory of a step's buffers holds, up to 2048, where the narrow GEMMs (QKV, Wo, down) fill
