@@ -432,11 +432,11 @@ void launch_attn_mfma(AttnParams p, int max_total_keys, FragPlanes out, hipStrea
   // 36.6 -> 22.7, a 2048-token prompt 224 -> 122; 16 KV heads, 8 x 60 nodes at 700 keys 41.1 -> 32.5)
   const int nodes = g == 1 && p.rm.n > 64 ? 128 : g <= 2 && p.rm.n > 32 ? 64 : 32;
   const int node_groups = (p.rm.n + nodes - 1) / nodes;
-  // Key splits by estimated time, in us, fitted to every split count of 283 launches (1 to 32 KV heads' groups of 1 to 8 heads, 1
+  // Key splits by estimated time, in us, fitted to every split count of 283 launches (8 and 32 KV heads, groups of 1 to 8 heads, 1
   // to 16 sequences, 1 to 128 nodes, 8 to 8192 keys, prompts to 2000 tokens; on average 1.7 % behind the best).  A key tile
   // takes a lone workgroup of a compute unit 1.05; two share it in 1.8, counted as two here, which keeps a second workgroup for
   // where it pays.  Splitting at all costs the merge launch and the traffic of the partial results, 2 + 0.2 per MB (32 heads, 8 KV
-  // heads: one node at 133 keys unsplit 14.9, in 3 splits 10.4; 64 nodes at 100 keys 17.1 and 15.3, at 1024 keys 47 and 19 in 12;
+  // heads: one node at 133 keys unsplit 14.9, in 3 splits 10.4; 64 nodes at 100 keys 17.1 and 15.3, at 1024 keys 52 and 19 in 12;
   // 128 nodes at 8192 keys 59.4 in 8, 55.5 in 16).  Where most keys are the launch's own new rows the workgroups' tiles grow from
   // one to all, so a split shortens only the last of them: 1.5 and 5.2 + 0.4 there (200 tokens unsplit 17.0, in 4 splits 20.9).
   const int wgs = p.rm.B * p.n_kv * node_groups, only = tune_int("CLOVER_ATTN_SPLITS", 0);

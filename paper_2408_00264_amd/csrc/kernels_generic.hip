@@ -676,7 +676,7 @@ static void launch_small_one(const SmallArgs& a, bool norm, dim3 grid, hipStream
 // Is the joint launch faster than what it replaces?  It saves launches and their round trips, and pays with a fifth of its
 // vector work for the squares, which every block sums for itself, and for SwiGLU with a second matrix that streams through the
 // L2 for every row block.  In units of blocks times columns of K, the crossings lie at (us, joint and separate):
-//   norm in front of one product    6 M   1024 wide: 128 x 2816 24.9 / 25.1, 128 x 4096 32.1 / 30.0; 4096: 48 x 2816 45.2 / 39.7
+//   norm in front of one product    6 M   1024 wide: 128 x 2816 24.9 / 25.1, 128 x 4096 32.1 / 30.0; 4096: 48 x 2816 45.2 / 39.9
 //   norm and three products        26 M   1024: 512 rows 85 / 96, 1024 rows 165 / 171; 4096, GQA: 64 rows 85.5 / 97, 128 rows 160 / 153
 //   norm, two products and SwiGLU  16 M   1024: 64 x 4096 33.8 / 38.7, 128 x 4096 61.7 / 59.6; 4096: 16 x 4096 33 / 50, 48 x 4096 98 / 93
 bool gemm_small_joins(const SmallGemm* g, int n, bool swiglu, int wdtype, int M, int K) {

@@ -4,7 +4,7 @@
 //   EPI 1:  out[M,F]    = planes of silu(X Wg^T) * (X Wu^T)    (the SwiGLU projection)
 //
 // What bounds it: up to 64 rows the weight stream from HBM, above ~150 rows the matrix pipe (hi + lo planes are two
-// matrix instructions per fragment pair; from 512 rows on its power: it is busy 82 to 90 % of the time at 2.0 to 2.2 GHz,
+// matrix instructions per fragment pair; from 512 rows on its power: it is busy 82 to 90 % of the time at 1.9 to 2.2 GHz,
 // and nothing but products runs at 2.25), and everywhere the load path of a compute unit, which takes the activations as well
 // as the weights.
 //
