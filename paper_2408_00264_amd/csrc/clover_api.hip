@@ -542,7 +542,7 @@ void run_layer(clover_ctx* x, const clover_layer_weights& lw, float* xres, RowMa
       } }
     const int sw = gemm_fast(x, KC_GEMM_WO, O, lw.wo, M, H, x->NQD);
     { Scope s(x, KC_RMSNORM);
-      launch_reduce_add_norm(xres, H, x->partial, sw, (size_t)M * H, H, lw.ffn_norm, c.dtype, c.rms_eps, A, M, H, x->st); }
+      launch_reduce_add_norm(xres, H, x->partial, sw, (size_t)M * H, H, lw.ffn_norm, c.rms_eps, A, M, H, x->st); }
     { Scope s(x, KC_GEMM_GATEUP);
       TileGemm g;
       memset(&g, 0, sizeof(g));
@@ -553,7 +553,7 @@ void run_layer(clover_ctx* x, const clover_layer_weights& lw, float* xres, RowMa
       launch_gemm_tile(g, x->st); }
     const int sd = gemm_fast(x, KC_GEMM_DOWN, Hf, lw.w_down, M, H, F);
     { Scope s(x, KC_RMSNORM);
-      launch_reduce_add_norm(xres, H, x->partial, sd, (size_t)M * H, H, next_gain, c.dtype, c.rms_eps, A, M, H, x->st); }
+      launch_reduce_add_norm(xres, H, x->partial, sd, (size_t)M * H, H, next_gain, c.rms_eps, A, M, H, x->st); }
     return;
   }
   // (few rows: the norm and the three projections in one launch, below the norm, both projections and SwiGLU)
@@ -594,7 +594,7 @@ FragPlanes norm_planes(clover_ctx* x, const float* src, const void* gain, int ro
   const clover_config& c = x->cfg;
   const FragPlanes A = frag_planes(x->a_norm, rows);
   Scope s(x, KC_RMSNORM);
-  launch_reduce_add_norm(const_cast<float*>(src), x->H, nullptr, 0, 0, 0, gain, c.dtype, c.rms_eps, A, rows, x->H, x->st);
+  launch_reduce_add_norm(const_cast<float*>(src), x->H, nullptr, 0, 0, 0, gain, c.rms_eps, A, rows, x->H, x->st);
   return A;
 }
 
@@ -746,7 +746,7 @@ void draft_expand_dynamic(clover_ctx* x, int B, const int* m, int* tree_tokens, 
         sp = gemm_fast(x, KC_GEMM_DRAFT, Cc, x->fc_w[j], rows, H, 2 * H);
       }
       { Scope s(x, KC_RMSNORM);
-        launch_reduce_add_norm(x->d_g, H, x->partial, sp, (size_t)rows * H, H, x->w.head_norm, c.dtype, c.rms_eps, A,
+        launch_reduce_add_norm(x->d_g, H, x->partial, sp, (size_t)rows * H, H, x->w.head_norm, c.rms_eps, A,
                                rows, H, x->st, j == 0 ? x->w.fc0_b : x->fc_b[j]); }
       lm_head_fast(x, A, rows, x->z);
     } else {
@@ -1140,7 +1140,7 @@ int draft_tree(clover_ctx* x, int32_t batch, const float* hid_acc, const int32_t
           sp = gemm_fast(x, KC_GEMM_DRAFT, Cc, x->fc_w[j], rows, H, 2 * H);
         }
         { Scope s(x, KC_RMSNORM);
-          launch_reduce_add_norm(x->d_g, H, x->partial, sp, (size_t)rows * H, H, x->w.head_norm, c.dtype, c.rms_eps, A,
+          launch_reduce_add_norm(x->d_g, H, x->partial, sp, (size_t)rows * H, H, x->w.head_norm, c.rms_eps, A,
                                  rows, H, x->st, j == 0 ? x->w.fc0_b : x->fc_b[j]); }
         lm_head_fast(x, A, rows, x->z);
         capture_draft_logits(x, j, rows);

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <stddef.h>
+#include <type_traits>
 
 #include "../../include/clover.h"
 #include "once_per_device.h"
@@ -54,6 +55,15 @@ __device__ __forceinline__ size_t kv_v_at(const KVLayout& kv, int b, int head, i
   return ((kv_page_of(kv, b, slot) * kv.n_kv + head) * kv.d + dim) * KV_PAGE + slot % KV_PAGE;
 }
 #endif
+
+// ---- launch helper -----------------------------------------------------------------------------
+// f(integral constant n) for n in LO .. HI: a kernel's loads of n partial results are counted at compile time
+template <int LO, int HI, class F>
+inline void with_count(int n, F&& f) {
+  if constexpr (LO < HI)
+    if (n > LO) return with_count<LO + 1, HI>(n, f);
+  f(std::integral_constant<int, LO>{});
+}
 
 // ---- staging loads: global -> LDS without a stop in registers -------------------------------------
 #ifdef __HIPCC__
@@ -199,10 +209,10 @@ void launch_split_planes(const float* x, int ldx, FragPlanes out, int rows, int 
 // Y[m,n] (=|+=) sum_s P[s*split_stride + m*ldp + n] (+ bias[n]);  mode 0 store, 1 add
 void launch_reduce(const float* P, int splits, size_t split_stride, int ldp, const void* bias, int wdtype, float* Y,
                    int ldy, int M, int N, int mode, hipStream_t st);
-// x[m,:] += sum_s P[s][m][:]  (splits may be 0); then, if gain: out[m,:] = planes of rmsnorm(x[m,:]) * gain
+// bf16 models: x[m,:] += sum_s P[s][m][:]  (splits may be 0); then, if gain: out[m,:] = planes of rmsnorm(x[m,:]) * gain
 // bias non-null: x[m,:] = bias + sum_s P[s][m][:] (the old x is not read)
 void launch_reduce_add_norm(float* x, int ldx, const float* P, int splits, size_t split_stride, int ldp,
-                            const void* gain, int wdtype, float eps, FragPlanes out, int rows, int H,
+                            const void* gain, float eps, FragPlanes out, int rows, int H,
                             hipStream_t st, const void* bias = nullptr);
 
 // ---- MFMA tree attention (head_dim 128, caches as bf16 planes) ---------------------------------

@@ -226,18 +226,32 @@ __device__ __forceinline__ void planes4(bf16_t* hi, bf16_t* lo, size_t off, cons
   *(uint2*)(hi + off) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
   *(uint2*)(lo + off) = make_uint2(l[0] | (l[1] << 16), l[2] | (l[3] << 16));
 }
-__device__ __forceinline__ float4 sum_partials4(const float* __restrict__ p, int nsp, size_t sps) {
-  float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int s0 = 0; s0 < nsp; s0 += 8) {
-    float4 q[8];
+// The K ranges are counted at compile time here and in reduce_add_norm_kernel: every load of a thread is requested in
+// straight-line code before the first is used.  With a runtime count the two halves of a pair were one round trip to memory
+// after the other, and most of the instructions were branches around loads of ranges that do not exist.  us per launch:
+// reduce_add_norm of 512 rows x 2 ranges 12.5 -> 10.0, 1024 x 1 17.9 -> 14.2, 2048 x 1 31.9 -> 26.2; rope_kv_planes of one row
+// x 8 ranges 5.6 -> 5.1, 64 x 4 5.2 -> 5.1, 512 x 2 10.8 -> 10.4.
+template <int NS>
+struct Partials4 {
+  float4 q[NS];
+  __device__ __forceinline__ void request(const float* __restrict__ p, size_t sps) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) q[j] = (s0 + j < nsp) ? *(const float4*)(p + (size_t)(s0 + j) * sps) : make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) { v.x += q[j].x; v.y += q[j].y; v.z += q[j].z; v.w += q[j].w; }
+    for (int s = 0; s < NS; ++s) q[s] = *(const float4*)(p + (size_t)s * sps);
   }
-  return v;
-}
-__global__ __launch_bounds__(256) void rope_kv_planes_kernel(const float* __restrict__ qkv, int ldqkv, int nsp, size_t sps,
+  __device__ __forceinline__ float4 add_to(float4 v) const {   // in range order
+#pragma unroll
+    for (int s = 0; s < NS; ++s) { v.x += q[s].x; v.y += q[s].y; v.z += q[s].z; v.w += q[s].w; }
+    return v;
+  }
+  __device__ __forceinline__ float4 sum() const { return add_to(make_float4(0.f, 0.f, 0.f, 0.f)); }
+};
+template <>
+struct Partials4<0> {
+  __device__ __forceinline__ void request(const float*, size_t) {}
+  __device__ __forceinline__ float4 add_to(float4 v) const { return v; }
+};
+template <int NS>
+__global__ __launch_bounds__(256) void rope_kv_planes_kernel(const float* __restrict__ qkv, int ldqkv, size_t sps,
                                                              const float* __restrict__ cos_t, const float* __restrict__ sin_t,
                                                              bf16_t* __restrict__ kc, bf16_t* __restrict__ vc, KVLayout kv,
                                                              const int* __restrict__ base_len, int n_q, RowMap rm,
@@ -252,7 +266,9 @@ __global__ __launch_bounds__(256) void rope_kv_planes_kernel(const float* __rest
     const int i = idx / per_row, rem = idx - i * per_row, hh = rem / quads, ii = (rem - hh * quads) * 4;
     const size_t row = (size_t)b * rm.R + min(i, rm.n - 1);
     const float* src = qkv + row * ldqkv + hh * d + ii;
-    const float4 x1 = sum_partials4(src, nsp, sps), x2 = sum_partials4(src + half, nsp, sps);
+    Partials4<NS> p1, p2;
+    p1.request(src, sps);
+    p2.request(src + half, sps);
     const float4 c = *(const float4*)(cos_t + row * half + ii), s = *(const float4*)(sin_t + row * half + ii);
     const int nv = rows_valid(rm, b), L = base_len[b];
     if (L + nv > kv.max_seq) {  // would overrun the cache: refuse, flag
@@ -260,6 +276,7 @@ __global__ __launch_bounds__(256) void rope_kv_planes_kernel(const float* __rest
       return;
     }
     if (i >= nv) return;
+    const float4 x1 = p1.sum(), x2 = p2.sum();
     float o1[4] = {x1.x * c.x - x2.x * s.x, x1.y * c.y - x2.y * s.y, x1.z * c.z - x2.z * s.z, x1.w * c.w - x2.w * s.w};
     float o2[4] = {x2.x * c.x + x1.x * s.x, x2.y * c.y + x1.y * s.y, x2.z * c.z + x1.z * s.z, x2.w * c.w + x1.w * s.w};
     if (hh < n_q) {
@@ -276,18 +293,19 @@ __global__ __launch_bounds__(256) void rope_kv_planes_kernel(const float* __rest
     const int n_eb = n_kv * d / 32;
     const int vblk = blockIdx.x - qk_blocks, eb = vblk % n_eb, nb0 = (vblk / n_eb) * 64;
     const int voff = (n_q + n_kv) * d + eb * 32;
-    float4 v[2];
+    Partials4<NS> p[2];
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       const int f = tid + 256 * j, node = min(nb0 + f / 8, rm.n - 1), e4 = (f % 8) * 4;
-      v[j] = sum_partials4(qkv + ((size_t)b * rm.R + node) * ldqkv + voff + e4, nsp, sps);
+      p[j].request(qkv + ((size_t)b * rm.R + node) * ldqkv + voff + e4, sps);
     }
     const int nv = rows_valid(rm, b), L = base_len[b];
     if (L + nv > kv.max_seq) return;  // (flagged by the first block)
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       const int f = tid + 256 * j, e4 = (f % 8) * 4;
-      tile[f / 8][e4] = v[j].x; tile[f / 8][e4 + 1] = v[j].y; tile[f / 8][e4 + 2] = v[j].z; tile[f / 8][e4 + 3] = v[j].w;
+      const float4 v = p[j].sum();
+      tile[f / 8][e4] = v.x; tile[f / 8][e4 + 1] = v.y; tile[f / 8][e4 + 2] = v.z; tile[f / 8][e4 + 3] = v.w;
     }
     __syncthreads();
     const int nl = tid % 64, node = nb0 + nl;
@@ -308,13 +326,15 @@ void launch_rope_kv_write(const float* qkv, int ldqkv, int qkv_splits, size_t qk
                           const float* sin_t, float* q_out, int ldq,
                           void* k_cache, void* v_cache, int kvdtype, KVLayout kv, const int* base_len, int n_q,
                           RowMap rm, int* err_flag, bf16_t* q_hi, bf16_t* q_lo, float q_scale, hipStream_t st) {
-  if (kvdtype == 1 && q_hi && kv.d % 32 == 0 && ldqkv % 4 == 0 && qkv_split_stride % 4 == 0 && ldq % 4 == 0) {
+  if (kvdtype == 1 && q_hi && kv.d % 32 == 0 && ldqkv % 4 == 0 && qkv_split_stride % 4 == 0 && ldq % 4 == 0 && qkv_splits <= TILE_MAX_K_PARTS) {
     const int per_row = (n_q + kv.n_kv) * (kv.d / 8);
     const int qk_blocks = (rm.n * per_row + 255) / 256;
     const int v_blocks = (kv.n_kv * kv.d / 32) * ((rm.n + 63) / 64);
-    rope_kv_planes_kernel<<<dim3(qk_blocks + v_blocks, rm.B), 256, 0, st>>>(
-        qkv, ldqkv, qkv_splits, qkv_split_stride, cos_t, sin_t, (bf16_t*)k_cache, (bf16_t*)v_cache, kv, base_len, n_q, rm,
-        err_flag, qk_blocks, q_hi, q_lo, ldq, q_scale);
+    with_count<1, TILE_MAX_K_PARTS>(qkv_splits, [&](auto nc) {
+      rope_kv_planes_kernel<decltype(nc)::value><<<dim3(qk_blocks + v_blocks, rm.B), 256, 0, st>>>(
+          qkv, ldqkv, qkv_split_stride, cos_t, sin_t, (bf16_t*)k_cache, (bf16_t*)v_cache, kv, base_len, n_q, rm,
+          err_flag, qk_blocks, q_hi, q_lo, ldq, q_scale);
+    });
     return;
   }
   const int vblocks = (kv.n_kv * kv.d + 7) / 8;
@@ -1164,74 +1184,84 @@ void launch_reduce(const float* P, int splits, size_t split_stride, int ldp, con
     reduce_kernel<bf16_t><<<grid, 256, 0, st>>>(P, splits, split_stride, ldp, (const bf16_t*)bias, Y, ldy, N, mode);
 }
 
-// one 1024-thread block per row: residual add of the partial tiles over K ranges (sixteen loads in flight per
-// thread, summed in split order), then RMSNorm written as planes in fragment order.  A thread keeps its (up to two)
-// float4 of the new row in registers across the block-wide sum of squares; wider rows re-read them.
-template <typename WT>
+// One block of up to 1024 threads per row: residual add of the partial tiles over NS ranges of K (all requested at once,
+// summed in range order), then RMSNorm written as planes in fragment order.  A thread keeps PC float4 of the new row in
+// registers across the block-wide sum of squares; rows wider than PC * 4096 re-read the rest.
+typedef bf16_t bf16x4_any __attribute__((ext_vector_type(4), aligned(2)));   // (weights owe no alignment beyond their element's)
+__device__ __forceinline__ float4 ld4_any(const bf16_t* p) {
+  const bf16x4_any u = *(const bf16x4_any*)p;
+  return make_float4(bf16_to_f32(u[0]), bf16_to_f32(u[1]), bf16_to_f32(u[2]), bf16_to_f32(u[3]));
+}
+template <int NS, int PC>
 __global__ __launch_bounds__(1024) void reduce_add_norm_kernel(float* __restrict__ x, int ldx,
-                                                               const float* __restrict__ P, int splits, size_t sps,
-                                                               int ldp, const WT* __restrict__ gain, float eps,
-                                                               FragPlanes out, int H, const WT* __restrict__ bias) {
+                                                               const float* __restrict__ P, size_t sps, int ldp,
+                                                               const bf16_t* __restrict__ gain, float eps,
+                                                               FragPlanes out, int H, const bf16_t* __restrict__ bias) {
   __shared__ float red[16];
   const size_t row = blockIdx.x;
   float* xr = x + row * ldx;
   const float* pr = P + row * ldp;
-  float ss = 0.f;
-  auto new_row = [&](int c) -> float4 {
-    float4 v = bias ? make_float4(ldf(bias, c), ldf(bias, c + 1), ldf(bias, c + 2), ldf(bias, c + 3))
-                    : *(const float4*)(xr + c);
-    for (int s0 = 0; s0 < splits; s0 += 16) {
-      float4 q[16];
+  const int c0 = threadIdx.x * 4, step = blockDim.x * 4;
+  float4 keep[PC], gn[PC];
+  Partials4<NS> q[PC];
 #pragma unroll
-      for (int j = 0; j < 16; ++j)
-        q[j] = (s0 + j < splits) ? *(const float4*)(pr + (size_t)(s0 + j) * sps + c) : make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-      for (int j = 0; j < 16; ++j) { v.x += q[j].x; v.y += q[j].y; v.z += q[j].z; v.w += q[j].w; }
-    }
-    if (splits > 0 || bias) *(float4*)(xr + c) = v;
-    ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
-    return v;
-  };
-  auto gain4 = [&](int c) { return make_float4(ldf(gain, c), ldf(gain, c + 1), ldf(gain, c + 2), ldf(gain, c + 3)); };
-  const int c0 = threadIdx.x * 4;
-  float4 keep[2], gn[2];
-#pragma unroll
-  for (int it = 0; it < 2; ++it) {  // (static indices: the two kept pieces live in registers)
-    const int c = c0 + it * 4096;
+  for (int it = 0; it < PC; ++it) {  // (static indices: the kept pieces live in registers)
+    const int c = c0 + it * step;
     if (c < H) {
-      if (gain) gn[it] = gain4(c);
-      keep[it] = new_row(c);
+      q[it].request(pr + c, sps);
+      keep[it] = bias ? ld4_any(bias + c) : *(const float4*)(xr + c);
+      if (gain) gn[it] = ld4_any(gain + c);
     }
   }
-  for (int c = c0 + 8192; c < H; c += 4096) new_row(c);
+  float ss = 0.f;
+  auto put = [&](int c, float4 v) {
+    if (NS > 0 || bias) *(float4*)(xr + c) = v;
+    ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+  };
+#pragma unroll
+  for (int it = 0; it < PC; ++it) {
+    const int c = c0 + it * step;
+    if (c < H) { keep[it] = q[it].add_to(keep[it]); put(c, keep[it]); }
+  }
+  if (PC > 1)
+    for (int c = c0 + PC * step; c < H; c += step) {
+      Partials4<NS> r;
+      r.request(pr + c, sps);
+      put(c, r.add_to(bias ? ld4_any(bias + c) : *(const float4*)(xr + c)));
+    }
   if (!gain) return;
   ss = wave_sum(ss);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
   __syncthreads();
   float tot = 0.f;
 #pragma unroll
-  for (int w = 0; w < 16; ++w) tot += red[w];
+  for (int w = 0; w < 16; ++w)
+    if (w * 64 < (int)blockDim.x) tot += red[w];
   const float scale = 1.0f / sqrtf(tot / (float)H + eps);
   auto emit = [&](int c, float4 v, float4 g4) {
     frag_store4(out, (int)row, c, v.x * scale * g4.x, v.y * scale * g4.y, v.z * scale * g4.z, v.w * scale * g4.w);
   };
 #pragma unroll
-  for (int it = 0; it < 2; ++it) {
-    const int c = c0 + it * 4096;
+  for (int it = 0; it < PC; ++it) {
+    const int c = c0 + it * step;
     if (c < H) emit(c, keep[it], gn[it]);
   }
-  for (int c = c0 + 8192; c < H; c += 4096) emit(c, *(const float4*)(xr + c), gain4(c));  // written by this same thread above
+  if (PC > 1)
+    for (int c = c0 + PC * step; c < H; c += step) emit(c, *(const float4*)(xr + c), ld4_any(gain + c));  // written by this same thread above
 }
+// splits <= TILE_MAX_K_PARTS; gain and bias are bf16
 void launch_reduce_add_norm(float* x, int ldx, const float* P, int splits, size_t split_stride, int ldp,
-                            const void* gain, int wdtype, float eps, FragPlanes out, int rows, int H,
+                            const void* gain, float eps, FragPlanes out, int rows, int H,
                             hipStream_t st, const void* bias) {
   if (rows <= 0) return;
-  if (wdtype == 0)
-    reduce_add_norm_kernel<float><<<rows, 1024, 0, st>>>(x, ldx, P, splits, split_stride, ldp, (const float*)gain, eps,
-                                                        out, H, (const float*)bias);
-  else
-    reduce_add_norm_kernel<bf16_t><<<rows, 1024, 0, st>>>(x, ldx, P, splits, split_stride, ldp, (const bf16_t*)gain,
-                                                         eps, out, H, (const bf16_t*)bias);
+  with_count<0, TILE_MAX_K_PARTS>(splits, [&](auto nc) {
+    constexpr int NS = decltype(nc)::value;
+    const int threads = std::min(1024, (H / 4 + 63) / 64 * 64);
+    if (H <= 4096)
+      reduce_add_norm_kernel<NS, 1><<<rows, threads, 0, st>>>(x, ldx, P, split_stride, ldp, (const bf16_t*)gain, eps, out, H, (const bf16_t*)bias);
+    else
+      reduce_add_norm_kernel<NS, 2><<<rows, threads, 0, st>>>(x, ldx, P, split_stride, ldp, (const bf16_t*)gain, eps, out, H, (const bf16_t*)bias);
+  });
 }
 
 }  // namespace clv
