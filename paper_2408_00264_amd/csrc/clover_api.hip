@@ -502,12 +502,20 @@ void gemm_generic(clover_ctx* x, int cls, const float* X, int ldx, const void* W
   launch_gemm_generic(X, ldx, W, bias, x->cfg.dtype, Y, ldy, M, N, K, mode, x->st);
 }
 
+// The split of the MFMA attention over the sequences of `rm` (M rows in all) behind at most cached[b] keys each.
+AttnPlan plan_attention(clover_ctx* x, const int* cached, const RowMap& rm, int M, bool chain) {
+  if (!x->attn_fast) return AttnPlan{};
+  std::vector<int> keys(rm.B);
+  for (int b = 0; b < rm.B; ++b) keys[b] = cached[b] + rm.n;
+  return attn_plan(keys.data(), rm.B, rm.n, x->cfg.n_kv_heads, x->cfg.n_q_heads, chain, (int)(x->split_rows / M));
+}
+
 // One LLaMA decoder layer over the rows of `rm` (residual stream xres, leading dimension H).
 // MFMA path: on entry the planes of a_norm hold RMSNorm(xres) * attn_norm of this layer; on exit they
 // hold RMSNorm(xres) * next_gain (skipped when next_gain is null).  Generic path: norms are computed here.
 void run_layer(clover_ctx* x, const clover_layer_weights& lw, float* xres, RowMap rm, int M, char* kc_layer,
                char* vc_layer, const int* base_len, const unsigned long long* anc, const void* next_gain,
-               int key_bound, int anc_stride = 0 /* nodes per sequence in a per-sequence mask table */,
+               const AttnPlan& attn /* of the MFMA attention */, int anc_stride = 0 /* nodes per sequence in a per-sequence mask table */,
                const int* iv = nullptr /* interval labels: decide visibility instead of anc */,
                int seq0 = 0 /* the rows belong to sequence seq0 + (their index in rm) */) {
   const clover_config& c = x->cfg;
@@ -534,8 +542,8 @@ void run_layer(clover_ctx* x, const clover_layer_weights& lw, float* xres, RowMa
         ap.v_hi = (const bf16_t*)vc_layer; ap.v_plane = x->v_layer_elems;
         ap.kv = kvl; ap.max_seq = c.max_seq; ap.n_kv = c.n_kv_heads; ap.n_q = c.n_q_heads;
         ap.base_len = base_len; ap.anc = anc; ap.iv = iv; ap.anc_stride = anc_stride; ap.rm = rm;
-        ap.o_part = x->o_part; ap.ml_part = x->ml_part; ap.rows_total = M; ap.max_splits = (int)(x->split_rows / M);
-        launch_attn_mfma(ap, key_bound, O, x->st);
+        ap.o_part = x->o_part; ap.ml_part = x->ml_part; ap.rows_total = M; ap.out = O; ap.plan = attn;
+        launch_attn_mfma(ap, x->st);
       } else {
         launch_attn_generic(x->q_rot, x->NQD, kc_layer, vc_layer, x->kvdtype, kvl, base_len, anc, c.n_q_heads, nullptr,
                             x->NQD, O, rm, x->st, anc_stride, iv);
@@ -1071,8 +1079,7 @@ int draft_tree(clover_ctx* x, int32_t batch, const float* hid_acc, const int32_t
   // route packs them (16 sequences x 32 nodes: 80 rows instead of 485)
   const RowMap in{B, R, n, m}, rm{B, fused ? n : R, n, m};
   const int M = (B - 1) * rm.R + n;
-  int aug_bound = 0;
-  for (int b = 0; b < B; ++b) aug_bound = std::max(aug_bound, x->aug_ub[b] + n);
+  const AttnPlan plan = plan_attention(x, x->aug_ub.data(), rm, M, true);
   if (fused) {
     const FragPlanes A = frag_planes(x->a_norm, M), Y = frag_planes(x->pl_y, M);
     // embeddings of the follow-up tokens come from the LM-head rows; AD1 over (hidden state, embedding)
@@ -1094,7 +1101,7 @@ int draft_tree(clover_ctx* x, int32_t batch, const float* hid_acc, const int32_t
   for (int l = 0; l < c.aug_layers; ++l)
     run_layer(x, x->aug[l], x->xd, rm, M, x->aug_kc + (size_t)l * x->k_layer_elems * x->kv_esz,
               x->aug_vc + (size_t)l * x->v_layer_elems * x->kv_esz, x->d_aug_len, nullptr /* the new rows form a chain */,
-              l + 1 < c.aug_layers ? x->aug[l + 1].attn_norm : nullptr, aug_bound);
+              l + 1 < c.aug_layers ? x->aug[l + 1].attn_norm : nullptr, plan);
   {
     // root state and token: node 0 of the static tree, candidate 0 of the dynamic one
     float* root_state = x->dyn_on ? x->dyn_state : x->d_state;
@@ -1190,8 +1197,7 @@ int verify_tree(clover_ctx* x, int32_t batch, const int32_t* tree_tokens, float*
     if (x->len_ub[b] + n_nodes > c.max_seq) return fail(x, CLOVER_E_CAPACITY, "sequence could exceed max_seq (call clover_seq_len to refresh the bound)");
   const RowMap rm{B, R, n_nodes, nullptr};
   const int M = (B - 1) * R + n_nodes;
-  int key_bound = 0;
-  for (int b = 0; b < B; ++b) key_bound = std::max(key_bound, x->len_ub[b] + n_nodes);
+  const AttnPlan plan = plan_attention(x, x->len_ub.data(), rm, M, false);
   { Scope s(x, KC_EMBED); launch_embed(x->w.embed, c.dtype, tree_tokens, c.vocab, hidden, H, H, rm, x->st); }
   { Scope s(x, KC_ROPE_KV);
     launch_rope_table(x->d_seq_len, depth_tab, c.rope_base, c.head_dim, x->cos_t, x->sin_t, rm, x->st, topo_stride); }
@@ -1199,7 +1205,7 @@ int verify_tree(clover_ctx* x, int32_t batch, const int32_t* tree_tokens, float*
   for (int l = 0; l < c.n_layers; ++l)
     run_layer(x, x->layers[l], hidden, rm, M, x->kc + (size_t)l * x->k_layer_elems * x->kv_esz,
               x->vc + (size_t)l * x->v_layer_elems * x->kv_esz, x->d_seq_len, anc_tab,
-              l + 1 < c.n_layers ? x->layers[l + 1].attn_norm : x->w.final_norm, key_bound, topo_stride, iv_tab);
+              l + 1 < c.n_layers ? x->layers[l + 1].attn_norm : x->w.final_norm, plan, topo_stride, iv_tab);
   if (x->fast) {
     lm_head_fast(x, frag_planes(x->a_norm, M), M, logits);
   } else {
@@ -1276,11 +1282,11 @@ int clover_prefill(clover_ctx* x, int32_t b, const int32_t* tokens, int32_t n, f
     { Scope s(x, KC_EMBED); launch_embed(x->w.embed, c.dtype, tokens + c0, c.vocab, xres, H, H, rm, x->st); }
     { Scope s(x, KC_ROPE_KV); launch_rope_table(len_b, nullptr, c.rope_base, c.head_dim, x->cos_t, x->sin_t, rm, x->st); }
     if (x->fast) norm_planes(x, xres, x->layers[0].attn_norm, M);
-    const int key_bound = x->len_ub[b] + M;
+    const AttnPlan plan = plan_attention(x, &x->len_ub[b], rm, M, true);
     for (int l = 0; l < c.n_layers; ++l)
       run_layer(x, x->layers[l], xres, rm, M, x->kc + (size_t)l * x->k_layer_elems * x->kv_esz,
                 x->vc + (size_t)l * x->v_layer_elems * x->kv_esz, len_b, nullptr,
-                l + 1 < c.n_layers ? x->layers[l + 1].attn_norm : nullptr, key_bound, 0, nullptr, b);
+                l + 1 < c.n_layers ? x->layers[l + 1].attn_norm : nullptr, plan, 0, nullptr, b);
     { Scope s(x, KC_DRAFT_MISC); launch_add_scalar(len_b, M, x->st); }
     x->len_ub[b] += M;
     if (last) {
@@ -1305,11 +1311,11 @@ int clover_prefill(clover_ctx* x, int32_t b, const int32_t* tokens, int32_t n, f
       run_ad(x, x->w.ad1, xres, x->d_e, Md, x->xd);
       { Scope s(x, KC_ROPE_KV); launch_rope_table(aug_len_b, nullptr, c.rope_base, c.head_dim, x->cos_t, x->sin_t, rd, x->st); }
       if (x->fast) norm_planes(x, x->xd, x->aug[0].attn_norm, Md);
-      const int aug_bound = x->aug_ub[b] + Md;
+      const AttnPlan plan_d = plan_attention(x, &x->aug_ub[b], rd, Md, true);
       for (int l = 0; l < c.aug_layers; ++l)
         run_layer(x, x->aug[l], x->xd, rd, Md, x->aug_kc + (size_t)l * x->k_layer_elems * x->kv_esz,
                   x->aug_vc + (size_t)l * x->v_layer_elems * x->kv_esz, aug_len_b, nullptr,
-                  l + 1 < c.aug_layers ? x->aug[l + 1].attn_norm : nullptr, aug_bound, 0, nullptr, b);
+                  l + 1 < c.aug_layers ? x->aug[l + 1].attn_norm : nullptr, plan_d, 0, nullptr, b);
       { Scope s(x, KC_DRAFT_MISC); launch_add_scalar(aug_len_b, Md, x->st); }
       x->aug_ub[b] += Md;
     }

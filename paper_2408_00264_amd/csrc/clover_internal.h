@@ -216,6 +216,16 @@ void launch_reduce_add_norm(float* x, int ldx, const float* P, int splits, size_
                             hipStream_t st, const void* bias = nullptr);
 
 // ---- MFMA tree attention (head_dim 128, caches as bf16 planes) ---------------------------------
+// How the key tiles of a launch's sequences are dealt to workgroups.  Every sequence is cut into ranges of `tiles` key tiles, so a
+// short one has fewer ranges than a long one; a unit is a (sequence, range).  With a table unit[u] = sequence | range << 8 | (the
+// only range: 1) << 15, ranges[b] = ranges of sequence b; without (more sequences or units than it holds) all sequences have `most` ranges,
+// those behind a sequence's last tile idle.
+constexpr int ATTN_TAB = 256;
+struct AttnPlan {
+  int tiles, n_units, most, tab;
+  unsigned short unit[ATTN_TAB];
+  unsigned char ranges[ATTN_TAB];
+};
 struct AttnParams {
   const bf16_t *q_hi, *q_lo; int ldq;    // [rows, n_q*128] planes: RoPE applied, scaled by 1/sqrt(128)
   const bf16_t* k_hi; size_t k_plane;    // K planes of one layer (paged, see KVLayout); lo = hi + k_plane
@@ -228,15 +238,17 @@ struct AttnParams {
                                          //   when given they decide visibility instead of the bit sets
   int anc_stride;                        // nodes per sequence in a per-sequence mask table, 0: one table for all
   RowMap rm;
-  float* o_part;                         // [max_splits][rows_total][n_q][128]
-  float* ml_part;                        // [max_splits][rows_total][n_q][2]
-  int rows_total, max_splits;
-  int tiles_per_split, n_splits;         // filled in by launch_attn_mfma
-  FragPlanes out;                        // finished rows where there is one split; filled in by launch_attn_mfma
+  float* o_part;                         // [plan.most][rows_total][n_q][128]
+  float* ml_part;                        // [plan.most][rows_total][n_q][2]
+  int rows_total;
+  FragPlanes out;                        // finished rows
+  AttnPlan plan;
 };
 bool attn_mfma_supported(int head_dim, int n_q, int n_kv, int max_seq);
-// max_total_keys: host-side upper bound of base_len[b] + rm.n over the batch (sizes the key splits)
-void launch_attn_mfma(AttnParams p, int max_total_keys, FragPlanes out, hipStream_t st);
+// keys[b]: host-side upper bound of base_len[b] + n for each of the B sequences of n rows; max_ranges: what the partial results
+// have room for; chain: the rows form a chain
+AttnPlan attn_plan(const int* keys, int B, int n, int n_kv, int n_q, bool chain, int max_ranges);
+void launch_attn_mfma(const AttnParams& p, hipStream_t st);
 
 // ---- fragment-major weights and the GEMM that reads them ----------------------------------------
 // [N,K] row-major bf16 -> rows row0 .. row0+N-1 of a packed matrix of n_rows rows, [K/32][n_rows/16][64 lanes][8]: lane

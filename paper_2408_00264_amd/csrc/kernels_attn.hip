@@ -16,9 +16,10 @@
 // What bounds it: the waits between the steps of a tile (matrix pipe 69 % busy over the 2048-row passes of an 8192-token prompt,
 // two workgroups to a CU, 42 % with one, 96 nodes at 8192 keys), so what counts is wavefronts in flight (120 registers and 66 KB of LDS: two workgroups of eight to a
 // CU), independent work inside a wavefront (scores of the next tile beside the probabilities of this one) and no exchange
-// between lanes.  8B shape, 8 KV heads, us per launch, before (tiles one after the other, row maximum exchanged in every tile)
-// and now: 64 nodes at 1024 keys 14.1 / 12.9, 96 at 8192 54.9 / 47.8, 8 x 32 ragged to 2048 37.1 / 35.1, one row at 1024
-// 9.1 / 8.1, prompts in 2048-row passes 475 / 342 (8192 tokens, average).  Two blocks of 16 nodes per wavefront (half the
+// between lanes.  A launch of few tiles is mostly its first ones: Q, then the tiles that are in no cache, are requested before
+// anything is waited for (64 nodes at 1024 keys: scores of the first tile 5 us after the launch's start, 2.7 for two more tiles, 1.9
+// for the results).  8B shape, 8 KV heads, us per launch: 64 nodes at 1024 keys 12.6, 96 at 8192 45, 8 x 32 ragged to 2048
+// 30, one row at 1024 7.6, prompts in 2048-row passes 342 (8192 tokens, average).  Two blocks of 16 nodes per wavefront (half the
 // LDS reads) need 220 registers and with them half the wavefronts: 574 there.  Reading fragments two pairs ahead by
 // scheduling barriers: 360.
 //
@@ -69,7 +70,8 @@ constexpr int AT_TK = KV_PAGE;    // keys per tile = one page of the caches
 // sub-tile tt, head-dim columns 32 ks ..), V^T: blocks [plane][db] (head-dim rows 16 db .., the 32 keys).
 constexpr int AT_FRAG = 512;                  // bf16 elements of a fragment block
 constexpr int AT_KSTAGE = 16 * AT_FRAG, AT_VSTAGE = 16 * AT_FRAG;   // one staged tile: 16 KB of K, 16 KB of V^T
-constexpr int AT_NKB = 2, AT_NVB = 2;         // K and V^T buffers: tile i in buffers i % 2
+constexpr int AT_NKB = 2, AT_NVB = 2;         // K and V^T buffers: tile i in buffers i % 2 (four of each, requested three tiles ahead:
+                                              // 0.7 to 1 us slower in every launch from 3 to 26 tiles a workgroup)
 constexpr int AT_LDS_EL = AT_NKB * AT_KSTAGE + AT_NVB * AT_VSTAGE;
 constexpr float LOG2E = 1.44269504088896f;
 constexpr float AT_SLACK = 8.f;               // log2 of how far a score may exceed the reference of the soft-max
@@ -90,11 +92,20 @@ __global__ __launch_bounds__(64 * G * WM) void attn_mfma_kernel(AttnParams p) {
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int l16 = lane & 15, g4 = lane >> 4;
   const bool chain = p.anc == nullptr && p.iv == nullptr;
-  // (a chain's last nodes see most keys: their workgroups first, so that the short ones fill the gaps at the end)
-  const int ngi = blockIdx.y / p.n_kv, ng = chain ? (int)gridDim.y / p.n_kv - 1 - ngi : ngi;
-  const int split = blockIdx.x, kvh = blockIdx.y % p.n_kv, b = blockIdx.z;
+  // Grid: KV heads (ids 8 apart share an XCD), then the node groups that read the same tiles, then the units.  A chain's last nodes
+  // see most keys: its node groups are outermost, the last ones first, so that the short ones fill the gaps at the end.
+  const int kvh = blockIdx.x, ng = chain ? (int)gridDim.z - 1 - (int)blockIdx.z : (int)blockIdx.y;
+  const int unit = chain ? blockIdx.y : blockIdx.z;
+  int b, split;
+  bool whole;   // the sequence has one range: no partial results
+  if (p.plan.tab) {
+    const unsigned ent = p.plan.unit[unit];
+    b = (int)(ent & 255u); split = (int)(ent >> 8 & 127u); whole = (ent >> 15) != 0;
+  } else {
+    b = unit / p.plan.most; split = unit - b * p.plan.most; whole = p.plan.most == 1;
+  }
   const RowMap& rm = p.rm;
-  const int t0 = split * p.tiles_per_split;
+  const int t0 = split * p.plan.tiles;
   const int head = kvh * G + wave % G;
   const int node0 = ng * NODES + (wave / G) * MB * 16;   // this wavefront's first node
 
@@ -143,10 +154,32 @@ __global__ __launch_bounds__(64 * G * WM) void attn_mfma_kernel(AttnParams p) {
       lds_load16<false>((gbyte_ptr)src, v_lane, lds0 + 2u * (unsigned)(AT_NKB * AT_KSTAGE + buf * AT_VSTAGE + f * AT_FRAG));
     }
   };
-  // The first key tile is requested before anything else is waited for (its address needs the page table only:
-  // keys past the cache are clamped and masked later), so its HBM latency overlaps the loads of the lengths,
+  // ---- Q fragments (already scaled and split by the RoPE kernel) and masks: requested in front of the first tiles, which are
+  // not in any cache and would hold them up (loads return in order), and before the lengths are known.  Rows behind the last
+  // node read some row's and are multiplied along; their results are never stored.
+  Frag qh[MB][4], ql[MB][4];
+  unsigned long long a0[MB], a1[MB];
+  int my_enter[MB];
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb) {
+    const int node = min(node0 + mb * 16 + l16, rm.n - 1);
+    const size_t qo = ((size_t)b * rm.R + node) * p.ldq + head * AT_D + g4 * 8, mo = 2 * ((size_t)b * p.anc_stride + node);
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      qh[mb][ks].u = *(const u32x4*)(p.q_hi + qo + ks * 32);
+      ql[mb][ks].u = *(const u32x4*)(p.q_lo + qo + ks * 32);
+    }
+    const bool bits = !chain && !p.iv;
+    a0[mb] = bits ? p.anc[mo] : 0ull;
+    a1[mb] = bits ? p.anc[mo + 1] : 0ull;
+    my_enter[mb] = p.iv ? p.iv[mo] : 0;
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  // The first tiles are requested before anything else is waited for (their addresses need the page table only:
+  // keys past the cache are clamped and masked later), so their HBM latency overlaps the loads of the lengths,
   // the masks and Q.
   stage_k(0, page_of(0));
+  if (p.plan.tiles > 1) stage_k(1, page_of(1));   // (used if the range has a second tile)
   stage_v(0, page_of(0));
   const int nv = rm.n_valid ? min(rm.n_valid[b], rm.n) : rm.n;
   const int L = p.base_len[b];
@@ -161,33 +194,7 @@ __global__ __launch_bounds__(64 * G * WM) void attn_mfma_kernel(AttnParams p) {
   const bool work = __builtin_amdgcn_readfirstlane(node0) < nv;   // (a wavefront without nodes only helps with the staging)
   const int open = L + (chain ? ng * NODES : 0);
   const int n_tiles = ((chain ? min(total, L + ng * NODES + NODES) : total) + AT_TK - 1) / AT_TK;
-  const int n = min(n_tiles, t0 + p.tiles_per_split) - t0;   // tiles of this split (<= 0: none)
-  if (n > 1) stage_k(1, page_of(1));
-
-  // ---- Q fragments (already scaled and split by the RoPE kernel), ancestor masks ----
-  Frag qh[MB][4], ql[MB][4];
-  unsigned long long a0[MB], a1[MB];
-  int my_enter[MB];
-#pragma unroll
-  for (int mb = 0; mb < MB; ++mb) {
-    const int node = node0 + mb * 16 + l16;
-    const bool ok = node < nv;
-    const bool bits = !chain && !p.iv;
-    a0[mb] = ok && bits ? p.anc[2 * ((size_t)b * p.anc_stride + node)] : 0ull;
-    a1[mb] = ok && bits ? p.anc[2 * ((size_t)b * p.anc_stride + node) + 1] : 0ull;
-    my_enter[mb] = ok && p.iv ? p.iv[2 * ((size_t)b * p.anc_stride + node)] : 0;
-    const size_t qo = ((size_t)b * rm.R + (ok ? node : 0)) * p.ldq + head * AT_D + g4 * 8;
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      qh[mb][ks].u = (u32x4){0u, 0u, 0u, 0u};
-      ql[mb][ks].u = (u32x4){0u, 0u, 0u, 0u};
-      if (ok) {
-        qh[mb][ks].u = *(const u32x4*)(p.q_hi + qo + ks * 32);
-        ql[mb][ks].u = *(const u32x4*)(p.q_lo + qo + ks * 32);
-      }
-    }
-  }
-
+  const int n = min(n_tiles, t0 + p.plan.tiles) - t0;   // tiles of this split (<= 0: none)
   f32x4 O[8][MB];
 #pragma unroll
   for (int db = 0; db < 8; ++db)
@@ -307,7 +314,7 @@ __global__ __launch_bounds__(64 * G * WM) void attn_mfma_kernel(AttnParams p) {
     }
   };
 
-  // ---- the loop over this split's key tiles: the scores of tile i + 1 (matrix pipe) are computed beside the probabilities of
+  // ---- the loop over this range's key tiles: the scores of tile i + 1 (matrix pipe) are computed beside the probabilities of
   // tile i (vector ALU), so K runs one tile ahead of V^T.  Requested at the top of iteration i: K tile i + 2 into the buffer of
   // tile i (its scores were computed in iteration i - 1, every wavefront is past that barrier), V^T tile i + 1.  Both are
   // complete, and visible to every wavefront, at the barrier that ends iteration i: each wavefront waits for its own
@@ -342,8 +349,8 @@ __global__ __launch_bounds__(64 * G * WM) void attn_mfma_kernel(AttnParams p) {
     if (work) { probabilities(sa, ph, pl); output((n - 1) & 1, ph, pl); }
   }
 
-  wait_staging<0>();   // (a split without tiles still has its first staging loads in flight)
-  // ---- one split: the finished rows as planes; several: the partial result of this split ----
+  wait_staging<0>();   // (a range without tiles still has its first staging loads in flight)
+  // ---- one range of keys: the finished rows as planes; several: the partial result of this range ----
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb) {
     const int node = node0 + mb * 16 + l16;
@@ -352,7 +359,7 @@ __global__ __launch_bounds__(64 * G * WM) void attn_mfma_kernel(AttnParams p) {
     lsum += __shfl_xor(lsum, 32, 64);
     if (node >= nv) continue;
     const size_t row = (size_t)b * rm.R + node;
-    if (p.n_splits == 1) {
+    if (whole) {
 #pragma unroll
       for (int db = 0; db < 8; ++db) {
         const f32x4 v = O[db][mb];
@@ -373,41 +380,55 @@ __global__ __launch_bounds__(64 * G * WM) void attn_mfma_kernel(AttnParams p) {
   }
 }
 
-// merge the splits of one (row, head): out = sum_s 2^{m_s - M} O_s / sum_s 2^{m_s - M} l_s, as planes.
-// One thread owns four adjacent channels of one head; the (m, l) pairs and then the partial rows of
-// all splits are loaded as one batch each, so a thread waits for memory twice, not once per split.
+// merge the ranges of one (row, head): out = sum_s 2^{m_s - M} O_s / sum_s 2^{m_s - M} l_s, as planes.
+// One thread owns four adjacent channels of one head; the (m, l) pairs and the partial rows of all ranges are requested before
+// the first is used.  The number of ranges is rounded up to one of a few compile-time counts (the last range again, weight 0).
 constexpr int MG_HEADS = 8;   // heads per workgroup (32 threads each)
-constexpr int MG_MAXS = 16;   // >= the largest split count the launcher picks
-__global__ __launch_bounds__(MG_HEADS * 32) void attn_merge_kernel(const float* __restrict__ o_part,
-                                                                    const float* __restrict__ ml_part, int n_splits,
-                                                                    int rows_total, int n_q, FragPlanes out, RowMap rm) {
-  const int i = blockIdx.x, b = blockIdx.y;
-  const int head = blockIdx.z * MG_HEADS + (threadIdx.x >> 5), d4 = (threadIdx.x & 31) * 4;
-  const int nv = rm.n_valid ? min(rm.n_valid[b], rm.n) : rm.n;
-  if (i >= nv || head >= n_q) return;
-  const size_t row = (size_t)b * rm.R + i;
-  const size_t sstride = (size_t)rows_total * n_q;   // (row, head) pairs per split
-  const size_t pr0 = row * n_q + head;
-  float2 ml[MG_MAXS];
+constexpr int MG_MAXS = 16;   // >= the largest number of ranges that attn_plan picks
+template <int NS>
+__device__ __forceinline__ void merge_ranges(const float* __restrict__ o, const float* __restrict__ ml_p, size_t stride, int ns,
+                                             const FragPlanes& out, int row, int col) {
+  float2 ml[NS];
+  float4 v[NS];
 #pragma unroll
-  for (int s = 0; s < MG_MAXS; ++s)
-    ml[s] = s < n_splits ? *(const float2*)(ml_part + (pr0 + s * sstride) * 2) : make_float2(-INFINITY, 0.f);
-  float4 o[MG_MAXS];
+  for (int s = 0; s < NS; ++s) ml[s] = *(const float2*)(ml_p + (size_t)min(s, ns - 1) * stride * 2);
 #pragma unroll
-  for (int s = 0; s < MG_MAXS; ++s)
-    o[s] = s < n_splits ? *(const float4*)(o_part + (pr0 + s * sstride) * AT_D + d4) : make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int s = 0; s < NS; ++s) v[s] = *(const float4*)(o + (size_t)min(s, ns - 1) * stride * AT_D);
   float M = -INFINITY;
 #pragma unroll
-  for (int s = 0; s < MG_MAXS; ++s) M = fmaxf(M, ml[s].x);
+  for (int s = 0; s < NS; ++s) M = fmaxf(M, ml[s].x);
   float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
   float den = 0.f;
 #pragma unroll
-  for (int s = 0; s < MG_MAXS; ++s) {  // split order: the sum does not depend on how the loads were batched
-    const float wgt = ml[s].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml[s].x - M);
+  for (int s = 0; s < NS; ++s) {  // in range order
+    const float wgt = s >= ns || ml[s].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml[s].x - M);
     den += wgt * ml[s].y;
-    num.x += wgt * o[s].x; num.y += wgt * o[s].y; num.z += wgt * o[s].z; num.w += wgt * o[s].w;
+    num.x += wgt * v[s].x; num.y += wgt * v[s].y; num.z += wgt * v[s].z; num.w += wgt * v[s].w;
   }
-  frag_store4(out, (int)row, head * AT_D + d4, num.x / den, num.y / den, num.z / den, num.w / den);
+  frag_store4(out, row, col, num.x / den, num.y / den, num.z / den, num.w / den);
+}
+struct MergeArgs {
+  const float *o_part, *ml_part;
+  int rows_total, n_q, most, tab;
+  FragPlanes out;
+  RowMap rm;
+  unsigned char ranges[ATTN_TAB];
+};
+__global__ __launch_bounds__(MG_HEADS * 32) void attn_merge_kernel(MergeArgs p) {
+  const int i = blockIdx.x, b = blockIdx.y;
+  const int head = blockIdx.z * MG_HEADS + (threadIdx.x >> 5), d4 = (threadIdx.x & 31) * 4;
+  const int ns = p.tab ? (int)p.ranges[b] : p.most;
+  const RowMap& rm = p.rm;
+  const int nv = rm.n_valid ? min(rm.n_valid[b], rm.n) : rm.n;
+  if (ns == 1 || i >= nv || head >= p.n_q) return;   // (one range: the attention kernel has written the rows)
+  const size_t row = (size_t)b * rm.R + i;
+  const size_t stride = (size_t)p.rows_total * p.n_q;   // (row, head) pairs per range
+  const size_t pr0 = row * p.n_q + head;
+  const float *o = p.o_part + pr0 * AT_D + d4, *ml = p.ml_part + pr0 * 2;
+  if (ns <= 4) merge_ranges<4>(o, ml, stride, ns, p.out, (int)row, head * AT_D + d4);
+  else if (ns <= 8) merge_ranges<8>(o, ml, stride, ns, p.out, (int)row, head * AT_D + d4);
+  else if (ns <= 12) merge_ranges<12>(o, ml, stride, ns, p.out, (int)row, head * AT_D + d4);
+  else merge_ranges<16>(o, ml, stride, ns, p.out, (int)row, head * AT_D + d4);
 }
 
 bool attn_mfma_supported(int head_dim, int n_q, int n_kv, int max_seq) {
@@ -424,14 +445,16 @@ static void launch_attn_one(const AttnParams& p, dim3 grid, hipStream_t st) {
   attn_mfma_kernel<G, WM, MB><<<grid, 64 * G * WM, lds, st>>>(p);
 }
 
-void launch_attn_mfma(AttnParams p, int max_total_keys, FragPlanes out, hipStream_t st) {
-  const int g = p.n_q / p.n_kv;
-  const int n_tiles = (max_total_keys + AT_TK - 1) / AT_TK;
-  // Nodes per workgroup: with one or two query heads per KV head 64 or 128 where they are there, so that up to eight
-  // wavefronts share a staged tile (32 heads of their own K/V, us: 64 nodes at 512 keys 13.6 -> 11.2, 128 nodes at 1500 keys
-  // 36.6 -> 22.7, a 2048-token prompt 224 -> 122; 16 KV heads, 8 x 60 nodes at 700 keys 41.1 -> 32.5)
-  const int nodes = g == 1 && p.rm.n > 64 ? 128 : g <= 2 && p.rm.n > 32 ? 64 : 32;
-  const int node_groups = (p.rm.n + nodes - 1) / nodes;
+// Nodes per workgroup: with one or two query heads per KV head 64 or 128 where they are there, so that up to eight
+// wavefronts share a staged tile (32 heads of their own K/V, us: 64 nodes at 512 keys 13.6 -> 11.2, 128 nodes at 1500 keys
+// 36.6 -> 22.7, a 2048-token prompt 224 -> 122; 16 KV heads, 8 x 60 nodes at 700 keys 41.1 -> 32.5)
+static int group_nodes(int g, int n) { return g == 1 && n > 64 ? 128 : g <= 2 && n > 32 ? 64 : 32; }
+
+AttnPlan attn_plan(const int* keys, int B, int n, int n_kv, int n_q, bool chain, int max_ranges) {
+  const int nodes = group_nodes(n_q / n_kv, n), per_unit = n_kv * ((n + nodes - 1) / nodes);
+  int most_keys = 0;
+  for (int b = 0; b < B; ++b) most_keys = std::max(most_keys, keys[b]);
+  const int n_tiles = (most_keys + AT_TK - 1) / AT_TK;
   // Key splits by estimated time, in us, fitted to every split count of 283 launches (8 and 32 KV heads, groups of 1 to 8 heads, 1
   // to 16 sequences, 1 to 128 nodes, 8 to 8192 keys, prompts to 2000 tokens; on average 1.7 % behind the best).  A key tile
   // takes a lone workgroup of a compute unit 1.05; two share it in 1.8, counted as two here, which keeps a second workgroup for
@@ -439,21 +462,46 @@ void launch_attn_mfma(AttnParams p, int max_total_keys, FragPlanes out, hipStrea
   // heads: one node at 133 keys unsplit 14.9, in 3 splits 10.4; 64 nodes at 100 keys 17.1 and 15.3, at 1024 keys 52 and 19 in 12;
   // 128 nodes at 8192 keys 59.4 in 8, 55.5 in 16).  Where most keys are the launch's own new rows the workgroups' tiles grow from
   // one to all, so a split shortens only the last of them: 1.5 and 5.2 + 0.4 there (200 tokens unsplit 17.0, in 4 splits 20.9).
-  const int wgs = p.rm.B * p.n_kv * node_groups, only = tune_int("CLOVER_ATTN_SPLITS", 0);
-  const double mb = (double)p.rm.B * p.rm.n * p.n_q * AT_D * 4e-6;
-  const bool fresh = p.anc == nullptr && p.iv == nullptr && 2 * p.rm.n > max_total_keys;
+  // With equally many ranges for all sequences the longest one would set every workgroup's tiles and the short ones' workgroups
+  // would idle; ranges of equal length give the short ones fewer.  Sequences of 32 nodes between 256 and 2048 keys, us: 8 of them
+  // 37 -> 30, 16 of them 63 -> 46; 2 x 40 nodes at 238 and 1252 keys 16.6 -> 13.8.
+  const int only = tune_int("CLOVER_ATTN_SPLITS", 0), limit = std::min(max_ranges, MG_MAXS);
+  const double mb = (double)n * n_q * AT_D * 4e-6;   // of a range's partial results
+  const bool fresh = chain && 2 * n > most_keys;
   const double tile = fresh ? 1.5 : 1.05, merge = fresh ? 5.2 : 2.0, per_mb = fresh ? 0.4 : 0.2;
-  int splits = 1;
+  const bool table = B <= ATTN_TAB;
+  AttnPlan plan{n_tiles, B, 1, 0, {}, {}};
   double best = 1e30;
-  for (int s = 1; s <= std::min(p.max_splits, MG_MAXS) && s <= (n_tiles + 1) / 2; ++s) {
-    const int tiles = (n_tiles + s - 1) / s, n = (n_tiles + tiles - 1) / tiles;
-    const double t = tile * tiles * ((wgs * n + 255) / 256) + (n > 1 ? merge + per_mb * mb * n : 0.0);
-    if (only > 0 ? s <= only : t < best) { best = t; splits = s; }
+  const int step = (n_tiles + 255) / 256;   // (long caches: 256 lengths of a range are looked at)
+  for (int c = n_tiles; c >= std::min(2, n_tiles) && (n_tiles + c - 1) / c <= limit; c -= step) {
+    const int most = (n_tiles + c - 1) / c;
+    int units = 0, parts = 0;
+    for (int b = 0; b < B; ++b) {
+      const int r = ((keys[b] + AT_TK - 1) / AT_TK + c - 1) / c;
+      units += r;
+      parts += r > 1 ? r : 0;
+    }
+    const bool tab = table && units <= ATTN_TAB && units != B * most;   // (equally many ranges each need no table)
+    if (!tab) { units = B * most; parts = most > 1 ? units : 0; }
+    const double t = tile * c * ((units * per_unit + 255) / 256) + (most > 1 ? merge + per_mb * mb * parts : 0.0);
+    if (only > 0 ? most <= only : t < best) { best = t; plan.tiles = c; plan.n_units = units; plan.most = most; plan.tab = tab; }
   }
-  p.tiles_per_split = (n_tiles + splits - 1) / splits;
-  p.n_splits = (n_tiles + p.tiles_per_split - 1) / p.tiles_per_split;
-  p.out = out;
-  dim3 grid(p.n_splits, node_groups * p.n_kv, p.rm.B);
+  if (plan.tab) {
+    int u = 0;
+    for (int b = 0; b < B; ++b) {
+      const int r = ((keys[b] + AT_TK - 1) / AT_TK + plan.tiles - 1) / plan.tiles;
+      plan.ranges[b] = (unsigned char)r;
+      for (int s = 0; s < r; ++s) plan.unit[u++] = (unsigned short)(b | s << 8 | (r == 1 ? 0x8000 : 0));
+    }
+  }
+  return plan;
+}
+
+void launch_attn_mfma(const AttnParams& p, hipStream_t st) {
+  const int g = p.n_q / p.n_kv, nodes = group_nodes(g, p.rm.n);
+  const unsigned groups = (unsigned)((p.rm.n + nodes - 1) / nodes), units = (unsigned)p.plan.n_units;
+  const bool chain = p.anc == nullptr && p.iv == nullptr;
+  const dim3 grid((unsigned)p.n_kv, chain ? units : groups, chain ? groups : units);
   switch (g) {
     case 1:
       if (nodes == 128) launch_attn_one<1, 8, 1>(p, grid, st);
@@ -464,9 +512,11 @@ void launch_attn_mfma(AttnParams p, int max_total_keys, FragPlanes out, hipStrea
     case 4: launch_attn_one<4, 2, 1>(p, grid, st); break;
     default: launch_attn_one<8, 1, 2>(p, grid, st); break;
   }
-  if (p.n_splits > 1)
-    attn_merge_kernel<<<dim3(p.rm.n, p.rm.B, (p.n_q + MG_HEADS - 1) / MG_HEADS), MG_HEADS * 32, 0, st>>>(
-        p.o_part, p.ml_part, p.n_splits, p.rows_total, p.n_q, out, p.rm);
+  if (p.plan.most > 1) {
+    MergeArgs m{p.o_part, p.ml_part, p.rows_total, p.n_q, p.plan.most, p.plan.tab, p.out, p.rm, {}};
+    std::copy(p.plan.ranges, p.plan.ranges + ATTN_TAB, m.ranges);
+    attn_merge_kernel<<<dim3(p.rm.n, p.rm.B, (p.n_q + MG_HEADS - 1) / MG_HEADS), MG_HEADS * 32, 0, st>>>(m);
+  }
 }
 
 }  // namespace clv
