@@ -350,7 +350,7 @@ void carve(clover_ctx* x, char* base, size_t* total) {
   x->QKVN = (c.n_q_heads + 2 * c.n_kv_heads) * d;
   x->k_layer_elems = (size_t)B * c.max_seq * c.n_kv_heads * d;
   x->d_pages = cv.take<int>((size_t)B * (c.max_seq / KV_PAGE));
-  x->kv = KVLayout{B, c.max_seq, c.n_kv_heads, d, x->k_layer_elems, c.max_seq / KV_PAGE, 0, nullptr};
+  x->kv = KVLayout{B, c.max_seq, c.n_kv_heads, d, 1, 0, c.max_seq / KV_PAGE, 0, nullptr};
   x->v_layer_elems = x->k_layer_elems;
   x->d_seq_len = cv.take<int>(B);
   x->d_aug_len = cv.take<int>(B);
@@ -401,6 +401,8 @@ void carve(clover_ctx* x, char* base, size_t* total) {
   x->packed = cv.take<char>(packed_bytes ? packed_bytes : 256);
   x->fast = fast;
   x->kvdtype = fast ? 1 : 0;
+  x->kv.planes = fast ? 2 : 1;
+  x->kv.plane = fast ? (size_t)KV_PAGE * d : 0;
   x->kv_layer_stride = fast ? 2 * x->k_layer_elems : x->k_layer_elems;
   x->attn_fast = fast && attn_mfma_supported(d, c.n_q_heads, c.n_kv_heads, c.max_seq);
   // From here on nothing outlives the call that wrote it, so a prompt pass may lay it out in its own way.
@@ -538,8 +540,7 @@ void run_layer(clover_ctx* x, const clover_layer_weights& lw, float* xres, RowMa
         AttnParams ap;
         memset(&ap, 0, sizeof(ap));
         ap.q_hi = q_hi; ap.q_lo = q_lo; ap.ldq = x->NQD;
-        ap.k_hi = (const bf16_t*)kc_layer; ap.k_plane = x->k_layer_elems;
-        ap.v_hi = (const bf16_t*)vc_layer; ap.v_plane = x->v_layer_elems;
+        ap.k = (const bf16_t*)kc_layer; ap.v = (const bf16_t*)vc_layer;
         ap.kv = kvl; ap.max_seq = c.max_seq; ap.n_kv = c.n_kv_heads; ap.n_q = c.n_q_heads;
         ap.base_len = base_len; ap.anc = anc; ap.iv = iv; ap.anc_stride = anc_stride; ap.rm = rm;
         ap.o_part = x->o_part; ap.ml_part = x->ml_part; ap.rows_total = M; ap.out = O; ap.plan = attn;

@@ -29,30 +29,40 @@ struct RowMap {
 constexpr int KV_PAGE = 32;   // cached positions per page (= the key tile of the MFMA attention)
 struct KVLayout {
   // Paged caches, one pair per layer.  A page holds KV_PAGE consecutive positions of one sequence for all KV heads:
-  //   K page:  [n_kv][KV_PAGE][d]      V page (transposed):  [n_kv][d][KV_PAGE]
-  // so the K rows and the V^T columns of one (page, head) -- one key tile of the attention -- are one contiguous
-  // block each.  Position `slot` of sequence b lives in page pages[(b + b0) * T + slot / KV_PAGE] (identity when
-  // pages is null), at row slot % KV_PAGE.
-  // kvdtype 0: fp32 elements.  kvdtype 1: each cache is two bf16 planes (hi, then lo `plane` elements
-  // later) with hi + lo == value to 16 mantissa bits -- the operand format of the MFMA attention.
+  // so K, and V^T, of one (page, head) -- one key tile of the attention -- are one contiguous block each.  Position `slot` of
+  // sequence b lives in page pages[(b + b0) * T + slot / KV_PAGE] (identity when pages is null), at row r = slot % KV_PAGE.
+  //   planes 1 (kvdtype 0): fp32 elements, K [n_kv][KV_PAGE][d], V transposed [n_kv][d][KV_PAGE].
+  //   planes 2 (kvdtype 1): two bf16 planes (hi, then lo `plane` elements later) with hi + lo == value to 16 mantissa bits,
+  // [n_kv][planes][KV_PAGE x d] in the order in which the MFMA attention stages a block: KBs of 64 lanes x 8 elements, lane
+  // 16 g + l of KB (half, k) of K holding row 8 (l / 4) + 4 half + l % 4, columns 32 k + 8 g .., of KB k of V^T row (channel)
+  // 16 k + l, positions 8 g ...  A staging load then takes its KB lane by lane; with rows in the cache its lanes jumped by 256
+  // bytes in K and by 64 in V^T.  And a key tile is two streams of 16 KB instead of four of 8.  Attention, us per
+  // launch: 96 nodes at 8192 keys 49 -> 45, a 1024-token prompt 53.7 -> 50.5, an 8192-token one 345 -> 342.
   int max_batch, max_seq, n_kv, d;
+  int planes;
   size_t plane;
   int T;               // pages per sequence = max_seq / KV_PAGE
   int b0;              // added to every sequence index (a call that works on one sequence of the batch)
   const int* pages;    // dev [max_batch * T] page table, or null
 };
 #ifdef __HIPCC__
-__device__ __forceinline__ size_t kv_page_of(const KVLayout& kv, int b, int slot) {
+// element index of block (page, head) of the position
+__device__ __forceinline__ size_t kv_block(const KVLayout& kv, int b, int slot, int head) {
   const int lp = (b + kv.b0) * kv.T + slot / KV_PAGE;
-  return (size_t)(kv.pages ? kv.pages[lp] : lp);
+  return ((size_t)(kv.pages ? kv.pages[lp] : lp) * kv.n_kv + head) * kv.planes * (KV_PAGE * kv.d);
 }
-// element index of K[b][slot][head][0] (d contiguous elements follow)
+// element index of K[b][slot][head][c] = kv_k_at + kv_k_col(c); four columns c % 4 == 0 are contiguous
 __device__ __forceinline__ size_t kv_k_at(const KVLayout& kv, int b, int slot, int head) {
-  return ((kv_page_of(kv, b, slot) * kv.n_kv + head) * KV_PAGE + slot % KV_PAGE) * kv.d;
+  const int r = slot % KV_PAGE;
+  return kv_block(kv, b, slot, head) + (kv.planes == 1 ? r * kv.d : ((r >> 2) & 1) * 16 * kv.d + ((r >> 3) * 4 + (r & 3)) * 8);
 }
-// element index of V^T[b][head][dim][slot] (the rest of the page's positions follow contiguously)
+__device__ __forceinline__ int kv_k_col(const KVLayout& kv, int c) {
+  return kv.planes == 1 ? c : (c >> 5) * 512 + ((c >> 3) & 3) * 128 + (c & 7);
+}
+// element index of V^T[b][head][dim][slot]; four positions slot % 4 == 0 are contiguous
 __device__ __forceinline__ size_t kv_v_at(const KVLayout& kv, int b, int head, int dim, int slot) {
-  return ((kv_page_of(kv, b, slot) * kv.n_kv + head) * kv.d + dim) * KV_PAGE + slot % KV_PAGE;
+  const int r = slot % KV_PAGE;
+  return kv_block(kv, b, slot, head) + (kv.planes == 1 ? dim * KV_PAGE + r : (dim >> 4) * 512 + ((r >> 3) * 16 + (dim & 15)) * 8 + (r & 7));
 }
 #endif
 
@@ -228,8 +238,7 @@ struct AttnPlan {
 };
 struct AttnParams {
   const bf16_t *q_hi, *q_lo; int ldq;    // [rows, n_q*128] planes: RoPE applied, scaled by 1/sqrt(128)
-  const bf16_t* k_hi; size_t k_plane;    // K planes of one layer (paged, see KVLayout); lo = hi + k_plane
-  const bf16_t* v_hi; size_t v_plane;    // V^T planes
+  const bf16_t *k, *v;                   // K and V^T planes of one layer (paged, see KVLayout)
   KVLayout kv;
   int max_seq, n_kv, n_q;
   const int* base_len;                   // dev [B]

@@ -109,19 +109,16 @@ __global__ __launch_bounds__(64 * G * WM) void attn_mfma_kernel(AttnParams p) {
   const int head = kvh * G + wave % G;
   const int node0 = ng * NODES + (wave / G) * MB * 16;   // this wavefront's first node
 
-  // ---- staging: global -> LDS without a stop in registers.  A wavefront instruction moves one fragment block: lane l
-  // fetches the 16 bytes the MFMA operand layout wants at l * 16 (K: key 8 (l%16 / 4) + 4 tt + l%16 % 4, columns
-  // 32 ks + 8 (l / 16) ..; V^T: row 16 db + l % 16, keys 8 (l / 16) ..) and the hardware writes them to
-  // (LDS base of the block) + l * 16.  The 16 blocks of a K and of a V^T tile are dealt to the workgroup's wavefronts.
-  // Key tile t of this sequence is page pages[b * T + t] of the paged caches: the K rows and the V^T columns of
-  // (page, KV head) are one contiguous 8 KB block each per plane.  An address is a uniform base plus the lane's 32-bit
-  // offset, so staging costs no vector-ALU instruction.  The compiler is not told that these loads write the LDS (it would wait for all of
+  // ---- staging: global -> LDS without a stop in registers.  A wavefront instruction moves one fragment block, a contiguous KB of
+  // the cache, which holds the 16 bytes that the MFMA operand layout wants of lane l at l * 16 (K: key 8 (l%16 / 4) + 4 tt +
+  // l%16 % 4, columns 32 ks + 8 (l / 16) ..; V^T: row 16 db + l % 16, keys 8 (l / 16) ..).  The 16 blocks of a K and of a V^T
+  // tile are dealt to the workgroup's wavefronts.  Key tile t of this sequence is page pages[b * T + t] of the paged caches: K
+  // and V^T of (page, KV head) are 16 contiguous KB each.  An address is a uniform base plus the lane's 32-bit offset, so staging costs no vector-ALU instruction.  The compiler is not told that these loads write the LDS (it would wait for all of
   // them before every LDS read that follows): the waits before the barriers below are written by hand.
   constexpr int NT = 64 * G * WM, NW = G * WM;
   constexpr int FPW = 16 / NW;          // K blocks and V^T blocks per wavefront and tile
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-  const unsigned k_lane = (unsigned)((((l16 >> 2) * 8 + (l16 & 3)) * AT_D + g4 * 8) * 2);   // bytes
-  const unsigned v_lane = (unsigned)((l16 * AT_TK + g4 * 8) * 2);
+  const unsigned lane_off = (unsigned)lane * 16u;
   bf16_t* const k_lds = sm;
   bf16_t* const v_lds = sm + AT_NKB * AT_KSTAGE;
   const KVLayout& kv = p.kv;
@@ -136,24 +133,16 @@ __global__ __launch_bounds__(64 * G * WM) void attn_mfma_kernel(AttnParams p) {
   auto page_of = [&](int i) __attribute__((always_inline)) -> int { return __builtin_amdgcn_readlane(pgv, i & 63); };
   read_pages(0);
   const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)sm;   // LDS byte address of sm
-  auto stage_k = [&](int buf, int page) __attribute__((always_inline)) {
-    const size_t blk = ((size_t)page * kv.n_kv + kvh) * (size_t)(KV_PAGE * AT_D);   // elements; K and V^T blocks are equal
+  auto stage = [&](const bf16_t* cache, int page, int at /* LDS element */) __attribute__((always_inline)) {
+    const bf16_t* src = cache + ((size_t)page * kv.n_kv + kvh) * (size_t)(2 * KV_PAGE * AT_D);   // K and V^T blocks are equal
 #pragma unroll
     for (int j = 0; j < FPW; ++j) {
-      const int f = wave_u * FPW + j, plane = f >> 3;
-      const bf16_t* src = p.k_hi + blk + (size_t)plane * p.k_plane + ((f >> 2) & 1) * 4 * AT_D + (f & 3) * 32;
-      lds_load16<false>((gbyte_ptr)src, k_lane, lds0 + 2u * (unsigned)(buf * AT_KSTAGE + f * AT_FRAG));
+      const int f = wave_u * FPW + j;
+      lds_load16<false>((gbyte_ptr)(src + f * AT_FRAG), lane_off, lds0 + 2u * (unsigned)(at + f * AT_FRAG));
     }
   };
-  auto stage_v = [&](int buf, int page) __attribute__((always_inline)) {
-    const size_t blk = ((size_t)page * kv.n_kv + kvh) * (size_t)(KV_PAGE * AT_D);
-#pragma unroll
-    for (int j = 0; j < FPW; ++j) {
-      const int f = wave_u * FPW + j, plane = f >> 3;
-      const bf16_t* src = p.v_hi + blk + (size_t)plane * p.v_plane + (f & 7) * 16 * AT_TK;
-      lds_load16<false>((gbyte_ptr)src, v_lane, lds0 + 2u * (unsigned)(AT_NKB * AT_KSTAGE + buf * AT_VSTAGE + f * AT_FRAG));
-    }
-  };
+  auto stage_k = [&](int buf, int page) __attribute__((always_inline)) { stage(p.k, page, buf * AT_KSTAGE); };
+  auto stage_v = [&](int buf, int page) __attribute__((always_inline)) { stage(p.v, page, AT_NKB * AT_KSTAGE + buf * AT_VSTAGE); };
   // ---- Q fragments (already scaled and split by the RoPE kernel) and masks: requested in front of the first tiles, which are
   // not in any cache and would hold them up (loads return in order), and before the lengths are known.  Rows behind the last
   // node read some row's and are multiplied along; their results are never stored.

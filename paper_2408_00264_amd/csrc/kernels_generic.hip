@@ -196,8 +196,8 @@ __global__ void rope_kv_write_kernel(const float* __restrict__ qkv, int ldqkv, i
       }
     } else {
       const size_t base = kv_k_at(kv, b, slot, hh - n_q);
-      stkv(kc, base + ii, kv.plane, o1);
-      stkv(kc, base + ii + half, kv.plane, o2);
+      stkv(kc, base + kv_k_col(kv, ii), kv.plane, o1);
+      stkv(kc, base + kv_k_col(kv, ii + half), kv.plane, o2);
     }
   } else {
     const int vb = blockIdx.x - rm.n * hc;
@@ -285,9 +285,9 @@ __global__ __launch_bounds__(256) void rope_kv_planes_kernel(const float* __rest
       planes4(q_hi, q_lo, row * ldq + hh * d + ii, o1);
       planes4(q_hi, q_lo, row * ldq + hh * d + ii + half, o2);
     } else {
-      const size_t base = kv_k_at(kv, b, L + i, hh - n_q) + ii;
-      planes4(kc, kc + kv.plane, base, o1);
-      planes4(kc, kc + kv.plane, base + half, o2);
+      const size_t base = kv_k_at(kv, b, L + i, hh - n_q);
+      planes4(kc, kc + kv.plane, base + kv_k_col(kv, ii), o1);
+      planes4(kc, kc + kv.plane, base + kv_k_col(kv, ii + half), o2);
     }
   } else {
     const int n_eb = n_kv * d / 32;
@@ -409,14 +409,15 @@ __global__ __launch_bounds__(64) void attn_generic_kernel(const float* __restric
     const size_t kr = kv_k_at(kv, b, min(s, kv.max_seq - 1), g);
     float4 kx[D / 4];
 #pragma unroll
-    for (int c = 0; c < D / 4; ++c) kx[c] = ldkv4(kc, kr + c * 4, kv.plane);
+    for (int c = 0; c < D / 4; ++c)   // (kv_k_col(4 c), at compile time)
+      kx[c] = ldkv4(kc, kr + (std::is_same<KT, float>::value ? c * 4 : (c >> 3) * 512 + ((c >> 1) & 3) * 128 + (c & 1) * 4), kv.plane);
     float4 vx[16];
     auto load_v = [&](int u) __attribute__((always_inline)) {   // channel lane + 64 u of the tile's two pages
 #pragma unroll
       for (int pg = 0; pg < 2; ++pg) {
         const size_t at = kv_v_at(kv, b, g, lane + 64 * u, min(t * 64 + pg * KV_PAGE, kv.max_seq - KV_PAGE));
 #pragma unroll
-        for (int c = 0; c < 8; ++c) vx[pg * 8 + c] = ldkv4(vc, at + c * 4, kv.plane);
+        for (int c = 0; c < 8; ++c) vx[pg * 8 + c] = ldkv4(vc, at + (std::is_same<KT, float>::value ? c * 4 : (c >> 1) * 128 + (c & 1) * 4), kv.plane);
       }
     };
     load_v(0);
@@ -1069,7 +1070,7 @@ __global__ void compact_kv_kernel(KT* __restrict__ kc, KT* __restrict__ vc, KVLa
   for (int i = 0; i < mb; ++i) {
     const int a = acc_idx[(size_t)b * R + i];
     if (a == i || a < 0 || L + a >= kv.max_seq) continue;
-    mvkv(kbase, kv_k_at(kv, b, L + i, head) + dim, kv_k_at(kv, b, L + a, head) + dim, kv.plane);
+    mvkv(kbase, kv_k_at(kv, b, L + i, head) + kv_k_col(kv, dim), kv_k_at(kv, b, L + a, head) + kv_k_col(kv, dim), kv.plane);
     mvkv(vbase, kv_v_at(kv, b, head, dim, L + i), kv_v_at(kv, b, head, dim, L + a), kv.plane);
   }
 }
@@ -1107,7 +1108,7 @@ __global__ void read_kv_kernel(const KT* __restrict__ kc, const KT* __restrict__
   const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= (size_t)n_slots * width) return;
   const int s = (int)(idx / width), col = (int)(idx % width);
-  k_out[idx] = ldkv(kc, kv_k_at(kv, b, slot0 + s, col / kv.d) + col % kv.d, kv.plane);
+  k_out[idx] = ldkv(kc, kv_k_at(kv, b, slot0 + s, col / kv.d) + kv_k_col(kv, col % kv.d), kv.plane);
   v_out[idx] = ldkv(vc, kv_v_at(kv, b, col / kv.d, col % kv.d, slot0 + s), kv.plane);
 }
 void launch_read_kv(const void* k_cache, const void* v_cache, int kvdtype, KVLayout kv, int b, int slot0, int n_slots,
@@ -1130,7 +1131,7 @@ __global__ void write_kv_kernel(KT* __restrict__ kc, KT* __restrict__ vc, KVLayo
   const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= (size_t)n_slots * width) return;
   const int s = (int)(idx / width), col = (int)(idx % width);
-  stkv(kc, kv_k_at(kv, b, slot0 + s, col / kv.d) + col % kv.d, kv.plane, k_in[idx]);
+  stkv(kc, kv_k_at(kv, b, slot0 + s, col / kv.d) + kv_k_col(kv, col % kv.d), kv.plane, k_in[idx]);
   stkv(vc, kv_v_at(kv, b, col / kv.d, col % kv.d, slot0 + s), kv.plane, v_in[idx]);
 }
 void launch_write_kv(void* k_cache, void* v_cache, int kvdtype, KVLayout kv, int b, int slot0, int n_slots,
