@@ -50,8 +50,6 @@ struct TreeHost {
   std::vector<int> parent, rank, depth, first_child, n_child;
   std::vector<int> lvl_nodes;           // internal nodes, grouped by depth
   std::vector<int> lvl_off;             // [max_depth+2]: internal nodes of depth j are lvl_nodes[lvl_off[j]..lvl_off[j+1])
-  std::vector<int> par_row;             // per node: index of its parent within the parent's depth group
-  std::vector<int> node_off;            // [max_depth+2]: nodes of depth j are [node_off[j], node_off[j+1])
   std::vector<int> kmax;                // per depth j: 1 + max rank among children of depth-j nodes
   std::vector<unsigned long long> anc;  // [n][2] (all zero for trees of more than 128 nodes: those use the labels)
   std::vector<int> iv;                  // [n][2] interval labels: enter, exit of a depth-first numbering
@@ -95,13 +93,13 @@ struct clover_ctx : RowBufs {
   bool attn_fast;
   // device regions
   int *d_seq_len, *d_aug_len, *d_err;
-  int *d_depth, *d_parent, *d_rank, *d_first_child, *d_n_child, *d_lvl_nodes, *d_par_row;
+  int *d_depth, *d_parent, *d_rank, *d_first_child, *d_n_child, *d_lvl_nodes;
   unsigned long long* d_anc;
   int* d_pages;            // page table [max_batch][max_seq / KV_PAGE] (used once clover_set_page_table was called)
   int* d_iv;               // interval labels of the static tree [R][2]
   bool interval;           // CLOVER_FLAG_INTERVAL_MASK: tree attention reads the labels instead of the bit sets
   char *kc, *vc, *aug_kc, *aug_vc;
-  float *d_cat, *d_g, *d_s, *d_state, *d_rootx, *z;
+  float *d_cat, *d_g, *d_state, *d_rootx, *z;
   void* cand;
   int* topk_ids;
   char* packed;            // fragment-major copies of every linear weight (MFMA path)
@@ -166,7 +164,6 @@ int build_tree(const clover_config& cfg, const clover_tree* t, TreeHost& out, st
   h.depth.assign(n, 0);
   h.first_child.assign(n, 0);
   h.n_child.assign(n, 0);
-  h.par_row.assign(n, 0);
   for (int u = 1; u < n; ++u) {
     const int p = h.parent[u];
     if (p < 0 || p >= u) return bad("parent index must satisfy 0 <= parent[u] < u");
@@ -187,31 +184,20 @@ int build_tree(const clover_config& cfg, const clover_tree* t, TreeHost& out, st
   h.is_chain = true;
   for (int u = 1; u < n; ++u) h.is_chain = h.is_chain && (h.parent[u] == u - 1);
   h.lvl_off.assign(h.max_depth + 2, 0);
-  h.node_off.assign(h.max_depth + 2, 0);
   h.kmax.assign(h.max_depth + 1, 0);
-  std::vector<int> row_in_level(n, -1);
   for (int j = 0; j <= h.max_depth; ++j) {
     h.lvl_off[j] = (int)h.lvl_nodes.size();
     for (int u = 0; u < n; ++u) {
       if (h.depth[u] != j) continue;
       if (h.n_child[u] > 0) {
-        row_in_level[u] = (int)h.lvl_nodes.size() - h.lvl_off[j];
         h.lvl_nodes.push_back(u);
         for (int c = h.first_child[u]; c < h.first_child[u] + h.n_child[u]; ++c) h.kmax[j] = std::max(h.kmax[j], h.rank[c] + 1);
       }
     }
   }
   h.lvl_off[h.max_depth + 1] = (int)h.lvl_nodes.size();
-  {
-    int u = 0;
-    for (int j = 0; j <= h.max_depth; ++j) {
-      h.node_off[j] = u;
-      while (u < n && h.depth[u] == j) ++u;
-    }
-    h.node_off[h.max_depth + 1] = n;
-    if (u != n) return bad("depth must be non-decreasing");
-  }
-  for (int u = 1; u < n; ++u) h.par_row[u] = row_in_level[h.parent[u]];
+  for (int u = 1; u < n; ++u)
+    if (h.depth[u] < h.depth[u - 1]) return bad("depth must be non-decreasing");
   h.anc.assign((size_t)2 * n, 0ull);
   for (int u = 0; u < n && n <= CLOVER_MAX_NODES; ++u) {
     if (u > 0) { h.anc[2 * u] = h.anc[2 * h.parent[u]]; h.anc[2 * u + 1] = h.anc[2 * h.parent[u] + 1]; }
@@ -361,7 +347,6 @@ void carve(clover_ctx* x, char* base, size_t* total) {
   x->d_first_child = cv.take<int>(R);
   x->d_n_child = cv.take<int>(R);
   x->d_lvl_nodes = cv.take<int>(R);
-  x->d_par_row = cv.take<int>(R);
   x->d_anc = cv.take<unsigned long long>(2 * R);
   x->d_iv = cv.take<int>(2 * R);
   x->kc = cv.take<char>(x->k_layer_elems * x->kv_esz * c.n_layers);
@@ -425,7 +410,7 @@ void carve(clover_ctx* x, char* base, size_t* total) {
   b.d_e = cv.take<float>((size_t)rows * H);
   x->d_cat = cv.take<float>(rows16 * 2 * H);
   x->d_g = cv.take<float>((size_t)rows * H);
-  x->d_s = cv.take<float>((size_t)rows * H);
+  cv.take<float>((size_t)rows * H);   // (a step has no use for it; it lengthens the passes of a prompt)
   x->d_state = cv.take<float>((size_t)rows * H);
   x->d_rootx = cv.take<float>((size_t)B * H);
   x->z = cv.take<float>((size_t)rows * c.vocab);
@@ -607,6 +592,18 @@ FragPlanes norm_planes(clover_ctx* x, const float* src, const void* gain, int ro
   return A;
 }
 
+// rotary tables of a pass behind base_len cached positions
+RopeRows rope_rows(const clover_ctx* x, const int* base_len, const int* depth = nullptr, int depth_stride = 0) {
+  return RopeRows{base_len, depth, depth_stride, x->cfg.rope_base, x->cfg.head_dim, x->cos_t, x->sin_t};
+}
+// start of a pass over the target's layers: embeddings in `res`, rotary tables, on the MFMA path planes for the first layer
+void start_pass(clover_ctx* x, const int* tok, float* res, const RowMap& rm, int M, const RopeRows& rope) {
+  const clover_config& c = x->cfg;
+  Scope s(x, KC_EMBED);
+  launch_pass_start(PassStart{x->w.embed, tok, c.vocab, res, x->H, x->H, rm, rope, x->fast ? x->layers[0].attn_norm : nullptr,
+                              c.rms_eps, frag_planes(x->a_norm, M)}, c.dtype, x->st);
+}
+
 // Can draft_tree take the fused route?  (The gate kernel deals whole heads to its lanes.)
 bool draft_fused_ok(clover_ctx* x) { return x->fast && ad_gate_fused_supported(x->H, x->cfg.ad_heads); }
 
@@ -626,7 +623,8 @@ void run_ad_fused(clover_ctx* x, const clover_ad_weights& ad, FragPlanes A, Frag
 }
 
 // Attention Decoder on `rows` contiguous rows: out = x + gate(q(norm(x)), k(y)) * v(y)
-void run_ad(clover_ctx* x, const clover_ad_weights& ad, const float* xin, const float* y, int rows, float* out) {
+void run_ad(clover_ctx* x, const clover_ad_weights& ad, const float* xin, const float* y, int rows, float* out,
+            AdNodes to = AdNodes{} /* of the routes without draft_fused_ok */) {
   const clover_config& c = x->cfg;
   const int H = x->H;
   if (x->fast) {
@@ -658,7 +656,7 @@ void run_ad(clover_ctx* x, const clover_ad_weights& ad, const float* xin, const 
     }
   }
   { Scope s(x, KC_AD_GATE);
-    launch_ad_gate(xin, H, x->ad_q, x->ad_k, x->ad_v, H, c.ad_heads, out, H, nullptr, 0, rows, x->st); }
+    launch_ad_gate(xin, H, x->ad_q, x->ad_k, x->ad_v, H, c.ad_heads, out, rows, x->st, to); }
 }
 
 // Y = X W^T + bias for a draft-side FC with fp32 input X [rows, K]
@@ -697,8 +695,8 @@ void lm_head_generic(clover_ctx* x, const float* src, const void* gain, int rows
   gemm_generic(x, KC_GEMM_LMHEAD, x->a_norm, H, x->w.lm_head, nullptr, out, c.vocab, rows, c.vocab, H, 0);
 }
 
-// logits of `rows` contiguous rows of g through the head norm and the shared LM head, then top-k
-void run_head(clover_ctx* x, const float* g, int rows, int k /* 0: logits only, left in x->z */) {
+// logits of `rows` contiguous rows of g through the head norm and the shared LM head, into x->z
+void run_head(clover_ctx* x, const float* g, int rows) {
   const clover_config& c = x->cfg;
   const int H = x->H;
   if (x->fast) {
@@ -707,7 +705,6 @@ void run_head(clover_ctx* x, const float* g, int rows, int k /* 0: logits only, 
   } else {
     lm_head_generic(x, g, x->w.head_norm, rows, x->z);
   }
-  if (k > 0) { Scope s(x, KC_TOPK); launch_topk(x->z, c.vocab, c.vocab, rows, k, x->cand, x->topk_ids, x->st); }
 }
 
 // test hook: copy the logits of the depth-j internal nodes (rows x vocab in x->z) behind those of the shallower depths
@@ -765,12 +762,10 @@ void draft_expand_dynamic(clover_ctx* x, int B, const int* m, int* tree_tokens, 
         { Scope s(x, KC_DRAFT_MISC);
           launch_draft_gather(x->dyn_state, t.cand_tok, nodes, t.cand_par, n_lvl, B, C, H, x->w.lm_head, c.dtype, c.vocab,
                               x->d_xs, x->d_e, x->d_cat, x->st, ns, C); }
-        run_ad(x, x->w.ad2, x->d_xs, x->d_e, rows, x->d_s);
-        { Scope s(x, KC_DRAFT_MISC);
-          launch_draft_scatter_state(x->d_s, nodes, n_lvl, B, C, H, x->dyn_state, x->d_cat, x->st, ns); }
+        run_ad(x, x->w.ad2, x->d_xs, x->d_e, rows, x->dyn_state, AdNodes{nodes, n_lvl, C, ns, x->d_cat});
         run_fc(x, x->d_cat, 2 * H, x->fc_w[j], x->fc_b[j], x->d_g, rows);
       }
-      run_head(x, x->d_g, rows, 0);
+      run_head(x, x->d_g, rows);
     }
     capture_draft_logits(x, j, rows);
     { Scope s(x, KC_TOPK);
@@ -795,7 +790,6 @@ int upload_tree(clover_ctx* x) {
   up(x->d_first_child, t.first_child.data(), n * sizeof(int));
   up(x->d_n_child, t.n_child.data(), n * sizeof(int));
   up(x->d_lvl_nodes, t.lvl_nodes.data(), t.lvl_nodes.size() * sizeof(int));
-  up(x->d_par_row, t.par_row.data(), n * sizeof(int));
   up(x->d_anc, t.anc.data(), 2 * n * sizeof(unsigned long long));
   up(x->d_iv, t.iv.data(), 2 * n * sizeof(int));
   if (e == hipSuccess) e = hipStreamSynchronize(x->st);  // the host vectors may change after return
@@ -831,20 +825,19 @@ int accept_common(clover_ctx* x, int batch, const int* tree_tokens, const float*
       launch_topk_lse(logits, c.vocab, c.vocab, M, 1, x->cand, x->topk_aux, x->topk_ids, x->topk_vals, x->topk_lse, x->st, inv_t); }
     { Scope s(x, KC_ACCEPT);
       launch_accept_sample(logits, c.vocab, x->topk_lse, inv_t, tree_tokens, fc_tab, nc_tab, x->dyn_on ? R : 0, batch, R,
-                           uniforms, m, acc_idx, new_tokens, next_tok,
+                           uniforms, m, acc_idx, new_tokens, next_tok, x->d_seq_len,
                            (double*)x->topk_aux /* read by the launch above, free now */, x->st); }
   } else {
   { Scope s(x, KC_TOPK); launch_topk(logits, c.vocab, c.vocab, M, 1, x->cand, x->topk_ids, x->st); }
   { Scope s(x, KC_ACCEPT);
     launch_accept_walk(x->topk_ids, tree_tokens, x->dyn_on ? x->dyn.t_first_child : x->d_first_child,
                        x->dyn_on ? x->dyn.t_n_child : x->d_n_child, n_nodes, batch, R, n_forced, forced_next,
-                       m, acc_idx, new_tokens, next_tok, x->st, x->dyn_on ? R : 0); }
+                       m, acc_idx, new_tokens, next_tok, x->d_seq_len, x->st, x->dyn_on ? R : 0); }
   }
   { Scope s(x, KC_COMPACT);
-    launch_compact_kv(x->kc, x->vc, x->kvdtype, x->kv, c.n_layers, x->kv_layer_stride, x->kv_layer_stride, x->d_seq_len, m,
-                      acc_idx, batch, R, x->st);
-    launch_gather_hidden(hidden, acc_idx, m, batch, R, x->H, hid_acc, x->st);
-    launch_add_len(x->d_seq_len, m, batch, x->st); }
+    const int most = n_forced ? n_nodes : std::min((x->dyn_on ? x->dyn.D : t.max_depth) + 1, R);
+    launch_accept_move(x->kc, x->vc, x->kvdtype, x->kv, c.n_layers, x->kv_layer_stride, x->d_seq_len, m, acc_idx, batch, R, most,
+                       hidden, x->H, hid_acc, x->st); }
   return finish(x, "accept");
 }
 
@@ -1081,22 +1074,22 @@ int draft_tree(clover_ctx* x, int32_t batch, const float* hid_acc, const int32_t
   const RowMap in{B, R, n, m}, rm{B, fused ? n : R, n, m};
   const int M = (B - 1) * rm.R + n;
   const AttnPlan plan = plan_attention(x, x->aug_ub.data(), rm, M, true);
+  const RopeRows rope = rope_rows(x, x->d_aug_len);
   if (fused) {
     const FragPlanes A = frag_planes(x->a_norm, M), Y = frag_planes(x->pl_y, M);
     // embeddings of the follow-up tokens come from the LM-head rows; AD1 over (hidden state, embedding)
     { Scope s(x, KC_DRAFT_MISC);
-      launch_draft_pre(hid_acc, next_tok, x->w.ad1.norm, c.rms_eps, x->w.lm_head, c.vocab, H, in, A, Y, x->st); }
+      launch_draft_pre(hid_acc, next_tok, x->w.ad1.norm, c.rms_eps, x->w.lm_head, c.vocab, H, in,
+                       rope, A, Y, x->st); }
     AdGateArgs g;
     memset(&g, 0, sizeof(g));
     g.x = hid_acc; g.ldx = H; g.out = x->xd; g.ldo = H; g.n_lvl = n; g.R = R;
     g.gain = x->aug[0].attn_norm; g.norm = A;   // planes for the Augmenting Block's first layer
     run_ad_fused(x, x->w.ad1, A, Y, M, g);
-    { Scope s(x, KC_ROPE_KV); launch_rope_table(x->d_aug_len, nullptr, c.rope_base, c.head_dim, x->cos_t, x->sin_t, rm, x->st); }
   } else {
   // embeddings of the follow-up tokens come from the LM-head rows
-  { Scope s(x, KC_EMBED); launch_embed(x->w.lm_head, c.dtype, next_tok, c.vocab, x->d_e, H, H, rm, x->st); }
+  { Scope s(x, KC_EMBED); launch_pass_start(PassStart{x->w.lm_head, next_tok, c.vocab, x->d_e, H, H, rm, rope, nullptr, 0.f, {}}, c.dtype, x->st); }
   run_ad(x, x->w.ad1, hid_acc, x->d_e, M, x->xd);
-  { Scope s(x, KC_ROPE_KV); launch_rope_table(x->d_aug_len, nullptr, c.rope_base, c.head_dim, x->cos_t, x->sin_t, rm, x->st); }
   if (x->fast) norm_planes(x, x->xd, x->aug[0].attn_norm, M);
   }
   for (int l = 0; l < c.aug_layers; ++l)
@@ -1112,8 +1105,7 @@ int draft_tree(clover_ctx* x, int32_t batch, const float* hid_acc, const int32_t
     if (fused) {
       launch_draft_root_fused(x->xd, next_tok, m, B, R, n, H, root_state, root_tok, frag_planes(x->pl_y, B), x->d_aug_len, x->st, Rs);
     } else {
-      launch_draft_root(x->xd, next_tok, m, B, R, H, x->d_rootx, root_state, root_tok, x->st, Rs);
-      launch_add_len(x->d_aug_len, m, B, x->st);
+      launch_draft_root(x->xd, next_tok, m, B, R, H, x->d_rootx, root_state, root_tok, x->d_aug_len, x->st, Rs);
     }
   }
   for (int b = 0; b < B; ++b) x->aug_ub[b] += n;
@@ -1127,6 +1119,11 @@ int draft_tree(clover_ctx* x, int32_t batch, const float* hid_acc, const int32_t
       const int n_lvl = t.lvl_off[j + 1] - t.lvl_off[j];
       if (n_lvl == 0) break;
       const int rows = B * n_lvl;
+      auto rank = [&] {   // top-k of every row and with it the tokens of the nodes' children
+        Scope s(x, KC_TOPK);
+        launch_topk(x->z, c.vocab, c.vocab, rows, t.kmax[j], x->cand, x->topk_ids, x->st,
+                    TopkChildren{x->d_lvl_nodes + t.lvl_off[j], x->d_first_child, x->d_n_child, x->d_rank, m, n_lvl, R, tree_tokens});
+      };
       if (fused) {
         // depth j: (AD2 over the parent's state and the node's token embedding, then) FC_j; the FC's partial tiles
         // and bias go straight into the head norm
@@ -1152,11 +1149,7 @@ int draft_tree(clover_ctx* x, int32_t batch, const float* hid_acc, const int32_t
                                  rows, H, x->st, j == 0 ? x->w.fc0_b : x->fc_b[j]); }
         lm_head_fast(x, A, rows, x->z);
         capture_draft_logits(x, j, rows);
-        { Scope s(x, KC_TOPK);
-          launch_topk(x->z, c.vocab, c.vocab, rows, t.kmax[j], x->cand, x->topk_ids, x->st); }
-        { Scope s(x, KC_DRAFT_MISC);
-          launch_draft_assign(x->topk_ids, x->d_par_row, x->d_rank, t.node_off[j + 1], t.node_off[j + 2], n_lvl, B, R, m,
-                              tree_tokens, x->st); }
+        rank();
         continue;
       }
       if (j == 0) {
@@ -1166,16 +1159,12 @@ int draft_tree(clover_ctx* x, int32_t batch, const float* hid_acc, const int32_t
         { Scope s(x, KC_DRAFT_MISC);
           launch_draft_gather(x->d_state, tree_tokens, nodes, x->d_parent, n_lvl, B, R, H, x->w.lm_head, c.dtype,
                               c.vocab, x->d_xs, x->d_e, x->d_cat, x->st); }
-        run_ad(x, x->w.ad2, x->d_xs, x->d_e, rows, x->d_s);
-        { Scope s(x, KC_DRAFT_MISC);
-          launch_draft_scatter_state(x->d_s, nodes, n_lvl, B, R, H, x->d_state, x->d_cat, x->st); }
+        run_ad(x, x->w.ad2, x->d_xs, x->d_e, rows, x->d_state, AdNodes{nodes, n_lvl, R, 0, x->d_cat});
         run_fc(x, x->d_cat, 2 * H, x->fc_w[j], x->fc_b[j], x->d_g, rows);
       }
-      run_head(x, x->d_g, rows, t.kmax[j]);
+      run_head(x, x->d_g, rows);
       capture_draft_logits(x, j, rows);
-      { Scope s(x, KC_DRAFT_MISC);
-        launch_draft_assign(x->topk_ids, x->d_par_row, x->d_rank, t.node_off[j + 1], t.node_off[j + 2], n_lvl, B, R, m,
-                            tree_tokens, x->st); }
+      rank();
     }
   }
   return finish(x, "draft_tree");
@@ -1199,10 +1188,7 @@ int verify_tree(clover_ctx* x, int32_t batch, const int32_t* tree_tokens, float*
   const RowMap rm{B, R, n_nodes, nullptr};
   const int M = (B - 1) * R + n_nodes;
   const AttnPlan plan = plan_attention(x, x->len_ub.data(), rm, M, false);
-  { Scope s(x, KC_EMBED); launch_embed(x->w.embed, c.dtype, tree_tokens, c.vocab, hidden, H, H, rm, x->st); }
-  { Scope s(x, KC_ROPE_KV);
-    launch_rope_table(x->d_seq_len, depth_tab, c.rope_base, c.head_dim, x->cos_t, x->sin_t, rm, x->st, topo_stride); }
-  if (x->fast) norm_planes(x, hidden, x->layers[0].attn_norm, M);
+  start_pass(x, tree_tokens, hidden, rm, M, rope_rows(x, x->d_seq_len, depth_tab, topo_stride));
   for (int l = 0; l < c.n_layers; ++l)
     run_layer(x, x->layers[l], hidden, rm, M, x->kc + (size_t)l * x->k_layer_elems * x->kv_esz,
               x->vc + (size_t)l * x->v_layer_elems * x->kv_esz, x->d_seq_len, anc_tab,
@@ -1280,9 +1266,7 @@ int clover_prefill(clover_ctx* x, int32_t b, const int32_t* tokens, int32_t n, f
     const bool last = c0 + M == n;
     const RowMap rm{1, P, M, nullptr};
     // ---- target: embedding, layers with causal attention (no mask table: a chain), K/V in place ----
-    { Scope s(x, KC_EMBED); launch_embed(x->w.embed, c.dtype, tokens + c0, c.vocab, xres, H, H, rm, x->st); }
-    { Scope s(x, KC_ROPE_KV); launch_rope_table(len_b, nullptr, c.rope_base, c.head_dim, x->cos_t, x->sin_t, rm, x->st); }
-    if (x->fast) norm_planes(x, xres, x->layers[0].attn_norm, M);
+    start_pass(x, tokens + c0, xres, rm, M, rope_rows(x, len_b));
     const AttnPlan plan = plan_attention(x, &x->len_ub[b], rm, M, true);
     for (int l = 0; l < c.n_layers; ++l)
       run_layer(x, x->layers[l], xres, rm, M, x->kc + (size_t)l * x->k_layer_elems * x->kv_esz,
@@ -1308,9 +1292,10 @@ int clover_prefill(clover_ctx* x, int32_t b, const int32_t* tokens, int32_t n, f
     const int Md = last ? M - 1 : M;
     if (Md > 0) {
       const RowMap rd{1, P, Md, nullptr};
-      { Scope s(x, KC_EMBED); launch_embed(x->w.lm_head, c.dtype, tokens + c0 + 1, c.vocab, x->d_e, H, H, rd, x->st); }
+      { Scope s(x, KC_EMBED);
+        launch_pass_start(PassStart{x->w.lm_head, tokens + c0 + 1, c.vocab, x->d_e, H, H, rd, rope_rows(x, aug_len_b), nullptr, 0.f, {}},
+                          c.dtype, x->st); }
       run_ad(x, x->w.ad1, xres, x->d_e, Md, x->xd);
-      { Scope s(x, KC_ROPE_KV); launch_rope_table(aug_len_b, nullptr, c.rope_base, c.head_dim, x->cos_t, x->sin_t, rd, x->st); }
       if (x->fast) norm_planes(x, x->xd, x->aug[0].attn_norm, Md);
       const AttnPlan plan_d = plan_attention(x, &x->aug_ub[b], rd, Md, true);
       for (int l = 0; l < c.aug_layers; ++l)

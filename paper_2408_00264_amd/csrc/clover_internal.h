@@ -141,13 +141,37 @@ inline void allow_dynamic_lds(OncePerDevice& once, const void* kernel, int bytes
 #endif
 
 // ---- generic (fp32 ALU) kernels; wdtype: 0 fp32, 1 bf16 ---------------------------------------
-void launch_embed(const void* table, int wdtype, const int* tok, int vocab, float* out, int ldo, int H,
-                  RowMap rm, hipStream_t st);
+// rotary tables: row (b, i) of the pass sits at position base_len[b] + (depth ? depth[i] : i)
+struct RopeRows {
+  const int *base_len, *depth;   // dev [B]; dev [n] or null
+  int depth_stride;              // nodes per sequence in a per-sequence depth table, 0: one table for all
+  float base; int d;
+  float *cos_t, *sin_t;          // [rows][d / 2]
+};
+#ifdef __HIPCC__
+__device__ __forceinline__ void rope_row(const RopeRows& r, int b, int i, size_t row) {
+  const int half = r.d / 2;
+  if ((int)threadIdx.x >= half) return;
+  const int pos = r.base_len[b] + (r.depth ? r.depth[(size_t)b * r.depth_stride + i] : i);
+  for (int c = threadIdx.x; c < half; c += blockDim.x) {
+    const double inv = pow((double)r.base, -2.0 * (double)c / (double)r.d);
+    const double ang = (double)pos * inv;
+    r.cos_t[row * half + c] = (float)cos(ang);
+    r.sin_t[row * half + c] = (float)sin(ang);
+  }
+}
+#endif
+// start of a pass: out[row] = table[tok[row]], the rotary tables, and where gain is given (bf16 models) planes of RMSNorm(out) * gain
+struct PassStart {
+  const void* table; const int* tok; int vocab;
+  float* out; int ldo, H;
+  RowMap rm;
+  RopeRows rope;
+  const void* gain; float eps; FragPlanes planes;
+};
+void launch_pass_start(const PassStart& p, int wdtype, hipStream_t st);
 void launch_rmsnorm(const float* x, int ldx, const void* gain, int wdtype, float eps, float* out, int ldo, int H,
                     int rows, hipStream_t st);
-// depth_stride: 0 when all sequences share one tree, else the per-sequence stride of the depth table
-void launch_rope_table(const int* base_len, const int* depth /*null: row index*/, float rope_base, int d,
-                       float* cos_t, float* sin_t, RowMap rm, hipStream_t st, int depth_stride = 0);
 void launch_rope_kv_write(const float* qkv, int ldqkv, int qkv_splits, size_t qkv_split_stride, const float* cos_t, const float* sin_t, float* q_out, int ldq,
                           void* k_cache, void* v_cache, int kvdtype, KVLayout kv, const int* base_len, int n_q,
                           RowMap rm, int* err_flag, bf16_t* q_hi /*null: fp32 q_out*/, bf16_t* q_lo, float q_scale,
@@ -171,13 +195,19 @@ struct SmallGemm {
 bool gemm_small_joins(const SmallGemm* g, int n, bool swiglu, int wdtype, int M, int K);
 void launch_gemm_small(const SmallGemm* g, int n, bool swiglu, int wdtype, int M, int K, int mode, float eps, hipStream_t st);
 void launch_swiglu(const float* g, const float* u, float* h, size_t n, hipStream_t st);
+// nodes non-null: row b * n_lvl + r of the result goes to row b * R + nodes[b * stride + r] of out, and to cat[row][0 .. H-1]
+struct AdNodes { const int* nodes; int n_lvl, R, stride; float* cat /*[rows, 2H]*/; };
 void launch_ad_gate(const float* x, int ldx, const float* q, const float* k, const float* v, int H, int heads,
-                    float* out, int ldo, float* out2, int ldo2, int rows, hipStream_t st);
+                    float* out, int rows, hipStream_t st, AdNodes to = AdNodes{});
 
 // top-k of each row of z[rows, V] by (value desc, id asc); k <= CLOVER_MAX_RANK.
 // cand: scratch [rows][chunks][16] of (float,int) pairs; out_ids [rows][16]; chunks = topk_chunks(V).
 int topk_chunks(int V);
-void launch_topk(const float* z, int ldz, int V, int rows, int k, void* cand, int* out_ids, hipStream_t st);
+// tokens non-null: row b * n_lvl + r ranks node u = nodes[r] of sequence b, and tokens[b * R + c] = the row's id of rank[c] for each
+// child c of u (rank[c] < k); sequences with m[b] < 1 are left alone
+struct TopkChildren { const int *nodes, *first_child, *n_child, *rank, *m; int n_lvl, R; int* tokens; };
+void launch_topk(const float* z, int ldz, int V, int rows, int k, void* cand, int* out_ids, hipStream_t st,
+                 TopkChildren to = TopkChildren{});
 
 // ---- draft-tree bookkeeping -------------------------------------------------------------------
 // gather for level rows: row (b,r) <- node u = lvl_nodes[r]; xs = state[b][parent(u)], e = lm_head[token[b][u]]
@@ -186,28 +216,21 @@ void launch_draft_gather(const float* state, const int* tokens, const int* lvl_n
                          int B, int R, int H, const void* lm_head, int wdtype, int vocab, float* xs, float* e,
                          float* cat /*[rows,2H], second half <- e*/, hipStream_t st, int nodes_stride = 0,
                          int parent_stride = 0);
-// state[b][u] <- s rows (also first half of cat)
-void launch_draft_scatter_state(const float* s, const int* lvl_nodes, int n_lvl, int B, int R, int H, float* state,
-                                float* cat, hipStream_t st, int nodes_stride = 0);
-// root rows: xs_root[b] = a[b][m[b]-1]; state[b][0] = same; tokens[b][0] = next_tok[b][m[b]-1]
+// root rows: xs_root[b] = a[b][m[b]-1]; state[b][0] = same; tokens[b][0] = next_tok[b][m[b]-1]; aug_len[b] += m[b]
 // (Rs: row stride of state and tokens when it differs from R, the stride of a and next_tok)
 void launch_draft_root(const float* a, const int* next_tok, const int* m, int B, int R, int H, float* root_x,
-                       float* state, int* tokens, hipStream_t st, int Rs = 0);
-// tokens[b][c] = ids[(b*n_par + par_row[c])*16 + rank[c]] for children c in [c0,c1); skipped when m[b] < 1
-void launch_draft_assign(const int* ids, const int* par_row, const int* rank, int c0, int c1, int n_par, int B, int R,
-                         const int* m, int* tokens, hipStream_t st);
-void launch_add_len(int* len, const int* m, int B, hipStream_t st);
+                       float* state, int* tokens, int* aug_len, hipStream_t st, int Rs = 0);
 void launch_add_scalar(int* p, int v, hipStream_t st);   // *p += v
 
 // ---- accept / compact -------------------------------------------------------------------------
 void launch_accept_walk(const int* argmax, const int* tokens, const int* first_child, const int* n_child, int n_nodes,
                         int B, int R, const int* n_forced, const int* forced_next, int* m, int* acc_idx,
-                        int* new_tokens, int* next_tok, hipStream_t st, int child_stride = 0);
-void launch_compact_kv(void* k_cache, void* v_cache, int kvdtype, KVLayout kv, int n_layers, size_t k_layer_elems,
-                       size_t v_layer_elems, const int* len, const int* m, const int* acc_idx, int B, int R,
-                       hipStream_t st);
-void launch_gather_hidden(const float* hidden, const int* acc_idx, const int* m, int B, int R, int H, float* hid_acc,
-                          hipStream_t st);
+                        int* new_tokens, int* next_tok, int* seq_len /* += m */, hipStream_t st, int child_stride = 0);
+// behind the walk (len includes m): K/V rows of the accepted nodes to their slots in every layer, hid_acc[b][i] = hidden[b][acc_idx[i]];
+// m[b] <= max_rows
+void launch_accept_move(void* k_cache, void* v_cache, int kvdtype, KVLayout kv, int n_layers, size_t layer_elems, const int* len,
+                        const int* m, const int* acc_idx, int B, int R, int max_rows, const float* hidden, int H, float* hid_acc,
+                        hipStream_t st);
 void launch_read_kv(const void* k_cache, const void* v_cache, int kvdtype, KVLayout kv, int b, int slot0, int n_slots,
                     float* k_out, float* v_out, hipStream_t st);
 void launch_write_kv(void* k_cache, void* v_cache, int kvdtype, KVLayout kv, int b, int slot0, int n_slots,
@@ -288,9 +311,9 @@ TileForm tile_gemm_form(int M, int N, int K, int epi, int k_parts);
 
 // ---- fused bookkeeping kernels of the draft head (MFMA path, bf16 weights) ----------------------
 // planes of RMSNorm(hid[row]) * gain -> a and of the embedding of tok[row] -> y, rows of `rm` in,
-// row b * rm.n + i out
+// row b * rm.n + i out, and its rotary table (for every i < rm.n)
 void launch_draft_pre(const float* hid, const int* tok, const void* gain, float eps, const void* table, int vocab, int H,
-                      RowMap rm, FragPlanes a, FragPlanes y, hipStream_t st);
+                      RowMap rm, const RopeRows& rope, FragPlanes a, FragPlanes y, hipStream_t st);
 // Attention-Decoder gate reading the q and (k|v) GEMMs' partial tiles and adding the biases itself
 struct AdGateArgs {
   const float* x; int ldx;                    // residual input rows
@@ -339,7 +362,7 @@ void launch_topk_lse(const float* z, int ldz, int V, int rows, int k, void* cand
 int sample_chunks(int V);
 void launch_accept_sample(const float* logits, int V, const float* lse, float inv_temp, const int* tokens,
                           const int* first_child, const int* n_child, int child_stride, int B, int R,
-                          const float* uniforms, int* m, int* acc_idx, int* new_tokens, int* next_tok,
+                          const float* uniforms, int* m, int* acc_idx, int* new_tokens, int* next_tok, int* seq_len /* += m */,
                           double* mass /* scratch, B * sample_chunks(V) */, hipStream_t st);
 void launch_dyn_assign(const DynTree& t, int j, int B, const int* ids, const float* vals, const float* lse, const int* m,
                        hipStream_t st);

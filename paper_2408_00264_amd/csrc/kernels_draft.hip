@@ -6,7 +6,7 @@
 // element-wise steps between two GEMMs are folded into ONE kernel each, and those kernels read the
 // GEMMs' partial sums over K ranges (and add the bias) themselves instead of waiting for a reduce pass:
 //
-//   draft_pre      rows of (hidden state, follow-up token)  -> planes of RMSNorm(x)*gain, planes of the embedding
+//   draft_pre      rows of (hidden state, follow-up token)  -> planes of RMSNorm(x)*gain, planes of the embedding, rotary table
 //   ad_gate_fused  q/k/v partials + biases -> per-head cosine gate, residual; writes the result where the next
 //                  step wants it (fp32 row, normalised planes for the Augmenting Block, or the
 //                  regressive state of a tree node plus the first half of the FC input planes)
@@ -70,9 +70,10 @@ __device__ __forceinline__ void embed_row_planes(const bf16_t* __restrict__ tabl
 __global__ __launch_bounds__(256) void draft_pre_kernel(const float* __restrict__ hid, const int* __restrict__ tok,
                                                         const bf16_t* __restrict__ gain, float eps,
                                                         const bf16_t* __restrict__ table, int vocab, int H, RowMap rm,
-                                                        FragPlanes a, FragPlanes y) {
+                                                        RopeRows rope, FragPlanes a, FragPlanes y) {
   __shared__ float red[4];
   const int i = blockIdx.x, b = blockIdx.y;
+  rope_row(rope, b, i, (size_t)b * rm.n + i);
   const int nv = rm.n_valid ? min(rm.n_valid[b], rm.n) : rm.n;
   if (i >= nv) return;
   const size_t row = (size_t)b * rm.R + i;
@@ -217,9 +218,9 @@ __global__ __launch_bounds__(256) void draft_level_kernel(const float* __restric
 }  // namespace
 
 void launch_draft_pre(const float* hid, const int* tok, const void* gain, float eps, const void* table, int vocab, int H,
-                      RowMap rm, FragPlanes a, FragPlanes y, hipStream_t st) {
+                      RowMap rm, const RopeRows& rope, FragPlanes a, FragPlanes y, hipStream_t st) {
   draft_pre_kernel<<<dim3(rm.n, rm.B), 256, 0, st>>>(hid, tok, (const bf16_t*)gain, eps, (const bf16_t*)table, vocab, H,
-                                                     rm, a, y);
+                                                     rm, rope, a, y);
 }
 
 // a head must span a power-of-two number (<= 64) of four-column lanes

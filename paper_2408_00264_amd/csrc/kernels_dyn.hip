@@ -295,7 +295,7 @@ __global__ __launch_bounds__(64) void sample_walk_kernel(
     const float* __restrict__ logits, int V, const float* __restrict__ lse, float inv_temp, const int* __restrict__ tokens,
     const int* __restrict__ first_child, const int* __restrict__ n_child, int child_stride, int R,
     const float* __restrict__ uniforms, int* __restrict__ m, int* __restrict__ acc_idx, int* __restrict__ new_tokens,
-    int* __restrict__ next_tok) {
+    int* __restrict__ next_tok, int* __restrict__ seq_len) {
   const int b = blockIdx.x, lane = threadIdx.x;
   const size_t o = (size_t)b * R;
   first_child += (size_t)b * child_stride;
@@ -329,7 +329,10 @@ __global__ __launch_bounds__(64) void sample_walk_kernel(
     }
     ++len;
   }
-  if (lane == 0) m[b] = len;
+  if (lane == 0) {
+    m[b] = len;
+    seq_len[b] += len;   // (launch_accept_move subtracts it again)
+  }
 }
 
 // what is left of p at the last accepted node of a sequence: p without the node's children
@@ -463,11 +466,11 @@ __global__ __launch_bounds__(256) void sample_pick_kernel(
 int sample_chunks(int V) { return (V + SAMPLE_CHUNK - 1) / SAMPLE_CHUNK; }
 void launch_accept_sample(const float* logits, int V, const float* lse, float inv_temp, const int* tokens,
                           const int* first_child, const int* n_child, int child_stride, int B, int R,
-                          const float* uniforms, int* m, int* acc_idx, int* new_tokens, int* next_tok, double* mass,
+                          const float* uniforms, int* m, int* acc_idx, int* new_tokens, int* next_tok, int* seq_len, double* mass,
                           hipStream_t st) {
   const int chunks = sample_chunks(V);
   sample_walk_kernel<<<B, 64, 0, st>>>(logits, V, lse, inv_temp, tokens, first_child, n_child, child_stride, R, uniforms, m, acc_idx,
-                                       new_tokens, next_tok);
+                                       new_tokens, next_tok, seq_len);
   sample_mass_kernel<<<dim3(chunks, B), 256, 0, st>>>(logits, V, lse, inv_temp, tokens, first_child, n_child, child_stride, R, m,
                                                       acc_idx, mass);
   sample_pick_kernel<<<B, 256, 0, st>>>(logits, V, lse, inv_temp, tokens, first_child, n_child, child_stride, R, uniforms, m, acc_idx,

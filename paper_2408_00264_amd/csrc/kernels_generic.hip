@@ -45,16 +45,6 @@ __device__ __forceinline__ float wave_max(float v) {
   for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
   return v;
 }
-__device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    unsigned lo = __shfl_xor((unsigned)(v & 0xFFFFFFFFull), o, 64);
-    unsigned hi = __shfl_xor((unsigned)(v >> 32), o, 64);
-    unsigned long long w = ((unsigned long long)hi << 32) | lo;
-    v = w > v ? w : v;
-  }
-  return v;
-}
 // sum over a 256-thread block; `red` is 4 floats of LDS.  All threads get the result.
 __device__ __forceinline__ float block_sum_256(float v, float* red) {
   v = wave_sum(v);
@@ -64,30 +54,19 @@ __device__ __forceinline__ float block_sum_256(float v, float* red) {
   return red[0] + red[1] + red[2] + red[3];
 }
 
+// Four elements at once from wherever an element may lie: callers owe their tensors no more, and the load instruction takes it.
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef bf16_t bf16x4_any __attribute__((ext_vector_type(4), aligned(2)));
+__device__ __forceinline__ float4 ld4_any(const float* p) {
+  const f32x4_any u = *(const f32x4_any*)p;
+  return make_float4(u[0], u[1], u[2], u[3]);
+}
+__device__ __forceinline__ float4 ld4_any(const bf16_t* p) {
+  const bf16x4_any u = *(const bf16x4_any*)p;
+  return make_float4(bf16_to_f32(u[0]), bf16_to_f32(u[1]), bf16_to_f32(u[2]), bf16_to_f32(u[3]));
+}
+
 __device__ __forceinline__ int rows_valid(const RowMap& rm, int b) { return rm.n_valid ? min(rm.n_valid[b], rm.n) : rm.n; }
-
-// ------------------------------------------------------------------------------------------
-// embedding gather: out[row, 0:H] = table[tok[row], :]
-// ------------------------------------------------------------------------------------------
-template <typename WT>
-__global__ void embed_kernel(const WT* __restrict__ table, const int* __restrict__ tok, int vocab,
-                             float* __restrict__ out, int ldo, int H, RowMap rm) {
-  const int b = blockIdx.y, i = blockIdx.x;
-  if (i >= rows_valid(rm, b)) return;
-  const size_t row = (size_t)b * rm.R + i;
-  int t = tok[row];
-  t = t < 0 ? 0 : (t >= vocab ? vocab - 1 : t);
-  for (int c = threadIdx.x; c < H; c += blockDim.x) out[row * ldo + c] = ldf(table, (size_t)t * H + c);
-}
-
-void launch_embed(const void* table, int wdtype, const int* tok, int vocab, float* out, int ldo, int H, RowMap rm,
-                  hipStream_t st) {
-  dim3 grid(rm.n, rm.B);
-  if (wdtype == 0)
-    embed_kernel<float><<<grid, 256, 0, st>>>((const float*)table, tok, vocab, out, ldo, H, rm);
-  else
-    embed_kernel<bf16_t><<<grid, 256, 0, st>>>((const bf16_t*)table, tok, vocab, out, ldo, H, rm);
-}
 
 // ------------------------------------------------------------------------------------------
 // RMSNorm: out = x * rsqrt(mean(x^2) + eps) * gain      (one block per row)
@@ -112,29 +91,6 @@ void launch_rmsnorm(const float* x, int ldx, const void* gain, int wdtype, float
     rmsnorm_kernel<float><<<rows, 256, 0, st>>>(x, ldx, (const float*)gain, eps, out, ldo, H);
   else
     rmsnorm_kernel<bf16_t><<<rows, 256, 0, st>>>(x, ldx, (const bf16_t*)gain, eps, out, ldo, H);
-}
-
-// ------------------------------------------------------------------------------------------
-// rotary tables: row (b,i) sits at position base_len[b] + (depth ? depth[i] : i)
-// ------------------------------------------------------------------------------------------
-__global__ void rope_table_kernel(const int* __restrict__ base_len, const int* __restrict__ depth, float rope_base,
-                                  int d, float* __restrict__ cos_t, float* __restrict__ sin_t, RowMap rm,
-                                  int depth_stride) {
-  const int b = blockIdx.y, i = blockIdx.x, half = d / 2;
-  const size_t row = (size_t)b * rm.R + i;
-  const int pos = base_len[b] + (depth ? depth[(size_t)b * depth_stride + i] : i);
-  for (int c = threadIdx.x; c < half; c += blockDim.x) {
-    const double inv = pow((double)rope_base, -2.0 * (double)c / (double)d);
-    const double ang = (double)pos * inv;
-    cos_t[row * half + c] = (float)cos(ang);
-    sin_t[row * half + c] = (float)sin(ang);
-  }
-}
-
-void launch_rope_table(const int* base_len, const int* depth, float rope_base, int d, float* cos_t, float* sin_t,
-                       RowMap rm, hipStream_t st, int depth_stride) {
-  dim3 grid(rm.n, rm.B);
-  rope_table_kernel<<<grid, 64, 0, st>>>(base_len, depth, rope_base, d, cos_t, sin_t, rm, depth_stride);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -755,8 +711,13 @@ void launch_swiglu(const float* g, const float* u, float* h, size_t n, hipStream
 // ------------------------------------------------------------------------------------------
 __global__ void ad_gate_kernel(const float* __restrict__ x, int ldx, const float* __restrict__ q,
                                const float* __restrict__ k, const float* __restrict__ v, int H, int heads,
-                               float* __restrict__ out, int ldo, float* __restrict__ out2, int ldo2) {
+                               float* __restrict__ out, AdNodes to) {
   const size_t row = blockIdx.x;
+  size_t orow = row;
+  if (to.nodes) {
+    const int b = (int)row / to.n_lvl, r = (int)row - b * to.n_lvl;
+    orow = (size_t)b * to.R + to.nodes[(size_t)b * to.stride + r];
+  }
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, hd = H / heads;
   for (int h = wave; h < heads; h += 4) {
     const size_t o = row * H + (size_t)h * hd;
@@ -769,15 +730,15 @@ __global__ void ad_gate_kernel(const float* __restrict__ x, int ldx, const float
     const float att = qk / (fmaxf(sqrtf(qq), 1e-8f) * fmaxf(sqrtf(kk), 1e-8f));
     for (int c = lane; c < hd; c += 64) {
       const float r = x[row * ldx + h * hd + c] + att * v[o + c];
-      out[row * ldo + h * hd + c] = r;
-      if (out2) out2[row * ldo2 + h * hd + c] = r;
+      out[orow * H + h * hd + c] = r;
+      if (to.cat) to.cat[row * 2 * H + h * hd + c] = r;
     }
   }
 }
 void launch_ad_gate(const float* x, int ldx, const float* q, const float* k, const float* v, int H, int heads,
-                    float* out, int ldo, float* out2, int ldo2, int rows, hipStream_t st) {
+                    float* out, int rows, hipStream_t st, AdNodes to) {
   if (rows <= 0) return;
-  ad_gate_kernel<<<rows, 256, 0, st>>>(x, ldx, q, k, v, H, heads, out, ldo, out2, ldo2);
+  ad_gate_kernel<<<rows, 256, 0, st>>>(x, ldx, q, k, v, H, heads, out, to);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -791,16 +752,36 @@ __device__ __forceinline__ unsigned long long topk_key(float v, int id) {
   u = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
   return ((unsigned long long)u << 32) | (unsigned long long)(0xFFFFFFFFu - (unsigned)id);
 }
-__device__ __forceinline__ unsigned long long block_max_u64_256(unsigned long long v, unsigned long long* red) {
-  v = wave_max_u64(v);
+// largest of the wavefront's values, along the lanes of a row, then over the rows (a few clocks a step; an exchange through the
+// LDS crossbar takes 50 to 100, and a ranking is a chain of them: the chunks of a top-8 of 8 rows x 128256 8.6 -> 6.8 us)
+__device__ __forceinline__ unsigned wave_max_u32(unsigned v) {
+  v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false));   // row_shr:1, 2, 4, 8
+  v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false));
+  v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false));
+  v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false));
+  v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false));   // row_bcast:15 into rows 1 and 3
+  v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false));   // row_bcast:31 into rows 2 and 3
+  return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
+}
+__device__ __forceinline__ unsigned long long wave_max_key(unsigned long long v) {
+  const unsigned hi = (unsigned)(v >> 32), top = wave_max_u32(hi);
+  return ((unsigned long long)top << 32) | wave_max_u32(hi == top ? (unsigned)v : 0u);
+}
+// the largest key of 256 threads, round r of a ranking: the rounds take turns in `red`, so one barrier each is enough
+__device__ __forceinline__ unsigned long long block_max_key(unsigned long long v, unsigned long long (&red)[2][4], int r) {
+  v = wave_max_key(v);
+  unsigned long long* q = red[r & 1];
+  if ((threadIdx.x & 63) == 0) q[threadIdx.x >> 6] = v;
   __syncthreads();
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  unsigned long long r = red[0];
-  r = red[1] > r ? red[1] : r;
-  r = red[2] > r ? red[2] : r;
-  r = red[3] > r ? red[3] : r;
-  return r;
+  const unsigned long long a = q[0] > q[1] ? q[0] : q[1], b = q[2] > q[3] ? q[2] : q[3];
+  return a > b ? a : b;
+}
+// tokens of the children of the node that row `row` of a depth expands, from the row's ranked ids
+__device__ __forceinline__ void assign_children(const TopkChildren& to, const int* ids, int row) {
+  const int b = row / to.n_lvl, u = to.nodes[row - b * to.n_lvl];
+  if (to.m[b] < 1) return;
+  const int c = to.first_child[u] + (int)threadIdx.x;
+  if ((int)threadIdx.x < to.n_child[u]) to.tokens[(size_t)b * to.R + c] = ids[to.rank[c]];
 }
 
 constexpr int TOPK_CHUNK = 2048;
@@ -808,8 +789,10 @@ constexpr int TOPK_EPT = TOPK_CHUNK / 256;
 int topk_chunks(int V) { return (V + TOPK_CHUNK - 1) / TOPK_CHUNK; }
 
 __global__ __launch_bounds__(256) void topk_stage1_kernel(const float* __restrict__ z, int ldz, int V, int k,
-                                                          unsigned long long* __restrict__ cand, int* __restrict__ out_ids) {
-  __shared__ unsigned long long red[4];
+                                                          unsigned long long* __restrict__ cand, int* __restrict__ out_ids,
+                                                          TopkChildren to) {
+  __shared__ unsigned long long red[2][4];
+  __shared__ int ids[16];
   const int chunk = blockIdx.x, row = blockIdx.y, chunks = gridDim.x;
   unsigned long long key[TOPK_EPT];
 #pragma unroll
@@ -822,15 +805,18 @@ __global__ __launch_bounds__(256) void topk_stage1_kernel(const float* __restric
     unsigned long long best = 0ull;
 #pragma unroll
     for (int e = 0; e < TOPK_EPT; ++e) best = key[e] > best ? key[e] : best;
-    best = block_max_u64_256(best, red);
+    best = block_max_key(best, red, r);
 #pragma unroll
     for (int e = 0; e < TOPK_EPT; ++e)
       if (key[e] == best) key[e] = 0ull;
     if (threadIdx.x == 0) {
-      if (out_ids) out_ids[row * 16 + r] = (int)(0xFFFFFFFFu - (unsigned)(best & 0xFFFFFFFFull));   // the only chunk
+      if (out_ids) out_ids[row * 16 + r] = ids[r] = (int)(0xFFFFFFFFu - (unsigned)(best & 0xFFFFFFFFull));   // the only chunk
       else cand[((size_t)row * chunks + chunk) * 16 + r] = best;
     }
   }
+  if (!out_ids || !to.tokens) return;   // (uniform)
+  __syncthreads();
+  assign_children(to, ids, row);
 }
 
 // stage 1 for k = 1 (the target's argmax over every row): one wavefront per chunk, 16-byte loads, the 64-bit key only for
@@ -858,13 +844,14 @@ __global__ __launch_bounds__(256) void argmax_stage1_kernel(const float* __restr
     }
   }
   unsigned long long key = id >= 0 ? ((unsigned long long)best << 32) | (unsigned long long)(0xFFFFFFFFu - (unsigned)id) : 0ull;
-  key = wave_max_u64(key);
+  key = wave_max_key(key);
   if (lane == 0) cand[((size_t)row * chunks + chunk) * 16] = key;
 }
 
 __global__ __launch_bounds__(256) void topk_stage2_kernel(const unsigned long long* __restrict__ cand, int chunks,
-                                                          int k, int* __restrict__ out_ids) {
-  __shared__ unsigned long long red[4];
+                                                          int k, int* __restrict__ out_ids, TopkChildren to) {
+  __shared__ unsigned long long red[2][4];
+  __shared__ int ids[16];
   const int row = blockIdx.x;
   const int total = chunks * k;  // <= 63*16 for V <= 129024; loop handles more
   unsigned long long key[8];
@@ -877,26 +864,29 @@ __global__ __launch_bounds__(256) void topk_stage2_kernel(const unsigned long lo
     unsigned long long best = 0ull;
 #pragma unroll
     for (int e = 0; e < 8; ++e) best = key[e] > best ? key[e] : best;
-    best = block_max_u64_256(best, red);
+    best = block_max_key(best, red, r);
 #pragma unroll
     for (int e = 0; e < 8; ++e)
       if (key[e] == best) key[e] = 0ull;
-    if (threadIdx.x == 0) out_ids[row * 16 + r] = (int)(0xFFFFFFFFu - (unsigned)(best & 0xFFFFFFFFull));
+    if (threadIdx.x == 0) out_ids[row * 16 + r] = ids[r] = (int)(0xFFFFFFFFu - (unsigned)(best & 0xFFFFFFFFull));
   }
+  if (!to.tokens) return;   // (uniform)
+  __syncthreads();
+  assign_children(to, ids, row);
 }
 
-void launch_topk(const float* z, int ldz, int V, int rows, int k, void* cand, int* out_ids, hipStream_t st) {
+void launch_topk(const float* z, int ldz, int V, int rows, int k, void* cand, int* out_ids, hipStream_t st, TopkChildren to) {
   if (rows <= 0) return;
   const int chunks = topk_chunks(V);  // chunks * k <= 2048 is checked at init (vocab <= 262144)
   if (chunks == 1) {   // (a vocabulary of up to 2048: nothing to merge)
-    topk_stage1_kernel<<<dim3(1, rows), 256, 0, st>>>(z, ldz, V, k, (unsigned long long*)cand, out_ids);
+    topk_stage1_kernel<<<dim3(1, rows), 256, 0, st>>>(z, ldz, V, k, (unsigned long long*)cand, out_ids, to);
     return;
   }
   if (k == 1 && V % 4 == 0 && ldz % 4 == 0 && ((uintptr_t)z & 15) == 0)
     argmax_stage1_kernel<<<dim3((chunks + 3) / 4, rows), 256, 0, st>>>(z, ldz, V, chunks, (unsigned long long*)cand);
   else
-    topk_stage1_kernel<<<dim3(chunks, rows), 256, 0, st>>>(z, ldz, V, k, (unsigned long long*)cand, nullptr);
-  topk_stage2_kernel<<<rows, 256, 0, st>>>((const unsigned long long*)cand, chunks, k, out_ids);
+    topk_stage1_kernel<<<dim3(chunks, rows), 256, 0, st>>>(z, ldz, V, k, (unsigned long long*)cand, nullptr, TopkChildren{});
+  topk_stage2_kernel<<<rows, 256, 0, st>>>((const unsigned long long*)cand, chunks, k, out_ids, to);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -932,27 +922,9 @@ void launch_draft_gather(const float* state, const int* tokens, const int* lvl_n
                                                       (const bf16_t*)lm_head, vocab, xs, e, cat, nodes_stride, parent_stride);
 }
 
-__global__ void draft_scatter_state_kernel(const float* __restrict__ s, const int* __restrict__ lvl_nodes, int n_lvl,
-                                           int R, int H, float* __restrict__ state, float* __restrict__ cat,
-                                           int nodes_stride) {
-  const int r = blockIdx.x, b = blockIdx.y;
-  const int u = lvl_nodes[(size_t)b * nodes_stride + r];
-  const size_t row = (size_t)b * n_lvl + r;
-  for (int c = threadIdx.x; c < H; c += blockDim.x) {
-    const float v = s[row * H + c];
-    state[((size_t)b * R + u) * H + c] = v;
-    cat[row * 2 * H + c] = v;
-  }
-}
-void launch_draft_scatter_state(const float* s, const int* lvl_nodes, int n_lvl, int B, int R, int H, float* state,
-                                float* cat, hipStream_t st, int nodes_stride) {
-  if (n_lvl <= 0) return;
-  draft_scatter_state_kernel<<<dim3(n_lvl, B), 256, 0, st>>>(s, lvl_nodes, n_lvl, R, H, state, cat, nodes_stride);
-}
-
 __global__ void draft_root_kernel(const float* __restrict__ a, const int* __restrict__ next_tok,
                                   const int* __restrict__ m, int R, int H, float* __restrict__ root_x,
-                                  float* __restrict__ state, int* __restrict__ tokens, int Rs) {
+                                  float* __restrict__ state, int* __restrict__ tokens, int* __restrict__ aug_len, int Rs) {
   const int b = blockIdx.x;
   const int mb = min(m[b], R);
   for (int c = threadIdx.x; c < H; c += blockDim.x) {
@@ -960,32 +932,15 @@ __global__ void draft_root_kernel(const float* __restrict__ a, const int* __rest
     root_x[(size_t)b * H + c] = v;
     state[((size_t)b * Rs) * H + c] = v;
   }
-  if (threadIdx.x == 0 && mb >= 1) tokens[(size_t)b * Rs] = next_tok[(size_t)b * R + mb - 1];
+  if (threadIdx.x == 0) {
+    if (mb >= 1) tokens[(size_t)b * Rs] = next_tok[(size_t)b * R + mb - 1];
+    aug_len[b] += max(m[b], 0);
+  }
 }
 void launch_draft_root(const float* a, const int* next_tok, const int* m, int B, int R, int H, float* root_x,
-                       float* state, int* tokens, hipStream_t st, int Rs) {
-  draft_root_kernel<<<B, 256, 0, st>>>(a, next_tok, m, R, H, root_x, state, tokens, Rs ? Rs : R);
+                       float* state, int* tokens, int* aug_len, hipStream_t st, int Rs) {
+  draft_root_kernel<<<B, 256, 0, st>>>(a, next_tok, m, R, H, root_x, state, tokens, aug_len, Rs ? Rs : R);
 }
-
-__global__ void draft_assign_kernel(const int* __restrict__ ids, const int* __restrict__ par_row,
-                                    const int* __restrict__ rank, int c0, int c1, int n_par, int R,
-                                    const int* __restrict__ m, int* __restrict__ tokens) {
-  const int b = blockIdx.x;
-  if (m[b] < 1) return;
-  for (int c = c0 + threadIdx.x; c < c1; c += blockDim.x)
-    tokens[(size_t)b * R + c] = ids[((size_t)b * n_par + par_row[c]) * 16 + rank[c]];
-}
-void launch_draft_assign(const int* ids, const int* par_row, const int* rank, int c0, int c1, int n_par, int B, int R,
-                         const int* m, int* tokens, hipStream_t st) {
-  if (c1 <= c0) return;
-  draft_assign_kernel<<<B, 128, 0, st>>>(ids, par_row, rank, c0, c1, n_par, R, m, tokens);
-}
-
-__global__ void add_len_kernel(int* __restrict__ len, const int* __restrict__ m, int B) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b < B) len[b] += max(m[b], 0);
-}
-void launch_add_len(int* len, const int* m, int B, hipStream_t st) { add_len_kernel<<<(B + 63) / 64, 64, 0, st>>>(len, m, B); }
 
 __global__ void add_scalar_kernel(int* __restrict__ p, int v) { *p += v; }
 void launch_add_scalar(int* p, int v, hipStream_t st) { add_scalar_kernel<<<1, 1, 0, st>>>(p, v); }
@@ -1006,7 +961,7 @@ __global__ void accept_walk_kernel(const int* __restrict__ argmax, const int* __
                                    int B, int R, const int* __restrict__ n_forced,
                                    const int* __restrict__ forced_next, int* __restrict__ m,
                                    int* __restrict__ acc_idx, int* __restrict__ new_tokens,
-                                   int* __restrict__ next_tok, int child_stride) {
+                                   int* __restrict__ next_tok, int* __restrict__ seq_len, int child_stride) {
   const int b = blockIdx.x * blockDim.x + threadIdx.x;
   if (b >= B) return;
   const size_t o = (size_t)b * R;
@@ -1043,29 +998,40 @@ __global__ void accept_walk_kernel(const int* __restrict__ argmax, const int* __
   new_tokens[o + len - 1] = bonus;
   next_tok[o + len - 1] = bonus;
   m[b] = len;
+  seq_len[b] += len;   // (launch_accept_move subtracts it again)
 }
 void launch_accept_walk(const int* argmax, const int* tokens, const int* first_child, const int* n_child, int n_nodes,
                         int B, int R, const int* n_forced, const int* forced_next, int* m, int* acc_idx,
-                        int* new_tokens, int* next_tok, hipStream_t st, int child_stride) {
+                        int* new_tokens, int* next_tok, int* seq_len, hipStream_t st, int child_stride) {
   accept_walk_kernel<<<(B + 63) / 64, 64, 0, st>>>(argmax, tokens, first_child, n_child, n_nodes, B, R, n_forced,
-                                                   forced_next, m, acc_idx, new_tokens, next_tok, child_stride);
+                                                   forced_next, m, acc_idx, new_tokens, next_tok, seq_len, child_stride);
 }
 
 // ------------------------------------------------------------------------------------------
-// KV compaction: slot L+i <- slot L+acc_idx[i], ascending i.  A thread owns one cache column for
-// all rows, so the in-place moves of a column are ordered without any barrier.
+// What an accept call moves once the walk has written m and acc_idx and added m to the lengths, in one launch: blocks y < n_layers
+// compact the K/V rows of a layer, slot L+i <- slot L+acc_idx[i], ascending i (a thread owns one cache column for all rows,
+// so the in-place moves of a column are ordered without any barrier); the others gather one accepted hidden row each.
 // ------------------------------------------------------------------------------------------
 template <typename KT>
-__global__ void compact_kv_kernel(KT* __restrict__ kc, KT* __restrict__ vc, KVLayout kv, size_t k_layer_elems,
-                                  size_t v_layer_elems, const int* __restrict__ len, const int* __restrict__ m,
-                                  const int* __restrict__ acc_idx, int R) {
-  const int col = blockIdx.x * blockDim.x + threadIdx.x, layer = blockIdx.y, b = blockIdx.z;
-  const int width = kv.n_kv * kv.d;
-  if (col >= width) return;
-  const int mb = m[b], L = len[b];
-  if (mb <= 0 || L + mb > kv.max_seq) return;
-  KT* kbase = kc + (size_t)layer * k_layer_elems;
-  KT* vbase = vc + (size_t)layer * v_layer_elems;
+__global__ void accept_move_kernel(KT* __restrict__ kc, KT* __restrict__ vc, KVLayout kv, int n_layers, size_t layer_elems,
+                                   const int* __restrict__ len, const int* __restrict__ m, const int* __restrict__ acc_idx,
+                                   int R, const float* __restrict__ hidden, int H, float* __restrict__ hid_acc) {
+  const int b = blockIdx.z, mb = m[b];
+  if ((int)blockIdx.y >= n_layers) {
+    const int i = blockIdx.y - n_layers;
+    if (i >= mb) return;
+    const int a = acc_idx[(size_t)b * R + i];
+    if (a < 0 || a >= R) return;
+    for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < H; c += gridDim.x * blockDim.x)
+      hid_acc[((size_t)b * R + i) * H + c] = hidden[((size_t)b * R + a) * H + c];
+    return;
+  }
+  const int col = blockIdx.x * blockDim.x + threadIdx.x, layer = blockIdx.y;
+  if (col >= kv.n_kv * kv.d || mb <= 0) return;
+  const int L = len[b] - mb;
+  if (L + mb > kv.max_seq) return;
+  KT* kbase = kc + (size_t)layer * layer_elems;
+  KT* vbase = vc + (size_t)layer * layer_elems;
   const int head = col / kv.d, dim = col % kv.d;
   for (int i = 0; i < mb; ++i) {
     const int a = acc_idx[(size_t)b * R + i];
@@ -1074,31 +1040,14 @@ __global__ void compact_kv_kernel(KT* __restrict__ kc, KT* __restrict__ vc, KVLa
     mvkv(vbase, kv_v_at(kv, b, head, dim, L + i), kv_v_at(kv, b, head, dim, L + a), kv.plane);
   }
 }
-void launch_compact_kv(void* k_cache, void* v_cache, int kvdtype, KVLayout kv, int n_layers, size_t k_layer_elems,
-                       size_t v_layer_elems, const int* len, const int* m, const int* acc_idx, int B, int R,
-                       hipStream_t st) {
-  const int width = kv.n_kv * kv.d;
-  dim3 grid((width + 255) / 256, n_layers, B);
+void launch_accept_move(void* k_cache, void* v_cache, int kvdtype, KVLayout kv, int n_layers, size_t layer_elems, const int* len,
+                        const int* m, const int* acc_idx, int B, int R, int max_rows, const float* hidden, int H, float* hid_acc,
+                        hipStream_t st) {
+  const dim3 grid((kv.n_kv * kv.d + 255) / 256, n_layers + max_rows, B);
   if (kvdtype == 0)
-    compact_kv_kernel<float><<<grid, 256, 0, st>>>((float*)k_cache, (float*)v_cache, kv, k_layer_elems, v_layer_elems,
-                                                   len, m, acc_idx, R);
+    accept_move_kernel<float><<<grid, 256, 0, st>>>((float*)k_cache, (float*)v_cache, kv, n_layers, layer_elems, len, m, acc_idx, R, hidden, H, hid_acc);
   else
-    compact_kv_kernel<bf16_t><<<grid, 256, 0, st>>>((bf16_t*)k_cache, (bf16_t*)v_cache, kv, k_layer_elems,
-                                                    v_layer_elems, len, m, acc_idx, R);
-}
-
-__global__ void gather_hidden_kernel(const float* __restrict__ hidden, const int* __restrict__ acc_idx,
-                                     const int* __restrict__ m, int R, int H, float* __restrict__ hid_acc) {
-  const int i = blockIdx.x, b = blockIdx.y;
-  if (i >= m[b]) return;
-  const int a = acc_idx[(size_t)b * R + i];
-  if (a < 0 || a >= R) return;
-  for (int c = threadIdx.x; c < H; c += blockDim.x)
-    hid_acc[((size_t)b * R + i) * H + c] = hidden[((size_t)b * R + a) * H + c];
-}
-void launch_gather_hidden(const float* hidden, const int* acc_idx, const int* m, int B, int R, int H, float* hid_acc,
-                          hipStream_t st) {
-  gather_hidden_kernel<<<dim3(R, B), 256, 0, st>>>(hidden, acc_idx, m, R, H, hid_acc);
+    accept_move_kernel<bf16_t><<<grid, 256, 0, st>>>((bf16_t*)k_cache, (bf16_t*)v_cache, kv, n_layers, layer_elems, len, m, acc_idx, R, hidden, H, hid_acc);
 }
 
 template <typename KT>
@@ -1149,8 +1098,6 @@ void launch_write_kv(void* k_cache, void* v_cache, int kvdtype, KVLayout kv, int
 // ------------------------------------------------------------------------------------------
 // split-bf16 planes and partial-sum consumers
 // ------------------------------------------------------------------------------------------
-// (16 bytes at once from any multiple of 4: the operator's callers owe x no more, and the load instruction takes it)
-typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 __global__ void split_planes_kernel(const float* __restrict__ x, int ldx, FragPlanes out, int K) {
   const int row = blockIdx.y;
   const int c = (blockIdx.x * blockDim.x + threadIdx.x) * 4;
@@ -1185,14 +1132,82 @@ void launch_reduce(const float* P, int splits, size_t split_stride, int ldp, con
     reduce_kernel<bf16_t><<<grid, 256, 0, st>>>(P, splits, split_stride, ldp, (const bf16_t*)bias, Y, ldy, N, mode);
 }
 
+// total over the block of every thread's v; `red` holds a float per wavefront
+__device__ __forceinline__ float block_sum_up_to_1024(float v, float* red) {
+  v = wave_sum(v);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+  __syncthreads();
+  float tot = 0.f;
+#pragma unroll
+  for (int w = 0; w < 16; ++w)
+    if (w * 64 < (int)blockDim.x) tot += red[w];
+  return tot;
+}
+
+// Start of a pass, one block per row (b, i): out = table[tok] where the row is valid, with a gain its RMSNorm as planes, and the
+// row's rotary table at position base_len[b] + (depth ? depth[i] : i).  Three small launches' work; what bounds it is the chain
+// token -> table row -> norm, with the angles' arithmetic beside it.
+template <typename WT, int PC>
+__global__ __launch_bounds__(1024) void pass_start_kernel(PassStart p) {
+  __shared__ float red[16];
+  const RowMap& rm = p.rm;
+  const int b = blockIdx.y, i = blockIdx.x;
+  const size_t row = (size_t)b * rm.R + i;
+  const bool valid = i < rows_valid(rm, b);
+  const int H = p.H, c0 = threadIdx.x * 4, step = blockDim.x * 4;
+  float4 keep[PC], gn[PC];
+  float ss = 0.f;
+  if (valid) {
+    int t = p.tok[row];
+    t = t < 0 ? 0 : (t >= p.vocab ? p.vocab - 1 : t);
+    const WT* src = (const WT*)p.table + (size_t)t * H;
+    auto copy = [&](int c) -> float4 {
+      const float4 v = ld4_any(src + c);
+      *(f32x4_any*)(p.out + row * p.ldo + c) = (f32x4_any){v.x, v.y, v.z, v.w};
+      ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+      return v;
+    };
+#pragma unroll
+    for (int it = 0; it < PC; ++it) {
+      const int c = c0 + it * step;
+      if (c < H) {
+        if (p.gain) gn[it] = ld4_any((const WT*)p.gain + c);
+        keep[it] = copy(c);
+      }
+    }
+    if (PC > 1)
+      for (int c = c0 + PC * step; c < H; c += step) copy(c);
+  }
+  rope_row(p.rope, b, i, row);
+  if (!p.gain || !valid) return;   // (uniform)
+  const float tot = block_sum_up_to_1024(ss, red);
+  const float scale = 1.0f / sqrtf(tot / (float)H + p.eps);
+  auto emit = [&](int c, float4 v, float4 g4) {
+    frag_store4(p.planes, (int)row, c, v.x * scale * g4.x, v.y * scale * g4.y, v.z * scale * g4.z, v.w * scale * g4.w);
+  };
+#pragma unroll
+  for (int it = 0; it < PC; ++it) {
+    const int c = c0 + it * step;
+    if (c < H) emit(c, keep[it], gn[it]);
+  }
+  if (PC > 1)
+    for (int c = c0 + PC * step; c < H; c += step) emit(c, ld4_any(p.out + row * p.ldo + c), ld4_any((const WT*)p.gain + c));   // written by this same thread above
+}
+void launch_pass_start(const PassStart& p, int wdtype, hipStream_t st) {
+  const dim3 grid(p.rm.n, p.rm.B);
+  const int threads = std::min(1024, (p.H / 4 + 63) / 64 * 64);
+  if (wdtype == 0) {
+    if (p.H <= 4096) pass_start_kernel<float, 1><<<grid, threads, 0, st>>>(p);
+    else pass_start_kernel<float, 2><<<grid, threads, 0, st>>>(p);
+  } else {
+    if (p.H <= 4096) pass_start_kernel<bf16_t, 1><<<grid, threads, 0, st>>>(p);
+    else pass_start_kernel<bf16_t, 2><<<grid, threads, 0, st>>>(p);
+  }
+}
+
 // One block of up to 1024 threads per row: residual add of the partial tiles over NS ranges of K (all requested at once,
 // summed in range order), then RMSNorm written as planes in fragment order.  A thread keeps PC float4 of the new row in
 // registers across the block-wide sum of squares; rows wider than PC * 4096 re-read the rest.
-typedef bf16_t bf16x4_any __attribute__((ext_vector_type(4), aligned(2)));   // (weights owe no alignment beyond their element's)
-__device__ __forceinline__ float4 ld4_any(const bf16_t* p) {
-  const bf16x4_any u = *(const bf16x4_any*)p;
-  return make_float4(bf16_to_f32(u[0]), bf16_to_f32(u[1]), bf16_to_f32(u[2]), bf16_to_f32(u[3]));
-}
 template <int NS, int PC>
 __global__ __launch_bounds__(1024) void reduce_add_norm_kernel(float* __restrict__ x, int ldx,
                                                                const float* __restrict__ P, size_t sps, int ldp,
@@ -1231,13 +1246,7 @@ __global__ __launch_bounds__(1024) void reduce_add_norm_kernel(float* __restrict
       put(c, r.add_to(bias ? ld4_any(bias + c) : *(const float4*)(xr + c)));
     }
   if (!gain) return;
-  ss = wave_sum(ss);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
-  __syncthreads();
-  float tot = 0.f;
-#pragma unroll
-  for (int w = 0; w < 16; ++w)
-    if (w * 64 < (int)blockDim.x) tot += red[w];
+  const float tot = block_sum_up_to_1024(ss, red);
   const float scale = 1.0f / sqrtf(tot / (float)H + eps);
   auto emit = [&](int c, float4 v, float4 g4) {
     frag_store4(out, (int)row, c, v.x * scale * g4.x, v.y * scale * g4.y, v.z * scale * g4.z, v.w * scale * g4.w);
