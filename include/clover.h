@@ -330,7 +330,7 @@ int clover_op_swiglu(const float *X, const void *Wg, const void *Wu, void *plane
                      void *scratch, size_t scratch_bytes, void *hip_stream);
 
 /* Host only: the form of the MFMA GEMM that a launch takes.  form[0]: 0 = one row block, four wavefronts side by side, else
- * RB (a workgroup owns 32 RB rows); form[1]: CB (32 CB columns); form[2]: row tiles; form[3]: ranges of K; form[4]: stages
+ * RB (a workgroup owns 32 RB rows); form[1]: CB (32 CB columns, or 16 fewer); form[2]: row tiles; form[3]: ranges of K; form[4]: stages
  * per range.  epi 0: Y[M,N] over k_parts ranges of K, or over those that clover_op_gemm sums (k_parts 0; more than 256 rows:
  * those that a model's pass sums); epi 1: clover_op_swiglu with N = F.  CLOVER_E_SHAPE unless N % 16 == 0, K % 128 == 0 and
  * k_parts is a count the kernel takes. */

@@ -1536,7 +1536,7 @@ int clover_op_gemm_form(int32_t epi, int32_t M, int32_t N, int32_t K, int32_t k_
       (k_parts > 0 && K / 32 % k_parts != 0) || (epi == 1 && k_parts > 1))
     return fail(nullptr, CLOVER_E_SHAPE, "shape not supported by the MFMA GEMM");
   const TileForm f = tile_gemm_form(M, N, K, epi, k_parts == 0 && epi == 0 && M <= 256 ? op_gemm_scratch(M, N, K).kp : k_parts);
-  form[0] = f.rb; form[1] = f.cb; form[2] = f.row_tiles; form[3] = f.k_parts; form[4] = f.stages;
+  form[0] = f.rb; form[1] = (f.wb + 1) / 2; form[2] = f.row_tiles; form[3] = f.k_parts; form[4] = f.stages;
   return CLOVER_OK;
 }
 

@@ -306,7 +306,7 @@ constexpr int TILE_MAX_K_PARTS = 8;
 int tile_gemm_pick_k_parts(int M, int N, int K);
 void launch_gemm_tile(const TileGemm& g, hipStream_t st);
 // what launch_gemm_tile runs for M rows (N = F for epi 1; k_parts 0: its own choice)
-struct TileForm { int rb, cb, row_tiles, k_parts, stages; };
+struct TileForm { int rb, wb /* column blocks of 16 */, row_tiles, k_parts, stages; };
 TileForm tile_gemm_form(int M, int N, int K, int epi, int k_parts);
 
 // ---- fused bookkeeping kernels of the draft head (MFMA path, bf16 weights) ----------------------

@@ -3,12 +3,13 @@
 //   EPI 0:  Y[M,N]      = X[M,K] * W[N,K]^T                   (fp32; over k_parts ranges of K: partial tiles)
 //   EPI 1:  out[M,F]    = planes of silu(X Wg^T) * (X Wu^T)    (the SwiGLU projection)
 //
-// What bounds it: up to 64 rows the weight stream from HBM, above ~150 rows the matrix pipe (hi + lo planes are two
+// What bounds it: up to 16 rows the weight stream from HBM, above ~150 rows the matrix pipe (hi + lo planes are two
 // matrix instructions per fragment pair; from 512 rows on its power: it is busy 82 to 90 % of the time at 1.9 to 2.2 GHz,
-// and nothing but products runs at 2.25), and everywhere the load path of a compute unit, which takes the activations as well
-// as the weights.
+// and nothing but products runs at 2.25), and in between the lines that a compute unit can have in flight: about 130 of 128 bytes
+// (counters: requests x their latency / cycles, gate+up at 64 rows 126, at one row 146), 1000 clocks each for weights and 350 for
+// activations out of the L2, so what counts is lines per compute unit, and buffers beyond 16 KB do not help.
 //
-// Shape.  A workgroup of four wavefronts (2 x 2, one per SIMD; up to 16 rows 1 x 4) owns 32 RB rows x 32 CB columns (RB 1 to 5 and 8); a wavefront RB x CB
+// Shape.  A workgroup of four wavefronts (2 x 2, one per SIMD; up to 16 rows 1 x 4) owns 32 RB rows x 16 WB columns (RB 1 to 5 and 8); a wavefront RB x WB / 2
 // products of 16 x 16.  Both operands go global -> LDS directly, 32 columns of K per stage, as 1 KB blocks that are
 // contiguous in global memory too (one load instruction each), NBUF stages deep: the loads of stage s + NBUF are issued
 // while stage s is multiplied.  In flight per workgroup (mostly one to a compute unit): NBUF stages of 2 KB per 16 rows and
@@ -29,7 +30,7 @@
 // Many rows, tiles of up to 160 / of 256 rows (and half the staged bytes per product): gate+up 179 / 154 at 512, 351 / 306
 // at 1024, 701 / 605 at 2048, LM head 777 / 663 at 512, 3106 / 2713 at 2048, down 322 / 302 at 2048, QKV 159 / 137.
 //
-// RB, CB and the K ranges are chosen per launch (pick_tile).
+// RB, WB and the K ranges are chosen per launch (pick_tile).
 #include "clover_internal.h"
 
 #include <algorithm>
@@ -78,27 +79,28 @@ __device__ __forceinline__ void wait_barrier() {
 // RB 0: the form for up to 16 rows: one row block, the four wavefronts side by side on its columns, 64 columns of K per
 // stage.  (As RB 1, half of the activation loads would fetch the same row block again: gate+up at one row 40 us of which
 // the weights alone take 36 and the activations 11.)
-template <int RB, int CB>
+// WB: weight blocks (16 columns) of a workgroup.
+template <int RB, int WB>
 struct TileShape {
   static constexpr bool ONE = RB == 0;
   static constexpr int KS = ONE ? 2 : 1;               // 32-column steps per stage
   static constexpr int RBT = ONE ? 1 : 2 * RB;         // row blocks of the workgroup
   static constexpr int RBW = ONE ? 1 : RB;             // row and column blocks of a wavefront
-  static constexpr int CBW = ONE ? CB / 2 : CB;
-  static constexpr int WB = 2 * CB;                    // weight blocks of the workgroup per step
+  static constexpr int CBW = ONE ? (WB + 3) / 4 : (WB + 1) / 2;
   static constexpr int XF = KS * RBT * 2, WF = KS * WB;   // fragment blocks of a stage: activations (hi, lo), weights
+  static constexpr int WREST = WF % 4;                 // weight blocks that the four wavefronts share in their last load
   static constexpr int STAGE = (XF + WF) * 1024;       // bytes
   static constexpr int NBUF = std::min(6, 160 * 1024 / STAGE);   // (12 for the narrow tiles measured 2 % slower)
-  static constexpr int EPI_LD = CB * 32 + 16;          // EPI 1: LDS row stride of the finished planes (bytes)
+  static constexpr int EPI_LD = WB * 16 + (WB % 2 ? 32 : 16);    // EPI 1: LDS row stride of the finished planes (bytes): an odd number of 16-byte pieces
   static constexpr int LDS = std::max(NBUF * STAGE, 2 * RBT * 16 * EPI_LD);
 };
 
 // NT: non-temporal loads, for weights that no other workgroup reads (gate+up at 64 rows 47.0 -> 44.6 us; where row tiles
 // share them it costs: 256 rows 96.5 -> 100).
-template <int RB, int CB, int EPI, bool NT>
+template <int RB, int WB, int EPI, bool NT>
 __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(TileGemm p) {
-  using T = TileShape<RB, CB>;
-  constexpr int XF = T::XF, WF = T::WF, WB = T::WB, STAGE = T::STAGE, NBUF = T::NBUF;
+  using T = TileShape<RB, WB>;
+  constexpr int XF = T::XF, WF = T::WF, WREST = T::WREST, STAGE = T::STAGE, NBUF = T::NBUF;
   constexpr int KS = T::KS, RBT = T::RBT, RBW = T::RBW, CBW = T::CBW;
   constexpr int XL = XF / 4, WL = (WF + 3) / 4, L = XL + WL;   // staging loads per wavefront and stage
   constexpr int NRS = 2 * RBW + CBW, NR = KS * NRS;            // fragments a wavefront reads per step and stage
@@ -108,6 +110,9 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(TileGemm p) {
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int l16 = lane & 15, g4 = lane >> 4;
   const int wr = T::ONE ? 0 : wave & 1, wc = T::ONE ? wave : wave >> 1;
+  // first column block of the wavefront, and the first that it stores: where the blocks do not divide, the last wavefronts' begin
+  // earlier and the overlap is computed twice
+  const int wb0 = min(wc * CBW, WB - CBW), wown = wc * CBW;
   // workgroup id -> (row tile, column tile, K range): ids 8 apart share an XCD (dealt round-robin), so the row tiles
   // of the same columns are neighbours in that XCD's own order and find the weights in its L2
   const int rt = (p.M + 16 * RBT - 1) / (16 * RBT);
@@ -142,14 +147,19 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(TileGemm p) {
     xoff[j] = lane16 + (unsigned)(f / RBT) * (unsigned)xstage + (unsigned)rblk * 2048u + (unsigned)(wave & 1) * 1024u;
   }
 #pragma unroll
-  for (int i = 0; i < WL; ++i) {   // (an odd block count: two wavefronts stage the last block again, same bytes)
-    const int f = min(i * 4 + wave, WF - 1), c = min(tile * WB + f % WB, n_wb - 1);
-    woff[i] = lane16 + (unsigned)(f / WB) * (unsigned)wstage + (unsigned)c * 1024u;
+  for (int i = 0; i < WL; ++i) {   // (the last load: 16 WREST lanes of every wavefront take the blocks that are left, piece after piece)
+    const bool rest = WREST > 0 && i == WL - 1;
+    const int pc = rest ? min(wave * 16 * WREST + lane, 64 * WREST - 1) : wave * 64 + lane, f = i * 4 + (pc >> 6), c = min(tile * WB + f % WB, n_wb - 1);
+    woff[i] = (unsigned)(pc & 63) * 16u + (unsigned)(f / WB) * (unsigned)wstage + (unsigned)c * 1024u;
   }
   const char* xp = (const char*)p.X.p + (size_t)kt0 * xstage;   // the stage that is requested next
   const char* wp = (const char*)p.W + (size_t)kt0 * wstage;
   const unsigned ldsw = lds0 + (unsigned)wave * 1024u;
-  const unsigned wlast = (unsigned)__builtin_amdgcn_readfirstlane((XF + min((WL - 1) * 4 + wave, WF - 1) - wave) * 1024);   // the last load's destination
+  // The last load's destination and lanes.  (Two wavefronts used to stage the last blocks a second time.  A compute unit has
+  // about 130 lines of 128 bytes in flight, whatever the buffers hold, so a line that is loaded twice costs its share of the
+  // kernel, as do compute units without a workgroup.  64 rows: gate+up of 11008 channels 45.4 -> 40.9 us, QKV 16.7 -> 15.6.)
+  const unsigned wlast = (unsigned)__builtin_amdgcn_readfirstlane((XF + (WL - 1) * 4) * 1024 + wave * (WREST * 256 - 1024));
+  const unsigned long long some_lanes = (1ull << (16 * WREST)) - 1ull;
   // Load j of the stage at (xp, wp), M0 set in front of it: at least one instruction (or the no-op) has to lie in between.
   // Contract: each load has one set_m0 of its own, with no other load and no jump in between.  The load cannot say that it
   // reads M0, so nothing but that order -- kept, both are volatile -- and the absence of compiler-made writes of M0 carries
@@ -171,7 +181,10 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(TileGemm p) {
     } else {
       const unsigned off = woff[j - XL];
       const gbyte_ptr src = (gbyte_ptr)wp;
-      if constexpr (NT) asm volatile("global_load_lds_dwordx4 %0, %1 nt" : : "v"(off), "s"(src));
+      if constexpr (WREST > 0 && j == L - 1) {   // (every lane is active here: the kernel's control flow is uniform)
+        if constexpr (NT) asm volatile("s_mov_b64 exec, %2\n\tglobal_load_lds_dwordx4 %0, %1 nt\n\ts_mov_b64 exec, -1" : : "v"(off), "s"(src), "s"(some_lanes));
+        else asm volatile("s_mov_b64 exec, %2\n\tglobal_load_lds_dwordx4 %0, %1\n\ts_mov_b64 exec, -1" : : "v"(off), "s"(src), "s"(some_lanes));
+      } else if constexpr (NT) asm volatile("global_load_lds_dwordx4 %0, %1 nt" : : "v"(off), "s"(src));
       else asm volatile("global_load_lds_dwordx4 %0, %1" : : "v"(off), "s"(src));
     }
   };
@@ -199,7 +212,7 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(TileGemm p) {
 
   Frag fa[NR], fb[NR];   // per step: [2 rb + plane], then [2 RBW + column block]
   const char* const xrd = sm + wr * RBW * 2048 + l16 * 64 + ((g4 ^ ((0 - (l16 >> 2)) & 3)) * 16);
-  const char* const wrd = sm + (XF + wc * CBW) * 1024 + lane * 16;
+  const char* const wrd = sm + (XF + wb0) * 1024 + lane * 16;
   auto read1 = [&](Frag (&f)[NR], auto rc, unsigned buf) __attribute__((always_inline)) {
     constexpr int k = decltype(rc)::value / NRS, r = decltype(rc)::value % NRS;
     if constexpr (r < 2 * RBW) f[k * NRS + r].u = *(const u32x4*)(xrd + buf + (k * RBT * 2 + r) * 1024);
@@ -282,27 +295,27 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(TileGemm p) {
           h[r] = t_rn(o);
           l[r] = t_rn(o - __uint_as_float(h[r] << 16));
         }
-        if (rb + up < RBW) {
-          char* dst = sm + ((wr * RBW + rb + up) * 16 + l16) * LD + ((wc * CBW + c) * 8 + cl) * 2;
+        if (rb + up < RBW && wb0 + c >= wown) {
+          char* dst = sm + ((wr * RBW + rb + up) * 16 + l16) * LD + ((wb0 + c) * 8 + cl) * 2;
           *(uint2*)dst = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
           *(uint2*)(dst + PLANE) = make_uint2(l[0] | (l[1] << 16), l[2] | (l[3] << 16));
         }
       }
     __syncthreads();
-    // pairs of pieces (8 columns each; 2 CB of them, an even number that starts at an even piece): 16 rows x 32 bytes of
-    // a KB block per half wavefront
-    constexpr int PAIRS = CB;
-    for (int i = tid; i < PAIRS * RBT * 64; i += 256) {
-      const int q = i & 1, r = (i >> 1) & 15, plane = (i >> 5) & 1, rb = (i >> 6) % RBT, pc = (i >> 6) / RBT * 2 + q;
-      const int row = rb * 16 + r, m = row0 + row, col = (tile * 2 * CB + pc) * 8;
+    // pieces of 8 columns, in pairs where their number is even (and a tile starts at an even piece): 16 rows x 32 bytes of a KB
+    // block per half wavefront, else x 16
+    constexpr int PP = WB % 2 ? 1 : 2, PL = PP - 1;   // pieces side by side; their bits of an index
+    for (int i = tid; i < WB * RBT * 32; i += 256) {
+      const int q = i & PL, r = (i >> PL) & 15, plane = (i >> (PL + 4)) & 1, rb = (i >> (PL + 5)) % RBT, pc = (i >> (PL + 5)) / RBT * PP + q;
+      const int row = rb * 16 + r, m = row0 + row, col = (tile * WB + pc) * 8;
       if (m < p.M && col < p.N)
         *(u32x4*)(p.out.p + frag_at(p.out, m, col) + plane * 512) = *(const u32x4*)(sm + plane * PLANE + row * LD + pc * 16);
     }
   } else {
 #pragma unroll
     for (int c = 0; c < CBW; ++c) {
-      const int blk = tile * WB + wc * CBW + c;
-      if (blk * 16 >= p.N) continue;
+      const int blk = tile * WB + wb0 + c;
+      if (blk * 16 >= p.N || wb0 + c < wown) continue;
       const int col = blk * 16 + 4 * g4;
 #pragma unroll
       for (int rb = 0; rb < RBW; ++rb) {
@@ -314,44 +327,46 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(TileGemm p) {
   }
 }
 
-template <int RB, int CB, int EPI, bool NT>
+template <int RB, int WB, int EPI, bool NT>
 void launch_tile_one(const TileGemm& g, int wgs, hipStream_t st) {
-  constexpr int lds = TileShape<RB, CB>::LDS;
+  constexpr int lds = TileShape<RB, WB>::LDS;
   static OncePerDevice once;
-  allow_dynamic_lds(once, (const void*)gemm_tile_kernel<RB, CB, EPI, NT>, lds);
-  gemm_tile_kernel<RB, CB, EPI, NT><<<wgs, 256, lds, st>>>(g);
+  allow_dynamic_lds(once, (const void*)gemm_tile_kernel<RB, WB, EPI, NT>, lds);
+  gemm_tile_kernel<RB, WB, EPI, NT><<<wgs, 256, lds, st>>>(g);
 }
 template <int EPI, bool NT>
-void launch_tile_many(const TileGemm& g, int rb, int cb, int wgs, hipStream_t st) {   // rb 3..5, cb 4, 6, 7, 8; rb 3, cb 3
+void launch_tile_many(const TileGemm& g, int rb, int wb, int wgs, hipStream_t st) {   // rb 3..5, wb 8, 12, 14, 16; rb 3, wb 6
 #define CLV_TL(RB_)                                                   \
-  if (cb == 4) launch_tile_one<RB_, 4, EPI, NT>(g, wgs, st);          \
-  else if (cb == 6) launch_tile_one<RB_, 6, EPI, NT>(g, wgs, st);     \
-  else if (cb == 7) launch_tile_one<RB_, 7, EPI, NT>(g, wgs, st);     \
-  else launch_tile_one<RB_, 8, EPI, NT>(g, wgs, st);
-  if (rb == 3 && cb == 3) launch_tile_one<3, 3, EPI, NT>(g, wgs, st);
+  if (wb == 8) launch_tile_one<RB_, 8, EPI, NT>(g, wgs, st);          \
+  else if (wb == 12) launch_tile_one<RB_, 12, EPI, NT>(g, wgs, st);   \
+  else if (wb == 14) launch_tile_one<RB_, 14, EPI, NT>(g, wgs, st);   \
+  else launch_tile_one<RB_, 16, EPI, NT>(g, wgs, st);
+  if (rb == 3 && wb == 6) launch_tile_one<3, 6, EPI, NT>(g, wgs, st);
   else if (rb == 3) { CLV_TL(3) } else if (rb == 4) { CLV_TL(4) } else { CLV_TL(5) }
 #undef CLV_TL
 }
 template <int EPI>
-void launch_tile_big(const TileGemm& g, int cb, int wgs, hipStream_t st) {   // rb 8 (always several row tiles): cb 6, 7, 8
-  if (cb == 6) launch_tile_one<8, 6, EPI, false>(g, wgs, st);
-  else if (cb == 7) launch_tile_one<8, 7, EPI, false>(g, wgs, st);
-  else launch_tile_one<8, 8, EPI, false>(g, wgs, st);
+void launch_tile_big(const TileGemm& g, int wb, int wgs, hipStream_t st) {   // rb 8 (always several row tiles): wb 12, 14, 16
+  if (wb == 12) launch_tile_one<8, 12, EPI, false>(g, wgs, st);
+  else if (wb == 14) launch_tile_one<8, 14, EPI, false>(g, wgs, st);
+  else launch_tile_one<8, 16, EPI, false>(g, wgs, st);
 }
 template <int EPI>
-void launch_tile_few(const TileGemm& g, int rb, int cb, int wgs, hipStream_t st) {    // rb 0: cb 4, 6; rb 1: cb 3, 4, 6; rb 2: cb 3, 4, 6, 8
-  if (rb == 0 && cb == 4) launch_tile_one<0, 4, EPI, true>(g, wgs, st);
-  else if (rb == 0) launch_tile_one<0, 6, EPI, true>(g, wgs, st);
-  else if (rb == 1 && cb == 3) launch_tile_one<1, 3, EPI, true>(g, wgs, st);
-  else if (rb == 2 && cb == 3) launch_tile_one<2, 3, EPI, true>(g, wgs, st);
-  else if (rb == 1 && cb == 4) launch_tile_one<1, 4, EPI, true>(g, wgs, st);
-  else if (rb == 1) launch_tile_one<1, 6, EPI, true>(g, wgs, st);
-  else if (cb == 4) launch_tile_one<2, 4, EPI, true>(g, wgs, st);
-  else if (cb == 6) launch_tile_one<2, 6, EPI, true>(g, wgs, st);
-  else launch_tile_one<2, 8, EPI, true>(g, wgs, st);
+void launch_tile_few(const TileGemm& g, int rb, int wb, int wgs, hipStream_t st) {    // rb 0: wb 8, 12; rb 1: wb 6, 7, 8, 12; rb 2: wb 6, 7, 8, 12, 16
+  if (rb == 0 && wb == 8) launch_tile_one<0, 8, EPI, true>(g, wgs, st);
+  else if (rb == 0) launch_tile_one<0, 12, EPI, true>(g, wgs, st);
+  else if (rb == 1 && wb == 6) launch_tile_one<1, 6, EPI, true>(g, wgs, st);
+  else if (rb == 1 && wb == 7) launch_tile_one<1, 7, EPI, true>(g, wgs, st);
+  else if (rb == 1 && wb == 8) launch_tile_one<1, 8, EPI, true>(g, wgs, st);
+  else if (rb == 1) launch_tile_one<1, 12, EPI, true>(g, wgs, st);
+  else if (wb == 6) launch_tile_one<2, 6, EPI, true>(g, wgs, st);
+  else if (wb == 7) launch_tile_one<2, 7, EPI, true>(g, wgs, st);
+  else if (wb == 8) launch_tile_one<2, 8, EPI, true>(g, wgs, st);
+  else if (wb == 12) launch_tile_one<2, 12, EPI, true>(g, wgs, st);
+  else launch_tile_one<2, 16, EPI, true>(g, wgs, st);
 }
 
-struct TilePick { int rb, cb, kp; };
+struct TilePick { int rb, wb, kp; };
 
 // Tile and K ranges of a launch by estimated time, in clocks.  A stage of a workgroup takes the longest of its matrix
 // instructions, of its 1 KB loads at 40 B/clk (what is left of the load path's 55 beside the LDS reads) and of an HBM
@@ -378,7 +393,7 @@ TilePick pick_tile(int M, int N, int K, int epi, int kp_fixed) {
   const int rb_lo = M > 64 ? 3 : M / 32, rb_hi = M > 64 ? 5 : M / 32, KT = K / TL_KST;
   const int only_rb = tune_int("CLOVER_TILE_RB", 0), only_cb = tune_int("CLOVER_TILE_CB", 0), only_kp = tune_int("CLOVER_TILE_KP", 0);
   const bool many = M > 256 && K >= 1024;
-  TilePick best{rb_lo, 4, 1};
+  TilePick best{rb_lo, 8, 1};
   double best_t = 1e30;
   for (int rb = rb_lo; rb <= (many ? 8 : rb_hi); ++rb)
     for (int cb : cbs) {
@@ -397,12 +412,16 @@ TilePick pick_tile(int M, int N, int K, int epi, int kp_fixed) {
         if (kp_fixed <= 0 && only_kp > 0 && kp != only_kp) continue;
         const double work = rounds * (KT / kp) * stage, a = work * work, b = stream * stream;
         const double t = std::sqrt(std::sqrt(a * a + b * b)) + rounds * 5000.0 + (kp > 1 ? kp * (double)M * N * 8.0 / 2300.0 : 0.0);
-        if (t < best_t) { best_t = t; best = TilePick{rb, cb, kp}; }
+        if (t < best_t) { best_t = t; best = TilePick{rb, 2 * cb, kp}; }
       }
     }
   // Up to 16 rows over the whole K: the one-row-block form (gate+up 41 -> 36 us, LM head 165 -> 157 at one row).  Over K
   // ranges its 64-column stages are too coarse for 8 to 16 of them (QKV 10.9 -> 12.7, Wo and down 13.5 -> 14.0).
-  if (one && best.kp == 1 && best.cb != 3) best.rb = 0;
+  if (one && best.kp == 1 && best.wb != 6) best.rb = 0;
+  // Seven column blocks instead of eight where one round of workgroups still holds them: more compute units share the lines that
+  // are loaded.  gate+up of 14336 channels, 224 -> 256 workgroups: 23 rows 38.5 -> 37.5 us, 64 rows 46.9 -> 45.8; 80 and 96 rows gain
+  // less than half a percent, and one row, bound by the weight stream itself, loses one.
+  if ((best.rb == 1 || best.rb == 2) && best.wb == 8 && M <= 32 * best.rb && (blocks + 6) / 7 * best.kp <= TL_CUS && tune_int("CLOVER_TILE_WB7", 1)) best.wb = 7;
   return best;
 }
 
@@ -414,7 +433,7 @@ int tile_gemm_pick_k_parts(int M, int N, int K) { return pick_tile(M, N, K, 0, 0
 TileForm tile_gemm_form(int M, int N, int K, int epi, int k_parts) {
   const TilePick t = pick_tile(M, N, K, epi, epi == 1 ? 1 : k_parts);
   const int rows = t.rb == 0 ? 16 : 32 * t.rb;
-  return TileForm{t.rb, t.cb, (M + rows - 1) / rows, t.kp, K / (t.rb == 0 ? 2 * TL_KST : TL_KST) / t.kp};
+  return TileForm{t.rb, t.wb, (M + rows - 1) / rows, t.kp, K / (t.rb == 0 ? 2 * TL_KST : TL_KST) / t.kp};
 }
 
 void launch_gemm_tile(const TileGemm& g_in, hipStream_t st) {
@@ -422,14 +441,14 @@ void launch_gemm_tile(const TileGemm& g_in, hipStream_t st) {
   if (g.k_parts < 1 || g.epi == 1) g.k_parts = 1;
   const TileForm t = tile_gemm_form(g.M, g.N, g.K, g.epi, g.k_parts);
   const int blocks = g.epi == 1 ? g.N / 8 : g.N / 16, rt = t.row_tiles;
-  g.n_units = (blocks + 2 * t.cb - 1) / (2 * t.cb) * g.k_parts;
+  g.n_units = (blocks + t.wb - 1) / t.wb * g.k_parts;
   const int wgs = rt > 1 ? (g.n_units + 7) / 8 * 8 * rt : g.n_units;
   auto go = [&](auto epic) {
     constexpr int EPI = decltype(epic)::value;
-    if (t.rb == 8) launch_tile_big<EPI>(g, t.cb, wgs, st);
-    else if (t.rb < 3) launch_tile_few<EPI>(g, t.rb, t.cb, wgs, st);
-    else if (rt > 1) launch_tile_many<EPI, false>(g, t.rb, t.cb, wgs, st);
-    else launch_tile_many<EPI, true>(g, t.rb, t.cb, wgs, st);
+    if (t.rb == 8) launch_tile_big<EPI>(g, t.wb, wgs, st);
+    else if (t.rb < 3) launch_tile_few<EPI>(g, t.rb, t.wb, wgs, st);
+    else if (rt > 1) launch_tile_many<EPI, false>(g, t.rb, t.wb, wgs, st);
+    else launch_tile_many<EPI, true>(g, t.rb, t.wb, wgs, st);
   };
   if (g.epi == 1) go(std::integral_constant<int, 1>{});
   else go(std::integral_constant<int, 0>{});
