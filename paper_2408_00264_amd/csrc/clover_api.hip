@@ -769,10 +769,9 @@ void draft_expand_dynamic(clover_ctx* x, int B, const int* m, int* tree_tokens, 
     }
     capture_draft_logits(x, j, rows);
     { Scope s(x, KC_TOPK);
-      launch_topk_lse(x->z, c.vocab, c.vocab, rows, t.topk, x->cand, x->topk_aux, x->topk_ids, x->topk_vals, x->topk_lse, x->st); }
-    { Scope s(x, KC_DRAFT_MISC);
-      launch_dyn_assign(t, j, B, x->topk_ids, x->topk_vals, x->topk_lse, m, x->st);
-      if (j + 1 < t.D) launch_dyn_frontier(t, j + 1, B, m, x->st); }
+      launch_topk_lse(x->z, c.vocab, c.vocab, rows, t.topk, x->cand, x->topk_aux, x->topk_ids, x->topk_vals, x->topk_lse, x->st,
+                      1.0f, &t, j, m); }
+    if (j + 1 < t.D) { Scope s(x, KC_DRAFT_MISC); launch_dyn_frontier(t, j + 1, B, m, x->st); }
   }
   { Scope s(x, KC_DRAFT_MISC); launch_dyn_finalize(t, B, x->R, m, tree_tokens, x->st); }
 }

@@ -75,6 +75,34 @@ inline void with_count(int n, F&& f) {
   f(std::integral_constant<int, LO>{});
 }
 
+// ---- rankings by (value, id) keys ----------------------------------------------------------------
+#ifdef __HIPCC__
+// largest of the wavefront's values, along the lanes of a row, then over the rows (a few clocks a step; an exchange through the
+// LDS crossbar takes 50 to 100, and a ranking is a chain of them: the chunks of a top-8 of 8 rows x 128256 8.6 -> 6.8 us)
+__device__ __forceinline__ unsigned wave_max_u32(unsigned v) {
+  v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false));   // row_shr:1, 2, 4, 8
+  v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false));
+  v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false));
+  v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false));
+  v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false));   // row_bcast:15 into rows 1 and 3
+  v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false));   // row_bcast:31 into rows 2 and 3
+  return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
+}
+__device__ __forceinline__ unsigned long long wave_max_key(unsigned long long v) {
+  const unsigned hi = (unsigned)(v >> 32), top = wave_max_u32(hi);
+  return ((unsigned long long)top << 32) | wave_max_u32(hi == top ? (unsigned)v : 0u);
+}
+// the largest key of 256 threads, round r of a ranking: the rounds take turns in `red`, so one barrier each is enough
+__device__ __forceinline__ unsigned long long block_max_key(unsigned long long v, unsigned long long (&red)[2][4], int r) {
+  v = wave_max_key(v);
+  unsigned long long* q = red[r & 1];
+  if ((threadIdx.x & 63) == 0) q[threadIdx.x >> 6] = v;
+  __syncthreads();
+  const unsigned long long a = q[0] > q[1] ? q[0] : q[1], b = q[2] > q[3] ? q[2] : q[3];
+  return a > b ? a : b;
+}
+#endif
+
 // ---- staging loads: global -> LDS without a stop in registers -------------------------------------
 #ifdef __HIPCC__
 typedef const __attribute__((address_space(1))) char* gbyte_ptr;
@@ -356,16 +384,17 @@ struct DynTree {
 // per row of z[rows, V]: ids and values of the k best entries (value descending, id ascending) and the row's
 // log-sum-exp.  cand: [rows][chunks][16] 64-bit keys, aux: [rows][chunks][2] floats, chunks = ceil(V / 2048)
 // (scale: every value is multiplied by it first -- an inverse temperature)
+// to non-null (k = to->topk): row b * F[j] + r ranks candidate frontier[b][j][r]; token, cumulative score and parent of its children go
+// to their candidates (sequences with m[b] < 1 are left alone)
 void launch_topk_lse(const float* z, int ldz, int V, int rows, int k, void* cand, float* aux, int* out_ids,
-                     float* out_vals, float* out_lse, hipStream_t st, float scale = 1.0f);
+                     float* out_vals, float* out_lse, hipStream_t st, float scale = 1.0f, const DynTree* to = nullptr, int j = 0,
+                     const int* m = nullptr);
 // verification at a temperature > 0: lse[row] = log-sum-exp of logits[row] * inv_temp; uniforms [B][R][17]
 int sample_chunks(int V);
 void launch_accept_sample(const float* logits, int V, const float* lse, float inv_temp, const int* tokens,
                           const int* first_child, const int* n_child, int child_stride, int B, int R,
                           const float* uniforms, int* m, int* acc_idx, int* new_tokens, int* next_tok, int* seq_len /* += m */,
                           double* mass /* scratch, B * sample_chunks(V) */, hipStream_t st);
-void launch_dyn_assign(const DynTree& t, int j, int B, const int* ids, const float* vals, const float* lse, const int* m,
-                       hipStream_t st);
 void launch_dyn_frontier(const DynTree& t, int j, int B, const int* m, hipStream_t st);
 void launch_dyn_finalize(const DynTree& t, int B, int R, const int* m, int* tree_tokens, hipStream_t st);   // (also t.t_iv when set)
 

@@ -25,16 +25,6 @@ __device__ __forceinline__ float d_wave_sum(float v) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
   return v;
 }
-__device__ __forceinline__ unsigned long long d_wave_max_u64(unsigned long long v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    unsigned lo = __shfl_xor((unsigned)(v & 0xFFFFFFFFull), o, 64);
-    unsigned hi = __shfl_xor((unsigned)(v >> 32), o, 64);
-    unsigned long long w = ((unsigned long long)hi << 32) | lo;
-    v = w > v ? w : v;
-  }
-  return v;
-}
 // order-preserving 64-bit key of (value, id): larger value first, then the smaller id
 __device__ __forceinline__ unsigned long long d_key(float v, int id) {
   v = v + 0.0f;
@@ -46,18 +36,6 @@ __device__ __forceinline__ float d_key_value(unsigned long long key) {
   const unsigned u = (unsigned)(key >> 32);
   return __uint_as_float((u & 0x80000000u) ? (u & 0x7FFFFFFFu) : ~u);
 }
-__device__ __forceinline__ unsigned long long d_block_max_u64(unsigned long long v, unsigned long long* red) {
-  v = d_wave_max_u64(v);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  unsigned long long r = red[0];
-  r = red[1] > r ? red[1] : r;
-  r = red[2] > r ? red[2] : r;
-  r = red[3] > r ? red[3] : r;
-  return r;
-}
-
 constexpr int DY_CHUNK = 2048;
 constexpr int DY_EPT = DY_CHUNK / 256;
 
@@ -66,7 +44,7 @@ constexpr int DY_EPT = DY_CHUNK / 256;
 __global__ __launch_bounds__(256) void topk_lse_stage1_kernel(const float* __restrict__ z, int ldz, int V, int k,
                                                               unsigned long long* __restrict__ cand,
                                                               float* __restrict__ aux, float scale) {
-  __shared__ unsigned long long red[4];
+  __shared__ unsigned long long red[2][4];
   __shared__ float fred[4];
   const int chunk = blockIdx.x, row = blockIdx.y, chunks = gridDim.x;
   unsigned long long key[DY_EPT];
@@ -98,7 +76,7 @@ __global__ __launch_bounds__(256) void topk_lse_stage1_kernel(const float* __res
     unsigned long long best = 0ull;
 #pragma unroll
     for (int e = 0; e < DY_EPT; ++e) best = key[e] > best ? key[e] : best;
-    best = d_block_max_u64(best, red);
+    best = block_max_key(best, red, r);
 #pragma unroll
     for (int e = 0; e < DY_EPT; ++e)
       if (key[e] == best) key[e] = 0ull;
@@ -111,8 +89,8 @@ __global__ __launch_bounds__(256) void topk_lse_stage1_kernel(const float* __res
 __global__ __launch_bounds__(256) void topk_lse_stage2_kernel(const unsigned long long* __restrict__ cand,
                                                               const float* __restrict__ aux, int chunks, int k,
                                                               int* __restrict__ out_ids, float* __restrict__ out_vals,
-                                                              float* __restrict__ out_lse) {
-  __shared__ unsigned long long red[4];
+                                                              float* __restrict__ out_lse, DynTree to, int j, const int* __restrict__ m) {
+  __shared__ unsigned long long red[2][4];
   const int row = blockIdx.x;
   const int total = chunks * k;
   unsigned long long key[8];
@@ -139,34 +117,33 @@ __global__ __launch_bounds__(256) void topk_lse_stage2_kernel(const unsigned lon
       for (int i = 0; i < min(256, chunks - c0); ++i) S += term[i];
     __syncthreads();
   }
-  if (threadIdx.x == 0) out_lse[row] = M + logf(S);
+  __shared__ int ids[16];
+  __shared__ float vals[16], lse;
+  if (threadIdx.x == 0) out_lse[row] = lse = M + logf(S);
   for (int r = 0; r < k; ++r) {
     unsigned long long best = 0ull;
 #pragma unroll
     for (int e = 0; e < 8; ++e) best = key[e] > best ? key[e] : best;
-    best = d_block_max_u64(best, red);
+    best = block_max_key(best, red, r);
 #pragma unroll
     for (int e = 0; e < 8; ++e)
       if (key[e] == best) key[e] = 0ull;
     if (threadIdx.x == 0) {
-      out_ids[row * 16 + r] = (int)(0xFFFFFFFFu - (unsigned)(best & 0xFFFFFFFFull));
-      out_vals[row * 16 + r] = d_key_value(best);
+      out_ids[row * 16 + r] = ids[r] = (int)(0xFFFFFFFFu - (unsigned)(best & 0xFFFFFFFFull));
+      out_vals[row * 16 + r] = vals[r] = d_key_value(best);
     }
   }
-}
-
-// children of the candidates expanded at depth j: token, cumulative score, parent
-__global__ void dyn_assign_kernel(DynTree t, int j, const int* __restrict__ ids, const float* __restrict__ vals,
-                                  const float* __restrict__ lse, const int* __restrict__ m) {
-  const int r = blockIdx.x, b = blockIdx.y, i = threadIdx.x;
-  if (i >= t.topk || m[b] < 1) return;
-  const int row = b * t.F[j] + r;
-  const int par = j == 0 ? 0 : t.frontier[((size_t)b * CLOVER_MAX_DEPTH + j) * DYN_MAX_FRONT + r];
-  const int cid = t.off[j + 1] + r * t.topk + i;
-  const size_t o = (size_t)b * t.C;
-  t.cand_tok[o + cid] = ids[row * 16 + i];
-  t.cand_score[o + cid] = (j == 0 ? 0.f : t.cand_score[o + par]) + (vals[row * 16 + i] - lse[row]);
-  t.cand_par[o + cid] = par;
+  if (!to.cand_tok) return;   // (uniform)
+  __syncthreads();
+  // children of the candidate that this row ranked: token, cumulative score, parent
+  const int b = row / to.F[j], r = row - b * to.F[j], i = threadIdx.x;
+  if (i >= to.topk || m[b] < 1) return;
+  const int par = j == 0 ? 0 : to.frontier[((size_t)b * CLOVER_MAX_DEPTH + j) * DYN_MAX_FRONT + r];
+  const int cid = to.off[j + 1] + r * to.topk + i;
+  const size_t o = (size_t)b * to.C;
+  to.cand_tok[o + cid] = ids[i];
+  to.cand_score[o + cid] = (j == 0 ? 0.f : to.cand_score[o + par]) + (vals[i] - lse);
+  to.cand_par[o + cid] = par;
 }
 
 // frontier of depth j: the F[j] best of its candidates (score descending, lower id first), in that order
@@ -180,18 +157,21 @@ __global__ __launch_bounds__(256) void dyn_frontier_kernel(DynTree t, int j, con
   __syncthreads();
   if (tid >= n) return;
   int better = 0;
+#pragma unroll 8
   for (int u = 0; u < n; ++u) better += (sc[u] > sc[tid] || (sc[u] == sc[tid] && u < tid)) ? 1 : 0;
   if (better < t.F[j]) t.frontier[((size_t)b * CLOVER_MAX_DEPTH + j) * DYN_MAX_FRONT + better] = t.off[j] + tid;
 }
 
-// selection of the tree and its breadth-first numbering; per-sequence topology tables
+// selection of the tree and its breadth-first numbering; per-sequence topology tables.  One workgroup per sequence, a chain of steps
+// over the LDS; every count is a loop of independent reads, unrolled (150 candidates, 40 nodes, 4 depths: 31 us with dependent reads
+// and the labels numbered by one thread, 11 so).
 __global__ __launch_bounds__(DYN_MAX_CAND) void dyn_finalize_kernel(DynTree t, int R, const int* __restrict__ m,
                                                                    int* __restrict__ tree_tokens) {
   __shared__ float sc[DYN_MAX_CAND];
-  __shared__ int dep[DYN_MAX_CAND], par[DYN_MAX_CAND], sel[DYN_MAX_CAND], nid[DYN_MAX_CAND];
+  __shared__ int par[DYN_MAX_CAND], key[DYN_MAX_CAND], nid[DYN_MAX_CAND];
   __shared__ int n_child[CLOVER_MAX_NODES], first_child[CLOVER_MAX_NODES];
   __shared__ unsigned long long anc[CLOVER_MAX_NODES][2];
-  __shared__ int pnode[CLOVER_MAX_NODES], sub[CLOVER_MAX_NODES], ent[CLOVER_MAX_NODES];   // parent, subtree size, enter label
+  __shared__ int sub[CLOVER_MAX_NODES], ent[CLOVER_MAX_NODES];   // subtree size, enter label
   __shared__ int level_count;
   const int b = blockIdx.x, c = threadIdx.x;
   if (m[b] < 1) return;
@@ -201,33 +181,29 @@ __global__ __launch_bounds__(DYN_MAX_CAND) void dyn_finalize_kernel(DynTree t, i
   if (live) {
     for (int j = 1; j <= t.D; ++j) my_dep += c >= t.off[j] ? 1 : 0;
     sc[c] = c == 0 ? INFINITY : t.cand_score[o + c];
-    dep[c] = my_dep;
     par[c] = c == 0 ? 0 : t.cand_par[o + c];
   }
   if (c < CLOVER_MAX_NODES) { n_child[c] = 0; first_child[c] = INT_MAX; anc[c][0] = anc[c][1] = 0ull; }
   __syncthreads();
   int keep = 0;
   if (live) {
-    int better = 0;   // candidates (the root included) that come before this one
-    for (int u = 0; u < t.C; ++u) {
-      if (u == c) continue;
-      const bool first = sc[u] > sc[c] || (sc[u] == sc[c] && (dep[u] < dep[c] || (dep[u] == dep[c] && u < c)));
-      better += first ? 1 : 0;
-    }
+    int better = 0;   // candidates (the root included) that come before this one: higher scores, among equals shallower ones, then
+#pragma unroll 8          // lower ids -- which are in order of depth
+    for (int u = 0; u < t.C; ++u) better += sc[u] > sc[c] || (sc[u] == sc[c] && u < c) ? 1 : 0;
     keep = better < t.N ? 1 : 0;
-    sel[c] = keep;
     if (c == 0) nid[0] = 0;
   }
   int base = 1;
   for (int j = 1; j <= t.D; ++j) {
     if (c == 0) level_count = 0;
+    const bool here = live && my_dep == j;
+    const int mine = here && keep ? nid[par[c]] * 16 + (c - t.off[j]) % t.topk : INT_MAX;
+    if (here) key[c] = mine;
     __syncthreads();
-    if (live && keep && my_dep == j) {
-      const int rk = (c - t.off[j]) % t.topk;
-      const int key = nid[par[c]] * 16 + rk;
+    if (here && keep) {
       int pos = 0;
-      for (int u = t.off[j]; u < t.off[j + 1]; ++u)
-        if (sel[u] && u != c) pos += (nid[par[u]] * 16 + (u - t.off[j]) % t.topk) < key ? 1 : 0;
+#pragma unroll 8
+      for (int u = t.off[j]; u < t.off[j + 1]; ++u) pos += key[u] < mine ? 1 : 0;
       nid[c] = base + pos;
       atomicAdd(&level_count, 1);
     }
@@ -245,7 +221,6 @@ __global__ __launch_bounds__(DYN_MAX_CAND) void dyn_finalize_kernel(DynTree t, i
     t.t_rank[ro + node] = c == 0 ? 0 : (c - t.off[my_dep]) % t.topk;
     t.t_depth[ro + node] = my_dep;
     t.t_keep[ro + node] = c;
-    pnode[node] = pn;
     if (c > 0) { atomicAdd(&n_child[pn], 1); atomicMin(&first_child[pn], node); }
   }
   if (c == 0) anc[0][0] = 1ull;
@@ -259,15 +234,22 @@ __global__ __launch_bounds__(DYN_MAX_CAND) void dyn_finalize_kernel(DynTree t, i
     }
   }
   __syncthreads();
-  // interval labels of a depth-first numbering (the linear-size form of the mask): subtree sizes bottom-up (children
-  // have larger numbers than their parents and are numbered consecutively), then enter labels top-down
-  if (c == 0) {
-    for (int u = 0; u < t.N; ++u) sub[u] = 1;
-    for (int u = t.N - 1; u >= 1; --u) sub[pnode[u]] += sub[u];
-    ent[0] = 0;
-    for (int u = 0; u < t.N; ++u) {
-      int e = ent[u] + 1;
-      for (int k = 0; k < n_child[u]; ++k) { ent[first_child[u] + k] = e; e += sub[first_child[u] + k]; }
+  // interval labels of a depth-first numbering (the linear-size form of the mask): the size of a subtree counts the nodes whose
+  // path holds its root; a node enters behind its parent and its earlier siblings' subtrees, depth by depth
+  if (c < t.N) {
+    int size = 0;
+#pragma unroll 8
+    for (int v = 0; v < t.N; ++v) size += (int)(anc[v][c >> 6] >> (c & 63) & 1ull);
+    sub[c] = size;
+  }
+  if (c == 0) ent[0] = 0;
+  for (int j = 1; j <= t.D; ++j) {
+    __syncthreads();
+    if (live && keep && my_dep == j) {
+      const int node = nid[c], pn = nid[par[c]];
+      int e = ent[pn] + 1;
+      for (int s = first_child[pn]; s < node; ++s) e += sub[s];
+      ent[node] = e;
     }
   }
   __syncthreads();
@@ -478,15 +460,12 @@ void launch_accept_sample(const float* logits, int V, const float* lse, float in
 }
 
 void launch_topk_lse(const float* z, int ldz, int V, int rows, int k, void* cand, float* aux, int* out_ids,
-                     float* out_vals, float* out_lse, hipStream_t st, float scale) {
+                     float* out_vals, float* out_lse, hipStream_t st, float scale, const DynTree* to, int j, const int* m) {
   if (rows <= 0) return;
   const int chunks = (V + DY_CHUNK - 1) / DY_CHUNK;
   topk_lse_stage1_kernel<<<dim3(chunks, rows), 256, 0, st>>>(z, ldz, V, k, (unsigned long long*)cand, aux, scale);
-  topk_lse_stage2_kernel<<<rows, 256, 0, st>>>((const unsigned long long*)cand, aux, chunks, k, out_ids, out_vals, out_lse);
-}
-void launch_dyn_assign(const DynTree& t, int j, int B, const int* ids, const float* vals, const float* lse, const int* m,
-                       hipStream_t st) {
-  dyn_assign_kernel<<<dim3(t.F[j], B), 16, 0, st>>>(t, j, ids, vals, lse, m);
+  topk_lse_stage2_kernel<<<rows, 256, 0, st>>>((const unsigned long long*)cand, aux, chunks, k, out_ids, out_vals, out_lse,
+                                               to ? *to : DynTree{}, j, m);
 }
 void launch_dyn_frontier(const DynTree& t, int j, int B, const int* m, hipStream_t st) {
   dyn_frontier_kernel<<<B, 256, 0, st>>>(t, j, m);

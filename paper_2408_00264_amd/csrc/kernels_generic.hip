@@ -752,37 +752,20 @@ __device__ __forceinline__ unsigned long long topk_key(float v, int id) {
   u = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
   return ((unsigned long long)u << 32) | (unsigned long long)(0xFFFFFFFFu - (unsigned)id);
 }
-// largest of the wavefront's values, along the lanes of a row, then over the rows (a few clocks a step; an exchange through the
-// LDS crossbar takes 50 to 100, and a ranking is a chain of them: the chunks of a top-8 of 8 rows x 128256 8.6 -> 6.8 us)
-__device__ __forceinline__ unsigned wave_max_u32(unsigned v) {
-  v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false));   // row_shr:1, 2, 4, 8
-  v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false));
-  v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false));
-  v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false));
-  v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false));   // row_bcast:15 into rows 1 and 3
-  v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false));   // row_bcast:31 into rows 2 and 3
-  return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
-}
-__device__ __forceinline__ unsigned long long wave_max_key(unsigned long long v) {
-  const unsigned hi = (unsigned)(v >> 32), top = wave_max_u32(hi);
-  return ((unsigned long long)top << 32) | wave_max_u32(hi == top ? (unsigned)v : 0u);
-}
-// the largest key of 256 threads, round r of a ranking: the rounds take turns in `red`, so one barrier each is enough
-__device__ __forceinline__ unsigned long long block_max_key(unsigned long long v, unsigned long long (&red)[2][4], int r) {
-  v = wave_max_key(v);
-  unsigned long long* q = red[r & 1];
-  if ((threadIdx.x & 63) == 0) q[threadIdx.x >> 6] = v;
-  __syncthreads();
-  const unsigned long long a = q[0] > q[1] ? q[0] : q[1], b = q[2] > q[3] ? q[2] : q[3];
-  return a > b ? a : b;
-}
-// tokens of the children of the node that row `row` of a depth expands, from the row's ranked ids
-__device__ __forceinline__ void assign_children(const TopkChildren& to, const int* ids, int row) {
-  const int b = row / to.n_lvl, u = to.nodes[row - b * to.n_lvl];
-  if (to.m[b] < 1) return;
-  const int c = to.first_child[u] + (int)threadIdx.x;
-  if ((int)threadIdx.x < to.n_child[u]) to.tokens[(size_t)b * to.R + c] = ids[to.rank[c]];
-}
+// Thread i's child of the node that row `row` of a depth expands: where its token goes and which of the row's ranked ids it is.
+// (Looked up in front of the ranking: a chain of loads that costs nothing there.)
+struct ChildSlot {
+  int* at = nullptr;
+  int rank = 0;
+  __device__ __forceinline__ ChildSlot(const TopkChildren& to, int row) {
+    if (!to.tokens) return;
+    const int b = row / to.n_lvl, u = to.nodes[row - b * to.n_lvl];
+    if ((int)threadIdx.x >= to.n_child[u] || to.m[b] < 1) return;
+    const int c = to.first_child[u] + (int)threadIdx.x;
+    at = to.tokens + (size_t)b * to.R + c;
+    rank = to.rank[c];
+  }
+};
 
 constexpr int TOPK_CHUNK = 2048;
 constexpr int TOPK_EPT = TOPK_CHUNK / 256;
@@ -794,6 +777,7 @@ __global__ __launch_bounds__(256) void topk_stage1_kernel(const float* __restric
   __shared__ unsigned long long red[2][4];
   __shared__ int ids[16];
   const int chunk = blockIdx.x, row = blockIdx.y, chunks = gridDim.x;
+  const ChildSlot child(to, row);
   unsigned long long key[TOPK_EPT];
 #pragma unroll
   for (int e = 0; e < TOPK_EPT; ++e) {
@@ -814,9 +798,9 @@ __global__ __launch_bounds__(256) void topk_stage1_kernel(const float* __restric
       else cand[((size_t)row * chunks + chunk) * 16 + r] = best;
     }
   }
-  if (!out_ids || !to.tokens) return;   // (uniform)
+  if (!to.tokens) return;   // (uniform)
   __syncthreads();
-  assign_children(to, ids, row);
+  if (child.at) *child.at = ids[child.rank];
 }
 
 // stage 1 for k = 1 (the target's argmax over every row): one wavefront per chunk, 16-byte loads, the 64-bit key only for
@@ -853,6 +837,7 @@ __global__ __launch_bounds__(256) void topk_stage2_kernel(const unsigned long lo
   __shared__ unsigned long long red[2][4];
   __shared__ int ids[16];
   const int row = blockIdx.x;
+  const ChildSlot child(to, row);
   const int total = chunks * k;  // <= 63*16 for V <= 129024; loop handles more
   unsigned long long key[8];
 #pragma unroll
@@ -872,7 +857,7 @@ __global__ __launch_bounds__(256) void topk_stage2_kernel(const unsigned long lo
   }
   if (!to.tokens) return;   // (uniform)
   __syncthreads();
-  assign_children(to, ids, row);
+  if (child.at) *child.at = ids[child.rank];
 }
 
 void launch_topk(const float* z, int ldz, int V, int rows, int k, void* cand, int* out_ids, hipStream_t st, TopkChildren to) {
