@@ -145,7 +145,8 @@ __global__ __launch_bounds__(64 * G * WM) void attn_mfma_kernel(AttnParams p) {
   auto stage_v = [&](int buf, int page) __attribute__((always_inline)) { stage(p.v, page, AT_NKB * AT_KSTAGE + buf * AT_VSTAGE); };
   // ---- Q fragments (already scaled and split by the RoPE kernel) and masks: requested in front of the first tiles, which are
   // not in any cache and would hold them up (loads return in order), and before the lengths are known.  Rows behind the last
-  // node read some row's and are multiplied along; their results are never stored.
+  // node read some row's, or what an earlier call left there, and are multiplied along; their results are never stored and
+  // `limit` does not ask them.
   Frag qh[MB][4], ql[MB][4];
   unsigned long long a0[MB], a1[MB];
   int my_enter[MB];
@@ -181,6 +182,9 @@ __global__ __launch_bounds__(64 * G * WM) void attn_mfma_kernel(AttnParams p) {
   if (p.iv)
     for (int w = tid; w < nv; w += NT) kiv[w] = *(const int2*)(p.iv + 2 * ((size_t)b * p.anc_stride + w));
   const bool work = __builtin_amdgcn_readfirstlane(node0) < nv;   // (a wavefront without nodes only helps with the staging)
+  unsigned long long valid[MB];   // lanes whose row is a node
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb) valid[mb] = __builtin_amdgcn_ballot_w64(node0 + mb * 16 + l16 < nv);
   const int open = L + (chain ? ng * NODES : 0);
   const int n_tiles = ((chain ? min(total, L + ng * NODES + NODES) : total) + AT_TK - 1) / AT_TK;
   const int n = min(n_tiles, t0 + p.plan.tiles) - t0;   // tiles of this split (<= 0: none)
@@ -248,8 +252,7 @@ __global__ __launch_bounds__(64 * G * WM) void attn_mfma_kernel(AttnParams p) {
     }
   };
   auto limit = [&](int t, f32x4 (&sc)[2][MB]) __attribute__((always_inline)) {
-    // Uniform: some key of the tile may be hidden from some row (keys in front of `open` are visible to every row).  Rows past
-    // the last node are multiplied along, their results are never stored.
+    // Uniform: some key of the tile may be hidden from some row (keys in front of `open` are visible to every row).
     if ((t + 1) * AT_TK > open) {
       const int w0 = t * AT_TK + 8 * g4 - L;   // the lane's keys are slots L + w0 .. + 7: new rows w0 .. where not negative
 #pragma unroll
@@ -278,16 +281,18 @@ __global__ __launch_bounds__(64 * G * WM) void attn_mfma_kernel(AttnParams p) {
     // The reference moves only when some score exceeds it by a factor of 2^AT_SLACK (the first visible scores exceed "none"):
     // probabilities up to that factor above one are as exact in floating point as those below one, and the exchange between
     // the lanes of a row and the rescaling drop out of nearly every tile.
+    // Rows behind the last node have no say: what an earlier call left in them would decide when the valid rows beside them are
+    // rescaled, and with that their last bits.
     float tmax[MB];
-    bool above = false;
+    unsigned long long above = 0ull;
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
       tmax[mb] = sc[0][mb][0];
 #pragma unroll
       for (int e = 1; e < 8; ++e) tmax[mb] = fmaxf(tmax[mb], sc[e >> 2][mb][e & 3]);
-      above = above || tmax[mb] * LOG2E > m2[mb] + AT_SLACK;
+      above |= __builtin_amdgcn_ballot_w64(tmax[mb] * LOG2E > m2[mb] + AT_SLACK) & valid[mb];
     }
-    if (__builtin_amdgcn_ballot_w64(above) != 0ull) {
+    if (above != 0ull) {
 #pragma unroll
       for (int mb = 0; mb < MB; ++mb) {
         float t2 = fmaxf(tmax[mb], __shfl_xor(tmax[mb], 16, 64));
