@@ -184,6 +184,7 @@ __global__ __launch_bounds__(DYN_MAX_CAND) void dyn_finalize_kernel(DynTree t, i
     par[c] = c == 0 ? 0 : t.cand_par[o + c];
   }
   if (c < CLOVER_MAX_NODES) { n_child[c] = 0; first_child[c] = INT_MAX; anc[c][0] = anc[c][1] = 0ull; }
+  if (c == 0) nid[0] = 0;   // (read by other threads in front of the next barrier)
   __syncthreads();
   int keep = 0;
   if (live) {
@@ -191,7 +192,6 @@ __global__ __launch_bounds__(DYN_MAX_CAND) void dyn_finalize_kernel(DynTree t, i
 #pragma unroll 8          // lower ids -- which are in order of depth
     for (int u = 0; u < t.C; ++u) better += sc[u] > sc[c] || (sc[u] == sc[c] && u < c) ? 1 : 0;
     keep = better < t.N ? 1 : 0;
-    if (c == 0) nid[0] = 0;
   }
   int base = 1;
   for (int j = 1; j <= t.D; ++j) {
