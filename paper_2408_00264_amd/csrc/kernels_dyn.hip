@@ -146,6 +146,10 @@ __global__ __launch_bounds__(256) void topk_lse_stage2_kernel(const unsigned lon
   to.cand_par[o + cid] = par;
 }
 
+// A score that is no number (its logits were none, or infinite) ranks as minus infinity: every candidate then has a place of its
+// own in the order, behind its parent, and no more candidates are kept than there are nodes.
+__device__ __forceinline__ float rank_score(float s) { return s == s ? s : -INFINITY; }
+
 // frontier of depth j: the F[j] best of its candidates (score descending, lower id first), in that order
 __global__ __launch_bounds__(256) void dyn_frontier_kernel(DynTree t, int j, const int* __restrict__ m) {
   __shared__ float sc[DYN_MAX_CAND];
@@ -153,7 +157,7 @@ __global__ __launch_bounds__(256) void dyn_frontier_kernel(DynTree t, int j, con
   if (m[b] < 1) return;
   const int n = t.off[j + 1] - t.off[j];
   const size_t o = (size_t)b * t.C;
-  if (tid < n) sc[tid] = t.cand_score[o + t.off[j] + tid];
+  if (tid < n) sc[tid] = rank_score(t.cand_score[o + t.off[j] + tid]);
   __syncthreads();
   if (tid >= n) return;
   int better = 0;
@@ -180,7 +184,7 @@ __global__ __launch_bounds__(DYN_MAX_CAND) void dyn_finalize_kernel(DynTree t, i
   int my_dep = 0;
   if (live) {
     for (int j = 1; j <= t.D; ++j) my_dep += c >= t.off[j] ? 1 : 0;
-    sc[c] = c == 0 ? INFINITY : t.cand_score[o + c];
+    sc[c] = c == 0 ? INFINITY : rank_score(t.cand_score[o + c]);
     par[c] = c == 0 ? 0 : t.cand_par[o + c];
   }
   if (c < CLOVER_MAX_NODES) { n_child[c] = 0; first_child[c] = INT_MAX; anc[c][0] = anc[c][1] = 0ull; }

@@ -11,6 +11,8 @@
 #include <ucontext.h>
 
 #define __global__ static
+#define __device__ static
+#define __forceinline__ inline
 #define __launch_bounds__(n)
 
 struct Index { int x, y, z; };

@@ -53,7 +53,7 @@ def run(tmp_path_factory):
     src = open(os.path.join(ROOT, "paper_2408_00264_amd", "csrc", "kernels_dyn.hip")).read()
     head = open(os.path.join(ROOT, "paper_2408_00264_amd", "csrc", "clover_internal.h")).read()
     kernels = [re.search(r"^__global__ [^\n]*void %s\(.*?^}" % name, src, re.S | re.M)[0] for name in ("dyn_frontier_kernel", "dyn_finalize_kernel")]
-    text = re.search(r"^struct DynTree \{.*?^\};", head, re.S | re.M)[0] + "\n" + "\n".join(kernels)
+    text = re.search(r"^struct DynTree \{.*?^\};", head, re.S | re.M)[0] + "\n" + re.search(r"^__device__ [^\n]*rank_score.*", src, re.M)[0] + "\n" + "\n".join(kernels)
 
     def shared(d):                                      # __shared__ T a[N], b[N][M], c;
         names = [re.fullmatch(r"\s*(\w+)((?:\[[^\]]+\])*)\s*", part) for part in d[2].split(",")]
@@ -129,7 +129,9 @@ def _expected(off, par, sc, topk, D, N):
 SHAPES = [(4, 3, 3, 16), (16, 1, 8, 100), (8, 8, 4, 64), (1, 1, 1, 2), (16, 16, 1, 1), (2, 64, 7, 128), (10, 6, 5, 128)]
 SCORES = {"spread": lambda rng: lambda p: p - rng.random() * 4,
           "ties": lambda rng: lambda p: p - rng.randrange(2),
-          "minus infinity": lambda rng: lambda p: p - rng.choice([1.0, math.inf])}
+          "minus infinity": lambda rng: lambda p: p - rng.choice([1.0, math.inf]),
+          "some no number": lambda rng: lambda p: rng.choice([p - rng.random(), math.nan]),
+          "no number": lambda rng: lambda p: math.nan}
 
 
 @pytest.mark.parametrize("kind", SCORES)
