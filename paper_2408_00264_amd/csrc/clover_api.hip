@@ -919,6 +919,9 @@ int clover_init(const clover_config* cfg, const clover_weights* w, const clover_
   launch_fill_i32(x->d_seq_len, 0, cfg->max_batch, x->st);
   launch_fill_i32(x->d_aug_len, 0, cfg->max_batch, x->st);
   launch_fill_i32(x->d_err, 0, 1, x->st);
+  // A draft call leaves a skipped sequence's dynamic tables alone, but its rows are computed along and index by them: candidate 0
+  // and a root without children until a call fills them in.
+  launch_fill_i32(x->dyn.cand_tok, 0, (int)(x->dyn.t_iv + 2 * x->step.rows - x->dyn.cand_tok), x->st);
   if (x->fast) {
     // the MFMA attention multiplies masked probabilities (exact zeros) with whatever the cache rows of a
     // tile hold, so the caches must never contain non-finite garbage
