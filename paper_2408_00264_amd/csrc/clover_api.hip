@@ -8,6 +8,7 @@
 #include <cstdio>
 #include <cstring>
 #include <string>
+#include <utility>
 #include <vector>
 
 using namespace clv;
@@ -797,6 +798,7 @@ int upload_tree(clover_ctx* x) {
 }
 
 int finish(clover_ctx* x, const char* what) {
+  if (const char* why = std::exchange(g_not_launched, nullptr)) return fail(x, CLOVER_E_STATE, std::string(what) + ": " + why);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(x, CLOVER_E_HIP, std::string(what) + ": " + hipGetErrorString(e));
   return CLOVER_OK;

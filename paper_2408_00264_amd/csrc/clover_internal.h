@@ -67,12 +67,16 @@ __device__ __forceinline__ size_t kv_v_at(const KVLayout& kv, int b, int head, i
 #endif
 
 // ---- launch helper -----------------------------------------------------------------------------
-// f(integral constant n) for n in LO .. HI: a kernel's loads of n partial results are counted at compile time
+// what a launcher of this thread could not launch, until the entry point that called it reports it (null: nothing)
+inline thread_local const char* g_not_launched = nullptr;
+// f(integral constant n) for n in LO .. HI: a kernel's loads of n partial results are counted at compile time.  Another count is
+// not rounded to one of these -- the kernel would leave out ranges or add what nothing wrote: nothing is launched and the call fails.
 template <int LO, int HI, class F>
 inline void with_count(int n, F&& f) {
+  if (n == LO) return f(std::integral_constant<int, LO>{});
   if constexpr (LO < HI)
     if (n > LO) return with_count<LO + 1, HI>(n, f);
-  f(std::integral_constant<int, LO>{});
+  g_not_launched = "no kernel for this count of partial results";
 }
 
 // ---- rankings by (value, id) keys ----------------------------------------------------------------
