@@ -336,6 +336,9 @@ int clover_op_swiglu(const float *X, const void *Wg, const void *Wu, void *plane
  * k_parts is a count the kernel takes. */
 int clover_op_gemm_form(int32_t epi, int32_t M, int32_t N, int32_t K, int32_t k_parts, int32_t form[5]);
 
+/* Host only: columns of the launch's tile, exactly (form[1] rounds 112 up to 4 x 32).  Arguments and errors as above. */
+int clover_op_gemm_tile_columns(int32_t epi, int32_t M, int32_t N, int32_t K, int32_t k_parts, int32_t *columns);
+
 #ifdef __cplusplus
 }
 #endif

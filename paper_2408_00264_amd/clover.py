@@ -27,7 +27,7 @@ EXPORTS = [
     "clover_read_kv", "clover_write_kv", "clover_set_seq_len", "clover_capture_draft_logits", "clover_set_dynamic_tree", "clover_read_dynamic_tree", "clover_path_info", "clover_profile_enable", "clover_profile_collect", "clover_kernel_class_count",
     "clover_kernel_class_name", "clover_last_error", "clover_last_global_error",
     "clover_op_gemm_scratch_bytes", "clover_op_gemm", "clover_op_gemm_static",
-    "clover_op_swiglu_scratch_bytes", "clover_op_swiglu", "clover_op_gemm_form",
+    "clover_op_swiglu_scratch_bytes", "clover_op_swiglu", "clover_op_gemm_form", "clover_op_gemm_tile_columns",
 ]
 
 
@@ -105,7 +105,8 @@ def load_library(path: Optional[str] = None) -> C.CDLL:
     lib.clover_op_swiglu_scratch_bytes.argtypes = [i32, i32, i32]
     lib.clover_op_swiglu_scratch_bytes.restype = C.c_size_t
     lib.clover_op_swiglu.argtypes = [vp, vp, vp, vp, i32, i32, i32, vp, C.c_size_t, vp]
-    lib.clover_op_gemm_form.argtypes = [i32, i32, i32, i32, i32, C.POINTER(C.c_int32)]
+    for f in (lib.clover_op_gemm_form, lib.clover_op_gemm_tile_columns):
+        f.argtypes = [i32, i32, i32, i32, i32, C.POINTER(C.c_int32)]
     lib.clover_op_gemm_static.argtypes = [i32, i32, vp, vp, vp, i32, i32, i32, i32, vp]
     for n in EXPORTS:
         getattr(lib, n)  # every declared symbol must be exported

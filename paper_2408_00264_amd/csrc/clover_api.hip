@@ -1534,13 +1534,26 @@ int clover_op_swiglu(const float* X, const void* Wg, const void* Wu, void* plane
   return CLOVER_OK;
 }
 
-int clover_op_gemm_form(int32_t epi, int32_t M, int32_t N, int32_t K, int32_t k_parts, int32_t form[5]) {
-  if (!form) return fail(nullptr, CLOVER_E_NULL, "null argument");
+static int op_gemm_tile(int epi, int M, int N, int K, int k_parts, const int32_t* out, TileForm& f) {
+  if (!out) return fail(nullptr, CLOVER_E_NULL, "null argument");
   if (epi < 0 || epi > 1 || M < 1 || N < 1 || K < 1 || !mfma_shape_ok(N, K) || k_parts < 0 || k_parts > TILE_MAX_K_PARTS ||
       (k_parts > 0 && K / 32 % k_parts != 0) || (epi == 1 && k_parts > 1))
     return fail(nullptr, CLOVER_E_SHAPE, "shape not supported by the MFMA GEMM");
-  const TileForm f = tile_gemm_form(M, N, K, epi, k_parts == 0 && epi == 0 && M <= 256 ? op_gemm_scratch(M, N, K).kp : k_parts);
+  f = tile_gemm_form(M, N, K, epi, k_parts == 0 && epi == 0 && M <= 256 ? op_gemm_scratch(M, N, K).kp : k_parts);
+  return CLOVER_OK;
+}
+int clover_op_gemm_form(int32_t epi, int32_t M, int32_t N, int32_t K, int32_t k_parts, int32_t form[5]) {
+  TileForm f;
+  const int rc = op_gemm_tile(epi, M, N, K, k_parts, form, f);
+  if (rc) return rc;
   form[0] = f.rb; form[1] = (f.wb + 1) / 2; form[2] = f.row_tiles; form[3] = f.k_parts; form[4] = f.stages;
+  return CLOVER_OK;
+}
+int clover_op_gemm_tile_columns(int32_t epi, int32_t M, int32_t N, int32_t K, int32_t k_parts, int32_t* columns) {
+  TileForm f;
+  const int rc = op_gemm_tile(epi, M, N, K, k_parts, columns, f);
+  if (rc) return rc;
+  *columns = 16 * f.wb;
   return CLOVER_OK;
 }
 

@@ -2,8 +2,8 @@
 few-output fp32 kernel at one row, one column, K tails and the tile count where the larger tiles take over.  `PLAIN` and
 `SWIGLU`: every form (tile, one or several row tiles) of the MFMA kernel, each with fewer stages of K than buffers and with
 more, odd stage counts, first and last rows of a row block; the form is asserted, so that another choice by the rule shows.
-(The plain result with RB 5 and several row tiles needs more rows than the operator takes; its loop is that of the SwiGLU
-cases of that form.)"""
+CB counts 32 columns, 3.5 of them are the tiles of seven blocks.  (The plain result with RB 5 and several row tiles needs more
+rows than the operator takes; its loop is that of the SwiGLU cases of that form.)"""
 import ctypes as C
 
 import numpy as np
@@ -60,16 +60,16 @@ def test_gemm_tile_edges(path, dtype, M, N, K):
 
 # (M, N, K, RB, CB, row tiles, stages)
 PLAIN = [
-    (1, 26000, 128, 0, 4, 1, 2), (1, 34704, 128, 0, 6, 1, 2), (1, 16, 128, 1, 3, 1, 4), (17, 26000, 128, 1, 4, 1, 4),
-    (17, 34704, 128, 1, 6, 1, 4), (33, 16, 128, 2, 3, 1, 4), (33, 26000, 128, 2, 4, 1, 4), (33, 34704, 128, 2, 6, 1, 4),
+    (1, 26000, 128, 0, 4, 1, 2), (1, 34704, 128, 0, 6, 1, 2), (1, 16, 128, 1, 3, 1, 4), (17, 26000, 128, 1, 3.5, 1, 4),
+    (17, 34704, 128, 1, 6, 1, 4), (33, 16, 128, 2, 3, 1, 4), (33, 26000, 128, 2, 3.5, 1, 4), (33, 34704, 128, 2, 6, 1, 4),
     (33, 52000, 128, 2, 8, 1, 4), (65, 16, 128, 3, 3, 1, 4), (97, 16, 128, 3, 3, 2, 4), (65, 26000, 128, 3, 4, 1, 4),
     (200, 8192, 128, 3, 4, 3, 4), (65, 34704, 128, 3, 6, 1, 4), (200, 10928, 128, 3, 6, 3, 4), (65, 52000, 128, 3, 7, 1, 4),
     (200, 17344, 128, 3, 7, 3, 4), (65, 58384, 128, 3, 8, 1, 4), (200, 19472, 128, 3, 8, 3, 4), (97, 26000, 128, 4, 4, 1, 4),
     (200, 16384, 128, 4, 4, 2, 4), (97, 34704, 128, 4, 6, 1, 4), (200, 21856, 128, 4, 6, 2, 4), (97, 52000, 128, 4, 7, 1, 4),
     (200, 26000, 128, 4, 7, 2, 4), (97, 58384, 128, 4, 8, 1, 4), (200, 29184, 128, 4, 8, 2, 4), (129, 29184, 128, 5, 4, 1, 4),
     (129, 34704, 128, 5, 6, 1, 4), (129, 52000, 128, 5, 7, 1, 4), (129, 58384, 128, 5, 8, 1, 4),
-    (15, 26000, 640, 0, 4, 1, 10), (15, 34704, 640, 0, 6, 1, 10), (15, 16, 640, 1, 3, 1, 20), (15, 12992, 640, 1, 4, 1, 10),
-    (15, 17344, 640, 1, 6, 1, 10), (50, 16, 640, 2, 3, 1, 20), (50, 12992, 640, 2, 4, 1, 10), (50, 34704, 640, 2, 6, 1, 20),
+    (15, 26000, 640, 0, 4, 1, 10), (15, 34704, 640, 0, 6, 1, 10), (15, 16, 640, 1, 3, 1, 20), (15, 12992, 640, 1, 3.5, 1, 10),
+    (15, 17344, 640, 1, 6, 1, 10), (50, 16, 640, 2, 3, 1, 20), (50, 12992, 640, 2, 3.5, 1, 10), (50, 34704, 640, 2, 6, 1, 20),
     (50, 52000, 640, 2, 8, 1, 20), (95, 16, 640, 3, 3, 1, 20), (127, 16, 640, 3, 3, 2, 20), (95, 26000, 640, 3, 4, 1, 20),
     (250, 8192, 640, 3, 4, 3, 20), (95, 34704, 640, 3, 6, 1, 20), (250, 10928, 640, 3, 6, 3, 20),
     (95, 52000, 640, 3, 7, 1, 20), (250, 17344, 640, 3, 7, 3, 20), (95, 58384, 640, 3, 8, 1, 20),
@@ -77,14 +77,19 @@ PLAIN = [
     (127, 34704, 640, 4, 6, 1, 20), (250, 21856, 640, 4, 6, 2, 20), (127, 52000, 640, 4, 7, 1, 20),
     (250, 26000, 640, 4, 7, 2, 20), (127, 58384, 640, 4, 8, 1, 20), (250, 29184, 640, 4, 8, 2, 20),
     (159, 29184, 640, 5, 4, 1, 20), (159, 34704, 640, 5, 6, 1, 20), (159, 52000, 640, 5, 7, 1, 20),
-    (159, 58384, 640, 5, 8, 1, 20), (1, 16, 2176, 1, 3, 1, 17), (1, 6496, 2176, 1, 4, 1, 17), (1, 8672, 1920, 1, 6, 1, 15),
-    (33, 16, 2176, 2, 3, 1, 17), (33, 6496, 1920, 2, 4, 1, 15), (33, 8672, 2176, 2, 6, 1, 17), (65, 16, 2176, 3, 3, 1, 17),
+    (159, 58384, 640, 5, 8, 1, 20), (1, 16, 2176, 1, 3, 1, 17), (1, 6496, 2176, 1, 3.5, 1, 17), (1, 8672, 1920, 1, 6, 1, 15),
+    (33, 16, 2176, 2, 3, 1, 17), (33, 6496, 1920, 2, 3.5, 1, 15), (33, 8672, 2176, 2, 6, 1, 17), (65, 16, 2176, 3, 3, 1, 17),
     (65, 6496, 2176, 3, 4, 1, 17), (65, 8672, 2176, 3, 6, 1, 17),
+    # eight blocks for up to 64 rows: few and many stages, several ranges of K with odd and even stage counts
+    (17, 28704, 128, 1, 4, 1, 4), (32, 28704, 640, 1, 4, 1, 20), (33, 28704, 128, 2, 4, 1, 4), (64, 29008, 640, 2, 4, 1, 20),
+    (15, 14368, 640, 1, 4, 1, 10), (31, 14368, 640, 1, 4, 1, 10), (50, 14352, 2176, 2, 4, 1, 34), (1, 7712, 1920, 1, 4, 1, 15),
+    (32, 7184, 2176, 1, 4, 1, 17), (33, 7200, 1920, 2, 4, 1, 15), (64, 8192, 2176, 2, 4, 1, 17), (9, 4096, 4096, 1, 4, 1, 16),
+    (17, 4096, 4096, 1, 4, 1, 16), (64, 4096, 4096, 2, 4, 1, 16),
 ]
 # (M, F, K, RB, CB, row tiles, stages)
 SWIGLU = [
-    (1, 12992, 128, 0, 4, 1, 2), (1, 17344, 128, 0, 6, 1, 2), (1, 32, 128, 1, 3, 1, 4), (17, 12992, 128, 1, 4, 1, 4),
-    (17, 17344, 128, 1, 6, 1, 4), (33, 32, 128, 2, 3, 1, 4), (33, 12992, 128, 2, 4, 1, 4), (33, 17344, 128, 2, 6, 1, 4),
+    (1, 12992, 128, 0, 4, 1, 2), (1, 17344, 128, 0, 6, 1, 2), (1, 32, 128, 1, 3, 1, 4), (17, 12992, 128, 1, 3.5, 1, 4),
+    (17, 17344, 128, 1, 6, 1, 4), (33, 32, 128, 2, 3, 1, 4), (33, 12992, 128, 2, 3.5, 1, 4), (33, 17344, 128, 2, 6, 1, 4),
     (33, 27552, 128, 2, 8, 1, 4), (65, 32, 128, 3, 3, 1, 4), (97, 32, 128, 3, 3, 2, 4), (65, 12992, 128, 3, 4, 1, 4),
     (512, 2048, 128, 3, 4, 6, 4), (65, 17344, 128, 3, 6, 1, 4), (512, 2720, 128, 3, 6, 6, 4), (65, 27552, 128, 3, 7, 1, 4),
     (1000, 2432, 128, 3, 7, 11, 4), (65, 29184, 128, 3, 8, 1, 4), (700, 3648, 128, 3, 8, 8, 4), (97, 12992, 128, 4, 4, 1, 4),
@@ -92,8 +97,8 @@ SWIGLU = [
     (400, 6880, 128, 4, 7, 4, 4), (97, 29184, 128, 4, 8, 1, 4), (1000, 3648, 128, 4, 8, 8, 4), (129, 14592, 128, 5, 4, 1, 4),
     (640, 4096, 128, 5, 4, 4, 4), (129, 17344, 128, 5, 6, 1, 4), (700, 4864, 128, 5, 6, 5, 4), (129, 27552, 128, 5, 7, 1, 4),
     (400, 8672, 128, 5, 7, 3, 4), (129, 29184, 128, 5, 8, 1, 4), (700, 5792, 128, 5, 8, 5, 4), (15, 12992, 640, 0, 4, 1, 10),
-    (15, 17344, 640, 0, 6, 1, 10), (15, 32, 640, 1, 3, 1, 20), (31, 12992, 640, 1, 4, 1, 20), (31, 17344, 640, 1, 6, 1, 20),
-    (50, 32, 640, 2, 3, 1, 20), (50, 12992, 640, 2, 4, 1, 20), (50, 17344, 640, 2, 6, 1, 20), (50, 27552, 640, 2, 8, 1, 20),
+    (15, 17344, 640, 0, 6, 1, 10), (15, 32, 640, 1, 3, 1, 20), (31, 12992, 640, 1, 3.5, 1, 20), (31, 17344, 640, 1, 6, 1, 20),
+    (50, 32, 640, 2, 3, 1, 20), (50, 12992, 640, 2, 3.5, 1, 20), (50, 17344, 640, 2, 6, 1, 20), (50, 27552, 640, 2, 8, 1, 20),
     (95, 32, 640, 3, 3, 1, 20), (127, 32, 640, 3, 3, 2, 20), (95, 12992, 640, 3, 4, 1, 20), (960, 1216, 640, 3, 4, 10, 20),
     (95, 17344, 640, 3, 6, 1, 20), (799, 1824, 640, 3, 6, 9, 20), (95, 27552, 640, 3, 7, 1, 20),
     (960, 2432, 640, 3, 7, 10, 20), (95, 29184, 640, 3, 8, 1, 20), (450, 5792, 640, 3, 8, 5, 20),
@@ -102,14 +107,16 @@ SWIGLU = [
     (127, 29184, 640, 4, 8, 1, 20), (960, 4096, 640, 4, 8, 8, 20), (159, 14592, 640, 5, 4, 1, 20),
     (620, 4096, 640, 5, 4, 4, 20), (159, 17344, 640, 5, 6, 1, 20), (960, 3648, 640, 5, 6, 6, 20),
     (159, 27552, 640, 5, 7, 1, 20), (799, 5152, 640, 5, 7, 5, 20), (159, 29184, 640, 5, 8, 1, 20),
-    (960, 4864, 640, 5, 8, 6, 20),
+    (960, 4864, 640, 5, 8, 6, 20), (17, 14368, 128, 1, 4, 1, 4), (31, 16384, 640, 1, 4, 1, 20), (33, 14368, 128, 2, 4, 1, 4),
+    (50, 16352, 640, 2, 4, 1, 20),
 ]
 
 
 def _form(lib, epi, M, N, K):
-    f = (C.c_int32 * 5)()
+    f, columns = (C.c_int32 * 5)(), C.c_int32()
     assert lib.clover_op_gemm_form(epi, M, N, K, 1 if epi else 0, f) == 0, lib.clover_last_global_error()
-    return f[0], f[1], f[2], f[4]
+    assert lib.clover_op_gemm_tile_columns(epi, M, N, K, 1 if epi else 0, C.byref(columns)) == 0
+    return f[0], columns.value / 32, f[2], f[4]
 
 
 def _operands(torch, M, N, K, seed, n):
