@@ -110,7 +110,7 @@ struct clover_ctx : RowBufs {
   // dynamic (score-pruned) tree: candidates, frontiers and the per-sequence topology tables
   bool dyn_on = false;
   DynTree dyn{};
-  float *topk_vals, *topk_lse, *topk_aux;
+  float *topk_lse, *topk_aux;
   float* dyn_state;        // [B][DYN_MAX_CAND][H] draft states of the expanded candidates
   float* draft_capture = nullptr;   // test hook: device buffer that receives every depth's draft logits
   size_t draft_capture_floats = 0;
@@ -415,7 +415,6 @@ void carve(clover_ctx* x, char* base, size_t* total) {
   x->d_state = cv.take<float>((size_t)rows * H);
   x->d_rootx = cv.take<float>((size_t)B * H);
   x->z = cv.take<float>((size_t)rows * c.vocab);
-  x->topk_vals = cv.take<float>((size_t)rows * 16);
   x->topk_lse = cv.take<float>((size_t)rows);
   x->topk_aux = cv.take<float>(std::max((size_t)rows * topk_chunks(c.vocab), (size_t)B * sample_chunks(c.vocab)) * 2);
   x->dyn_state = cv.take<float>((size_t)B * DYN_MAX_CAND * H);
@@ -770,8 +769,7 @@ void draft_expand_dynamic(clover_ctx* x, int B, const int* m, int* tree_tokens, 
     }
     capture_draft_logits(x, j, rows);
     { Scope s(x, KC_TOPK);
-      launch_topk_lse(x->z, c.vocab, c.vocab, rows, t.topk, x->cand, x->topk_aux, x->topk_ids, x->topk_vals, x->topk_lse, x->st,
-                      1.0f, &t, j, m); }
+      launch_topk_lse(x->z, c.vocab, c.vocab, rows, t.topk, x->cand, x->topk_aux, x->topk_lse, x->st, 1.0f, &t, j, m); }
     if (j + 1 < t.D) { Scope s(x, KC_DRAFT_MISC); launch_dyn_frontier(t, j + 1, B, m, x->st); }
   }
   { Scope s(x, KC_DRAFT_MISC); launch_dyn_finalize(t, B, x->R, m, tree_tokens, x->st); }
@@ -823,7 +821,7 @@ int accept_common(clover_ctx* x, int batch, const int* tree_tokens, const float*
     // temperature > 0: per-row log-sum-exp of logits / T, then the sampled walk
     const float inv_t = 1.0f / temperature;
     { Scope s(x, KC_TOPK);
-      launch_topk_lse(logits, c.vocab, c.vocab, M, 1, x->cand, x->topk_aux, x->topk_ids, x->topk_vals, x->topk_lse, x->st, inv_t); }
+      launch_topk_lse(logits, c.vocab, c.vocab, M, 1, x->cand, x->topk_aux, x->topk_lse, x->st, inv_t); }
     { Scope s(x, KC_ACCEPT);
       launch_accept_sample(logits, c.vocab, x->topk_lse, inv_t, tree_tokens, fc_tab, nc_tab, x->dyn_on ? R : 0, batch, R,
                            uniforms, m, acc_idx, new_tokens, next_tok, x->d_seq_len,

@@ -385,14 +385,12 @@ struct DynTree {
   unsigned long long* t_anc;               // dev [B][R][2]
   int* t_iv;                               // dev [B][R][2]: interval labels (enter, exit) of the tree as verified
 };
-// per row of z[rows, V]: ids and values of the k best entries (value descending, id ascending) and the row's
-// log-sum-exp.  cand: [rows][chunks][16] 64-bit keys, aux: [rows][chunks][2] floats, chunks = ceil(V / 2048)
-// (scale: every value is multiplied by it first -- an inverse temperature)
-// to non-null (k = to->topk): row b * F[j] + r ranks candidate frontier[b][j][r]; token, cumulative score and parent of its children go
-// to their candidates (sequences with m[b] < 1 are left alone)
-void launch_topk_lse(const float* z, int ldz, int V, int rows, int k, void* cand, float* aux, int* out_ids,
-                     float* out_vals, float* out_lse, hipStream_t st, float scale = 1.0f, const DynTree* to = nullptr, int j = 0,
-                     const int* m = nullptr);
+// log-sum-exp of each row of z[rows, V], every value multiplied by `scale` first (an inverse temperature).  cand:
+// [rows][chunks][16] 64-bit keys, aux: [rows][chunks][2] floats, chunks = ceil(V / 2048)
+// to non-null (k = to->topk): row b * F[j] + r ranks candidate frontier[b][j][r] by (value descending, id ascending); token, cumulative
+// score and parent of its k children go to their candidates (sequences with m[b] < 1 are left alone)
+void launch_topk_lse(const float* z, int ldz, int V, int rows, int k, void* cand, float* aux, float* out_lse, hipStream_t st,
+                     float scale = 1.0f, const DynTree* to = nullptr, int j = 0, const int* m = nullptr);
 // verification at a temperature > 0: lse[row] = log-sum-exp of logits[row] * inv_temp; uniforms [B][R][17]
 int sample_chunks(int V);
 void launch_accept_sample(const float* logits, int V, const float* lse, float inv_temp, const int* tokens,

@@ -84,11 +84,10 @@ __global__ __launch_bounds__(256) void topk_lse_stage1_kernel(const float* __res
   }
 }
 
-// stage 2: the row's k best ids and values, and its log-sum-exp (chunks merged in chunk order by one thread,
-// so the sum does not depend on the launch shape)
+// stage 2: the row's log-sum-exp (chunks merged in chunk order by one thread, so the sum does not depend on the launch
+// shape) and, for a dynamic tree, its k best entries as the children of its candidate
 __global__ __launch_bounds__(256) void topk_lse_stage2_kernel(const unsigned long long* __restrict__ cand,
                                                               const float* __restrict__ aux, int chunks, int k,
-                                                              int* __restrict__ out_ids, float* __restrict__ out_vals,
                                                               float* __restrict__ out_lse, DynTree to, int j, const int* __restrict__ m) {
   __shared__ unsigned long long red[2][4];
   const int row = blockIdx.x;
@@ -120,6 +119,7 @@ __global__ __launch_bounds__(256) void topk_lse_stage2_kernel(const unsigned lon
   __shared__ int ids[16];
   __shared__ float vals[16], lse;
   if (threadIdx.x == 0) out_lse[row] = lse = M + logf(S);
+  if (!to.cand_tok) return;   // (uniform)
   for (int r = 0; r < k; ++r) {
     unsigned long long best = 0ull;
 #pragma unroll
@@ -129,11 +129,10 @@ __global__ __launch_bounds__(256) void topk_lse_stage2_kernel(const unsigned lon
     for (int e = 0; e < 8; ++e)
       if (key[e] == best) key[e] = 0ull;
     if (threadIdx.x == 0) {
-      out_ids[row * 16 + r] = ids[r] = (int)(0xFFFFFFFFu - (unsigned)(best & 0xFFFFFFFFull));
-      out_vals[row * 16 + r] = vals[r] = d_key_value(best);
+      ids[r] = (int)(0xFFFFFFFFu - (unsigned)(best & 0xFFFFFFFFull));
+      vals[r] = d_key_value(best);
     }
   }
-  if (!to.cand_tok) return;   // (uniform)
   __syncthreads();
   // children of the candidate that this row ranked: token, cumulative score, parent
   const int b = row / to.F[j], r = row - b * to.F[j], i = threadIdx.x;
@@ -463,13 +462,12 @@ void launch_accept_sample(const float* logits, int V, const float* lse, float in
                                         mass, chunks, new_tokens, next_tok);
 }
 
-void launch_topk_lse(const float* z, int ldz, int V, int rows, int k, void* cand, float* aux, int* out_ids,
-                     float* out_vals, float* out_lse, hipStream_t st, float scale, const DynTree* to, int j, const int* m) {
+void launch_topk_lse(const float* z, int ldz, int V, int rows, int k, void* cand, float* aux, float* out_lse, hipStream_t st,
+                     float scale, const DynTree* to, int j, const int* m) {
   if (rows <= 0) return;
   const int chunks = (V + DY_CHUNK - 1) / DY_CHUNK;
   topk_lse_stage1_kernel<<<dim3(chunks, rows), 256, 0, st>>>(z, ldz, V, k, (unsigned long long*)cand, aux, scale);
-  topk_lse_stage2_kernel<<<rows, 256, 0, st>>>((const unsigned long long*)cand, aux, chunks, k, out_ids, out_vals, out_lse,
-                                               to ? *to : DynTree{}, j, m);
+  topk_lse_stage2_kernel<<<rows, 256, 0, st>>>((const unsigned long long*)cand, aux, chunks, k, out_lse, to ? *to : DynTree{}, j, m);
 }
 void launch_dyn_frontier(const DynTree& t, int j, int B, const int* m, hipStream_t st) {
   dyn_frontier_kernel<<<B, 256, 0, st>>>(t, j, m);
