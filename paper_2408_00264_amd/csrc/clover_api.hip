@@ -533,8 +533,8 @@ void run_layer(clover_ctx* x, const clover_layer_weights& lw, float* xres, RowMa
         ap.k = (const bf16_t*)kc_layer; ap.v = (const bf16_t*)vc_layer;
         ap.kv = kvl; ap.max_seq = c.max_seq; ap.n_kv = c.n_kv_heads; ap.n_q = c.n_q_heads;
         ap.base_len = base_len; ap.anc = anc; ap.iv = iv; ap.anc_stride = anc_stride; ap.rm = rm;
-        ap.o_part = x->o_part; ap.ml_part = x->ml_part; ap.rows_total = M; ap.out = O; ap.plan = attn;
-        launch_attn_mfma(ap, x->st);
+        ap.o_part = x->o_part; ap.ml_part = x->ml_part; ap.rows_total = M; ap.out = O;
+        launch_attn_mfma(ap, attn, x->st);
       } else {
         launch_attn_generic(x->q_rot, x->NQD, kc_layer, vc_layer, x->kvdtype, kvl, base_len, anc, c.n_q_heads, nullptr,
                             x->NQD, O, rm, x->st, anc_stride, iv);

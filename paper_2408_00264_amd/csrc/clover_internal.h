@@ -286,10 +286,12 @@ void launch_reduce_add_norm(float* x, int ldx, const float* P, int splits, size_
 // only range: 1) << 15, ranges[b] = ranges of sequence b; without (more sequences or units than it holds) all sequences have `most` ranges,
 // those behind a sequence's last tile idle.
 constexpr int ATTN_TAB = 256;
-struct AttnPlan {
+struct AttnUnits {
   int tiles, n_units, most, tab;
   unsigned short unit[ATTN_TAB];
-  unsigned char ranges[ATTN_TAB];
+};
+struct AttnPlan : AttnUnits {
+  unsigned char ranges[ATTN_TAB];        // (the merge's)
 };
 struct AttnParams {
   const bf16_t *q_hi, *q_lo; int ldq;    // [rows, n_q*128] planes: RoPE applied, scaled by 1/sqrt(128)
@@ -306,13 +308,13 @@ struct AttnParams {
   float* ml_part;                        // [plan.most][rows_total][n_q][2]
   int rows_total;
   FragPlanes out;                        // finished rows
-  AttnPlan plan;
+  AttnUnits plan;
 };
 bool attn_mfma_supported(int head_dim, int n_q, int n_kv, int max_seq);
 // keys[b]: host-side upper bound of base_len[b] + n for each of the B sequences of n rows; max_ranges: what the partial results
 // have room for; chain: the rows form a chain
 AttnPlan attn_plan(const int* keys, int B, int n, int n_kv, int n_q, bool chain, int max_ranges);
-void launch_attn_mfma(const AttnParams& p, hipStream_t st);
+void launch_attn_mfma(AttnParams p, const AttnPlan& plan, hipStream_t st);
 
 // ---- fragment-major weights and the GEMM that reads them ----------------------------------------
 // [N,K] row-major bf16 -> rows row0 .. row0+N-1 of a packed matrix of n_rows rows, [K/32][n_rows/16][64 lanes][8]: lane

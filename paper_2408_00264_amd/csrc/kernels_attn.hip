@@ -464,7 +464,7 @@ AttnPlan attn_plan(const int* keys, int B, int n, int n_kv, int n_q, bool chain,
   const bool fresh = chain && 2 * n > most_keys;
   const double tile = fresh ? 1.5 : 1.05, merge = fresh ? 5.2 : 2.0, per_mb = fresh ? 0.4 : 0.2;
   const bool table = B <= ATTN_TAB;
-  AttnPlan plan{n_tiles, B, 1, 0, {}, {}};
+  AttnPlan plan{{n_tiles, B, 1, 0, {}}, {}};
   double best = 1e30;
   const int step = (n_tiles + 255) / 256;   // (long caches: 256 lengths of a range are looked at)
   for (int c = n_tiles; c >= std::min(2, n_tiles) && (n_tiles + c - 1) / c <= limit; c -= step) {
@@ -491,7 +491,8 @@ AttnPlan attn_plan(const int* keys, int B, int n, int n_kv, int n_q, bool chain,
   return plan;
 }
 
-void launch_attn_mfma(const AttnParams& p, hipStream_t st) {
+void launch_attn_mfma(AttnParams p, const AttnPlan& plan, hipStream_t st) {
+  p.plan = plan;
   const int g = p.n_q / p.n_kv, nodes = group_nodes(g, p.rm.n);
   const unsigned groups = (unsigned)((p.rm.n + nodes - 1) / nodes), units = (unsigned)p.plan.n_units;
   const bool chain = p.anc == nullptr && p.iv == nullptr;
@@ -508,7 +509,7 @@ void launch_attn_mfma(const AttnParams& p, hipStream_t st) {
   }
   if (p.plan.most > 1) {
     MergeArgs m{p.o_part, p.ml_part, p.rows_total, p.n_q, p.plan.most, p.plan.tab, p.out, p.rm, {}};
-    std::copy(p.plan.ranges, p.plan.ranges + ATTN_TAB, m.ranges);
+    std::copy(plan.ranges, plan.ranges + ATTN_TAB, m.ranges);
     attn_merge_kernel<<<dim3(p.rm.n, p.rm.B, (p.n_q + MG_HEADS - 1) / MG_HEADS), MG_HEADS * 32, 0, st>>>(m);
   }
 }
