@@ -449,10 +449,12 @@ AttnPlan attn_plan(const int* keys, int B, int n, int n_kv, int n_q, bool chain,
   int most_keys = 0;
   for (int b = 0; b < B; ++b) most_keys = std::max(most_keys, keys[b]);
   const int n_tiles = (most_keys + AT_TK - 1) / AT_TK;
-  // Key splits by estimated time, in us, fitted to every split count of 283 launches (8 and 32 KV heads, groups of 1 to 8 heads, 1
-  // to 16 sequences, 1 to 128 nodes, 8 to 8192 keys, prompts to 2000 tokens; on average 1.7 % behind the best).  A key tile
-  // takes a lone workgroup of a compute unit 1.05; two share it in 1.8, counted as two here, which keeps a second workgroup for
-  // where it pays.  Splitting at all costs the merge launch and the traffic of the partial results, 2 + 0.2 per MB (32 heads, 8 KV
+  // Key splits by estimated time, in us, fitted to every split count of 283 launches over sequences of equal length (8 and 32 KV
+  // heads, groups of 1 to 8 heads, 1 to 16 sequences, 1 to 128 nodes, 8 to 8192 keys, prompts to 2000 tokens; on average 1.7 %
+  // behind the best; over 20 batches of unequal ones 2.1 %, most of it 8 x 32 nodes with 32 KV heads, 84.5 where 3 splits take 71.3).
+  // A key tile adds 1.0 to a lone workgroup of a compute unit that has 16 nodes, 1.2 to one with all 32, 2.0 to 2.5 to two of those
+  // together (8192 keys; what a launch takes besides is left out): 1.05 here, and two count as twice one, which keeps a second
+  // workgroup for where it pays.  Splitting at all costs the merge launch and the traffic of the partial results, 2 + 0.2 per MB (32 heads, 8 KV
   // heads: one node at 133 keys unsplit 14.9, in 3 splits 10.4; 64 nodes at 100 keys 17.1 and 15.3, at 1024 keys 52 and 19 in 12;
   // 128 nodes at 8192 keys 59.4 in 8, 55.5 in 16).  Where most keys are the launch's own new rows the workgroups' tiles grow from
   // one to all, so a split shortens only the last of them: 1.5 and 5.2 + 0.4 there (200 tokens unsplit 17.0, in 4 splits 20.9).

@@ -5,9 +5,10 @@
 //
 // What bounds it: up to 16 rows the weight stream from HBM, above ~150 rows the matrix pipe (hi + lo planes are two
 // matrix instructions per fragment pair; from 512 rows on its power: it is busy 82 to 90 % of the time at 1.9 to 2.2 GHz,
-// and nothing but products runs at 2.25), and in between the lines that a compute unit can have in flight: about 130 of 128 bytes
-// (counters: requests x their latency / cycles, gate+up at 64 rows 126, at one row 146), 1000 clocks each for weights and 350 for
-// activations out of the L2, so what counts is lines per compute unit, and buffers beyond 16 KB do not help.
+// and nothing but products runs at 2.25), and in between the read requests that a compute unit has in flight: by counters (the sum
+// of their latencies / its busy cycles) 144 at one row, 133 at 23, 121 at 64, 107 to 110 at 80 and 96 in gate+up, 88 to 96 from 133
+// rows on, whatever the stage buffers hold beyond 16 KB; 980 clocks each at one row, nearly all of them weights, 670 at 64, where
+// half are activations out of the L2.  So what counts is lines per compute unit.
 //
 // Shape.  A workgroup of four wavefronts (2 x 2, one per SIMD; up to 16 rows 1 x 4) owns 32 RB rows x 16 WB columns (RB 1 to 5 and 8); a wavefront RB x WB / 2
 // products of 16 x 16.  Both operands go global -> LDS directly, 32 columns of K per stage, as 1 KB blocks that are
@@ -155,9 +156,9 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(TileGemm p) {
   const char* xp = (const char*)p.X.p + (size_t)kt0 * xstage;   // the stage that is requested next
   const char* wp = (const char*)p.W + (size_t)kt0 * wstage;
   const unsigned ldsw = lds0 + (unsigned)wave * 1024u;
-  // The last load's destination and lanes.  (Two wavefronts used to stage the last blocks a second time.  A compute unit has
-  // about 130 lines of 128 bytes in flight, whatever the buffers hold, so a line that is loaded twice costs its share of the
-  // kernel, as do compute units without a workgroup.  64 rows: gate+up of 11008 channels 45.4 -> 40.9 us, QKV 16.7 -> 15.6.)
+  // The last load's destination and lanes.  (Two wavefronts used to stage the last blocks a second time, and a line that is loaded
+  // twice costs its share of the kernel.  64 rows, both in tiles of 96 columns, six blocks a stage: gate+up of 11008 channels 45.4 ->
+  // 40.9 us, QKV 16.7 -> 15.6.)
   const unsigned wlast = (unsigned)__builtin_amdgcn_readfirstlane((XF + (WL - 1) * 4) * 1024 + wave * (WREST * 256 - 1024));
   const unsigned long long some_lanes = (1ull << (16 * WREST)) - 1ull;
   // Load j of the stage at (xp, wp), M0 set in front of it: at least one instruction (or the no-op) has to lie in between.
