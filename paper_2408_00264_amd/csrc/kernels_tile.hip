@@ -6,9 +6,9 @@
 // What bounds it: up to 16 rows the weight stream from HBM, above ~150 rows the matrix pipe (hi + lo planes are two
 // matrix instructions per fragment pair; from 512 rows on its power: it is busy 82 to 90 % of the time at 1.9 to 2.2 GHz,
 // and nothing but products runs at 2.25), and in between the read requests that a compute unit has in flight: by counters (the sum
-// of their latencies / its busy cycles) 144 at one row, 133 at 23, 121 at 64, 107 to 110 at 80 and 96 in gate+up, 88 to 96 from 133
-// rows on, whatever the stage buffers hold beyond 16 KB; 980 clocks each at one row, nearly all of them weights, 670 at 64, where
-// half are activations out of the L2.  So what counts is lines per compute unit.
+// of their latencies / its busy cycles) about 145 at one row of gate+up, 135 at 23, 120 at 64, 110 at 80 and 96, 90 to 95 at 133 and
+// 256, whatever the stage buffers hold beyond 16 KB; 1000 clocks each at one row, nearly all of them weights, 700 at 64, where half
+// are activations out of the L2.  So what counts is lines per compute unit.
 //
 // Shape.  A workgroup of four wavefronts (2 x 2, one per SIMD; up to 16 rows 1 x 4) owns 32 RB rows x 16 WB columns (RB 1 to 5 and 8); a wavefront RB x WB / 2
 // products of 16 x 16.  Both operands go global -> LDS directly, 32 columns of K per stage, as 1 KB blocks that are
