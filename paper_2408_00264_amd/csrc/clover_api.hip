@@ -95,6 +95,7 @@ struct clover_ctx : RowBufs {
   // device regions
   int *d_seq_len, *d_aug_len, *d_err;
   int *d_depth, *d_parent, *d_rank, *d_first_child, *d_n_child, *d_lvl_nodes;
+  unsigned* d_meet;        // meetings of the workgroups that share a GEMM tile
   unsigned long long* d_anc;
   int* d_pages;            // page table [max_batch][max_seq / KV_PAGE] (used once clover_set_page_table was called)
   int* d_iv;               // interval labels of the static tree [R][2]
@@ -257,7 +258,10 @@ std::vector<TileBytes> tile_bytes(const clover_config& c, int rows) {
     auto bytes = [&](int N, int K) {   // (a tuning build that changes the ranges afterwards makes room for them here)
       return (size_t)std::max(tile_gemm_pick_k_parts(M, N, K), tune_int("CLOVER_TILE_KP_ROOM", 1)) * std::min(M, rows) * N * sizeof(float);
     };
-    t.attn = std::max(t.attn, std::max(bytes(s[0].N, s[0].K), bytes(s[1].N, s[1].K)));
+    auto exchanged = [&](int N, int K) {
+      return tile_gemm_exchange_bytes(std::min(M, rows), N, K, std::max(tile_gemm_pick_k_parts(M, N, K), tune_int("CLOVER_TILE_KP_ROOM", 1)));
+    };
+    t.attn = std::max({t.attn, bytes(s[0].N, s[0].K), exchanged(s[0].N, s[0].K), bytes(s[1].N, s[1].K)});
     t.down = std::max(t.down, bytes(s[2].N, s[2].K));
     t.ad = std::max(t.ad, align256(bytes(s[3].N, s[3].K)) + bytes(2 * c.hidden, c.hidden));
     t.fc = std::max(t.fc, bytes(s[4].N, s[4].K));
@@ -355,6 +359,7 @@ void carve(clover_ctx* x, char* base, size_t* total) {
   x->d_lvl_nodes = cv.take<int>(R);
   x->d_anc = cv.take<unsigned long long>(2 * R);
   x->d_iv = cv.take<int>(2 * R);
+  x->d_meet = cv.take<unsigned>(TILE_MEETINGS * MEET_STRIDE);
   x->kc = cv.take<char>(x->k_layer_elems * x->kv_esz * c.n_layers);
   x->vc = cv.take<char>(x->v_layer_elems * x->kv_esz * c.n_layers);
   x->aug_kc = cv.take<char>(x->k_layer_elems * x->kv_esz * c.aug_layers);
@@ -474,6 +479,17 @@ int gemm_fast(clover_ctx* x, int cls, FragPlanes X, const void* W, int M, int N,
   launch_gemm_tile(g, x->st);
   return g.k_parts;
 }
+// a launch whose workgroups finish the tiles of several K ranges between them
+TileGemm exchanging_gemm(clover_ctx* x, FragPlanes X, const void* W, int M, int N, int K) {
+  TileGemm g;
+  memset(&g, 0, sizeof(g));
+  g.X = X;
+  g.W = (const bf16_t*)W;
+  g.M = M; g.N = N; g.K = K;
+  g.k_parts = tile_gemm_pick_k_parts(M, N, K);
+  g.part = x->partial; g.meet = x->d_meet; g.polls = tune_int("CLOVER_MEET_POLLS", MEET_POLLS);
+  return g;
+}
 // Y = X W^T + bias through the MFMA path, for the small draft-side linears
 void linear_fast(clover_ctx* x, FragPlanes X, const void* W, const void* bias, float* Y, int ldy, int M, int N, int K) {
   const int sp = gemm_fast(x, KC_GEMM_DRAFT, X, W, M, N, K);
@@ -520,11 +536,12 @@ void run_layer(clover_ctx* x, const clover_layer_weights& lw, float* xres, RowMa
     const FragPlanes A = frag_planes(x->a_norm, M), O = frag_planes(x->attn_out, M), Hf = frag_planes(x->h_ffn, M);
     bf16_t* const q_hi = (bf16_t*)x->q_rot;
     bf16_t* const q_lo = q_hi + (size_t)x->rows * x->NQD;
-    const int sq = gemm_fast(x, KC_GEMM_QKV, A, lw.wq /* q, k and v rows */, M, x->QKVN, H);
-    { Scope s(x, KC_ROPE_KV);
-      launch_rope_kv_write(x->partial, x->QKVN, sq, (size_t)M * x->QKVN, x->cos_t, x->sin_t, x->q_rot, x->NQD, kc_layer,
-                           vc_layer, x->kvdtype, kvl, base_len, c.n_q_heads, rm, x->d_err,
-                           x->attn_fast ? q_hi : nullptr, q_lo, 1.0f / sqrtf((float)d), x->st); }
+    { Scope s(x, KC_GEMM_QKV);   // (rotation and cache write included)
+      TileGemm g = exchanging_gemm(x, A, lw.wq /* q, k and v rows */, M, x->QKVN, H);
+      g.epi = 3;
+      g.qkv = QkvOut{c.n_q_heads, d, x->attn_fast ? q_hi : nullptr, q_lo, 1.0f / sqrtf((float)d), x->q_rot, x->NQD,
+                     (bf16_t*)kc_layer, (bf16_t*)vc_layer, kvl, x->cos_t, x->sin_t, base_len, rm, x->d_err};
+      launch_gemm_tile(g, x->st); }
     { Scope s(x, KC_ATTN);
       if (x->attn_fast) {
         AttnParams ap;
@@ -567,8 +584,8 @@ void run_layer(clover_ctx* x, const clover_layer_weights& lw, float* xres, RowMa
       gemm_generic(x, KC_GEMM_QKV, x->a_norm, H, ws[sgm], nullptr, x->qkv + off, x->QKVN, M, sn[sgm], H, 0);
   }
   { Scope s(x, KC_ROPE_KV);
-    launch_rope_kv_write(x->qkv, x->QKVN, 1, 0, x->cos_t, x->sin_t, x->q_rot, x->NQD, kc_layer, vc_layer, x->kvdtype,
-                         kvl, base_len, c.n_q_heads, rm, x->d_err, nullptr, nullptr, 0.f, x->st); }
+    launch_rope_kv_write(x->qkv, x->QKVN, x->cos_t, x->sin_t, x->q_rot, x->NQD, (float*)kc_layer, (float*)vc_layer, kvl, base_len,
+                         c.n_q_heads, rm, x->d_err, x->st); }
   { Scope s(x, KC_ATTN);
     launch_attn_generic(x->q_rot, x->NQD, kc_layer, vc_layer, x->kvdtype, kvl, base_len, anc, c.n_q_heads, x->attn_out,
                         x->NQD, FragPlanes{}, rm, x->st, anc_stride, iv); }
@@ -924,6 +941,7 @@ int clover_init(const clover_config* cfg, const clover_weights* w, const clover_
   launch_fill_i32(x->d_seq_len, 0, cfg->max_batch, x->st);
   launch_fill_i32(x->d_aug_len, 0, cfg->max_batch, x->st);
   launch_fill_i32(x->d_err, 0, 1, x->st);
+  launch_fill_i32((int*)x->d_meet, 0, TILE_MEETINGS * MEET_STRIDE, x->st);
   // A draft call leaves a skipped sequence's dynamic tables alone, but its rows are computed along and index by them: candidate 0
   // and a root without children until a call fills them in.
   launch_fill_i32(x->dyn.cand_tok, 0, (int)(x->dyn.t_iv + 2 * x->step.rows - x->dyn.cand_tok), x->st);
@@ -943,19 +961,20 @@ int clover_init(const clover_config* cfg, const clover_weights* w, const clover_
       cur += (size_t)N * K * 2;
     };
     // linears that share their input, as one matrix: every pointer names the whole
-    auto pack_joint = [&](std::initializer_list<std::pair<const void**, int>> parts, int K) {
+    struct Part { const void** w; int rows, rotary_d; };
+    auto pack_joint = [&](std::initializer_list<Part> parts, int K) {
       int n_rows = 0, row0 = 0;
-      for (const auto& p : parts) n_rows += p.second;
-      for (const auto& p : parts) {
-        launch_pack_weight(*p.first, cur, p.second, K, row0, n_rows, x->st);
-        *p.first = cur;
-        row0 += p.second;
+      for (const Part& p : parts) n_rows += p.rows;
+      for (const Part& p : parts) {
+        launch_pack_weight(*p.w, cur, p.rows, K, row0, n_rows, x->st, p.rotary_d);
+        *p.w = cur;
+        row0 += p.rows;
       }
       cur += (size_t)n_rows * K * 2;
     };
     const int H = x->H, d = cfg->head_dim, F = cfg->ffn;
     auto pack_layer = [&](clover_layer_weights& l) {
-      pack_joint({{&l.wq, cfg->n_q_heads * d}, {&l.wk, cfg->n_kv_heads * d}, {&l.wv, cfg->n_kv_heads * d}}, H);
+      pack_joint({{&l.wq, cfg->n_q_heads * d, d}, {&l.wk, cfg->n_kv_heads * d, d}, {&l.wv, cfg->n_kv_heads * d, 0}}, H);
       pack(l.wo, H, x->NQD);
       launch_pack_gate_up(l.w_gate, l.w_up, cur, F, H, x->st);
       l.w_gate = l.w_up = cur;
@@ -966,7 +985,7 @@ int clover_init(const clover_config* cfg, const clover_weights* w, const clover_
     for (auto& l : x->aug) pack_layer(l);
     x->lm_head_pk = x->w.lm_head;
     pack(x->lm_head_pk, cfg->vocab, H);
-    for (clover_ad_weights* a : {&x->w.ad1, &x->w.ad2}) { pack(a->wq, H, H); pack_joint({{&a->wk, H}, {&a->wv, H}}, H); }
+    for (clover_ad_weights* a : {&x->w.ad1, &x->w.ad2}) { pack(a->wq, H, H); pack_joint({{&a->wk, H, 0}, {&a->wv, H, 0}}, H); }
     pack(x->w.fc0_w, H, H);
     for (int j = 1; j < cfg->draft_depths; ++j) pack(x->fc_w[j], H, 2 * H);
     if ((size_t)(cur - x->packed) > x->packed_bytes) { delete x; return fail(nullptr, CLOVER_E_CAPACITY, "internal: packed weights overflow"); }

@@ -164,6 +164,20 @@ __device__ __forceinline__ void frag_store4(const FragPlanes& f, int row, int co
 #endif
 
 #ifdef __HIPCC__
+// Four elements at once from wherever an element may lie: callers owe their tensors no more, and the load instruction takes it.
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef bf16_t bf16x4_any __attribute__((ext_vector_type(4), aligned(2)));
+__device__ __forceinline__ float4 ld4_any(const float* p) {
+  const f32x4_any u = *(const f32x4_any*)p;
+  return make_float4(u[0], u[1], u[2], u[3]);
+}
+__device__ __forceinline__ float4 ld4_any(const bf16_t* p) {
+  const bf16x4_any u = *(const bf16x4_any*)p;
+  return make_float4(__uint_as_float((unsigned)u[0] << 16), __uint_as_float((unsigned)u[1] << 16), __uint_as_float((unsigned)u[2] << 16),
+                     __uint_as_float((unsigned)u[3] << 16));
+}
+__device__ __forceinline__ int rows_valid(const RowMap& rm, int b) { return rm.n_valid ? min(rm.n_valid[b], rm.n) : rm.n; }
+
 // raises the limit of a kernel's dynamic LDS, once per device
 inline void allow_dynamic_lds(OncePerDevice& once, const void* kernel, int bytes) {
   int dev = -1;
@@ -204,10 +218,8 @@ struct PassStart {
 void launch_pass_start(const PassStart& p, int wdtype, hipStream_t st);
 void launch_rmsnorm(const float* x, int ldx, const void* gain, int wdtype, float eps, float* out, int ldo, int H,
                     int rows, hipStream_t st);
-void launch_rope_kv_write(const float* qkv, int ldqkv, int qkv_splits, size_t qkv_split_stride, const float* cos_t, const float* sin_t, float* q_out, int ldq,
-                          void* k_cache, void* v_cache, int kvdtype, KVLayout kv, const int* base_len, int n_q,
-                          RowMap rm, int* err_flag, bf16_t* q_hi /*null: fp32 q_out*/, bf16_t* q_lo, float q_scale,
-                          hipStream_t st);
+void launch_rope_kv_write(const float* qkv, int ldqkv, const float* cos_t, const float* sin_t, float* q_out, int ldq, float* k_cache,
+                          float* v_cache, KVLayout kv, const int* base_len, int n_q, RowMap rm, int* err_flag, hipStream_t st);
 void launch_attn_generic(const float* q, int ldq, const void* k_cache, const void* v_cache, int kvdtype, KVLayout kv,
                          const int* base_len, const unsigned long long* anc /*[n][2]*/, int n_q, float* out, int ldo,
                          FragPlanes planes /*instead of fp32 when planes.p is non-null*/, RowMap rm,
@@ -322,23 +334,45 @@ void launch_attn_mfma(AttnParams p, const AttnPlan& plan, hipStream_t st);
 // contiguous KB.  K steps outermost: the workgroups of a launch walk K side by side and so read one contiguous region
 // at a time.  (Row blocks outermost, every workgroup reads at the same offset of its own power-of-two-sized blocks;
 // gate+up at one row 43 -> 40 us, LM head 168 -> 164, 64 rows and more within noise.)
-void launch_pack_weight(const void* src, void* dst, int N, int K, int row0, int n_rows, hipStream_t st);
+// rotary_d > 0: the rows of each head of that size in rotary order, so that a block of 16 holds 8 rows 8j .. of the head's first half and
+// the 8 rows of the second half that are rotated with them.
+void launch_pack_weight(const void* src, void* dst, int N, int K, int row0, int n_rows, hipStream_t st, int rotary_d = 0);
 // gate and up, each [F,K], as one matrix of 2F rows: block b holds rows 8b .. 8b+7 of the gate, then those of the up
 void launch_pack_gate_up(const void* gate, const void* up, void* dst, int F, int K, hipStream_t st);
+// What the QKV projection's launch does with its sums: q and k rotated (half-split pairing), q out, k and v into the cache.  W holds the
+// q and k rows of every head in rotary order (launch_pack_weight).
+struct QkvOut {
+  int n_q, d;                         // query heads; the caches' KV heads follow from kv
+  bf16_t *q_hi, *q_lo; float q_scale; // planes of q * q_scale for the MFMA attention; q_hi null: fp32 q
+  float* q; int ldq;
+  bf16_t *kc, *vc; KVLayout kv;
+  const float *cos_t, *sin_t;         // [rows][d / 2]
+  const int* base_len; RowMap rm; int* err_flag;
+};
 struct TileGemm {
   FragPlanes X;                       // activations [M, K]
   const bf16_t* W;                    // packed [N, K]; epi 1: gate and up interleaved, [2N, K]
   float* Y; int ldy;                  // epi 0: fp32 [M, N]; range r of K writes Y + r * split_stride
   FragPlanes out;                     // epi 1: planes of silu(X Wg^T) * (X Wu^T), [M, N]
   int M, N, K;
-  int epi;                            // 0 plain, 1 SwiGLU
-  int k_parts; size_t split_stride;   // epi 0 only
-  int n_units;                        // filled in by launch_gemm_tile: column tiles x K ranges
+  int epi;                            // 0 plain, 1 SwiGLU, 3 QKV
+  int k_parts; size_t split_stride;   // (split_stride: epi 0 only)
+  QkvOut qkv;                         // epi 3
+  // epi 3 over several ranges of K: their workgroups exchange partial tiles in `part` (tile_gemm_exchange_bytes) and finish the tile
+  // in shares, and meet in `meet`, TILE_MEETINGS words MEET_STRIDE apart (zero before the first launch that uses them)
+  float* part; unsigned* meet; int polls;
+  // filled in by launch_gemm_tile: column tiles x K ranges; row blocks of a row tile that has them all; 1: the ranges of a tile
+  // are on different XCDs
+  int n_units, row_blocks, spread;
 };
+constexpr int TILE_MEETINGS = 256, MEET_STRIDE = 16;
+constexpr int MEET_POLLS = 256;       // looks of a member at the word before it leaves its share to the last one (100 us or so)
 constexpr int TILE_MAX_K_PARTS = 8;
 // K ranges of a narrow output; the same for all M that round up to the same multiple of 32
 int tile_gemm_pick_k_parts(int M, int N, int K);
 void launch_gemm_tile(const TileGemm& g, hipStream_t st);
+// bytes of `part` for M rows over k_parts ranges
+size_t tile_gemm_exchange_bytes(int M, int N, int K, int k_parts);
 // what launch_gemm_tile runs for M rows (N = F for epi 1; k_parts 0: its own choice)
 struct TileForm { int rb, wb /* column blocks of 16 */, row_tiles, k_parts, stages; };
 TileForm tile_gemm_form(int M, int N, int K, int epi, int k_parts);

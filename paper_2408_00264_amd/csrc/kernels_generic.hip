@@ -54,20 +54,6 @@ __device__ __forceinline__ float block_sum_256(float v, float* red) {
   return red[0] + red[1] + red[2] + red[3];
 }
 
-// Four elements at once from wherever an element may lie: callers owe their tensors no more, and the load instruction takes it.
-typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
-typedef bf16_t bf16x4_any __attribute__((ext_vector_type(4), aligned(2)));
-__device__ __forceinline__ float4 ld4_any(const float* p) {
-  const f32x4_any u = *(const f32x4_any*)p;
-  return make_float4(u[0], u[1], u[2], u[3]);
-}
-__device__ __forceinline__ float4 ld4_any(const bf16_t* p) {
-  const bf16x4_any u = *(const bf16x4_any*)p;
-  return make_float4(bf16_to_f32(u[0]), bf16_to_f32(u[1]), bf16_to_f32(u[2]), bf16_to_f32(u[3]));
-}
-
-__device__ __forceinline__ int rows_valid(const RowMap& rm, int b) { return rm.n_valid ? min(rm.n_valid[b], rm.n) : rm.n; }
-
 // ------------------------------------------------------------------------------------------
 // RMSNorm: out = x * rsqrt(mean(x^2) + eps) * gain      (one block per row)
 // ------------------------------------------------------------------------------------------
@@ -94,29 +80,14 @@ void launch_rmsnorm(const float* x, int ldx, const void* gain, int wdtype, float
 }
 
 // ------------------------------------------------------------------------------------------
-// RoPE on q and k (half-split pairing), K rows and transposed V columns into the cache; sums the
-// QKV projection's partial tiles on the way (fixed order, eight loads in flight).
+// RoPE on q and k (half-split pairing), K rows and transposed V columns into the cache (fp32 models; the MFMA path's QKV GEMM does
+// both itself).
 // blocks [0, n*hc): 256 (head, pair) items of one row; then blocks of 8 (head,dim) lines of V^T
 // ------------------------------------------------------------------------------------------
-__device__ __forceinline__ float sum_partials(const float* __restrict__ p, int nsp, size_t sps) {
-  float v = 0.f;
-  for (int s0 = 0; s0 < nsp; s0 += 8) {
-    float q[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) q[j] = (s0 + j < nsp) ? p[(size_t)(s0 + j) * sps] : 0.f;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) v += q[j];
-  }
-  return v;
-}
-
-template <typename KT>
-__global__ void rope_kv_write_kernel(const float* __restrict__ qkv, int ldqkv, int nsp, size_t sps,
-                                     const float* __restrict__ cos_t,
+__global__ void rope_kv_write_kernel(const float* __restrict__ qkv, int ldqkv, const float* __restrict__ cos_t,
                                      const float* __restrict__ sin_t, float* __restrict__ q_out, int ldq,
-                                     KT* __restrict__ kc, KT* __restrict__ vc, KVLayout kv,
-                                     const int* __restrict__ base_len, int n_q, RowMap rm, int* err_flag, int hc,
-                                     bf16_t* __restrict__ q_hi, bf16_t* __restrict__ q_lo, float q_scale) {
+                                     float* __restrict__ kc, float* __restrict__ vc, KVLayout kv,
+                                     const int* __restrict__ base_len, int n_q, RowMap rm, int* err_flag, int hc) {
   const int b = blockIdx.y;
   const int nv = rows_valid(rm, b);
   const int L = base_len[b];
@@ -131,62 +102,29 @@ __global__ void rope_kv_write_kernel(const float* __restrict__ qkv, int ldqkv, i
     const int idx = (blockIdx.x % hc) * 256 + threadIdx.x;
     if (idx >= (n_q + n_kv) * half) return;
     const size_t row = (size_t)b * rm.R + i;
-    const int slot = L + i;
     const float* src = qkv + row * ldqkv;
     const int hh = idx / half, ii = idx - hh * half;
     const float c = cos_t[row * half + ii], s = sin_t[row * half + ii];
-    const float x1 = sum_partials(src + hh * d + ii, nsp, sps);
-    const float x2 = sum_partials(src + hh * d + ii + half, nsp, sps);
+    const float x1 = src[hh * d + ii], x2 = src[hh * d + ii + half];
     const float o1 = x1 * c - x2 * s, o2 = x2 * c + x1 * s;
-    if (hh < n_q) {
-      if (q_hi) {  // operand format of the MFMA attention: pre-scaled (hi, lo) bf16 planes
-        const float s1 = o1 * q_scale, s2 = o2 * q_scale;
-        const bf16_t h1 = f32_to_bf16(s1), h2 = f32_to_bf16(s2);
-        q_hi[row * ldq + hh * d + ii] = h1;
-        q_hi[row * ldq + hh * d + ii + half] = h2;
-        q_lo[row * ldq + hh * d + ii] = f32_to_bf16(s1 - bf16_to_f32(h1));
-        q_lo[row * ldq + hh * d + ii + half] = f32_to_bf16(s2 - bf16_to_f32(h2));
-      } else {
-        q_out[row * ldq + hh * d + ii] = o1;
-        q_out[row * ldq + hh * d + ii + half] = o2;
-      }
-    } else {
-      const size_t base = kv_k_at(kv, b, slot, hh - n_q);
-      stkv(kc, base + kv_k_col(kv, ii), kv.plane, o1);
-      stkv(kc, base + kv_k_col(kv, ii + half), kv.plane, o2);
-    }
+    float* out = hh < n_q ? q_out + row * ldq + hh * d : kc + kv_k_at(kv, b, L + i, hh - n_q);
+    out[ii] = o1;
+    out[ii + half] = o2;
   } else {
     const int vb = blockIdx.x - rm.n * hc;
     const int voff = (n_q + n_kv) * d;
     for (int idx = threadIdx.x; idx < 8 * rm.n; idx += blockDim.x) {
       const int node = idx % rm.n, e = vb * 8 + idx / rm.n;
       if (node >= nv || e >= n_kv * d) continue;
-      const float v = sum_partials(qkv + ((size_t)b * rm.R + node) * ldqkv + voff + e, nsp, sps);
-      stkv(vc, kv_v_at(kv, b, e / d, e % d, L + node), kv.plane, v);
+      vc[kv_v_at(kv, b, e / d, e % d, L + node)] = qkv[((size_t)b * rm.R + node) * ldqkv + voff + e];
     }
   }
 }
 
-// The same operation for the MFMA path's formats (q as pre-scaled bf16 planes, bf16-plane caches), vectorised:
-// a thread of the first blocks rotates four adjacent pairs of one head (float4 loads of every partial, issued
-// before anything else is waited for; 8-byte plane stores); the last blocks transpose 64 nodes x 32 channels of V
-// through LDS so that the partials are read along the channels and V^T is written along the nodes.
-__device__ __forceinline__ void planes4(bf16_t* hi, bf16_t* lo, size_t off, const float (&o)[4]) {
-  unsigned h[4], l[4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const bf16_t hb = f32_to_bf16(o[r]);
-    h[r] = hb;
-    l[r] = f32_to_bf16(o[r] - bf16_to_f32(hb));
-  }
-  *(uint2*)(hi + off) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
-  *(uint2*)(lo + off) = make_uint2(l[0] | (l[1] << 16), l[2] | (l[3] << 16));
-}
-// The K ranges are counted at compile time here and in reduce_add_norm_kernel: every load of a thread is requested in
+// The K ranges are counted at compile time: every load of a thread is requested in
 // straight-line code before the first is used.  With a runtime count the two halves of a pair were one round trip to memory
 // after the other, and most of the instructions were branches around loads of ranges that do not exist.  us per launch:
-// reduce_add_norm of 512 rows x 2 ranges 12.5 -> 10.0, 1024 x 1 17.9 -> 14.2, 2048 x 1 31.9 -> 26.2; rope_kv_planes of one row
-// x 8 ranges 5.6 -> 5.1, 64 x 4 5.2 -> 5.1, 512 x 2 10.8 -> 10.4.
+// reduce_add_norm of 512 rows x 2 ranges 12.5 -> 10.0, 1024 x 1 17.9 -> 14.2, 2048 x 1 31.9 -> 26.2.
 template <int NS>
 struct Partials4 {
   float4 q[NS];
@@ -206,102 +144,12 @@ struct Partials4<0> {
   __device__ __forceinline__ void request(const float*, size_t) {}
   __device__ __forceinline__ float4 add_to(float4 v) const { return v; }
 };
-template <int NS>
-__global__ __launch_bounds__(256) void rope_kv_planes_kernel(const float* __restrict__ qkv, int ldqkv, size_t sps,
-                                                             const float* __restrict__ cos_t, const float* __restrict__ sin_t,
-                                                             bf16_t* __restrict__ kc, bf16_t* __restrict__ vc, KVLayout kv,
-                                                             const int* __restrict__ base_len, int n_q, RowMap rm,
-                                                             int* err_flag, int qk_blocks, bf16_t* __restrict__ q_hi,
-                                                             bf16_t* __restrict__ q_lo, int ldq, float q_scale) {
-  __shared__ float tile[64][33];
-  const int b = blockIdx.y, tid = threadIdx.x;
-  const int d = kv.d, half = d / 2, n_kv = kv.n_kv;
-  if ((int)blockIdx.x < qk_blocks) {
-    const int quads = half / 4, per_row = (n_q + n_kv) * quads;
-    const int idx = blockIdx.x * 256 + tid;
-    const int i = idx / per_row, rem = idx - i * per_row, hh = rem / quads, ii = (rem - hh * quads) * 4;
-    const size_t row = (size_t)b * rm.R + min(i, rm.n - 1);
-    const float* src = qkv + row * ldqkv + hh * d + ii;
-    Partials4<NS> p1, p2;
-    p1.request(src, sps);
-    p2.request(src + half, sps);
-    const float4 c = *(const float4*)(cos_t + row * half + ii), s = *(const float4*)(sin_t + row * half + ii);
-    const int nv = rows_valid(rm, b), L = base_len[b];
-    if (L + nv > kv.max_seq) {  // would overrun the cache: refuse, flag
-      if (tid == 0 && blockIdx.x == 0) atomicOr(err_flag, 1);
-      return;
-    }
-    if (i >= nv) return;
-    const float4 x1 = p1.sum(), x2 = p2.sum();
-    float o1[4] = {x1.x * c.x - x2.x * s.x, x1.y * c.y - x2.y * s.y, x1.z * c.z - x2.z * s.z, x1.w * c.w - x2.w * s.w};
-    float o2[4] = {x2.x * c.x + x1.x * s.x, x2.y * c.y + x1.y * s.y, x2.z * c.z + x1.z * s.z, x2.w * c.w + x1.w * s.w};
-    if (hh < n_q) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) { o1[r] *= q_scale; o2[r] *= q_scale; }
-      planes4(q_hi, q_lo, row * ldq + hh * d + ii, o1);
-      planes4(q_hi, q_lo, row * ldq + hh * d + ii + half, o2);
-    } else {
-      const size_t base = kv_k_at(kv, b, L + i, hh - n_q);
-      planes4(kc, kc + kv.plane, base + kv_k_col(kv, ii), o1);
-      planes4(kc, kc + kv.plane, base + kv_k_col(kv, ii + half), o2);
-    }
-  } else {
-    const int n_eb = n_kv * d / 32;
-    const int vblk = blockIdx.x - qk_blocks, eb = vblk % n_eb, nb0 = (vblk / n_eb) * 64;
-    const int voff = (n_q + n_kv) * d + eb * 32;
-    Partials4<NS> p[2];
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int f = tid + 256 * j, node = min(nb0 + f / 8, rm.n - 1), e4 = (f % 8) * 4;
-      p[j].request(qkv + ((size_t)b * rm.R + node) * ldqkv + voff + e4, sps);
-    }
-    const int nv = rows_valid(rm, b), L = base_len[b];
-    if (L + nv > kv.max_seq) return;  // (flagged by the first block)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int f = tid + 256 * j, e4 = (f % 8) * 4;
-      const float4 v = p[j].sum();
-      tile[f / 8][e4] = v.x; tile[f / 8][e4 + 1] = v.y; tile[f / 8][e4 + 2] = v.z; tile[f / 8][e4 + 3] = v.w;
-    }
-    __syncthreads();
-    const int nl = tid % 64, node = nb0 + nl;
-    if (node >= nv) return;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int e = tid / 64 + 4 * j;
-      const float val = tile[nl][e];
-      const size_t at = kv_v_at(kv, b, (eb * 32 + e) / d, (eb * 32 + e) % d, L + node);
-      const bf16_t hb = f32_to_bf16(val);
-      vc[at] = hb;
-      vc[at + kv.plane] = f32_to_bf16(val - bf16_to_f32(hb));
-    }
-  }
-}
-
-void launch_rope_kv_write(const float* qkv, int ldqkv, int qkv_splits, size_t qkv_split_stride, const float* cos_t,
-                          const float* sin_t, float* q_out, int ldq,
-                          void* k_cache, void* v_cache, int kvdtype, KVLayout kv, const int* base_len, int n_q,
-                          RowMap rm, int* err_flag, bf16_t* q_hi, bf16_t* q_lo, float q_scale, hipStream_t st) {
-  if (kvdtype == 1 && q_hi && kv.d % 32 == 0 && ldqkv % 4 == 0 && qkv_split_stride % 4 == 0 && ldq % 4 == 0 && qkv_splits <= TILE_MAX_K_PARTS) {
-    const int per_row = (n_q + kv.n_kv) * (kv.d / 8);
-    const int qk_blocks = (rm.n * per_row + 255) / 256;
-    const int v_blocks = (kv.n_kv * kv.d / 32) * ((rm.n + 63) / 64);
-    with_count<1, TILE_MAX_K_PARTS>(qkv_splits, [&](auto nc) {
-      rope_kv_planes_kernel<decltype(nc)::value><<<dim3(qk_blocks + v_blocks, rm.B), 256, 0, st>>>(
-          qkv, ldqkv, qkv_split_stride, cos_t, sin_t, (bf16_t*)k_cache, (bf16_t*)v_cache, kv, base_len, n_q, rm,
-          err_flag, qk_blocks, q_hi, q_lo, ldq, q_scale);
-    });
-    return;
-  }
+void launch_rope_kv_write(const float* qkv, int ldqkv, const float* cos_t, const float* sin_t, float* q_out, int ldq, float* k_cache,
+                          float* v_cache, KVLayout kv, const int* base_len, int n_q, RowMap rm, int* err_flag, hipStream_t st) {
   const int vblocks = (kv.n_kv * kv.d + 7) / 8;
   const int hc = ((n_q + kv.n_kv) * (kv.d / 2) + 255) / 256;
-  dim3 grid(rm.n * hc + vblocks, rm.B);
-  if (kvdtype == 0)
-    rope_kv_write_kernel<float><<<grid, 256, 0, st>>>(qkv, ldqkv, qkv_splits, qkv_split_stride, cos_t, sin_t, q_out, ldq, (float*)k_cache,
-                                                      (float*)v_cache, kv, base_len, n_q, rm, err_flag, hc, q_hi, q_lo, q_scale);
-  else
-    rope_kv_write_kernel<bf16_t><<<grid, 256, 0, st>>>(qkv, ldqkv, qkv_splits, qkv_split_stride, cos_t, sin_t, q_out, ldq, (bf16_t*)k_cache,
-                                                       (bf16_t*)v_cache, kv, base_len, n_q, rm, err_flag, hc, q_hi, q_lo, q_scale);
+  rope_kv_write_kernel<<<dim3(rm.n * hc + vblocks, rm.B), 256, 0, st>>>(qkv, ldqkv, cos_t, sin_t, q_out, ldq, k_cache, v_cache, kv, base_len,
+                                                                        n_q, rm, err_flag, hc);
 }
 
 // ------------------------------------------------------------------------------------------
