@@ -359,7 +359,6 @@ void carve(clover_ctx* x, char* base, size_t* total) {
   x->d_lvl_nodes = cv.take<int>(R);
   x->d_anc = cv.take<unsigned long long>(2 * R);
   x->d_iv = cv.take<int>(2 * R);
-  x->d_meet = cv.take<unsigned>(TILE_MEETINGS * MEET_STRIDE);
   x->kc = cv.take<char>(x->k_layer_elems * x->kv_esz * c.n_layers);
   x->vc = cv.take<char>(x->v_layer_elems * x->kv_esz * c.n_layers);
   x->aug_kc = cv.take<char>(x->k_layer_elems * x->kv_esz * c.aug_layers);
@@ -436,6 +435,7 @@ void carve(clover_ctx* x, char* base, size_t* total) {
   b.pl_y = cv.take<float>(rows16 * 2 * H);
   static_cast<RowBufs&>(*x) = b;
   if (base) carve_passes(x, base + own, cv.off - own);
+  x->d_meet = cv.take<unsigned>(TILE_MEETINGS * MEET_STRIDE);   // (behind what passes lay out: it outlives them)
   *total = cv.off;
 }
 
@@ -478,17 +478,6 @@ int gemm_fast(clover_ctx* x, int cls, FragPlanes X, const void* W, int M, int N,
   g.k_parts = tile_gemm_pick_k_parts(M, N, K);
   launch_gemm_tile(g, x->st);
   return g.k_parts;
-}
-// a launch whose workgroups finish the tiles of several K ranges between them
-TileGemm exchanging_gemm(clover_ctx* x, FragPlanes X, const void* W, int M, int N, int K) {
-  TileGemm g;
-  memset(&g, 0, sizeof(g));
-  g.X = X;
-  g.W = (const bf16_t*)W;
-  g.M = M; g.N = N; g.K = K;
-  g.k_parts = tile_gemm_pick_k_parts(M, N, K);
-  g.part = x->partial; g.meet = x->d_meet; g.polls = tune_int("CLOVER_MEET_POLLS", MEET_POLLS);
-  return g;
 }
 // Y = X W^T + bias through the MFMA path, for the small draft-side linears
 void linear_fast(clover_ctx* x, FragPlanes X, const void* W, const void* bias, float* Y, int ldy, int M, int N, int K) {
@@ -536,12 +525,28 @@ void run_layer(clover_ctx* x, const clover_layer_weights& lw, float* xres, RowMa
     const FragPlanes A = frag_planes(x->a_norm, M), O = frag_planes(x->attn_out, M), Hf = frag_planes(x->h_ffn, M);
     bf16_t* const q_hi = (bf16_t*)x->q_rot;
     bf16_t* const q_lo = q_hi + (size_t)x->rows * x->NQD;
-    { Scope s(x, KC_GEMM_QKV);   // (rotation and cache write included)
-      TileGemm g = exchanging_gemm(x, A, lw.wq /* q, k and v rows */, M, x->QKVN, H);
-      g.epi = 3;
+    // Two to four ranges of K and up to 160 rows: the launch sums, rotates and stores by itself, which is faster than leaving that to a
+    // second one.  us, one launch and two: 64 rows 18.6 and 21.0, with 32 KV heads 27.5 and 29.8, 133 rows 27.3 and 27.8.  Eight ranges
+    // (up to 32 rows) meet later and leave eight parts to read: a step of 23 rows is 0.8 % slower so; 256 rows the same, 512 rows 0.5 %
+    // slower (a member has a dozen blocks to finish), one range (prompts) the same.  Heads of 64 have no second launch.
+    const int sq = tile_gemm_pick_k_parts(M, x->QKVN, H);
+    if (!x->attn_fast || (sq >= 2 && sq <= 4 && M <= 160)) {
+      Scope s(x, KC_GEMM_QKV);
+      TileGemmQkv g;
+      memset(&g, 0, sizeof(g));
+      g.X = A;
+      g.W = (const bf16_t*)lw.wq;   // q, k and v rows
+      g.M = M; g.N = x->QKVN; g.K = H; g.k_parts = sq;
+      g.part = x->partial; g.meet = x->d_meet; g.polls = tune_int("CLOVER_MEET_POLLS", MEET_POLLS);
       g.qkv = QkvOut{c.n_q_heads, d, x->attn_fast ? q_hi : nullptr, q_lo, 1.0f / sqrtf((float)d), x->q_rot, x->NQD,
                      (bf16_t*)kc_layer, (bf16_t*)vc_layer, kvl, x->cos_t, x->sin_t, base_len, rm, x->d_err};
-      launch_gemm_tile(g, x->st); }
+      launch_gemm_qkv(g, x->st);
+    } else {
+      gemm_fast(x, KC_GEMM_QKV, A, lw.wq, M, x->QKVN, H);
+      Scope s(x, KC_ROPE_KV);
+      launch_rope_kv_planes(x->partial, x->QKVN, sq, (size_t)M * x->QKVN, x->cos_t, x->sin_t, (bf16_t*)kc_layer, (bf16_t*)vc_layer, kvl,
+                            base_len, c.n_q_heads, rm, x->d_err, q_hi, q_lo, x->NQD, 1.0f / sqrtf((float)d), x->st);
+    }
     { Scope s(x, KC_ATTN);
       if (x->attn_fast) {
         AttnParams ap;

@@ -220,6 +220,10 @@ void launch_rmsnorm(const float* x, int ldx, const void* gain, int wdtype, float
                     int rows, hipStream_t st);
 void launch_rope_kv_write(const float* qkv, int ldqkv, const float* cos_t, const float* sin_t, float* q_out, int ldq, float* k_cache,
                           float* v_cache, KVLayout kv, const int* base_len, int n_q, RowMap rm, int* err_flag, hipStream_t st);
+// the same behind a QKV GEMM that left partial tiles, heads of q and k in rotary order; q as planes, caches of two planes
+void launch_rope_kv_planes(const float* qkv, int ldqkv, int splits, size_t split_stride, const float* cos_t, const float* sin_t, bf16_t* k_cache,
+                           bf16_t* v_cache, KVLayout kv, const int* base_len, int n_q, RowMap rm, int* err_flag, bf16_t* q_hi, bf16_t* q_lo,
+                           int ldq, float q_scale, hipStream_t st);
 void launch_attn_generic(const float* q, int ldq, const void* k_cache, const void* v_cache, int kvdtype, KVLayout kv,
                          const int* base_len, const unsigned long long* anc /*[n][2]*/, int n_q, float* out, int ldo,
                          FragPlanes planes /*instead of fp32 when planes.p is non-null*/, RowMap rm,
@@ -355,15 +359,18 @@ struct TileGemm {
   float* Y; int ldy;                  // epi 0: fp32 [M, N]; range r of K writes Y + r * split_stride
   FragPlanes out;                     // epi 1: planes of silu(X Wg^T) * (X Wu^T), [M, N]
   int M, N, K;
-  int epi;                            // 0 plain, 1 SwiGLU, 3 QKV
+  int epi;                            // 0 plain, 1 SwiGLU
   int k_parts; size_t split_stride;   // (split_stride: epi 0 only)
-  QkvOut qkv;                         // epi 3
-  // epi 3 over several ranges of K: their workgroups exchange partial tiles in `part` (tile_gemm_exchange_bytes) and finish the tile
-  // in shares, and meet in `meet`, TILE_MEETINGS words MEET_STRIDE apart (zero before the first launch that uses them)
+  int n_units;                        // filled in by launch_gemm_tile: column tiles x K ranges
+};
+// epi 3.  (Apart from the others, whose launches would otherwise carry the longer arguments: 0.2 us each.)
+struct TileGemmQkv : TileGemm {
+  QkvOut qkv;
+  // over several ranges of K: their workgroups exchange partial tiles in `part` (tile_gemm_exchange_bytes) and finish the tile in
+  // shares, and meet in `meet`, TILE_MEETINGS words MEET_STRIDE apart (zero before the first launch that uses them)
   float* part; unsigned* meet; int polls;
-  // filled in by launch_gemm_tile: column tiles x K ranges; row blocks of a row tile that has them all; 1: the ranges of a tile
-  // are on different XCDs
-  int n_units, row_blocks, spread;
+  // filled in by launch_gemm_qkv: row blocks of a row tile that has them all; 1: the ranges of a tile are on different XCDs
+  int row_blocks, spread;
 };
 constexpr int TILE_MEETINGS = 256, MEET_STRIDE = 16;
 constexpr int MEET_POLLS = 256;       // looks of a member at the word before it leaves its share to the last one (100 us or so)
@@ -371,6 +378,7 @@ constexpr int TILE_MAX_K_PARTS = 8;
 // K ranges of a narrow output; the same for all M that round up to the same multiple of 32
 int tile_gemm_pick_k_parts(int M, int N, int K);
 void launch_gemm_tile(const TileGemm& g, hipStream_t st);
+void launch_gemm_qkv(const TileGemmQkv& g, hipStream_t st);
 // bytes of `part` for M rows over k_parts ranges
 size_t tile_gemm_exchange_bytes(int M, int N, int K, int k_parts);
 // what launch_gemm_tile runs for M rows (N = F for epi 1; k_parts 0: its own choice)

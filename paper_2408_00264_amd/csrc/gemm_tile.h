@@ -226,10 +226,34 @@ struct QkvBlock {
   }
 };
 
+// The blocks of a member's share that come next: what they need besides their sums (epi 3).
+template <int EPI> using TileArgs = std::conditional_t<EPI == 3, TileGemmQkv, TileGemm>;
+template <int EPI, int NB>
+struct Pending {
+  __device__ __forceinline__ Pending(const TileGemm&, int, int, int, int, int, int, int) {}
+  __device__ __forceinline__ void request() {}
+};
+template <int NB>
+struct Pending<3, NB> {
+  const TileGemmQkv& p;
+  const int row0, col0, l16, g4, rows_here, cols_here;   // first row and column block of the tile; row and column blocks that it has
+  Walk walk;
+  QkvRow row;
+  QkvBlock blk[NB];
+  __device__ __forceinline__ Pending(const TileGemmQkv& p_, int row0_, int tile, int WB, int member, int wave, int l16_, int g4_)
+      : p(p_), row0(row0_), col0(tile * WB), l16(l16_), g4(g4_), rows_here(min(p_.row_blocks, (p_.M - row0_ + 15) / 16)),
+        cols_here(min(WB, p_.N / 16 - tile * WB)), walk(rows_here, wave, p_.k_parts, member) {}
+  __device__ __forceinline__ void request() {
+    row.request(p.qkv, row0 + walk.r * 16 + l16, p.M);
+#pragma unroll
+    for (int i = 0; i < NB; ++i) blk[i].request(p.qkv, row, col0 + walk.c + i * walk.c_step, g4);
+  }
+};
+
 // NT: non-temporal loads, for weights that no other workgroup reads (gate+up at 64 rows 47.0 -> 44.6 us; where row tiles
 // share them it costs: 256 rows 96.5 -> 100).
 template <int RB, int WB, int EPI, bool NT>
-__global__ __launch_bounds__(256, 1) void gemm_tile_kernel(TileGemm p) {
+__global__ __launch_bounds__(256, 1) void gemm_tile_kernel(TileArgs<EPI> p) {
   using T = TileShape<RB, WB>;
   constexpr int XF = T::XF, WF = T::WF, WREST = T::WREST, STAGE = T::STAGE, NBUF = T::NBUF;
   constexpr int KS = T::KS, RBT = T::RBT, RBW = T::RBW, CBW = T::CBW;
@@ -254,7 +278,9 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(TileGemm p) {
     unit = (j / rt) * 8 + xcd;
   }
   int part, tile;
-  if (EPI >= 2 && p.k_parts > 1 && !p.spread) {
+  bool together = false;   // the ranges of a tile on one XCD
+  if constexpr (EPI == 3) together = p.k_parts > 1 && !p.spread;
+  if (together) {
     // The workgroups that exchange partial tiles share an XCD: they meet in its L2 (8 of 32 KB each: 1.8 us, on different XCDs 5.5).
     // Each XCD has a range of adjacent tiles and the ranges of K are interleaved, stage by stage, so the whole launch still walks
     // the matrix side by side (33 MB streamed so 6.6 us, with contiguous ranges 7.4).
@@ -269,23 +295,15 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(TileGemm p) {
     tile = unit / p.k_parts;
   }
   const int NS = p.K / (TL_KST * KS) / p.k_parts;      // stages of this workgroup's K range
-  const int kt0 = EPI >= 2 ? part * KS : part * NS * KS;
+  const int kt0 = EPI == 3 ? part * KS : part * NS * KS;
   const int row0 = rh * 16 * RBT;
 
   // ---- exchange: what the first blocks of the workgroup's share need besides their sums is requested in front of everything else
   // (tiles of up to 128 rows have the registers to keep it) ----
-  constexpr int NB = EPI == 3 ? 2 : 1;   // blocks at a time
+  constexpr int NB = 2;   // blocks at a time
   constexpr bool EARLY = RB <= 4;
-  const int rows_here = min(p.row_blocks, (p.M - row0 + 15) / 16), cols_here = min(WB, p.N / 16 - tile * WB);
-  Walk walk(rows_here, wave, p.k_parts, part);
-  QkvRow frow;
-  QkvBlock fblk[NB];
-  auto request = [&]() __attribute__((always_inline)) {
-    frow.request(p.qkv, row0 + walk.r * 16 + l16, p.M);
-#pragma unroll
-    for (int i = 0; i < NB; ++i) fblk[i].request(p.qkv, frow, tile * WB + walk.c + i * walk.c_step, g4);
-  };
-  if (EPI == 3 && EARLY && p.k_parts > 1) request();
+  Pending<EPI, NB> next(p, row0, tile, WB, part, wave, l16, g4);
+  if (EPI == 3 && EARLY && p.k_parts > 1) next.request();
 
   // ---- staging: activation block f of a stage = (row block f / 2, plane f % 2), weight block c = 16 rows of W (epi 1:
   // 8 gate and the 8 up rows of the same F columns, so that a lane pair (l, l + 32) ends up with both factors).  Row
@@ -347,7 +365,7 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(TileGemm p) {
       else asm volatile("global_load_lds_dwordx4 %0, %1" : : "v"(off), "s"(src));
     }
   };
-  const size_t n_between = EPI >= 2 ? p.k_parts : 1, xstep = n_between * KS * xstage, wstep = n_between * KS * wstage;
+  const size_t n_between = EPI == 3 ? p.k_parts : 1, xstep = n_between * KS * xstage, wstep = n_between * KS * wstage;
   // (xp, wp) from stage t to t + 1, or not behind the last one: that one is requested again, into a buffer that nothing reads
   // any more; those loads hit the cache, and a loop without conditions keeps the accumulators in place -- with separate
   // code for the last NBUF stages the allocator moved all of them at every hand-over
@@ -470,7 +488,7 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(TileGemm p) {
       if (m < p.M && col < p.N)
         *(u32x4*)(p.out.p + frag_at(p.out, m, col) + plane * 512) = *(const u32x4*)(sm + plane * PLANE + row * LD + pc * 16);
     }
-  } else if (EPI == 3) {
+  } else if constexpr (EPI == 3) {
     if (p.k_parts == 1) {
       // the wavefront's blocks through its part of the LDS, as many columns at a time as fit, so that what is done with a block is
       // there once (unrolled over 64 accumulators it did not fit the registers)
@@ -518,7 +536,7 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(TileGemm p) {
     __syncthreads();
     unsigned* const todo = (unsigned*)sm;
     if (tid == 0) *todo = meet(DeviceWord{p.meet + (size_t)(rh * tiles + tile) * MEET_STRIDE}, (unsigned)S, (unsigned)part, p.polls);
-    if (!EARLY) request();
+    if (!EARLY) next.request();
     __syncthreads();
     // (its own share; those of members that did not wait, if it came last)
     auto finish = [&](auto nc) __attribute__((always_inline)) {
@@ -530,14 +548,14 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(TileGemm p) {
           auto fetch = [&]() __attribute__((always_inline)) {
 #pragma unroll
             for (int i = 0; i < NB; ++i) {
-              const int c = walk.c + i * walk.c_step;
-              const unsigned off = walk.r < rows_here && c < cols_here ? (unsigned)(walk.r * WB + c) * 1024u + lane16 : 0x70000000u;
+              const int c = next.walk.c + i * next.walk.c_step;
+              const unsigned off = next.walk.r < next.rows_here && c < next.cols_here ? (unsigned)(next.walk.r * WB + c) * 1024u + lane16 : 0x70000000u;
 #pragma unroll
               for (int s = 0; s < NS; ++s) q[i][s] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(parts, off + (unsigned)(s * U) * 1024u, 0, DEVICE_SCOPE));
             }
           };
           fetch();
-          while (walk.r < rows_here) {
+          while (next.walk.r < next.rows_here) {
             f32x4 v[NB];
 #pragma unroll
             for (int i = 0; i < NB; ++i) {
@@ -545,28 +563,28 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(TileGemm p) {
 #pragma unroll
               for (int s = 1; s < NS; ++s) v[i] += q[i][s];
             }
-            QkvRow row = frow;
+            QkvRow row = next.row;
             QkvBlock blk[NB];
-            const int c_now = walk.c, c_step = walk.c_step;
+            const int c_now = next.walk.c, c_step = next.walk.c_step;
 #pragma unroll
-            for (int i = 0; i < NB; ++i) blk[i] = fblk[i];
+            for (int i = 0; i < NB; ++i) blk[i] = next.blk[i];
             // what is next is requested in front of the stores: a load behind them would wait for them
-            walk.next(NB, cols_here);
-            request();
+            next.walk.next(NB, next.cols_here);
+            next.request();
             fetch();
             row.request_page(p.qkv);
             if (row.here) {
 #pragma unroll
               for (int i = 0; i < NB; ++i)
-                if (c_now + i * c_step < cols_here) blk[i].put(p.qkv, row, v[i], g4);
+                if (c_now + i * c_step < next.cols_here) blk[i].put(p.qkv, row, v[i], g4);
             }
           }
         }
         left &= ~(1u << who);
         if (left == 0u) return;
         who = __builtin_ctz(left);
-        walk = Walk(rows_here, wave, S, who);
-        request();
+        next.walk = Walk(next.rows_here, wave, S, who);
+        next.request();
       }
     };
     if (S <= 4) finish(std::integral_constant<int, 4>{});
@@ -588,14 +606,14 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(TileGemm p) {
 }
 
 template <int RB, int WB, int EPI, bool NT>
-void launch_tile_one(const TileGemm& g, int wgs, hipStream_t st) {
+void launch_tile_one(const TileArgs<EPI>& g, int wgs, hipStream_t st) {
   constexpr int lds = TileShape<RB, WB>::LDS;
   static OncePerDevice once;
   allow_dynamic_lds(once, (const void*)gemm_tile_kernel<RB, WB, EPI, NT>, lds);
   gemm_tile_kernel<RB, WB, EPI, NT><<<wgs, 256, lds, st>>>(g);
 }
 template <int EPI, bool NT>
-void launch_tile_many(const TileGemm& g, int rb, int wb, int wgs, hipStream_t st) {   // rb 3..5, wb 8, 12, 14, 16; rb 3, wb 6
+void launch_tile_many(const TileArgs<EPI>& g, int rb, int wb, int wgs, hipStream_t st) {   // rb 3..5, wb 8, 12, 14, 16; rb 3, wb 6
 #define CLV_TL(RB_)                                                   \
   if (wb == 8) launch_tile_one<RB_, 8, EPI, NT>(g, wgs, st);          \
   else if (wb == 12) launch_tile_one<RB_, 12, EPI, NT>(g, wgs, st);   \
@@ -606,13 +624,13 @@ void launch_tile_many(const TileGemm& g, int rb, int wb, int wgs, hipStream_t st
 #undef CLV_TL
 }
 template <int EPI>
-void launch_tile_big(const TileGemm& g, int wb, int wgs, hipStream_t st) {   // rb 8 (always several row tiles): wb 12, 14, 16
+void launch_tile_big(const TileArgs<EPI>& g, int wb, int wgs, hipStream_t st) {   // rb 8 (always several row tiles): wb 12, 14, 16
   if (wb == 12) launch_tile_one<8, 12, EPI, false>(g, wgs, st);
   else if (wb == 14) launch_tile_one<8, 14, EPI, false>(g, wgs, st);
   else launch_tile_one<8, 16, EPI, false>(g, wgs, st);
 }
 template <int EPI>
-void launch_tile_few(const TileGemm& g, int rb, int wb, int wgs, hipStream_t st) {    // rb 0: wb 8, 12; rb 1: wb 6, 7, 8, 12; rb 2: wb 6, 7, 8, 12, 16
+void launch_tile_few(const TileArgs<EPI>& g, int rb, int wb, int wgs, hipStream_t st) {    // rb 0: wb 8, 12; rb 1: wb 6, 7, 8, 12; rb 2: wb 6, 7, 8, 12, 16
   if (rb == 0 && wb == 8) launch_tile_one<0, 8, EPI, true>(g, wgs, st);
   else if (rb == 0) launch_tile_one<0, 12, EPI, true>(g, wgs, st);
   else if (rb == 1 && wb == 6) launch_tile_one<1, 6, EPI, true>(g, wgs, st);
@@ -628,7 +646,7 @@ void launch_tile_few(const TileGemm& g, int rb, int wb, int wgs, hipStream_t st)
 
 // one form of the kernel; which of them, pick_tile (kernels_tile.hip)
 template <int EPI>
-void launch_tile(const TileGemm& g, const TileForm& t, int wgs, hipStream_t st) {
+void launch_tile(const TileArgs<EPI>& g, const TileForm& t, int wgs, hipStream_t st) {
   if (t.rb == 8) launch_tile_big<EPI>(g, t.wb, wgs, st);
   else if (t.rb < 3) launch_tile_few<EPI>(g, t.rb, t.wb, wgs, st);
   else if (t.row_tiles > 1) launch_tile_many<EPI, false>(g, t.rb, t.wb, wgs, st);

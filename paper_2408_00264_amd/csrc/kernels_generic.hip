@@ -121,10 +121,26 @@ __global__ void rope_kv_write_kernel(const float* __restrict__ qkv, int ldqkv, c
   }
 }
 
-// The K ranges are counted at compile time: every load of a thread is requested in
+// The same operation for launches of the MFMA path whose QKV GEMM does not do it itself (heads of q and k in rotary order, q as pre-scaled bf16 planes, bf16-plane caches), vectorised:
+// a thread of the first blocks rotates four adjacent channels of one head (float4 loads of every partial, issued
+// before anything else is waited for; 8-byte plane stores); the last blocks transpose 64 nodes x 32 channels of V
+// through LDS so that the partials are read along the channels and V^T is written along the nodes.
+__device__ __forceinline__ void planes4(bf16_t* hi, bf16_t* lo, size_t off, const float (&o)[4]) {
+  unsigned h[4], l[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const bf16_t hb = f32_to_bf16(o[r]);
+    h[r] = hb;
+    l[r] = f32_to_bf16(o[r] - bf16_to_f32(hb));
+  }
+  *(uint2*)(hi + off) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
+  *(uint2*)(lo + off) = make_uint2(l[0] | (l[1] << 16), l[2] | (l[3] << 16));
+}
+// The K ranges are counted at compile time here and in reduce_add_norm_kernel: every load of a thread is requested in
 // straight-line code before the first is used.  With a runtime count the two halves of a pair were one round trip to memory
 // after the other, and most of the instructions were branches around loads of ranges that do not exist.  us per launch:
-// reduce_add_norm of 512 rows x 2 ranges 12.5 -> 10.0, 1024 x 1 17.9 -> 14.2, 2048 x 1 31.9 -> 26.2.
+// reduce_add_norm of 512 rows x 2 ranges 12.5 -> 10.0, 1024 x 1 17.9 -> 14.2, 2048 x 1 31.9 -> 26.2; rope_kv_planes of one row
+// x 8 ranges 5.6 -> 5.1, 64 x 4 5.2 -> 5.1, 512 x 2 10.8 -> 10.4.
 template <int NS>
 struct Partials4 {
   float4 q[NS];
@@ -144,6 +160,93 @@ struct Partials4<0> {
   __device__ __forceinline__ void request(const float*, size_t) {}
   __device__ __forceinline__ float4 add_to(float4 v) const { return v; }
 };
+template <int NS>
+__global__ __launch_bounds__(256) void rope_kv_planes_kernel(const float* __restrict__ qkv, int ldqkv, size_t sps,
+                                                             const float* __restrict__ cos_t, const float* __restrict__ sin_t,
+                                                             bf16_t* __restrict__ kc, bf16_t* __restrict__ vc, KVLayout kv,
+                                                             const int* __restrict__ base_len, int n_q, RowMap rm,
+                                                             int* err_flag, int qk_blocks, bf16_t* __restrict__ q_hi,
+                                                             bf16_t* __restrict__ q_lo, int ldq, float q_scale) {
+  __shared__ float tile[64][33];
+  const int b = blockIdx.y, tid = threadIdx.x;
+  const int d = kv.d, half = d / 2, n_kv = kv.n_kv;
+  if ((int)blockIdx.x < qk_blocks) {
+    // four of a head's channels in rotary order (launch_pack_weight) to a thread, so that the partials are read as they lie; the
+    // channels that are rotated with them are two lanes away
+    const int quads = d / 4, per_row = (n_q + n_kv) * quads;
+    const int idx = blockIdx.x * 256 + tid;
+    const int i = idx / per_row, rem = idx - i * per_row, hh = rem / quads, p4 = rem - hh * quads, ii = (p4 >> 2) * 8 + (p4 & 1) * 4;
+    const bool second = p4 & 2;
+    const size_t row = (size_t)b * rm.R + min(i, rm.n - 1);
+    Partials4<NS> p;
+    p.request(qkv + row * ldqkv + rem * 4, sps);
+    const float4 c = *(const float4*)(cos_t + row * half + ii), s = *(const float4*)(sin_t + row * half + ii);
+    const int nv = rows_valid(rm, b), L = base_len[b];
+    if (L + nv > kv.max_seq) {  // would overrun the cache: refuse, flag
+      if (tid == 0 && blockIdx.x == 0) atomicOr(err_flag, 1);
+      return;
+    }
+    if (i >= nv) return;   // (four adjacent lanes have one row)
+    const float4 v = p.sum();
+    const float x[4] = {v.x, v.y, v.z, v.w}, cs[4] = {c.x, c.y, c.z, c.w}, sn[4] = {s.x, s.y, s.z, s.w};
+    float o[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float y = __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x[r]), 0x4e, 0xf, 0xf, false));   // quad_perm 2 3 0 1
+      o[r] = second ? x[r] * cs[r] + y * sn[r] : x[r] * cs[r] - y * sn[r];
+    }
+    const int col = ii + (second ? half : 0);
+    if (hh < n_q) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) o[r] *= q_scale;
+      planes4(q_hi, q_lo, row * ldq + hh * d + col, o);
+    } else {
+      planes4(kc, kc + kv.plane, kv_k_at(kv, b, L + i, hh - n_q) + kv_k_col(kv, col), o);
+    }
+  } else {
+    const int n_eb = n_kv * d / 32;
+    const int vblk = blockIdx.x - qk_blocks, eb = vblk % n_eb, nb0 = (vblk / n_eb) * 64;
+    const int voff = (n_q + n_kv) * d + eb * 32;
+    Partials4<NS> p[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int f = tid + 256 * j, node = min(nb0 + f / 8, rm.n - 1), e4 = (f % 8) * 4;
+      p[j].request(qkv + ((size_t)b * rm.R + node) * ldqkv + voff + e4, sps);
+    }
+    const int nv = rows_valid(rm, b), L = base_len[b];
+    if (L + nv > kv.max_seq) return;  // (flagged by the first block)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int f = tid + 256 * j, e4 = (f % 8) * 4;
+      const float4 v = p[j].sum();
+      tile[f / 8][e4] = v.x; tile[f / 8][e4 + 1] = v.y; tile[f / 8][e4 + 2] = v.z; tile[f / 8][e4 + 3] = v.w;
+    }
+    __syncthreads();
+    const int nl = tid % 64, node = nb0 + nl;
+    if (node >= nv) return;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int e = tid / 64 + 4 * j;
+      const float val = tile[nl][e];
+      const size_t at = kv_v_at(kv, b, (eb * 32 + e) / d, (eb * 32 + e) % d, L + node);
+      const bf16_t hb = f32_to_bf16(val);
+      vc[at] = hb;
+      vc[at + kv.plane] = f32_to_bf16(val - bf16_to_f32(hb));
+    }
+  }
+}
+
+void launch_rope_kv_planes(const float* qkv, int ldqkv, int splits, size_t split_stride, const float* cos_t, const float* sin_t, bf16_t* k_cache,
+                           bf16_t* v_cache, KVLayout kv, const int* base_len, int n_q, RowMap rm, int* err_flag, bf16_t* q_hi, bf16_t* q_lo,
+                           int ldq, float q_scale, hipStream_t st) {
+  const int per_row = (n_q + kv.n_kv) * (kv.d / 4);
+  const int qk_blocks = (rm.n * per_row + 255) / 256;
+  const int v_blocks = (kv.n_kv * kv.d / 32) * ((rm.n + 63) / 64);
+  with_count<1, TILE_MAX_K_PARTS>(splits, [&](auto nc) {
+    rope_kv_planes_kernel<decltype(nc)::value><<<dim3(qk_blocks + v_blocks, rm.B), 256, 0, st>>>(
+        qkv, ldqkv, split_stride, cos_t, sin_t, k_cache, v_cache, kv, base_len, n_q, rm, err_flag, qk_blocks, q_hi, q_lo, ldq, q_scale);
+  });
+}
 void launch_rope_kv_write(const float* qkv, int ldqkv, const float* cos_t, const float* sin_t, float* q_out, int ldq, float* k_cache,
                           float* v_cache, KVLayout kv, const int* base_len, int n_q, RowMap rm, int* err_flag, hipStream_t st) {
   const int vblocks = (kv.n_kv * kv.d + 7) / 8;

@@ -10,7 +10,7 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 void launch_tile_plain(const TileGemm& g, const TileForm& t, int wgs, hipStream_t st);
 void launch_tile_swiglu(const TileGemm& g, const TileForm& t, int wgs, hipStream_t st);
-void launch_tile_qkv(const TileGemm& g, const TileForm& t, int wgs, hipStream_t st);
+void launch_tile_qkv(const TileGemmQkv& g, const TileForm& t, int wgs, hipStream_t st);
 
 namespace {
 
@@ -96,20 +96,26 @@ size_t tile_gemm_exchange_bytes(int M, int N, int K, int k_parts) {
 void launch_gemm_tile(const TileGemm& g_in, hipStream_t st) {
   TileGemm g = g_in;
   if (g.k_parts < 1 || g.epi == 1) g.k_parts = 1;
-  const TileForm t = tile_gemm_form(g.M, g.N, g.K, g.epi == 1, g.k_parts);
-  const int blocks = g.epi == 1 ? g.N / 8 : g.N / 16, rt = t.row_tiles, tiles = (blocks + t.wb - 1) / t.wb;
+  const TileForm t = tile_gemm_form(g.M, g.N, g.K, g.epi, g.k_parts);
+  const int blocks = g.epi == 1 ? g.N / 8 : g.N / 16, rt = t.row_tiles;
+  g.n_units = (blocks + t.wb - 1) / t.wb * g.k_parts;
+  const int wgs = rt > 1 ? (g.n_units + 7) / 8 * 8 * rt : g.n_units;
+  (g.epi == 1 ? launch_tile_swiglu : launch_tile_plain)(g, t, wgs, st);
+}
+
+void launch_gemm_qkv(const TileGemmQkv& g_in, hipStream_t st) {
+  TileGemmQkv g = g_in;
+  const TileForm t = tile_gemm_form(g.M, g.N, g.K, 0, g.k_parts);
+  const int rt = t.row_tiles, tiles = (g.N / 16 + t.wb - 1) / t.wb, per_xcd = (tiles + 7) / 8 * rt * g.k_parts;
   g.n_units = tiles * g.k_parts;
+  g.row_blocks = std::min(t.rb == 0 ? 1 : 2 * t.rb, (g.M + 15) / 16);
+  g.spread = per_xcd > TL_CUS / 8;   // (a member of a second round would keep those of the first waiting)
   int wgs = rt > 1 ? (g.n_units + 7) / 8 * 8 * rt : g.n_units;
-  if (g.epi >= 2) {
-    g.row_blocks = std::min(t.rb == 0 ? 1 : 2 * t.rb, (g.M + 15) / 16);
-    const int per_xcd = (tiles + 7) / 8 * rt * g.k_parts;
-    g.spread = per_xcd > TL_CUS / 8;   // (a member of a second round would keep those of the first waiting)
-    if (g.k_parts > 1) {
-      if (tiles * rt > TILE_MEETINGS) { g_not_launched = "more tiles than meetings"; return; }
-      if (!g.spread) wgs = 8 * per_xcd;
-    }
+  if (g.k_parts > 1) {
+    if (tiles * rt > TILE_MEETINGS) { g_not_launched = "more tiles than meetings"; return; }
+    if (!g.spread) wgs = 8 * per_xcd;
   }
-  (g.epi == 1 ? launch_tile_swiglu : g.epi == 3 ? launch_tile_qkv : launch_tile_plain)(g, t, wgs, st);
+  launch_tile_qkv(g, t, wgs, st);
 }
 
 // ------------------------------------------------------------------------------------------

@@ -2,5 +2,5 @@
 #include "gemm_tile.h"
 
 namespace clv {
-void launch_tile_qkv(const TileGemm& g, const TileForm& t, int wgs, hipStream_t st) { launch_tile<3>(g, t, wgs, st); }
+void launch_tile_qkv(const TileGemmQkv& g, const TileForm& t, int wgs, hipStream_t st) { launch_tile<3>(g, t, wgs, st); }
 }  // namespace clv
