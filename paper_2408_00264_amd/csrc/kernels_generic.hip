@@ -262,7 +262,7 @@ void launch_rope_kv_write(const float* qkv, int ldqkv, const float* cos_t, const
 // iv != null: new row w is visible to row i iff enter[w] <= enter[i] <= exit[w] (interval labels, two ints per node).
 // ------------------------------------------------------------------------------------------
 // What bounds it: memory round trips.  A lane fetches its key's row and its channel's 64 values in 16-byte pieces that are all
-// requested before the first is used (3 launches of 16 rows x 80 keys: 64 us with one 4-byte load after the other, 22 so).
+// requested before the first is used.  (fp32 caches: attn_fp32_kernel below.)
 // Tiles that are hidden from a row altogether are not loaded, and a chain's row ends with its own tile (bf16 model with heads of
 // 64, 1000 tokens in one pass: 1300 -> 730 us a layer; fp32 with heads of 128: 880 -> 480).
 __device__ __forceinline__ float4 ldkv4(const float* p, size_t i, size_t) { return *(const float4*)(p + i); }
@@ -375,20 +375,152 @@ __global__ __launch_bounds__(64) void attn_generic_kernel(const float* __restric
   }
 }
 
+// The same over fp32 caches, a workgroup of one to four wavefronts that share a row's key tiles.  What bounds it: memory round trips,
+// and the load path of a compute unit, which takes a clock or more per line that an instruction touches.  So a page of K, [32][D],
+// and of V^T, [D][32], is read as it lies, a KB per instruction: D / 4 lanes have a key's row and add their products up between them, 8
+// lanes have a channel's 32 positions and add theirs up once, at the end.  (With a lane per key, and per channel, 64 lines per
+// instruction and one wavefront, us per launch, 4 heads of 64: 16 nodes at 64 keys 7.3 -> 5.6, by events 64 nodes at 300 15.8 -> 9.5, 16 at
+// 900 31 -> 12.5; 8 heads of 128: 16 nodes at 300 keys 19.3 -> 12.6, at 2000 95 -> 32, 128 at 2000 235 -> 77.)
+// Wavefronts of a row and head: as many as the chip has idle SIMDs for (one / two / four, 8 heads of 128 at 300 keys: 512 rows x heads
+// 24.8, 16.9, 15.1, 1024 29.2, 22.2, 25.7; at 2000 keys 107, 65, 45 and 119, 77, 79).
+constexpr int AF_WAVES = 4;   // most wavefronts of a row and head
+template <int CTRL>
+__device__ __forceinline__ float dpp_add(float v) {   // v + the lane's that CTRL names, all of which have one
+  return v + __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), CTRL, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float sum_of_8(float v) { return dpp_add<0x141>(dpp_add<0x4e>(dpp_add<0xb1>(v))); }   // quad_perm, quad_perm, row_half_mirror
+template <int D>
+__global__ __launch_bounds__(64 * AF_WAVES) void attn_fp32_kernel(const float* __restrict__ q, int ldq, const float* __restrict__ kc,
+                                                                  const float* __restrict__ vc, KVLayout kv, const int* __restrict__ base_len,
+                                                                  const unsigned long long* __restrict__ anc, int n_q, float* __restrict__ out,
+                                                                  int ldo, RowMap rm, int anc_stride, const int* __restrict__ iv) {
+  constexpr int LPK = D / 4, KPI = 64 / LPK, NP = D / 8;   // lanes of a key, keys of a load, loads of a page
+  __shared__ __attribute__((aligned(16))) float ps_all[AF_WAVES][64];
+  __shared__ float all_m[AF_WAVES], all_l[AF_WAVES], all_o[AF_WAVES][D];
+  const int h = blockIdx.x, i = blockIdx.y, b = blockIdx.z, lane = threadIdx.x & 63, waves = blockDim.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  float* const ps = ps_all[wave];
+  const size_t row = (size_t)b * rm.R + i;
+  const bool chain = anc == nullptr && iv == nullptr, bits = anc != nullptr && iv == nullptr;
+  const int nv = rows_valid(rm, b), L = base_len[b];
+  const unsigned long long a0 = bits ? anc[2 * ((size_t)b * anc_stride + i)] : 0ull;
+  const unsigned long long a1 = bits ? anc[2 * ((size_t)b * anc_stride + i) + 1] : 0ull;
+  const int my_enter = iv ? iv[2 * ((size_t)b * anc_stride + i)] : 0;
+  const int x = lane % LPK, key = KPI * x + lane / LPK;   // the lane's four channels of q and k; its key of a tile for the soft-max
+  float4 qv = *(const float4*)(q + row * ldq + h * D + 4 * x);
+  if (i >= nv || L + nv > kv.max_seq) return;   // (whole workgroup)
+  const float scale = 1.0f / sqrtf((float)D);
+  qv.x *= scale; qv.y *= scale; qv.z *= scale; qv.w *= scale;
+  const int g = h / (n_q / kv.n_kv);
+  float mrun = -INFINITY, lrun = 0.f, o[NP];   // o: channel 8 c + lane / 8, the lane's positions only
+#pragma unroll
+  for (int c = 0; c < NP; ++c) o[c] = 0.f;
+  const int total = L + (chain ? i + 1 : rm.n);   // (a chain's row sees nothing behind itself)
+  const int ntiles = (total + 63) / 64;
+  for (int t = wave; t < ntiles; t += waves) {
+    const int s = t * 64 + key;
+    bool vis = s < L;
+    if (!vis && s < total) {
+      const int w = s - L;
+      if (chain) vis = true;
+      else if (iv) vis = iv[2 * ((size_t)b * anc_stride + w)] <= my_enter && my_enter <= iv[2 * ((size_t)b * anc_stride + w) + 1];
+      else vis = ((w < 64 ? (a0 >> w) : (a1 >> (w - 64))) & 1ull) != 0ull;
+    }
+    if (__builtin_amdgcn_ballot_w64(vis) == 0ull) continue;   // uniform: nothing of a hidden tile is loaded
+    // (a page behind the cache's last one is read from there and never used)
+    const size_t at[2] = {kv_block(kv, b, t * 64, g) + lane * 4, kv_block(kv, b, min(t * 64 + KV_PAGE, kv.max_seq - 1), g) + lane * 4};
+    float4 kx[2][NP], vx[2][NP];
+#pragma unroll
+    for (int pg = 0; pg < 2; ++pg)
+#pragma unroll
+      for (int c = 0; c < NP; ++c) kx[pg][c] = *(const float4*)(kc + at[pg] + c * 256);
+    auto load_v = [&](int pg) __attribute__((always_inline)) {
+#pragma unroll
+      for (int c = 0; c < NP; ++c) vx[pg][c] = *(const float4*)(vc + at[pg] + c * 256);
+    };
+    load_v(0);
+    if (D == 64) load_v(1);
+    float sc = -INFINITY;
+#pragma unroll
+    for (int pg = 0; pg < 2; ++pg)
+#pragma unroll
+      for (int c = 0; c < NP; ++c) {   // keys KPI (NP pg + c) ..: every lane of a key ends up with its score
+        const float4 k4 = kx[pg][c];
+        float v = dpp_add<0x140>(sum_of_8(qv.x * k4.x + qv.y * k4.y + qv.z * k4.z + qv.w * k4.w));   // row_mirror
+        if (D == 128) v += __shfl_xor(v, 16, 64);
+        sc = x == NP * pg + c ? v : sc;
+      }
+    if (D != 64) load_v(1);
+    sc = vis ? sc : -INFINITY;
+    const float mnew = fmaxf(mrun, wave_max(sc));
+    if (mnew == -INFINITY) continue;  // uniform across the wave (every visible score is)
+    const float p = vis ? expf(sc - mnew) : 0.f;
+    const float corr = (mrun == -INFINITY) ? 0.f : expf(mrun - mnew);
+    mrun = mnew;
+    // (the wavefront's own LDS words, which it accesses in order; only the compiler has to keep to it)
+    __builtin_amdgcn_wave_barrier();
+    asm volatile("" ::: "memory");
+    ps[key] = p;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+    lrun = lrun * corr + p;   // (the lane's share)
+#pragma unroll
+    for (int c = 0; c < NP; ++c) o[c] *= corr;
+#pragma unroll
+    for (int pg = 0; pg < 2; ++pg) {
+      const float4 pj = *(const float4*)(ps + pg * KV_PAGE + (lane & 7) * 4);
+#pragma unroll
+      for (int c = 0; c < NP; ++c) {   // (a hidden key's value, or an unwritten slot's, has no part in the sum whatever it holds)
+        const float4 v4 = vx[pg][c];
+        o[c] += pj.x != 0.f ? pj.x * v4.x : 0.f;
+        o[c] += pj.y != 0.f ? pj.y * v4.y : 0.f;
+        o[c] += pj.z != 0.f ? pj.z * v4.z : 0.f;
+        o[c] += pj.w != 0.f ? pj.w * v4.w : 0.f;
+      }
+    }
+  }
+  // the wavefronts' results relative to the largest of their references, in their order
+  lrun = wave_sum(lrun);
+#pragma unroll
+  for (int c = 0; c < NP; ++c) {
+    o[c] = sum_of_8(o[c]);
+    if ((lane & 7) == 0) all_o[wave][8 * c + lane / 8] = o[c];
+  }
+  if (lane == 0) { all_m[wave] = mrun; all_l[wave] = lrun; }
+  __syncthreads();
+  float m = -INFINITY, l = 0.f;
+  for (int w = 0; w < waves; ++w) m = fmaxf(m, all_m[w]);
+  for (int c = threadIdx.x; c < D; c += blockDim.x) {
+    float v = 0.f;
+    l = 0.f;
+    for (int w = 0; w < waves; ++w) {
+      if (all_m[w] == -INFINITY) continue;   // (saw no key)
+      const float f = expf(all_m[w] - m);
+      l += f * all_l[w];
+      v += f * all_o[w][c];
+    }
+    out[row * ldo + h * D + c] = v * (1.0f / l);
+  }
+}
+
 void launch_attn_generic(const float* q, int ldq, const void* k_cache, const void* v_cache, int kvdtype, KVLayout kv,
                          const int* base_len, const unsigned long long* anc, int n_q, float* out, int ldo,
                          FragPlanes planes, RowMap rm, hipStream_t st, int anc_stride, const int* iv) {
   const dim3 grid(n_q, rm.n, rm.B);
-  auto go = [&](auto kc, auto vc, auto dc) {
-    using KT = std::remove_const_t<std::remove_pointer_t<decltype(kc)>>;
-    attn_generic_kernel<KT, decltype(dc)::value><<<grid, 64, 0, st>>>(q, ldq, kc, vc, kv, base_len, anc, n_q, out, ldo, planes, rm, anc_stride, iv);
+  auto go = [&](auto dc) {   // head_dim is 64 or 128
+    constexpr int D = decltype(dc)::value;
+    if (kvdtype == 0) {
+      const size_t wgs = (size_t)n_q * rm.n * rm.B;
+      const int waves = tune_int("CLOVER_AF_WAVES", wgs <= 512 ? 4 : wgs <= 1024 ? 2 : 1);
+      attn_fp32_kernel<D><<<grid, 64 * waves, 0, st>>>(q, ldq, (const float*)k_cache, (const float*)v_cache, kv, base_len, anc, n_q, out, ldo,
+                                                       rm, anc_stride, iv);
+    } else {
+      attn_generic_kernel<bf16_t, D><<<grid, 64, 0, st>>>(q, ldq, (const bf16_t*)k_cache, (const bf16_t*)v_cache, kv, base_len, anc, n_q, out,
+                                                          ldo, planes, rm, anc_stride, iv);
+    }
   };
-  auto with_d = [&](auto kc, auto vc) {   // head_dim is 64 or 128
-    if (kv.d == 64) go(kc, vc, std::integral_constant<int, 64>{});
-    else go(kc, vc, std::integral_constant<int, 128>{});
-  };
-  if (kvdtype == 0) with_d((const float*)k_cache, (const float*)v_cache);
-  else with_d((const bf16_t*)k_cache, (const bf16_t*)v_cache);
+  if (kv.d == 64) go(std::integral_constant<int, 64>{});
+  else go(std::integral_constant<int, 128>{});
 }
 
 // ------------------------------------------------------------------------------------------
