@@ -2,6 +2,8 @@
 //
 //   EPI 0:  Y[M,N]      = X[M,K] * W[N,K]^T                   (fp32; over k_parts ranges of K: partial tiles)
 //   EPI 1:  out[M,F]    = planes of silu(X Wg^T) * (X Wu^T)    (the SwiGLU projection)
+//   EPI 3:  q, k, v     = X * W^T, q and k rotated, k and v into the caches (the QKV projection; k_parts ranges of K are summed
+//                         inside the launch by the workgroups that have them, exchange.h)
 //
 // What bounds it: up to 16 rows the weight stream from HBM, above ~150 rows the matrix pipe (hi + lo planes are two
 // matrix instructions per fragment pair; from 512 rows on its power: it is busy 82 to 90 % of the time at 1.9 to 2.2 GHz,
@@ -24,7 +26,8 @@
 //   rows        1          23         64         80         133    256
 //   gate+up     35.0 (43)  37.7 (49)  44.8 (55)  50.6 (80)  69.8   83.4 (101)
 //   down        18.9 (21)  20.4       25.4 (30)  27.2 (36)  36.3   51.4 (57)
-//   QKV          9.7 (12)  11.2       14.9 (18)  16.2 (27)  20.5   25.7 (34)
+//   QKV          9.7 (12)  11.2       14.9 (18)  16.2 (27)  20.5   25.7 (34)   (EPI 0; EPI 3 at 64 rows: 18.6, of which, by clock in
+//                the kernel, 1.1 the partial tile's way out, 1.5 the meeting, 1.2 the parts' way in, 1.3 rotation and stores)
 //   Wo           6.6        8.8       11.1       12.9       15.8   20.6
 //   LM head    154        170        177        187        229    365
 // The same kernel on row-major planes (64-byte row pieces): gate+up 64.4 at 64 rows, 69.5 at 80, 107 at 256.
