@@ -453,7 +453,10 @@ __global__ __launch_bounds__(64 * AF_WAVES) void attn_fp32_kernel(const float* _
     if (D != 64) load_v(1);
     sc = vis ? sc : -INFINITY;
     const float mnew = fmaxf(mrun, wave_max(sc));
-    if (mnew == -INFINITY) continue;  // uniform across the wave (every visible score is)
+    if (mnew == -INFINITY) {   // uniform across the wave: every visible score is, or no number, which fmaxf leaves out
+      lrun = vis && sc != sc ? sc : lrun;
+      continue;
+    }
     const float p = vis ? expf(sc - mnew) : 0.f;
     const float corr = (mrun == -INFINITY) ? 0.f : expf(mrun - mnew);
     mrun = mnew;
@@ -494,7 +497,7 @@ __global__ __launch_bounds__(64 * AF_WAVES) void attn_fp32_kernel(const float* _
     float v = 0.f;
     l = 0.f;
     for (int w = 0; w < waves; ++w) {
-      if (all_m[w] == -INFINITY) continue;   // (saw no key)
+      if (all_m[w] == -INFINITY && all_l[w] == 0.f) continue;   // (saw no key; its sum is no number if it saw one whose score is none)
       const float f = expf(all_m[w] - m);
       l += f * all_l[w];
       v += f * all_o[w][c];
