@@ -528,9 +528,13 @@ void run_layer(clover_ctx* x, const clover_layer_weights& lw, float* xres, RowMa
     // Two to four ranges of K and up to 160 rows: the launch sums, rotates and stores by itself, which is faster than leaving that to a
     // second one.  us, one launch and two: 64 rows 18.6 and 21.0, with 32 KV heads 27.5 and 29.8, 133 rows 27.3 and 27.8.  Eight ranges
     // (up to 32 rows) meet later and leave eight parts to read: a step of 23 rows is 0.8 % slower so; 256 rows the same, 512 rows 0.5 %
-    // slower (a member has a dozen blocks to finish), one range (prompts) the same.  Heads of 64 have no second launch.
+    // slower (a member has a dozen blocks to finish), one range (prompts) the same.
+    // Models without MFMA attention (heads of 64, groups other than 1, 2, 4, 8), whose q stays in fp32: above 32 rows.  us a layer, one
+    // launch and two: 2048 channels, 32 heads of 64 over 8: one row 64.8 and 63.8, 16 66.5 and 66.0, 32 73.7 and 73.1, 33 79.9 and 80.3,
+    // 64 88.1 and 90.9, 256 167 and 173, a prompt of 1024 824 and 849; 3584 channels, 28 heads of 128 over 4 (at 64 rows seven ranges on
+    // different XCDs): 122.2 and 121.1, 129.3 and 128.5, 138.8 and 138.8, 145.5 and 146.4, 163.9 and 167.5, 422 and 422, 1919 and 1947.
     const int sq = tile_gemm_pick_k_parts(M, x->QKVN, H);
-    if (!x->attn_fast || (sq >= 2 && sq <= 4 && M <= 160)) {
+    if (x->attn_fast ? sq >= 2 && sq <= 4 && M <= 160 : M > 32) {
       Scope s(x, KC_GEMM_QKV);
       TileGemmQkv g;
       memset(&g, 0, sizeof(g));
@@ -544,8 +548,14 @@ void run_layer(clover_ctx* x, const clover_layer_weights& lw, float* xres, RowMa
     } else {
       gemm_fast(x, KC_GEMM_QKV, A, lw.wq, M, x->QKVN, H);
       Scope s(x, KC_ROPE_KV);
-      launch_rope_kv_planes(x->partial, x->QKVN, sq, (size_t)M * x->QKVN, x->cos_t, x->sin_t, (bf16_t*)kc_layer, (bf16_t*)vc_layer, kvl,
-                            base_len, c.n_q_heads, rm, x->d_err, q_hi, q_lo, x->NQD, 1.0f / sqrtf((float)d), x->st);
+      const size_t stride = (size_t)M * x->QKVN;
+      bf16_t *const kc = (bf16_t*)kc_layer, *const vc = (bf16_t*)vc_layer;
+      if (x->attn_fast)
+        launch_rope_kv_planes(x->partial, x->QKVN, sq, stride, x->cos_t, x->sin_t, kc, vc, kvl, base_len, c.n_q_heads, rm, x->d_err, q_hi, q_lo,
+                              x->NQD, 1.0f / sqrtf((float)d), x->st);
+      else
+        launch_rope_kv_parts(x->partial, x->QKVN, sq, stride, x->cos_t, x->sin_t, x->q_rot, x->NQD, kc, vc, kvl, base_len, c.n_q_heads, rm,
+                             x->d_err, x->st);
     }
     { Scope s(x, KC_ATTN);
       if (x->attn_fast) {

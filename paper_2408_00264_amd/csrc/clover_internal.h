@@ -220,7 +220,11 @@ void launch_rmsnorm(const float* x, int ldx, const void* gain, int wdtype, float
                     int rows, hipStream_t st);
 void launch_rope_kv_write(const float* qkv, int ldqkv, const float* cos_t, const float* sin_t, float* q_out, int ldq, float* k_cache,
                           float* v_cache, KVLayout kv, const int* base_len, int n_q, RowMap rm, int* err_flag, hipStream_t st);
-// the same behind a QKV GEMM that left partial tiles, heads of q and k in rotary order; q as planes, caches of two planes
+// the same behind a QKV GEMM that left partial tiles, heads of q and k in rotary order; caches of two planes.  q in fp32, few rows:
+void launch_rope_kv_parts(const float* qkv, int ldqkv, int splits, size_t split_stride, const float* cos_t, const float* sin_t, float* q_out,
+                          int ldq, bf16_t* k_cache, bf16_t* v_cache, KVLayout kv, const int* base_len, int n_q, RowMap rm, int* err_flag,
+                          hipStream_t st);
+// q as planes:
 void launch_rope_kv_planes(const float* qkv, int ldqkv, int splits, size_t split_stride, const float* cos_t, const float* sin_t, bf16_t* k_cache,
                            bf16_t* v_cache, KVLayout kv, const int* base_len, int n_q, RowMap rm, int* err_flag, bf16_t* q_hi, bf16_t* q_lo,
                            int ldq, float q_scale, hipStream_t st);

@@ -80,14 +80,28 @@ void launch_rmsnorm(const float* x, int ldx, const void* gain, int wdtype, float
 }
 
 // ------------------------------------------------------------------------------------------
-// RoPE on q and k (half-split pairing), K rows and transposed V columns into the cache (fp32 models; the MFMA path's QKV GEMM does
-// both itself).
+// RoPE on q and k (half-split pairing), K rows and transposed V columns into the cache; q stays in fp32.  For fp32 models, and for few
+// rows of bf16 models whose heads have no MFMA attention: there the QKV GEMM leaves partial tiles, heads of q and k in rotary order
+// (launch_pack_weight).  (Those could take the kernel below as well; us a layer with it / with this one, 2048 channels, 32 heads of 64
+// over 8: one row 64.2 / 62.2, 16 rows 67.3 / 66.3.)
 // blocks [0, n*hc): 256 (head, pair) items of one row; then blocks of 8 (head,dim) lines of V^T
 // ------------------------------------------------------------------------------------------
-__global__ void rope_kv_write_kernel(const float* __restrict__ qkv, int ldqkv, const float* __restrict__ cos_t,
+template <typename KT>
+__device__ __forceinline__ float qkv_at(const float* __restrict__ p, int nsp, size_t sps) {   // the sum of the ranges, in their order
+  if constexpr (std::is_same<KT, float>::value) return *p;
+  float q[TILE_MAX_K_PARTS], v = 0.f;
+#pragma unroll
+  for (int j = 0; j < TILE_MAX_K_PARTS; ++j) q[j] = j < nsp ? p[(size_t)j * sps] : 0.f;
+#pragma unroll
+  for (int j = 0; j < TILE_MAX_K_PARTS; ++j) v += q[j];
+  return v;
+}
+template <typename KT>
+__global__ void rope_kv_write_kernel(const float* __restrict__ qkv, int ldqkv, int nsp, size_t sps, const float* __restrict__ cos_t,
                                      const float* __restrict__ sin_t, float* __restrict__ q_out, int ldq,
-                                     float* __restrict__ kc, float* __restrict__ vc, KVLayout kv,
+                                     KT* __restrict__ kc, KT* __restrict__ vc, KVLayout kv,
                                      const int* __restrict__ base_len, int n_q, RowMap rm, int* err_flag, int hc) {
+  constexpr bool ROTARY = !std::is_same<KT, float>::value;   // order of a head's columns
   const int b = blockIdx.y;
   const int nv = rows_valid(rm, b);
   const int L = base_len[b];
@@ -102,27 +116,33 @@ __global__ void rope_kv_write_kernel(const float* __restrict__ qkv, int ldqkv, c
     const int idx = (blockIdx.x % hc) * 256 + threadIdx.x;
     if (idx >= (n_q + n_kv) * half) return;
     const size_t row = (size_t)b * rm.R + i;
-    const float* src = qkv + row * ldqkv;
     const int hh = idx / half, ii = idx - hh * half;
     const float c = cos_t[row * half + ii], s = sin_t[row * half + ii];
-    const float x1 = src[hh * d + ii], x2 = src[hh * d + ii + half];
+    const float* src = qkv + row * ldqkv + hh * d + (ROTARY ? (ii >> 3) * 16 + (ii & 7) : ii);
+    const float x1 = qkv_at<KT>(src, nsp, sps), x2 = qkv_at<KT>(src + (ROTARY ? 8 : half), nsp, sps);
     const float o1 = x1 * c - x2 * s, o2 = x2 * c + x1 * s;
-    float* out = hh < n_q ? q_out + row * ldq + hh * d : kc + kv_k_at(kv, b, L + i, hh - n_q);
-    out[ii] = o1;
-    out[ii + half] = o2;
+    if (hh < n_q) {
+      q_out[row * ldq + hh * d + ii] = o1;
+      q_out[row * ldq + hh * d + ii + half] = o2;
+    } else {
+      const size_t base = kv_k_at(kv, b, L + i, hh - n_q);
+      stkv(kc, base + kv_k_col(kv, ii), kv.plane, o1);
+      stkv(kc, base + kv_k_col(kv, ii + half), kv.plane, o2);
+    }
   } else {
     const int vb = blockIdx.x - rm.n * hc;
     const int voff = (n_q + n_kv) * d;
     for (int idx = threadIdx.x; idx < 8 * rm.n; idx += blockDim.x) {
       const int node = idx % rm.n, e = vb * 8 + idx / rm.n;
       if (node >= nv || e >= n_kv * d) continue;
-      vc[kv_v_at(kv, b, e / d, e % d, L + node)] = qkv[((size_t)b * rm.R + node) * ldqkv + voff + e];
+      const float v = qkv_at<KT>(qkv + ((size_t)b * rm.R + node) * ldqkv + voff + e, nsp, sps);
+      stkv(vc, kv_v_at(kv, b, e / d, e % d, L + node), kv.plane, v);
     }
   }
 }
 
-// The same operation for launches of the MFMA path whose QKV GEMM does not do it itself (heads of q and k in rotary order, q as pre-scaled bf16 planes, bf16-plane caches), vectorised:
-// a thread of the first blocks rotates four adjacent channels of one head (float4 loads of every partial, issued
+// The same operation in front of the MFMA attention, for launches whose QKV GEMM does not do it itself (heads of q and k in rotary order,
+// q as pre-scaled bf16 planes, bf16-plane caches), vectorised: a thread of the first blocks rotates four adjacent channels of one head (float4 loads of every partial, issued
 // before anything else is waited for; 8-byte plane stores); the last blocks transpose 64 nodes x 32 channels of V
 // through LDS so that the partials are read along the channels and V^T is written along the nodes.
 __device__ __forceinline__ void planes4(bf16_t* hi, bf16_t* lo, size_t off, const float (&o)[4]) {
@@ -247,12 +267,24 @@ void launch_rope_kv_planes(const float* qkv, int ldqkv, int splits, size_t split
         qkv, ldqkv, split_stride, cos_t, sin_t, k_cache, v_cache, kv, base_len, n_q, rm, err_flag, qk_blocks, q_hi, q_lo, ldq, q_scale);
   });
 }
-void launch_rope_kv_write(const float* qkv, int ldqkv, const float* cos_t, const float* sin_t, float* q_out, int ldq, float* k_cache,
-                          float* v_cache, KVLayout kv, const int* base_len, int n_q, RowMap rm, int* err_flag, hipStream_t st) {
+template <typename KT>
+static void launch_rope_kv_one(const float* qkv, int ldqkv, int splits, size_t split_stride, const float* cos_t, const float* sin_t, float* q_out,
+                               int ldq, KT* k_cache, KT* v_cache, KVLayout kv, const int* base_len, int n_q, RowMap rm, int* err_flag,
+                               hipStream_t st) {
   const int vblocks = (kv.n_kv * kv.d + 7) / 8;
   const int hc = ((n_q + kv.n_kv) * (kv.d / 2) + 255) / 256;
-  rope_kv_write_kernel<<<dim3(rm.n * hc + vblocks, rm.B), 256, 0, st>>>(qkv, ldqkv, cos_t, sin_t, q_out, ldq, k_cache, v_cache, kv, base_len,
-                                                                        n_q, rm, err_flag, hc);
+  rope_kv_write_kernel<KT><<<dim3(rm.n * hc + vblocks, rm.B), 256, 0, st>>>(qkv, ldqkv, splits, split_stride, cos_t, sin_t, q_out, ldq, k_cache,
+                                                                            v_cache, kv, base_len, n_q, rm, err_flag, hc);
+}
+void launch_rope_kv_write(const float* qkv, int ldqkv, const float* cos_t, const float* sin_t, float* q_out, int ldq, float* k_cache,
+                          float* v_cache, KVLayout kv, const int* base_len, int n_q, RowMap rm, int* err_flag, hipStream_t st) {
+  launch_rope_kv_one(qkv, ldqkv, 1, 0, cos_t, sin_t, q_out, ldq, k_cache, v_cache, kv, base_len, n_q, rm, err_flag, st);
+}
+void launch_rope_kv_parts(const float* qkv, int ldqkv, int splits, size_t split_stride, const float* cos_t, const float* sin_t, float* q_out,
+                          int ldq, bf16_t* k_cache, bf16_t* v_cache, KVLayout kv, const int* base_len, int n_q, RowMap rm, int* err_flag,
+                          hipStream_t st) {
+  if (splits > TILE_MAX_K_PARTS) { g_not_launched = "no kernel for this count of partial results"; return; }
+  launch_rope_kv_one(qkv, ldqkv, splits, split_stride, cos_t, sin_t, q_out, ldq, k_cache, v_cache, kv, base_len, n_q, rm, err_flag, st);
 }
 
 // ------------------------------------------------------------------------------------------

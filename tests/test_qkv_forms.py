@@ -16,13 +16,13 @@ CASES = [(4096, 32, 8, 128, 1, 1, 1, 8), (4096, 32, 8, 128, 1, 16, 24, 8), (4096
          (640, 5, 5, 128, 2, 9, 40, 2), (256, 4, 1, 64, 1, 12, 12, 1), (512, 32, 32, 128, 12, 50, 51, 1), (2048, 16, 16, 128, 9, 60, 60, 1)]
 
 
-@pytest.mark.parametrize("H,n_q,n_kv,d,batch,nodes,R,ranges", CASES)
-def test_keys_and_values(H, n_q, n_kv, d, batch, nodes, R, ranges):
+def _compare(H, n_q, n_kv, d, batch, nodes, R):
+    """One layer by the MFMA path and by the fp32-ALU kernels.  Returns whether the former's attention is the MFMA one too, and the launches
+    of its QKV projection and of the rotation behind it."""
     import torch
-    lib = clover.load_library()
-    M, N, form = (batch - 1) * R + nodes, (n_q + 2 * n_kv) * d, (C.c_int32 * 5)()
-    assert lib.clover_op_gemm_form(0, M, N, H, ranges, form) == 0
-    print(f"qkv M={M} N={N} K={H} form={list(form)}", flush=True)
+    assert torch.cuda.is_available()
+    M = (batch - 1) * R + nodes
+    print(f"qkv M={M} N={(n_q + 2 * n_kv) * d} K={H}", flush=True)
     shape = synth.scaled(synth.CONFIGS[3], name="qkv-forms", n_layers=1, hidden=H, n_q_heads=n_q, n_kv_heads=n_kv, head_dim=d, ffn=512,
                          vocab=2048, ad_heads=n_q if H % n_q == 0 else 4, seed=23)
     dev_w = clover.upload_weights(synth.WeightStore(shape))
@@ -37,25 +37,27 @@ def test_keys_and_values(H, n_q, n_kv, d, batch, nodes, R, ranges):
     tok = torch.randint(0, shape.vocab, (batch, R), generator=torch.Generator().manual_seed(1)).int()
     out = []
     for flags in (0, clover.FLAG_GENERIC):
-        g = clover.Clover(shape, dev_w, parent, rank, batch, max_seq, R, flags=flags)
+        g = clover.Clover(shape, dev_w, parent, rank, batch, max_seq, R, flags=flags | (clover.FLAG_INTERVAL_MASK if R > 128 else 0))
         if flags == 0:
-            assert g.path_info() & 1
+            path = g.path_info()
+            assert path & 1
             g.set_page_table(pages)
         g.set_seq_len(lens, [max(v - 1, 0) for v in lens])
         for b in range(batch):                                 # (the cached rows: zeros)
             if lens[b]:
                 g.write_kv(0, 0, b, 0, np.zeros((lens[b], n_kv, d), np.float32), np.zeros((lens[b], n_kv, d), np.float32))
         g.tree_tokens.copy_(tok)
+        g.profile_enable(flags == 0)
         g.verify_tree(batch)
         torch.cuda.synchronize()
+        if flags == 0:
+            ran = g.profile_collect()
         assert list(g.seq_len()) == lens                       # (no guard fired)
         # every slot: those behind the nodes stay as they were, zeros on the MFMA path
         kv = [g.read_kv(0, 0, b, 0, max_seq if flags == 0 else lens[b] + nodes) for b in range(batch)]
         out.append((kv, g.hidden[:, :nodes].double().cpu()))
         g.close()
-    # products of normalised rows and N(0, 0.02) weights, 16 mantissa bits on one side (the bound of the GEMM's own tests), turned
-    # by an angle, and once more 2^-17 of a value of up to 5 sigma
-    tol = 4e-5 * np.sqrt(H) * 0.02 * 4 * 1.5 + 2.0 ** -17 * 5 * 0.02 * np.sqrt(H)
+    tol = _tolerance(H)
     for b in range(batch):
         for got, want in zip(out[0][0][b], out[1][0][b]):
             new = slice(lens[b], lens[b] + nodes)
@@ -63,3 +65,59 @@ def test_keys_and_values(H, n_q, n_kv, d, batch, nodes, R, ranges):
             assert not got[:lens[b]].any() and not got[lens[b] + nodes:].any()
     # the rows' results through attention and FFN (the bound of the attention's tests; keys and values of another scale with H)
     assert (out[0][1] - out[1][1]).abs().max().item() <= 2e-3 * max(1.0, H / 1024)
+    return bool(path & 2), ran["gemm_qkv"][1], ran["rope_kv_write"][1]
+
+
+def _tolerance(H):
+    """of keys and values: products of normalised rows and N(0, 0.02) weights, 16 mantissa bits on one side (the bound of the GEMM's own
+    tests), turned by an angle, and once more 2^-17 of a value of up to 5 sigma"""
+    return 4e-5 * np.sqrt(H) * 0.02 * 4 * 1.5 + 2.0 ** -17 * 5 * 0.02 * np.sqrt(H)
+
+
+@pytest.mark.parametrize("H,n_q,n_kv,d,batch,nodes,R,ranges", CASES)
+def test_keys_and_values(H, n_q, n_kv, d, batch, nodes, R, ranges):
+    import torch   # (in front of the library, which then finds torch's HIP runtime)
+    assert torch.cuda.is_available()
+    lib = clover.load_library()
+    assert lib.clover_op_gemm_form(0, (batch - 1) * R + nodes, (n_q + 2 * n_kv) * d, H, ranges, (C.c_int32 * 5)()) == 0
+    _compare(H, n_q, n_kv, d, batch, nodes, R)
+
+
+# Heads of 64, and groups of seven, three and five heads, which the MFMA attention does not take: two launches up to 32 rows, one above, over
+# one to eight ranges of K on one XCD and on several, by tiles of 64 to 256 rows, the last of them not whole, whose results are finished
+# two blocks, a row of blocks or a part of a row of blocks at a time.
+WITHOUT_MFMA_ATTENTION = [(1024, 6, 3, 64, 1, 1, 1), (896, 7, 1, 128, 1, 17, 17), (2560, 20, 4, 128, 1, 24, 24), (256, 4, 1, 64, 2, 16, 16),
+                          (1024, 6, 3, 64, 1, 33, 33), (256, 4, 4, 64, 2, 40, 41), (2048, 32, 8, 64, 2, 47, 50), (1024, 16, 2, 64, 7, 19, 23),
+                          (2048, 32, 8, 64, 4, 90, 100), (3584, 28, 4, 128, 1, 64, 64), (2304, 36, 9, 64, 1, 97, 97), (3584, 28, 4, 128, 3, 99, 101),
+                          (1152, 9, 3, 128, 1, 130, 133), (2432, 38, 38, 64, 1, 130, 133), (3840, 32, 8, 64, 3, 99, 100),
+                          (5120, 28, 4, 128, 2, 250, 256), (1024, 28, 4, 128, 8, 250, 256), (2432, 38, 38, 64, 8, 250, 256)]
+
+
+@pytest.mark.parametrize("H,n_q,n_kv,d,batch,nodes,R", WITHOUT_MFMA_ATTENTION)
+def test_keys_and_values_without_mfma_attention(H, n_q, n_kv, d, batch, nodes, R):
+    rows = (batch - 1) * R + nodes
+    assert _compare(H, n_q, n_kv, d, batch, nodes, R) == (False, 1, 1 if rows <= 32 else 0)
+
+
+@pytest.mark.parametrize("H,n_q,n_kv,d", [(1024, 6, 3, 64), (896, 7, 1, 128)])
+def test_prompts_without_mfma_attention(H, n_q, n_kv, d):
+    """one range of K, in tiles of many rows, the last of them with a part of its rows; the last row's result rests on its q as well"""
+    import torch
+    assert torch.cuda.is_available()
+    n = 553
+    shape = synth.scaled(synth.CONFIGS[3], name="qkv-prompt", n_layers=1, hidden=H, n_q_heads=n_q, n_kv_heads=n_kv, head_dim=d, ffn=512, vocab=2048,
+                         ad_heads=4, seed=29)
+    dev_w = clover.upload_weights(synth.WeightStore(shape))
+    parent, rank = np.array([-1, 0, 0], np.int32), np.array([0, 0, 1], np.int32)
+    tok = torch.randint(0, shape.vocab, (n,), generator=torch.Generator().manual_seed(3)).int().cuda()
+    out = []
+    for flags in (0, clover.FLAG_GENERIC):
+        g = clover.Clover(shape, dev_w, parent, rank, 1, 640, 64, flags=flags, prefill_rows=256)
+        g.prefill_prompt(0, tok)
+        torch.cuda.synchronize()
+        if flags == 0:
+            assert g.path_info() == 1
+        out.append((*g.read_kv(0, 0, 0, 0, n), g.hid_acc[0, 0].double().cpu().numpy()))
+        g.close()
+    for got, want, tol in zip(*out, (_tolerance(H), _tolerance(H), 2e-3 * max(1.0, H / 1024))):
+        assert np.abs(got - want).max() <= tol, (np.abs(got - want).max(), tol)
