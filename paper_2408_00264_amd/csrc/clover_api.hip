@@ -254,12 +254,17 @@ std::vector<TileBytes> tile_bytes(const clover_config& c, int rows) {
   model_gemm_shapes(c, s);   // QKV, Wo, down, an Attention Decoder's q, the FC
   std::vector<TileBytes> v;
   TileBytes t{256, 256, 256, 256};
+  const bool mfma_attention = attn_mfma_supported(c.head_dim, c.n_q_heads, c.n_kv_heads, c.max_seq);
   for (int M = 32; M < rows + 32; M += 32) {   // one row count of each class of equal K ranges
     auto bytes = [&](int N, int K) {   // (a tuning build that changes the ranges afterwards makes room for them here)
       return (size_t)std::max(tile_gemm_pick_k_parts(M, N, K), tune_int("CLOVER_TILE_KP_ROOM", 1)) * std::min(M, rows) * N * sizeof(float);
     };
     auto exchanged = [&](int N, int K) {
-      return tile_gemm_exchange_bytes(std::min(M, rows), N, K, std::max(tile_gemm_pick_k_parts(M, N, K), tune_int("CLOVER_TILE_KP_ROOM", 1)));
+      const int m = std::min(M, rows), room = tune_int("CLOVER_TILE_KP_ROOM", 1);
+      if (room > 1) return tile_gemm_exchange_bytes(tile_gemm_form(m, N, K, 0, std::max(tile_gemm_pick_k_parts(m, N, K), room)), m, N);
+      TileForm form;
+      const bool joins = tile_gemm_qkv_joins(m, N, K, tile_gemm_pick_k_parts(m, N, K), mfma_attention, &form);
+      return joins ? tile_gemm_exchange_bytes(form, m, N) : 0;
     };
     t.attn = std::max({t.attn, bytes(s[0].N, s[0].K), exchanged(s[0].N, s[0].K), bytes(s[1].N, s[1].K)});
     t.down = std::max(t.down, bytes(s[2].N, s[2].K));
@@ -525,26 +530,19 @@ void run_layer(clover_ctx* x, const clover_layer_weights& lw, float* xres, RowMa
     const FragPlanes A = frag_planes(x->a_norm, M), O = frag_planes(x->attn_out, M), Hf = frag_planes(x->h_ffn, M);
     bf16_t* const q_hi = (bf16_t*)x->q_rot;
     bf16_t* const q_lo = q_hi + (size_t)x->rows * x->NQD;
-    // Two to four ranges of K and up to 160 rows: the launch sums, rotates and stores by itself, which is faster than leaving that to a
-    // second one.  us, one launch and two: 64 rows 18.6 and 21.0, with 32 KV heads 27.5 and 29.8, 133 rows 27.3 and 27.8.  Eight ranges
-    // (up to 32 rows) meet later and leave eight parts to read: a step of 23 rows is 0.8 % slower so; 256 rows the same, 512 rows 0.5 %
-    // slower (a member has a dozen blocks to finish), one range (prompts) the same.
-    // Models without MFMA attention (heads of 64, groups other than 1, 2, 4, 8), whose q stays in fp32: above 32 rows.  us a layer, one
-    // launch and two: 2048 channels, 32 heads of 64 over 8: one row 64.8 and 63.8, 16 66.5 and 66.0, 32 73.7 and 73.1, 33 79.9 and 80.3,
-    // 64 88.1 and 90.9, 256 167 and 173, a prompt of 1024 824 and 849; 3584 channels, 28 heads of 128 over 4 (at 64 rows seven ranges on
-    // different XCDs): 122.2 and 121.1, 129.3 and 128.5, 138.8 and 138.8, 145.5 and 146.4, 163.9 and 167.5, 422 and 422, 1919 and 1947.
     const int sq = tile_gemm_pick_k_parts(M, x->QKVN, H);
-    if (x->attn_fast ? sq >= 2 && sq <= 4 && M <= 160 : M > 32) {
+    TileForm form;
+    if (tile_gemm_qkv_joins(M, x->QKVN, H, sq, x->attn_fast, &form)) {
       Scope s(x, KC_GEMM_QKV);
       TileGemmQkv g;
       memset(&g, 0, sizeof(g));
       g.X = A;
       g.W = (const bf16_t*)lw.wq;   // q, k and v rows
-      g.M = M; g.N = x->QKVN; g.K = H; g.k_parts = sq;
+      g.M = M; g.N = x->QKVN; g.K = H;
       g.part = x->partial; g.meet = x->d_meet; g.polls = tune_int("CLOVER_MEET_POLLS", MEET_POLLS);
       g.qkv = QkvOut{c.n_q_heads, d, x->attn_fast ? q_hi : nullptr, q_lo, 1.0f / sqrtf((float)d), x->q_rot, x->NQD,
                      (bf16_t*)kc_layer, (bf16_t*)vc_layer, kvl, x->cos_t, x->sin_t, base_len, rm, x->d_err};
-      launch_gemm_qkv(g, x->st);
+      launch_gemm_qkv(g, form, x->st);
     } else {
       gemm_fast(x, KC_GEMM_QKV, A, lw.wq, M, x->QKVN, H);
       Scope s(x, KC_ROPE_KV);

@@ -382,12 +382,14 @@ constexpr int TILE_MAX_K_PARTS = 8;
 // K ranges of a narrow output; the same for all M that round up to the same multiple of 32
 int tile_gemm_pick_k_parts(int M, int N, int K);
 void launch_gemm_tile(const TileGemm& g, hipStream_t st);
-void launch_gemm_qkv(const TileGemmQkv& g, hipStream_t st);
-// bytes of `part` for M rows over k_parts ranges
-size_t tile_gemm_exchange_bytes(int M, int N, int K, int k_parts);
 // what launch_gemm_tile runs for M rows (N = F for epi 1; k_parts 0: its own choice)
 struct TileForm { int rb, wb /* column blocks of 16 */, row_tiles, k_parts, stages; };
 TileForm tile_gemm_form(int M, int N, int K, int epi, int k_parts);
+// whether the QKV projection's launch rotates and stores by itself (epi 3; which form of it, if so) or leaves that to a second one
+bool tile_gemm_qkv_joins(int M, int N, int K, int k_parts, bool mfma_attention, TileForm* form);
+// bytes of `part` for M rows
+size_t tile_gemm_exchange_bytes(const TileForm& t, int M, int N);
+void launch_gemm_qkv(const TileGemmQkv& g, const TileForm& t, hipStream_t st);
 
 // ---- fused bookkeeping kernels of the draft head (MFMA path, bf16 weights) ----------------------
 // planes of RMSNorm(hid[row]) * gain -> a and of the embedding of tok[row] -> y, rows of `rm` in,

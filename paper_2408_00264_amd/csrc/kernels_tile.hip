@@ -86,11 +86,33 @@ TileForm tile_gemm_form(int M, int N, int K, int epi, int k_parts) {
   return TileForm{t.rb, t.wb, (M + rows - 1) / rows, t.kp, K / (t.rb == 0 ? 2 * TL_KST : TL_KST) / t.kp};
 }
 
-size_t tile_gemm_exchange_bytes(int M, int N, int K, int k_parts) {
-  if (k_parts < 2) return 0;
-  const TileForm t = tile_gemm_form(M, N, K, 0, k_parts);
-  const int rows = std::min(2 * t.rb, (M + 15) / 16), tiles = (N / 16 + t.wb - 1) / t.wb;
-  return (size_t)t.row_tiles * tiles * k_parts * rows * t.wb * 1024;
+static int tiles_of(const TileForm& t, int N) { return (N / 16 + t.wb - 1) / t.wb; }
+// workgroups of an XCD that has the ranges of its tiles together
+static int wgs_per_xcd(const TileForm& t, int N) { return (tiles_of(t, N) + 7) / 8 * t.row_tiles * t.k_parts; }
+
+// Measured by whole verify passes, one launch and two in turn, us a layer (profiles/qkv_joint_sweep.txt).
+//
+// With MFMA attention, one launch - two: 48 and 64 rows over three or four ranges -0.4 to -3.2 of 54 to 365 (4096 channels, 64 rows -1.6 of
+// 138, with 32 KV heads -2.0), 33 rows and up to 32 -2.1 to +0.4.  Two ranges: up to 32 rows -2.1 to +0.7, above +0.4 to +4.4
+// (4096 channels, 32 KV heads, 128 rows +3.6 of 185): a member has half the tile to finish.  65 to 128 rows in one row tile: -3.6 to 0
+// where a range has 16 stages or more, +0.5 to +1.5 where it has fewer (1024, 1280 and 1536 channels).  More row tiles: -2.0 to
+// +1.2 (4096 channels, 8 KV heads, 128 rows +1.1).  Above 128 rows, and ranges on different XCDs: +3.7 to -2.9, and 256 rows and more the
+// same or slower.  Five to eight ranges, which few rows have: a step of 23 rows 0.8 % slower.
+//
+// Without it (heads of 64, groups other than 1, 2, 4, 8), where the second launch writes q in fp32; one launch and two: 2048 channels, 32
+// heads of 64 over 8: one row 64.8 and 63.8, 16 66.5 and 66.0, 32 73.7 and 73.1, 33 79.9 and 80.3, 64 88.1 and 90.9, 256 167 and 173, a prompt
+// of 1024 824 and 849; 3584 channels, 28 heads of 128 over 4 (at 64 rows seven ranges on different XCDs): 122.2 and 121.1, 129.3 and
+// 128.5, 138.8 and 138.8, 145.5 and 146.4, 163.9 and 167.5, 422 and 422, 1919 and 1947.
+bool tile_gemm_qkv_joins(int M, int N, int K, int k_parts, bool mfma_attention, TileForm* form) {
+  if (mfma_attention && (M > 128 || k_parts > 4 || k_parts < (M <= 32 ? 2 : 3))) return false;
+  if (!mfma_attention && M <= 32) return false;
+  const TileForm t = *form = tile_gemm_form(M, N, K, 0, k_parts);
+  if (k_parts > 1 && tiles_of(t, N) * t.row_tiles > TILE_MEETINGS) return false;
+  return !mfma_attention || (t.row_tiles == 1 && wgs_per_xcd(t, N) <= TL_CUS / 8 && (M <= 64 || t.stages >= 16));
+}
+size_t tile_gemm_exchange_bytes(const TileForm& t, int M, int N) {
+  if (t.k_parts < 2) return 0;
+  return (size_t)t.row_tiles * tiles_of(t, N) * t.k_parts * std::min(2 * t.rb, (M + 15) / 16) * t.wb * 1024;
 }
 
 void launch_gemm_tile(const TileGemm& g_in, hipStream_t st) {
@@ -103,18 +125,15 @@ void launch_gemm_tile(const TileGemm& g_in, hipStream_t st) {
   (g.epi == 1 ? launch_tile_swiglu : launch_tile_plain)(g, t, wgs, st);
 }
 
-void launch_gemm_qkv(const TileGemmQkv& g_in, hipStream_t st) {
+void launch_gemm_qkv(const TileGemmQkv& g_in, const TileForm& t, hipStream_t st) {
   TileGemmQkv g = g_in;
-  const TileForm t = tile_gemm_form(g.M, g.N, g.K, 0, g.k_parts);
-  const int rt = t.row_tiles, tiles = (g.N / 16 + t.wb - 1) / t.wb, per_xcd = (tiles + 7) / 8 * rt * g.k_parts;
+  const int rt = t.row_tiles, tiles = tiles_of(t, g.N), per_xcd = wgs_per_xcd(t, g.N);
+  g.k_parts = t.k_parts;
   g.n_units = tiles * g.k_parts;
   g.row_blocks = std::min(t.rb == 0 ? 1 : 2 * t.rb, (g.M + 15) / 16);
   g.spread = per_xcd > TL_CUS / 8;   // (a member of a second round would keep those of the first waiting)
   int wgs = rt > 1 ? (g.n_units + 7) / 8 * 8 * rt : g.n_units;
-  if (g.k_parts > 1) {
-    if (tiles * rt > TILE_MEETINGS) { g_not_launched = "more tiles than meetings"; return; }
-    if (!g.spread) wgs = 8 * per_xcd;
-  }
+  if (g.k_parts > 1 && !g.spread) wgs = 8 * per_xcd;
   launch_tile_qkv(g, t, wgs, st);
 }
 

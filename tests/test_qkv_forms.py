@@ -1,6 +1,6 @@
-"""The QKV projection's launch, which also rotates, writes q and fills the caches: its tiles over one and several ranges of K, whole and
+"""The QKV projection, its rotation and its way into the caches, in one launch or two: tiles over one and several ranges of K, whole and
 partial row blocks and last tiles, sequences with unused rows between them, both head sizes, shuffled pages.  Reference: the
-fp32-ALU kernels of the same model."""
+fp32-ALU kernels of the same model.  Which launches ran is asserted by the profile."""
 import ctypes as C
 
 import numpy as np
@@ -8,12 +8,29 @@ import pytest
 
 from paper_2408_00264_amd import clover, synth
 
-pytestmark = pytest.mark.gpu
-# (hidden, query heads, KV heads, head size, sequences, nodes, rows of a sequence, K ranges that the rule takes)
-CASES = [(4096, 32, 8, 128, 1, 1, 1, 8), (4096, 32, 8, 128, 1, 16, 24, 8), (4096, 32, 8, 128, 1, 17, 17, 8), (4096, 32, 8, 128, 2, 30, 33, 4),
-         (4096, 32, 8, 128, 3, 32, 32, 4), (4096, 32, 8, 128, 1, 120, 128, 4), (4096, 32, 8, 128, 8, 32, 32, 4),
-         (1024, 8, 2, 128, 1, 5, 5, 4), (1024, 8, 2, 128, 3, 50, 60, 4), (1024, 6, 3, 64, 1, 33, 33, 4), (1024, 6, 3, 64, 7, 19, 23, 4),
-         (640, 5, 5, 128, 2, 9, 40, 2), (256, 4, 1, 64, 1, 12, 12, 1), (512, 32, 32, 128, 12, 50, 51, 1), (2048, 16, 16, 128, 9, 60, 60, 1)]
+# (hidden, query heads, KV heads, head size, sequences, nodes, rows of a sequence, K ranges that the rule takes, launches)
+CASES = [(4096, 32, 8, 128, 1, 1, 1, 8, 2), (4096, 32, 8, 128, 1, 16, 24, 8, 2), (4096, 32, 8, 128, 1, 17, 17, 8, 2), (4096, 32, 8, 128, 2, 30, 33, 4, 1),
+         (4096, 32, 8, 128, 3, 32, 32, 4, 1), (4096, 32, 8, 128, 1, 120, 128, 4, 2), (4096, 32, 8, 128, 8, 32, 32, 4, 2),
+         (1024, 8, 2, 128, 1, 5, 5, 4, 1), (1024, 8, 2, 128, 3, 50, 60, 4, 2), (640, 5, 5, 128, 2, 9, 40, 2, 2),
+         (512, 32, 32, 128, 12, 50, 51, 1, 2), (2048, 16, 16, 128, 9, 60, 60, 1, 2),
+         # few rows of two ranges; the widest tiles of up to 64 rows; tiles of 96 and 128, whose last row block is not whole
+         (640, 5, 5, 128, 1, 9, 9, 2, 1), (4096, 32, 32, 128, 1, 8, 8, 4, 1), (5120, 40, 40, 128, 1, 49, 49, 4, 1), (4096, 32, 32, 128, 2, 41, 50, 4, 1),
+         (2560, 20, 20, 128, 1, 83, 83, 4, 1), (2560, 20, 20, 128, 1, 118, 128, 4, 1), (3072, 24, 24, 128, 4, 27, 28, 3, 1),
+         # short ranges; several row tiles with their ranges on several XCDs; more than 128 rows
+         (1024, 8, 2, 128, 3, 30, 33, 4, 2), (3072, 24, 24, 128, 1, 160, 160, 3, 2), (2560, 20, 20, 128, 1, 133, 133, 4, 2)]
+
+
+# (the library's own functions, by their C++ names)
+def _ranges(M, N, K):
+    return clover.load_library()._ZN3clv22tile_gemm_pick_k_partsEiii(M, N, K)
+
+
+def _joins(M, N, K, ranges, mfma_attention):
+    """whether one launch does it all, and its (row blocks / 2, column blocks, row tiles, ranges, stages)"""
+    form = (C.c_int * 5)()
+    f = clover.load_library()._ZN3clv19tile_gemm_qkv_joinsEiiiibPNS_8TileFormE
+    f.restype, f.argtypes = C.c_bool, [C.c_int] * 4 + [C.c_bool, C.c_void_p]
+    return f(M, N, K, ranges, mfma_attention, form), list(form)
 
 
 def _compare(H, n_q, n_kv, d, batch, nodes, R):
@@ -74,13 +91,13 @@ def _tolerance(H):
     return 4e-5 * np.sqrt(H) * 0.02 * 4 * 1.5 + 2.0 ** -17 * 5 * 0.02 * np.sqrt(H)
 
 
-@pytest.mark.parametrize("H,n_q,n_kv,d,batch,nodes,R,ranges", CASES)
-def test_keys_and_values(H, n_q, n_kv, d, batch, nodes, R, ranges):
+@pytest.mark.gpu
+@pytest.mark.parametrize("H,n_q,n_kv,d,batch,nodes,R,ranges,launches", CASES)
+def test_keys_and_values(H, n_q, n_kv, d, batch, nodes, R, ranges, launches):
     import torch   # (in front of the library, which then finds torch's HIP runtime)
     assert torch.cuda.is_available()
-    lib = clover.load_library()
-    assert lib.clover_op_gemm_form(0, (batch - 1) * R + nodes, (n_q + 2 * n_kv) * d, H, ranges, (C.c_int32 * 5)()) == 0
-    _compare(H, n_q, n_kv, d, batch, nodes, R)
+    assert _ranges((batch - 1) * R + nodes, (n_q + 2 * n_kv) * d, H) == ranges
+    assert _compare(H, n_q, n_kv, d, batch, nodes, R) == (True, 1, launches - 1)
 
 
 # Heads of 64, and groups of seven, three and five heads, which the MFMA attention does not take: two launches up to 32 rows, one above, over
@@ -90,15 +107,18 @@ WITHOUT_MFMA_ATTENTION = [(1024, 6, 3, 64, 1, 1, 1), (896, 7, 1, 128, 1, 17, 17)
                           (1024, 6, 3, 64, 1, 33, 33), (256, 4, 4, 64, 2, 40, 41), (2048, 32, 8, 64, 2, 47, 50), (1024, 16, 2, 64, 7, 19, 23),
                           (2048, 32, 8, 64, 4, 90, 100), (3584, 28, 4, 128, 1, 64, 64), (2304, 36, 9, 64, 1, 97, 97), (3584, 28, 4, 128, 3, 99, 101),
                           (1152, 9, 3, 128, 1, 130, 133), (2432, 38, 38, 64, 1, 130, 133), (3840, 32, 8, 64, 3, 99, 100),
-                          (5120, 28, 4, 128, 2, 250, 256), (1024, 28, 4, 128, 8, 250, 256), (2432, 38, 38, 64, 8, 250, 256)]
+                          (5120, 28, 4, 128, 2, 250, 256), (1024, 28, 4, 128, 8, 250, 256), (2432, 38, 38, 64, 8, 250, 256),
+                          (1024, 6, 3, 64, 7, 19, 23), (256, 4, 1, 64, 1, 12, 12)]
 
 
+@pytest.mark.gpu
 @pytest.mark.parametrize("H,n_q,n_kv,d,batch,nodes,R", WITHOUT_MFMA_ATTENTION)
 def test_keys_and_values_without_mfma_attention(H, n_q, n_kv, d, batch, nodes, R):
     rows = (batch - 1) * R + nodes
     assert _compare(H, n_q, n_kv, d, batch, nodes, R) == (False, 1, 1 if rows <= 32 else 0)
 
 
+@pytest.mark.gpu
 @pytest.mark.parametrize("H,n_q,n_kv,d", [(1024, 6, 3, 64), (896, 7, 1, 128)])
 def test_prompts_without_mfma_attention(H, n_q, n_kv, d):
     """one range of K, in tiles of many rows, the last of them with a part of its rows; the last row's result rests on its q as well"""
@@ -121,3 +141,31 @@ def test_prompts_without_mfma_attention(H, n_q, n_kv, d):
         g.close()
     for got, want, tol in zip(*out, (_tolerance(H), _tolerance(H), 2e-3 * max(1.0, H / 1024))):
         assert np.abs(got - want).max() <= tol, (np.abs(got - want).max(), tol)
+
+
+def test_what_one_launch_takes():
+    """The rule over widths, heads and row counts: workgroups that exchange partial tiles in front of the MFMA attention share an XCD and one row
+    tile, and no launch has more tiles than there are meetings."""
+    import torch   # noqa: F401 (in front of the library)
+    taken = 0
+    for H in range(256, 8193, 256):
+        for n_q, n_kv, d in {(H // 128, H // 128, 128), (H // 128, max(1, H // 512), 128), (H // 64, max(1, H // 256), 64), (28, 4, 128), (40, 8, 128), (7, 1, 128)}:
+            if n_q % n_kv:
+                continue
+            N, mfma = (n_q + 2 * n_kv) * d, d == 128 and n_q // n_kv in (1, 2, 4, 8)
+            for M in (1, 16, 17, 32, 33, 64, 65, 96, 97, 128, 129, 160, 256, 512, 1000, 2048):
+                ranges = _ranges(M, N, H)
+                one, (rb, wb, row_tiles, kp, stages) = _joins(M, N, H, ranges, mfma)
+                if not one:
+                    continue
+                taken += 1
+                assert kp == ranges
+                tiles = -(-N // 16 // wb)
+                assert kp == 1 or tiles * row_tiles <= 256
+                if mfma:
+                    assert 2 <= kp <= 4 and row_tiles == 1 and rb <= 4 and -(-tiles // 8) * kp <= 32, (H, n_q, n_kv, M, rb, wb, row_tiles, kp)
+                    assert M <= 32 or kp >= 3
+                    assert M <= 64 or (M <= 128 and stages >= 16)
+                else:
+                    assert M > 32
+    assert taken > 500, taken
