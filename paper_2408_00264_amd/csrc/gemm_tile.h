@@ -634,9 +634,12 @@ void launch_tile_big(const TileArgs<EPI>& g, int wb, int wgs, hipStream_t st) { 
 }
 template <int EPI>
 void launch_tile_few(const TileArgs<EPI>& g, int rb, int wb, int wgs, hipStream_t st) {    // rb 0: wb 8, 12; rb 1: wb 6, 7, 8, 12; rb 2: wb 6, 7, 8, 12, 16
-  if (rb == 0 && wb == 8) launch_tile_one<0, 8, EPI, true>(g, wgs, st);
-  else if (rb == 0) launch_tile_one<0, 12, EPI, true>(g, wgs, st);
-  else if (rb == 1 && wb == 6) launch_tile_one<1, 6, EPI, true>(g, wgs, st);
+  if (rb == 0) {
+    if constexpr (EPI != 3) {   // (few rows over one range of K: the QKV projection leaves rotation and stores to a second launch)
+      if (wb == 8) launch_tile_one<0, 8, EPI, true>(g, wgs, st);
+      else launch_tile_one<0, 12, EPI, true>(g, wgs, st);
+    } else g_not_launched = "no such form of the QKV projection";
+  } else if (rb == 1 && wb == 6) launch_tile_one<1, 6, EPI, true>(g, wgs, st);
   else if (rb == 1 && wb == 7) launch_tile_one<1, 7, EPI, true>(g, wgs, st);
   else if (rb == 1 && wb == 8) launch_tile_one<1, 8, EPI, true>(g, wgs, st);
   else if (rb == 1) launch_tile_one<1, 12, EPI, true>(g, wgs, st);

@@ -130,7 +130,7 @@ void launch_gemm_qkv(const TileGemmQkv& g_in, const TileForm& t, hipStream_t st)
   const int rt = t.row_tiles, tiles = tiles_of(t, g.N), per_xcd = wgs_per_xcd(t, g.N);
   g.k_parts = t.k_parts;
   g.n_units = tiles * g.k_parts;
-  g.row_blocks = std::min(t.rb == 0 ? 1 : 2 * t.rb, (g.M + 15) / 16);
+  g.row_blocks = std::min(2 * t.rb, (g.M + 15) / 16);
   g.spread = per_xcd > TL_CUS / 8;   // (a member of a second round would keep those of the first waiting)
   int wgs = rt > 1 ? (g.n_units + 7) / 8 * 8 * rt : g.n_units;
   if (g.k_parts > 1 && !g.spread) wgs = 8 * per_xcd;
