@@ -96,6 +96,7 @@ struct clover_ctx : RowBufs {
   int *d_seq_len, *d_aug_len, *d_err;
   int *d_depth, *d_parent, *d_rank, *d_first_child, *d_n_child, *d_lvl_nodes;
   unsigned* d_meet;        // meetings of the workgroups that share a GEMM tile
+  int meet_polls;          // looks of one of them before it leaves its share to the last
   unsigned long long* d_anc;
   int* d_pages;            // page table [max_batch][max_seq / KV_PAGE] (used once clover_set_page_table was called)
   int* d_iv;               // interval labels of the static tree [R][2]
@@ -124,6 +125,9 @@ struct clover_ctx : RowBufs {
   std::vector<ProfEvent> prof_events;
   std::vector<ProfEvent> prof_pool;
 };
+
+// (test hook: with 0 nearly every member leaves its share to the last arrival)
+void clv::set_meet_polls(clover_ctx* x, int polls) { x->meet_polls = polls; }
 
 namespace {
 
@@ -539,7 +543,7 @@ void run_layer(clover_ctx* x, const clover_layer_weights& lw, float* xres, RowMa
       g.X = A;
       g.W = (const bf16_t*)lw.wq;   // q, k and v rows
       g.M = M; g.N = x->QKVN; g.K = H;
-      g.part = x->partial; g.meet = x->d_meet; g.polls = tune_int("CLOVER_MEET_POLLS", MEET_POLLS);
+      g.part = x->partial; g.meet = x->d_meet; g.polls = x->meet_polls;
       g.qkv = QkvOut{c.n_q_heads, d, x->attn_fast ? q_hi : nullptr, q_lo, 1.0f / sqrtf((float)d), x->q_rot, x->NQD,
                      (bf16_t*)kc_layer, (bf16_t*)vc_layer, kvl, x->cos_t, x->sin_t, base_len, rm, x->d_err};
       launch_gemm_qkv(g, form, x->st);
@@ -951,6 +955,7 @@ int clover_init(const clover_config* cfg, const clover_weights* w, const clover_
   x->m_upper = cfg->max_nodes;
   x->only_prefills = true;
   x->interval = (cfg->flags & CLOVER_FLAG_INTERVAL_MASK) != 0;
+  x->meet_polls = MEET_POLLS;
   launch_fill_i32(x->d_seq_len, 0, cfg->max_batch, x->st);
   launch_fill_i32(x->d_aug_len, 0, cfg->max_batch, x->st);
   launch_fill_i32(x->d_err, 0, 1, x->st);

@@ -378,6 +378,7 @@ struct TileGemmQkv : TileGemm {
 };
 constexpr int TILE_MEETINGS = 256, MEET_STRIDE = 16;
 constexpr int MEET_POLLS = 256;       // looks of a member at the word before it leaves its share to the last one (100 us or so)
+void set_meet_polls(clover_ctx* x, int polls);   // of this context's launches
 constexpr int TILE_MAX_K_PARTS = 8;
 // K ranges of a narrow output; the same for all M that round up to the same multiple of 32
 int tile_gemm_pick_k_parts(int M, int N, int K);

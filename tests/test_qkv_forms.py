@@ -33,9 +33,8 @@ def _joins(M, N, K, ranges, mfma_attention):
     return f(M, N, K, ranges, mfma_attention, form), list(form)
 
 
-def _compare(H, n_q, n_kv, d, batch, nodes, R):
-    """One layer by the MFMA path and by the fp32-ALU kernels.  Returns whether the former's attention is the MFMA one too, and the launches
-    of its QKV projection and of the rotation behind it."""
+def _model(H, n_q, n_kv, d, batch, nodes, R):
+    """(shape, weights, parents, ranks, cached rows, slots, page table, tokens) of a model of one layer"""
     import torch
     assert torch.cuda.is_available()
     M = (batch - 1) * R + nodes
@@ -52,6 +51,14 @@ def _compare(H, n_q, n_kv, d, batch, nodes, R):
     max_seq = (max(lens) + 2 * R + 63) // 32 * 32
     pages = rng.permutation(batch * max_seq // 32).astype(np.int32)
     tok = torch.randint(0, shape.vocab, (batch, R), generator=torch.Generator().manual_seed(1)).int()
+    return shape, dev_w, parent, rank, lens, max_seq, pages, tok
+
+
+def _compare(H, n_q, n_kv, d, batch, nodes, R):
+    """One layer by the MFMA path and by the fp32-ALU kernels.  Returns whether the former's attention is the MFMA one too, and the launches
+    of its QKV projection and of the rotation behind it."""
+    shape, dev_w, parent, rank, lens, max_seq, pages, tok = _model(H, n_q, n_kv, d, batch, nodes, R)
+    import torch
     out = []
     for flags in (0, clover.FLAG_GENERIC):
         g = clover.Clover(shape, dev_w, parent, rank, batch, max_seq, R, flags=flags | (clover.FLAG_INTERVAL_MASK if R > 128 else 0))
@@ -116,6 +123,49 @@ WITHOUT_MFMA_ATTENTION = [(1024, 6, 3, 64, 1, 1, 1), (896, 7, 1, 128, 1, 17, 17)
 def test_keys_and_values_without_mfma_attention(H, n_q, n_kv, d, batch, nodes, R):
     rows = (batch - 1) * R + nodes
     assert _compare(H, n_q, n_kv, d, batch, nodes, R) == (False, 1, 1 if rows <= 32 else 0)
+
+
+# Tiles of 32, 64, 128, 160 and 256 rows (those of 160 and more request what they need only behind the meeting); ranges on one XCD, and
+# six of them on several; heads with and without MFMA attention.
+LEAVING = [(1024, 8, 2, 128, 1, 5, 5), (4096, 32, 8, 128, 2, 30, 33), (3072, 24, 24, 128, 4, 27, 28), (2304, 36, 9, 64, 1, 97, 97),
+           (2432, 38, 38, 64, 1, 130, 133), (5120, 28, 4, 128, 2, 250, 256)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("H,n_q,n_kv,d,batch,nodes,R", LEAVING)
+def test_members_that_leave(H, n_q, n_kv, d, batch, nodes, R):
+    """Workgroups that look at the meeting's word once or not at all leave their share to the last one.  A share is summed in the order
+    of the ranges whoever does it, so that no bit of the results changes, pass after pass in the same words."""
+    shape, dev_w, parent, rank, lens, max_seq, pages, tok = _model(H, n_q, n_kv, d, batch, nodes, R)
+    import torch
+    set_polls = clover.load_library()._ZN3clv14set_meet_pollsEP10clover_ctxi
+    set_polls.restype, set_polls.argtypes = None, [C.c_void_p, C.c_int]
+    out = []
+    for polls in (None, 0, 1):
+        g = clover.Clover(shape, dev_w, parent, rank, batch, max_seq, R, flags=clover.FLAG_INTERVAL_MASK if R > 128 else 0)
+        g.set_page_table(pages)
+        if polls is not None:
+            set_polls(g.ctx, polls)
+        g.set_seq_len(lens, [max(v - 1, 0) for v in lens])
+        for b in range(batch):
+            if lens[b]:
+                g.write_kv(0, 0, b, 0, np.zeros((lens[b], n_kv, d), np.float32), np.zeros((lens[b], n_kv, d), np.float32))
+        got = []
+        for i in range(3):                                     # (other tokens: nothing that is left of the pass before is right)
+            g.tree_tokens.copy_((tok + i) % shape.vocab)
+            g.profile_enable(True)
+            g.verify_tree(batch)
+            torch.cuda.synchronize()
+            ran = g.profile_collect()
+            assert (ran["gemm_qkv"][1], ran["rope_kv_write"][1]) == (1, 0)
+            got.append(g.hidden[:, :nodes].cpu().numpy())
+            got += [v for b in range(batch) for v in g.read_kv(0, 0, b, 0, max_seq)]
+        assert list(g.seq_len()) == lens
+        out.append(got)
+        g.close()
+    for other in out[1:]:
+        for a, b in zip(out[0], other):
+            assert np.array_equal(a, b)
 
 
 @pytest.mark.gpu
