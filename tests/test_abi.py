@@ -200,5 +200,8 @@ int main() {
                     "-o", str(exe)], check=True)
     assert subprocess.run([str(exe)]).returncode == 0
     # and every kernel that asks for more goes through it
-    for f in ("kernels_tile.hip", "kernels_attn.hip", "kernels_generic.hip", "kernels_dyn.hip", "kernels_draft.hip"):
-        assert "hipFuncSetAttribute" not in open(os.path.join(ROOT, "paper_2408_00264_amd", "csrc", f)).read(), f
+    csrc = os.path.join(ROOT, "paper_2408_00264_amd", "csrc")
+    sources = {f: open(os.path.join(csrc, f)).read() for f in os.listdir(csrc) if f.endswith((".hip", ".h"))}
+    assert {f for f, text in sources.items() if "hipFuncSetAttribute" in text} == {"clover_internal.h"}
+    assert sources["clover_internal.h"].count("hipFuncSetAttribute") == 1
+    assert {f for f, text in sources.items() if "allow_dynamic_lds" in text} >= {"gemm_tile.h", "kernels_attn.hip"}   # (the search finds them)

@@ -34,4 +34,14 @@ def test_calls_report_what_was_not_launched():
     body = re.search(r"^int finish\(.*?^}", api, re.S | re.M)[0]
     assert "g_not_launched" in body and "CLOVER_E_STATE" in body
     ops = api[api.index("size_t clover_op_gemm_scratch_bytes"):]          # (the operators have no context and end without finish)
-    assert "launch_reduce_add_norm" not in ops and "launch_rope_kv_write" not in ops
+    refusing = set()   # launchers that may launch nothing
+    for f in sorted(os.listdir(CSRC)):
+        if f.endswith((".hip", ".h")):
+            for m in re.finditer(r"^(?:template <[^\n]*>\n)?(?:static )?(?:inline )?void (launch_\w+)\(.*?^}", open(os.path.join(CSRC, f)).read(), re.S | re.M):
+                if re.search(r"with_count<|g_not_launched =", m[0]):
+                    refusing.add(m[1])
+    assert refusing >= {"launch_reduce_add_norm", "launch_rope_kv_planes", "launch_rope_kv_parts", "launch_tile_few"}, refusing   # (the search finds them)
+    tile = open(os.path.join(CSRC, "gemm_tile.h")).read()                 # (of the GEMM's forms only the QKV projection's refuses)
+    assert tile.count("g_not_launched") == 1 and re.search(r"if constexpr \(EPI != 3\) {[^}]*} else g_not_launched =", tile)
+    for name in refusing - {"launch_tile_few"} | {"launch_gemm_qkv"}:
+        assert name + "(" not in ops, name
