@@ -229,8 +229,8 @@ void launch_rope_kv_planes(const float* qkv, int ldqkv, int splits, size_t split
                            bf16_t* v_cache, KVLayout kv, const int* base_len, int n_q, RowMap rm, int* err_flag, bf16_t* q_hi, bf16_t* q_lo,
                            int ldq, float q_scale, hipStream_t st);
 void launch_attn_generic(const float* q, int ldq, const void* k_cache, const void* v_cache, int kvdtype, KVLayout kv,
-                         const int* base_len, const unsigned long long* anc /*[n][2]*/, int n_q, float* out, int ldo,
-                         FragPlanes planes /*instead of fp32 when planes.p is non-null*/, RowMap rm,
+                         const int* base_len, const unsigned long long* anc /*[n][2]*/, int n_q, float* out /*of fp32 caches*/, int ldo,
+                         FragPlanes planes /*the results over caches of bf16 planes*/, RowMap rm,
                          hipStream_t st, int anc_stride = 0 /*nodes per sequence in a per-sequence mask table, 0: shared*/,
                          const int* iv = nullptr /*[n][2] interval labels: decide visibility instead of anc when given*/);
 // mode 0: Y = X W^T (+bias); mode 1: Y += X W^T (+bias)

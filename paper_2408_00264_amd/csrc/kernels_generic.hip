@@ -288,16 +288,16 @@ void launch_rope_kv_parts(const float* qkv, int ldqkv, int splits, size_t split_
 }
 
 // ------------------------------------------------------------------------------------------
-// tree-masked attention, one wavefront per (row, q head).  Keys: cached slots [0,L) all visible,
+// tree-masked attention.  Keys: cached slots [0,L) all visible,
 // then the rm.n new rows at slots L+w, visible iff bit w of the row's ancestor mask is set.
 // anc == null: the rows form a chain (row i sees new rows 0..i), any number of rows.
 // iv != null: new row w is visible to row i iff enter[w] <= enter[i] <= exit[w] (interval labels, two ints per node).
 // ------------------------------------------------------------------------------------------
-// What bounds it: memory round trips.  A lane fetches its key's row and its channel's 64 values in 16-byte pieces that are all
-// requested before the first is used.  (fp32 caches: attn_fp32_kernel below.)
-// Tiles that are hidden from a row altogether are not loaded, and a chain's row ends with its own tile (bf16 model with heads of
-// 64, 1000 tokens in one pass: 1300 -> 730 us a layer; fp32 with heads of 128: 880 -> 480).
-__device__ __forceinline__ float4 ldkv4(const float* p, size_t i, size_t) { return *(const float4*)(p + i); }
+// Over caches of two bf16 planes, for heads that the MFMA attention does not take (fp32 caches: attn_fp32_kernel below): one wavefront per
+// (row, query head), results as planes.  What bounds it: memory round trips.  A lane fetches its key's row and its channel's 64 values
+// in pieces of four that are all requested before the first is used.
+// Tiles that are hidden from a row altogether are not loaded, and a chain's row ends with its own tile (heads of 64, 1000 tokens in one
+// pass: 1300 -> 730 us a layer).
 __device__ __forceinline__ float4 ldkv4(const bf16_t* p, size_t i, size_t plane) {
   const uint2 h = *(const uint2*)(p + i), l = *(const uint2*)(p + i + plane);
   return make_float4(__uint_as_float(h.x << 16) + __uint_as_float(l.x << 16),
@@ -305,12 +305,11 @@ __device__ __forceinline__ float4 ldkv4(const bf16_t* p, size_t i, size_t plane)
                      __uint_as_float(h.y << 16) + __uint_as_float(l.y << 16),
                      __uint_as_float(h.y & 0xFFFF0000u) + __uint_as_float(l.y & 0xFFFF0000u));
 }
-template <typename KT, int D>
-__global__ __launch_bounds__(64) void attn_generic_kernel(const float* __restrict__ q, int ldq, const KT* __restrict__ kc,
-                                                          const KT* __restrict__ vc, KVLayout kv, const int* __restrict__ base_len,
+template <int D>
+__global__ __launch_bounds__(64) void attn_generic_kernel(const float* __restrict__ q, int ldq, const bf16_t* __restrict__ kc,
+                                                          const bf16_t* __restrict__ vc, KVLayout kv, const int* __restrict__ base_len,
                                                           const unsigned long long* __restrict__ anc, int n_q,
-                                                          float* __restrict__ out, int ldo, FragPlanes planes, RowMap rm,
-                                                          int anc_stride, const int* __restrict__ iv) {
+                                                          FragPlanes planes, RowMap rm, int anc_stride, const int* __restrict__ iv) {
   __shared__ __attribute__((aligned(16))) float qs[D];
   __shared__ __attribute__((aligned(16))) float ps[64];
   const int h = blockIdx.x, i = blockIdx.y, b = blockIdx.z, lane = threadIdx.x;
@@ -349,14 +348,14 @@ __global__ __launch_bounds__(64) void attn_generic_kernel(const float* __restric
     float4 kx[D / 4];
 #pragma unroll
     for (int c = 0; c < D / 4; ++c)   // (kv_k_col(4 c), at compile time)
-      kx[c] = ldkv4(kc, kr + (std::is_same<KT, float>::value ? c * 4 : (c >> 3) * 512 + ((c >> 1) & 3) * 128 + (c & 1) * 4), kv.plane);
+      kx[c] = ldkv4(kc, kr + (c >> 3) * 512 + ((c >> 1) & 3) * 128 + (c & 1) * 4, kv.plane);
     float4 vx[16];
     auto load_v = [&](int u) __attribute__((always_inline)) {   // channel lane + 64 u of the tile's two pages
 #pragma unroll
       for (int pg = 0; pg < 2; ++pg) {
         const size_t at = kv_v_at(kv, b, g, lane + 64 * u, min(t * 64 + pg * KV_PAGE, kv.max_seq - KV_PAGE));
 #pragma unroll
-        for (int c = 0; c < 8; ++c) vx[pg * 8 + c] = ldkv4(vc, at + (std::is_same<KT, float>::value ? c * 4 : (c >> 1) * 128 + (c & 1) * 4), kv.plane);
+        for (int c = 0; c < 8; ++c) vx[pg * 8 + c] = ldkv4(vc, at + (c >> 1) * 128 + (c & 1) * 4, kv.plane);
       }
     };
     load_v(0);
@@ -396,14 +395,10 @@ __global__ __launch_bounds__(64) void attn_generic_kernel(const float* __restric
   for (int u = 0; u < D / 64; ++u) {
     const int c = h * D + 64 * u + lane;
     const float v = o[u] * inv;
-    if (planes.p) {
-      bf16_t* dst = planes.p + frag_at(planes, (int)row, c);
-      const bf16_t hb = f32_to_bf16(v);
-      dst[0] = hb;
-      dst[512] = f32_to_bf16(v - bf16_to_f32(hb));
-    } else {
-      out[row * ldo + c] = v;
-    }
+    bf16_t* dst = planes.p + frag_at(planes, (int)row, c);
+    const bf16_t hb = f32_to_bf16(v);
+    dst[0] = hb;
+    dst[512] = f32_to_bf16(v - bf16_to_f32(hb));
   }
 }
 
@@ -550,8 +545,8 @@ void launch_attn_generic(const float* q, int ldq, const void* k_cache, const voi
       attn_fp32_kernel<D><<<grid, 64 * waves, 0, st>>>(q, ldq, (const float*)k_cache, (const float*)v_cache, kv, base_len, anc, n_q, out, ldo,
                                                        rm, anc_stride, iv);
     } else {
-      attn_generic_kernel<bf16_t, D><<<grid, 64, 0, st>>>(q, ldq, (const bf16_t*)k_cache, (const bf16_t*)v_cache, kv, base_len, anc, n_q, out,
-                                                          ldo, planes, rm, anc_stride, iv);
+      attn_generic_kernel<D><<<grid, 64, 0, st>>>(q, ldq, (const bf16_t*)k_cache, (const bf16_t*)v_cache, kv, base_len, anc, n_q, planes, rm,
+                                                  anc_stride, iv);
     }
   };
   if (kv.d == 64) go(std::integral_constant<int, 64>{});
