@@ -142,9 +142,9 @@ __global__ void rope_kv_write_kernel(const float* __restrict__ qkv, int ldqkv, i
 }
 
 // The same operation in front of the MFMA attention, for launches whose QKV GEMM does not do it itself (heads of q and k in rotary order,
-// q as pre-scaled bf16 planes, bf16-plane caches), vectorised: a thread of the first blocks rotates four adjacent channels of one head (float4 loads of every partial, issued
-// before anything else is waited for; 8-byte plane stores); the last blocks transpose 64 nodes x 32 channels of V
-// through LDS so that the partials are read along the channels and V^T is written along the nodes.
+// q as pre-scaled bf16 planes, bf16-plane caches), vectorised: a thread of the first blocks rotates four adjacent channels of one head
+// (float4 loads of every partial, issued before anything else is waited for; 8-byte plane stores); the last blocks transpose 64 nodes x
+// 32 channels of V through LDS so that the partials are read along the channels and V^T is written along the nodes.
 __device__ __forceinline__ void planes4(bf16_t* hi, bf16_t* lo, size_t off, const float (&o)[4]) {
   unsigned h[4], l[4];
 #pragma unroll
